@@ -139,6 +139,23 @@ def test_reorder_threads_on_the_unstructured_workload_reduced(monkeypatch):
             assert_same_blocking(w["A"], w["col_block"], tau)
 
 
+@pytest.mark.parametrize("threads", ["1", "5"])
+@pytest.mark.parametrize("n_blocks", [64, 65, 129, 192, 257])
+def test_reorder_by_bit_set_scan_and_by_lists_at_the_word_counts_of_the_scan(monkeypatch, threads, n_blocks):
+    # bit sets of 1, 2, 4, 4 (padded) and 5 words; a class count that is no multiple of 8; skewed block
+    # frequencies (rare blocks make short lists, common ones a bit-set scan), patterns that repeat, merges
+    monkeypatch.setenv("VBR_SA1_THREADS", threads)
+    rng = np.random.default_rng(n_blocks)
+    freq = np.minimum(0.9, 1.5 / (1 + np.arange(n_blocks)))
+    base = rng.random((90, n_blocks)) < freq
+    rows = [np.nonzero(base[rng.integers(90)] ^ (rng.random(n_blocks) < 0.01))[0] * 2 for _ in range(701)]
+    csr = csr_from_rows([r.tolist() for r in rows], 2 * n_blocks)
+    for tau in (0.05, 0.3, 0.5, 0.75, 0.99, 1.0):
+        p0, g0 = oracle.sa1(csr, 2, tau)
+        perm, rg = binding.sa1_reorder(csr, 2, tau)
+        assert np.array_equal(perm, p0) and np.array_equal(rg, g0), tau
+
+
 @pytest.mark.parametrize("name,scale,noise", [("c1", 1.0, True), ("c1", 1.0, False), ("c2", 0.25, True),
                                                ("c3", 0.125, True), ("c4", 0.125, True), ("c5", 0.0625, True)])
 def test_workloads_small_scale_bit_exact(name, scale, noise):
