@@ -447,6 +447,25 @@ def test_csr_comparator_matches_oracle(dtype):
         check_c(out[:, :n].astype(np.float64), c_ref, s, "csr %s m=%d n=%d" % (dtype, m, n))
 
 
+@pytest.mark.parametrize("n,ldb_pad,dtype", [(8, 0, "f16"), (128, 0, "bf16"), (136, 8, "f16"), (264, 56, "bf16"), (1160, 0, "f16")])
+def test_csr_comparator_at_the_row_lengths_where_it_splits(n, ldb_pad, dtype):
+    # a row per 16 (32) lanes, per wave, per workgroup: lengths around a batch of 16 entries, around the
+    # limits 256 and 1024, empty rows in between; one column tile and several, a ragged last one, rows of B
+    # inside and across cache lines
+    import torch
+    rng = np.random.default_rng(n)
+    k = 2600
+    lens = [0, 1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 0, 255, 256, 257, 300, 512, 513, 1023, 1024, 1025, 1300, 2049, 2600, 0] + [5] * 30
+    csr = csr_from_rows([sorted(rng.choice(k, size=x, replace=False).tolist()) for x in lens], k, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, k, n + ldb_pad, dtype)
+    b = torch_io.bits_to_device(bits, dtype)[:, :n]
+    c = torch.full((len(lens), n), float("nan"), dtype=torch.float32, device="cuda:0")
+    binding.CsrDev(csr).upload("cuda:0").spmm(b, c)
+    torch.cuda.synchronize()
+    c_ref, s = oracle.spmm(csr, np.ascontiguousarray(bits[:, :n]))
+    check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
+
+
 def test_csr_comparator_and_blocked_path_agree_on_the_graph_workload():
     import torch
     w = synth.workload("rmat", scale=0.125)
