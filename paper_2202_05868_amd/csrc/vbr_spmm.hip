@@ -38,6 +38,7 @@ typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4v *lds_short4_ptr;
 typedef __attribute__((address_space(3))) short8v *lds_short8_ptr;
+typedef __attribute__((address_space(3))) float4v *lds_float4_ptr;
 typedef __attribute__((address_space(3))) unsigned char *lds_u8_ptr;
 typedef __attribute__((address_space(4))) const int32_t *const_i32_ptr;
 
@@ -374,23 +375,33 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
         wait_vmcnt<0>();                           // no load may still be writing LDS when the workgroup ends
     }
 
-    // C rows go back to their original positions through perm; beta = 0
+    // C rows go back to their original positions through perm; beta = 0.  A lane holds 4 columns of ONE row, so a
+    // store straight from the accumulators touches 16 rows, 64 bytes each: half lines, which leave L2 as partial
+    // writes (graph of 16384 nodes, N = 4096: 330 MB written for 268).  The wave turns every slab round in LDS (its own
+    // 16 rows x 272 bytes: no bank conflicts) and stores 4 rows x 256 bytes at a time, around the caches' write
+    // allocation.  That graph: 260 -> 222 us; 8192 x 8192 with 700 000 stored entries, N = 2048: 23.1 -> 18.7 us;
+    // 16384 x 16384 with row groups of 16 to 128 rows, N = 512: 26.4 -> 23.5 us.
+    int32_t orig[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
         const int rr = s * kSlabRows + s16;
-        const int64_t orig = rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
-        if (orig >= 0) {                 // a position of the low-row list may be padding (-1)
-            float *crow = p.C + orig * p.ldc;
+        orig[s] = rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
+    }
+    if (n_ks > 0) __builtin_amdgcn_s_barrier();     // the rings are read no more
+    constexpr int kOutRow = kWaveN * 4 + 16;
+    static_assert(4 * kSlabRows * kOutRow <= tile_lds_bytes<S, NS, DA>(), "the turned slabs of the four waves fit the rings");
+    const lds_u8_ptr out = sm + wave * kSlabRows * kOutRow;
 #pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                const int n = n0 + wave * kWaveN + 16 * f + 4 * q;
-                if (n >= p.N) continue;
-                // tall tiles and gathered tiles store around the caches' write allocation (measured: the
-                // dense 4096 x 16384 x 4096 product 0.44 -> 0.37 ms, the graph workload 213 -> 204 us; no
-                // gain, or a small loss, for the lower classes on whole column blocks)
-                if constexpr (S >= 8 || GATHER) __builtin_nontemporal_store(acc[s][f], reinterpret_cast<float4v *>(crow + n));
-                else *reinterpret_cast<float4v *>(crow + n) = acc[s][f];
-            }
+    for (int s = 0; s < S; ++s) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) *(lds_float4_ptr)(out + s16 * kOutRow + f * 64 + q * 16) = acc[s][f];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4v x = *(lds_float4_ptr)(out + (4 * i + q) * kOutRow + s16 * 16);
+            const int32_t row = __shfl(orig[s], 4 * i + q);
+            const int n = n0 + wave * kWaveN + 4 * s16;
+            // a position of the low-row list may be padding (-1)
+            if (row >= 0 && n < p.N) __builtin_nontemporal_store(x, reinterpret_cast<float4v *>(p.C + row * p.ldc + n));
         }
     }
 }
