@@ -156,20 +156,22 @@ int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C_dev, int64
  * The kernel launches one vbr_spmm call with dense width N issues, in issue order (for reporting;
  * vbr_spmm itself launches from the same plan).  Rows of groups lower than 16 rows are multiplied
  * 128 at a time, by the panel kernel (their slabs of 16 rows share the B rows of the union of their
- * column blocks) or by the tile kernel on column-gathered slabs (every slab loads exactly the B rows
- * of the columns its rows touch), whichever packing needs fewer loads; the other groups by the tile
+ * column blocks) or by the tile kernel on column-gathered tiles of 1 to 4 slabs (every tile loads exactly the
+ * B rows of the columns its rows touch), whichever packing needs fewer loads; the other groups by the tile
  * kernel, on whole column blocks or, where the blocks are mostly fill-in, on the columns the rows
- * of a tile touch (VBR_LAUNCH_GATHER_*), either in one launch per class of tile
- * height that occurs (1, 2, 3-4, 5-8 slabs of 16 rows) or, for small matrices, in one launch that
- * mixes the classes: between 0 and VBR_MAX_LAUNCHES launches.  kinds / tiles / workgroups (each
- * room for VBR_MAX_LAUNCHES entries, any may be NULL) receive the kernel, the number of row tiles
- * or panels, and the grid size of each launch.
+ * of a tile touch (VBR_LAUNCH_GATHER_*).  A gathered tile with far more columns than the others is deep: four
+ * workgroups per 256 columns, whose waves split its columns.  For small matrices one launch takes all tiles;
+ * otherwise the deep tiles, the other gathered tiles and every class of block tiles (1, 2, 3-4, 5-8
+ * slabs of 16 rows) have a launch each: between 0 and VBR_MAX_LAUNCHES launches.  kinds / tiles / workgroups (each
+ * room for VBR_MAX_LAUNCHES entries, any may be NULL) receive the kernel, the number of row tiles (a deep
+ * tile counts four times) or panels, and the grid size of each launch.
  */
 enum { VBR_MAX_LAUNCHES = 9 };
 enum {
     VBR_LAUNCH_PANEL = 0, VBR_LAUNCH_TILE_1 = 1, VBR_LAUNCH_TILE_2 = 2, VBR_LAUNCH_TILE_4 = 3,
     VBR_LAUNCH_TILE_8 = 4, VBR_LAUNCH_TILE_MIXED = 5,
-    VBR_LAUNCH_GATHER_1 = 6, VBR_LAUNCH_GATHER_2 = 7, VBR_LAUNCH_GATHER_4 = 8, VBR_LAUNCH_GATHER_8 = 9
+    VBR_LAUNCH_GATHER_1 = 6, VBR_LAUNCH_GATHER_2 = 7, VBR_LAUNCH_GATHER_4 = 8, VBR_LAUNCH_GATHER_MIXED = 9,
+    VBR_LAUNCH_GATHER_DEEP = 10
 };
 int vbr_get_launches(const vbr_t *v, int64_t N, int32_t *n_launches, int32_t *kinds, int64_t *tiles,
                      int64_t *workgroups);

@@ -1,17 +1,21 @@
 // VBR construction on the host: index arrays of the format (section 2 and the last paragraph of
 // section 3.1 of the paper), values packed as MFMA fragments, and the workgroup schedule.
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
-#include <cstring>
+#include <memory>
 #include <new>
+#include <utility>
 #include <vector>
 
+#include "host_threads.h"
 #include "vbr_host.h"
 
 namespace vbrk {
 namespace {
 
 inline int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
+inline int64_t steps_of(int64_t rows_of_b) { return (rows_of_b + kStepK - 1) / kStepK; }
 
 inline int slab_class(int n_slabs)   // kernels exist for 1, 2, 4 and 8 slabs
 {
@@ -30,117 +34,277 @@ inline bool use_panels(int lg_gran, int64_t short_rows) { return lg_gran >= 3 &&
 // and up to 8 fragments (8 loads) per 128 columns; a one-slab tile 32 B rows x 256 columns (16 loads)
 // and one fragment.  The direct-to-LDS load instruction is the unit of cost of both kernels.
 constexpr int64_t kPanelStepCost = 32, kTileStepCost = 17;
-constexpr int64_t kTileMaxGatherSteps = 64;  // K-steps a column-gathered tile of several slabs may walk before it is cut in two
 constexpr int64_t kSlabMaxCols = 1024;       // columns a slab of low rows gathers before the next group starts a new slab
 
-int build_impl(const vbr_csr_t *csr, const int32_t *perm, const int32_t *row_groups, int32_t G,
-               int32_t col_block, vbr *v)
+// What a tile takes, in nanoseconds per workgroup of 256 columns: per K-step by its height (rates measured on full
+// launches), and as much as four K-steps to start and to store.  Block tiles: 1, 2, 4, 8 slabs.  Gathered tiles: 1 to 4
+// slabs; in the deep form (the four waves split the K-steps, 64 columns each) 1 or 2 slabs.
+constexpr int64_t kBlockStepNs[4] = {190, 215, 300, 370};
+constexpr int64_t kGatherStepNs[kMaxGatherSlabs] = {240, 255, 280, 300};
+constexpr int64_t kDeepStepNs[kMaxDeepSlabs] = {290, 350};
+constexpr int64_t kTileStartSteps = 4;
+constexpr int64_t kDeepSteps = 32;           // no tile of fewer K-steps is deep
+constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: height costs workgroups, and there are few
+constexpr int64_t kMixedMaxWorkgroups = 4096;
+constexpr int64_t kSegmentSlabs = 64;        // the cutting of the slab list into tiles is optimised over stretches of this length
+
+inline int64_t gather_cost(int64_t cols, int n_slabs, int64_t deep_steps)
 {
-    const int64_t M = csr->n_rows;
-    const int64_t KB = csr->n_cols / col_block;
+    const int64_t ks = steps_of(cols);
+    if (ks < deep_steps) return (ks + kTileStartSteps) * kGatherStepNs[n_slabs - 1];
+    if (n_slabs <= kMaxDeepSlabs) return (ks + kTileStartSteps) * kDeepStepNs[n_slabs - 1];
+    return INT64_MAX / 4;
+}
+
+// What a thread needs to count and look up the columns and column blocks of a few rows.
+struct Scratch {
+    std::vector<int32_t> stamp, pos;   // per column
+    std::vector<int32_t> block_pos;    // per column block
+    int32_t now = 0;
+    void fit(int64_t n_cols, int64_t n_blocks)
+    {
+        if (!stamp.empty()) return;
+        stamp.assign((size_t)std::max<int64_t>(n_cols, 1), 0);
+        pos.resize(stamp.size());
+        block_pos.assign((size_t)std::max<int64_t>(n_blocks, 1), -1);
+    }
+    // columns of the row that none of the rows since the last begin() had
+    void begin()
+    {
+        if (now == INT32_MAX) { std::fill(stamp.begin(), stamp.end(), 0); now = 0; }
+        ++now;
+    }
+    int64_t add(const vbr_csr_t *csr, int64_t row)
+    {
+        int64_t fresh = 0;
+        for (int64_t p = csr->row_ptr[row]; p < csr->row_ptr[row + 1]; ++p) {
+            int32_t &s = stamp[csr->col_idx[p]];
+            fresh += s != now;
+            s = now;
+        }
+        return fresh;
+    }
+};
+
+class Builder {
+public:
+    Builder(const vbr_csr_t *csr, const int32_t *perm, const int32_t *row_groups, int32_t G, int32_t col_block, vbr *v)
+        : csr(csr), perm(perm), rg(row_groups), G(G), cb(col_block), M(csr->n_rows), KB(csr->n_cols / col_block), v(v),
+          team(threads_for(csr->nnz + csr->n_rows, 1 << 15)), scratch((size_t)team.size())
+    {
+    }
+    int build();
+
+private:
+    enum Kind : uint8_t { kLow, kBlocks, kGathered };
+    struct Piece {                     // a stretch of groups, worked on by one thread
+        int32_t g0, g1;
+        std::vector<int32_t> blocks;   // column blocks of its groups, one group after the other
+        int64_t first_block;
+    };
+
+    int64_t nnz_of(int64_t q0, int64_t q1) const
+    {
+        int64_t n = 0;
+        for (int64_t q = q0; q < q1; ++q) n += csr->row_ptr[perm[q] + 1] - csr->row_ptr[perm[q]];
+        return n;
+    }
+    // f(scratch, i) for i in [0, n), dealt in runs of `run` to whoever is free
+    template <class F>
+    void each(int64_t n, int64_t run, F f)
+    {
+        std::atomic<int64_t> next(0);
+        auto work = [&](int member) {
+            Scratch &s = scratch[(size_t)member];
+            s.fit(csr->n_cols, KB);
+            for (;;) {
+                const int64_t b = next.fetch_add(run);
+                if (b >= n) break;
+                for (int64_t i = b; i < std::min(n, b + run); ++i) f(s, i);
+            }
+        };
+        if (n <= run) work(0);
+        else team.run(work);
+    }
+
+    void index_blocks();
+    Kind kind_of(Scratch &s, int64_t r0, int64_t r1, int64_t n_blocks);
+    int block_tiles();
+    void order_low_rows();
+    bool hubs_first();
+    void cluster_low_groups();
+    void choose_panels();
+    int emit_panel(int64_t chunk);
+    void append_gathered_groups();
+    void cut_into_tiles();
+    int emit_gather_tiles();
+    void fill_values();
+    void schedule();
+    void lay_out();
+
+    const vbr_csr_t *csr;
+    const int32_t *perm, *rg;
+    const int32_t G, cb;
+    const int64_t M, KB;
+    vbr *v;
+    Team team;
+    std::vector<Scratch> scratch;
+    std::vector<Kind> kind;
+    std::vector<Piece> pieces;
+    std::vector<int32_t> low_groups, gathered_groups;
+    std::vector<TileDesc> tiles;       // block tiles in creation order
+    int64_t a_units = 0;               // running size of the packed values, in units of 8 values
+    int gran = 1, per_step = kStepK;
+    bool panels_on = false;
+    int64_t low_slabs = 0;             // slabs of low rows; those of the gathered groups follow in the row list
+    std::vector<int32_t> prow_group;   // group of every position of the row list, -1 = padding
+    std::vector<int64_t> panel_dst, panel_src;   // values of the panels: position in vals <- position in csr->vals
+    std::vector<std::pair<int64_t, int64_t>> panel_range;   // [begin, end) of the panels' values, in units of 8
+};
+
+int Builder::build()
+{
     v->n_rows = M;
     v->n_cols = csr->n_cols;
     v->nnz = csr->nnz;
-    v->col_block = col_block;
+    v->col_block = cb;
     v->dtype = csr->dtype;
     v->n_groups = G;
     v->perm.assign(perm, perm + M);
-    v->row_groups.assign(row_groups, row_groups + G + 1);
+    v->row_groups.assign(rg, rg + G + 1);
 
     // B rows are gathered in granules of 2^lg_gran consecutive rows: the largest power of two
     // that divides the block width, at most one K-step.
     int lg = 0;
-    while (lg < 5 && col_block % (2 << lg) == 0) ++lg;
+    while (lg < 5 && cb % (2 << lg) == 0) ++lg;
     v->lg_gran = lg;
-    const int gran = 1 << lg;
-    const int per_step = kStepK >> lg;   // krow entries per K-step
+    gran = 1 << lg;
+    per_step = kStepK >> lg;             // krow entries per K-step
     int64_t short_rows = 0;
     for (int32_t g = 0; g < G; ++g)
-        if (row_groups[g + 1] - row_groups[g] < kSlabRows) short_rows += row_groups[g + 1] - row_groups[g];
-    const bool panels_on = use_panels(lg, short_rows);
+        if (rg[g + 1] - rg[g] < kSlabRows) short_rows += rg[g + 1] - rg[g];
+    panels_on = use_panels(lg, short_rows);
 
-    v->blk_ptr.assign((size_t)G + 1, 0);
-    v->blk_off.assign(1, 0);
-    v->ks_ptr.assign((size_t)G + 1, 0);
-    v->group_first_tile.assign((size_t)G + 1, 0);
-    v->group_prow.assign((size_t)std::max<int32_t>(G, 1), -1);
-    std::vector<int32_t> pos_of_block((size_t)std::max<int64_t>(KB, 1), -1);
-    std::vector<int32_t> blocks;
-    std::vector<int32_t> low_groups;            // groups lower than a slab, in group order
-    std::vector<int32_t> tall_gathered;         // taller groups whose tiles gather single columns
-    std::vector<int64_t> col_stamp((size_t)std::max<int64_t>(csr->n_cols, 1), -1);
-    int64_t col_stamp_id = 0;
-    std::vector<TileDesc> tiles;
-    int64_t a_units = 0;   // running size of the packed values, in units of 8 values
+    index_blocks();
+    int rc = block_tiles();
+    if (rc != VBR_OK) return rc;
+    v->row_pos.assign((size_t)M, -1);
+    order_low_rows();
+    choose_panels();
+    for (int64_t c = 0; c < (int64_t)v->chunk_panel.size(); ++c)
+        if (v->chunk_panel[(size_t)c] >= 0) {
+            rc = emit_panel(c);
+            if (rc != VBR_OK) return rc;
+        }
+    append_gathered_groups();
+    cut_into_tiles();
+    rc = emit_gather_tiles();
+    if (rc != VBR_OK) return rc;
+    fill_values();
+    schedule();
+    lay_out();
+    return VBR_OK;
+}
 
-    // pass 1: the VBR index arrays; K-step gather lists and tiles of the tall groups; the row list
-    // of the short groups
+// The VBR index arrays, and what becomes of every group.
+void Builder::index_blocks()
+{
+    // stretches of groups of about the same number of entries
+    const int64_t want = std::max<int64_t>(1, (csr->nnz + M) / (8 * team.size()));
+    pieces.clear();
+    int64_t load = 0;
     for (int32_t g = 0; g < G; ++g) {
-        const int64_t r0 = row_groups[g], r1 = row_groups[g + 1];
-        const int64_t h = r1 - r0;
-        blocks.clear();
-        for (int64_t q = r0; q < r1; ++q) {
-            const int64_t r = perm[q];
-            int64_t last = -1;
-            for (int64_t p = csr->row_ptr[r]; p < csr->row_ptr[r + 1]; ++p) {
-                const int64_t j = csr->col_idx[p] / col_block;
-                if (j != last) {
-                    if (pos_of_block[j] < 0) { pos_of_block[j] = 0; blocks.push_back((int32_t)j); }
-                    last = j;
+        if (pieces.empty() || load >= want) {
+            if (!pieces.empty()) pieces.back().g1 = g;
+            pieces.push_back(Piece{g, G, {}, 0});
+            load = 0;
+        }
+        load += nnz_of(rg[g], rg[g + 1]) + (rg[g + 1] - rg[g]);
+    }
+    kind.assign((size_t)G, kLow);
+    v->blk_ptr.assign((size_t)G + 1, 0);
+    each((int64_t)pieces.size(), 1, [&](Scratch &s, int64_t i) {
+        Piece &pc = pieces[(size_t)i];
+        for (int32_t g = pc.g0; g < pc.g1; ++g) {
+            const size_t at = pc.blocks.size();
+            for (int64_t q = rg[g]; q < rg[g + 1]; ++q) {
+                const int64_t r = perm[q];
+                int64_t last = -1, end = 0;             // the columns rise: one division per block, not per entry
+                for (int64_t p = csr->row_ptr[r]; p < csr->row_ptr[r + 1]; ++p) {
+                    const int64_t c = csr->col_idx[p];
+                    if (c < end) continue;
+                    last = c / cb;
+                    end = (last + 1) * cb;
+                    if (s.block_pos[last] < 0) { s.block_pos[last] = 0; pc.blocks.push_back((int32_t)last); }
                 }
             }
+            std::sort(pc.blocks.begin() + (std::ptrdiff_t)at, pc.blocks.end());
+            for (size_t k = at; k < pc.blocks.size(); ++k) s.block_pos[pc.blocks[k]] = -1;
+            const int64_t nb = (int64_t)(pc.blocks.size() - at);
+            v->blk_ptr[(size_t)g + 1] = nb;
+            kind[g] = kind_of(s, rg[g], rg[g + 1], nb);
         }
-        std::sort(blocks.begin(), blocks.end());
-        for (int32_t j : blocks) pos_of_block[j] = -1;
-        const int64_t nb = (int64_t)blocks.size();
-        for (int64_t t = 0; t < nb; ++t) {
-            v->blk_col.push_back(blocks[t]);
-            v->blk_off.push_back(v->blk_off.back() + h * col_block);
-        }
-        v->blk_ptr[g + 1] = v->blk_ptr[g] + nb;
-        v->ks_ptr[g + 1] = v->ks_ptr[g];
-        v->group_first_tile[g + 1] = v->group_first_tile[g];
+    });
+    for (int32_t g = 0; g < G; ++g) v->blk_ptr[(size_t)g + 1] += v->blk_ptr[g];
+    std::vector<int64_t> first_off((size_t)pieces.size() + 1, 0);
+    for (size_t i = 0; i < pieces.size(); ++i) {
+        pieces[i].first_block = v->blk_ptr[pieces[i].g0];
+        int64_t area = 0;
+        for (int32_t g = pieces[i].g0; g < pieces[i].g1; ++g) area += (v->blk_ptr[g + 1] - v->blk_ptr[g]) * (int64_t)(rg[g + 1] - rg[g]) * cb;
+        first_off[i + 1] = first_off[i] + area;
+    }
+    v->blk_col.resize((size_t)v->blk_ptr[G]);
+    v->blk_off.resize((size_t)v->blk_ptr[G] + 1);
+    v->blk_off[0] = 0;
+    each((int64_t)pieces.size(), 1, [&](Scratch &, int64_t i) {
+        Piece &pc = pieces[(size_t)i];
+        std::copy(pc.blocks.begin(), pc.blocks.end(), v->blk_col.begin() + pc.first_block);
+        int64_t off = first_off[(size_t)i];
+        for (int32_t g = pc.g0; g < pc.g1; ++g)
+            for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) v->blk_off[(size_t)b + 1] = off += (int64_t)(rg[g + 1] - rg[g]) * cb;
+        std::vector<int32_t>().swap(pc.blocks);
+    });
+    for (int32_t g = 0; g < G; ++g) {
+        if (kind[g] == kLow) low_groups.push_back(g);
+        if (kind[g] == kGathered) gathered_groups.push_back(g);
+    }
+}
 
-        if (h < kSlabRows) {                        // low group: its rows join the low rows (ordered below)
-            low_groups.push_back(g);
-            continue;
-        }
+// Groups lower than a slab join the low rows.  The blocks of a taller group may hold many columns without a single
+// entry; when tiles that gather only the columns their rows touch take clearly less time, the group is packed that way.
+Builder::Kind Builder::kind_of(Scratch &s, int64_t r0, int64_t r1, int64_t n_blocks)
+{
+    const int64_t h = r1 - r0, n_ks = steps_of(n_blocks * cb), slabs = (h + kSlabRows - 1) / kSlabRows;
+    if (h < kSlabRows) return kLow;
+    const int64_t nt = (slabs + kMaxSlabs - 1) / kMaxSlabs;
+    int64_t by_blocks = 0, by_columns = 0;
+    for (int64_t t = 0; t < nt; ++t) by_blocks += n_ks * kBlockStepNs[slab_class((int)(slabs / nt + (t < slabs % nt ? 1 : 0)))];
+    const int64_t step = kMaxGatherSlabs * kSlabRows;
+    for (int64_t q = r0; q < r1; q += step) {
+        const int64_t e = std::min(r1, q + step);
+        int64_t cols = 0;
+        s.begin();
+        for (int64_t i = q; i < e; ++i) cols += s.add(csr, perm[i]);
+        by_columns += steps_of(cols) * kGatherStepNs[(e - q + kSlabRows - 1) / kSlabRows - 1];
+        if (5 * by_columns > 4 * by_blocks) return kBlocks;
+    }
+    return kGathered;
+}
 
-        const int64_t Kg = nb * col_block;
-        const int64_t n_ks = (Kg + kStepK - 1) / kStepK;
-        const int64_t slabs = (h + kSlabRows - 1) / kSlabRows;
-        const int64_t nt = (slabs + kMaxSlabs - 1) / kMaxSlabs;
-        // Blocks with much fill-in hold many columns without a single entry.  When the columns the
-        // rows of the group's tiles actually touch need at most two thirds of the K-steps of its whole
-        // blocks, the tiles gather those columns instead (a gathered load costs the load path about
-        // a third more than a load of whole blocks); they are packed after the low rows, below.
-        {
-            int64_t gather_ks = 0, row = 0;
-            for (int64_t t = 0; t < nt; ++t) {
-                const int64_t s = slabs / nt + (t < slabs % nt ? 1 : 0);
-                const int64_t n_rows = std::min<int64_t>(s * kSlabRows, h - row);
-                ++col_stamp_id;
-                int64_t cols_t = 0;
-                for (int64_t q = r0 + row; q < r0 + row + n_rows; ++q)
-                    for (int64_t p = csr->row_ptr[perm[q]]; p < csr->row_ptr[perm[q] + 1]; ++p)
-                        if (col_stamp[csr->col_idx[p]] != col_stamp_id) { col_stamp[csr->col_idx[p]] = col_stamp_id; ++cols_t; }
-                gather_ks += (cols_t + kStepK - 1) / kStepK;
-                row += n_rows;
-            }
-            if (3 * gather_ks <= 2 * nt * n_ks) {
-                tall_gathered.push_back(g);
-                continue;
-            }
-        }
+// K-step gather lists and tiles of the groups that are multiplied block by block.
+int Builder::block_tiles()
+{
+    v->ks_ptr.assign((size_t)G + 1, 0);
+    v->group_first_tile.assign((size_t)G + 1, 0);
+    for (int32_t g = 0; g < G; ++g) {
+        v->ks_ptr[(size_t)g + 1] = v->ks_ptr[g];
+        v->group_first_tile[(size_t)g + 1] = v->group_first_tile[g];
+        if (kind[g] != kBlocks) continue;
+        const int64_t h = rg[g + 1] - rg[g], n_ks = steps_of((v->blk_ptr[g + 1] - v->blk_ptr[g]) * cb);
+        const int64_t slabs = (h + kSlabRows - 1) / kSlabRows, nt = (slabs + kMaxSlabs - 1) / kMaxSlabs;
         if (v->ks_ptr[g] + n_ks > INT32_MAX / 64) return VBR_EINVAL;
-        v->ks_ptr[g + 1] = v->ks_ptr[g] + n_ks;
-        for (int64_t e = 0; e < n_ks * per_step; ++e) {
-            const int64_t k = e * gran;
-            if (k < Kg) v->krow.push_back((int32_t)((int64_t)blocks[k / col_block] * col_block + k % col_block));
-            else v->krow.push_back(-1);
-        }
-
-        v->group_first_tile[g + 1] = v->group_first_tile[g] + nt;
+        v->ks_ptr[(size_t)g + 1] += n_ks;
+        v->group_first_tile[(size_t)g + 1] += nt;
         int64_t row = 0;
         for (int64_t t = 0; t < nt; ++t) {
             const int64_t s = slabs / nt + (t < slabs % nt ? 1 : 0);
@@ -148,7 +312,7 @@ int build_impl(const vbr_csr_t *csr, const int32_t *perm, const int32_t *row_gro
             td.ks_begin = (int32_t)v->ks_ptr[g];
             td.n_ks = (int32_t)n_ks;
             td.a_off = a_units;
-            td.row_begin = (int32_t)(r0 + row);
+            td.row_begin = (int32_t)(rg[g] + row);
             td.n_rows = (int32_t)std::min<int64_t>(s * kSlabRows, h - row);
             td.n_slabs = (int32_t)s;
             td.group = g;
@@ -157,408 +321,535 @@ int build_impl(const vbr_csr_t *csr, const int32_t *perm, const int32_t *row_gro
             tiles.push_back(td);
         }
     }
+    v->krow.resize((size_t)(v->ks_ptr[G] * per_step));
+    each((int64_t)pieces.size(), 1, [&](Scratch &, int64_t i) {
+        for (int32_t g = pieces[(size_t)i].g0; g < pieces[(size_t)i].g1; ++g) {
+            const int64_t n = (v->ks_ptr[g + 1] - v->ks_ptr[g]) * per_step, Kg = (v->blk_ptr[g + 1] - v->blk_ptr[g]) * cb;
+            int32_t *out = v->krow.data() + v->ks_ptr[g] * per_step;
+            for (int64_t e = 0; e < n; ++e) {
+                const int64_t k = e * gran;
+                out[e] = k < Kg ? (int32_t)((int64_t)v->blk_col[(size_t)(v->blk_ptr[g] + k / cb)] * cb + k % cb) : -1;
+            }
+        }
+    });
+    return VBR_OK;
+}
 
-    // The order of the low groups in the low-row list is free (C is written through the row list).
-    // Slabs cut from a list in which groups with similar block patterns follow each other gather
-    // far fewer B rows, so the list is built cluster by cluster: the first group not yet placed
-    // leads a cluster and takes with it every later group that shares at least half of the smaller
-    // of the two block sets with the LEADER (overlap coefficient >= 1/2, which unlike the Jaccard
-    // similarity does not fade when both sets carry noise blocks of their own; no pattern update:
-    // this only orders the packing, the blocking is the caller's).  Candidates come from an index column block -> low groups.  When
-    // the first 512 leaders find next to nothing (unstructured matrices), the rest keeps its order.
+// The order of the low rows in the row list is free (C is written through the list).  Tiles cut from a list in
+// which rows with similar columns follow each other gather far fewer B rows.
+void Builder::order_low_rows()
+{
+    if (!hubs_first()) cluster_low_groups();
+    low_slabs = ((int64_t)v->prow.size() + kSlabRows - 1) / kSlabRows;
+    v->panel_slabs = low_slabs > 0 ? kPanelSlabs : 0;
+}
+
+// Graphs with hubs: the longer a row, the more of its columns are those of the next longer one.  Where tiles of 64
+// rows share at least a fifth more in the order of falling length than in the order of the blocking, that order
+// is taken (graph of 16384 nodes: 0.37 gathered B rows per entry, against 0.49).
+bool Builder::hubs_first()
+{
+    std::vector<int32_t> given, sorted;        // positions in perm
+    int64_t longest = 0;
+    for (const int32_t g : low_groups)
+        for (int32_t q = rg[g]; q < rg[g + 1]; ++q) {
+            given.push_back(q);
+            longest = std::max(longest, csr->row_ptr[perm[q] + 1] - csr->row_ptr[perm[q]]);
+        }
+    const int64_t n = (int64_t)given.size(), step = kMaxGatherSlabs * kSlabRows;
+    if (n < kMergeMinSlabs * kSlabRows) return false;
+    std::vector<int32_t> at((size_t)longest + 2, 0);
+    auto key = [&](int32_t q) { return (size_t)(longest - (csr->row_ptr[perm[q] + 1] - csr->row_ptr[perm[q]])); };
+    for (const int32_t q : given) ++at[key(q) + 1];
+    for (size_t k = 0; k <= (size_t)longest; ++k) at[k + 1] += at[k];
+    sorted.resize((size_t)n);
+    for (const int32_t q : given) sorted[(size_t)at[key(q)]++] = q;
+    std::atomic<int64_t> shared[2] = {{0}, {0}};
+    const int64_t n_tiles = (n + step - 1) / step;
+    each(2 * n_tiles, 4, [&](Scratch &s, int64_t i) {
+        const std::vector<int32_t> &list = i < n_tiles ? given : sorted;
+        const int64_t b = (i % n_tiles) * step;
+        int64_t cols = 0;
+        s.begin();
+        for (int64_t k = b; k < std::min(n, b + step); ++k) cols += s.add(csr, perm[list[(size_t)k]]);
+        shared[i / n_tiles] += cols;
+    });
+    if (5 * shared[1] > 4 * shared[0]) return false;
+    v->prow.resize((size_t)n);
+    for (int64_t i = 0; i < n; ++i) {
+        v->prow[(size_t)i] = perm[sorted[(size_t)i]];
+        v->row_pos[(size_t)sorted[(size_t)i]] = (int32_t)i;
+    }
+    return true;
+}
+
+// Otherwise the list is built cluster by cluster: the first group not yet placed
+// leads a cluster and takes with it every later group that shares at least half of the smaller
+// of the two block sets with the LEADER (overlap coefficient >= 1/2, which unlike the Jaccard
+// similarity does not fade when both sets carry noise blocks of their own; no pattern update:
+// this only orders the packing, the blocking is the caller's).  Candidates come from an index column block -> low groups.  When
+// the first 512 leaders find next to nothing (unstructured matrices), the rest keeps its order.
+void Builder::cluster_low_groups()
+{
+    const int64_t n_low = (int64_t)low_groups.size();
+    std::vector<int32_t> order, cluster_first;      // cluster_first: index in `order` of every cluster's leader
+    order.reserve((size_t)n_low);
+    std::vector<int64_t> inv_ptr((size_t)KB + 1, 0);
+    for (const int32_t g : low_groups)
+        for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) inv_ptr[v->blk_col[b] + 1]++;
+    for (int64_t b = 0; b < KB; ++b) inv_ptr[b + 1] += inv_ptr[b];
+    std::vector<int32_t> inv((size_t)inv_ptr[KB]);
     {
-        const int64_t n_low = (int64_t)low_groups.size();
-        std::vector<int32_t> order, cluster_first;      // cluster_first: index in `order` of every cluster's leader
-        order.reserve((size_t)n_low);
-        std::vector<int64_t> inv_ptr((size_t)KB + 1, 0);
-        for (const int32_t g : low_groups)
-            for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) inv_ptr[v->blk_col[b] + 1]++;
-        for (int64_t b = 0; b < KB; ++b) inv_ptr[b + 1] += inv_ptr[b];
-        std::vector<int32_t> inv((size_t)inv_ptr[KB]);
-        {
-            std::vector<int64_t> fill(inv_ptr.begin(), inv_ptr.end() - 1);
-            for (int64_t i = 0; i < n_low; ++i) {
-                const int32_t g = low_groups[i];
-                for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) inv[fill[v->blk_col[b]]++] = (int32_t)i;
-            }
-        }
-        std::vector<int64_t> first(inv_ptr.begin(), inv_ptr.end() - 1);
-        std::vector<uint8_t> placed((size_t)n_low, 0);
-        std::vector<int32_t> cnt((size_t)n_low, 0), hit;
-        int64_t leaders = 0, followers = 0;
-        bool clustering = true;
+        std::vector<int64_t> fill(inv_ptr.begin(), inv_ptr.end() - 1);
         for (int64_t i = 0; i < n_low; ++i) {
-            if (placed[i]) continue;
-            placed[i] = 1;
-            cluster_first.push_back((int32_t)order.size());
-            order.push_back((int32_t)i);
-            if (!clustering) continue;
             const int32_t g = low_groups[i];
-            const int64_t li = v->blk_ptr[g + 1] - v->blk_ptr[g];
-            hit.clear();
-            for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) {
-                const int32_t blk = v->blk_col[b];
-                int64_t &f = first[blk];
-                while (f < inv_ptr[blk + 1] && inv[f] <= i) ++f;
-                for (int64_t e = f; e < inv_ptr[blk + 1]; ++e) {
-                    const int32_t j = inv[e];
-                    if (!placed[j] && cnt[j]++ == 0) hit.push_back(j);
-                }
-            }
-            // the followers join in rising order; only they are sorted (the candidates are thousands per
-            // leader on an unstructured matrix, the followers few)
-            size_t n_pass = 0;
-            for (const int32_t j : hit) {
-                const int32_t gj = low_groups[j];
-                const int64_t I = cnt[j], lj = v->blk_ptr[gj + 1] - v->blk_ptr[gj];
-                cnt[j] = 0;
-                if (2 * I >= std::min(li, lj)) hit[n_pass++] = j;
-            }
-            std::sort(hit.begin(), hit.begin() + (std::ptrdiff_t)n_pass);
-            for (size_t k = 0; k < n_pass; ++k) { placed[hit[k]] = 1; order.push_back(hit[k]); ++followers; }
-            if (++leaders == 512 && followers < 64) clustering = false;
-        }
-        // A cluster of two slabs' worth of rows or more begins and ends on a slab boundary (the list is
-        // padded with -1: positions without a row), so that no slab mixes it with its neighbours.  And no
-        // slab gathers more than kSlabMaxCols columns if it can be helped: a group whose columns would
-        // take the slab beyond that starts a new slab (unrelated rows add up their columns, and the
-        // longest slab of a launch, one workgroup per column tile, is what the launch waits for).
-        cluster_first.push_back((int32_t)order.size());
-        std::vector<int64_t> col_slab((size_t)std::max<int64_t>(csr->n_cols, 1), -1);   // slab that last counted the column
-        int64_t slab_id = 0, slab_cols = 0;
-        auto pad_to_slab = [&]() {
-            while (v->prow.size() % kSlabRows != 0) v->prow.push_back(-1);
-            ++slab_id;
-            slab_cols = 0;
-        };
-        for (size_t c = 0; c + 1 < cluster_first.size(); ++c) {
-            int64_t rows = 0;
-            for (int32_t o = cluster_first[c]; o < cluster_first[c + 1]; ++o)
-                rows += row_groups[low_groups[order[o]] + 1] - row_groups[low_groups[order[o]]];
-            const bool align = rows >= 2 * kSlabRows;
-            if (align) pad_to_slab();
-            for (int32_t o = cluster_first[c]; o < cluster_first[c + 1]; ++o) {
-                const int32_t g = low_groups[order[o]];
-                int64_t fresh = 0;                      // columns of the group the current slab does not hold yet
-                for (int64_t q = row_groups[g]; q < row_groups[g + 1]; ++q)
-                    for (int64_t p = csr->row_ptr[perm[q]]; p < csr->row_ptr[perm[q] + 1]; ++p)
-                        fresh += col_slab[csr->col_idx[p]] != slab_id;
-                if (v->prow.size() % kSlabRows != 0 && slab_cols + fresh > kSlabMaxCols) pad_to_slab();
-                v->group_prow[g] = (int32_t)v->prow.size();
-                for (int64_t q = row_groups[g]; q < row_groups[g + 1]; ++q) {
-                    if (v->prow.size() % kSlabRows == 0) { ++slab_id; slab_cols = 0; }      // a new slab begins here
-                    for (int64_t p = csr->row_ptr[perm[q]]; p < csr->row_ptr[perm[q] + 1]; ++p)
-                        if (col_slab[csr->col_idx[p]] != slab_id) { col_slab[csr->col_idx[p]] = slab_id; ++slab_cols; }
-                    v->prow.push_back(perm[q]);
-                }
-            }
-            if (align) pad_to_slab();
+            for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) inv[fill[v->blk_col[b]]++] = (int32_t)i;
         }
     }
-
-    // pass 2: the low rows, in chunks of 8 slabs.
-    const int64_t n_prows = (int64_t)v->prow.size();
-    std::vector<int32_t> prow_group((size_t)n_prows, -1);     // -1: a padding position
-    for (int32_t g = 0; g < G; ++g)
-        if (v->group_prow[g] >= 0)
-            for (int64_t i = 0; i < row_groups[g + 1] - row_groups[g]; ++i) prow_group[v->group_prow[g] + i] = g;
-    const int R = kPanelSlabs;
-    v->panel_slabs = n_prows > 0 ? R : 0;
-    const int max_frags = kPanelMaxFrags;
-    const int64_t panel_rows = (int64_t)R * kSlabRows;
-    const int64_t n_panels = (n_prows + panel_rows - 1) / panel_rows;       // chunks
-    v->p_union_ptr.assign(1, 0);
-    std::vector<uint32_t> blk_mask;            // per union block: slabs that store it
-    std::vector<int64_t> frag_of;              // [logical step][slab] -> fragment ordinal in the panel, -1
-    std::vector<int64_t> fill_dst, fill_src;   // low-row values: position in vals <- position in csr->vals
-    std::vector<int32_t> pos_of_col((size_t)std::max<int64_t>(csr->n_cols, 1), -1);
-    std::vector<int32_t> cols;
-    v->chunk_gather.assign((size_t)n_panels, 0);
-    v->chunk_index.assign((size_t)n_panels, 0);
-    int64_t g_ks = 0;                          // K-steps of the gathered tiles so far
-
-    auto emit_panel = [&](int64_t pn) -> int {
-        v->chunk_index[pn] = (int32_t)v->panels.size();
-        const int64_t i0 = pn * panel_rows, i1 = std::min(n_prows, i0 + panel_rows);
-        // union of blocks, and per block the slabs that hold it
-        blocks.clear();
-        for (int64_t i = i0; i < i1; ++i) {
-            const int32_t g = prow_group[i];
-            if (g < 0 || (i > i0 && prow_group[i - 1] == g)) continue;
-            for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b)
-                if (pos_of_block[v->blk_col[b]] < 0) { pos_of_block[v->blk_col[b]] = 0; blocks.push_back(v->blk_col[b]); }
+    std::vector<int64_t> first(inv_ptr.begin(), inv_ptr.end() - 1);
+    std::vector<uint8_t> placed((size_t)n_low, 0);
+    std::vector<int32_t> cnt((size_t)n_low, 0), hit;
+    int64_t leaders = 0, followers = 0;
+    bool clustering = true;
+    for (int64_t i = 0; i < n_low; ++i) {
+        if (placed[i]) continue;
+        placed[i] = 1;
+        cluster_first.push_back((int32_t)order.size());
+        order.push_back((int32_t)i);
+        if (!clustering) continue;
+        const int32_t g = low_groups[i];
+        const int64_t li = v->blk_ptr[g + 1] - v->blk_ptr[g];
+        hit.clear();
+        for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) {
+            const int32_t blk = v->blk_col[b];
+            int64_t &f = first[blk];
+            while (f < inv_ptr[blk + 1] && inv[f] <= i) ++f;
+            for (int64_t e = f; e < inv_ptr[blk + 1]; ++e) {
+                const int32_t j = inv[e];
+                if (!placed[j] && cnt[j]++ == 0) hit.push_back(j);
+            }
         }
-        std::sort(blocks.begin(), blocks.end());
-        const int64_t nu = (int64_t)blocks.size();
-        for (int64_t u = 0; u < nu; ++u) pos_of_block[blocks[u]] = (int32_t)u;
-        blk_mask.assign((size_t)nu, 0u);
-        for (int64_t i = i0; i < i1; ++i) {
-            const int32_t g = prow_group[i];
-            if (g < 0) continue;
-            const uint32_t bit = 1u << ((i - i0) / kSlabRows);
-            for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) blk_mask[pos_of_block[v->blk_col[b]]] |= bit;
+        // the followers join in rising order; only they are sorted (the candidates are thousands per
+        // leader on an unstructured matrix, the followers few)
+        size_t n_pass = 0;
+        for (const int32_t j : hit) {
+            const int32_t gj = low_groups[j];
+            const int64_t I = cnt[j], lj = v->blk_ptr[gj + 1] - v->blk_ptr[gj];
+            cnt[j] = 0;
+            if (2 * I >= std::min(li, lj)) hit[n_pass++] = j;
         }
-        v->p_union.insert(v->p_union.end(), blocks.begin(), blocks.end());
-        v->p_union_ptr.push_back((int64_t)v->p_union.size());
+        std::sort(hit.begin(), hit.begin() + (std::ptrdiff_t)n_pass);
+        for (size_t k = 0; k < n_pass; ++k) { placed[hit[k]] = 1; order.push_back(hit[k]); ++followers; }
+        if (++leaders == 512 && followers < 64) clustering = false;
+    }
+    // A cluster of two slabs' worth of rows or more begins and ends on a slab boundary (the list is
+    // padded with -1: positions without a row), so that no slab mixes it with its neighbours.  And no
+    // slab gathers more than kSlabMaxCols columns if it can be helped: a group whose columns would
+    // take the slab beyond that starts a new slab (unrelated rows add up their columns, and the
+    // longest slab of a launch, one workgroup per column tile, is what the launch waits for).
+    cluster_first.push_back((int32_t)order.size());
+    Scratch &s = scratch[0];
+    s.fit(csr->n_cols, KB);
+    s.begin();
+    int64_t slab_cols = 0;
+    auto new_slab = [&]() { s.begin(); slab_cols = 0; };
+    auto pad_to_slab = [&]() {
+        while (v->prow.size() % kSlabRows != 0) v->prow.push_back(-1);
+        new_slab();
+    };
+    for (size_t c = 0; c + 1 < cluster_first.size(); ++c) {
+        int64_t rows = 0;
+        for (int32_t o = cluster_first[c]; o < cluster_first[c + 1]; ++o)
+            rows += rg[low_groups[order[o]] + 1] - rg[low_groups[order[o]]];
+        const bool align = rows >= 2 * kSlabRows;
+        if (align) pad_to_slab();
+        for (int32_t o = cluster_first[c]; o < cluster_first[c + 1]; ++o) {
+            const int32_t g = low_groups[order[o]];
+            int64_t fresh = 0;                      // columns of the group the current slab does not hold yet
+            for (int64_t q = rg[g]; q < rg[g + 1]; ++q)
+                for (int64_t p = csr->row_ptr[perm[q]]; p < csr->row_ptr[perm[q] + 1]; ++p)
+                    fresh += s.stamp[csr->col_idx[p]] != s.now;
+            if (v->prow.size() % kSlabRows != 0 && slab_cols + fresh > kSlabMaxCols) pad_to_slab();
+            for (int64_t q = rg[g]; q < rg[g + 1]; ++q) {
+                if (v->prow.size() % kSlabRows == 0) new_slab();      // a new slab begins here
+                slab_cols += s.add(csr, perm[q]);
+                v->row_pos[(size_t)q] = (int32_t)v->prow.size();
+                v->prow.push_back(perm[q]);
+            }
+        }
+        if (align) pad_to_slab();
+    }
+}
 
-        PanelDesc pd;
-        pd.ks_begin = (int32_t)v->pk_mask.size();
-        pd.a_off = a_units;
-        pd.row_begin = (int32_t)i0;
-        pd.n_rows = (int32_t)(i1 - i0);
-        pd.pad = 0;
-        pd.meta_begin = (int32_t)(v->pk_meta.size() / (size_t)(1 + per_step));
-        const int64_t Ku = nu * col_block;
-        const int64_t T = (Ku + kStepK - 1) / kStepK;
-        frag_of.assign((size_t)(T * R), -1);
-        int64_t n_frags = 0;
-        for (int64_t t = 0; t < T; ++t) {
-            uint32_t m = 0;
-            for (int64_t u = (t * kStepK) / col_block; u <= std::min(nu - 1, (t * kStepK + kStepK - 1) / col_block); ++u) m |= blk_mask[u];
-            // a physical K-step carries at most max_frags fragments: split the rest into repeats
-            while (m != 0) {
-                uint32_t part = 0;
-                int cnt = 0;
-                for (int s = 0; s < R && cnt < max_frags; ++s)
-                    if (m >> s & 1) { part |= 1u << s; frag_of[(size_t)(t * R + s)] = n_frags + cnt; ++cnt; }
-                m &= ~part;
-                v->pk_mask.push_back(part);
-                v->pk_logical.push_back((int32_t)t);
-                v->pk_frag.push_back(n_frags);
-                n_frags += cnt;
-                for (int e = 0; e < per_step; ++e) {
-                    const int64_t k = t * kStepK + (int64_t)e * gran;
-                    v->pk_row.push_back(k < Ku ? (int32_t)((int64_t)blocks[k / col_block] * col_block + k % col_block) : -1);
+// Which chunks of 8 slabs of low rows are packed as panels.
+void Builder::choose_panels()
+{
+    const int64_t n_prows = (int64_t)v->prow.size(), panel_rows = (int64_t)kPanelSlabs * kSlabRows;
+    const int64_t n_chunks = (n_prows + panel_rows - 1) / panel_rows;
+    v->chunk_panel.assign((size_t)n_chunks, -1);
+    if (!panels_on) return;
+    prow_group.assign((size_t)n_prows, -1);
+    for (const int32_t g : low_groups)
+        for (int64_t q = rg[g]; q < rg[g + 1]; ++q) prow_group[(size_t)v->row_pos[(size_t)q]] = g;
+    // loads of the two packings for the chunk (per 256 columns of C)
+    std::vector<uint8_t> panel((size_t)n_chunks, 0);
+    each(n_chunks, 4, [&](Scratch &s, int64_t c) {
+        const int64_t i0 = c * panel_rows, i1 = std::min(n_prows, i0 + panel_rows);
+        std::vector<int32_t> blocks;
+        int64_t cost_gather = 0;
+        for (int64_t s0 = i0; s0 < i1; s0 += kSlabRows) {
+            int64_t cols = 0;
+            s.begin();
+            for (int64_t i = s0; i < std::min(i1, s0 + kSlabRows); ++i) {
+                if (v->prow[(size_t)i] < 0) continue;
+                cols += s.add(csr, v->prow[(size_t)i]);
+                for (int64_t p = csr->row_ptr[v->prow[(size_t)i]]; p < csr->row_ptr[v->prow[(size_t)i] + 1]; ++p) {
+                    const int32_t j = csr->col_idx[p] / cb;
+                    if (s.block_pos[j] < 0) { s.block_pos[j] = 0; blocks.push_back(j); }
                 }
             }
+            cost_gather += steps_of(cols) * kTileStepCost;
         }
-        pd.n_ks = (int32_t)v->pk_mask.size() - pd.ks_begin;
-        if ((int64_t)v->pk_mask.size() > INT32_MAX / 64) return VBR_EINVAL;
-        // the device's K-step stream: one record per physical step, then the look-ahead padding
-        for (int64_t ph = pd.ks_begin; ph < pd.ks_begin + pd.n_ks + (pd.n_ks > 0 ? kPanelMetaPad : 0); ++ph) {
-            const int64_t src_ph = std::min<int64_t>(ph, pd.ks_begin + pd.n_ks - 1);
-            v->pk_meta.push_back(ph < pd.ks_begin + pd.n_ks ? (int32_t)v->pk_mask[ph] : 0);
-            for (int e = 0; e < per_step; ++e) v->pk_meta.push_back(v->pk_row[(size_t)src_ph * per_step + e]);
-        }
-        // values: one full 16 x 32 fragment per (physical step, present slab).  Only the target
-        // position of every entry is noted here; the value array is allocated once, at its final
-        // size, after the last panel.
-        for (int64_t i = i0; i < i1; ++i) {
-            const int64_t r = v->prow[i];
-            if (r < 0) continue;
-            const int s = (int)((i - i0) / kSlabRows), mrow = (int)((i - i0) % kSlabRows);
-            for (int64_t p = csr->row_ptr[r]; p < csr->row_ptr[r + 1]; ++p) {
-                const int64_t c = csr->col_idx[p];
-                const int64_t k = (int64_t)pos_of_block[c / col_block] * col_block + c % col_block;
-                fill_dst.push_back(a_units * 8 + frag_of[(size_t)((k / kStepK) * R + s)] * kFragElems +
-                                   frag_index(mrow, (int)(k % kStepK), kSlabRows));
-                fill_src.push_back(p);
+        for (const int32_t j : blocks) s.block_pos[j] = -1;
+        panel[(size_t)c] = cost_gather >= steps_of((int64_t)blocks.size() * cb) * kPanelStepCost;
+    });
+    int32_t n = 0;
+    for (int64_t c = 0; c < n_chunks; ++c)
+        if (panel[(size_t)c]) v->chunk_panel[(size_t)c] = n++;
+}
+
+int Builder::emit_panel(int64_t pn)
+{
+    const int R = kPanelSlabs;
+    const int64_t panel_rows = (int64_t)R * kSlabRows, n_prows = (int64_t)v->prow.size();
+    const int64_t i0 = pn * panel_rows, i1 = std::min(n_prows, i0 + panel_rows);
+    Scratch &s = scratch[0];
+    s.fit(csr->n_cols, KB);
+    if (v->p_union_ptr.empty()) v->p_union_ptr.assign(1, 0);
+    // union of blocks, and per block the slabs that hold it
+    std::vector<int32_t> blocks;
+    auto groups_of_chunk = [&](auto f) {
+        for (int64_t i = i0; i < i1; ++i)
+            if (prow_group[(size_t)i] >= 0) f(i, prow_group[(size_t)i]);
+    };
+    groups_of_chunk([&](int64_t i, int32_t g) {
+        if (i > i0 && prow_group[(size_t)i - 1] == g) return;
+        for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b)
+            if (s.block_pos[v->blk_col[b]] < 0) { s.block_pos[v->blk_col[b]] = 0; blocks.push_back(v->blk_col[b]); }
+    });
+    std::sort(blocks.begin(), blocks.end());
+    const int64_t nu = (int64_t)blocks.size();
+    for (int64_t u = 0; u < nu; ++u) s.block_pos[blocks[u]] = (int32_t)u;
+    std::vector<uint32_t> blk_mask((size_t)nu, 0u);
+    groups_of_chunk([&](int64_t i, int32_t g) {
+        if (i > i0 && prow_group[(size_t)i - 1] == g && i % kSlabRows != 0) return;
+        for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) blk_mask[s.block_pos[v->blk_col[b]]] |= 1u << ((i - i0) / kSlabRows);
+    });
+    v->p_union.insert(v->p_union.end(), blocks.begin(), blocks.end());
+    v->p_union_ptr.push_back((int64_t)v->p_union.size());
+
+    PanelDesc pd;
+    pd.ks_begin = (int32_t)v->pk_mask.size();
+    pd.a_off = a_units;
+    pd.row_begin = (int32_t)i0;
+    pd.n_rows = (int32_t)(i1 - i0);
+    pd.pad = 0;
+    pd.meta_begin = (int32_t)(v->pk_meta.size() / (size_t)(1 + per_step));
+    const int64_t Ku = nu * cb, T = steps_of(Ku);
+    std::vector<int64_t> frag_of((size_t)(T * R), -1);      // [logical step][slab] -> fragment ordinal in the panel, -1
+    int64_t n_frags = 0;
+    for (int64_t t = 0; t < T; ++t) {
+        uint32_t m = 0;
+        for (int64_t u = (t * kStepK) / cb; u <= std::min(nu - 1, (t * kStepK + kStepK - 1) / cb); ++u) m |= blk_mask[u];
+        // a physical K-step carries at most kPanelMaxFrags fragments: split the rest into repeats
+        while (m != 0) {
+            uint32_t part = 0;
+            int cnt = 0;
+            for (int sl = 0; sl < R && cnt < kPanelMaxFrags; ++sl)
+                if (m >> sl & 1) { part |= 1u << sl; frag_of[(size_t)(t * R + sl)] = n_frags + cnt; ++cnt; }
+            m &= ~part;
+            v->pk_mask.push_back(part);
+            v->pk_logical.push_back((int32_t)t);
+            v->pk_frag.push_back(n_frags);
+            n_frags += cnt;
+            for (int e = 0; e < per_step; ++e) {
+                const int64_t k = t * kStepK + (int64_t)e * gran;
+                v->pk_row.push_back(k < Ku ? (int32_t)((int64_t)blocks[k / cb] * cb + k % cb) : -1);
             }
         }
-        a_units += n_frags * (kFragElems / 8);
-        for (int64_t u = 0; u < nu; ++u) pos_of_block[blocks[u]] = -1;
-        v->panels.push_back(pd);
-        return VBR_OK;
-    };
+    }
+    pd.n_ks = (int32_t)v->pk_mask.size() - pd.ks_begin;
+    if ((int64_t)v->pk_mask.size() > INT32_MAX / 64) return VBR_EINVAL;
+    // the device's K-step stream: one record per physical step, then the look-ahead padding
+    for (int64_t ph = pd.ks_begin; ph < pd.ks_begin + pd.n_ks + (pd.n_ks > 0 ? kPanelMetaPad : 0); ++ph) {
+        const int64_t src_ph = std::min<int64_t>(ph, pd.ks_begin + pd.n_ks - 1);
+        v->pk_meta.push_back(ph < pd.ks_begin + pd.n_ks ? (int32_t)v->pk_mask[ph] : 0);
+        for (int e = 0; e < per_step; ++e) v->pk_meta.push_back(v->pk_row[(size_t)src_ph * per_step + e]);
+    }
+    // values: one full 16 x 32 fragment per (physical step, present slab).  Only the target
+    // position of every entry is noted here; the values are packed once the size of all of them is known.
+    for (int64_t i = i0; i < i1; ++i) {
+        const int64_t r = v->prow[(size_t)i];
+        if (r < 0) continue;
+        const int sl = (int)((i - i0) / kSlabRows), mrow = (int)((i - i0) % kSlabRows);
+        for (int64_t p = csr->row_ptr[r]; p < csr->row_ptr[r + 1]; ++p) {
+            const int64_t c = csr->col_idx[p];
+            const int64_t k = (int64_t)s.block_pos[c / cb] * cb + c % cb;
+            panel_dst.push_back(a_units * 8 + frag_of[(size_t)((k / kStepK) * R + sl)] * kFragElems +
+                                frag_index(mrow, (int)(k % kStepK), kSlabRows));
+            panel_src.push_back(p);
+        }
+    }
+    panel_range.emplace_back(a_units, a_units + n_frags * (kFragElems / 8));
+    a_units += n_frags * (kFragElems / 8);
+    for (int64_t u = 0; u < nu; ++u) s.block_pos[blocks[u]] = -1;
+    v->panels.push_back(pd);
+    return VBR_OK;
+}
 
-    // A column-gathered tile over the positions [s0, s1) of the low-row list (up to 8 slabs): its K
-    // dimension is the ascending list of the columns its rows touch, cut into K-steps of 32.
-    auto emit_gather_tile = [&](int64_t s0, int64_t s1, int32_t group_code) -> int {
-        cols.clear();
-        for (int64_t i = s0; i < s1; ++i) {
-            const int64_t r = v->prow[i];
+// The rows of the taller groups that gather single columns follow the low rows in the row list, every group from a
+// slab boundary on and, inside it, the longest rows first.
+void Builder::append_gathered_groups()
+{
+    std::vector<int32_t> pos;
+    for (const int32_t g : gathered_groups) {
+        while (v->prow.size() % kSlabRows != 0) v->prow.push_back(-1);
+        pos.clear();
+        for (int32_t q = rg[g]; q < rg[g + 1]; ++q) pos.push_back(q);
+        std::stable_sort(pos.begin(), pos.end(), [&](int32_t a, int32_t b) {
+            return csr->row_ptr[perm[a] + 1] - csr->row_ptr[perm[a]] > csr->row_ptr[perm[b] + 1] - csr->row_ptr[perm[b]];
+        });
+        for (const int32_t q : pos) {
+            v->row_pos[(size_t)q] = (int32_t)v->prow.size();
+            v->prow.push_back(perm[q]);
+        }
+    }
+}
+
+// Cuts the slabs of the row list (those in no panel) into gathered tiles of 1 to 4 consecutive slabs.  A taller tile
+// loads a B row once for all its slabs and multiplies it for all of them: what it gains is the columns they share.
+// The cut of least estimated time is found stretch by stretch.
+//   - Slabs of low rows are joined only where that saves at least a seventh of the gathered rows (joining slabs that
+//     share nothing would make fewer, longer workgroups), and only if there are kMergeMinSlabs of them.
+//   - A tile of more K-steps than a resident workgroup's share of the whole (at N = 2048) would still be at it when the
+//     rest is done.  It is "deep": the waves of a workgroup split its K-steps, and four workgroups its 256 columns.
+void Builder::cut_into_tiles()
+{
+    const int64_t n_slabs = ((int64_t)v->prow.size() + kSlabRows - 1) / kSlabRows;
+    v->slab_tile.assign((size_t)n_slabs, -1);
+    // group of slabs of the row list that a tile may not leave: low rows 0, gathered groups 1, 2, ...
+    std::vector<int32_t> part((size_t)n_slabs, 0);
+    for (size_t i = 0; i < gathered_groups.size(); ++i)
+        for (int64_t q = rg[gathered_groups[i]]; q < rg[gathered_groups[i] + 1]; ++q)
+            part[(size_t)(v->row_pos[(size_t)q] / kSlabRows)] = (int32_t)i + 1;
+    auto in_panel = [&](int64_t sl) { return part[(size_t)sl] == 0 && v->chunk_panel[(size_t)(sl / kPanelSlabs)] >= 0; };
+    // columns of the tile of len slabs from slab i on, -1 = not possible
+    std::vector<int32_t> cols((size_t)n_slabs * kMaxGatherSlabs, -1);
+    each(n_slabs, 16, [&](Scratch &s, int64_t i) {
+        if (in_panel(i)) return;
+        int64_t n = 0;
+        s.begin();
+        for (int len = 1; len <= kMaxGatherSlabs; ++len) {
+            const int64_t sl = i + len - 1;
+            if (sl >= n_slabs || part[(size_t)sl] != part[(size_t)i] || in_panel(sl)) break;
+            for (int64_t k = sl * kSlabRows; k < std::min((sl + 1) * kSlabRows, (int64_t)v->prow.size()); ++k)
+                if (v->prow[(size_t)k] >= 0) n += s.add(csr, v->prow[(size_t)k]);
+            cols[(size_t)(i * kMaxGatherSlabs + len - 1)] = (int32_t)n;
+        }
+    });
+    // stretches
+    std::vector<std::pair<int64_t, int64_t>> runs;
+    for (int64_t i = 0; i < n_slabs;) {
+        if (in_panel(i)) { ++i; continue; }
+        int64_t e = i + 1;
+        while (e < n_slabs && e - i < kSegmentSlabs && part[(size_t)e] == part[(size_t)i] && !in_panel(e)) ++e;
+        runs.emplace_back(i, e);
+        i = e;
+    }
+    std::vector<std::vector<uint8_t>> cut(runs.size());     // lengths of the tiles of every stretch, in order
+    std::atomic<int64_t> total(0);
+    auto best_cuts = [&](int64_t deep_steps) {
+        total = 0;
+        each((int64_t)runs.size(), 2, [&](Scratch &, int64_t r) {
+            const int64_t b = runs[(size_t)r].first, n = runs[(size_t)r].second - b;
+            const bool low = part[(size_t)b] == 0, single = low && low_slabs < kMergeMinSlabs;
+            std::vector<int64_t> best((size_t)n + 1, INT64_MAX / 2);
+            std::vector<uint8_t> len_of((size_t)n + 1, 0);
+            best[0] = 0;
+            for (int64_t i = 0; i < n; ++i) {
+                int64_t alone = 0;
+                for (int len = 1; len <= kMaxGatherSlabs && i + len <= n; ++len) {
+                    const int64_t c = cols[(size_t)((b + i) * kMaxGatherSlabs + len - 1)];
+                    alone += cols[(size_t)((b + i + len - 1) * kMaxGatherSlabs)];
+                    if (len > 1 && (single || (low && 7 * c > 6 * alone))) continue;
+                    const int64_t cost = best[(size_t)i] + gather_cost(c, len, deep_steps);
+                    if (cost < best[(size_t)(i + len)]) { best[(size_t)(i + len)] = cost; len_of[(size_t)(i + len)] = (uint8_t)len; }
+                }
+            }
+            cut[(size_t)r].clear();
+            int64_t steps = 0;
+            for (int64_t e = n; e > 0; e -= len_of[(size_t)e]) {
+                cut[(size_t)r].push_back(len_of[(size_t)e]);
+                steps += steps_of(cols[(size_t)((b + e - len_of[(size_t)e]) * kMaxGatherSlabs + len_of[(size_t)e] - 1)]);
+            }
+            std::reverse(cut[(size_t)r].begin(), cut[(size_t)r].end());
+            total += steps;
+        });
+    };
+    best_cuts(INT32_MAX);
+    v->deep_steps = (int32_t)std::min<int64_t>(INT32_MAX, std::max<int64_t>(kDeepSteps, total * 8 / 768));
+    best_cuts(v->deep_steps);
+    for (size_t r = 0; r < runs.size(); ++r) {
+        int64_t sl = runs[r].first;
+        for (const uint8_t len : cut[r]) {
+            TileDesc td;
+            td.ks_begin = 0;
+            td.n_ks = (int32_t)steps_of(cols[(size_t)(sl * kMaxGatherSlabs + len - 1)]);
+            td.a_off = 0;
+            td.row_begin = (int32_t)(sl * kSlabRows);
+            int64_t end = std::min<int64_t>((sl + len) * kSlabRows, (int64_t)v->prow.size());
+            while (v->prow[(size_t)end - 1] < 0) --end;                    // padding behind the last row
+            td.n_rows = (int32_t)(end - sl * kSlabRows);
+            td.n_slabs = (td.n_rows + kSlabRows - 1) / kSlabRows;
+            td.group = td.n_ks >= v->deep_steps ? kTileDeep : kTileGathered;
+            for (int k = 0; k < len; ++k) v->slab_tile[(size_t)(sl + k)] = (int32_t)v->gtiles.size();
+            v->gtiles.push_back(td);
+            sl += len;
+        }
+    }
+}
+
+// Column lists of the gathered tiles: the ascending list of the columns its rows touch, cut into K-steps of 32.  The
+// last K-step is filled up with the last column again: its place in the fragments is the first, the others hold zeros.
+int Builder::emit_gather_tiles()
+{
+    int64_t g_ks = 0;
+    for (TileDesc &td : v->gtiles) {
+        if (g_ks + td.n_ks > INT32_MAX / 64) return VBR_EINVAL;
+        td.ks_begin = (int32_t)g_ks;
+        td.a_off = a_units;
+        g_ks += td.n_ks;
+        a_units += td.n_ks * tile_kstep_stride(td.n_rows, td.n_slabs) / 8;
+    }
+    v->gcol.resize((size_t)(g_ks * kStepK));
+    each((int64_t)v->gtiles.size(), 4, [&](Scratch &s, int64_t i) {
+        const TileDesc &td = v->gtiles[(size_t)i];
+        int32_t *out = v->gcol.data() + (int64_t)td.ks_begin * kStepK, *at = out;
+        s.begin();
+        for (int64_t k = td.row_begin; k < (int64_t)td.row_begin + td.n_rows; ++k) {
+            const int64_t r = v->prow[(size_t)k];
             if (r < 0) continue;
             for (int64_t p = csr->row_ptr[r]; p < csr->row_ptr[r + 1]; ++p)
-                if (pos_of_col[csr->col_idx[p]] < 0) { pos_of_col[csr->col_idx[p]] = 0; cols.push_back(csr->col_idx[p]); }
+                if (s.stamp[csr->col_idx[p]] != s.now) { s.stamp[csr->col_idx[p]] = s.now; *at++ = csr->col_idx[p]; }
         }
-        std::sort(cols.begin(), cols.end());
-        for (size_t k = 0; k < cols.size(); ++k) pos_of_col[cols[k]] = (int32_t)k;
-        const int64_t n_ks = ((int64_t)cols.size() + kStepK - 1) / kStepK;
-        if (g_ks + n_ks > INT32_MAX / 64) return VBR_EINVAL;
-        TileDesc td;
-        td.ks_begin = (int32_t)g_ks;
-        td.n_ks = (int32_t)n_ks;
-        td.a_off = a_units;
-        td.row_begin = (int32_t)s0;
-        td.n_rows = (int32_t)(s1 - s0);
-        td.n_slabs = (int32_t)((s1 - s0 + kSlabRows - 1) / kSlabRows);
-        td.group = group_code;
-        const int64_t stride = tile_kstep_stride(td.n_rows, td.n_slabs);
-        const int rows_last = td.n_rows - (td.n_slabs - 1) * kSlabRows;
-        for (int64_t i = s0; i < s1; ++i) {
-            const int64_t r = v->prow[i];
-            if (r < 0) continue;
-            const int slab = (int)((i - s0) / kSlabRows), m = (int)((i - s0) % kSlabRows);
-            const int rows = slab == td.n_slabs - 1 ? rows_last : kSlabRows;
-            for (int64_t p = csr->row_ptr[r]; p < csr->row_ptr[r + 1]; ++p) {
-                const int64_t k = pos_of_col[csr->col_idx[p]];
-                fill_dst.push_back(a_units * 8 + (k / kStepK) * stride + (int64_t)slab * kFragElems + frag_index(m, (int)(k % kStepK), rows));
-                fill_src.push_back(p);
-            }
-        }
-        for (int64_t k = 0; k < n_ks * kStepK; ++k) v->gcol.push_back(k < (int64_t)cols.size() ? cols[k] : -1);
-        for (const int32_t c : cols) pos_of_col[c] = -1;
-        a_units += n_ks * stride / 8;
-        g_ks += n_ks;
-        v->gtiles.push_back(td);
-        return VBR_OK;
-    };
-    // the slabs of a chunk of low rows as column-gathered tiles
-    auto emit_gather = [&](int64_t pn) -> int {
-        const int64_t i0 = pn * panel_rows, i1 = std::min(n_prows, i0 + panel_rows);
-        v->chunk_gather[pn] = 1;
-        v->chunk_index[pn] = (int32_t)v->gtiles.size();
-        for (int64_t s0 = i0; s0 < i1; s0 += kSlabRows) {
-            const int rc = emit_gather_tile(s0, std::min(i1, s0 + kSlabRows), -1);
-            if (rc != VBR_OK) return rc;
-        }
-        return VBR_OK;
-    };
+        std::sort(out, at);
+        if (at > out) std::fill(at, out + (int64_t)td.n_ks * kStepK, at[-1]);
+    });
+    return VBR_OK;
+}
 
-    for (int64_t pn = 0; pn < n_panels; ++pn) {
-        const int64_t i0 = pn * panel_rows, i1 = std::min(n_prows, i0 + panel_rows);
-        bool gather = !panels_on;
-        if (!gather) {
-            // loads of the two packings for this chunk (per 256 columns of C)
-            blocks.clear();
-            int64_t cost_gather = 0;
-            for (int64_t s0 = i0; s0 < i1; s0 += kSlabRows) {
-                cols.clear();
-                for (int64_t i = s0; i < std::min(i1, s0 + kSlabRows); ++i) {
-                    const int64_t r = v->prow[i];
-                    if (r < 0) continue;
-                    for (int64_t p = csr->row_ptr[r]; p < csr->row_ptr[r + 1]; ++p) {
-                        const int32_t c = csr->col_idx[p];
-                        if (pos_of_col[c] < 0) { pos_of_col[c] = 0; cols.push_back(c); }
-                        const int32_t j = c / col_block;
-                        if (pos_of_block[j] < 0) { pos_of_block[j] = 0; blocks.push_back(j); }
-                    }
-                }
-                for (const int32_t c : cols) pos_of_col[c] = -1;
-                cost_gather += (((int64_t)cols.size() + kStepK - 1) / kStepK) * kTileStepCost;
-            }
-            for (const int32_t j : blocks) pos_of_block[j] = -1;
-            const int64_t cost_panel = (((int64_t)blocks.size() * col_block + kStepK - 1) / kStepK) * kPanelStepCost;
-            gather = cost_gather < cost_panel;
-        }
-        const int rc = gather ? emit_gather(pn) : emit_panel(pn);
-        if (rc != VBR_OK) return rc;
-    }
-
-    // the tiles of the tall groups that gather single columns: their rows follow the low rows in the row list
-    v->group_gt_first.assign((size_t)std::max<int32_t>(G, 1), -1);
-    for (const int32_t g : tall_gathered) {
-        const int64_t r0 = row_groups[g], h = row_groups[g + 1] - r0;
-        const int64_t slabs = (h + kSlabRows - 1) / kSlabRows;
-        const int64_t nt = (slabs + kMaxSlabs - 1) / kMaxSlabs;
-        v->group_gt_first[g] = (int32_t)v->gtiles.size();
-        // A tile whose rows touch more than kTileMaxGatherSteps K-steps' worth of columns is cut in two
-        // (at a slab boundary; a single slab into two partial ones): fewer rows share each gathered B row,
-        // but the longest tile of a launch, one workgroup per column tile, is what the launch waits for.
-        struct Range { int64_t q0, q1; };
-        std::vector<Range> todo;
-        int64_t row = 0;
-        for (int64_t t = 0; t < nt; ++t) {
-            const int64_t s = slabs / nt + (t < slabs % nt ? 1 : 0);
-            const int64_t n_rows = std::min<int64_t>(s * kSlabRows, h - row);
-            todo.push_back(Range{r0 + row, r0 + row + n_rows});
-            row += n_rows;
-        }
-        for (size_t i = 0; i < todo.size(); ++i) {          // in row order: a cut tile is replaced by its halves in place
-            const Range rg_ = todo[i];
-            const int64_t n_rows = rg_.q1 - rg_.q0, n_slabs = (n_rows + kSlabRows - 1) / kSlabRows;
-            if (n_rows > 1) {
-                ++col_stamp_id;
-                int64_t cols_t = 0;
-                for (int64_t q = rg_.q0; q < rg_.q1; ++q)
-                    for (int64_t p = csr->row_ptr[perm[q]]; p < csr->row_ptr[perm[q] + 1]; ++p)
-                        if (col_stamp[csr->col_idx[p]] != col_stamp_id) { col_stamp[csr->col_idx[p]] = col_stamp_id; ++cols_t; }
-                if (cols_t > kTileMaxGatherSteps * kStepK) {
-                    const int64_t mid = n_slabs > 1 ? rg_.q0 + (n_slabs / 2) * kSlabRows : rg_.q0 + n_rows / 2;
-                    todo[i] = Range{rg_.q0, mid};
-                    todo.insert(todo.begin() + (int64_t)i + 1, Range{mid, rg_.q1});
-                    --i;
-                    continue;
-                }
-            }
-            const int64_t s0 = (int64_t)v->prow.size();
-            for (int64_t q = rg_.q0; q < rg_.q1; ++q) v->prow.push_back(perm[q]);
-            const int rc = emit_gather_tile(s0, s0 + n_rows, -2 - g);
-            if (rc != VBR_OK) return rc;
-        }
-    }
-
-    // pass 3: the values.  One allocation: tiles' fragments, panels' fragments, and one fragment
-    // of zeros behind the last value (loads that run past a panel's data stay inside, and the
-    // panel kernel's filler loads read it).
-    v->vals.assign((size_t)a_units * 8 + kFragElems, 0);
+// The values: one allocation, block tiles' fragments, panels' fragments, gathered tiles' fragments, and one fragment
+// of zeros behind the last value (loads that run past a panel's data stay inside, and the
+// panel kernel's filler loads read it).  Every tile clears and fills its own part.
+void Builder::fill_values()
+{
+    v->vals.allocate((size_t)a_units * 8 + kFragElems);
+    std::fill(v->vals.data() + a_units * 8, v->vals.data() + v->vals.size(), (uint16_t)0);
     const uint16_t *src = static_cast<const uint16_t *>(csr->vals);
-    for (size_t e = 0; e < fill_dst.size(); ++e) v->vals[(size_t)fill_dst[e]] = src[fill_src[e]];
-    for (int32_t g = 0; g < G; ++g) {
-        if (v->group_first_tile[g] == v->group_first_tile[g + 1]) continue;
-        for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) pos_of_block[v->blk_col[b]] = (int32_t)(b - v->blk_ptr[g]);
-        for (int64_t t = v->group_first_tile[g]; t < v->group_first_tile[g + 1]; ++t) {
-            const TileDesc &td = tiles[t];
-            const int64_t stride = tile_kstep_stride(td.n_rows, td.n_slabs);
-            const int rows_last = td.n_rows - (td.n_slabs - 1) * kSlabRows;
-            uint16_t *dst = &v->vals[(size_t)td.a_off * 8];
+    uint16_t *vals = v->vals.data();
+    for (const auto &r : panel_range) std::fill(vals + r.first * 8, vals + r.second * 8, (uint16_t)0);
+    for (size_t e = 0; e < panel_dst.size(); ++e) vals[panel_dst[e]] = src[panel_src[e]];
+    // a row of a tile: entry at place k of the tile's K dimension
+    auto place = [&](const TileDesc &td, uint16_t *dst, int64_t stride, int32_t rr, int64_t k) -> uint16_t & {
+        const int slab = rr / kSlabRows, m = rr % kSlabRows;
+        const int rows = slab == td.n_slabs - 1 ? td.n_rows - slab * kSlabRows : kSlabRows;
+        return dst[(k / kStepK) * stride + (int64_t)slab * kFragElems + frag_index(m, (int)(k % kStepK), rows)];
+    };
+    const int64_t n_block = (int64_t)tiles.size();
+    each(n_block + (int64_t)v->gtiles.size(), 1, [&](Scratch &s, int64_t i) {
+        const TileDesc &td = i < n_block ? tiles[(size_t)i] : v->gtiles[(size_t)(i - n_block)];
+        const int64_t stride = tile_kstep_stride(td.n_rows, td.n_slabs);
+        uint16_t *dst = vals + td.a_off * 8;
+        std::fill(dst, dst + td.n_ks * stride, (uint16_t)0);
+        if (i < n_block) {
+            const int64_t b0 = v->blk_ptr[td.group], b1 = v->blk_ptr[td.group + 1];
+            for (int64_t b = b0; b < b1; ++b) s.block_pos[v->blk_col[b]] = (int32_t)(b - b0);
             for (int32_t rr = 0; rr < td.n_rows; ++rr) {
                 const int64_t r = perm[td.row_begin + rr];
-                const int slab = rr / kSlabRows, m = rr % kSlabRows;
-                const int rows = slab == td.n_slabs - 1 ? rows_last : kSlabRows;
+                int64_t end = 0, shift = 0;
                 for (int64_t p = csr->row_ptr[r]; p < csr->row_ptr[r + 1]; ++p) {
                     const int64_t c = csr->col_idx[p];
-                    const int64_t k = (int64_t)pos_of_block[c / col_block] * col_block + c % col_block;
-                    dst[(k / kStepK) * stride + (int64_t)slab * kFragElems + frag_index(m, (int)(k % kStepK), rows)] = src[p];
+                    if (c >= end) {
+                        const int64_t j = c / cb;
+                        end = (j + 1) * cb;
+                        shift = ((int64_t)s.block_pos[j] - j) * cb;
+                    }
+                    place(td, dst, stride, rr, c + shift) = src[p];
                 }
             }
+            for (int64_t b = b0; b < b1; ++b) s.block_pos[v->blk_col[b]] = -1;
+        } else {
+            const int32_t *list = v->gcol.data() + (int64_t)td.ks_begin * kStepK;
+            for (int64_t k = (int64_t)td.n_ks * kStepK; k-- > 0;) s.pos[list[k]] = (int32_t)k;      // of equal ones the first
+            for (int32_t rr = 0; rr < td.n_rows; ++rr) {
+                const int64_t r = v->prow[(size_t)td.row_begin + rr];
+                if (r < 0) continue;
+                for (int64_t p = csr->row_ptr[r]; p < csr->row_ptr[r + 1]; ++p) place(td, dst, stride, rr, s.pos[csr->col_idx[p]]) = src[p];
+            }
         }
-        for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) pos_of_block[v->blk_col[b]] = -1;
-    }
-
-    // schedule: tiles grouped by slab class (one kernel instantiation each), heaviest first
-    const int64_t NT = (int64_t)tiles.size();
-    std::vector<int32_t> order(NT);
-    for (int64_t i = 0; i < NT; ++i) order[i] = (int32_t)i;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-        const int ca = slab_class(tiles[a].n_slabs), cb = slab_class(tiles[b].n_slabs);
-        if (ca != cb) return ca < cb;
-        const int64_t wa = (int64_t)tiles[a].n_ks * tiles[a].n_slabs, wb = (int64_t)tiles[b].n_ks * tiles[b].n_slabs;
-        return wa > wb;
     });
-    v->tiles.resize(NT);
-    v->tile_of_group_order.resize(NT);
+}
+
+// The tiles as the device holds them: block tiles by slab class, then gathered tiles by class (deep, 1, 2, 3 to 4
+// slabs), each class the longest first; a deep tile four times, once for every quarter of a column tile.
+void Builder::schedule()
+{
+    const int64_t NT = (int64_t)tiles.size();
+    std::vector<int32_t> order((size_t)NT);
+    for (int64_t i = 0; i < NT; ++i) order[(size_t)i] = (int32_t)i;
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+        const int ca = slab_class(tiles[a].n_slabs), cb_ = slab_class(tiles[b].n_slabs);
+        if (ca != cb_) return ca < cb_;
+        return (int64_t)tiles[a].n_ks * tiles[a].n_slabs > (int64_t)tiles[b].n_ks * tiles[b].n_slabs;
+    });
+    v->tiles.resize((size_t)NT);
+    v->tile_of_group_order.resize((size_t)NT);
     for (int c = 0; c < 5; ++c) v->class_begin[c] = 0;
     for (int64_t i = 0; i < NT; ++i) {
-        v->tiles[i] = tiles[order[i]];
-        v->tile_of_group_order[order[i]] = (int32_t)i;
-        v->class_begin[slab_class(tiles[order[i]].n_slabs) + 1]++;
+        v->tiles[(size_t)i] = tiles[(size_t)order[(size_t)i]];
+        v->tile_of_group_order[(size_t)order[(size_t)i]] = (int32_t)i;
+        v->class_begin[slab_class(v->tiles[(size_t)i].n_slabs) + 1]++;
     }
     for (int c = 0; c < 4; ++c) v->class_begin[c + 1] += v->class_begin[c];
 
-    // the gathered tiles as the device holds them: by slab class, heaviest first
-    {
-        const int64_t NG = (int64_t)v->gtiles.size();
-        std::vector<int32_t> gorder(NG);
-        for (int64_t i = 0; i < NG; ++i) gorder[i] = (int32_t)i;
-        std::stable_sort(gorder.begin(), gorder.end(), [&](int32_t a, int32_t b) {
-            const int ca = slab_class(v->gtiles[a].n_slabs), cb = slab_class(v->gtiles[b].n_slabs);
-            if (ca != cb) return ca < cb;
-            return (int64_t)v->gtiles[a].n_ks * v->gtiles[a].n_slabs > (int64_t)v->gtiles[b].n_ks * v->gtiles[b].n_slabs;
-        });
-        v->gtiles_dev.resize(NG);
-        for (int c = 0; c < 5; ++c) v->gclass_begin[c] = 0;
-        for (int64_t i = 0; i < NG; ++i) {
-            v->gtiles_dev[i] = v->gtiles[gorder[i]];
-            v->gclass_begin[slab_class(v->gtiles[gorder[i]].n_slabs) + 1]++;
+    const int64_t NG = (int64_t)v->gtiles.size();
+    std::vector<int32_t> gorder((size_t)NG);
+    for (int64_t i = 0; i < NG; ++i) gorder[(size_t)i] = (int32_t)i;
+    auto gather_class = [](const TileDesc &t) { return t.group == kTileDeep ? 0 : 1 + slab_class(t.n_slabs); };
+    std::stable_sort(gorder.begin(), gorder.end(), [&](int32_t a, int32_t b) {
+        const TileDesc &ta = v->gtiles[(size_t)a], &tb = v->gtiles[(size_t)b];
+        if (gather_class(ta) != gather_class(tb)) return gather_class(ta) < gather_class(tb);
+        return (int64_t)ta.n_ks * ta.n_slabs > (int64_t)tb.n_ks * tb.n_slabs;
+    });
+    for (int c = 0; c < 5; ++c) v->gclass_begin[c] = 0;
+    for (const int32_t i : gorder) {
+        TileDesc td = v->gtiles[(size_t)i];
+        const int c = gather_class(td);
+        for (int quarter = 0; quarter < (c == 0 ? 4 : 1); ++quarter) {
+            if (c == 0) td.group = kTileDeep - quarter;
+            v->gtiles_dev.push_back(td);
+            v->gclass_begin[c + 1]++;
         }
-        for (int c = 0; c < 4; ++c) v->gclass_begin[c + 1] += v->gclass_begin[c];
     }
+    for (int c = 0; c < 4; ++c) v->gclass_begin[c + 1] += v->gclass_begin[c];
+}
 
+void Builder::lay_out()
+{
     DeviceLayout &L = v->lay;
     L.zeros_off = 0;                   // 256 zero bytes the kernel reads for padding
     L.tiles_off = 256;
-    L.krow_off = align_up(L.tiles_off + (NT + (int64_t)v->gtiles.size()) * (int64_t)sizeof(TileDesc), 256);
+    L.krow_off = align_up(L.tiles_off + (int64_t)(v->tiles.size() + v->gtiles_dev.size()) * (int64_t)sizeof(TileDesc), 256);
     L.perm_off = align_up(L.krow_off + (int64_t)v->krow.size() * 4, 256);
     L.panels_off = align_up(L.perm_off + M * 4, 256);
     L.pk_meta_off = align_up(L.panels_off + (int64_t)v->panels.size() * (int64_t)sizeof(PanelDesc), 256);
@@ -566,7 +857,6 @@ int build_impl(const vbr_csr_t *csr, const int32_t *perm, const int32_t *row_gro
     L.gcol_off = align_up(L.prow_off + (int64_t)v->prow.size() * 4, 256);
     L.vals_off = align_up(L.gcol_off + (int64_t)v->gcol.size() * 4, 256);
     L.total = std::max<int64_t>(256, align_up(L.vals_off + (int64_t)v->vals.size() * 2, 256));
-    return VBR_OK;
 }
 
 }  // namespace
@@ -592,10 +882,10 @@ extern "C" int vbr_build(const vbr_csr_t *csr, const int32_t *perm, const int32_
             if (perm[i] < 0 || perm[i] >= M || seen[perm[i]]) return VBR_EINVAL;   // not a bijection
             seen[perm[i]] = 1;
         }
-        vbr *v = new vbr();
-        rc = vbrk::build_impl(csr, perm, row_groups, n_groups, col_block, v);
-        if (rc != VBR_OK) { delete v; return rc; }
-        *out = v;
+        std::unique_ptr<vbr> v(new vbr());
+        rc = vbrk::Builder(csr, perm, row_groups, n_groups, col_block, v.get()).build();
+        if (rc != VBR_OK) return rc;
+        *out = v.release();
         return VBR_OK;
     } catch (const std::bad_alloc &) {
         return VBR_ENOMEM;
@@ -628,71 +918,42 @@ extern "C" int vbr_unpack_block(const vbr_t *v, int64_t blk, void *dst_)
     const int64_t pos = blk - v->blk_ptr[g];
     const int64_t cb = v->col_block;
     uint16_t *dst = static_cast<uint16_t *>(dst_);
-    if (v->group_prow[g] >= 0) {
-        // low group: its rows sit in one chunk of the low rows (or two), packed as a panel or as
-        // column-gathered tiles
+    if (v->group_first_tile[g] == v->group_first_tile[g + 1]) {
+        // the rows of the group sit in the row list, each in a slab of a panel or of a column-gathered tile
         const int64_t h = v->row_groups[g + 1] - v->row_groups[g];
-        const int R = v->panel_slabs;
-        const int64_t panel_rows = (int64_t)R * kSlabRows;
         for (int64_t i = 0; i < h; ++i) {
-            const int64_t pi = v->group_prow[g] + i;
-            const int64_t pn = pi / panel_rows;
-            if (v->chunk_gather[pn]) {
-                // the slab's column list is ascending up to its padding: look every column of the block up
-                const TileDesc &td = v->gtiles[v->chunk_index[pn] + (pi - pn * panel_rows) / kSlabRows];
-                const int m = (int)(pi - td.row_begin);
-                const int32_t *cb0 = &v->gcol[(size_t)td.ks_begin * kStepK], *ce = cb0 + (size_t)td.n_ks * kStepK;
-                while (ce > cb0 && ce[-1] < 0) --ce;
-                const int64_t stride = tile_kstep_stride(td.n_rows, 1);
+            const int64_t pi = v->row_pos[(size_t)(v->row_groups[g] + i)], t = v->slab_tile[(size_t)(pi / kSlabRows)];
+            if (t >= 0) {
+                // the tile's column list rises, its last column may repeat: look every column of the block up
+                const TileDesc &td = v->gtiles[(size_t)t];
+                const int slab = (int)((pi - td.row_begin) / kSlabRows), m = (int)((pi - td.row_begin) % kSlabRows);
+                const int rows = slab == td.n_slabs - 1 ? td.n_rows - slab * kSlabRows : kSlabRows;
+                const int32_t *cb0 = v->gcol.data() + (int64_t)td.ks_begin * kStepK, *ce = cb0 + (int64_t)td.n_ks * kStepK;
+                const int64_t stride = tile_kstep_stride(td.n_rows, td.n_slabs);
                 for (int64_t c = 0; c < cb; ++c) {
                     const int32_t col = (int32_t)((int64_t)v->blk_col[blk] * cb + c);
                     const int32_t *it = std::lower_bound(cb0, ce, col);
                     if (it == ce || *it != col) { dst[i * cb + c] = 0; continue; }      // fill-in: not stored
                     const int64_t k = it - cb0;
-                    dst[i * cb + c] = v->vals[(size_t)td.a_off * 8 + (size_t)((k / kStepK) * stride) + frag_index(m, (int)(k % kStepK), td.n_rows)];
+                    dst[i * cb + c] = v->vals[(size_t)td.a_off * 8 + (size_t)((k / kStepK) * stride) + (size_t)slab * kFragElems + frag_index(m, (int)(k % kStepK), rows)];
                 }
                 continue;
             }
-            const int64_t pidx = v->chunk_index[pn];
+            const int64_t pidx = v->chunk_panel[(size_t)(pi / ((int64_t)v->panel_slabs * kSlabRows))];
             const PanelDesc &pd = v->panels[pidx];
             const int s = (int)((pi - pd.row_begin) / kSlabRows), m = (int)((pi - pd.row_begin) % kSlabRows);
             const int32_t *ub = &v->p_union[v->p_union_ptr[pidx]], *ue = &v->p_union[0] + v->p_union_ptr[pidx + 1];
             const int64_t u = std::lower_bound(ub, ue, v->blk_col[blk]) - ub;
             for (int64_t c = 0; c < cb; ++c) {
                 const int64_t k = u * cb + c;
-                const int32_t t = (int32_t)(k / kStepK);
-                // physical steps of logical step t are consecutive; take the one that carries slab s
+                const int32_t t32 = (int32_t)(k / kStepK);
+                // physical steps of a logical step are consecutive; take the one that carries slab s
                 const int32_t *lb = &v->pk_logical[pd.ks_begin], *le = lb + pd.n_ks;
-                int64_t ph = pd.ks_begin + (std::lower_bound(lb, le, t) - lb);
+                int64_t ph = pd.ks_begin + (std::lower_bound(lb, le, t32) - lb);
                 while (!(v->pk_mask[ph] >> s & 1)) ++ph;
                 const int rank = __builtin_popcount(v->pk_mask[ph] & ((1u << s) - 1u));
                 dst[i * cb + c] = v->vals[(size_t)pd.a_off * 8 + (size_t)(v->pk_frag[ph] + rank) * kFragElems +
                                           frag_index(m, (int)(k % kStepK), kSlabRows)];
-            }
-        }
-        return VBR_OK;
-    }
-    if (v->group_gt_first[g] >= 0) {
-        // tall group whose tiles gather single columns: the tiles follow each other, each with its own column list
-        const int64_t h = v->row_groups[g + 1] - v->row_groups[g];
-        int64_t row = 0;
-        for (int64_t t = v->group_gt_first[g]; row < h; ++t) {
-            const TileDesc &td = v->gtiles[t];
-            const int32_t *cb0 = &v->gcol[(size_t)td.ks_begin * kStepK], *ce = cb0 + (size_t)td.n_ks * kStepK;
-            while (ce > cb0 && ce[-1] < 0) --ce;
-            const int64_t stride = tile_kstep_stride(td.n_rows, td.n_slabs);
-            const int rows_last = td.n_rows - (td.n_slabs - 1) * kSlabRows;
-            for (int32_t rr = 0; rr < td.n_rows; ++rr, ++row) {
-                const int slab = rr / kSlabRows, m = rr % kSlabRows;
-                const int rows = slab == td.n_slabs - 1 ? rows_last : kSlabRows;
-                for (int64_t c = 0; c < cb; ++c) {
-                    const int32_t col = (int32_t)((int64_t)v->blk_col[blk] * cb + c);
-                    const int32_t *it = std::lower_bound(cb0, ce, col);
-                    if (it == ce || *it != col) { dst[row * cb + c] = 0; continue; }          // fill-in: not stored
-                    const int64_t k = it - cb0;
-                    dst[row * cb + c] = v->vals[(size_t)td.a_off * 8 + (size_t)((k / kStepK) * stride) + (size_t)slab * kFragElems +
-                                                frag_index(m, (int)(k % kStepK), rows)];
-                }
             }
         }
         return VBR_OK;
@@ -774,21 +1035,23 @@ extern "C" int vbr_audit(const vbr_t *v)
     }
     if ((int64_t)v->gcol.size() % kStepK != 0) return VBR_EINVAL;
     for (const int32_t c : v->gcol)
-        if (c < -1 || c >= K) return VBR_EINVAL;
-    if (v->gtiles_dev.size() != v->gtiles.size() || v->gclass_begin[0] != 0 || v->gclass_begin[4] != (int32_t)v->gtiles.size()) return VBR_EINVAL;
-    for (int c = 0; c < 4; ++c)
-        for (int32_t t = v->gclass_begin[c]; t < v->gclass_begin[c + 1]; ++t)
-            if (slab_class(v->gtiles_dev[t].n_slabs) != c) return VBR_EINVAL;
-    for (const TileDesc &td : v->gtiles_dev) {
-        if (td.n_rows < 1 || td.n_slabs != (td.n_rows + kSlabRows - 1) / kSlabRows || td.n_slabs > kMaxSlabs || td.group >= 0) return VBR_EINVAL;
-        if (td.row_begin < 0 || (int64_t)td.row_begin + td.n_rows > (int64_t)v->prow.size()) return VBR_EINVAL;
-        if (td.n_ks < 0 || td.ks_begin < 0 || ((int64_t)td.ks_begin + td.n_ks) * kStepK > (int64_t)v->gcol.size()) return VBR_EINVAL;
-        if (td.a_off < 0 || td.a_off * 8 + (int64_t)td.n_ks * tile_kstep_stride(td.n_rows, td.n_slabs) > n_vals - kFragElems) return VBR_EINVAL;
+        if (c < 0 || c >= K) return VBR_EINVAL;
+    if (v->gclass_begin[0] != 0 || v->gclass_begin[4] != (int32_t)v->gtiles_dev.size()) return VBR_EINVAL;
+    for (int c = 0; c < 4; ++c) {
+        if (v->gclass_begin[c + 1] < v->gclass_begin[c]) return VBR_EINVAL;
+        for (int32_t t = v->gclass_begin[c]; t < v->gclass_begin[c + 1]; ++t) {
+            const TileDesc &td = v->gtiles_dev[(size_t)t];
+            if (c == 0 ? td.group > kTileDeep || td.group <= kTileDeep - 4 || td.n_slabs > kMaxDeepSlabs : td.group != kTileGathered || slab_class(td.n_slabs) != c - 1) return VBR_EINVAL;
+            if (td.n_rows < 1 || td.n_slabs != (td.n_rows + kSlabRows - 1) / kSlabRows || td.n_slabs > kMaxGatherSlabs) return VBR_EINVAL;
+            if (td.row_begin < 0 || (int64_t)td.row_begin + td.n_rows > (int64_t)v->prow.size()) return VBR_EINVAL;
+            if (td.n_ks < 0 || td.ks_begin < 0 || ((int64_t)td.ks_begin + td.n_ks) * kStepK > (int64_t)v->gcol.size()) return VBR_EINVAL;
+            if (td.a_off < 0 || td.a_off * 8 + (int64_t)td.n_ks * tile_kstep_stride(td.n_rows, td.n_slabs) > n_vals - kFragElems) return VBR_EINVAL;
+        }
     }
     for (size_t i = v->vals.size() - kFragElems; i < v->vals.size(); ++i)
         if (v->vals[i] != 0) return VBR_EINVAL;                                               // the zero fragment
     const DeviceLayout &L = v->lay;
-    const int64_t ends[9] = {L.zeros_off + 256, L.tiles_off + (int64_t)(v->tiles.size() + v->gtiles.size()) * (int64_t)sizeof(TileDesc),
+    const int64_t ends[9] = {L.zeros_off + 256, L.tiles_off + (int64_t)(v->tiles.size() + v->gtiles_dev.size()) * (int64_t)sizeof(TileDesc),
                               L.krow_off + (int64_t)v->krow.size() * 4, L.perm_off + M * 4,
                               L.panels_off + (int64_t)v->panels.size() * (int64_t)sizeof(PanelDesc),
                               L.pk_meta_off + (int64_t)v->pk_meta.size() * 4, L.prow_off + (int64_t)v->prow.size() * 4,
@@ -815,32 +1078,36 @@ static int64_t grid_size(int64_t T, int64_t Q)
 }
 
 // The panels first (they are the long-running workgroups), then either one mixed launch (several
-// slab classes, none of which alone gives every CU a couple of workgroups) or one launch per slab
-// class present.
+// classes, none of which alone gives every CU a couple of workgroups) or: the deep tiles, the other gathered tiles,
+// and one launch per class of block tiles present.
 int plan_launches(const vbr *v, int64_t N, Launch out[VBR_MAX_LAUNCHES])
 {
     int n = 0;
     const int64_t Qt = (N + kTileN - 1) / kTileN, Qp = (N + kPanelN - 1) / kPanelN;
     if (!v->panels.empty())
         out[n++] = Launch{VBR_LAUNCH_PANEL, 0, (int32_t)v->panels.size(), grid_size((int64_t)v->panels.size(), Qp)};
-    // Eight tile classes, contiguous in the device's tile array: tiles of 1, 2, 3-4, 5-8 slabs that
-    // gather whole column blocks, then the same four of tiles that gather single columns.  Several
-    // classes that together do not give every CU a few workgroups share one launch of the mixed
-    // kernel; otherwise every class present gets a launch of its own kernel, the gathered ones first.
-    // (Mixing only the small classes of a large matrix was measured and lost: the mixed kernel holds
-    // the LDS of the tallest class, and the tall tiles of the graph workload, few but with long block
-    // lists, ran 20 % longer in it.)
+    // Eight tile classes, contiguous in the device's tile array: block tiles of 1, 2, 3-4, 5-8 slabs, then gathered
+    // tiles: deep, 1, 2, 3-4 slabs.  Several classes that together do not give every CU a few workgroups share one
+    // launch of the mixed kernel.  Otherwise the deep tiles go first, in a launch of their own, the other gathered
+    // tiles share one if they are of several heights (the kernel for up to 4 slabs keeps three workgroups on a CU),
+    // and every class of block tiles has its own.  (Mixing only the small classes of block tiles of a large matrix was
+    // measured and lost: the mixed kernel holds the LDS of the tallest class.)
     const int32_t T_blk = v->class_begin[4];
-    int classes = 0;
-    for (int c = 0; c < 4; ++c) classes += (v->class_begin[c + 1] > v->class_begin[c]) + (v->gclass_begin[c + 1] > v->gclass_begin[c]);
-    const int64_t T_all = (int64_t)T_blk + v->gclass_begin[4];
-    if (classes > 1 && T_all * Qt < 4096) {
+    const int32_t *gb = v->gclass_begin;
+    int classes = 0, gathered = 0;
+    for (int c = 0; c < 4; ++c) classes += (v->class_begin[c + 1] > v->class_begin[c]) + (gb[c + 1] > gb[c]);
+    for (int c = 1; c < 4; ++c) gathered += gb[c + 1] > gb[c];
+    const int64_t T_all = (int64_t)T_blk + gb[4];
+    if (classes > 1 && T_all * Qt < kMixedMaxWorkgroups) {
         out[n++] = Launch{VBR_LAUNCH_TILE_MIXED, 0, (int32_t)T_all, grid_size(T_all, Qt)};
         return n;
     }
-    for (int c = 0; c < 4; ++c) {
-        const int32_t T = v->gclass_begin[c + 1] - v->gclass_begin[c];
-        if (T > 0) out[n++] = Launch{VBR_LAUNCH_GATHER_1 + c, T_blk + v->gclass_begin[c], T, grid_size(T, Qt)};
+    if (gb[1] > gb[0]) out[n++] = Launch{VBR_LAUNCH_GATHER_DEEP, T_blk, gb[1], grid_size(gb[1], Qt)};
+    if (gathered > 1) {
+        out[n++] = Launch{VBR_LAUNCH_GATHER_MIXED, T_blk + gb[1], gb[4] - gb[1], grid_size(gb[4] - gb[1], Qt)};
+    } else {
+        for (int c = 1; c < 4; ++c)
+            if (gb[c + 1] > gb[c]) out[n++] = Launch{VBR_LAUNCH_GATHER_1 + c - 1, T_blk + gb[c], gb[c + 1] - gb[c], grid_size(gb[c + 1] - gb[c], Qt)};
     }
     for (int c = 0; c < 4; ++c) {
         const int32_t T = v->class_begin[c + 1] - v->class_begin[c];

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <cstdint>
+#include <memory>
 #include <vector>
 
 #include "vbr_spmm.h"
@@ -14,6 +15,8 @@ constexpr int kSlabRows = 16;       // rows of one MFMA slab
 constexpr int kStepK = 32;          // B rows consumed per K-step (one 16x16x32 MFMA deep)
 constexpr int kMaxSlabs = 8;        // slabs per workgroup tile (128 rows)
 constexpr int kFragElems = kSlabRows * kStepK;   // 512 16-bit values = 1 KiB per (slab, K-step)
+constexpr int kMaxGatherSlabs = 4;  // slabs per column-gathered tile (64 rows) ...
+constexpr int kMaxDeepSlabs = 2;    // ... and per deep one (32 rows)
 constexpr int kTileN = 256;         // C columns per workgroup of the tile kernel
 constexpr int kPanelN = 128;        // C columns per workgroup of the panel kernel
 constexpr int kXcd = 8;             // L2 domains; workgroup i runs on domain i % 8
@@ -26,8 +29,10 @@ struct TileDesc {
     int32_t row_begin;   // position in perm of the tile's first row
     int32_t n_rows;      // rows of the tile, 1 .. 16 * n_slabs
     int32_t n_slabs;     // ceil(n_rows / 16)
-    int32_t group;       // row group the tile belongs to
+    int32_t group;       // row group the tile belongs to; column-gathered tiles: kTileGathered, or kTileDeep less the quarter
+                         // of a 256-column tile (0 .. 3) a workgroup takes
 };
+constexpr int32_t kTileGathered = -1, kTileDeep = -2;
 static_assert(sizeof(TileDesc) == 32, "TileDesc is read by the kernel as 2 x 16 bytes");
 
 // Position inside a (slab, K-step) fragment of the value at slab row m and K-step-local column
@@ -77,6 +82,20 @@ struct DeviceLayout {
     int64_t gcol_off = 0;      // (the column-gathered tiles follow the other tiles in the tiles section)
 };
 
+// The packed values on the host: not cleared when allocated, every tile writes its own part.
+class HostValues {
+public:
+    void allocate(size_t n) { p_.reset(new uint16_t[n]); n_ = n; }
+    uint16_t *data() { return p_.get(); }
+    const uint16_t *data() const { return p_.get(); }
+    size_t size() const { return n_; }
+    const uint16_t &operator[](size_t i) const { return p_[i]; }
+
+private:
+    std::unique_ptr<uint16_t[]> p_;
+    size_t n_ = 0;
+};
+
 }  // namespace vbrk
 
 struct vbr {
@@ -95,22 +114,22 @@ struct vbr {
     int32_t class_begin[5] = {0, 0, 0, 0, 0};  // tiles of slab class c (1,2,4,8 slabs) are [class_begin[c], class_begin[c+1])
     std::vector<int64_t> group_first_tile;      // [n_groups+1] tiles of a group in creation order (for unpack)
     std::vector<int32_t> tile_of_group_order;   // creation order -> index in `tiles`
-    std::vector<uint16_t> vals;          // packed fragments: tiles first, then panels, then 1 KiB of zeros
-    // Rows of groups of height < 16 ("low rows") are collected in permuted order (prow) and cut into
-    // chunks of 128 rows = 8 slabs.  A chunk is packed either as ONE PANEL (its slabs share the B rows
-    // of the union of their column blocks) or as 8 COLUMN-GATHERED TILES (each slab gathers exactly
-    // the B rows of the columns its own rows touch), whichever needs fewer loads.
+    vbrk::HostValues vals;               // packed fragments: block tiles, panels, gathered tiles, then 1 KiB of zeros
+    // Rows that are not multiplied in block tiles stand in a row list (prow): first those of groups of height < 16
+    // ("low rows"), in an order of the packing's own, then those of taller groups whose blocks are mostly fill-in.
+    // The list is cut into slabs of 16 positions.  A chunk of 8 slabs of low rows may be packed as ONE PANEL (its
+    // slabs share the B rows of the union of their column blocks); all other slabs form COLUMN-GATHERED TILES of 1
+    // to 4 slabs, which gather exactly the B rows of the columns their own rows touch.
     int32_t panel_slabs = 0;             // slabs per chunk (8); 0 = the matrix has no low rows
-    std::vector<int32_t> prow;           // original row of every low row, in permuted order
-    std::vector<int32_t> group_prow;     // [n_groups] first low-row position of a low group, -1 for the others
-    std::vector<uint8_t> chunk_gather;   // [n_chunks] 1 = packed as column-gathered tiles, 0 = as a panel
-    std::vector<int32_t> chunk_index;    // [n_chunks] index of its panel in `panels`, or of its first tile in `gtiles`
-    std::vector<vbrk::TileDesc> gtiles;   // column-gathered tiles in creation order: row_begin = position in prow; group = -1 for
-                                         // a slab of low rows, -2 - g for a tile of the tall group g (1 .. 8 slabs)
-    std::vector<vbrk::TileDesc> gtiles_dev;      // the same tiles as the device holds them: by slab class, heaviest first
-    int32_t gclass_begin[5] = {0, 0, 0, 0, 0};   // gathered tiles of slab class c are gtiles_dev[gclass_begin[c] .. gclass_begin[c+1])
-    std::vector<int32_t> group_gt_first;         // [n_groups] first gathered tile of a tall group packed that way, -1 otherwise
-    std::vector<int32_t> gcol;           // per K-step of a gathered tile 32 columns of A (= rows of B), ascending, -1 = padding
+    int32_t deep_steps = 0;              // K-steps from which on a gathered tile is split over K (a "deep" tile)
+    std::vector<int32_t> prow;           // original row of every position of the row list, -1 = padding
+    std::vector<int32_t> row_pos;        // [n_rows] position in the row list of every position in perm, -1 = block tile
+    std::vector<int32_t> chunk_panel;    // [n_chunks] index of its panel in `panels`, -1 = gathered tiles
+    std::vector<int32_t> slab_tile;      // [n_slabs] index in `gtiles` of the slab's tile, -1 = in a panel
+    std::vector<vbrk::TileDesc> gtiles;   // column-gathered tiles in creation order: row_begin = position in prow
+    std::vector<vbrk::TileDesc> gtiles_dev;      // the same tiles as the device holds them: by class, longest first, deep ones four times
+    int32_t gclass_begin[5] = {0, 0, 0, 0, 0};   // deep tiles, tiles of 1, 2, 3-4 slabs: class c is gtiles_dev[gclass_begin[c] .. gclass_begin[c+1])
+    std::vector<int32_t> gcol;           // per K-step of a gathered tile 32 columns of A (= rows of B), rising, the last column repeated to the end
     std::vector<vbrk::PanelDesc> panels;
     std::vector<int32_t> pk_row;         // host only: first B row of each granule of each physical K-step, -1 = padding
     std::vector<uint32_t> pk_mask;       // host only: slabs present in each physical K-step

@@ -39,6 +39,7 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4v *lds_short4_ptr;
 typedef __attribute__((address_space(3))) short8v *lds_short8_ptr;
 typedef __attribute__((address_space(3))) float4v *lds_float4_ptr;
+typedef __attribute__((address_space(3))) int32_t *lds_i32_ptr;
 typedef __attribute__((address_space(3))) unsigned char *lds_u8_ptr;
 typedef __attribute__((address_space(4))) const int32_t *const_i32_ptr;
 
@@ -48,10 +49,9 @@ struct Params {
     const int32_t *perm;
     const int32_t *gcol;      // column-gathered tiles: their column lists ...
     const int32_t *prow;      // ... and the list of the low rows their row positions refer to
-    int32_t b_fits32;         // the rows of B the matrix can touch span less than 4 GiB: 32-bit offsets from B suffice
+    int32_t b_fits24;         // the rows of B the matrix can touch span less than 4 GiB, their number and length in bytes less than 2^24
     const uint16_t *vals;
     const uint16_t *zeros;    // 256 zero bytes: source of padding rows, padding lanes and columns >= N
-    const uint16_t *zfrag;    // 1 KiB of zeros behind the last fragment: padding rows of the column-gathered tiles
     const uint16_t *B;
     float *C;
     int64_t ldb, ldc;
@@ -90,6 +90,13 @@ __device__ __forceinline__ void dma16_base(uint32_t voff, const void *base, uint
                  "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_base)) : "memory");
 }
 
+// 4 bytes per active lane into LDS: lane l's at lds_base + 4 l
+__device__ __forceinline__ void dma4(const void *gptr, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(gptr),
+                 "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_base)) : "memory");
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt()
 {
@@ -119,8 +126,10 @@ __device__ __forceinline__ bool map_workgroup(int T, int Q, int &tile, int &ntil
     return tile < T;
 }
 
+constexpr int kListSteps = 8;                     // K-steps whose column lists a wave of a gathered tile requests with one load
+constexpr int kListBytes = 2 * 4 * kListSteps * 8 * 4;   // two such lists for each of the 4 waves, 8 columns per K-step
 template <int S, int NS, int DA>
-constexpr int tile_lds_bytes() { return NS * kPanelBytes + (DA + 1) * S * kFragBytes; }
+constexpr int tile_lds_bytes(bool gather = false) { return NS * kPanelBytes + (DA + 1) * S * kFragBytes + (gather ? kListBytes : 0); }
 
 // GATHER: the tile is a slab of rows of low row groups whose K dimension is the list of the single
 // COLUMNS its rows touch (one gather entry per B row, krow = that list) instead of whole column
@@ -143,7 +152,6 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
     const lds_u8_ptr sm = (lds_u8_ptr)smem;
     const uint32_t smem_base = (uint32_t)(uintptr_t)sm;      // LDS byte address, for M0
     const char *zeros = reinterpret_cast<const char *>(p.zeros);
-    const char *zpad = reinterpret_cast<const char *>(p.zfrag);
     const int n_ks = td.n_ks;
     const int q = lane >> 4, s16 = lane & 15;
 
@@ -216,49 +224,41 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
         // K-step whose B loads are issued next (rb0) and the one after (rb1): scalar loads, issued
         // two iterations ahead of their use.  Narrower blocks look their rows up per lane at issue
         // time instead, with an ordinary load the compiler waits for (slow, but rare and simple).
-        // Column-gathered tiles: the 8 B rows of the wave, one list entry each, as 8 scalars.
-        struct Rows { int r[GATHER ? 8 : 1]; };
-        Rows rb0, rb1;
-        rb0.r[0] = rb1.r[0] = -1;
-        auto load_rows = [&](int ks) -> Rows {
+        int32_t rb0 = -1, rb1 = -1;
+        auto load_rows = [&](int ks) -> int32_t {
             // past the end: reload the last K-step (never computed); wave-uniform, and said so, or the
             // lookups below become vector loads, which cost the load path as much as a load of B
             const int kc = __builtin_amdgcn_readfirstlane(ks < n_ks ? ks : n_ks - 1);
-            Rows out;
-            if constexpr (GATHER) {
-                const const_i32_ptr src = (const_i32_ptr)p.gcol + ((int64_t)td.ks_begin + kc) * kStepK + 8 * wave;
+            return lg >= 3 ? krow[(kc * kStepK + 8 * wave) >> lg] : -1;
+        };
+        // Column-gathered tiles: the wave's 8 columns of a K-step lie in LDS, fetched by the wave itself for 8 K-steps with
+        // one load (scalar loads of them, one per K-step, missed the scalar cache every time and were waited for in
+        // every K-step: what each lane needs for the K-step after next is read one K-step ahead instead).
+        int32_t ent[4] = {-1, -1, -1, -1};
+        const lds_u8_ptr lists = sm + kBRing + NAS * kAStage + wave * (kListBytes / 4);
+        auto issue_list = [&](int batch) {
+            const int k = batch * kListSteps + (lane >> 3);
+            dma4(p.gcol + ((int64_t)td.ks_begin + (k < n_ks ? k : n_ks - 1)) * kStepK + 8 * wave + (lane & 7),
+                 smem_base + kBRing + NAS * kAStage + wave * (kListBytes / 4) + (batch & 1) * (kListBytes / 8));
+        };
+        auto read_list = [&](int ks) {
+            const lds_u8_ptr at = lists + (ks & (2 * kListSteps - 1)) * 32 + half * 4;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) out.r[j] = src[j];
-            } else {
-                out.r[0] = lg >= 3 ? krow[(kc * kStepK + 8 * wave) >> lg] : -1;
-            }
-            return out;
+            for (int i = 0; i < 4; ++i) ent[i] = *(lds_i32_ptr)(at + i * 8);
         };
         auto issue_b = [&](int ks, int slot) {
             const uint32_t sb = smem_base + slot * kPanelBytes + 8 * wave * kRowBytes;
             if constexpr (GATHER) {
-                // the two row pointers of a load are computed on the scalar unit (a padding entry points
-                // at the kilobyte of zeros behind the values); a lane only selects its half's pointer and
-                // adds its column offset
-                if (p.b_fits32 && rb0.r[7] >= 0) {
-                    // all of B lies within 4 GiB and none of the wave's 8 entries is padding (the list
-                    // ascends, padding trails): scalar base + 32-bit lane offsets, the cheaper form of the load
+                // (behind the last column of the tile the list repeats it: the fragments hold zeros there)
+                if (p.b_fits24) {        // scalar base + 32-bit lane offsets, the cheaper form of the load
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint32_t o0 = (uint32_t)rb0.r[2 * i] * ldb_bytes, o1 = (uint32_t)rb0.r[2 * i + 1] * ldb_bytes;
-                        dma16_base((half ? o1 : o0) + b_coff[i], Btile, sb + 2 * i * kRowBytes);
-                    }
+                    for (int i = 0; i < 4; ++i) dma16_base(__umul24((uint32_t)ent[i], ldb_bytes) + b_coff[i], Btile, sb + 2 * i * kRowBytes);
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int e0 = rb0.r[2 * i], e1 = rb0.r[2 * i + 1];
-                        const char *p0 = e0 >= 0 ? Btile + (uint64_t)(uint32_t)e0 * ldb_bytes : zpad;
-                        const char *p1 = e1 >= 0 ? Btile + (uint64_t)(uint32_t)e1 * ldb_bytes : zpad;
-                        dma16((half ? p1 : p0) + b_coff[i], sb + 2 * i * kRowBytes);
-                    }
+                    for (int i = 0; i < 4; ++i) dma16(Btile + (uint64_t)(uint32_t)ent[i] * ldb_bytes + b_coff[i], sb + 2 * i * kRowBytes);
                 }
-            } else if (tile_fast && rb0.r[0] >= 0) {
-                const char *rowptr = Btile + (uint64_t)(uint32_t)rb0.r[0] * ldb_bytes;          // scalar, 64-bit
+            } else if (tile_fast && rb0 >= 0) {
+                const char *rowptr = Btile + (uint64_t)(uint32_t)rb0 * ldb_bytes;          // scalar, 64-bit
 #pragma unroll
                 for (int i = 0; i < 4; ++i) dma16_base(b_lane[i], rowptr, sb + 2 * i * kRowBytes);
             } else {         // narrow blocks, padding rows or column tail: zeros come from the zero page
@@ -266,7 +266,7 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r = 8 * wave + 2 * i + half;
-                    const int e = lg >= 3 ? rb0.r[0] : p.krow[(int64_t)td.ks_begin * (kStepK >> lg) + ((kc * kStepK + r) >> lg)];
+                    const int e = lg >= 3 ? rb0 : p.krow[(int64_t)td.ks_begin * (kStepK >> lg) + ((kc * kStepK + r) >> lg)];
                     const char *src = (e >= 0 && b_col_ok[i]) ? Btile + (int64_t)(e + (r & gmask)) * ldb_bytes + b_col[i] : zeros;
                     dma16(src, sb + 2 * i * kRowBytes);
                 }
@@ -339,15 +339,28 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
         // iterations early: A(0 .. DA-NS), then B(t), A(DA-NS+1+t) for t = 0 .. NS-2; iteration ks
         // then issues B(ks+NS-1), A(ks+DA).  The prologue re-loads the last K-step for K-steps past the
         // end of a very short tile, so that the loop always starts with the same loads in flight.
-        rb0 = load_rows(0);
-        rb1 = load_rows(1);
+        if constexpr (GATHER) {
+            issue_list(0);
+            if (n_ks > kListSteps) issue_list(1);
+        } else {
+            rb0 = load_rows(0);
+            rb1 = load_rows(1);
+        }
 #pragma unroll
         for (int k = 0; k <= DA - NS; ++k) issue_a(k, k);
+        if constexpr (GATHER) {
+            wait_vmcnt<0>();
+            read_list(0);
+        }
 #pragma unroll
         for (int t = 0; t < NS - 1; ++t) {
             issue_b(t, t);
-            rb0 = rb1;
-            rb1 = load_rows(t + 2);
+            if constexpr (GATHER) {
+                read_list(t + 1);
+            } else {
+                rb0 = rb1;
+                rb1 = load_rows(t + 2);
+            }
             issue_a(DA - NS + 1 + t, DA - NS + 1 + t);
         }
         int bslot = 0, aslot = 0;
@@ -358,17 +371,26 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
             if (ks + DA > n_ks) wait_vmcnt<0>();
             else wait_stage(ks);                   // this wave's loads of K-step ks have landed
             __builtin_amdgcn_s_barrier();          // ... and everybody else's; the slots of K-step ks-1 are free
-            asm volatile("" ::"s"(rb0.r[0]));      // the scalar row lookup is waited for here, not behind the LDS reads
+            if constexpr (!GATHER) asm volatile("" ::"s"(rb0));      // the scalar row lookup is waited for here, not behind the LDS reads
             read_frags(bslot, aslot);
             // the load path is what bounds the kernel: a wave that is about to issue its loads goes
             // ahead of the waves that are multiplying (measured: 3-4 % on the 16-row workload)
             __builtin_amdgcn_s_setprio(3);
             if (ks + NS - 1 < n_ks) issue_b(ks + NS - 1, bslot == 0 ? NS - 1 : bslot - 1);
             if (ks + DA < n_ks) issue_a(ks + DA, aslot == 0 ? NAS - 1 : aslot - 1);
+            if constexpr (GATHER) {
+                // the next list but one, into the place of the one whose last K-step has been read (an extra load in
+                // flight only makes the counted waits stricter)
+                const int next = ks + NS;
+                if ((next & (kListSteps - 1)) == 1 && (next / kListSteps + 1) * kListSteps < n_ks) issue_list(next / kListSteps + 1);
+                read_list(next);
+            }
             __builtin_amdgcn_s_setprio(0);
             multiply();
-            rb0 = rb1;
-            rb1 = load_rows(ks + NS + 1);
+            if constexpr (!GATHER) {
+                rb0 = rb1;
+                rb1 = load_rows(ks + NS + 1);
+            }
             bslot = bslot == NS - 1 ? 0 : bslot + 1;
             aslot = aslot == NAS - 1 ? 0 : aslot + 1;
         }
@@ -387,7 +409,7 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
         const int rr = s * kSlabRows + s16;
         orig[s] = rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
     }
-    if (n_ks > 0) __builtin_amdgcn_s_barrier();     // the rings are read no more
+    if (n_ks > 0) __syncthreads();                  // the rings are read no more
     constexpr int kOutRow = kWaveN * 4 + 16;
     static_assert(4 * kSlabRows * kOutRow <= tile_lds_bytes<S, NS, DA>(), "the turned slabs of the four waves fit the rings");
     const lds_u8_ptr out = sm + wave * kSlabRows * kOutRow;
@@ -406,36 +428,200 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
     }
 }
 
+constexpr int kDeepN = 64;                        // C columns per workgroup of a deep tile
+constexpr int kDeepRow = kDeepN * 2;              // one staged B row: 128 bytes
+constexpr int kDeepList = kStepK * 4;             // the list entries of a K-step
+constexpr int kDeepSlots = 2;
+template <int S>
+constexpr int deep_wave_bytes() { return kDeepSlots * (kStepK * kDeepRow + S * kFragBytes + kDeepList); }
+
+// A deep tile: a gathered tile of one or two slabs whose column list is so long that a workgroup of the tile kernel, which
+// takes the K-steps one after the other, would still be at it when the rest of the launch is done (a hub of a graph:
+// thousands of columns, 0.3 us per K-step).  Here a workgroup owns 64 columns of C and its four waves take the
+// K-steps in turn, each with an LDS ring of its own and without a barrier; the four partial sums are added in LDS, in
+// a fixed order.  The price is S fragments per 64 columns instead of per 256: 24 loads per K-step for two slabs
+// instead of 18.
+template <int DT, int S>
+__device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, const int n0, unsigned char *smem)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (n0 >= p.N) return;
+    const lds_u8_ptr sm = (lds_u8_ptr)smem;
+    const int q = lane >> 4, s16 = lane & 15;
+    constexpr int kB = kStepK * kDeepRow, kA = S * kFragBytes;
+    const lds_u8_ptr mine = sm + wave * deep_wave_bytes<S>();
+    const uint32_t base = (uint32_t)(uintptr_t)mine;             // [B slots][A slots][list slots]
+    const lds_u8_ptr lists = mine + kDeepSlots * (kB + kA);
+    const int n_ks = td.n_ks;
+
+    float4v acc[S][4];
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int f = 0; f < 4; ++f) acc[s][f] = float4v{0.f, 0.f, 0.f, 0.f};
+
+    // B: load i brings rows 8 i + lane / 8 of the K-step, 128 bytes each.  LDS chunk c' of row r holds global chunk
+    // c' ^ 2 ((r / 2) % 4): the eight rows half a wave reads with one transposed read fall into distinct banks.
+    const int last_chunk = (p.N - n0 < kDeepN ? p.N - n0 : kDeepN) / 8 - 1;
+    const int chunk = (lane & 7) ^ (2 * (lane >> 4 & 3));
+    const char *Bcol = reinterpret_cast<const char *>(p.B) + (int64_t)n0 * 2 + (chunk <= last_chunk ? chunk : last_chunk) * 16;
+    const uint64_t ldb_bytes = (uint64_t)p.ldb * 2;
+    const int rows_last = td.n_rows - (td.n_slabs - 1) * kSlabRows;
+    const uint32_t a_stride_bytes = (uint32_t)(((td.n_slabs - 1) * kFragElems + rows_last * kStepK) * 2);
+    const char *Abase = reinterpret_cast<const char *>(p.vals) + td.a_off * 16;
+    const int32_t *list = p.gcol + (int64_t)td.ks_begin * kStepK;
+    auto issue_list = [&](int ks, int slot) {
+        if (lane < kStepK) dma4(list + (int64_t)ks * kStepK + lane, base + kDeepSlots * (kB + kA) + slot * kDeepList);
+    };
+    auto issue = [&](int ks, int slot) {
+        int32_t e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[i] = *(lds_i32_ptr)(lists + slot * kDeepList + (8 * i + (lane >> 3)) * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            dma16(Bcol + (uint64_t)(uint32_t)e[i] * ldb_bytes, base + slot * kB + i * 1024);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int sl = s < td.n_slabs ? s : td.n_slabs - 1;               // no second slab: the first again, never stored
+            const int rows = sl == td.n_slabs - 1 ? rows_last : kSlabRows;
+            if (s16 < rows) dma16_base((uint32_t)((sl * kFragElems + (q * rows + s16) * 8) * 2), Abase + (int64_t)ks * a_stride_bytes,
+                                       base + kDeepSlots * kB + slot * kA + s * kFragBytes);
+        }
+    };
+    uint32_t b_off[4];
+    {
+        const int R0 = 16 * (q >> 1) + 4 * (q & 1) + (s16 >> 2);               // the other four rows: R0 + 8, the same swizzle
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            const int c = 2 * f + ((s16 & 3) >> 1);
+            b_off[f] = R0 * kDeepRow + ((c ^ (2 * (R0 >> 1 & 3))) << 4) + (s16 & 1) * 8;
+        }
+    }
+    // The wave's K-steps are wave, wave + 4, ...  One K-step is in flight while the one before it is multiplied; the
+    // list of a K-step is requested a K-step before its rows.
+    if (wave < n_ks) {
+        issue_list(wave, 0);
+        wait_vmcnt<0>();
+        issue(wave, 0);
+        if (wave + 4 < n_ks) issue_list(wave + 4, 1);
+        int slot = 0;
+        for (int ks = wave; ks < n_ks; ks += 4, slot ^= 1) {
+            wait_vmcnt<0>();
+            short8v bfrag[4], afrag[S];
+            const lds_u8_ptr sb = mine + slot * kB, sa = mine + kDeepSlots * kB + slot * kA;
+#pragma unroll
+            for (int f = 0; f < 4; ++f) {
+                const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(sb + b_off[f]));
+                const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(sb + b_off[f] + 8 * kDeepRow));
+                bfrag[f] = short8v{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            }
+#pragma unroll
+            for (int s = 0; s < S; ++s) afrag[s] = *(lds_short8_ptr)(sa + s * kFragBytes + lane * 16);
+            if (ks + 4 < n_ks) issue(ks + 4, slot ^ 1);
+            if (ks + 8 < n_ks) issue_list(ks + 8, slot);
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int f = 0; f < 4; ++f) acc[s][f] = mfma16x16x32<DT>(bfrag[f], afrag[s], acc[s][f]);
+        }
+    }
+
+    int32_t orig[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int rr = s * kSlabRows + 4 * wave + q;                           // this lane's row when the sums are stored
+        orig[s] = rr < td.n_rows ? p.prow[td.row_begin + rr] : -1;
+    }
+    constexpr int kOutRow = kDeepN * 4 + 16, kOutSlab = kSlabRows * kOutRow;
+    __syncthreads();                                                           // nobody reads the rings any more
+    const lds_u8_ptr out = sm + wave * S * kOutSlab;
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int f = 0; f < 4; ++f) *(lds_float4_ptr)(out + s * kOutSlab + s16 * kOutRow + f * 64 + q * 16) = acc[s][f];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const lds_u8_ptr at = sm + s * kOutSlab + (4 * wave + q) * kOutRow + s16 * 16;
+        float4v x = *(lds_float4_ptr)at;
+#pragma unroll
+        for (int w = 1; w < 4; ++w) x += *(lds_float4_ptr)(at + w * S * kOutSlab);
+        const int n = n0 + 4 * s16;
+        if (orig[s] >= 0 && n < p.N) __builtin_nontemporal_store(x, reinterpret_cast<float4v *>(p.C + orig[s] * p.ldc + n));
+    }
+}
+
+template <int S>
+constexpr int deep_lds_bytes()
+{
+    const int ring = 4 * deep_wave_bytes<S>(), out = 4 * S * kSlabRows * (kDeepN * 4 + 16);
+    return ring > out ? ring : out;
+}
+
+template <int DT>
+__device__ __forceinline__ void deep_tile(const Params &p, const TileDesc &td, int ntile, unsigned char *smem)
+{
+    const int n0 = ntile * kTileN + (kTileDeep - td.group) * kDeepN;
+    if (td.n_slabs <= 1) deep_body<DT, 1>(p, td, n0, smem);
+    else deep_body<DT, 2>(p, td, n0, smem);
+}
+
+template <int DT>
+__global__ void __launch_bounds__(kThreads) vbr_spmm_deep_kernel(const Params p)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[deep_lds_bytes<2>()];
+    int tile, ntile;
+    if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
+    deep_tile<DT>(p, p.tiles[tile], ntile, smem);
+}
+
 // Measured on the 16-row workload: two ring slots and four resident workgroups per CU (36 KiB of
 // LDS each) beat deeper rings with fewer workgroups; the gather is bound by how many independent
 // instruction streams feed the texture-address unit, not by the depth of any one of them.
 template <int DT, int S, int NS, int DA, bool GATHER = false>
 __global__ void __launch_bounds__(kThreads) vbr_spmm_kernel(const Params p)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<S, NS, DA>()];
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<S, NS, DA>(GATHER)];
     int tile, ntile;
     if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
     tile_body<DT, S, NS, DA, GATHER>(p, p.tiles[tile], ntile, smem);
 }
 
-// All slab classes in one launch, for matrices whose classes are each too small to fill the chip:
-// the workgroup picks the code of its tile's class (registers and LDS are those of the largest).
+// All gathered tiles that are not deep in one launch.
 template <int DT, int NS, int DA>
+__device__ __forceinline__ void gather_tile(const Params &p, const TileDesc &td, int ntile, unsigned char *smem)
+{
+    if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA, true>(p, td, ntile, smem);
+    else if (td.n_slabs <= 2) tile_body<DT, 2, NS, DA, true>(p, td, ntile, smem);
+    else tile_body<DT, 4, NS, DA, true>(p, td, ntile, smem);
+}
+template <int DT, int NS, int DA>
+__global__ void __launch_bounds__(kThreads) vbr_spmm_gather_kernel(const Params p)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<4, NS, DA>(true)];
+    int tile, ntile;
+    if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
+    gather_tile<DT, NS, DA>(p, p.tiles[tile], ntile, smem);
+}
+
+// All classes in one launch, for matrices whose classes are each too small to fill the chip:
+// the workgroup picks the code of its tile's class (registers and LDS are those of the tallest the matrix has, MAXS).
+template <int DT, int NS, int DA, int MAXS>
 __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<8, NS, DA>()];
+    constexpr int kGather = tile_lds_bytes<4, NS, DA>(true) > deep_lds_bytes<2>() ? tile_lds_bytes<4, NS, DA>(true) : deep_lds_bytes<2>();
+    constexpr int kLds = tile_lds_bytes<MAXS, NS, DA>() > kGather ? tile_lds_bytes<MAXS, NS, DA>() : kGather;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
     int tile, ntile;
     if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
     const TileDesc td = p.tiles[tile];
-    if (td.group < 0) {                   // column-gathered
-        if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA, true>(p, td, ntile, smem);
-        else if (td.n_slabs <= 2) tile_body<DT, 2, NS, DA, true>(p, td, ntile, smem);
-        else if (td.n_slabs <= 4) tile_body<DT, 4, NS, DA, true>(p, td, ntile, smem);
-        else tile_body<DT, 8, NS, DA, true>(p, td, ntile, smem);
-    } else if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA>(p, td, ntile, smem);
+    if (td.group <= kTileDeep) deep_tile<DT>(p, td, ntile, smem);
+    else if (td.group == kTileGathered) gather_tile<DT, NS, DA>(p, td, ntile, smem);
+    else if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA>(p, td, ntile, smem);
     else if (td.n_slabs <= 2) tile_body<DT, 2, NS, DA>(p, td, ntile, smem);
-    else if (td.n_slabs <= 4) tile_body<DT, 4, NS, DA>(p, td, ntile, smem);
-    else tile_body<DT, 8, NS, DA>(p, td, ntile, smem);
+    else if (MAXS == 4 || td.n_slabs <= 4) tile_body<DT, 4, NS, DA>(p, td, ntile, smem);
+    else if constexpr (MAXS == 8) tile_body<DT, 8, NS, DA>(p, td, ntile, smem);
 }
 
 struct PanelParams {
@@ -669,7 +855,14 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             hipLaunchKernelGGL((vbr_spmm_panel_kernel<DT, 8, 4, 3>), grid, dim3(kPanelThreads), 0, stream, pp);
             break;
         case VBR_LAUNCH_TILE_MIXED:
-            hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, kStages, kADistance>), grid, dim3(kThreads), 0, stream, p);
+            if (v->class_begin[4] > v->class_begin[3]) hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, kStages, kADistance, 8>), grid, dim3(kThreads), 0, stream, p);
+            else hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, kStages, kADistance, 4>), grid, dim3(kThreads), 0, stream, p);
+            break;
+        case VBR_LAUNCH_GATHER_DEEP:
+            hipLaunchKernelGGL((vbr_spmm_deep_kernel<DT>), grid, dim3(kThreads), 0, stream, p);
+            break;
+        case VBR_LAUNCH_GATHER_MIXED:
+            hipLaunchKernelGGL((vbr_spmm_gather_kernel<DT, kStages, kADistance>), grid, dim3(kThreads), 0, stream, p);
             break;
         case VBR_LAUNCH_GATHER_1:
             hipLaunchKernelGGL((vbr_spmm_kernel<DT, 1, kStages, kADistance, true>), grid, dim3(kThreads), 0, stream, p);
@@ -679,9 +872,6 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             break;
         case VBR_LAUNCH_GATHER_4:
             hipLaunchKernelGGL((vbr_spmm_kernel<DT, 4, kStages, kADistance, true>), grid, dim3(kThreads), 0, stream, p);
-            break;
-        case VBR_LAUNCH_GATHER_8:
-            hipLaunchKernelGGL((vbr_spmm_kernel<DT, 8, kStagesTall, kADistance, true>), grid, dim3(kThreads), 0, stream, p);
             break;
         case VBR_LAUNCH_TILE_1:
             hipLaunchKernelGGL((vbr_spmm_kernel<DT, 1, kStages, kADistance>), grid, dim3(kThreads), 0, stream, p);
@@ -726,9 +916,8 @@ int create_device_objects(vbr *v)
 {
     if (v->ev_fork) return VBR_OK;
     // a matrix with one kind of work is one launch whatever N is: nothing to spread
-    int kinds = v->panels.empty() ? 0 : 1;
-    for (int c = 0; c < 4; ++c)
-        kinds += (v->class_begin[c + 1] > v->class_begin[c]) + (v->gclass_begin[c + 1] > v->gclass_begin[c]);
+    int kinds = (v->panels.empty() ? 0 : 1) + (v->gclass_begin[1] > 0) + (v->gclass_begin[4] > v->gclass_begin[1]);
+    for (int c = 0; c < 4; ++c) kinds += v->class_begin[c + 1] > v->class_begin[c];
     if (kinds <= 1) return VBR_OK;
     v->release_dev = release_device_objects;
     hipEvent_t ev;
@@ -823,8 +1012,7 @@ extern "C" int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C
     pp.n_panels = (int32_t)v->panels.size();
     pp.n_ntiles = (int32_t)((N + 127) / 128);
     p.gcol = reinterpret_cast<const int32_t *>(d + v->lay.gcol_off);
-    p.zfrag = pp.zfrag;
-    p.b_fits32 = (v->n_cols * ldb * 2 + N * 2) < ((int64_t)1 << 32) ? 1 : 0;
+    p.b_fits24 = (v->n_cols * ldb * 2 + N * 2) < ((int64_t)1 << 32) && v->n_cols <= (1 << 24) && ldb * 2 < (1 << 24) ? 1 : 0;
     p.prow = pp.prow;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     return v->dtype == VBR_F16 ? vbrk::launch_all<VBR_F16>(v, p, pp, stream) : vbrk::launch_all<VBR_BF16>(v, p, pp, stream);

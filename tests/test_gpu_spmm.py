@@ -146,6 +146,43 @@ def test_low_rows_packed_both_ways_in_one_matrix():
                               oracle.block_bits(csr, perm, rg, g, int(ix["blk_col"][blk]), cb))
 
 
+@pytest.mark.parametrize("n,rows_of_hubs,ldb_pad,dtype", [(8, 1, 0, "f16"), (72, 17, 8, "bf16"), (256, 32, 0, "f16"), (1096, 40, 0, "f16")])
+def test_tiles_with_long_column_lists_split_their_k_steps(n, rows_of_hubs, ldb_pad, dtype):
+    # a few rows with thousands of columns among 1100 short ones: their tiles (one slab, a partial second one)
+    # are split over the waves of a workgroup, 64 columns of C each; N below, at and past the 64- and 256-column tiles
+    rng = np.random.default_rng(n)
+    k = 4800
+    lens = [4700 - 37 * i for i in range(rows_of_hubs)] + [int(x) for x in rng.integers(0, 6, size=1100)]
+    csr = csr_from_rows([sorted(rng.choice(k, size=x, replace=False).tolist()) for x in lens], k, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, k, n, dtype)
+    perm = rng.permutation(len(lens)).astype(np.int32)
+    rg = np.arange(len(lens) + 1, dtype=np.int32)
+    c, v = gpu_spmm(csr, perm, rg, 16, bits, ldb_pad=ldb_pad, ldc_pad=4)
+    assert v.tile_ksteps().max() >= 128
+    index_bit_exact(v, csr, perm, rg, 16)
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "hub rows, n=%d" % n)
+
+
+@pytest.mark.parametrize("tail", [1, 15, 16, 33, 63, 64])
+def test_slabs_of_low_rows_that_share_columns_form_taller_tiles(tail):
+    # 1024 + tail single-row groups in clusters over the same columns: tiles of 1 to 4 slabs, the last one partial
+    rng = np.random.default_rng(tail)
+    k, m = 2048, 1024 + tail
+    rows = []
+    for i in range(m):
+        base = 128 * (i // 70 % 16)
+        rows.append(sorted(set((base + rng.choice(128, size=50, replace=False)).tolist() + rng.integers(0, k, size=2).tolist())))
+    csr = csr_from_rows(rows, k, rng)
+    bits = synth.dense_rhs(rng, k, 264, "f16")
+    perm, rg = np.arange(m, dtype=np.int32), np.arange(m + 1, dtype=np.int32)
+    c, v = gpu_spmm(csr, perm, rg, 4, bits)          # blocks of 4: no panels
+    assert v.schedule()["n_tiles"] < m // 32         # most tiles hold more than two slabs
+    index_bit_exact(v, csr, perm, rg, 4)
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "taller tiles")
+
+
 @pytest.mark.parametrize("col_block,n_blocks,density,dtype,n", [(16, 12, 0.03, "f16", 136), (32, 40, 0.01, "bf16", 264),
                                                               (16, 200, 0.004, "f16", 128)])
 def test_short_groups_wider_blocks_and_padded_leading_dimensions(col_block, n_blocks, density, dtype, n):
