@@ -34,6 +34,7 @@ inline bool use_panels(int lg_gran, int64_t short_rows) { return lg_gran >= 3 &&
 // and up to 8 fragments (8 loads) per 128 columns; a one-slab tile 32 B rows x 256 columns (16 loads)
 // and one fragment.  The direct-to-LDS load instruction is the unit of cost of both kernels.
 constexpr int64_t kPanelStepCost = 32, kTileStepCost = 17;
+constexpr int64_t kPanelMaxSteps = 64;       // a panel is not split over K: longer ones would outlast the launch
 constexpr int64_t kSlabMaxCols = 1024;       // columns a slab of low rows gathers before the next group starts a new slab
 
 // What a tile takes, in nanoseconds per workgroup of 256 columns: per K-step by its height (rates measured on full
@@ -45,6 +46,7 @@ constexpr int64_t kDeepStepNs[kMaxDeepSlabs] = {290, 350};
 constexpr int64_t kTileStartSteps = 4;
 constexpr int64_t kDeepSteps = 32;           // no tile of fewer K-steps is deep
 constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: height costs workgroups, and there are few
+constexpr int64_t kShortSteps = 8, kShortMinSlabs = 512;
 constexpr int64_t kMixedMaxWorkgroups = 4096;
 constexpr int64_t kSegmentSlabs = 64;        // the cutting of the slab list into tiles is optimised over stretches of this length
 
@@ -55,6 +57,10 @@ inline int64_t gather_cost(int64_t cols, int n_slabs, int64_t deep_steps)
     if (n_slabs <= kMaxDeepSlabs) return (ks + kTileStartSteps) * kDeepStepNs[n_slabs - 1];
     return INT64_MAX / 4;
 }
+
+// K-steps from which on a tile is deep, for a matrix of `total` K-steps: the share of one of 768 resident workgroups at
+// N = 2048.
+inline int64_t deep_from(int64_t total) { return std::max<int64_t>(kDeepSteps, total * 8 / 768); }
 
 // What a thread needs to count and look up the columns and column blocks of a few rows.
 struct Scratch {
@@ -264,7 +270,12 @@ void Builder::index_blocks()
             for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) v->blk_off[(size_t)b + 1] = off += (int64_t)(rg[g + 1] - rg[g]) * cb;
         std::vector<int32_t>().swap(pc.blocks);
     });
+    // A few groups with far more K-steps than the others set the time of a small matrix: gathered, their tiles can be deep.
+    int64_t total = csr->nnz / (2 * kStepK);
+    for (int32_t g = 0; g < G; ++g)
+        if (kind[g] == kBlocks) total += steps_of((v->blk_ptr[g + 1] - v->blk_ptr[g]) * cb);
     for (int32_t g = 0; g < G; ++g) {
+        if (kind[g] == kBlocks && steps_of((v->blk_ptr[g + 1] - v->blk_ptr[g]) * cb) >= deep_from(total)) kind[g] = kGathered;
         if (kind[g] == kLow) low_groups.push_back(g);
         if (kind[g] == kGathered) gathered_groups.push_back(g);
     }
@@ -351,11 +362,19 @@ bool Builder::hubs_first()
 {
     std::vector<int32_t> given, sorted;        // positions in perm
     int64_t longest = 0;
-    for (const int32_t g : low_groups)
+    int64_t low_rows = 0, other_rows = 0;
+    for (const int32_t g : low_groups) low_rows += rg[g + 1] - rg[g];
+    for (const int32_t g : gathered_groups)
+        if (v->blk_ptr[g + 1] > v->blk_ptr[g]) other_rows += rg[g + 1] - rg[g];
+    // the rows of gathered groups join the order if they are more than a few
+    const bool all = 16 * other_rows > low_rows;
+    for (int32_t g = 0; g < G; ++g) {
+        if (kind[g] == kBlocks || (kind[g] == kGathered && !all)) continue;
         for (int32_t q = rg[g]; q < rg[g + 1]; ++q) {
             given.push_back(q);
             longest = std::max(longest, csr->row_ptr[perm[q] + 1] - csr->row_ptr[perm[q]]);
         }
+    }
     const int64_t n = (int64_t)given.size(), step = kMaxGatherSlabs * kSlabRows;
     if (n < kMergeMinSlabs * kSlabRows) return false;
     std::vector<int32_t> at((size_t)longest + 2, 0);
@@ -379,6 +398,10 @@ bool Builder::hubs_first()
     for (int64_t i = 0; i < n; ++i) {
         v->prow[(size_t)i] = perm[sorted[(size_t)i]];
         v->row_pos[(size_t)sorted[(size_t)i]] = (int32_t)i;
+    }
+    if (all) {
+        low_groups.insert(low_groups.end(), gathered_groups.begin(), gathered_groups.end());
+        gathered_groups.clear();
     }
     return true;
 }
@@ -496,22 +519,28 @@ void Builder::choose_panels()
     each(n_chunks, 4, [&](Scratch &s, int64_t c) {
         const int64_t i0 = c * panel_rows, i1 = std::min(n_prows, i0 + panel_rows);
         std::vector<int32_t> blocks;
-        int64_t cost_gather = 0;
-        for (int64_t s0 = i0; s0 < i1; s0 += kSlabRows) {
-            int64_t cols = 0;
-            s.begin();
-            for (int64_t i = s0; i < std::min(i1, s0 + kSlabRows); ++i) {
-                if (v->prow[(size_t)i] < 0) continue;
-                cols += s.add(csr, v->prow[(size_t)i]);
-                for (int64_t p = csr->row_ptr[v->prow[(size_t)i]]; p < csr->row_ptr[v->prow[(size_t)i] + 1]; ++p) {
-                    const int32_t j = csr->col_idx[p] / cb;
-                    if (s.block_pos[j] < 0) { s.block_pos[j] = 0; blocks.push_back(j); }
-                }
+        int64_t cost_gather = INT64_MAX;                  // the cheaper of tiles of 1 and of 4 slabs
+        for (const int64_t slabs : {(int64_t)1, (int64_t)kMaxGatherSlabs}) {
+            int64_t cost = 0;
+            for (int64_t s0 = i0; s0 < i1; s0 += slabs * kSlabRows) {
+                int64_t cols = 0;
+                s.begin();
+                for (int64_t i = s0; i < std::min(i1, s0 + slabs * kSlabRows); ++i)
+                    if (v->prow[(size_t)i] >= 0) cols += s.add(csr, v->prow[(size_t)i]);
+                cost += steps_of(cols) * (kTileStepCost + slabs - 1);
             }
-            cost_gather += steps_of(cols) * kTileStepCost;
+            cost_gather = std::min(cost_gather, cost);
+        }
+        for (int64_t i = i0; i < i1; ++i) {
+            if (v->prow[(size_t)i] < 0) continue;
+            for (int64_t p = csr->row_ptr[v->prow[(size_t)i]]; p < csr->row_ptr[v->prow[(size_t)i] + 1]; ++p) {
+                const int32_t j = csr->col_idx[p] / cb;
+                if (s.block_pos[j] < 0) { s.block_pos[j] = 0; blocks.push_back(j); }
+            }
         }
         for (const int32_t j : blocks) s.block_pos[j] = -1;
-        panel[(size_t)c] = cost_gather >= steps_of((int64_t)blocks.size() * cb) * kPanelStepCost;
+        const int64_t steps = steps_of((int64_t)blocks.size() * cb);
+        panel[(size_t)c] = steps > 0 && steps <= kPanelMaxSteps && cost_gather >= steps * kPanelStepCost;
     });
     int32_t n = 0;
     for (int64_t c = 0; c < n_chunks; ++c)
@@ -630,7 +659,8 @@ void Builder::append_gathered_groups()
 // loads a B row once for all its slabs and multiplies it for all of them: what it gains is the columns they share.
 // The cut of least estimated time is found stretch by stretch.
 //   - Slabs of low rows are joined only where that saves at least a seventh of the gathered rows (joining slabs that
-//     share nothing would make fewer, longer workgroups), and only if there are kMergeMinSlabs of them.
+//     share nothing would make fewer, longer workgroups) and there are kMergeMinSlabs of them; or where the tile stays
+//     short, so that starting and storing are most of its time, and there are enough of them to fill the chip still.
 //   - A tile of more K-steps than a resident workgroup's share of the whole (at N = 2048) would still be at it when the
 //     rest is done.  It is "deep": the waves of a workgroup split its K-steps, and four workgroups its 256 columns.
 void Builder::cut_into_tiles()
@@ -681,7 +711,7 @@ void Builder::cut_into_tiles()
                 for (int len = 1; len <= kMaxGatherSlabs && i + len <= n; ++len) {
                     const int64_t c = cols[(size_t)((b + i) * kMaxGatherSlabs + len - 1)];
                     alone += cols[(size_t)((b + i + len - 1) * kMaxGatherSlabs)];
-                    if (len > 1 && (single || (low && 7 * c > 6 * alone))) continue;
+                    if (len > 1 && (single || (low && 7 * c > 6 * alone && !(steps_of(c) <= kShortSteps && low_slabs >= kShortMinSlabs)))) continue;
                     const int64_t cost = best[(size_t)i] + gather_cost(c, len, deep_steps);
                     if (cost < best[(size_t)(i + len)]) { best[(size_t)(i + len)] = cost; len_of[(size_t)(i + len)] = (uint8_t)len; }
                 }
@@ -697,7 +727,8 @@ void Builder::cut_into_tiles()
         });
     };
     best_cuts(INT32_MAX);
-    v->deep_steps = (int32_t)std::min<int64_t>(INT32_MAX, std::max<int64_t>(kDeepSteps, total * 8 / 768));
+    for (const TileDesc &td : tiles) total += td.n_ks;
+    v->deep_steps = (int32_t)std::min<int64_t>(INT32_MAX, deep_from(total));
     best_cuts(v->deep_steps);
     for (size_t r = 0; r < runs.size(); ++r) {
         int64_t sl = runs[r].first;

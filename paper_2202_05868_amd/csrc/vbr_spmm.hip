@@ -821,8 +821,10 @@ __global__ void __launch_bounds__(kPanelThreads) vbr_spmm_panel_kernel(const Pan
 }
 
 constexpr int kStages = 2;      // LDS ring of B panels
-constexpr int kStagesTall = 3;  // the same for tiles of 5 to 8 slabs (80 KiB of LDS, two workgroups per CU): measured 3 % (K = 16 384)
-                                // to 14 % (K = 8 192) faster than 2 on dense matrices; slower than 2 for every lower class
+constexpr int kStagesTall = 3;  // the same for block tiles of 5 to 8 slabs (80 KiB of LDS, two workgroups per CU): measured 3 % (K = 16 384)
+                                // to 14 % (K = 8 192) faster than 2 on dense matrices; and of 3 to 4 slabs (64 KiB, two per CU): blocks of
+                                // 64 x 64 at 40 %, N = 2048: 144 -> 126 us, at 5 %: 17.4 -> 16.0, N = 8192 the same; slower
+                                // than 2 for the lower classes, and for gathered tiles, which want the third workgroup
 constexpr int kADistance = 3;   // K-steps the A fragments are requested ahead
 
 template <int DT>
@@ -880,7 +882,7 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             hipLaunchKernelGGL((vbr_spmm_kernel<DT, 2, kStages, kADistance>), grid, dim3(kThreads), 0, stream, p);
             break;
         case VBR_LAUNCH_TILE_4:
-            hipLaunchKernelGGL((vbr_spmm_kernel<DT, 4, kStages, kADistance>), grid, dim3(kThreads), 0, stream, p);
+            hipLaunchKernelGGL((vbr_spmm_kernel<DT, 4, kStagesTall, kADistance>), grid, dim3(kThreads), 0, stream, p);
             break;
         default:
             hipLaunchKernelGGL((vbr_spmm_kernel<DT, 8, kStagesTall, kADistance>), grid, dim3(kThreads), 0, stream, p);
