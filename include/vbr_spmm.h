@@ -116,23 +116,12 @@ int64_t vbr_device_bytes(const vbr_t *v);
  * (a hipStream_t, NULL = default stream) and wait for the copy.  The handle keeps the pointer;
  * the buffer must outlive every vbr_spmm on this handle.  The library allocates no device memory.
  * Any col_block >= 1 is taken; widths that are multiples of 8 take the fast gather path.
- * For a matrix that needs more than one kind of kernel, the first upload of a handle also creates,
- * on the current device, three streams of default priority and four events (vbr_free destroys
- * them): a multiply of several launches spreads them over these streams, see vbr_spmm.
  */
 int vbr_upload(vbr_t *v, void *buf_dev, void *hip_stream);
 
 /*
  * C = A.B on the GPU (section 4.4.1), asynchronous on hip_stream, no synchronisation; one to
  * VBR_MAX_LAUNCHES kernel launches (vbr_get_launches lists them), no allocation, no memset.
- * Several launches of one call write disjoint rows of C and do not depend on each other: the
- * first runs on hip_stream, the others on the handle's own streams, which first wait for an event
- * recorded on hip_stream and which hip_stream then waits for, so the call is ordered against
- * earlier and later work on hip_stream like a single launch (measured on RMAT graphs: 0 to 13 %
- * shorter than the launches one behind the other).  Two calls on ONE handle from different streams
- * at the same time would share these streams and events: give each concurrent caller its own
- * handle.  With the environment variable VBR_SPMM_SERIAL set (read once), every launch stays on
- * hip_stream.
  *   B_dev  K x N row-major, 16-bit type of the matrix, leading dimension ldb (elements)
  *   C_dev  n_rows x N row-major fp32, leading dimension ldc (elements); OVERWRITTEN (beta = 0),
  *          rows in ORIGINAL row order (the reordering is internal); rows without entries get 0
@@ -160,18 +149,17 @@ int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C_dev, int64
  * B rows of the columns its rows touch), whichever packing needs fewer loads; the other groups by the tile
  * kernel, on whole column blocks or, where the blocks are mostly fill-in, on the columns the rows
  * of a tile touch (VBR_LAUNCH_GATHER_*).  A gathered tile with far more columns than the others is deep: four
- * workgroups per 256 columns, whose waves split its columns.  For small matrices one launch takes all tiles;
- * otherwise the deep tiles, the other gathered tiles and every class of block tiles (1, 2, 3-4, 5-8
- * slabs of 16 rows) have a launch each: between 0 and VBR_MAX_LAUNCHES launches.  kinds / tiles / workgroups (each
- * room for VBR_MAX_LAUNCHES entries, any may be NULL) receive the kernel, the number of row tiles (a deep
+ * workgroups per 256 columns, whose waves split its columns.  Tiles of one class (height, packing) are one launch
+ * of the kernel for it, tiles of several classes one launch of the mixed kernel; many tiles without
+ * an entry have a launch of their own behind it: between 0 and VBR_MAX_LAUNCHES launches.  kinds / tiles /
+ * workgroups (each room for VBR_MAX_LAUNCHES entries, any may be NULL) receive the kernel, the number of row tiles (a deep
  * tile counts four times) or panels, and the grid size of each launch.
  */
-enum { VBR_MAX_LAUNCHES = 9 };
+enum { VBR_MAX_LAUNCHES = 3 };
 enum {
     VBR_LAUNCH_PANEL = 0, VBR_LAUNCH_TILE_1 = 1, VBR_LAUNCH_TILE_2 = 2, VBR_LAUNCH_TILE_4 = 3,
     VBR_LAUNCH_TILE_8 = 4, VBR_LAUNCH_TILE_MIXED = 5,
-    VBR_LAUNCH_GATHER_1 = 6, VBR_LAUNCH_GATHER_2 = 7, VBR_LAUNCH_GATHER_4 = 8, VBR_LAUNCH_GATHER_MIXED = 9,
-    VBR_LAUNCH_GATHER_DEEP = 10
+    VBR_LAUNCH_GATHER_1 = 6, VBR_LAUNCH_GATHER_2 = 7, VBR_LAUNCH_GATHER_4 = 8
 };
 int vbr_get_launches(const vbr_t *v, int64_t N, int32_t *n_launches, int32_t *kinds, int64_t *tiles,
                      int64_t *workgroups);

@@ -22,6 +22,11 @@ inline int slab_class(int n_slabs)   // kernels exist for 1, 2, 4 and 8 slabs
     return n_slabs <= 1 ? 0 : n_slabs <= 2 ? 1 : n_slabs <= 4 ? 2 : 3;
 }
 
+inline int tile_class(const TileDesc &td)
+{
+    return td.group >= 0 ? slab_class(td.n_slabs) : td.group == kTileGathered ? kClassGather + slab_class(td.n_slabs) : kClassDeep;
+}
+
 // Rows of groups shorter than a slab go into panels when the block width allows the scalar
 // gather path and there are enough of them to give every CU a panel or two (a panel is one long
 // running workgroup per 128 columns; a handful of them would leave most of the chip idle).
@@ -47,7 +52,7 @@ constexpr int64_t kTileStartSteps = 4;
 constexpr int64_t kDeepSteps = 32;           // no tile of fewer K-steps is deep
 constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: height costs workgroups, and there are few
 constexpr int64_t kShortSteps = 8, kShortMinSlabs = 512;
-constexpr int64_t kMixedMaxWorkgroups = 4096;
+constexpr int64_t kEmptyApart = 512;         // workgroups
 constexpr int64_t kSegmentSlabs = 64;        // the cutting of the slab list into tiles is optimised over stretches of this length
 
 inline int64_t gather_cost(int64_t cols, int n_slabs, int64_t deep_steps)
@@ -158,7 +163,6 @@ private:
     std::vector<Kind> kind;
     std::vector<Piece> pieces;
     std::vector<int32_t> low_groups, gathered_groups;
-    std::vector<TileDesc> tiles;       // block tiles in creation order
     int64_t a_units = 0;               // running size of the packed values, in units of 8 values
     int gran = 1, per_step = kStepK;
     bool panels_on = false;
@@ -329,7 +333,7 @@ int Builder::block_tiles()
             td.group = g;
             a_units += n_ks * tile_kstep_stride(td.n_rows, td.n_slabs) / 8;
             row += td.n_rows;
-            tiles.push_back(td);
+            v->tiles.push_back(td);
         }
     }
     v->krow.resize((size_t)(v->ks_ptr[G] * per_step));
@@ -727,7 +731,7 @@ void Builder::cut_into_tiles()
         });
     };
     best_cuts(INT32_MAX);
-    for (const TileDesc &td : tiles) total += td.n_ks;
+    for (const TileDesc &td : v->tiles) total += td.n_ks;
     v->deep_steps = (int32_t)std::min<int64_t>(INT32_MAX, deep_from(total));
     best_cuts(v->deep_steps);
     for (size_t r = 0; r < runs.size(); ++r) {
@@ -796,9 +800,9 @@ void Builder::fill_values()
         const int rows = slab == td.n_slabs - 1 ? td.n_rows - slab * kSlabRows : kSlabRows;
         return dst[(k / kStepK) * stride + (int64_t)slab * kFragElems + frag_index(m, (int)(k % kStepK), rows)];
     };
-    const int64_t n_block = (int64_t)tiles.size();
+    const int64_t n_block = (int64_t)v->tiles.size();
     each(n_block + (int64_t)v->gtiles.size(), 1, [&](Scratch &s, int64_t i) {
-        const TileDesc &td = i < n_block ? tiles[(size_t)i] : v->gtiles[(size_t)(i - n_block)];
+        const TileDesc &td = i < n_block ? v->tiles[(size_t)i] : v->gtiles[(size_t)(i - n_block)];
         const int64_t stride = tile_kstep_stride(td.n_rows, td.n_slabs);
         uint16_t *dst = vals + td.a_off * 8;
         std::fill(dst, dst + td.n_ks * stride, (uint16_t)0);
@@ -831,48 +835,27 @@ void Builder::fill_values()
     });
 }
 
-// The tiles as the device holds them: block tiles by slab class, then gathered tiles by class (deep, 1, 2, 3 to 4
-// slabs), each class the longest first; a deep tile four times, once for every quarter of a column tile.
+// The tiles as the device holds them, whatever their kind: the longest first, those without a K-step (rows without
+// entries) last; a deep tile four times, once for every quarter of a column tile.
 void Builder::schedule()
 {
-    const int64_t NT = (int64_t)tiles.size();
-    std::vector<int32_t> order((size_t)NT);
-    for (int64_t i = 0; i < NT; ++i) order[(size_t)i] = (int32_t)i;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-        const int ca = slab_class(tiles[a].n_slabs), cb_ = slab_class(tiles[b].n_slabs);
-        if (ca != cb_) return ca < cb_;
-        return (int64_t)tiles[a].n_ks * tiles[a].n_slabs > (int64_t)tiles[b].n_ks * tiles[b].n_slabs;
-    });
-    v->tiles.resize((size_t)NT);
-    v->tile_of_group_order.resize((size_t)NT);
-    for (int c = 0; c < 5; ++c) v->class_begin[c] = 0;
-    for (int64_t i = 0; i < NT; ++i) {
-        v->tiles[(size_t)i] = tiles[(size_t)order[(size_t)i]];
-        v->tile_of_group_order[(size_t)order[(size_t)i]] = (int32_t)i;
-        v->class_begin[slab_class(v->tiles[(size_t)i].n_slabs) + 1]++;
+    struct Item { int64_t ns; TileDesc td; };
+    std::vector<Item> items;
+    auto put = [&](TileDesc td) {
+        const int c = tile_class(td);
+        const int64_t ns = c < kClassDeep ? kBlockStepNs[c] : c == kClassDeep ? kDeepStepNs[td.n_slabs - 1] / 4 : kGatherStepNs[td.n_slabs - 1];
+        items.push_back(Item{td.n_ks == 0 ? -1 : (td.n_ks + kTileStartSteps) * ns, td});
+    };
+    for (const TileDesc &td : v->tiles) put(td);
+    for (TileDesc td : v->gtiles)
+        for (int quarter = td.group == kTileDeep ? 3 : 0; quarter >= 0; --quarter, --td.group) put(td);
+    std::stable_sort(items.begin(), items.end(), [](const Item &a, const Item &b) { return a.ns > b.ns; });
+    for (const Item &it : items) {
+        v->dev_tiles.push_back(it.td);
+        if (it.td.n_ks == 0) continue;
+        v->n_work = (int32_t)v->dev_tiles.size();
+        v->class_count[tile_class(it.td)]++;
     }
-    for (int c = 0; c < 4; ++c) v->class_begin[c + 1] += v->class_begin[c];
-
-    const int64_t NG = (int64_t)v->gtiles.size();
-    std::vector<int32_t> gorder((size_t)NG);
-    for (int64_t i = 0; i < NG; ++i) gorder[(size_t)i] = (int32_t)i;
-    auto gather_class = [](const TileDesc &t) { return t.group == kTileDeep ? 0 : 1 + slab_class(t.n_slabs); };
-    std::stable_sort(gorder.begin(), gorder.end(), [&](int32_t a, int32_t b) {
-        const TileDesc &ta = v->gtiles[(size_t)a], &tb = v->gtiles[(size_t)b];
-        if (gather_class(ta) != gather_class(tb)) return gather_class(ta) < gather_class(tb);
-        return (int64_t)ta.n_ks * ta.n_slabs > (int64_t)tb.n_ks * tb.n_slabs;
-    });
-    for (int c = 0; c < 5; ++c) v->gclass_begin[c] = 0;
-    for (const int32_t i : gorder) {
-        TileDesc td = v->gtiles[(size_t)i];
-        const int c = gather_class(td);
-        for (int quarter = 0; quarter < (c == 0 ? 4 : 1); ++quarter) {
-            if (c == 0) td.group = kTileDeep - quarter;
-            v->gtiles_dev.push_back(td);
-            v->gclass_begin[c + 1]++;
-        }
-    }
-    for (int c = 0; c < 4; ++c) v->gclass_begin[c + 1] += v->gclass_begin[c];
 }
 
 void Builder::lay_out()
@@ -880,7 +863,7 @@ void Builder::lay_out()
     DeviceLayout &L = v->lay;
     L.zeros_off = 0;                   // 256 zero bytes the kernel reads for padding
     L.tiles_off = 256;
-    L.krow_off = align_up(L.tiles_off + (int64_t)(v->tiles.size() + v->gtiles_dev.size()) * (int64_t)sizeof(TileDesc), 256);
+    L.krow_off = align_up(L.tiles_off + (int64_t)v->dev_tiles.size() * (int64_t)sizeof(TileDesc), 256);
     L.perm_off = align_up(L.krow_off + (int64_t)v->krow.size() * 4, 256);
     L.panels_off = align_up(L.perm_off + M * 4, 256);
     L.pk_meta_off = align_up(L.panels_off + (int64_t)v->panels.size() * (int64_t)sizeof(PanelDesc), 256);
@@ -991,7 +974,7 @@ extern "C" int vbr_unpack_block(const vbr_t *v, int64_t blk, void *dst_)
     }
     int64_t row = 0;
     for (int64_t t = v->group_first_tile[g]; t < v->group_first_tile[g + 1]; ++t) {
-        const TileDesc &td = v->tiles[v->tile_of_group_order[t]];
+        const TileDesc &td = v->tiles[(size_t)t];
         const int64_t stride = tile_kstep_stride(td.n_rows, td.n_slabs);
         const int rows_last = td.n_rows - (td.n_slabs - 1) * kSlabRows;
         const uint16_t *src = &v->vals[(size_t)td.a_off * 8];
@@ -1023,19 +1006,25 @@ extern "C" int vbr_audit(const vbr_t *v)
         if (e < -1 || (e >= 0 && (int64_t)e + gran > K)) return VBR_EINVAL;
     if ((int64_t)v->krow.size() % per_step != 0) return VBR_EINVAL;
     const int64_t total_ks = (int64_t)v->krow.size() / per_step;
-    if (v->class_begin[0] != 0 || v->class_begin[4] != (int32_t)v->tiles.size()) return VBR_EINVAL;
-    for (int c = 0; c < 4; ++c) {
-        if (v->class_begin[c + 1] < v->class_begin[c]) return VBR_EINVAL;
-        for (int32_t t = v->class_begin[c]; t < v->class_begin[c + 1]; ++t) {
-            const TileDesc &td = v->tiles[t];
-            if (td.n_rows < 1 || td.n_slabs != (td.n_rows + kSlabRows - 1) / kSlabRows || td.n_slabs > kMaxSlabs) return VBR_EINVAL;
-            if (slab_class(td.n_slabs) != c) return VBR_EINVAL;
-            if (td.row_begin < 0 || (int64_t)td.row_begin + td.n_rows > M) return VBR_EINVAL;
-            if (td.n_ks < 0 || td.ks_begin < 0 || (int64_t)td.ks_begin + td.n_ks > total_ks) return VBR_EINVAL;
-            // the fragments of all its K-steps lie inside the values (the zero fragment at the end excluded)
-            if (td.a_off < 0 || td.a_off * 8 + (int64_t)td.n_ks * tile_kstep_stride(td.n_rows, td.n_slabs) > n_vals - kFragElems) return VBR_EINVAL;
+    if (v->n_work < 0 || v->n_work > (int32_t)v->dev_tiles.size()) return VBR_EINVAL;
+    int32_t count[kClasses] = {0};
+    for (size_t i = 0; i < v->dev_tiles.size(); ++i) {
+        const TileDesc &td = v->dev_tiles[i];
+        if (td.n_rows < 1 || td.n_slabs != (td.n_rows + kSlabRows - 1) / kSlabRows || td.n_slabs > kMaxSlabs) return VBR_EINVAL;
+        if (td.n_ks < 0 || td.ks_begin < 0 || (td.n_ks > 0) != ((int32_t)i < v->n_work)) return VBR_EINVAL;
+        if (td.group >= 0) {
+            if (td.row_begin < 0 || (int64_t)td.row_begin + td.n_rows > M || (int64_t)td.ks_begin + td.n_ks > total_ks) return VBR_EINVAL;
+        } else {
+            if (td.group <= kTileDeep - 4 || td.n_slabs > (td.group == kTileGathered ? kMaxGatherSlabs : kMaxDeepSlabs)) return VBR_EINVAL;
+            if (td.row_begin < 0 || (int64_t)td.row_begin + td.n_rows > (int64_t)v->prow.size()) return VBR_EINVAL;
+            if (((int64_t)td.ks_begin + td.n_ks) * kStepK > (int64_t)v->gcol.size()) return VBR_EINVAL;
         }
+        // the fragments of all its K-steps lie inside the values (the zero fragment at the end excluded)
+        if (td.a_off < 0 || td.a_off * 8 + (int64_t)td.n_ks * tile_kstep_stride(td.n_rows, td.n_slabs) > n_vals - kFragElems) return VBR_EINVAL;
+        if (td.n_ks > 0) ++count[tile_class(td)];
     }
+    for (int c = 0; c < kClasses; ++c)
+        if (count[c] != v->class_count[c]) return VBR_EINVAL;                                // the plan picks its kernel by these
     const int rec = 1 + per_step;
     if ((int64_t)v->pk_meta.size() % rec != 0) return VBR_EINVAL;
     const int64_t n_rec = (int64_t)v->pk_meta.size() / rec;
@@ -1067,22 +1056,10 @@ extern "C" int vbr_audit(const vbr_t *v)
     if ((int64_t)v->gcol.size() % kStepK != 0) return VBR_EINVAL;
     for (const int32_t c : v->gcol)
         if (c < 0 || c >= K) return VBR_EINVAL;
-    if (v->gclass_begin[0] != 0 || v->gclass_begin[4] != (int32_t)v->gtiles_dev.size()) return VBR_EINVAL;
-    for (int c = 0; c < 4; ++c) {
-        if (v->gclass_begin[c + 1] < v->gclass_begin[c]) return VBR_EINVAL;
-        for (int32_t t = v->gclass_begin[c]; t < v->gclass_begin[c + 1]; ++t) {
-            const TileDesc &td = v->gtiles_dev[(size_t)t];
-            if (c == 0 ? td.group > kTileDeep || td.group <= kTileDeep - 4 || td.n_slabs > kMaxDeepSlabs : td.group != kTileGathered || slab_class(td.n_slabs) != c - 1) return VBR_EINVAL;
-            if (td.n_rows < 1 || td.n_slabs != (td.n_rows + kSlabRows - 1) / kSlabRows || td.n_slabs > kMaxGatherSlabs) return VBR_EINVAL;
-            if (td.row_begin < 0 || (int64_t)td.row_begin + td.n_rows > (int64_t)v->prow.size()) return VBR_EINVAL;
-            if (td.n_ks < 0 || td.ks_begin < 0 || ((int64_t)td.ks_begin + td.n_ks) * kStepK > (int64_t)v->gcol.size()) return VBR_EINVAL;
-            if (td.a_off < 0 || td.a_off * 8 + (int64_t)td.n_ks * tile_kstep_stride(td.n_rows, td.n_slabs) > n_vals - kFragElems) return VBR_EINVAL;
-        }
-    }
     for (size_t i = v->vals.size() - kFragElems; i < v->vals.size(); ++i)
         if (v->vals[i] != 0) return VBR_EINVAL;                                               // the zero fragment
     const DeviceLayout &L = v->lay;
-    const int64_t ends[9] = {L.zeros_off + 256, L.tiles_off + (int64_t)(v->tiles.size() + v->gtiles_dev.size()) * (int64_t)sizeof(TileDesc),
+    const int64_t ends[9] = {L.zeros_off + 256, L.tiles_off + (int64_t)v->dev_tiles.size() * (int64_t)sizeof(TileDesc),
                               L.krow_off + (int64_t)v->krow.size() * 4, L.perm_off + M * 4,
                               L.panels_off + (int64_t)v->panels.size() * (int64_t)sizeof(PanelDesc),
                               L.pk_meta_off + (int64_t)v->pk_meta.size() * 4, L.prow_off + (int64_t)v->prow.size() * 4,
@@ -1108,42 +1085,32 @@ static int64_t grid_size(int64_t T, int64_t Q)
     return (int64_t)kXcd * ((T + (kXcd / Q) - 1) / (kXcd / Q));
 }
 
-// The panels first (they are the long-running workgroups), then either one mixed launch (several
-// classes, none of which alone gives every CU a couple of workgroups) or: the deep tiles, the other gathered tiles,
-// and one launch per class of block tiles present.
+// The panels, then the tiles: one launch of the kernel of their class, or of the mixed kernel if there are several.
+// One launch for all of them, not one per class: the classes' tails fill each other's gaps, and no launch waits for
+// another.  Measured against launches side by side on streams of their own, and one behind the other: row groups of 16 to 128
+// rows, N = 4096: 169 and 155 -> 137 us; graph of 16384 nodes, N = 4096: 192 and 195 -> 181; of 4096 nodes, N = 2048: 41 and
+// 24 -> 20.  Only tiles without a K-step, if there are many, have a launch of their own behind the others: they just
+// store zeros, and the kernel for them needs no more than that.
 int plan_launches(const vbr *v, int64_t N, Launch out[VBR_MAX_LAUNCHES])
 {
     int n = 0;
     const int64_t Qt = (N + kTileN - 1) / kTileN, Qp = (N + kPanelN - 1) / kPanelN;
     if (!v->panels.empty())
         out[n++] = Launch{VBR_LAUNCH_PANEL, 0, (int32_t)v->panels.size(), grid_size((int64_t)v->panels.size(), Qp)};
-    // Eight tile classes, contiguous in the device's tile array: block tiles of 1, 2, 3-4, 5-8 slabs, then gathered
-    // tiles: deep, 1, 2, 3-4 slabs.  Several classes that together do not give every CU a few workgroups share one
-    // launch of the mixed kernel.  Otherwise the deep tiles go first, in a launch of their own, the other gathered
-    // tiles share one if they are of several heights (the kernel for up to 4 slabs keeps three workgroups on a CU),
-    // and every class of block tiles has its own.  (Mixing only the small classes of block tiles of a large matrix was
-    // measured and lost: the mixed kernel holds the LDS of the tallest class.)
-    const int32_t T_blk = v->class_begin[4];
-    const int32_t *gb = v->gclass_begin;
-    int classes = 0, gathered = 0;
-    for (int c = 0; c < 4; ++c) classes += (v->class_begin[c + 1] > v->class_begin[c]) + (gb[c + 1] > gb[c]);
-    for (int c = 1; c < 4; ++c) gathered += gb[c + 1] > gb[c];
-    const int64_t T_all = (int64_t)T_blk + gb[4];
-    if (classes > 1 && T_all * Qt < kMixedMaxWorkgroups) {
-        out[n++] = Launch{VBR_LAUNCH_TILE_MIXED, 0, (int32_t)T_all, grid_size(T_all, Qt)};
-        return n;
+    static const int32_t kind_of_class[kClasses] = {VBR_LAUNCH_TILE_1, VBR_LAUNCH_TILE_2, VBR_LAUNCH_TILE_4, VBR_LAUNCH_TILE_8, VBR_LAUNCH_TILE_MIXED,
+                                                    VBR_LAUNCH_GATHER_1, VBR_LAUNCH_GATHER_2, VBR_LAUNCH_GATHER_4};
+    int classes = 0, last = 0;
+    for (int c = 0; c < kClasses; ++c)
+        if (v->class_count[c] > 0) { ++classes; last = c; }
+    const int32_t T_all = (int32_t)v->dev_tiles.size(), T_empty = T_all - v->n_work;
+    const bool apart = T_empty * Qt >= kEmptyApart;
+    const int32_t T = apart || v->n_work == 0 ? v->n_work : T_all;
+    // (tiles without a K-step are gathered ones of up to 4 slabs: that kernel takes them, and the mixed one)
+    if (T > 0) {
+        const bool one_kind = classes == 1 && (T == v->n_work || last == kClasses - 1);
+        out[n++] = Launch{one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED, 0, T, grid_size(T, Qt)};
     }
-    if (gb[1] > gb[0]) out[n++] = Launch{VBR_LAUNCH_GATHER_DEEP, T_blk, gb[1], grid_size(gb[1], Qt)};
-    if (gathered > 1) {
-        out[n++] = Launch{VBR_LAUNCH_GATHER_MIXED, T_blk + gb[1], gb[4] - gb[1], grid_size(gb[4] - gb[1], Qt)};
-    } else {
-        for (int c = 1; c < 4; ++c)
-            if (gb[c + 1] > gb[c]) out[n++] = Launch{VBR_LAUNCH_GATHER_1 + c - 1, T_blk + gb[c], gb[c + 1] - gb[c], grid_size(gb[c + 1] - gb[c], Qt)};
-    }
-    for (int c = 0; c < 4; ++c) {
-        const int32_t T = v->class_begin[c + 1] - v->class_begin[c];
-        if (T > 0) out[n++] = Launch{VBR_LAUNCH_TILE_1 + c, v->class_begin[c], T, grid_size(T, Qt)};
-    }
+    if (T < T_all) out[n++] = Launch{VBR_LAUNCH_GATHER_4, T, T_all - T, grid_size(T_all - T, Qt)};
     return n;
 }
 
@@ -1186,7 +1153,6 @@ extern "C" int64_t vbr_get_tile_ksteps(const vbr_t *v, int64_t *out, int64_t cap
 
 extern "C" void vbr_free(vbr_t *v)
 {
-    if (v && v->release_dev) v->release_dev(v);
     delete v;
 }
 

@@ -33,6 +33,8 @@ struct TileDesc {
                          // of a 256-column tile (0 .. 3) a workgroup takes
 };
 constexpr int32_t kTileGathered = -1, kTileDeep = -2;
+// Classes of tiles: block tiles of 1, 2, 3-4, 5-8 slabs, deep tiles, gathered tiles of 1, 2, 3-4 slabs.
+constexpr int kClassDeep = 4, kClassGather = 5, kClasses = 8;
 static_assert(sizeof(TileDesc) == 32, "TileDesc is read by the kernel as 2 x 16 bytes");
 
 // Position inside a (slab, K-step) fragment of the value at slab row m and K-step-local column
@@ -110,10 +112,12 @@ struct vbr {
     int32_t lg_gran = 0;                 // log2 of the B-row gather granularity (rows per krow entry)
     std::vector<int64_t> ks_ptr;         // [n_groups+1] first global K-step of each group
     std::vector<int32_t> krow;           // first B row of each granule of each K-step, -1 = padding
-    std::vector<vbrk::TileDesc> tiles;    // sorted by slab class, then by falling work
-    int32_t class_begin[5] = {0, 0, 0, 0, 0};  // tiles of slab class c (1,2,4,8 slabs) are [class_begin[c], class_begin[c+1])
-    std::vector<int64_t> group_first_tile;      // [n_groups+1] tiles of a group in creation order (for unpack)
-    std::vector<int32_t> tile_of_group_order;   // creation order -> index in `tiles`
+    std::vector<vbrk::TileDesc> tiles;    // block tiles, group by group
+    std::vector<int64_t> group_first_tile;      // [n_groups+1] tiles of a group in `tiles`
+    std::vector<vbrk::TileDesc> dev_tiles;      // `tiles` and `gtiles` as the device holds them: longest first, deep ones four times,
+                                                // those without a K-step last
+    int32_t n_work = 0;                         // of them with a K-step
+    int32_t class_count[vbrk::kClasses] = {0};  // of these, per class
     vbrk::HostValues vals;               // packed fragments: block tiles, panels, gathered tiles, then 1 KiB of zeros
     // Rows that are not multiplied in block tiles stand in a row list (prow): first those of groups of height < 16
     // ("low rows"), in an order of the packing's own, then those of taller groups whose blocks are mostly fill-in.
@@ -127,8 +131,6 @@ struct vbr {
     std::vector<int32_t> chunk_panel;    // [n_chunks] index of its panel in `panels`, -1 = gathered tiles
     std::vector<int32_t> slab_tile;      // [n_slabs] index in `gtiles` of the slab's tile, -1 = in a panel
     std::vector<vbrk::TileDesc> gtiles;   // column-gathered tiles in creation order: row_begin = position in prow
-    std::vector<vbrk::TileDesc> gtiles_dev;      // the same tiles as the device holds them: by class, longest first, deep ones four times
-    int32_t gclass_begin[5] = {0, 0, 0, 0, 0};   // deep tiles, tiles of 1, 2, 3-4 slabs: class c is gtiles_dev[gclass_begin[c] .. gclass_begin[c+1])
     std::vector<int32_t> gcol;           // per K-step of a gathered tile 32 columns of A (= rows of B), rising, the last column repeated to the end
     std::vector<vbrk::PanelDesc> panels;
     std::vector<int32_t> pk_row;         // host only: first B row of each granule of each physical K-step, -1 = padding
@@ -141,12 +143,4 @@ struct vbr {
     std::vector<int32_t> p_union;        // host only: ascending union of the column blocks of each panel
     vbrk::DeviceLayout lay;
     void *dev = nullptr;                 // uploaded buffer (caller-owned)
-    // A multiply of several launches forks them over side streams and joins them on the caller's
-    // stream (they write disjoint rows of C).  Created by vbr_upload on the device current then,
-    // released through `release_dev` by vbr_free; all opaque to the host-only translation units.
-    static constexpr int kSideStreams = 3;
-    void *side_stream[kSideStreams] = {nullptr, nullptr, nullptr};
-    void *ev_fork = nullptr;
-    void *ev_join[kSideStreams] = {nullptr, nullptr, nullptr};
-    void (*release_dev)(vbr *) = nullptr;
 };

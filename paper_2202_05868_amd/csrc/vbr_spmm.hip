@@ -4,11 +4,11 @@
 // brings the gathered B rows and the A fragments into rings of LDS slots with 128-bit direct-to-LDS
 // loads, and issues v_mfma_f32_16x16x32 on them.
 //   tile kernel    up to 8 slabs of ONE row group x 256 columns; K-steps = the group's column blocks
-//                  (one launch per slab class, or one mixed launch for small matrices)
-//   gathered tiles the same kernel with K-steps = the single columns its rows touch: slabs cut from the
-//                  rows of low groups, and tiles of tall groups whose blocks are mostly fill-in
+//   gathered tiles the same kernel with K-steps = the single columns its rows touch: up to 4 slabs of the
+//                  rows of low groups, and of tall groups whose blocks are mostly fill-in
+//   deep tiles     gathered tiles with very many columns: the waves of a workgroup split the K-steps
 //   panel kernel   8 slabs of low groups x 128 columns walking the union of their column blocks
-// The launches of one call are independent and are spread over the handle's streams (launch_all).
+// All tiles of a matrix are one launch.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -44,7 +44,7 @@ typedef __attribute__((address_space(3))) unsigned char *lds_u8_ptr;
 typedef __attribute__((address_space(4))) const int32_t *const_i32_ptr;
 
 struct Params {
-    const TileDesc *tiles;    // tiles of this launch: one slab class, all of them, or the column-gathered ones
+    const TileDesc *tiles;    // tiles of this launch
     const int32_t *krow;
     const int32_t *perm;
     const int32_t *gcol;      // column-gathered tiles: their column lists ...
@@ -431,7 +431,7 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
 constexpr int kDeepN = 64;                        // C columns per workgroup of a deep tile
 constexpr int kDeepRow = kDeepN * 2;              // one staged B row: 128 bytes
 constexpr int kDeepList = kStepK * 4;             // the list entries of a K-step
-constexpr int kDeepSlots = 2;
+constexpr int kDeepSlots = 2;                     // three workgroups on a CU
 template <int S>
 constexpr int deep_wave_bytes() { return kDeepSlots * (kStepK * kDeepRow + S * kFragBytes + kDeepList); }
 
@@ -498,16 +498,26 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
             b_off[f] = R0 * kDeepRow + ((c ^ (2 * (R0 >> 1 & 3))) << 4) + (s16 & 1) * 8;
         }
     }
-    // The wave's K-steps are wave, wave + 4, ...  One K-step is in flight while the one before it is multiplied; the
-    // list of a K-step is requested a K-step before its rows.
-    if (wave < n_ks) {
-        issue_list(wave, 0);
+    // The wave's own K-steps, 0 .. steps-1, are wave, wave + 4, ...  Iteration j issues the rows and fragments of step
+    // j + P and the list of step j + 2 P (clamped to the last): P steps are in flight while one is multiplied, and a
+    // list is there when its rows are requested.
+    constexpr int P = kDeepSlots - 1, kPerStep = 4 + S + 1;
+    static_assert((P - 1) * kPerStep < 64, "vmcnt is a 6-bit counter");
+    const int steps = wave < n_ks ? (n_ks - wave + 3) / 4 : 0;
+    auto list_at = [&](int j) { issue_list(wave + 4 * (j < steps ? j : steps - 1), j % kDeepSlots); };
+    if (steps > 0) {
+#pragma unroll
+        for (int t = 0; t < P; ++t) list_at(t);
         wait_vmcnt<0>();
-        issue(wave, 0);
-        if (wave + 4 < n_ks) issue_list(wave + 4, 1);
+#pragma unroll
+        for (int t = 0; t < P; ++t) {
+            issue(wave + 4 * (t < steps ? t : steps - 1), t);
+            list_at(t + P);
+        }
         int slot = 0;
-        for (int ks = wave; ks < n_ks; ks += 4, slot ^= 1) {
-            wait_vmcnt<0>();
+        for (int j = 0; j < steps; ++j) {
+            if (j + P <= steps) wait_vmcnt<(P - 1) * kPerStep>();     // everything up to the rows and fragments of step j
+            else wait_vmcnt<0>();
             short8v bfrag[4], afrag[S];
             const lds_u8_ptr sb = mine + slot * kB, sa = mine + kDeepSlots * kB + slot * kA;
 #pragma unroll
@@ -518,13 +528,17 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
             }
 #pragma unroll
             for (int s = 0; s < S; ++s) afrag[s] = *(lds_short8_ptr)(sa + s * kFragBytes + lane * 16);
-            if (ks + 4 < n_ks) issue(ks + 4, slot ^ 1);
-            if (ks + 8 < n_ks) issue_list(ks + 8, slot);
+            if (j + P < steps) {
+                issue(wave + 4 * (j + P), slot == 0 ? P : slot - 1);
+                list_at(j + 2 * P);
+            }
 #pragma unroll
             for (int s = 0; s < S; ++s)
 #pragma unroll
                 for (int f = 0; f < 4; ++f) acc[s][f] = mfma16x16x32<DT>(bfrag[f], afrag[s], acc[s][f]);
+            slot = slot == P ? 0 : slot + 1;
         }
+        wait_vmcnt<0>();
     }
 
     int32_t orig[S];
@@ -559,22 +573,12 @@ constexpr int deep_lds_bytes()
     return ring > out ? ring : out;
 }
 
-template <int DT>
-__device__ __forceinline__ void deep_tile(const Params &p, const TileDesc &td, int ntile, unsigned char *smem)
-{
-    const int n0 = ntile * kTileN + (kTileDeep - td.group) * kDeepN;
-    if (td.n_slabs <= 1) deep_body<DT, 1>(p, td, n0, smem);
-    else deep_body<DT, 2>(p, td, n0, smem);
-}
-
-template <int DT>
-__global__ void __launch_bounds__(kThreads) vbr_spmm_deep_kernel(const Params p)
-{
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[deep_lds_bytes<2>()];
-    int tile, ntile;
-    if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
-    deep_tile<DT>(p, p.tiles[tile], ntile, smem);
-}
+constexpr int kStages = 2;      // LDS ring of B panels
+constexpr int kStagesTall = 3;  // the same for block tiles of 5 to 8 slabs (80 KiB of LDS, two workgroups per CU): measured 3 % (K = 16 384)
+                                // to 14 % (K = 8 192) faster than 2 on dense matrices; and of 3 to 4 slabs (64 KiB, two per CU): blocks of
+                                // 64 x 64 at 40 %, N = 2048: 144 -> 126 us, at 5 %: 17.4 -> 16.0, N = 8192 the same; slower
+                                // than 2 for the lower classes, and for gathered tiles, which want the third workgroup
+constexpr int kADistance = 3;   // K-steps the A fragments are requested ahead
 
 // Measured on the 16-row workload: two ring slots and four resident workgroups per CU (36 KiB of
 // LDS each) beat deeper rings with fewer workgroups; the gather is bound by how many independent
@@ -588,39 +592,30 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_kernel(const Params p)
     tile_body<DT, S, NS, DA, GATHER>(p, p.tiles[tile], ntile, smem);
 }
 
-// All gathered tiles that are not deep in one launch.
-template <int DT, int NS, int DA>
-__device__ __forceinline__ void gather_tile(const Params &p, const TileDesc &td, int ntile, unsigned char *smem)
-{
-    if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA, true>(p, td, ntile, smem);
-    else if (td.n_slabs <= 2) tile_body<DT, 2, NS, DA, true>(p, td, ntile, smem);
-    else tile_body<DT, 4, NS, DA, true>(p, td, ntile, smem);
-}
-template <int DT, int NS, int DA>
-__global__ void __launch_bounds__(kThreads) vbr_spmm_gather_kernel(const Params p)
-{
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<4, NS, DA>(true)];
-    int tile, ntile;
-    if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
-    gather_tile<DT, NS, DA>(p, p.tiles[tile], ntile, smem);
-}
-
-// All classes in one launch, for matrices whose classes are each too small to fill the chip:
-// the workgroup picks the code of its tile's class (registers and LDS are those of the tallest the matrix has, MAXS).
-template <int DT, int NS, int DA, int MAXS>
+// Tiles of several classes in one launch: the workgroup picks the code of its tile's class.  Registers and LDS are those of
+// the largest: for block tiles of up to 4 slabs (MAXS) 50 KiB, three workgroups on a CU, and with 5 to 8 slabs 64 KiB, two,
+// which leaves the 3 to 4 slab class its ring of three.
+template <int DT, int MAXS>
 __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p)
 {
-    constexpr int kGather = tile_lds_bytes<4, NS, DA>(true) > deep_lds_bytes<2>() ? tile_lds_bytes<4, NS, DA>(true) : deep_lds_bytes<2>();
-    constexpr int kLds = tile_lds_bytes<MAXS, NS, DA>() > kGather ? tile_lds_bytes<MAXS, NS, DA>() : kGather;
+    constexpr int NS = kStages, DA = kADistance, NS4 = MAXS == 8 ? kStagesTall : kStages;
+    constexpr int kGather = std::max(tile_lds_bytes<4, NS, DA>(true), deep_lds_bytes<2>());
+    constexpr int kLds = std::max(kGather, std::max(tile_lds_bytes<MAXS, NS, DA>(), tile_lds_bytes<4, NS4, DA>()));
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
     int tile, ntile;
     if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
     const TileDesc td = p.tiles[tile];
-    if (td.group <= kTileDeep) deep_tile<DT>(p, td, ntile, smem);
-    else if (td.group == kTileGathered) gather_tile<DT, NS, DA>(p, td, ntile, smem);
-    else if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA>(p, td, ntile, smem);
+    if (td.group <= kTileDeep) {
+        const int n0 = ntile * kTileN + (kTileDeep - td.group) * kDeepN;
+        if (td.n_slabs <= 1) deep_body<DT, 1>(p, td, n0, smem);
+        else deep_body<DT, 2>(p, td, n0, smem);
+    } else if (td.group == kTileGathered) {
+        if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA, true>(p, td, ntile, smem);
+        else if (td.n_slabs <= 2) tile_body<DT, 2, NS, DA, true>(p, td, ntile, smem);
+        else tile_body<DT, 4, NS, DA, true>(p, td, ntile, smem);
+    } else if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA>(p, td, ntile, smem);
     else if (td.n_slabs <= 2) tile_body<DT, 2, NS, DA>(p, td, ntile, smem);
-    else if (MAXS == 4 || td.n_slabs <= 4) tile_body<DT, 4, NS, DA>(p, td, ntile, smem);
+    else if (MAXS == 4 || td.n_slabs <= 4) tile_body<DT, 4, NS4, DA>(p, td, ntile, smem);
     else if constexpr (MAXS == 8) tile_body<DT, 8, NS, DA>(p, td, ntile, smem);
 }
 
@@ -820,34 +815,16 @@ __global__ void __launch_bounds__(kPanelThreads) vbr_spmm_panel_kernel(const Pan
     }
 }
 
-constexpr int kStages = 2;      // LDS ring of B panels
-constexpr int kStagesTall = 3;  // the same for block tiles of 5 to 8 slabs (80 KiB of LDS, two workgroups per CU): measured 3 % (K = 16 384)
-                                // to 14 % (K = 8 192) faster than 2 on dense matrices; and of 3 to 4 slabs (64 KiB, two per CU): blocks of
-                                // 64 x 64 at 40 %, N = 2048: 144 -> 126 us, at 5 %: 17.4 -> 16.0, N = 8192 the same; slower
-                                // than 2 for the lower classes, and for gathered tiles, which want the third workgroup
-constexpr int kADistance = 3;   // K-steps the A fragments are requested ahead
 
 template <int DT>
-int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStream_t caller)
+int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStream_t stream)
 {
     Launch plan[VBR_MAX_LAUNCHES];
     const int n = plan_launches(v, base.N, plan);
     for (int i = 0; i < n; ++i)
         if (plan[i].grid > INT32_MAX) return VBR_EINVAL;
-    // Several launches write disjoint rows of C and are independent of each other: the first stays on
-    // the caller's stream, the others go to the side streams behind an event recorded on the caller's
-    // stream, and the caller's stream waits for each side stream's last launch.
-    static const bool serial = getenv("VBR_SPMM_SERIAL") != nullptr;
-    const bool fork = n > 1 && v->ev_fork && !serial;
-    if (fork) {
-        hipError_t e = hipEventRecord((hipEvent_t)v->ev_fork, caller);
-        for (int k = 0; e == hipSuccess && k < std::min(n - 1, (int)vbr::kSideStreams); ++k)
-            e = hipStreamWaitEvent((hipStream_t)v->side_stream[k], (hipEvent_t)v->ev_fork, 0);
-        if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
-    }
     for (int i = 0; i < n; ++i) {
         const Launch &L = plan[i];
-        hipStream_t stream = fork && i > 0 ? (hipStream_t)v->side_stream[(i - 1) % vbr::kSideStreams] : caller;
         Params p = base;
         p.tiles = base.tiles + L.first_tile;
         p.n_tiles = L.n_tiles;
@@ -857,14 +834,8 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             hipLaunchKernelGGL((vbr_spmm_panel_kernel<DT, 8, 4, 3>), grid, dim3(kPanelThreads), 0, stream, pp);
             break;
         case VBR_LAUNCH_TILE_MIXED:
-            if (v->class_begin[4] > v->class_begin[3]) hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, kStages, kADistance, 8>), grid, dim3(kThreads), 0, stream, p);
-            else hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, kStages, kADistance, 4>), grid, dim3(kThreads), 0, stream, p);
-            break;
-        case VBR_LAUNCH_GATHER_DEEP:
-            hipLaunchKernelGGL((vbr_spmm_deep_kernel<DT>), grid, dim3(kThreads), 0, stream, p);
-            break;
-        case VBR_LAUNCH_GATHER_MIXED:
-            hipLaunchKernelGGL((vbr_spmm_gather_kernel<DT, kStages, kADistance>), grid, dim3(kThreads), 0, stream, p);
+            if (v->class_count[3] > 0) hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, 8>), grid, dim3(kThreads), 0, stream, p);
+            else hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, 4>), grid, dim3(kThreads), 0, stream, p);
             break;
         case VBR_LAUNCH_GATHER_1:
             hipLaunchKernelGGL((vbr_spmm_kernel<DT, 1, kStages, kADistance, true>), grid, dim3(kThreads), 0, stream, p);
@@ -891,49 +862,6 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
     }
-    if (fork) {
-        for (int k = 0; k < std::min(n - 1, (int)vbr::kSideStreams); ++k) {
-            hipError_t e = hipEventRecord((hipEvent_t)v->ev_join[k], (hipStream_t)v->side_stream[k]);
-            if (e == hipSuccess) e = hipStreamWaitEvent(caller, (hipEvent_t)v->ev_join[k], 0);
-            if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
-        }
-    }
-    return VBR_OK;
-}
-
-// Streams and events of the forked launches; vbr_free calls this through the handle.
-void release_device_objects(vbr *v)
-{
-    for (int k = 0; k < vbr::kSideStreams; ++k) {
-        if (v->ev_join[k]) (void)hipEventDestroy((hipEvent_t)v->ev_join[k]);
-        if (v->side_stream[k]) (void)hipStreamDestroy((hipStream_t)v->side_stream[k]);
-        v->ev_join[k] = v->side_stream[k] = nullptr;
-    }
-    if (v->ev_fork) (void)hipEventDestroy((hipEvent_t)v->ev_fork);
-    v->ev_fork = nullptr;
-    v->release_dev = nullptr;
-}
-
-int create_device_objects(vbr *v)
-{
-    if (v->ev_fork) return VBR_OK;
-    // a matrix with one kind of work is one launch whatever N is: nothing to spread
-    int kinds = (v->panels.empty() ? 0 : 1) + (v->gclass_begin[1] > 0) + (v->gclass_begin[4] > v->gclass_begin[1]);
-    for (int c = 0; c < 4; ++c) kinds += v->class_begin[c + 1] > v->class_begin[c];
-    if (kinds <= 1) return VBR_OK;
-    v->release_dev = release_device_objects;
-    hipEvent_t ev;
-    hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-    if (e == hipSuccess) v->ev_fork = ev;
-    for (int k = 0; e == hipSuccess && k < vbr::kSideStreams; ++k) {
-        hipStream_t st;
-        e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);       // default priority
-        if (e != hipSuccess) break;
-        v->side_stream[k] = st;
-        e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-        if (e == hipSuccess) v->ev_join[k] = ev;
-    }
-    if (e != hipSuccess) { release_device_objects(v); set_last_hip_error((int)e); return VBR_EHIP; }
     return VBR_OK;
 }
 
@@ -950,14 +878,13 @@ extern "C" int vbr_upload(vbr_t *v, void *buf_dev, void *hip_stream)
     const vbrk::DeviceLayout &L = v->lay;
     struct Part { int64_t off; const void *src; size_t bytes; };
     static const unsigned char kZeros[256] = {0};
-    const Part parts[10] = {
-        {L.tiles_off + (int64_t)(v->tiles.size() * sizeof(vbrk::TileDesc)), v->gtiles_dev.data(), v->gtiles_dev.size() * sizeof(vbrk::TileDesc)},
+    const Part parts[9] = {
         {L.gcol_off, v->gcol.data(), v->gcol.size() * 4},
         {L.panels_off, v->panels.data(), v->panels.size() * sizeof(vbrk::PanelDesc)},
         {L.pk_meta_off, v->pk_meta.data(), v->pk_meta.size() * 4},
         {L.prow_off, v->prow.data(), v->prow.size() * 4},
         {L.zeros_off, kZeros, sizeof(kZeros)},
-        {L.tiles_off, v->tiles.data(), v->tiles.size() * sizeof(vbrk::TileDesc)},
+        {L.tiles_off, v->dev_tiles.data(), v->dev_tiles.size() * sizeof(vbrk::TileDesc)},
         {L.krow_off, v->krow.data(), v->krow.size() * 4},
         {L.perm_off, v->perm.data(), v->perm.size() * 4},
         {L.vals_off, v->vals.data(), v->vals.size() * 2},
@@ -970,7 +897,7 @@ extern "C" int vbr_upload(vbr_t *v, void *buf_dev, void *hip_stream)
     hipError_t e = hipStreamSynchronize(stream);
     if (e != hipSuccess) { vbrk::set_last_hip_error((int)e); return VBR_EHIP; }
     v->dev = buf_dev;
-    return vbrk::create_device_objects(v);
+    return VBR_OK;
 }
 
 extern "C" int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C_dev, int64_t ldc,
