@@ -57,6 +57,13 @@ __device__ __forceinline__ uint32_t row_lane(uint32_t x)     // lane I of every 
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x150 + I, 0xf, 0xf, false);
 }
 
+template <int U>
+__device__ __forceinline__ uint32_t row_pair(uint32_t x)     // lane 2U of every row of 16 lanes to its first eight, lane 2U + 1 to the others
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)x, 0x150 + 2 * U, 0xf, 0x3, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(lo, (int)x, 0x150 + 2 * U + 1, 0xf, 0xc, false);
+}
+
 // What bounds it: the B rows gathered through the caches, nnz N 2 bytes, at 64 bytes per cycle and compute unit.  So
 // everything is arranged for B to come from the L2 of the XCD and for enough loads to be in flight:
 //   - a wave owns 8 LANES columns; an XCD keeps to few column tiles at a time (map below), whose B it holds in its L2;
@@ -66,16 +73,17 @@ __device__ __forceinline__ uint32_t row_lane(uint32_t x)     // lane I of every 
 //   - rows beyond kCsrLongRow entries get a whole wave, rows beyond kCsrHugeRow a workgroup: its 64 / LANES (256 / LANES)
 //     groups of lanes take the entries in turn, and the partial sums are added at the end.
 // Entries past the end of a row are loads out of the buffer's range: they return zeros and cost no traffic.
-// LANES: 16 keeps the B a wave's column tile touches smallest (256 bytes a row); 32 where a tile of that width stays
-// in the L2 anyway or rows of B do not start on a cache line, because then 256 bytes of a row lie in three lines of 128.
-// Measured on a graph of 16384 nodes with 426 000 entries (rows of 0 to 3600), N = 4096: 680 -> 206 us (17 TB/s of gathered B), with B
-// and C beyond the caches 253 us; N = 256: 329 -> 26 us.  4096 x 16384 with 1638 entries a row, N = 4096: 3.56 -> 2.12 ms (26 TB/s).
+// LANES: 8, 16 or 32 (64, 128 or 256 columns a wave), chosen by csr_spmm.  With 8, the 16 lanes of a row take two entries
+// at a time and add their halves at the end.
+// Measured on a graph of 16384 nodes with 426 000 entries (rows of 0 to 3600), with B and C beyond the caches, N = 4096: 680 -> 208 us
+// (17 TB/s of gathered B); N = 256: 329 -> 22 us.  4096 x 16384 with 1638 entries a row, N = 4096: 3.56 -> 1.90 ms (29 TB/s).
 template <int DT, bool WIDE, int LANES>
 __global__ void __launch_bounds__(kCsrThreads) csr_spmm_kernel(const CsrParams p)
 {
-    constexpr int kGroups = 64 / LANES, kTileN = 8 * LANES;
+    constexpr bool kPair = LANES == 8;                               // 16 lanes own a row, two entries at a time
+    constexpr int kGroups = kPair ? 4 : 64 / LANES, kTileN = 8 * LANES;
     __shared__ float partial[3][kTileN];
-    const int lane = threadIdx.x & 63, g = lane / LANES, s16 = lane & 15, chunk0 = lane % LANES;
+    const int lane = threadIdx.x & 63, g = lane / (64 / kGroups), s16 = lane & 15, chunk0 = lane % LANES;
     // workgroup -> (column tile, four waves' rows): workgroups are dealt to the 8 L2 domains round-robin
     const int T = (p.n_waves + 3) / 4, Q = p.n_ntiles;
     const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
@@ -145,21 +153,36 @@ __global__ void __launch_bounds__(kCsrThreads) csr_spmm_kernel(const CsrParams p
         uint4v b[8];
 #define CSR_LOAD(U, S) b[U] = load(row_lane<U + S>(off))
 #define CSR_ADD(U, S) add(row_lane<U + S>(a), b[U])
-        CSR_LOAD(0, 0); CSR_LOAD(1, 0); CSR_LOAD(2, 0); CSR_LOAD(3, 0);
-        if (rounds > 4) { CSR_LOAD(4, 0); CSR_LOAD(5, 0); CSR_LOAD(6, 0); CSR_LOAD(7, 0); }
-        CSR_ADD(0, 0); CSR_ADD(1, 0); CSR_ADD(2, 0); CSR_ADD(3, 0);
-        if (rounds > 8) { CSR_LOAD(0, 8); CSR_LOAD(1, 8); CSR_LOAD(2, 8); CSR_LOAD(3, 8); }
-        if (rounds > 4) { CSR_ADD(4, 0); CSR_ADD(5, 0); CSR_ADD(6, 0); CSR_ADD(7, 0); }
-        if (rounds > 12) { CSR_LOAD(4, 8); CSR_LOAD(5, 8); CSR_LOAD(6, 8); CSR_LOAD(7, 8); }
-        if (rounds > 8) { CSR_ADD(0, 8); CSR_ADD(1, 8); CSR_ADD(2, 8); CSR_ADD(3, 8); }
-        if (rounds > 12) { CSR_ADD(4, 8); CSR_ADD(5, 8); CSR_ADD(6, 8); CSR_ADD(7, 8); }
+        if constexpr (kPair) {
+#define CSR_LOAD2(U) b[U] = load(row_pair<U>(off))
+#define CSR_ADD2(U) add(row_pair<U>(a), b[U])
+            CSR_LOAD2(0); CSR_LOAD2(1); CSR_LOAD2(2); CSR_LOAD2(3);
+            if (rounds > 8) { CSR_LOAD2(4); CSR_LOAD2(5); CSR_LOAD2(6); CSR_LOAD2(7); }
+            CSR_ADD2(0); CSR_ADD2(1); CSR_ADD2(2); CSR_ADD2(3);
+            if (rounds > 8) { CSR_ADD2(4); CSR_ADD2(5); CSR_ADD2(6); CSR_ADD2(7); }
+#undef CSR_LOAD2
+#undef CSR_ADD2
+        } else {
+            CSR_LOAD(0, 0); CSR_LOAD(1, 0); CSR_LOAD(2, 0); CSR_LOAD(3, 0);
+            if (rounds > 4) { CSR_LOAD(4, 0); CSR_LOAD(5, 0); CSR_LOAD(6, 0); CSR_LOAD(7, 0); }
+            CSR_ADD(0, 0); CSR_ADD(1, 0); CSR_ADD(2, 0); CSR_ADD(3, 0);
+            if (rounds > 8) { CSR_LOAD(0, 8); CSR_LOAD(1, 8); CSR_LOAD(2, 8); CSR_LOAD(3, 8); }
+            if (rounds > 4) { CSR_ADD(4, 0); CSR_ADD(5, 0); CSR_ADD(6, 0); CSR_ADD(7, 0); }
+            if (rounds > 12) { CSR_LOAD(4, 8); CSR_LOAD(5, 8); CSR_LOAD(6, 8); CSR_LOAD(7, 8); }
+            if (rounds > 8) { CSR_ADD(0, 8); CSR_ADD(1, 8); CSR_ADD(2, 8); CSR_ADD(3, 8); }
+            if (rounds > 12) { CSR_ADD(4, 8); CSR_ADD(5, 8); CSR_ADD(6, 8); CSR_ADD(7, 8); }
+        }
 #undef CSR_LOAD
 #undef CSR_ADD
+    }
+    if constexpr (kPair) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] += __shfl_xor(acc[i], 8);
     }
     if (parts > 1) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            if constexpr (LANES == 16) acc[i] += __shfl_xor(acc[i], 16);
+            if constexpr (LANES <= 16) acc[i] += __shfl_xor(acc[i], 16);
             acc[i] += __shfl_xor(acc[i], 32);
         }
     }
@@ -176,6 +199,12 @@ __global__ void __launch_bounds__(kCsrThreads) csr_spmm_kernel(const CsrParams p
     if (parts > 1 && g != 0) return;
     const int n = n0 + chunk0 * 8;
     if (row < 0 || n >= p.N) return;
+    if constexpr (kPair) {                                           // each half of the 16 lanes stores four of the eight columns
+        const int hi = lane >> 3 & 1;
+        const float4v out = hi ? float4v{acc[4], acc[5], acc[6], acc[7]} : float4v{acc[0], acc[1], acc[2], acc[3]};
+        __builtin_nontemporal_store(out, reinterpret_cast<float4v *>(p.C + row * p.ldc + n + 4 * hi));
+        return;
+    }
     float *c = p.C + row * p.ldc + n;
     __builtin_nontemporal_store(float4v{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<float4v *>(c));
     __builtin_nontemporal_store(float4v{acc[4], acc[5], acc[6], acc[7]}, reinterpret_cast<float4v *>(c + 4));
@@ -273,8 +302,13 @@ extern "C" int csr_spmm(const csr_dev_t *h, const void *B_dev, int64_t ldb, floa
     p.b_bytes = wide ? 0 : (uint32_t)b_bytes;
     p.n_rows = (int32_t)h->n_rows;
     p.N = (int32_t)N;
-    // 32 lanes a row: a column tile of 256 columns within half an L2 (4 MiB), or rows that start inside a cache line
-    const int lanes = N > 128 && (h->n_cols * 512 <= (2 << 20) || ldb % 64 != 0 || (reinterpret_cast<uintptr_t>(B_dev) & 127) != 0) ? 32 : 16;
+    // Lanes a row, i.e. columns a wave (8 per lane): narrow tiles keep the B that a tile touches smallest and give many waves,
+    // wide ones fetch and store B and C in longer pieces, which is what counts once they come from memory.  Measured with 64 / 128
+    // / 256 columns: 32768 x 32768, 16 entries a row, N = 256: 28.8 / 32 / 38 us; graph of 16384 nodes, N = 256: 22 / 26 / 37,
+    // N = 4096: 358 / 253 / 208, of 4096 nodes, N = 2048: 33 / 29 / 34; 224 entries a row, N = 512: 213 / 185 / 213, 388, N = 1024:
+    // 365 / 270 / 241.  Rows of B that start inside a cache line lie in one line more, which 64 columns pay twice.
+    const bool aligned = ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0;
+    const int lanes = N <= 64 || (N <= 256 && aligned) ? 8 : N > 128 && (!aligned || (N >= 1024 && h->nnz * N >= ((int64_t)1 << 29))) ? 32 : 16;
     p.n_ntiles = (int32_t)((N + 8 * lanes - 1) / (8 * lanes));
     // A workgroup for a row costs its barrier and the fourfold sum; it pays where one wave would still be at the row when
     // the rest is done, i.e. beyond the share of all entries that one of 4096 waves takes (graph, N = 256: 66 -> 26 us;
@@ -286,18 +320,18 @@ extern "C" int csr_spmm(const csr_dev_t *h, const void *B_dev, int64_t ldb, floa
     const int64_t n_huge = longer_than(huge_len), n_long = longer_than(vbrk::kCsrLongRow) - n_huge;
     p.n_huge = (int32_t)n_huge;
     p.n_long = (int32_t)n_long;
-    const int64_t rest = h->n_rows - n_huge - n_long, waves = 4 * n_huge + n_long + (rest * lanes + 63) / 64;
+    const int64_t rest = h->n_rows - n_huge - n_long, waves = 4 * n_huge + n_long + (rest * std::max(lanes, 16) + 63) / 64;
     p.n_waves = (int32_t)waves;
     const int64_t T = (waves + 3) / 4, Q = p.n_ntiles;
     const int64_t grid = Q >= 8 ? 8 * ((Q + 7) / 8) * T : 8 * ((T + 8 / Q - 1) / (8 / Q));
     if (waves > INT32_MAX || grid > INT32_MAX) return VBR_EUNSUPPORTED;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const int variant = (h->dtype == VBR_F16 ? 0 : 4) + (wide ? 2 : 0) + (lanes == 32 ? 1 : 0);
-    void (*const kernels[8])(vbrk::CsrParams) = {
-        vbrk::csr_spmm_kernel<VBR_F16, false, 16>, vbrk::csr_spmm_kernel<VBR_F16, false, 32>,
-        vbrk::csr_spmm_kernel<VBR_F16, true, 16>, vbrk::csr_spmm_kernel<VBR_F16, true, 32>,
-        vbrk::csr_spmm_kernel<VBR_BF16, false, 16>, vbrk::csr_spmm_kernel<VBR_BF16, false, 32>,
-        vbrk::csr_spmm_kernel<VBR_BF16, true, 16>, vbrk::csr_spmm_kernel<VBR_BF16, true, 32>};
+    const int variant = (h->dtype == VBR_F16 ? 0 : 6) + (wide ? 3 : 0) + (lanes == 32 ? 2 : lanes == 16 ? 1 : 0);
+    void (*const kernels[12])(vbrk::CsrParams) = {
+        vbrk::csr_spmm_kernel<VBR_F16, false, 8>, vbrk::csr_spmm_kernel<VBR_F16, false, 16>, vbrk::csr_spmm_kernel<VBR_F16, false, 32>,
+        vbrk::csr_spmm_kernel<VBR_F16, true, 8>, vbrk::csr_spmm_kernel<VBR_F16, true, 16>, vbrk::csr_spmm_kernel<VBR_F16, true, 32>,
+        vbrk::csr_spmm_kernel<VBR_BF16, false, 8>, vbrk::csr_spmm_kernel<VBR_BF16, false, 16>, vbrk::csr_spmm_kernel<VBR_BF16, false, 32>,
+        vbrk::csr_spmm_kernel<VBR_BF16, true, 8>, vbrk::csr_spmm_kernel<VBR_BF16, true, 16>, vbrk::csr_spmm_kernel<VBR_BF16, true, 32>};
     hipLaunchKernelGGL(kernels[variant], dim3((unsigned)grid), dim3(vbrk::kCsrThreads), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { vbrk::set_last_hip_error((int)e); return VBR_EHIP; }

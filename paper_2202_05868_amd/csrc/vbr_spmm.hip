@@ -12,7 +12,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cstdlib>
 #include <cstdint>
 #include <type_traits>
 
@@ -431,9 +430,8 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
 constexpr int kDeepN = 64;                        // C columns per workgroup of a deep tile
 constexpr int kDeepRow = kDeepN * 2;              // one staged B row: 128 bytes
 constexpr int kDeepList = kStepK * 4;             // the list entries of a K-step
-constexpr int kDeepSlots = 2;                     // three workgroups on a CU
-template <int S>
-constexpr int deep_wave_bytes() { return kDeepSlots * (kStepK * kDeepRow + S * kFragBytes + kDeepList); }
+template <int S, int SLOTS>
+constexpr int deep_wave_bytes() { return SLOTS * (kStepK * kDeepRow + S * kFragBytes + kDeepList); }
 
 // A deep tile: a gathered tile of one or two slabs whose column list is so long that a workgroup of the tile kernel, which
 // takes the K-steps one after the other, would still be at it when the rest of the launch is done (a hub of a graph:
@@ -441,7 +439,7 @@ constexpr int deep_wave_bytes() { return kDeepSlots * (kStepK * kDeepRow + S * k
 // K-steps in turn, each with an LDS ring of its own and without a barrier; the four partial sums are added in LDS, in
 // a fixed order.  The price is S fragments per 64 columns instead of per 256: 24 loads per K-step for two slabs
 // instead of 18.
-template <int DT, int S>
+template <int DT, int S, int SLOTS>
 __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, const int n0, unsigned char *smem)
 {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -450,9 +448,9 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
     const lds_u8_ptr sm = (lds_u8_ptr)smem;
     const int q = lane >> 4, s16 = lane & 15;
     constexpr int kB = kStepK * kDeepRow, kA = S * kFragBytes;
-    const lds_u8_ptr mine = sm + wave * deep_wave_bytes<S>();
+    const lds_u8_ptr mine = sm + wave * deep_wave_bytes<S, SLOTS>();
     const uint32_t base = (uint32_t)(uintptr_t)mine;             // [B slots][A slots][list slots]
-    const lds_u8_ptr lists = mine + kDeepSlots * (kB + kA);
+    const lds_u8_ptr lists = mine + SLOTS * (kB + kA);
     const int n_ks = td.n_ks;
 
     float4v acc[S][4];
@@ -472,7 +470,7 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
     const char *Abase = reinterpret_cast<const char *>(p.vals) + td.a_off * 16;
     const int32_t *list = p.gcol + (int64_t)td.ks_begin * kStepK;
     auto issue_list = [&](int ks, int slot) {
-        if (lane < kStepK) dma4(list + (int64_t)ks * kStepK + lane, base + kDeepSlots * (kB + kA) + slot * kDeepList);
+        if (lane < kStepK) dma4(list + (int64_t)ks * kStepK + lane, base + SLOTS * (kB + kA) + slot * kDeepList);
     };
     auto issue = [&](int ks, int slot) {
         int32_t e[4];
@@ -486,7 +484,7 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
             const int sl = s < td.n_slabs ? s : td.n_slabs - 1;               // no second slab: the first again, never stored
             const int rows = sl == td.n_slabs - 1 ? rows_last : kSlabRows;
             if (s16 < rows) dma16_base((uint32_t)((sl * kFragElems + (q * rows + s16) * 8) * 2), Abase + (int64_t)ks * a_stride_bytes,
-                                       base + kDeepSlots * kB + slot * kA + s * kFragBytes);
+                                       base + SLOTS * kB + slot * kA + s * kFragBytes);
         }
     };
     uint32_t b_off[4];
@@ -501,10 +499,10 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
     // The wave's own K-steps, 0 .. steps-1, are wave, wave + 4, ...  Iteration j issues the rows and fragments of step
     // j + P and the list of step j + 2 P (clamped to the last): P steps are in flight while one is multiplied, and a
     // list is there when its rows are requested.
-    constexpr int P = kDeepSlots - 1, kPerStep = 4 + S + 1;
+    constexpr int P = SLOTS - 1, kPerStep = 4 + S + 1;
     static_assert((P - 1) * kPerStep < 64, "vmcnt is a 6-bit counter");
     const int steps = wave < n_ks ? (n_ks - wave + 3) / 4 : 0;
-    auto list_at = [&](int j) { issue_list(wave + 4 * (j < steps ? j : steps - 1), j % kDeepSlots); };
+    auto list_at = [&](int j) { issue_list(wave + 4 * (j < steps ? j : steps - 1), j % SLOTS); };
     if (steps > 0) {
 #pragma unroll
         for (int t = 0; t < P; ++t) list_at(t);
@@ -519,7 +517,7 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
             if (j + P <= steps) wait_vmcnt<(P - 1) * kPerStep>();     // everything up to the rows and fragments of step j
             else wait_vmcnt<0>();
             short8v bfrag[4], afrag[S];
-            const lds_u8_ptr sb = mine + slot * kB, sa = mine + kDeepSlots * kB + slot * kA;
+            const lds_u8_ptr sb = mine + slot * kB, sa = mine + SLOTS * kB + slot * kA;
 #pragma unroll
             for (int f = 0; f < 4; ++f) {
                 const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(sb + b_off[f]));
@@ -566,10 +564,10 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
     }
 }
 
-template <int S>
+template <int S, int SLOTS>
 constexpr int deep_lds_bytes()
 {
-    const int ring = 4 * deep_wave_bytes<S>(), out = 4 * S * kSlabRows * (kDeepN * 4 + 16);
+    const int ring = 4 * deep_wave_bytes<S, SLOTS>(), out = 4 * S * kSlabRows * (kDeepN * 4 + 16);
     return ring > out ? ring : out;
 }
 
@@ -595,11 +593,11 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_kernel(const Params p)
 // Tiles of several classes in one launch: the workgroup picks the code of its tile's class.  Registers and LDS are those of
 // the largest: for block tiles of up to 4 slabs (MAXS) 50 KiB, three workgroups on a CU, and with 5 to 8 slabs 64 KiB, two,
 // which leaves the 3 to 4 slab class its ring of three.
-template <int DT, int MAXS>
+template <int DT, int MAXS, int SLOTS>
 __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p)
 {
     constexpr int NS = kStages, DA = kADistance, NS4 = MAXS == 8 ? kStagesTall : kStages;
-    constexpr int kGather = std::max(tile_lds_bytes<4, NS, DA>(true), deep_lds_bytes<2>());
+    constexpr int kGather = std::max(tile_lds_bytes<4, NS, DA>(true), deep_lds_bytes<2, SLOTS>());
     constexpr int kLds = std::max(kGather, std::max(tile_lds_bytes<MAXS, NS, DA>(), tile_lds_bytes<4, NS4, DA>()));
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
     int tile, ntile;
@@ -607,8 +605,8 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
     const TileDesc td = p.tiles[tile];
     if (td.group <= kTileDeep) {
         const int n0 = ntile * kTileN + (kTileDeep - td.group) * kDeepN;
-        if (td.n_slabs <= 1) deep_body<DT, 1>(p, td, n0, smem);
-        else deep_body<DT, 2>(p, td, n0, smem);
+        if (td.n_slabs <= 1) deep_body<DT, 1, SLOTS>(p, td, n0, smem);
+        else deep_body<DT, 2, SLOTS>(p, td, n0, smem);
     } else if (td.group == kTileGathered) {
         if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA, true>(p, td, ntile, smem);
         else if (td.n_slabs <= 2) tile_body<DT, 2, NS, DA, true>(p, td, ntile, smem);
@@ -834,8 +832,12 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             hipLaunchKernelGGL((vbr_spmm_panel_kernel<DT, 8, 4, 3>), grid, dim3(kPanelThreads), 0, stream, pp);
             break;
         case VBR_LAUNCH_TILE_MIXED:
-            if (v->class_count[3] > 0) hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, 8>), grid, dim3(kThreads), 0, stream, p);
-            else hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, 4>), grid, dim3(kThreads), 0, stream, p);
+            if (v->class_count[3] > 0) hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, 8, 2>), grid, dim3(kThreads), 0, stream, p);
+            // Deep rings of three cost the third workgroup on a CU and shorten the longest chain by a third: worth it up to three
+            // rounds of the 512 resident workgroups (graph of 16384 nodes: N = 512 47 -> 34 us, N = 2048 70 -> 78).
+            else if (v->class_count[kClassDeep] > 0 && (int64_t)p.n_tiles * p.n_ntiles <= 1536)
+                hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, 4, 3>), grid, dim3(kThreads), 0, stream, p);
+            else hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, 4, 2>), grid, dim3(kThreads), 0, stream, p);
             break;
         case VBR_LAUNCH_GATHER_1:
             hipLaunchKernelGGL((vbr_spmm_kernel<DT, 1, kStages, kADistance, true>), grid, dim3(kThreads), 0, stream, p);
