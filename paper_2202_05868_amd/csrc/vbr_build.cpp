@@ -291,6 +291,7 @@ Builder::Kind Builder::kind_of(Scratch &s, int64_t r0, int64_t r1, int64_t n_blo
 {
     const int64_t h = r1 - r0, n_ks = steps_of(n_blocks * cb), slabs = (h + kSlabRows - 1) / kSlabRows;
     if (h < kSlabRows) return kLow;
+    if (cb % 8 != 0) return kGathered;         // a wave loads 8 B rows of one granule
     const int64_t nt = (slabs + kMaxSlabs - 1) / kMaxSlabs;
     int64_t by_blocks = 0, by_columns = 0;
     for (int64_t t = 0; t < nt; ++t) by_blocks += n_ks * kBlockStepNs[slab_class((int)(slabs / nt + (t < slabs % nt ? 1 : 0)))];
@@ -342,8 +343,8 @@ int Builder::block_tiles()
             const int64_t n = (v->ks_ptr[g + 1] - v->ks_ptr[g]) * per_step, Kg = (v->blk_ptr[g + 1] - v->blk_ptr[g]) * cb;
             int32_t *out = v->krow.data() + v->ks_ptr[g] * per_step;
             for (int64_t e = 0; e < n; ++e) {
-                const int64_t k = e * gran;
-                out[e] = k < Kg ? (int32_t)((int64_t)v->blk_col[(size_t)(v->blk_ptr[g] + k / cb)] * cb + k % cb) : -1;
+                const int64_t k = std::min(e * gran, Kg - gran);      // the last K-step is filled up with the last granule (times zeros)
+                out[e] = (int32_t)((int64_t)v->blk_col[(size_t)(v->blk_ptr[g] + k / cb)] * cb + k % cb);
             }
         }
     });
@@ -1003,7 +1004,8 @@ extern "C" int vbr_audit(const vbr_t *v)
     for (int64_t i = 0; i < M; ++i)
         if (v->perm[i] < 0 || v->perm[i] >= M) return VBR_EINVAL;
     for (const int32_t e : v->krow)
-        if (e < -1 || (e >= 0 && (int64_t)e + gran > K)) return VBR_EINVAL;
+        if (e < 0 || (int64_t)e + gran > K) return VBR_EINVAL;
+    if (v->lg_gran < 3 && !v->krow.empty()) return VBR_EINVAL;      // the kernel takes whole groups of 8 rows
     if ((int64_t)v->krow.size() % per_step != 0) return VBR_EINVAL;
     const int64_t total_ks = (int64_t)v->krow.size() / per_step;
     if (v->n_work < 0 || v->n_work > (int32_t)v->dev_tiles.size()) return VBR_EINVAL;

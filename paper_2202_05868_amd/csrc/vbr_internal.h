@@ -111,7 +111,7 @@ struct vbr {
     // kernel-side data
     int32_t lg_gran = 0;                 // log2 of the B-row gather granularity (rows per krow entry)
     std::vector<int64_t> ks_ptr;         // [n_groups+1] first global K-step of each group
-    std::vector<int32_t> krow;           // first B row of each granule of each K-step, -1 = padding
+    std::vector<int32_t> krow;           // first B row of each granule of each K-step (granules of 8 rows or more), the last one repeated to the end
     std::vector<vbrk::TileDesc> tiles;    // block tiles, group by group
     std::vector<int64_t> group_first_tile;      // [n_groups+1] tiles of a group in `tiles`
     std::vector<vbrk::TileDesc> dev_tiles;      // `tiles` and `gtiles` as the device holds them: longest first, deep ones four times,

@@ -125,10 +125,14 @@ __device__ __forceinline__ bool map_workgroup(int T, int Q, int &tile, int &ntil
     return tile < T;
 }
 
-constexpr int kListSteps = 8;                     // K-steps whose column lists a wave of a gathered tile requests with one load
-constexpr int kListBytes = 2 * 4 * kListSteps * 8 * 4;   // two such lists for each of the 4 waves, 8 columns per K-step
-template <int S, int NS, int DA>
-constexpr int tile_lds_bytes(bool gather = false) { return NS * kPanelBytes + (DA + 1) * S * kFragBytes + (gather ? kListBytes : 0); }
+// B rows of the next K-steps, in LDS: one load of a wave brings those of 8 K-steps of a gathered tile (8 columns each) or of
+// 64 of a block tile (one granule each); two such lists for each of the 4 waves.
+constexpr int kListBytes = 2 * 4 * 64 * 4;
+// With 5 to 8 slabs there is no room for them beside two workgroups on a CU.
+template <int S, bool GATHER>
+constexpr bool has_lists() { return GATHER || S < 8; }
+template <int S, int NS, int DA, bool GATHER>
+constexpr int tile_lds_bytes() { return NS * kPanelBytes + (DA + 1) * S * kFragBytes + (has_lists<S, GATHER>() ? kListBytes : 0); }
 
 // GATHER: the tile is a slab of rows of low row groups whose K dimension is the list of the single
 // COLUMNS its rows touch (one gather entry per B row, krow = that list) instead of whole column
@@ -136,7 +140,8 @@ constexpr int tile_lds_bytes(bool gather = false) { return NS * kPanelBytes + (D
 template <int DT, int S, int NS, int DA, bool GATHER = false>
 __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, const int ntile, unsigned char *smem)
 {
-    static_assert(NS >= 2 && DA >= NS - 1, "A must be requested before the B panel of its K-step");
+    static_assert(NS >= 2 && DA >= NS, "A must be requested before the B panel of its K-step");
+    constexpr bool kLists = has_lists<S, GATHER>();
     constexpr int NA = S >= 4 ? S / 4 : 1;      // A loads per wave per K-step
     constexpr int NAS = DA + 1;
     constexpr int kAStage = S * kFragBytes;
@@ -150,7 +155,6 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
     const int n0 = ntile * kTileN;
     const lds_u8_ptr sm = (lds_u8_ptr)smem;
     const uint32_t smem_base = (uint32_t)(uintptr_t)sm;      // LDS byte address, for M0
-    const char *zeros = reinterpret_cast<const char *>(p.zeros);
     const int n_ks = td.n_ks;
     const int q = lane >> 4, s16 = lane & 15;
 
@@ -168,25 +172,18 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
         const int half = lane >> 5;
         const int lg = p.lg_gran;
         const int gmask = (1 << lg) - 1;
-        const const_i32_ptr krow = (const_i32_ptr)p.krow + (int64_t)td.ks_begin * (kStepK >> lg);
         const uint32_t ldb_bytes = (uint32_t)(p.ldb * 2);          // host checked: 32 rows of B span less than 2^32 bytes
         const char *Btile = reinterpret_cast<const char *>(p.B) + (int64_t)n0 * 2;
         // In the last column tile the chunks at or beyond column N do not exist: their lanes fetch
         // the tile's last existing chunk again (the C columns it would feed are never stored, and
-        // columns do not mix), so the fast path serves partial tiles too.
-        const bool tile_fast = lg >= 3;
+        // columns do not mix).
         const int last_chunk = (p.N - n0 < kTileN ? p.N - n0 : kTileN) / 8 - 1;
-        uint32_t b_col[4];       // byte offset of this lane's chunk from the tile's first column
-        uint32_t b_lane[4];      // fast path: offset of this lane's 16 bytes from the first row of the wave's granule
-        bool b_col_ok[4];
-        uint32_t b_coff[4];      // column-gathered tiles: the same, clamped to the tile's last existing chunk
+        uint32_t b_lane[4];      // offset of this lane's 16 bytes from the first row of the wave's granule; gathered tiles: from the row
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int chunk = (lane & 31) ^ (2 * (2 * i + half));
-            b_col[i] = chunk * 16;
-            b_col_ok[i] = chunk <= last_chunk;
-            b_coff[i] = (uint32_t)(chunk <= last_chunk ? chunk : last_chunk) * 16;      // past column N: the last chunk again
-            b_lane[i] = (uint32_t)((8 * wave + 2 * i + half) & gmask) * ldb_bytes + (chunk <= last_chunk ? chunk : last_chunk) * 16;
+            b_lane[i] = (uint32_t)(chunk <= last_chunk ? chunk : last_chunk) * 16;
+            if constexpr (!GATHER) b_lane[i] += (uint32_t)((8 * wave + 2 * i + half) & gmask) * ldb_bytes;
         }
 
         // ---- A staging.  A direct-to-LDS load costs the CU the same whatever its lane mask, so a
@@ -219,56 +216,53 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
             else return true;
         };
 
-        // First B row of the granule holding this wave's 8 rows (blocks at least 8 wide), for the
-        // K-step whose B loads are issued next (rb0) and the one after (rb1): scalar loads, issued
-        // two iterations ahead of their use.  Narrower blocks look their rows up per lane at issue
-        // time instead, with an ordinary load the compiler waits for (slow, but rare and simple).
-        int32_t rb0 = -1, rb1 = -1;
-        auto load_rows = [&](int ks) -> int32_t {
+        // The B rows of a K-step: of a block tile the first row of the granule that holds this wave's 8 rows, of a gathered one
+        // its 8 columns.  The wave fetches them into LDS for many K-steps with one load and reads them a K-step before their
+        // loads are issued.  (As scalar loads, one per K-step, they were waited for in every K-step; those of gathered tiles
+        // missed the scalar cache every time: noisy planted matrix 36 -> 29 us.)
+        constexpr int kSteps = GATHER ? 8 : 64;
+        int32_t ent[4] = {0, 0, 0, 0};
+        const lds_u8_ptr lists = sm + kBRing + NAS * kAStage + wave * (kListBytes / 4);
+        auto issue_list = [&](int batch) {
+            int k = batch * kSteps + (GATHER ? lane >> 3 : lane);
+            if (k > n_ks - 1) k = n_ks - 1;
+            const int32_t *src = GATHER ? p.gcol + ((int64_t)td.ks_begin + k) * kStepK + 8 * wave + (lane & 7)
+                                        : p.krow + ((((int64_t)td.ks_begin + k) * kStepK + 8 * wave) >> lg);
+            dma4(src, smem_base + kBRing + NAS * kAStage + wave * (kListBytes / 4) + (batch & 1) * (kListBytes / 8));
+        };
+        auto read_list = [&](int ks) {
+            if constexpr (GATHER) {
+                const lds_u8_ptr at = lists + (ks & (2 * kSteps - 1)) * 32 + half * 4;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ent[i] = *(lds_i32_ptr)(at + i * 8);
+            } else {
+                ent[0] = *(lds_i32_ptr)(lists + (ks & (2 * kSteps - 1)) * 4);
+            }
+        };
+        // Without lists: scalar loads, two K-steps ahead of their use.
+        int32_t rb0 = 0, rb1 = 0;
+        auto load_row = [&](int ks) -> int32_t {
             // past the end: reload the last K-step (never computed); wave-uniform, and said so, or the
             // lookups below become vector loads, which cost the load path as much as a load of B
             const int kc = __builtin_amdgcn_readfirstlane(ks < n_ks ? ks : n_ks - 1);
-            return lg >= 3 ? krow[(kc * kStepK + 8 * wave) >> lg] : -1;
+            return ((const_i32_ptr)p.krow)[(((int64_t)td.ks_begin + kc) * kStepK + 8 * wave) >> lg];
         };
-        // Column-gathered tiles: the wave's 8 columns of a K-step lie in LDS, fetched by the wave itself for 8 K-steps with
-        // one load (scalar loads of them, one per K-step, missed the scalar cache every time and were waited for in
-        // every K-step: what each lane needs for the K-step after next is read one K-step ahead instead).
-        int32_t ent[4] = {-1, -1, -1, -1};
-        const lds_u8_ptr lists = sm + kBRing + NAS * kAStage + wave * (kListBytes / 4);
-        auto issue_list = [&](int batch) {
-            const int k = batch * kListSteps + (lane >> 3);
-            dma4(p.gcol + ((int64_t)td.ks_begin + (k < n_ks ? k : n_ks - 1)) * kStepK + 8 * wave + (lane & 7),
-                 smem_base + kBRing + NAS * kAStage + wave * (kListBytes / 4) + (batch & 1) * (kListBytes / 8));
-        };
-        auto read_list = [&](int ks) {
-            const lds_u8_ptr at = lists + (ks & (2 * kListSteps - 1)) * 32 + half * 4;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) ent[i] = *(lds_i32_ptr)(at + i * 8);
-        };
-        auto issue_b = [&](int ks, int slot) {
+        auto issue_b = [&](int slot) {
             const uint32_t sb = smem_base + slot * kPanelBytes + 8 * wave * kRowBytes;
             if constexpr (GATHER) {
                 // (behind the last column of the tile the list repeats it: the fragments hold zeros there)
                 if (p.b_fits24) {        // scalar base + 32-bit lane offsets, the cheaper form of the load
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) dma16_base(__umul24((uint32_t)ent[i], ldb_bytes) + b_coff[i], Btile, sb + 2 * i * kRowBytes);
+                    for (int i = 0; i < 4; ++i) dma16_base(__umul24((uint32_t)ent[i], ldb_bytes) + b_lane[i], Btile, sb + 2 * i * kRowBytes);
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) dma16(Btile + (uint64_t)(uint32_t)ent[i] * ldb_bytes + b_coff[i], sb + 2 * i * kRowBytes);
+                    for (int i = 0; i < 4; ++i) dma16(Btile + (uint64_t)(uint32_t)ent[i] * ldb_bytes + b_lane[i], sb + 2 * i * kRowBytes);
                 }
-            } else if (tile_fast && rb0 >= 0) {
-                const char *rowptr = Btile + (uint64_t)(uint32_t)rb0 * ldb_bytes;          // scalar, 64-bit
+            } else {
+                const int32_t row = kLists ? __builtin_amdgcn_readfirstlane(ent[0]) : rb0;
+                const char *rowptr = Btile + (uint64_t)(uint32_t)row * ldb_bytes;          // scalar, 64-bit
 #pragma unroll
                 for (int i = 0; i < 4; ++i) dma16_base(b_lane[i], rowptr, sb + 2 * i * kRowBytes);
-            } else {         // narrow blocks, padding rows or column tail: zeros come from the zero page
-                const int kc = ks < n_ks ? ks : n_ks - 1;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int r = 8 * wave + 2 * i + half;
-                    const int e = lg >= 3 ? rb0 : p.krow[(int64_t)td.ks_begin * (kStepK >> lg) + ((kc * kStepK + r) >> lg)];
-                    const char *src = (e >= 0 && b_col_ok[i]) ? Btile + (int64_t)(e + (r & gmask)) * ldb_bytes + b_col[i] : zeros;
-                    dma16(src, sb + 2 * i * kRowBytes);
-                }
             }
         };
         auto issue_a = [&](int ks, int slot) {
@@ -338,27 +332,27 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
         // iterations early: A(0 .. DA-NS), then B(t), A(DA-NS+1+t) for t = 0 .. NS-2; iteration ks
         // then issues B(ks+NS-1), A(ks+DA).  The prologue re-loads the last K-step for K-steps past the
         // end of a very short tile, so that the loop always starts with the same loads in flight.
-        if constexpr (GATHER) {
+        if constexpr (kLists) {
             issue_list(0);
-            if (n_ks > kListSteps) issue_list(1);
+            if (n_ks > kSteps) issue_list(1);
         } else {
-            rb0 = load_rows(0);
-            rb1 = load_rows(1);
+            rb0 = load_row(0);
+            rb1 = load_row(1);
         }
 #pragma unroll
         for (int k = 0; k <= DA - NS; ++k) issue_a(k, k);
-        if constexpr (GATHER) {
+        if constexpr (kLists) {
             wait_vmcnt<0>();
             read_list(0);
         }
 #pragma unroll
         for (int t = 0; t < NS - 1; ++t) {
-            issue_b(t, t);
-            if constexpr (GATHER) {
+            issue_b(t);
+            if constexpr (kLists) {
                 read_list(t + 1);
             } else {
                 rb0 = rb1;
-                rb1 = load_rows(t + 2);
+                rb1 = load_row(t + 2);
             }
             issue_a(DA - NS + 1 + t, DA - NS + 1 + t);
         }
@@ -370,25 +364,25 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
             if (ks + DA > n_ks) wait_vmcnt<0>();
             else wait_stage(ks);                   // this wave's loads of K-step ks have landed
             __builtin_amdgcn_s_barrier();          // ... and everybody else's; the slots of K-step ks-1 are free
-            if constexpr (!GATHER) asm volatile("" ::"s"(rb0));      // the scalar row lookup is waited for here, not behind the LDS reads
+            if constexpr (!kLists) asm volatile("" ::"s"(rb0));      // the scalar row lookup is waited for here, not behind the LDS reads
             read_frags(bslot, aslot);
             // the load path is what bounds the kernel: a wave that is about to issue its loads goes
             // ahead of the waves that are multiplying (measured: 3-4 % on the 16-row workload)
             __builtin_amdgcn_s_setprio(3);
-            if (ks + NS - 1 < n_ks) issue_b(ks + NS - 1, bslot == 0 ? NS - 1 : bslot - 1);
+            if (ks + NS - 1 < n_ks) issue_b(bslot == 0 ? NS - 1 : bslot - 1);
             if (ks + DA < n_ks) issue_a(ks + DA, aslot == 0 ? NAS - 1 : aslot - 1);
-            if constexpr (GATHER) {
+            if constexpr (kLists) {
                 // the next list but one, into the place of the one whose last K-step has been read (an extra load in
                 // flight only makes the counted waits stricter)
                 const int next = ks + NS;
-                if ((next & (kListSteps - 1)) == 1 && (next / kListSteps + 1) * kListSteps < n_ks) issue_list(next / kListSteps + 1);
+                if ((next & (kSteps - 1)) == 1 && (next / kSteps + 1) * kSteps < n_ks && next > kSteps) issue_list(next / kSteps + 1);
                 read_list(next);
             }
             __builtin_amdgcn_s_setprio(0);
             multiply();
-            if constexpr (!GATHER) {
+            if constexpr (!kLists) {
                 rb0 = rb1;
-                rb1 = load_rows(ks + NS + 1);
+                rb1 = load_row(ks + NS + 1);
             }
             bslot = bslot == NS - 1 ? 0 : bslot + 1;
             aslot = aslot == NAS - 1 ? 0 : aslot + 1;
@@ -410,7 +404,7 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
     }
     if (n_ks > 0) __syncthreads();                  // the rings are read no more
     constexpr int kOutRow = kWaveN * 4 + 16;
-    static_assert(4 * kSlabRows * kOutRow <= tile_lds_bytes<S, NS, DA>(), "the turned slabs of the four waves fit the rings");
+    static_assert(4 * kSlabRows * kOutRow <= tile_lds_bytes<S, NS, DA, GATHER>(), "the turned slabs of the four waves fit the rings");
     const lds_u8_ptr out = sm + wave * kSlabRows * kOutRow;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -576,7 +570,9 @@ constexpr int kStagesTall = 3;  // the same for block tiles of 5 to 8 slabs (80 
                                 // to 14 % (K = 8 192) faster than 2 on dense matrices; and of 3 to 4 slabs (64 KiB, two per CU): blocks of
                                 // 64 x 64 at 40 %, N = 2048: 144 -> 126 us, at 5 %: 17.4 -> 16.0, N = 8192 the same; slower
                                 // than 2 for the lower classes, and for gathered tiles, which want the third workgroup
-constexpr int kADistance = 3;   // K-steps the A fragments are requested ahead
+constexpr int kStagesFew = 4;   // for tiles of 1 and 2 slabs in a launch whose workgroups are all resident with two on a CU
+constexpr int kADistance = 3;   // K-steps the A fragments are requested ahead (more than the ring of B panels has slots)
+constexpr int a_distance(int stages) { return stages > kADistance ? stages : kADistance; }
 
 // Measured on the 16-row workload: two ring slots and four resident workgroups per CU (36 KiB of
 // LDS each) beat deeper rings with fewer workgroups; the gather is bound by how many independent
@@ -584,22 +580,24 @@ constexpr int kADistance = 3;   // K-steps the A fragments are requested ahead
 template <int DT, int S, int NS, int DA, bool GATHER = false>
 __global__ void __launch_bounds__(kThreads) vbr_spmm_kernel(const Params p)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<S, NS, DA>(GATHER)];
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<S, NS, DA, GATHER>()];
     int tile, ntile;
     if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
     tile_body<DT, S, NS, DA, GATHER>(p, p.tiles[tile], ntile, smem);
 }
 
 // Tiles of several classes in one launch: the workgroup picks the code of its tile's class.  Registers and LDS are those of
-// the largest: for block tiles of up to 4 slabs (MAXS) 50 KiB, three workgroups on a CU, and with 5 to 8 slabs 64 KiB, two,
-// which leaves the 3 to 4 slab class its ring of three.
-template <int DT, int MAXS, int SLOTS>
+// the largest.  MAXS: the tallest block tile.  RING as above, SLOTS for deep tiles.
+template <int DT, int MAXS, int RING, int SLOTS>
 __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p)
 {
-    constexpr int NS = kStages, DA = kADistance, NS4 = MAXS == 8 ? kStagesTall : kStages;
-    constexpr int kGather = std::max(tile_lds_bytes<4, NS, DA>(true), deep_lds_bytes<2, SLOTS>());
-    constexpr int kLds = std::max(kGather, std::max(tile_lds_bytes<MAXS, NS, DA>(), tile_lds_bytes<4, NS4, DA>()));
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
+    constexpr int NS1 = RING, DA1 = a_distance(NS1);
+    constexpr int NSG = RING > kStages ? kStagesTall : kStages;                    // gathered, 3 to 4 slabs
+    constexpr int NS4 = MAXS == 8 ? kStagesTall : NSG, NS8 = RING > kStages ? kStagesTall : kStages;
+    constexpr int kLow = std::max(tile_lds_bytes<2, NS1, DA1, true>(), deep_lds_bytes<2, SLOTS>());
+    constexpr int k4 = std::max(tile_lds_bytes<4, NSG, kADistance, true>(), tile_lds_bytes<4, NS4, kADistance, false>());
+    constexpr int k8 = MAXS == 8 ? tile_lds_bytes<8, NS8, kADistance, false>() : 0;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[std::max(k8, std::max(k4, kLow))];
     int tile, ntile;
     if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
     const TileDesc td = p.tiles[tile];
@@ -608,13 +606,13 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
         if (td.n_slabs <= 1) deep_body<DT, 1, SLOTS>(p, td, n0, smem);
         else deep_body<DT, 2, SLOTS>(p, td, n0, smem);
     } else if (td.group == kTileGathered) {
-        if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA, true>(p, td, ntile, smem);
-        else if (td.n_slabs <= 2) tile_body<DT, 2, NS, DA, true>(p, td, ntile, smem);
-        else tile_body<DT, 4, NS, DA, true>(p, td, ntile, smem);
-    } else if (td.n_slabs <= 1) tile_body<DT, 1, NS, DA>(p, td, ntile, smem);
-    else if (td.n_slabs <= 2) tile_body<DT, 2, NS, DA>(p, td, ntile, smem);
-    else if (MAXS == 4 || td.n_slabs <= 4) tile_body<DT, 4, NS4, DA>(p, td, ntile, smem);
-    else if constexpr (MAXS == 8) tile_body<DT, 8, NS, DA>(p, td, ntile, smem);
+        if (td.n_slabs <= 1) tile_body<DT, 1, NS1, DA1, true>(p, td, ntile, smem);
+        else if (td.n_slabs <= 2) tile_body<DT, 2, NS1, DA1, true>(p, td, ntile, smem);
+        else tile_body<DT, 4, NSG, kADistance, true>(p, td, ntile, smem);
+    } else if (td.n_slabs <= 1) tile_body<DT, 1, NS1, DA1>(p, td, ntile, smem);
+    else if (td.n_slabs <= 2) tile_body<DT, 2, NS1, DA1>(p, td, ntile, smem);
+    else if (MAXS == 4 || td.n_slabs <= 4) tile_body<DT, 4, NS4, kADistance>(p, td, ntile, smem);
+    else if constexpr (MAXS == 8) tile_body<DT, 8, NS8, kADistance>(p, td, ntile, smem);
 }
 
 struct PanelParams {
@@ -827,40 +825,47 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
         p.tiles = base.tiles + L.first_tile;
         p.n_tiles = L.n_tiles;
         const dim3 grid((unsigned)L.grid);
-        switch (L.kind) {
-        case VBR_LAUNCH_PANEL:
+        if (L.kind == VBR_LAUNCH_PANEL) {
             hipLaunchKernelGGL((vbr_spmm_panel_kernel<DT, 8, 4, 3>), grid, dim3(kPanelThreads), 0, stream, pp);
-            break;
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
+            continue;
+        }
+        // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are
+        // resident then and their lists are long (16 x 16 blocks at 12 %, 2048 x 8192, N = 1024: 20.3 -> 18.4 us; a 1024 x 1024 matrix
+        // of at most 19 K-steps a tile: 8.2 -> 8.9).  With deep tiles, whose chain is the longest, up to three rounds
+        // (graph of 16384 nodes: N = 512 47 -> 34 us, N = 2048 70 -> 78).
+        const int64_t workgroups = (int64_t)p.n_tiles * p.n_ntiles;
+        const bool few = v->class_count[kClassDeep] > 0 ? workgroups <= 1536 : workgroups <= 512 && v->dev_tiles[0].n_ks >= 24;
+        void (*kernel)(Params) = nullptr;
+        switch (L.kind) {
         case VBR_LAUNCH_TILE_MIXED:
-            if (v->class_count[3] > 0) hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, 8, 2>), grid, dim3(kThreads), 0, stream, p);
-            // Deep rings of three cost the third workgroup on a CU and shorten the longest chain by a third: worth it up to three
-            // rounds of the 512 resident workgroups (graph of 16384 nodes: N = 512 47 -> 34 us, N = 2048 70 -> 78).
-            else if (v->class_count[kClassDeep] > 0 && (int64_t)p.n_tiles * p.n_ntiles <= 1536)
-                hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, 4, 3>), grid, dim3(kThreads), 0, stream, p);
-            else hipLaunchKernelGGL((vbr_spmm_mixed_kernel<DT, 4, 2>), grid, dim3(kThreads), 0, stream, p);
+            if (v->class_count[3] > 0) kernel = few ? vbr_spmm_mixed_kernel<DT, 8, kStagesFew, 3> : vbr_spmm_mixed_kernel<DT, 8, kStages, 2>;
+            else kernel = few ? vbr_spmm_mixed_kernel<DT, 4, kStagesFew, 3> : vbr_spmm_mixed_kernel<DT, 4, kStages, 2>;
             break;
         case VBR_LAUNCH_GATHER_1:
-            hipLaunchKernelGGL((vbr_spmm_kernel<DT, 1, kStages, kADistance, true>), grid, dim3(kThreads), 0, stream, p);
+            kernel = few ? vbr_spmm_kernel<DT, 1, kStagesFew, kStagesFew, true> : vbr_spmm_kernel<DT, 1, kStages, kADistance, true>;
             break;
         case VBR_LAUNCH_GATHER_2:
-            hipLaunchKernelGGL((vbr_spmm_kernel<DT, 2, kStages, kADistance, true>), grid, dim3(kThreads), 0, stream, p);
+            kernel = few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew, true> : vbr_spmm_kernel<DT, 2, kStages, kADistance, true>;
             break;
         case VBR_LAUNCH_GATHER_4:
-            hipLaunchKernelGGL((vbr_spmm_kernel<DT, 4, kStages, kADistance, true>), grid, dim3(kThreads), 0, stream, p);
+            kernel = few ? vbr_spmm_kernel<DT, 4, kStagesTall, kADistance, true> : vbr_spmm_kernel<DT, 4, kStages, kADistance, true>;
             break;
         case VBR_LAUNCH_TILE_1:
-            hipLaunchKernelGGL((vbr_spmm_kernel<DT, 1, kStages, kADistance>), grid, dim3(kThreads), 0, stream, p);
+            kernel = few ? vbr_spmm_kernel<DT, 1, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 1, kStages, kADistance>;
             break;
         case VBR_LAUNCH_TILE_2:
-            hipLaunchKernelGGL((vbr_spmm_kernel<DT, 2, kStages, kADistance>), grid, dim3(kThreads), 0, stream, p);
+            kernel = few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 2, kStages, kADistance>;
             break;
         case VBR_LAUNCH_TILE_4:
-            hipLaunchKernelGGL((vbr_spmm_kernel<DT, 4, kStagesTall, kADistance>), grid, dim3(kThreads), 0, stream, p);
+            kernel = vbr_spmm_kernel<DT, 4, kStagesTall, kADistance>;
             break;
         default:
-            hipLaunchKernelGGL((vbr_spmm_kernel<DT, 8, kStagesTall, kADistance>), grid, dim3(kThreads), 0, stream, p);
+            kernel = vbr_spmm_kernel<DT, 8, kStagesTall, kADistance>;
             break;
         }
+        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
     }
