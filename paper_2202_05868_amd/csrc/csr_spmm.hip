@@ -1,23 +1,22 @@
-// Comparator kernel: C = A.B straight from CSR (the role the sparse-library routine plays in
-// section 4.4.2 of the paper), one fp32 accumulator per output element, no matrix units.
+// C = A.B row by row from lists of entries, one fp32 accumulator per output element, no matrix units: the comparator (the
+// role the sparse-library routine plays in section 4.4.2 of the paper), and the form vbr_spmm multiplies a matrix in
+// whose blocking found nothing to share.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdint>
-#include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
+#include "host_threads.h"
 #include "vbr_host.h"
 
 struct csr_dev {
     int64_t n_rows = 0, n_cols = 0, nnz = 0;
     int32_t dtype = 0;
-    std::vector<int64_t> row_ptr;
-    std::vector<int32_t> col_idx;
-    std::vector<uint16_t> vals;
-    std::vector<int32_t> order;      // rows, longest first
-    int64_t col_off = 0, val_off = 0, order_off = 0, total = 256;
+    vbrk::EntryRows rows;
+    int64_t row_off = 0, col_off = 0, val_off = 0, total = 256;
     void *dev = nullptr;
 };
 
@@ -25,18 +24,13 @@ namespace vbrk {
 namespace {
 
 constexpr int kCsrThreads = 256;     // 4 waves
-constexpr int kCsrLongRow = 256;     // entries beyond which a row gets a wave of its own ...
-constexpr int kCsrHugeRow = 1024;    // ... and a workgroup of its own
 
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef float float2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-struct CsrParams {
-    const int64_t *row_ptr;
-    const int32_t *col_idx;
-    const uint16_t *vals;
-    const int32_t *order;
+struct EntryParams {
+    EntryRowsDev rows;
     const uint16_t *B;
     float *C;
     int64_t ldb, ldc;
@@ -70,15 +64,15 @@ __device__ __forceinline__ uint32_t row_pair(uint32_t x)     // lane 2U of every
 //   - LANES lanes own a row of A: each 16 of them fetch 16 entries with one load, and every one of the entries is then
 //     handed to all of them by a row broadcast of the vector unit.  Rows are taken longest first, so the rows
 //     of a wave have nearly the same length and the long ones start early;
-//   - rows beyond kCsrLongRow entries get a whole wave, rows beyond kCsrHugeRow a workgroup: its 64 / LANES (256 / LANES)
+//   - rows beyond kEntryLongRow entries get a whole wave, rows beyond kEntryHugeRow a workgroup: its 64 / LANES (256 / LANES)
 //     groups of lanes take the entries in turn, and the partial sums are added at the end.
 // Entries past the end of a row are loads out of the buffer's range: they return zeros and cost no traffic.
-// LANES: 8, 16 or 32 (64, 128 or 256 columns a wave), chosen by csr_spmm.  With 8, the 16 lanes of a row take two entries
+// LANES: 8, 16 or 32 (64, 128 or 256 columns a wave), chosen by plan_entry_rows.  With 8, the 16 lanes of a row take two entries
 // at a time and add their halves at the end.
 // Measured on a graph of 16384 nodes with 426 000 entries (rows of 0 to 3600), with B and C beyond the caches, N = 4096: 680 -> 208 us
 // (17 TB/s of gathered B); N = 256: 329 -> 22 us.  4096 x 16384 with 1638 entries a row, N = 4096: 3.56 -> 1.90 ms (29 TB/s).
 template <int DT, bool WIDE, int LANES>
-__global__ void __launch_bounds__(kCsrThreads) csr_spmm_kernel(const CsrParams p)
+__global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryParams p)
 {
     constexpr bool kPair = LANES == 8;                               // 16 lanes own a row, two entries at a time
     constexpr int kGroups = kPair ? 4 : 64 / LANES, kTileN = 8 * LANES;
@@ -101,10 +95,10 @@ __global__ void __launch_bounds__(kCsrThreads) csr_spmm_kernel(const CsrParams p
     const bool huge = tile < p.n_huge, whole = !huge && wave < 4 * p.n_huge + p.n_long;
     const int parts = huge ? 4 * kGroups : whole ? kGroups : 1, part = huge ? in_wg * kGroups + g : whole ? g : 0;
     const int first = p.n_huge + p.n_long, pos = huge ? tile : whole ? wave - 3 * p.n_huge : first + (wave - 3 * p.n_huge - first) * kGroups + g;
-    const int32_t row = pos < p.n_rows ? p.order[pos] : -1;
-    const int64_t p0 = row >= 0 ? p.row_ptr[row] : 0;
-    const int32_t len = row >= 0 ? (int32_t)(p.row_ptr[row + 1] - p0) : 0;
-    const int32_t max_len = __builtin_amdgcn_readfirstlane(len);    // the first row of a wave is its longest
+    const int32_t row = pos < p.n_rows ? p.rows.row[pos] : -1;
+    const int64_t from = p.rows.start[pos < p.n_rows ? pos : p.n_rows];
+    const int32_t len = (int32_t)(p.rows.start[pos < p.n_rows ? pos + 1 : p.n_rows] - from);
+    const int32_t max_len = __builtin_amdgcn_readfirstlane(len);     // the first row of a wave is its longest
     const int step = 16 * parts;
     const int e0 = parts * s16 + part;                               // this lane's entry of a batch
 
@@ -132,13 +126,11 @@ __global__ void __launch_bounds__(kCsrThreads) csr_spmm_kernel(const CsrParams p
         for (int i = 0; i < 8; ++i) acc[i] = __builtin_fmaf(a, half_to_f32<DT>(b[i >> 1], i & 1), acc[i]);
     };
     auto fetch = [&](int base, int32_t &col, uint32_t &a) {
-        const bool ok = base + e0 < len;
-        const int64_t at = ok ? p0 + base + e0 : 0;
         col = -1;
         a = 0;
-        if (ok) {
-            col = p.col_idx[at];
-            a = p.vals[at];
+        if (base + e0 < len) {
+            col = p.rows.col[from + base + e0];
+            a = p.rows.val[from + base + e0];
         }
     };
     int32_t col;
@@ -151,29 +143,29 @@ __global__ void __launch_bounds__(kCsrThreads) csr_spmm_kernel(const CsrParams p
         const int left = max_len - base;                             // entries of the longest row of the wave
         const int rounds = (left + parts - 1) / parts;
         uint4v b[8];
-#define CSR_LOAD(U, S) b[U] = load(row_lane<U + S>(off))
-#define CSR_ADD(U, S) add(row_lane<U + S>(a), b[U])
         if constexpr (kPair) {
-#define CSR_LOAD2(U) b[U] = load(row_pair<U>(off))
-#define CSR_ADD2(U) add(row_pair<U>(a), b[U])
-            CSR_LOAD2(0); CSR_LOAD2(1); CSR_LOAD2(2); CSR_LOAD2(3);
-            if (rounds > 8) { CSR_LOAD2(4); CSR_LOAD2(5); CSR_LOAD2(6); CSR_LOAD2(7); }
-            CSR_ADD2(0); CSR_ADD2(1); CSR_ADD2(2); CSR_ADD2(3);
-            if (rounds > 8) { CSR_ADD2(4); CSR_ADD2(5); CSR_ADD2(6); CSR_ADD2(7); }
-#undef CSR_LOAD2
-#undef CSR_ADD2
+#define ENTRY_LOAD(U) b[U] = load(row_pair<U>(off))
+#define ENTRY_ADD(U) add(row_pair<U>(a), b[U])
+            ENTRY_LOAD(0); ENTRY_LOAD(1); ENTRY_LOAD(2); ENTRY_LOAD(3);
+            if (rounds > 8) { ENTRY_LOAD(4); ENTRY_LOAD(5); ENTRY_LOAD(6); ENTRY_LOAD(7); }
+            ENTRY_ADD(0); ENTRY_ADD(1); ENTRY_ADD(2); ENTRY_ADD(3);
+            if (rounds > 8) { ENTRY_ADD(4); ENTRY_ADD(5); ENTRY_ADD(6); ENTRY_ADD(7); }
+#undef ENTRY_LOAD
+#undef ENTRY_ADD
         } else {
-            CSR_LOAD(0, 0); CSR_LOAD(1, 0); CSR_LOAD(2, 0); CSR_LOAD(3, 0);
-            if (rounds > 4) { CSR_LOAD(4, 0); CSR_LOAD(5, 0); CSR_LOAD(6, 0); CSR_LOAD(7, 0); }
-            CSR_ADD(0, 0); CSR_ADD(1, 0); CSR_ADD(2, 0); CSR_ADD(3, 0);
-            if (rounds > 8) { CSR_LOAD(0, 8); CSR_LOAD(1, 8); CSR_LOAD(2, 8); CSR_LOAD(3, 8); }
-            if (rounds > 4) { CSR_ADD(4, 0); CSR_ADD(5, 0); CSR_ADD(6, 0); CSR_ADD(7, 0); }
-            if (rounds > 12) { CSR_LOAD(4, 8); CSR_LOAD(5, 8); CSR_LOAD(6, 8); CSR_LOAD(7, 8); }
-            if (rounds > 8) { CSR_ADD(0, 8); CSR_ADD(1, 8); CSR_ADD(2, 8); CSR_ADD(3, 8); }
-            if (rounds > 12) { CSR_ADD(4, 8); CSR_ADD(5, 8); CSR_ADD(6, 8); CSR_ADD(7, 8); }
+#define ENTRY_LOAD(U, S) b[U] = load(row_lane<U + S>(off))
+#define ENTRY_ADD(U, S) add(row_lane<U + S>(a), b[U])
+            ENTRY_LOAD(0, 0); ENTRY_LOAD(1, 0); ENTRY_LOAD(2, 0); ENTRY_LOAD(3, 0);
+            if (rounds > 4) { ENTRY_LOAD(4, 0); ENTRY_LOAD(5, 0); ENTRY_LOAD(6, 0); ENTRY_LOAD(7, 0); }
+            ENTRY_ADD(0, 0); ENTRY_ADD(1, 0); ENTRY_ADD(2, 0); ENTRY_ADD(3, 0);
+            if (rounds > 8) { ENTRY_LOAD(0, 8); ENTRY_LOAD(1, 8); ENTRY_LOAD(2, 8); ENTRY_LOAD(3, 8); }
+            if (rounds > 4) { ENTRY_ADD(4, 0); ENTRY_ADD(5, 0); ENTRY_ADD(6, 0); ENTRY_ADD(7, 0); }
+            if (rounds > 12) { ENTRY_LOAD(4, 8); ENTRY_LOAD(5, 8); ENTRY_LOAD(6, 8); ENTRY_LOAD(7, 8); }
+            if (rounds > 8) { ENTRY_ADD(0, 8); ENTRY_ADD(1, 8); ENTRY_ADD(2, 8); ENTRY_ADD(3, 8); }
+            if (rounds > 12) { ENTRY_ADD(4, 8); ENTRY_ADD(5, 8); ENTRY_ADD(6, 8); ENTRY_ADD(7, 8); }
+#undef ENTRY_LOAD
+#undef ENTRY_ADD
         }
-#undef CSR_LOAD
-#undef CSR_ADD
     }
     if constexpr (kPair) {
 #pragma unroll
@@ -196,23 +188,56 @@ __global__ void __launch_bounds__(kCsrThreads) csr_spmm_kernel(const CsrParams p
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] += partial[0][chunk0 * 8 + i] + partial[1][chunk0 * 8 + i] + partial[2][chunk0 * 8 + i];
     }
-    if (parts > 1 && g != 0) return;
     const int n = n0 + chunk0 * 8;
-    if (row < 0 || n >= p.N) return;
-    if constexpr (kPair) {                                           // each half of the 16 lanes stores four of the eight columns
-        const int hi = lane >> 3 & 1;
-        const float4v out = hi ? float4v{acc[4], acc[5], acc[6], acc[7]} : float4v{acc[0], acc[1], acc[2], acc[3]};
-        __builtin_nontemporal_store(out, reinterpret_cast<float4v *>(p.C + row * p.ldc + n + 4 * hi));
-        return;
+    if (row >= 0 && n < p.N && (parts == 1 || g == 0)) {
+        float *c = p.C + row * p.ldc + n;
+        if constexpr (kPair) {                                       // each half of the 16 lanes stores four of the eight columns
+            const int hi = lane >> 3 & 1;
+            const float4v out = hi ? float4v{acc[4], acc[5], acc[6], acc[7]} : float4v{acc[0], acc[1], acc[2], acc[3]};
+            __builtin_nontemporal_store(out, reinterpret_cast<float4v *>(c + 4 * hi));
+        } else {
+            __builtin_nontemporal_store(float4v{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<float4v *>(c));
+            __builtin_nontemporal_store(float4v{acc[4], acc[5], acc[6], acc[7]}, reinterpret_cast<float4v *>(c + 4));
+        }
     }
-    float *c = p.C + row * p.ldc + n;
-    __builtin_nontemporal_store(float4v{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<float4v *>(c));
-    __builtin_nontemporal_store(float4v{acc[4], acc[5], acc[6], acc[7]}, reinterpret_cast<float4v *>(c + 4));
 }
 
 inline int64_t align_up256(int64_t x) { return (x + 255) / 256 * 256; }
 
 }  // namespace
+
+int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &rows, int64_t n_rows, int64_t n_cols,
+                      const void *B_dev, int64_t ldb, float *C_dev, int64_t ldc, int64_t N, void *hip_stream)
+{
+    EntryParams p;
+    p.rows = rows;
+    p.B = static_cast<const uint16_t *>(B_dev);
+    p.C = C_dev;
+    p.ldb = ldb;
+    p.ldc = ldc;
+    // B within 4 GiB (less a page for the offset that stands for "no entry"): 32-bit offsets from its first element
+    const int64_t b_bytes = n_cols > 0 ? ((n_cols - 1) * ldb + N) * 2 : 0;
+    const bool wide = b_bytes > 0xFFFFF000ll;
+    p.b_bytes = wide ? 0 : (uint32_t)b_bytes;
+    p.n_rows = (int32_t)n_rows;
+    p.N = (int32_t)N;
+    p.n_ntiles = (int32_t)((N + 8 * L.lanes - 1) / (8 * L.lanes));
+    p.n_huge = L.n_huge;
+    p.n_long = L.n_long;
+    p.n_waves = (int32_t)L.waves;
+    if (L.waves > INT32_MAX || L.grid > INT32_MAX) return VBR_EUNSUPPORTED;
+    const int variant = (dtype == VBR_F16 ? 0 : 6) + (wide ? 3 : 0) + (L.lanes == 32 ? 2 : L.lanes == 16 ? 1 : 0);
+    void (*const kernels[12])(EntryParams) = {
+        entry_rows_kernel<VBR_F16, false, 8>, entry_rows_kernel<VBR_F16, false, 16>, entry_rows_kernel<VBR_F16, false, 32>,
+        entry_rows_kernel<VBR_F16, true, 8>, entry_rows_kernel<VBR_F16, true, 16>, entry_rows_kernel<VBR_F16, true, 32>,
+        entry_rows_kernel<VBR_BF16, false, 8>, entry_rows_kernel<VBR_BF16, false, 16>, entry_rows_kernel<VBR_BF16, false, 32>,
+        entry_rows_kernel<VBR_BF16, true, 8>, entry_rows_kernel<VBR_BF16, true, 16>, entry_rows_kernel<VBR_BF16, true, 32>};
+    hipLaunchKernelGGL(kernels[variant], dim3((unsigned)L.grid), dim3(kCsrThreads), 0, static_cast<hipStream_t>(hip_stream), p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
+    return VBR_OK;
+}
+
 }  // namespace vbrk
 
 extern "C" int csr_spmm_create(const vbr_csr_t *csr, csr_dev_t **out)
@@ -222,28 +247,18 @@ extern "C" int csr_spmm_create(const vbr_csr_t *csr, csr_dev_t **out)
     const int rc = vbrk::validate_csr(csr, true);
     if (rc != VBR_OK) return rc;
     try {
-        csr_dev *h = new csr_dev();
+        std::unique_ptr<csr_dev> h(new csr_dev());
         h->n_rows = csr->n_rows;
         h->n_cols = csr->n_cols;
         h->nnz = csr->nnz;
         h->dtype = csr->dtype;
-        h->row_ptr.assign(csr->row_ptr, csr->row_ptr + csr->n_rows + 1);
-        h->col_idx.assign(csr->col_idx, csr->col_idx + csr->nnz);
-        const uint16_t *v = static_cast<const uint16_t *>(csr->vals);
-        h->vals.assign(v, v + csr->nnz);
-        // rows by falling length, by counting (a row has at most n_cols entries)
-        int64_t longest = 0;
-        for (int64_t i = 0; i < csr->n_rows; ++i) longest = std::max(longest, csr->row_ptr[i + 1] - csr->row_ptr[i]);
-        std::vector<int32_t> at((size_t)longest + 2, 0);
-        for (int64_t i = 0; i < csr->n_rows; ++i) ++at[(size_t)(longest - (csr->row_ptr[i + 1] - csr->row_ptr[i])) + 1];
-        for (int64_t k = 0; k <= longest; ++k) at[(size_t)k + 1] += at[(size_t)k];
-        h->order.resize((size_t)csr->n_rows);
-        for (int64_t i = 0; i < csr->n_rows; ++i) h->order[(size_t)at[(size_t)(longest - (csr->row_ptr[i + 1] - csr->row_ptr[i]))]++] = (int32_t)i;
-        h->col_off = vbrk::align_up256((csr->n_rows + 1) * 8);
+        vbrk::Team team(vbrk::threads_for(csr->nnz, 1 << 18));
+        vbrk::make_entry_rows(csr, team, 0, h->rows);
+        h->row_off = vbrk::align_up256((csr->n_rows + 1) * 8);
+        h->col_off = vbrk::align_up256(h->row_off + csr->n_rows * 4);
         h->val_off = vbrk::align_up256(h->col_off + csr->nnz * 4);
-        h->order_off = vbrk::align_up256(h->val_off + csr->nnz * 2);
-        h->total = vbrk::align_up256(h->order_off + csr->n_rows * 4 + 256);
-        *out = h;
+        h->total = vbrk::align_up256(h->val_off + csr->nnz * 2 + 256);
+        *out = h.release();
         return VBR_OK;
     } catch (const std::bad_alloc &) {
         return VBR_ENOMEM;
@@ -261,10 +276,10 @@ extern "C" int csr_upload(csr_dev_t *h, void *buf_dev, void *hip_stream)
     char *d = static_cast<char *>(buf_dev);
     struct Part { int64_t off; const void *src; size_t bytes; };
     const Part parts[4] = {
-        {0, h->row_ptr.data(), h->row_ptr.size() * 8},
-        {h->col_off, h->col_idx.data(), h->col_idx.size() * 4},
-        {h->val_off, h->vals.data(), h->vals.size() * 2},
-        {h->order_off, h->order.data(), h->order.size() * 4},
+        {0, h->rows.start.data(), h->rows.start.size() * 8},
+        {h->row_off, h->rows.row.data(), h->rows.row.size() * 4},
+        {h->col_off, h->rows.col.data(), h->rows.col.size() * 4},
+        {h->val_off, h->rows.val.data(), h->rows.val.size() * 2},
     };
     for (const Part &pt : parts) {
         if (pt.bytes == 0) continue;
@@ -287,55 +302,10 @@ extern "C" int csr_spmm(const csr_dev_t *h, const void *B_dev, int64_t ldb, floa
     if (!B_dev || !C_dev || ldb < N || ldc < N || ldb % 8 != 0 || ldc % 4 != 0) return VBR_EINVAL;
     if ((reinterpret_cast<uintptr_t>(B_dev) & 15) != 0 || (reinterpret_cast<uintptr_t>(C_dev) & 15) != 0) return VBR_EINVAL;
     const char *d = static_cast<const char *>(h->dev);
-    vbrk::CsrParams p;
-    p.row_ptr = reinterpret_cast<const int64_t *>(d);
-    p.col_idx = reinterpret_cast<const int32_t *>(d + h->col_off);
-    p.vals = reinterpret_cast<const uint16_t *>(d + h->val_off);
-    p.order = reinterpret_cast<const int32_t *>(d + h->order_off);
-    p.B = static_cast<const uint16_t *>(B_dev);
-    p.C = C_dev;
-    p.ldb = ldb;
-    p.ldc = ldc;
-    // B within 4 GiB (less a page for the offset that stands for "no entry"): 32-bit offsets from its first element
-    const int64_t b_bytes = h->n_cols > 0 ? ((h->n_cols - 1) * ldb + N) * 2 : 0;
-    const bool wide = b_bytes > 0xFFFFF000ll;
-    p.b_bytes = wide ? 0 : (uint32_t)b_bytes;
-    p.n_rows = (int32_t)h->n_rows;
-    p.N = (int32_t)N;
-    // Lanes a row, i.e. columns a wave (8 per lane): narrow tiles keep the B that a tile touches smallest and give many waves,
-    // wide ones fetch and store B and C in longer pieces, which is what counts once they come from memory.  Measured with 64 / 128
-    // / 256 columns: 32768 x 32768, 16 entries a row, N = 256: 28.8 / 32 / 38 us; graph of 16384 nodes, N = 256: 22 / 26 / 37,
-    // N = 4096: 358 / 253 / 208, of 4096 nodes, N = 2048: 33 / 29 / 34; 224 entries a row, N = 512: 213 / 185 / 213, 388, N = 1024:
-    // 365 / 270 / 241.  Rows of B that start inside a cache line lie in one line more, which 64 columns pay twice.
-    const bool aligned = ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0;
-    const int lanes = N <= 64 || (N <= 256 && aligned) ? 8 : N > 128 && (!aligned || (N >= 1024 && h->nnz * N >= ((int64_t)1 << 29))) ? 32 : 16;
-    p.n_ntiles = (int32_t)((N + 8 * lanes - 1) / (8 * lanes));
-    // A workgroup for a row costs its barrier and the fourfold sum; it pays where one wave would still be at the row when
-    // the rest is done, i.e. beyond the share of all entries that one of 4096 waves takes (graph, N = 256: 66 -> 26 us;
-    // a matrix whose rows all have 1638 entries is 20 % slower with it and stays without).
-    const int64_t huge_len = std::max<int64_t>(vbrk::kCsrHugeRow, h->nnz * p.n_ntiles / 4096);
-    auto longer_than = [&](int64_t len) {
-        return std::partition_point(h->order.begin(), h->order.end(), [&](int32_t r) { return h->row_ptr[r + 1] - h->row_ptr[r] > len; }) - h->order.begin();
-    };
-    const int64_t n_huge = longer_than(huge_len), n_long = longer_than(vbrk::kCsrLongRow) - n_huge;
-    p.n_huge = (int32_t)n_huge;
-    p.n_long = (int32_t)n_long;
-    const int64_t rest = h->n_rows - n_huge - n_long, waves = 4 * n_huge + n_long + (rest * std::max(lanes, 16) + 63) / 64;
-    p.n_waves = (int32_t)waves;
-    const int64_t T = (waves + 3) / 4, Q = p.n_ntiles;
-    const int64_t grid = Q >= 8 ? 8 * ((Q + 7) / 8) * T : 8 * ((T + 8 / Q - 1) / (8 / Q));
-    if (waves > INT32_MAX || grid > INT32_MAX) return VBR_EUNSUPPORTED;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const int variant = (h->dtype == VBR_F16 ? 0 : 6) + (wide ? 3 : 0) + (lanes == 32 ? 2 : lanes == 16 ? 1 : 0);
-    void (*const kernels[12])(vbrk::CsrParams) = {
-        vbrk::csr_spmm_kernel<VBR_F16, false, 8>, vbrk::csr_spmm_kernel<VBR_F16, false, 16>, vbrk::csr_spmm_kernel<VBR_F16, false, 32>,
-        vbrk::csr_spmm_kernel<VBR_F16, true, 8>, vbrk::csr_spmm_kernel<VBR_F16, true, 16>, vbrk::csr_spmm_kernel<VBR_F16, true, 32>,
-        vbrk::csr_spmm_kernel<VBR_BF16, false, 8>, vbrk::csr_spmm_kernel<VBR_BF16, false, 16>, vbrk::csr_spmm_kernel<VBR_BF16, false, 32>,
-        vbrk::csr_spmm_kernel<VBR_BF16, true, 8>, vbrk::csr_spmm_kernel<VBR_BF16, true, 16>, vbrk::csr_spmm_kernel<VBR_BF16, true, 32>};
-    hipLaunchKernelGGL(kernels[variant], dim3((unsigned)grid), dim3(vbrk::kCsrThreads), 0, stream, p);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) { vbrk::set_last_hip_error((int)e); return VBR_EHIP; }
-    return VBR_OK;
+    const vbrk::EntryRowsDev rows{reinterpret_cast<const int64_t *>(d), reinterpret_cast<const int32_t *>(d + h->row_off),
+                                  reinterpret_cast<const int32_t *>(d + h->col_off), reinterpret_cast<const uint16_t *>(d + h->val_off)};
+    const vbrk::EntryLaunch L = vbrk::plan_entry_rows(h->rows.start, N, ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0);
+    return vbrk::launch_entry_rows(L, h->dtype, rows, h->n_rows, h->n_cols, B_dev, ldb, C_dev, ldc, N, hip_stream);
 }
 
 extern "C" void csr_free(csr_dev_t *h) { delete h; }

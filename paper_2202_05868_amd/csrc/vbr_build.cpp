@@ -48,6 +48,8 @@ constexpr int64_t kSlabMaxCols = 1024;       // columns a slab of low rows gathe
 constexpr int64_t kBlockStepNs[4] = {190, 215, 300, 370};
 constexpr int64_t kGatherStepNs[kMaxGatherSlabs] = {240, 255, 280, 300};
 constexpr int64_t kDeepStepNs[kMaxDeepSlabs] = {290, 350};
+constexpr int64_t kEntryPs = 7000, kEntryRowPs = 30000;      // the same for entry rows, in picoseconds per entry and per row
+constexpr int64_t kEntriesMinRows = 8192;
 constexpr int64_t kTileStartSteps = 4;
 constexpr int64_t kDeepSteps = 32;           // no tile of fewer K-steps is deep
 constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: height costs workgroups, and there are few
@@ -140,6 +142,8 @@ private:
 
     void index_blocks();
     Kind kind_of(Scratch &s, int64_t r0, int64_t r1, int64_t n_blocks);
+    bool entries_cost_less();
+    void keep_entries();
     int block_tiles();
     void order_low_rows();
     bool hubs_first();
@@ -196,6 +200,11 @@ int Builder::build()
     panels_on = use_panels(lg, short_rows);
 
     index_blocks();
+    if (entries_cost_less()) {
+        keep_entries();
+        lay_out();
+        return VBR_OK;
+    }
     int rc = block_tiles();
     if (rc != VBR_OK) return rc;
     v->row_pos.assign((size_t)M, -1);
@@ -305,6 +314,66 @@ Builder::Kind Builder::kind_of(Scratch &s, int64_t r0, int64_t r1, int64_t n_blo
         if (5 * by_columns > 4 * by_blocks) return kBlocks;
     }
     return kGathered;
+}
+
+// Entries that share no B rows gain nothing from the matrix unit: a tile loads as many B rows as it has entries, and 16 values
+// of fragment for every one of them.  Then the whole matrix is kept as rows of entries (one kernel, one launch).  The tiles
+// are priced at tiles of 1 or of 4 slabs in the order of the blocking, or of falling length.  Unstructured matrices, 5e-4 of
+// the entries, N = 256: 32768 rows 33 -> 25 us, 8192 rows 9.2 -> 5.9; below some thousand rows both take what a launch takes.
+bool Builder::entries_cost_less()
+{
+    if (M < kEntriesMinRows) return false;
+    const int64_t cost = kEntryPs * csr->nnz + kEntryRowPs * M;
+    int64_t blocks = 0, rows = 0, nnz = 0, longest = 0;           // cost of the block tiles; rows and entries of all the others
+    std::vector<int32_t> given;
+    for (int32_t g = 0; g < G; ++g) {
+        if (kind[g] == kBlocks) {
+            const int64_t slabs = (rg[g + 1] - rg[g] + kSlabRows - 1) / kSlabRows;
+            blocks += (steps_of((v->blk_ptr[g + 1] - v->blk_ptr[g]) * cb) + kTileStartSteps) * ((slabs + kMaxSlabs - 1) / kMaxSlabs) *
+                      kBlockStepNs[slab_class((int)std::min<int64_t>(slabs, kMaxSlabs))] * 1000;
+            if (blocks > cost) return false;
+            continue;
+        }
+        for (int32_t q = rg[g]; q < rg[g + 1]; ++q) {
+            const int64_t n = csr->row_ptr[perm[q] + 1] - csr->row_ptr[perm[q]];
+            longest = std::max(longest, n);
+            nnz += n;
+            given.push_back(perm[q]);
+        }
+    }
+    rows = (int64_t)given.size();
+    const int64_t step = kMaxGatherSlabs * kSlabRows, n_tiles = (rows + step - 1) / step;
+    // what sharing would have to bring: columns at which tiles of 4 slabs cost as much
+    const int64_t most = ((cost - blocks) / (1000 * kGatherStepNs[kMaxGatherSlabs - 1]) - kTileStartSteps * n_tiles) * kStepK;
+    std::vector<int32_t> sorted((size_t)rows), at((size_t)longest + 2, 0);
+    auto key = [&](int32_t r) { return (size_t)(longest - (csr->row_ptr[r + 1] - csr->row_ptr[r])); };
+    for (const int32_t r : given) ++at[key(r) + 1];
+    for (size_t k = 0; k <= (size_t)longest; ++k) at[k + 1] += at[k];
+    for (const int32_t r : given) sorted[(size_t)at[key(r)]++] = r;
+    for (const std::vector<int32_t> *list : {&given, &sorted}) {
+        std::atomic<int64_t> cols(0);
+        each(n_tiles, 4, [&](Scratch &s, int64_t t) {
+            int64_t n = 0;
+            s.begin();
+            for (int64_t k = t * step; k < std::min(rows, (t + 1) * step); ++k) n += s.add(csr, (*list)[(size_t)k]);
+            cols += n;
+        });
+        if (cols <= most) return false;
+    }
+    // tiles of one slab, at best without a B row less than there are entries
+    return cost < blocks + 1000 * (steps_of(nnz) + kTileStartSteps * (rows / kSlabRows)) * kGatherStepNs[0];
+}
+
+void Builder::keep_entries()
+{
+    v->by_entries = true;
+    make_entry_rows(csr, team, kFragElems, v->entries);
+    v->ks_ptr.assign((size_t)G + 1, 0);
+    v->group_first_tile.assign((size_t)G + 1, 0);
+    std::vector<int32_t> pos((size_t)M);
+    for (int64_t i = 0; i < M; ++i) pos[(size_t)v->entries.row[(size_t)i]] = (int32_t)i;
+    v->row_pos.resize((size_t)M);
+    for (int64_t q = 0; q < M; ++q) v->row_pos[(size_t)q] = pos[(size_t)perm[q]];
 }
 
 // K-step gather lists and tiles of the groups that are multiplied block by block.
@@ -869,9 +938,10 @@ void Builder::lay_out()
     L.panels_off = align_up(L.perm_off + M * 4, 256);
     L.pk_meta_off = align_up(L.panels_off + (int64_t)v->panels.size() * (int64_t)sizeof(PanelDesc), 256);
     L.prow_off = align_up(L.pk_meta_off + (int64_t)v->pk_meta.size() * 4, 256);
-    L.gcol_off = align_up(L.prow_off + (int64_t)v->prow.size() * 4, 256);
-    L.vals_off = align_up(L.gcol_off + (int64_t)v->gcol.size() * 4, 256);
-    L.total = std::max<int64_t>(256, align_up(L.vals_off + (int64_t)v->vals.size() * 2, 256));
+    L.gcol_off = align_up(L.prow_off + (int64_t)(v->by_entries ? v->entries.row : v->prow).size() * 4, 256);
+    L.start_off = align_up(L.gcol_off + (int64_t)(v->by_entries ? v->entries.col : v->gcol).size() * 4, 256);
+    L.vals_off = align_up(L.start_off + (int64_t)v->entries.start.size() * 8, 256);
+    L.total = std::max<int64_t>(256, align_up(L.vals_off + (int64_t)(v->by_entries ? v->entries.val : v->vals).size() * 2, 256));
 }
 
 }  // namespace
@@ -933,6 +1003,18 @@ extern "C" int vbr_unpack_block(const vbr_t *v, int64_t blk, void *dst_)
     const int64_t pos = blk - v->blk_ptr[g];
     const int64_t cb = v->col_block;
     uint16_t *dst = static_cast<uint16_t *>(dst_);
+    if (v->by_entries) {
+        for (int64_t i = 0; i < v->row_groups[g + 1] - v->row_groups[g]; ++i) {
+            const int64_t e = v->row_pos[(size_t)(v->row_groups[g] + i)];
+            const int32_t *b = v->entries.col.data() + v->entries.start[(size_t)e], *end = v->entries.col.data() + v->entries.start[(size_t)e + 1];
+            for (int64_t c = 0; c < cb; ++c) {
+                const int32_t col = (int32_t)((int64_t)v->blk_col[blk] * cb + c);
+                const int32_t *it = std::lower_bound(b, end, col);
+                dst[i * cb + c] = it != end && *it == col ? v->entries.val[(size_t)(it - v->entries.col.data())] : 0;
+            }
+        }
+        return VBR_OK;
+    }
     if (v->group_first_tile[g] == v->group_first_tile[g + 1]) {
         // the rows of the group sit in the row list, each in a slab of a panel or of a column-gathered tile
         const int64_t h = v->row_groups[g + 1] - v->row_groups[g];
@@ -999,7 +1081,8 @@ extern "C" int vbr_audit(const vbr_t *v)
     if (!v) return VBR_EINVAL;
     const int64_t M = v->n_rows, K = v->n_cols;
     const int gran = 1 << v->lg_gran, per_step = kStepK >> v->lg_gran;
-    const int64_t n_vals = (int64_t)v->vals.size();
+    const HostValues &values = v->by_entries ? v->entries.val : v->vals;
+    const int64_t n_vals = (int64_t)values.size();
     if (n_vals < kFragElems || (int64_t)v->perm.size() != M) return VBR_EINVAL;
     for (int64_t i = 0; i < M; ++i)
         if (v->perm[i] < 0 || v->perm[i] >= M) return VBR_EINVAL;
@@ -1058,22 +1141,97 @@ extern "C" int vbr_audit(const vbr_t *v)
     if ((int64_t)v->gcol.size() % kStepK != 0) return VBR_EINVAL;
     for (const int32_t c : v->gcol)
         if (c < 0 || c >= K) return VBR_EINVAL;
-    for (size_t i = v->vals.size() - kFragElems; i < v->vals.size(); ++i)
-        if (v->vals[i] != 0) return VBR_EINVAL;                                               // the zero fragment
+    if (v->by_entries) {
+        const EntryRows &e = v->entries;
+        if (!v->dev_tiles.empty() || !v->panels.empty() || (int64_t)e.start.size() != M + 1 || (int64_t)e.row.size() != M) return VBR_EINVAL;
+        if (e.start[0] != 0 || e.start[(size_t)M] != (int64_t)e.col.size() || (int64_t)e.col.size() + kFragElems != n_vals) return VBR_EINVAL;
+        for (int64_t i = 0; i < M; ++i) {
+            if (e.row[(size_t)i] < 0 || e.row[(size_t)i] >= M || e.start[(size_t)i + 1] < e.start[(size_t)i]) return VBR_EINVAL;
+            if (i > 0 && e.start[(size_t)i + 1] - e.start[(size_t)i] > e.start[(size_t)i] - e.start[(size_t)i - 1]) return VBR_EINVAL;
+        }
+        for (const int32_t c : e.col)
+            if (c < 0 || c >= K) return VBR_EINVAL;
+    }
+    for (size_t i = (size_t)n_vals - kFragElems; i < (size_t)n_vals; ++i)
+        if (values[i] != 0) return VBR_EINVAL;                                               // the zero fragment
     const DeviceLayout &L = v->lay;
-    const int64_t ends[9] = {L.zeros_off + 256, L.tiles_off + (int64_t)v->dev_tiles.size() * (int64_t)sizeof(TileDesc),
+    const int64_t ends[10] = {L.zeros_off + 256, L.tiles_off + (int64_t)v->dev_tiles.size() * (int64_t)sizeof(TileDesc),
                               L.krow_off + (int64_t)v->krow.size() * 4, L.perm_off + M * 4,
                               L.panels_off + (int64_t)v->panels.size() * (int64_t)sizeof(PanelDesc),
-                              L.pk_meta_off + (int64_t)v->pk_meta.size() * 4, L.prow_off + (int64_t)v->prow.size() * 4,
-                              L.gcol_off + (int64_t)v->gcol.size() * 4, L.vals_off + n_vals * 2};
-    const int64_t begins[9] = {L.zeros_off, L.tiles_off, L.krow_off, L.perm_off, L.panels_off, L.pk_meta_off, L.prow_off,
-                               L.gcol_off, L.vals_off};
-    for (int i = 0; i < 9; ++i) {
+                              L.pk_meta_off + (int64_t)v->pk_meta.size() * 4, L.prow_off + (int64_t)(v->by_entries ? v->entries.row : v->prow).size() * 4,
+                              L.gcol_off + (int64_t)(v->by_entries ? v->entries.col : v->gcol).size() * 4,
+                              L.start_off + (int64_t)v->entries.start.size() * 8, L.vals_off + n_vals * 2};
+    const int64_t begins[10] = {L.zeros_off, L.tiles_off, L.krow_off, L.perm_off, L.panels_off, L.pk_meta_off, L.prow_off,
+                                L.gcol_off, L.start_off, L.vals_off};
+    for (int i = 0; i < 10; ++i) {
         if (begins[i] % 256 != 0 || ends[i] > L.total) return VBR_EINVAL;
-        if (i + 1 < 9 && ends[i] > begins[i + 1]) return VBR_EINVAL;                         // sections in this order, disjoint
+        if (i + 1 < 10 && ends[i] > begins[i + 1]) return VBR_EINVAL;                         // sections in this order, disjoint
     }
     return VBR_OK;
 }
+
+namespace vbrk {
+
+void make_entry_rows(const vbr_csr_t *csr, Team &team, int64_t tail, EntryRows &out)
+{
+    const int64_t M = csr->n_rows;
+    // by falling length, by counting (a row has at most n_cols entries)
+    int64_t longest = 0;
+    for (int64_t i = 0; i < M; ++i) longest = std::max(longest, csr->row_ptr[i + 1] - csr->row_ptr[i]);
+    std::vector<int32_t> at((size_t)longest + 2, 0);
+    for (int64_t i = 0; i < M; ++i) ++at[(size_t)(longest - (csr->row_ptr[i + 1] - csr->row_ptr[i])) + 1];
+    for (int64_t k = 0; k <= longest; ++k) at[(size_t)k + 1] += at[(size_t)k];
+    out.row.resize((size_t)M);
+    for (int64_t i = 0; i < M; ++i) out.row[(size_t)at[(size_t)(longest - (csr->row_ptr[i + 1] - csr->row_ptr[i]))]++] = (int32_t)i;
+    out.start.resize((size_t)M + 1);
+    out.start[0] = 0;
+    for (int64_t k = 0; k < M; ++k) out.start[(size_t)k + 1] = out.start[(size_t)k] + csr->row_ptr[out.row[(size_t)k] + 1] - csr->row_ptr[out.row[(size_t)k]];
+    out.col.resize((size_t)csr->nnz);
+    out.val.allocate((size_t)(csr->nnz + tail));
+    std::fill(out.val.data() + csr->nnz, out.val.data() + csr->nnz + tail, (uint16_t)0);
+    const uint16_t *v = static_cast<const uint16_t *>(csr->vals);
+    team.each(M, 256, [&](int64_t b, int64_t e) {
+        for (int64_t k = b; k < e; ++k) {
+            const int64_t p0 = csr->row_ptr[out.row[(size_t)k]], n = out.start[(size_t)k + 1] - out.start[(size_t)k];
+            std::copy(csr->col_idx + p0, csr->col_idx + p0 + n, out.col.data() + out.start[(size_t)k]);
+            std::copy(v + p0, v + p0 + n, out.val.data() + out.start[(size_t)k]);
+        }
+    });
+}
+
+EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t N, bool aligned)
+{
+    const int64_t M = (int64_t)start.size() - 1, nnz = start[(size_t)M];
+    EntryLaunch L;
+    // Lanes a row, i.e. columns a wave (8 per lane): narrow tiles keep the B that a tile touches smallest and give many waves,
+    // wide ones fetch and store B and C in longer pieces, which is what counts once they come from memory.  Measured with 64 / 128
+    // / 256 columns: 32768 x 32768, 16 entries a row, N = 256: 28.8 / 32 / 38 us; graph of 16384 nodes, N = 256: 22 / 26 / 37,
+    // N = 4096: 358 / 253 / 208, of 4096 nodes, N = 2048: 33 / 29 / 34; 224 entries a row, N = 512: 213 / 185 / 213, 388, N = 1024:
+    // 365 / 270 / 241.  Rows of B that start inside a cache line lie in one line more, which 64 columns pay twice.
+    L.lanes = N <= 64 || (N <= 256 && aligned) ? 8 : N > 128 && (!aligned || (N >= 1024 && nnz * N >= ((int64_t)1 << 29))) ? 32 : 16;
+    const int64_t Q = (N + 8 * L.lanes - 1) / (8 * L.lanes);
+    // A workgroup for a row costs its barrier and the fourfold sum; it pays where one wave would still be at the row when
+    // the rest is done, i.e. beyond the share of all entries that one of 4096 waves takes (graph, N = 256: 66 -> 26 us;
+    // a matrix whose rows all have 1638 entries is 20 % slower with it and stays without).
+    auto longer_than = [&](int64_t len) {
+        int64_t lo = 0, hi = M;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if (start[(size_t)mid + 1] - start[(size_t)mid] > len) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo;
+    };
+    L.n_huge = (int32_t)longer_than(std::max<int64_t>(kEntryHugeRow, nnz * Q / 4096));
+    L.n_long = (int32_t)longer_than(kEntryLongRow) - L.n_huge;
+    const int64_t groups = 64 / std::max(L.lanes, 16), sets = (M - L.n_huge - L.n_long + groups - 1) / groups;
+    L.waves = 4 * (int64_t)L.n_huge + L.n_long + sets;
+    const int64_t T = (L.waves + 3) / 4;
+    L.grid = Q >= 8 ? 8 * ((Q + 7) / 8) * T : 8 * ((T + 8 / Q - 1) / (8 / Q));
+    return L;
+}
+
+}  // namespace vbrk
 
 extern "C" int64_t vbr_device_bytes(const vbr_t *v) { return v ? v->lay.total : 0; }
 
@@ -1096,6 +1254,11 @@ static int64_t grid_size(int64_t T, int64_t Q)
 int plan_launches(const vbr *v, int64_t N, Launch out[VBR_MAX_LAUNCHES])
 {
     int n = 0;
+    if (v->by_entries) {
+        const EntryLaunch L = plan_entry_rows(v->entries.start, N, true);      // (B's alignment may widen the column tiles)
+        out[n++] = Launch{VBR_LAUNCH_ENTRIES, 0, (int32_t)v->n_rows, L.grid};
+        return n;
+    }
     const int64_t Qt = (N + kTileN - 1) / kTileN, Qp = (N + kPanelN - 1) / kPanelN;
     if (!v->panels.empty())
         out[n++] = Launch{VBR_LAUNCH_PANEL, 0, (int32_t)v->panels.size(), grid_size((int64_t)v->panels.size(), Qp)};
@@ -1135,9 +1298,9 @@ extern "C" int vbr_get_launches(const vbr_t *v, int64_t N, int32_t *n_launches, 
 extern "C" int vbr_get_schedule(const vbr_t *v, int64_t *n_tiles, int64_t *n_ksteps, int64_t *packed_elems)
 {
     if (!v) return VBR_EINVAL;
-    if (n_tiles) *n_tiles = (int64_t)v->tiles.size() + (int64_t)v->panels.size() + (int64_t)v->gtiles.size();
+    if (n_tiles) *n_tiles = v->by_entries ? v->n_rows : (int64_t)v->tiles.size() + (int64_t)v->panels.size() + (int64_t)v->gtiles.size();
     if (n_ksteps) *n_ksteps = v->ks_ptr.back() + (int64_t)v->pk_mask.size() + (int64_t)v->gcol.size() / vbrk::kStepK;
-    if (packed_elems) *packed_elems = (int64_t)v->vals.size();
+    if (packed_elems) *packed_elems = (int64_t)(v->by_entries ? v->entries.val : v->vals).size();
     return VBR_OK;
 }
 

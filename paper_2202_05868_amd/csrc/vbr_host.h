@@ -1,6 +1,7 @@
 // Declarations shared by the host-side translation units of the library.
 #pragma once
 
+#include "host_threads.h"
 #include "vbr_internal.h"
 
 namespace vbrk {
@@ -15,6 +16,24 @@ int sa1_reorder_impl(const vbr_csr_t *csr, int32_t col_block, double tau, int32_
 // kernel, first tile and number of tiles (or panels) of the launch, grid size.
 struct Launch { int32_t kind; int32_t first_tile, n_tiles; int64_t grid; };
 int plan_launches(const vbr *v, int64_t N, Launch out[VBR_MAX_LAUNCHES]);
+
+constexpr int kEntryLongRow = 256;     // entries beyond which a row gets a wave of its own ...
+constexpr int kEntryHugeRow = 1024;    // ... and a workgroup of its own
+
+// The rows of a matrix as lists of entries, and `tail` zeros behind the last value.
+void make_entry_rows(const vbr_csr_t *csr, Team &team, int64_t tail, EntryRows &out);
+
+// The same on the device.
+struct EntryRowsDev {
+    const int64_t *start;
+    const int32_t *row, *col;
+    const uint16_t *val;
+};
+struct EntryLaunch { int32_t lanes, n_huge, n_long; int64_t waves, grid; };
+// the launch for dense width N; aligned: rows of B begin on a cache line
+EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t N, bool aligned);
+int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &rows, int64_t n_rows, int64_t n_cols,
+                      const void *B_dev, int64_t ldb, float *C_dev, int64_t ldc, int64_t N, void *hip_stream);
 
 // Thread-local code of the last failing HIP call.
 void set_last_hip_error(int code);

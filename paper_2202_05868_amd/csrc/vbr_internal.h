@@ -81,7 +81,8 @@ constexpr int kPanelMetaPad = 12;    // records appended to a panel's K-step str
 struct DeviceLayout {
     int64_t zeros_off = 0, tiles_off = 0, krow_off = 0, perm_off = 0, vals_off = 0, total = 0;
     int64_t panels_off = 0, pk_meta_off = 0, prow_off = 0;
-    int64_t gcol_off = 0;      // (the column-gathered tiles follow the other tiles in the tiles section)
+    int64_t gcol_off = 0;      // by_entries: the columns of the entries; prow their rows, vals their values
+    int64_t start_off = 0;
 };
 
 // The packed values on the host: not cleared when allocated, every tile writes its own part.
@@ -96,6 +97,15 @@ public:
 private:
     std::unique_ptr<uint16_t[]> p_;
     size_t n_ = 0;
+};
+
+// Rows of a matrix as lists of entries, the longest row first (csr_spmm.hip multiplies them): positions 0 .. rows-1,
+// the entries of a position at start[pos] .. start[pos + 1] of col and val.
+struct EntryRows {
+    std::vector<int64_t> start;
+    std::vector<int32_t> row;        // C row of every position
+    std::vector<int32_t> col;
+    HostValues val;
 };
 
 }  // namespace vbrk
@@ -141,6 +151,9 @@ struct vbr {
     std::vector<int64_t> pk_frag;        // host only: ordinal of the step's first fragment inside its panel
     std::vector<int64_t> p_union_ptr;    // host only: [n_panels+1] into p_union
     std::vector<int32_t> p_union;        // host only: ascending union of the column blocks of each panel
+    // A matrix whose blocking found next to nothing to share is kept as entries only: no tiles, no panels, no values above.
+    bool by_entries = false;
+    vbrk::EntryRows entries;             // behind the last value 1 KiB of zeros, like `vals`
     vbrk::DeviceLayout lay;
     void *dev = nullptr;                 // uploaded buffer (caller-owned)
 };

@@ -164,6 +164,27 @@ def test_tiles_with_long_column_lists_split_their_k_steps(n, rows_of_hubs, ldb_p
     check_c(c, c_ref, s, "hub rows, n=%d" % n)
 
 
+@pytest.mark.parametrize("n,ldb_pad,dtype", [(8, 0, "f16"), (64, 64, "bf16"), (248, 0, "f16"), (256, 0, "f16"), (1032, 8, "bf16")])
+def test_large_matrix_that_shares_nothing_is_multiplied_entry_by_entry(n, ldb_pad, dtype):
+    # 8200 rows of 0 to 30 entries anywhere, some of 300 and one of 1500 (a wave, a workgroup for a row)
+    rng = np.random.default_rng(n)
+    k = 6400
+    lens = rng.integers(0, 31, size=8200)
+    lens[[5, 77, 4000]], lens[8100] = 300, 1500
+    csr = csr_from_rows([sorted(rng.choice(k, size=int(x), replace=False).tolist()) for x in lens], k, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, k, n, dtype)
+    perm, rg = rng.permutation(8200).astype(np.int32), np.arange(8201, dtype=np.int32)
+    c, v = gpu_spmm(csr, perm, rg, 32, bits, ldb_pad=ldb_pad, ldc_pad=4)
+    assert [p["kernel"] for p in v.launches(n)] == ["entry_rows_kernel"]
+    index_bit_exact(v, csr, perm, rg, 32)
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "entries, n=%d" % n)
+    ix = v.index()
+    for blk in rng.choice(ix["n_blocks"], size=100, replace=False):
+        g = int(np.searchsorted(ix["blk_ptr"], blk, side="right") - 1)
+        assert np.array_equal(v.unpack_block(int(blk), 1, 32), oracle.block_bits(csr, perm, rg, g, int(ix["blk_col"][blk]), 32))
+
+
 @pytest.mark.parametrize("tail", [1, 15, 16, 33, 63, 64])
 def test_slabs_of_low_rows_that_share_columns_form_taller_tiles(tail):
     # 1024 + tail single-row groups in clusters over the same columns: tiles of 1 to 4 slabs, the last one partial
