@@ -48,7 +48,7 @@ constexpr int64_t kSlabMaxCols = 1024;       // columns a slab of low rows gathe
 constexpr int64_t kBlockStepNs[4] = {190, 215, 300, 370};
 constexpr int64_t kGatherStepNs[kMaxGatherSlabs] = {240, 255, 280, 300};
 constexpr int64_t kDeepStepNs[kMaxDeepSlabs] = {290, 350};
-constexpr int64_t kEntryPs = 7000, kEntryRowPs = 30000;      // the same for entry rows, in picoseconds per entry and per row
+constexpr int64_t kEntryPs = 7000, kEntryRowPs = 15000;      // the same for entry rows, in picoseconds per entry and per row
 constexpr int64_t kEntriesMinRows = 8192;
 constexpr int64_t kTileStartSteps = 4;
 constexpr int64_t kDeepSteps = 32;           // no tile of fewer K-steps is deep
@@ -1207,8 +1207,11 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t N, bool a
     // wide ones fetch and store B and C in longer pieces, which is what counts once they come from memory.  Measured with 64 / 128
     // / 256 columns: 32768 x 32768, 16 entries a row, N = 256: 28.8 / 32 / 38 us; graph of 16384 nodes, N = 256: 22 / 26 / 37,
     // N = 4096: 358 / 253 / 208, of 4096 nodes, N = 2048: 33 / 29 / 34; 224 entries a row, N = 512: 213 / 185 / 213, 388, N = 1024:
-    // 365 / 270 / 241.  Rows of B that start inside a cache line lie in one line more, which 64 columns pay twice.
-    L.lanes = N <= 64 || (N <= 256 && aligned) ? 8 : N > 128 && (!aligned || (N >= 1024 && nnz * N >= ((int64_t)1 << 29))) ? 32 : 16;
+    // 365 / 270 / 241; 32768 rows of 16 entries and none long, N = 512: 46 / 57 / 72, N = 1024: 88 / 109 / 140.  Rows of B that start
+    // inside a cache line lie in one line more, which 64 columns pay twice.
+    const bool all_short = M > 0 && start[1] <= kEntryLongRow && nnz <= 32 * M;
+    if (N <= 64 || (aligned && (N <= 256 || all_short))) L.lanes = 8;
+    else L.lanes = N > 128 && (!aligned || (N >= 1024 && nnz * N >= ((int64_t)1 << 29))) ? 32 : 16;
     const int64_t Q = (N + 8 * L.lanes - 1) / (8 * L.lanes);
     // A workgroup for a row costs its barrier and the fourfold sum; it pays where one wave would still be at the row when
     // the rest is done, i.e. beyond the share of all entries that one of 4096 waves takes (graph, N = 256: 66 -> 26 us;
