@@ -54,6 +54,7 @@ constexpr int64_t kTileStartSteps = 4;
 constexpr int64_t kDeepSteps = 32;           // no tile of fewer K-steps is deep
 constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: height costs workgroups, and there are few
 constexpr int64_t kShortSteps = 8, kShortMinSlabs = 512;
+constexpr int64_t kSplitSteps = 12;
 constexpr int64_t kEmptyApart = 512;         // workgroups
 constexpr int64_t kSegmentSlabs = 64;        // the cutting of the slab list into tiles is optimised over stretches of this length
 
@@ -1254,11 +1255,11 @@ static int64_t grid_size(int64_t T, int64_t Q)
 // rows, N = 4096: 169 and 155 -> 137 us; graph of 16384 nodes, N = 4096: 192 and 195 -> 181; of 4096 nodes, N = 2048: 41 and
 // 24 -> 20.  Only tiles without a K-step, if there are many, have a launch of their own behind the others: they just
 // store zeros, and the kernel for them needs no more than that.
-int plan_launches(const vbr *v, int64_t N, Launch out[VBR_MAX_LAUNCHES])
+int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUNCHES])
 {
     int n = 0;
     if (v->by_entries) {
-        const EntryLaunch L = plan_entry_rows(v->entries.start, N, true);      // (B's alignment may widen the column tiles)
+        const EntryLaunch L = plan_entry_rows(v->entries.start, N, aligned);
         out[n++] = Launch{VBR_LAUNCH_ENTRIES, 0, (int32_t)v->n_rows, L.grid};
         return n;
     }
@@ -1276,7 +1277,11 @@ int plan_launches(const vbr *v, int64_t N, Launch out[VBR_MAX_LAUNCHES])
     // (tiles without a K-step are gathered ones of up to 4 slabs: that kernel takes them, and the mixed one)
     if (T > 0) {
         const bool one_kind = classes == 1 && (T == v->n_work || last == kClasses - 1);
-        out[n++] = Launch{one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED, 0, T, grid_size(T, Qt)};
+        // Tiles of one or two slabs with long lists whose workgroups leave CUs idle: four workgroups of 64 columns each instead, whose
+        // waves split the K-steps (16 x 16 blocks at 12 %, 1024 x 16000, N = 512, 128 workgroups: 26 -> 12 us; at 8 %, 1024 x 4096: 9.4 -> 5.6;
+        // no gain beyond one workgroup per CU, nor, 64 columns lying in two lines, at half of that where rows of B begin inside a line).
+        const bool split = one_kind && last % kClassGather < 2 && T * Qt <= (aligned ? 256 : 128) && v->dev_tiles[0].n_ks >= kSplitSteps;
+        out[n++] = Launch{one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED, 0, T, grid_size(T, split ? (N + kDeepN - 1) / kDeepN : Qt), split};
     }
     if (T < T_all) out[n++] = Launch{VBR_LAUNCH_GATHER_4, T, T_all - T, grid_size(T_all - T, Qt)};
     return n;
@@ -1288,7 +1293,7 @@ extern "C" int vbr_get_launches(const vbr_t *v, int64_t N, int32_t *n_launches, 
 {
     if (!v || !n_launches || N < 0) return VBR_EINVAL;
     vbrk::Launch plan[VBR_MAX_LAUNCHES];
-    const int n = (N == 0 || v->n_rows == 0) ? 0 : vbrk::plan_launches(v, N, plan);
+    const int n = (N == 0 || v->n_rows == 0) ? 0 : vbrk::plan_launches(v, N, N % 64 == 0, plan);
     *n_launches = n;
     for (int i = 0; i < n; ++i) {
         if (kinds) kinds[i] = plan[i].kind;

@@ -421,7 +421,6 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
     }
 }
 
-constexpr int kDeepN = 64;                        // C columns per workgroup of a deep tile
 constexpr int kDeepRow = kDeepN * 2;              // one staged B row: 128 bytes
 constexpr int kDeepList = kStepK * 4;             // the list entries of a K-step
 template <int S, int SLOTS>
@@ -433,7 +432,7 @@ constexpr int deep_wave_bytes() { return SLOTS * (kStepK * kDeepRow + S * kFragB
 // K-steps in turn, each with an LDS ring of its own and without a barrier; the four partial sums are added in LDS, in
 // a fixed order.  The price is S fragments per 64 columns instead of per 256: 24 loads per K-step for two slabs
 // instead of 18.
-template <int DT, int S, int SLOTS>
+template <int DT, int S, int SLOTS, bool GATHER = true>
 __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, const int n0, unsigned char *smem)
 {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -462,14 +461,24 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
     const int rows_last = td.n_rows - (td.n_slabs - 1) * kSlabRows;
     const uint32_t a_stride_bytes = (uint32_t)(((td.n_slabs - 1) * kFragElems + rows_last * kStepK) * 2);
     const char *Abase = reinterpret_cast<const char *>(p.vals) + td.a_off * 16;
-    const int32_t *list = p.gcol + (int64_t)td.ks_begin * kStepK;
+    // the B rows of a K-step: one by one, or the first row of the granule of every eight
+    const int lg = p.lg_gran, gmask = (1 << lg) - 1;
     auto issue_list = [&](int ks, int slot) {
-        if (lane < kStepK) dma4(list + (int64_t)ks * kStepK + lane, base + SLOTS * (kB + kA) + slot * kDeepList);
+        const int64_t k = (int64_t)td.ks_begin + ks;
+        const uint32_t to = base + SLOTS * (kB + kA) + slot * kDeepList;
+        if constexpr (GATHER) {
+            if (lane < kStepK) dma4(p.gcol + k * kStepK + lane, to);
+        } else {
+            if (lane < kStepK / 8) dma4(p.krow + ((k * kStepK + 8 * lane) >> lg), to);
+        }
     };
     auto issue = [&](int ks, int slot) {
         int32_t e[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) e[i] = *(lds_i32_ptr)(lists + slot * kDeepList + (8 * i + (lane >> 3)) * 4);
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (GATHER) e[i] = *(lds_i32_ptr)(lists + slot * kDeepList + (8 * i + (lane >> 3)) * 4);
+            else e[i] = *(lds_i32_ptr)(lists + slot * kDeepList + i * 4) + ((8 * i + (lane >> 3)) & gmask);
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             dma16(Bcol + (uint64_t)(uint32_t)e[i] * ldb_bytes, base + slot * kB + i * 1024);
@@ -537,7 +546,7 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
 #pragma unroll
     for (int s = 0; s < S; ++s) {
         const int rr = s * kSlabRows + 4 * wave + q;                           // this lane's row when the sums are stored
-        orig[s] = rr < td.n_rows ? p.prow[td.row_begin + rr] : -1;
+        orig[s] = rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
     }
     constexpr int kOutRow = kDeepN * 4 + 16, kOutSlab = kSlabRows * kOutRow;
     __syncthreads();                                                           // nobody reads the rings any more
@@ -613,6 +622,18 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
     else if (td.n_slabs <= 2) tile_body<DT, 2, NS1, DA1>(p, td, ntile, smem);
     else if (MAXS == 4 || td.n_slabs <= 4) tile_body<DT, 4, NS4, kADistance>(p, td, ntile, smem);
     else if constexpr (MAXS == 8) tile_body<DT, 8, NS8, kADistance>(p, td, ntile, smem);
+}
+
+// The deep form for every tile of one or two slabs, for launches whose workgroups would not fill the chip: four times as many,
+// each with a quarter of the chain.  64 columns of C per workgroup.
+template <int DT, int S, bool GATHER>
+__global__ void __launch_bounds__(kThreads) vbr_spmm_split_kernel(const Params p)
+{
+    constexpr int SLOTS = 3;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[deep_lds_bytes<S, SLOTS>()];
+    int tile, ntile;
+    if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
+    deep_body<DT, S, SLOTS, GATHER>(p, p.tiles[tile], ntile * kDeepN, smem);
 }
 
 struct PanelParams {
@@ -816,7 +837,7 @@ template <int DT>
 int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStream_t stream)
 {
     Launch plan[VBR_MAX_LAUNCHES];
-    const int n = plan_launches(v, base.N, plan);
+    const int n = plan_launches(v, base.N, base.ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(base.B) & 127) == 0, plan);
     for (int i = 0; i < n; ++i)
         if (plan[i].grid > INT32_MAX) return VBR_EINVAL;
     for (int i = 0; i < n; ++i) {
@@ -838,25 +859,26 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
         const int64_t workgroups = (int64_t)p.n_tiles * p.n_ntiles;
         const bool few = v->class_count[kClassDeep] > 0 ? workgroups <= 1536 : workgroups <= 512 && v->dev_tiles[0].n_ks >= 24;
         void (*kernel)(Params) = nullptr;
+        if (L.split) p.n_ntiles = (p.N + kDeepN - 1) / kDeepN;
         switch (L.kind) {
         case VBR_LAUNCH_TILE_MIXED:
             if (v->class_count[3] > 0) kernel = few ? vbr_spmm_mixed_kernel<DT, 8, kStagesFew, 3> : vbr_spmm_mixed_kernel<DT, 8, kStages, 2>;
             else kernel = few ? vbr_spmm_mixed_kernel<DT, 4, kStagesFew, 3> : vbr_spmm_mixed_kernel<DT, 4, kStages, 2>;
             break;
         case VBR_LAUNCH_GATHER_1:
-            kernel = few ? vbr_spmm_kernel<DT, 1, kStagesFew, kStagesFew, true> : vbr_spmm_kernel<DT, 1, kStages, kADistance, true>;
+            kernel = L.split ? vbr_spmm_split_kernel<DT, 1, true> : few ? vbr_spmm_kernel<DT, 1, kStagesFew, kStagesFew, true> : vbr_spmm_kernel<DT, 1, kStages, kADistance, true>;
             break;
         case VBR_LAUNCH_GATHER_2:
-            kernel = few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew, true> : vbr_spmm_kernel<DT, 2, kStages, kADistance, true>;
+            kernel = L.split ? vbr_spmm_split_kernel<DT, 2, true> : few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew, true> : vbr_spmm_kernel<DT, 2, kStages, kADistance, true>;
             break;
         case VBR_LAUNCH_GATHER_4:
             kernel = few ? vbr_spmm_kernel<DT, 4, kStagesTall, kADistance, true> : vbr_spmm_kernel<DT, 4, kStages, kADistance, true>;
             break;
         case VBR_LAUNCH_TILE_1:
-            kernel = few ? vbr_spmm_kernel<DT, 1, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 1, kStages, kADistance>;
+            kernel = L.split ? vbr_spmm_split_kernel<DT, 1, false> : few ? vbr_spmm_kernel<DT, 1, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 1, kStages, kADistance>;
             break;
         case VBR_LAUNCH_TILE_2:
-            kernel = few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 2, kStages, kADistance>;
+            kernel = L.split ? vbr_spmm_split_kernel<DT, 2, false> : few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 2, kStages, kADistance>;
             break;
         case VBR_LAUNCH_TILE_4:
             kernel = vbr_spmm_kernel<DT, 4, kStagesTall, kADistance>;
