@@ -54,7 +54,7 @@ constexpr int64_t kTileStartSteps = 4;
 constexpr int64_t kDeepSteps = 32;           // no tile of fewer K-steps is deep
 constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: height costs workgroups, and there are few
 constexpr int64_t kShortSteps = 8, kShortMinSlabs = 512;
-constexpr int64_t kSplitSteps = 12, kSmallSteps = 1152;
+constexpr int64_t kSplitSteps = 12, kSmallSteps = 1152, kFewTiles = 96;
 constexpr int64_t kEmptyApart = 512;         // workgroups
 constexpr int64_t kSegmentSlabs = 64;        // the cutting of the slab list into tiles is optimised over stretches of this length
 
@@ -738,7 +738,8 @@ void Builder::append_gathered_groups()
 //     short, so that starting and storing are most of its time, and there are enough of them to fill the chip still.
 //   - A tile of more K-steps than a resident workgroup's share of the whole (at N = 2048) would still be at it when the
 //     rest is done.  It is "deep": the waves of a workgroup split its K-steps, and four workgroups its 256 columns.
-//     In a matrix too small to fill the chip every longer tile of one or two slabs is.
+//     In a matrix too small to fill the chip every longer tile is, and not higher than two slabs (1024 x 1024 with 286 groups,
+//     N = 256: 8.2 -> 6.4 us; 2048 x 2048 with 631, N = 128: 15.0 -> 7.7).
 void Builder::cut_into_tiles()
 {
     const int64_t n_slabs = ((int64_t)v->prow.size() + kSlabRows - 1) / kSlabRows;
@@ -773,9 +774,9 @@ void Builder::cut_into_tiles()
         i = e;
     }
     std::vector<std::vector<uint8_t>> cut(runs.size());     // lengths of the tiles of every stretch, in order
-    std::atomic<int64_t> total(0);
+    std::atomic<int64_t> total(0), working(0);              // K-steps, tiles that have any
     auto best_cuts = [&](int64_t deep_steps) {
-        total = 0;
+        total = working = 0;
         each((int64_t)runs.size(), 2, [&](Scratch &, int64_t r) {
             const int64_t b = runs[(size_t)r].first, n = runs[(size_t)r].second - b;
             const bool low = part[(size_t)b] == 0, single = low && low_slabs < kMergeMinSlabs;
@@ -796,7 +797,9 @@ void Builder::cut_into_tiles()
             int64_t steps = 0;
             for (int64_t e = n; e > 0; e -= len_of[(size_t)e]) {
                 cut[(size_t)r].push_back(len_of[(size_t)e]);
-                steps += steps_of(cols[(size_t)((b + e - len_of[(size_t)e]) * kMaxGatherSlabs + len_of[(size_t)e] - 1)]);
+                const int64_t ks = steps_of(cols[(size_t)((b + e - len_of[(size_t)e]) * kMaxGatherSlabs + len_of[(size_t)e] - 1)]);
+                steps += ks;
+                working += ks > 0;
             }
             std::reverse(cut[(size_t)r].begin(), cut[(size_t)r].end());
             total += steps;
@@ -804,8 +807,8 @@ void Builder::cut_into_tiles()
     };
     best_cuts(INT32_MAX);
     for (const TileDesc &td : v->tiles) total += td.n_ks;
-    v->deep_steps = (int32_t)std::min<int64_t>(INT32_MAX, deep_from(total));
-    // (small matrices: 1024 x 1024 with 286 groups, N = 256: 8.2 -> 6.4 us)
+    working += (int64_t)v->tiles.size();
+    v->deep_steps = (int32_t)std::min<int64_t>(INT32_MAX, working <= kFewTiles ? kSplitSteps : deep_from(total));
     const int32_t mark = total < kSmallSteps ? (int32_t)std::min<int64_t>(v->deep_steps, kSplitSteps) : v->deep_steps;
     best_cuts(v->deep_steps);
     for (size_t r = 0; r < runs.size(); ++r) {
