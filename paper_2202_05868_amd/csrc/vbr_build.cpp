@@ -484,8 +484,9 @@ bool Builder::hubs_first()
 // Otherwise the list is built cluster by cluster: the first group not yet placed
 // leads a cluster and takes with it every later group that shares at least half of the smaller
 // of the two block sets with the LEADER (overlap coefficient >= 1/2, which unlike the Jaccard
-// similarity does not fade when both sets carry noise blocks of their own; no pattern update:
-// this only orders the packing, the blocking is the caller's).  Candidates come from an index column block -> low groups.  When
+// similarity does not fade when both sets carry noise blocks of their own), and then every later group with
+// three quarters of the blocks that most of these have (noisy planted matrix: 187 -> 128 tiles).  This only orders the packing, the
+// blocking is the caller's.  Candidates come from an index column block -> low groups.  When
 // the first 512 leaders find next to nothing (unstructured matrices), the rest keeps its order.
 void Builder::cluster_low_groups()
 {
@@ -506,7 +507,27 @@ void Builder::cluster_low_groups()
     }
     std::vector<int64_t> first(inv_ptr.begin(), inv_ptr.end() - 1);
     std::vector<uint8_t> placed((size_t)n_low, 0);
-    std::vector<int32_t> cnt((size_t)n_low, 0), hit;
+    std::vector<int32_t> cnt((size_t)n_low, 0), hit, core, in_cluster((size_t)KB, 0);
+    // the groups behind the leader i that share enough of the n given blocks, in rising order
+    auto join = [&](int64_t i, const int32_t *blks, int64_t n, auto enough) {
+        hit.clear();
+        for (int64_t k = 0; k < n; ++k) {
+            int64_t &f = first[blks[k]];
+            while (f < inv_ptr[blks[k] + 1] && inv[f] <= i) ++f;
+            for (int64_t e = f; e < inv_ptr[blks[k] + 1]; ++e) {
+                const int32_t j = inv[e];
+                if (!placed[j] && cnt[j]++ == 0) hit.push_back(j);
+            }
+        }
+        size_t n_pass = 0;
+        for (const int32_t j : hit) {
+            const int64_t I = cnt[j];
+            cnt[j] = 0;
+            if (enough(I, v->blk_ptr[low_groups[j] + 1] - v->blk_ptr[low_groups[j]])) hit[n_pass++] = j;
+        }
+        std::sort(hit.begin(), hit.begin() + (std::ptrdiff_t)n_pass);
+        for (size_t k = 0; k < n_pass; ++k) { placed[hit[k]] = 1; order.push_back(hit[k]); }
+    };
     int64_t leaders = 0, followers = 0;
     bool clustering = true;
     for (int64_t i = 0; i < n_low; ++i) {
@@ -517,27 +538,35 @@ void Builder::cluster_low_groups()
         if (!clustering) continue;
         const int32_t g = low_groups[i];
         const int64_t li = v->blk_ptr[g + 1] - v->blk_ptr[g];
-        hit.clear();
-        for (int64_t b = v->blk_ptr[g]; b < v->blk_ptr[g + 1]; ++b) {
-            const int32_t blk = v->blk_col[b];
-            int64_t &f = first[blk];
-            while (f < inv_ptr[blk + 1] && inv[f] <= i) ++f;
-            for (int64_t e = f; e < inv_ptr[blk + 1]; ++e) {
-                const int32_t j = inv[e];
-                if (!placed[j] && cnt[j]++ == 0) hit.push_back(j);
+        const size_t begin = order.size() - 1;
+        // (only the groups that join are sorted: the candidates are thousands per leader on an unstructured matrix)
+        join(i, v->blk_col.data() + v->blk_ptr[g], li, [&](int64_t I, int64_t lj) { return 2 * I >= std::min(li, lj); });
+        if (order.size() - begin >= 4) {
+            // what most members have in common is a better leader than the first of them, whose own noise blocks kept others out
+            core.clear();
+            for (size_t o = begin; o < order.size(); ++o)
+                for (int64_t b = v->blk_ptr[low_groups[order[o]]]; b < v->blk_ptr[low_groups[order[o]] + 1]; ++b)
+                    if (in_cluster[v->blk_col[b]]++ == 0) core.push_back(v->blk_col[b]);
+            size_t n = 0;
+            for (const int32_t blk : core) {
+                if (2 * (size_t)in_cluster[blk] >= order.size() - begin) core[n++] = blk;
+                in_cluster[blk] = 0;
             }
+            core.resize(n);
+            // ... nor do those stay that came for noise in common (one row too many costs its tile a slab)
+            for (const int32_t blk : core) in_cluster[blk] = 1;
+            size_t keep = begin + 1;
+            for (size_t o = begin + 1; o < order.size(); ++o) {
+                size_t I = 0;
+                for (int64_t b = v->blk_ptr[low_groups[order[o]]]; b < v->blk_ptr[low_groups[order[o]] + 1]; ++b) I += (size_t)in_cluster[v->blk_col[b]];
+                if (4 * I >= 3 * n) order[keep++] = order[o];
+                else placed[order[o]] = 0;
+            }
+            order.resize(keep);
+            for (const int32_t blk : core) in_cluster[blk] = 0;
+            if (n > 0) join(i, core.data(), (int64_t)n, [&](int64_t I, int64_t) { return 4 * I >= 3 * (int64_t)n; });
         }
-        // the followers join in rising order; only they are sorted (the candidates are thousands per
-        // leader on an unstructured matrix, the followers few)
-        size_t n_pass = 0;
-        for (const int32_t j : hit) {
-            const int32_t gj = low_groups[j];
-            const int64_t I = cnt[j], lj = v->blk_ptr[gj + 1] - v->blk_ptr[gj];
-            cnt[j] = 0;
-            if (2 * I >= std::min(li, lj)) hit[n_pass++] = j;
-        }
-        std::sort(hit.begin(), hit.begin() + (std::ptrdiff_t)n_pass);
-        for (size_t k = 0; k < n_pass; ++k) { placed[hit[k]] = 1; order.push_back(hit[k]); ++followers; }
+        followers += (int64_t)(order.size() - begin) - 1;
         if (++leaders == 512 && followers < 64) clustering = false;
     }
     // A cluster of two slabs' worth of rows or more begins and ends on a slab boundary (the list is
