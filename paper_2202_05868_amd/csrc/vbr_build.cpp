@@ -54,7 +54,7 @@ constexpr int64_t kTileStartSteps = 4;
 constexpr int64_t kDeepSteps = 32;           // no tile of fewer K-steps is deep
 constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: height costs workgroups, and there are few
 constexpr int64_t kShortSteps = 8, kShortMinSlabs = 512;
-constexpr int64_t kSplitSteps = 12, kSmallSteps = 1152, kFewTiles = 96;
+constexpr int64_t kSmallSteps = 1152, kFewTiles = 96;
 constexpr int64_t kEmptyApart = 512;         // workgroups
 constexpr int64_t kSegmentSlabs = 64;        // the cutting of the slab list into tiles is optimised over stretches of this length
 
@@ -837,7 +837,7 @@ void Builder::cut_into_tiles()
     best_cuts(INT32_MAX);
     for (const TileDesc &td : v->tiles) total += td.n_ks;
     working += (int64_t)v->tiles.size();
-    v->deep_steps = (int32_t)std::min<int64_t>(INT32_MAX, working <= kFewTiles ? kSplitSteps : deep_from(total));
+    v->deep_steps = (int32_t)std::min<int64_t>(INT32_MAX, working <= kFewTiles ? (int64_t)kSplitSteps : deep_from(total));
     const int32_t mark = total < kSmallSteps ? (int32_t)std::min<int64_t>(v->deep_steps, kSplitSteps) : v->deep_steps;
     best_cuts(v->deep_steps);
     for (size_t r = 0; r < runs.size(); ++r) {
@@ -1312,11 +1312,13 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
     // (tiles without a K-step are gathered ones of up to 4 slabs: that kernel takes them, and the mixed one)
     if (T > 0) {
         const bool one_kind = classes == 1 && (T == v->n_work || last == kClasses - 1);
-        // Tiles of one or two slabs with long lists whose workgroups leave CUs idle: four workgroups of 64 columns each instead, whose
+        // Tiles of up to four slabs with long lists whose workgroups leave CUs idle: four workgroups of 64 columns each instead, whose
         // waves split the K-steps (16 x 16 blocks at 12 %, 1024 x 16000, N = 512, 128 workgroups: 26 -> 12 us; at 8 %, 1024 x 4096: 9.4 -> 5.6;
         // no gain beyond one workgroup per CU, nor, 64 columns lying in two lines, at half of that where rows of B begin inside a line).
-        const bool split = one_kind && last % kClassGather < 2 && T * Qt <= (aligned ? 256 : 128) && v->dev_tiles[0].n_ks >= kSplitSteps;
-        out[n++] = Launch{one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED, 0, T, grid_size(T, split ? (N + kDeepN - 1) / kDeepN : Qt), split};
+        const bool split = T * Qt <= (aligned ? 320 : 128) && v->class_count[3] < T && v->dev_tiles[0].n_ks >= kSplitSteps;
+        const int32_t kind = one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED;
+        const int64_t grid = !split ? grid_size(T, Qt) : kind == VBR_LAUNCH_TILE_MIXED ? grid_size(4 * (int64_t)T, Qt) : grid_size(T, (N + kDeepN - 1) / kDeepN);
+        out[n++] = Launch{kind, 0, T, grid, split};
     }
     if (T < T_all) out[n++] = Launch{VBR_LAUNCH_GATHER_4, T, T_all - T, grid_size(T_all - T, Qt)};
     return n;

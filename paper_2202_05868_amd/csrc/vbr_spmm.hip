@@ -57,7 +57,8 @@ struct Params {
     int32_t N;
     int32_t lg_gran;
     int32_t n_tiles;          // T
-    int32_t n_ntiles;         // Q = ceil(N / 256)
+    int32_t n_ntiles;         // Q = ceil(N / 256), of the split kernel ceil(N / 64)
+    int32_t split;            // mixed kernel: n_tiles is four times the tiles, see there
 };
 
 template <int DT>
@@ -603,17 +604,31 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
     constexpr int NS1 = RING, DA1 = a_distance(NS1);
     constexpr int NSG = RING > kStages ? kStagesTall : kStages;                    // gathered, 3 to 4 slabs
     constexpr int NS4 = MAXS == 8 ? kStagesTall : NSG, NS8 = RING > kStages ? kStagesTall : kStages;
-    constexpr int kLow = std::max(tile_lds_bytes<2, NS1, DA1, true>(), deep_lds_bytes<2, SLOTS>());
+    constexpr int kLow = std::max(tile_lds_bytes<2, NS1, DA1, true>(), std::max(deep_lds_bytes<2, SLOTS>(), RING > kStages ? deep_lds_bytes<4, 2>() : 0));
     constexpr int k4 = std::max(tile_lds_bytes<4, NSG, kADistance, true>(), tile_lds_bytes<4, NS4, kADistance, false>());
     constexpr int k8 = MAXS == 8 ? tile_lds_bytes<8, NS8, kADistance, false>() : 0;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[std::max(k8, std::max(k4, kLow))];
     int tile, ntile;
     if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
-    const TileDesc td = p.tiles[tile];
+    // in a split launch every tile has four workgroups a column tile: quarters of it for the long ones, the others use the first
+    const int T = p.split ? p.n_tiles / 4 : p.n_tiles, quarter = tile / T;
+    const TileDesc td = p.tiles[tile - quarter * T];
     if (td.group <= kTileDeep) {
+        if (quarter != 0) return;
         const int n0 = ntile * kTileN + (kTileDeep - td.group) * kDeepN;
         if (td.n_slabs <= 1) deep_body<DT, 1, SLOTS>(p, td, n0, smem);
         else deep_body<DT, 2, SLOTS>(p, td, n0, smem);
+    } else if (RING > kStages && p.split && td.n_slabs <= 4 && td.n_ks >= kSplitSteps) {
+        const int n0 = ntile * kTileN + quarter * kDeepN;
+        const bool gathered = td.group == kTileGathered;
+        if (gathered && td.n_slabs <= 1) deep_body<DT, 1, SLOTS>(p, td, n0, smem);
+        else if (gathered && td.n_slabs <= 2) deep_body<DT, 2, SLOTS>(p, td, n0, smem);
+        else if (gathered) deep_body<DT, 4, 2>(p, td, n0, smem);
+        else if (td.n_slabs <= 1) deep_body<DT, 1, SLOTS, false>(p, td, n0, smem);
+        else if (td.n_slabs <= 2) deep_body<DT, 2, SLOTS, false>(p, td, n0, smem);
+        else deep_body<DT, 4, 2, false>(p, td, n0, smem);
+    } else if (quarter != 0) {
+        return;
     } else if (td.group == kTileGathered) {
         if (td.n_slabs <= 1) tile_body<DT, 1, NS1, DA1, true>(p, td, ntile, smem);
         else if (td.n_slabs <= 2) tile_body<DT, 2, NS1, DA1, true>(p, td, ntile, smem);
@@ -624,12 +639,12 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
     else if constexpr (MAXS == 8) tile_body<DT, 8, NS8, kADistance>(p, td, ntile, smem);
 }
 
-// The deep form for every tile of one or two slabs, for launches whose workgroups would not fill the chip: four times as many,
+// The deep form for every tile of up to four slabs, for launches whose workgroups would not fill the chip: four times as many,
 // each with a quarter of the chain.  64 columns of C per workgroup.
 template <int DT, int S, bool GATHER>
 __global__ void __launch_bounds__(kThreads) vbr_spmm_split_kernel(const Params p)
 {
-    constexpr int SLOTS = 3;
+    constexpr int SLOTS = S <= 2 ? 3 : 2;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[deep_lds_bytes<S, SLOTS>()];
     int tile, ntile;
     if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
@@ -857,9 +872,11 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
         // of at most 19 K-steps a tile: 8.2 -> 8.9).  With deep tiles, whose chain is the longest, up to three rounds
         // (graph of 16384 nodes: N = 512 47 -> 34 us, N = 2048 70 -> 78).
         const int64_t workgroups = (int64_t)p.n_tiles * p.n_ntiles;
-        const bool few = v->class_count[kClassDeep] > 0 ? workgroups <= 1536 : workgroups <= 512 && v->dev_tiles[0].n_ks >= 24;
+        const bool few = L.split ? true : v->class_count[kClassDeep] > 0 ? workgroups <= 1536 : workgroups <= 512 && v->dev_tiles[0].n_ks >= 24;
         void (*kernel)(Params) = nullptr;
-        if (L.split) p.n_ntiles = (p.N + kDeepN - 1) / kDeepN;
+        p.split = L.split && L.kind == VBR_LAUNCH_TILE_MIXED;
+        if (p.split) p.n_tiles *= 4;
+        else if (L.split) p.n_ntiles = (p.N + kDeepN - 1) / kDeepN;
         switch (L.kind) {
         case VBR_LAUNCH_TILE_MIXED:
             if (v->class_count[3] > 0) kernel = few ? vbr_spmm_mixed_kernel<DT, 8, kStagesFew, 3> : vbr_spmm_mixed_kernel<DT, 8, kStages, 2>;
@@ -872,7 +889,7 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             kernel = L.split ? vbr_spmm_split_kernel<DT, 2, true> : few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew, true> : vbr_spmm_kernel<DT, 2, kStages, kADistance, true>;
             break;
         case VBR_LAUNCH_GATHER_4:
-            kernel = few ? vbr_spmm_kernel<DT, 4, kStagesTall, kADistance, true> : vbr_spmm_kernel<DT, 4, kStages, kADistance, true>;
+            kernel = L.split ? vbr_spmm_split_kernel<DT, 4, true> : few ? vbr_spmm_kernel<DT, 4, kStagesTall, kADistance, true> : vbr_spmm_kernel<DT, 4, kStages, kADistance, true>;
             break;
         case VBR_LAUNCH_TILE_1:
             kernel = L.split ? vbr_spmm_split_kernel<DT, 1, false> : few ? vbr_spmm_kernel<DT, 1, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 1, kStages, kADistance>;
@@ -881,7 +898,7 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             kernel = L.split ? vbr_spmm_split_kernel<DT, 2, false> : few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 2, kStages, kADistance>;
             break;
         case VBR_LAUNCH_TILE_4:
-            kernel = vbr_spmm_kernel<DT, 4, kStagesTall, kADistance>;
+            kernel = L.split ? vbr_spmm_split_kernel<DT, 4, false> : vbr_spmm_kernel<DT, 4, kStagesTall, kADistance>;
             break;
         default:
             kernel = vbr_spmm_kernel<DT, 8, kStagesTall, kADistance>;

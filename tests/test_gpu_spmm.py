@@ -185,23 +185,25 @@ def test_large_matrix_that_shares_nothing_is_multiplied_entry_by_entry(n, ldb_pa
         assert np.array_equal(v.unpack_block(int(blk), 1, 32), oracle.block_bits(csr, perm, rg, g, int(ix["blk_col"][blk]), 32))
 
 
-@pytest.mark.parametrize("height,col_block,n,ldb_pad,dtype", [(16, 16, 64, 0, "f16"), (16, 8, 72, 56, "bf16"), (27, 32, 256, 0, "f16"), (32, 16, 24, 8, "f16")])
-def test_few_workgroups_with_long_lists_split_their_k_steps(height, col_block, n, ldb_pad, dtype):
-    # groups of one slab, of a full and of a partial second one, every granule width; N below and past 64 columns
-    rng = np.random.default_rng(height + col_block)
-    groups, kb = 5, 1536 // col_block
+@pytest.mark.parametrize("heights,col_block,n,ldb_pad,dtype", [([16] * 5, 16, 64, 0, "f16"), ([16] * 5, 8, 72, 56, "bf16"), ([27] * 5, 32, 256, 0, "f16"),
+                                                               ([32] * 5, 16, 24, 8, "f16"), ([49] * 3, 16, 320, 0, "f16"), ([64] * 3, 8, 64, 0, "bf16"),
+                                                               ([16, 40, 3, 64, 23, 9, 100], 16, 320, 0, "f16")])
+def test_few_workgroups_with_long_lists_split_their_k_steps(heights, col_block, n, ldb_pad, dtype):
+    # groups of one to four slabs, full and partial last ones, every granule width; N below and past 64 columns; then
+    # all kinds of tiles in one launch, those of more than four slabs not split
+    rng = np.random.default_rng(len(heights) + col_block)
+    kb = 1536 // col_block
     rows = []
-    for g in range(groups):
+    for h in heights:
         blocks = rng.choice(kb, size=kb // 2, replace=False)
         cols = np.sort((blocks[:, None] * col_block + np.arange(col_block)).reshape(-1))
-        rows += [cols[rng.random(cols.size) < 0.9].tolist() for _ in range(height)]
+        rows += [cols[rng.random(cols.size) < 0.9].tolist() for _ in range(h)]
     csr = csr_from_rows(rows, 1536, rng, dtype=dtype)
     bits = synth.dense_rhs(rng, 1536, n, dtype)
-    perm = np.arange(groups * height, dtype=np.int32)
-    rg = np.arange(0, groups * height + 1, height).astype(np.int32)
+    perm = np.arange(sum(heights), dtype=np.int32)
+    rg = np.cumsum([0] + heights).astype(np.int32)
     c, v = gpu_spmm(csr, perm, rg, col_block, bits, ldb_pad=ldb_pad, ldc_pad=4)
-    plan = v.launches(n)
-    assert len(plan) == 1 and plan[0]["kernel"].startswith("vbr_spmm_kernel<%d" % ((height + 15) // 16))
+    assert len(v.launches(n)) == 1 and v.tile_ksteps().max() >= 12
     index_bit_exact(v, csr, perm, rg, col_block)
     c_ref, s = oracle.spmm(csr, bits)
     check_c(c, c_ref, s, "split K-steps")
