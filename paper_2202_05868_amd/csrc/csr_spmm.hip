@@ -304,7 +304,7 @@ extern "C" int csr_spmm(const csr_dev_t *h, const void *B_dev, int64_t ldb, floa
     const char *d = static_cast<const char *>(h->dev);
     const vbrk::EntryRowsDev rows{reinterpret_cast<const int64_t *>(d), reinterpret_cast<const int32_t *>(d + h->row_off),
                                   reinterpret_cast<const int32_t *>(d + h->col_off), reinterpret_cast<const uint16_t *>(d + h->val_off)};
-    const vbrk::EntryLaunch L = vbrk::plan_entry_rows(h->rows.start, N, ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0);
+    const vbrk::EntryLaunch L = vbrk::plan_entry_rows(h->rows.start, h->n_cols, N, ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0);
     return vbrk::launch_entry_rows(L, h->dtype, rows, h->n_rows, h->n_cols, B_dev, ldb, C_dev, ldc, N, hip_stream);
 }
 

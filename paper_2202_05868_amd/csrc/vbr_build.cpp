@@ -1235,7 +1235,7 @@ void make_entry_rows(const vbr_csr_t *csr, Team &team, int64_t tail, EntryRows &
     });
 }
 
-EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t N, bool aligned)
+EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned)
 {
     const int64_t M = (int64_t)start.size() - 1, nnz = start[(size_t)M];
     EntryLaunch L;
@@ -1244,10 +1244,12 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t N, bool a
     // / 256 columns: 32768 x 32768, 16 entries a row, N = 256: 28.8 / 32 / 38 us; graph of 16384 nodes, N = 256: 22 / 26 / 37,
     // N = 4096: 358 / 253 / 208, of 4096 nodes, N = 2048: 33 / 29 / 34; 224 entries a row, N = 512: 213 / 185 / 213, 388, N = 1024:
     // 365 / 270 / 241; 32768 rows of 16 entries and none long, N = 512: 46 / 57 / 72, N = 1024: 88 / 109 / 140.  Rows of B that start
-    // inside a cache line lie in one line more, which 64 columns pay twice.
+    // inside a cache line lie in one line more, which 64 columns pay twice and 128 half: then 128 only where rows are short and three
+    // lines of every row of B come near the L2 (16384 rows of 5 entries, N = 1000: 31 us, with 256 columns 36; 32352 of 24, N = 632: 194, 152).
     const bool all_short = M > 0 && start[1] <= kEntryLongRow && nnz <= 32 * M;
     if (N <= 64 || (aligned && (N <= 256 || all_short))) L.lanes = 8;
-    else L.lanes = N > 128 && (!aligned || (N >= 1024 && nnz * N >= ((int64_t)1 << 29))) ? 32 : 16;
+    else if (aligned) L.lanes = N >= 1024 && nnz * N >= ((int64_t)1 << 29) ? 32 : 16;
+    else L.lanes = N > 128 && !(all_short && n_cols <= 16384) ? 32 : 16;
     const int64_t Q = (N + 8 * L.lanes - 1) / (8 * L.lanes);
     // A workgroup for a row costs its barrier and the fourfold sum; it pays where one wave would still be at the row when
     // the rest is done, i.e. beyond the share of all entries that one of 4096 waves takes (graph, N = 256: 66 -> 26 us;
@@ -1294,7 +1296,7 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
 {
     int n = 0;
     if (v->by_entries) {
-        const EntryLaunch L = plan_entry_rows(v->entries.start, N, aligned);
+        const EntryLaunch L = plan_entry_rows(v->entries.start, v->n_cols, N, aligned);
         out[n++] = Launch{VBR_LAUNCH_ENTRIES, 0, (int32_t)v->n_rows, L.grid};
         return n;
     }

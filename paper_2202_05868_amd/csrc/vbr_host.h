@@ -32,7 +32,7 @@ struct EntryRowsDev {
 };
 struct EntryLaunch { int32_t lanes, n_huge, n_long; int64_t waves, grid; };
 // the launch for dense width N; aligned: rows of B begin on a cache line
-EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t N, bool aligned);
+EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned);
 int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &rows, int64_t n_rows, int64_t n_cols,
                       const void *B_dev, int64_t ldb, float *C_dev, int64_t ldc, int64_t N, void *hip_stream);
 

@@ -963,7 +963,7 @@ extern "C" int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C
     if (v->by_entries) {
         const vbrk::EntryRowsDev rows{reinterpret_cast<const int64_t *>(d + v->lay.start_off), reinterpret_cast<const int32_t *>(d + v->lay.prow_off),
                                       reinterpret_cast<const int32_t *>(d + v->lay.gcol_off), reinterpret_cast<const uint16_t *>(d + v->lay.vals_off)};
-        const vbrk::EntryLaunch L = vbrk::plan_entry_rows(v->entries.start, N, ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0);
+        const vbrk::EntryLaunch L = vbrk::plan_entry_rows(v->entries.start, v->n_cols, N, ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0);
         return vbrk::launch_entry_rows(L, v->dtype, rows, v->n_rows, v->n_cols, B_dev, ldb, C_dev, ldc, N, hip_stream);
     }
     vbrk::Params p;
