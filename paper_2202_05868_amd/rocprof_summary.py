@@ -29,6 +29,15 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COPY_BYTES = 256 * 1024 * 1024
+MULTIPLY = "(name like '%vbr_spmm%' or name like '%entry_rows%')"      # the kernels a multiply launches
+
+
+def is_multiply(kernel: str) -> bool:
+    return "vbr_spmm" in kernel or "entry_rows" in kernel
+
+
+def short(kernel: str, n: int) -> str:
+    return kernel[kernel.find("vbr_spmm" if "vbr_spmm" in kernel else "entry_rows"):][:n]
 
 
 def run(cmd, log, limit):
@@ -69,7 +78,7 @@ def main() -> int:
     bj = run(["rocprofv3", "--kernel-trace", "--stats", "-d", os.path.join(out_dir, "trace"), "-o", "t", "--"] + bench +
              ["--steps", str(args.steps)], os.path.join(out_dir, "trace.err"), 400)
     con = sqlite3.connect(os.path.join(out_dir, "trace", "t_results.db"))
-    rows = con.execute("select name, start, end from kernels where name like '%vbr_spmm%' order by start").fetchall()
+    rows = con.execute("select name, start, end from kernels where %s order by start" % MULTIPLY).fetchall()
     per_step = len(bj["roofline"]["kernel"])
     timed = rows[-args.steps * per_step:] if per_step else []
     text += ["", "## kernel trace: per kernel, dispatches / average us, over ALL dispatches of the run and over the",
@@ -82,16 +91,14 @@ def main() -> int:
     for nm in names:
         all_d = [(e - s) / 1e3 for k, s, e in rows if k == nm]
         tim_d = [(e - s) / 1e3 for k, s, e in timed if k == nm]
-        short = nm[nm.find("vbr_spmm"):][:70]
         text.append("  %-70s all %5d / %9.3f us    timed %4d / %9.3f us" % (
-            short, len(all_d), sum(all_d) / len(all_d), len(tim_d), sum(tim_d) / max(1, len(tim_d))))
+            short(nm, 70), len(all_d), sum(all_d) / len(all_d), len(tim_d), sum(tim_d) / max(1, len(tim_d))))
         step_us += sum(tim_d) / max(1, args.steps)
     text.append("  kernel time per timed step (sum over its launches): %.3f us" % step_us)
     if per_step > 1:
         spans = [max(e for _, _, e in timed[i:i + per_step]) - min(b for _, b, _ in timed[i:i + per_step])
                  for i in range(0, len(timed), per_step)]
-        text.append("  the launches of one call run side by side (the first on the caller's stream, the others on the handle's own")
-        text.append("  streams), so their durations overlap: first start to last end of a timed step, average %.3f us" % (
+        text.append("  the launches of one call follow each other: first start to last end of a timed step, average %.3f us" % (
             sum(spans) / len(spans) / 1e3))
     text.append("bench.py in the same run: ms_per_step %.4f (HIP events around the %d timed steps), value %.1f %s, clock-ramp launches %d" % (
         bj["ms_per_step"], args.steps, bj["value"], bj["unit"], bj["clock_ramp_launches"]))
@@ -110,8 +117,8 @@ def main() -> int:
                 tag, tag, sub, shown, " ".join(pmc_tail))]
             spmm_sum[tag] = 0.0
             for k, val, cnt in q:
-                if "vbr_spmm" in k:
-                    text.append("  %-70s %14.1f KiB (n=%d)" % (k[k.find("vbr_spmm"):][:70], val, cnt))
+                if is_multiply(k):
+                    text.append("  %-70s %14.1f KiB (n=%d)" % (short(k, 70), val, cnt))
                     spmm_sum[tag] += val
                 elif "elementwise" in k and "Fill" not in k:
                     text.append("  %-70s %14.1f KiB (n=%d)" % ("256 MiB streaming kernel (torch.mul out=)", val, cnt))
@@ -130,29 +137,29 @@ def main() -> int:
             os.path.join(out_dir, "mfma.err"), 180)
         con = sqlite3.connect(os.path.join(out_dir, "mfma", "p_results.db"))
         q = con.execute("select kernel_name, counter_name, avg(value), count(*) from counters_collection "
-                        "where kernel_name like '%vbr_spmm%' group by kernel_name, counter_name").fetchall()
+                        "where %s group by kernel_name, counter_name" % MULTIPLY.replace("name", "kernel_name")).fetchall()
         text += ["", "## matrix-unit and LDS counters (per dispatch, average): rocprofv3 --pmc %s -d <out>/mfma -o p -- %s %s" % (
             " ".join(ctrs), shown, " ".join(pmc_tail[:-1]))]
         per = {}
         for k, c, val, cnt in q:
-            text.append("  %-60s %-28s %16.1f (n=%d)" % (k[k.find("vbr_spmm"):][:60], c, val, cnt))
+            text.append("  %-60s %-28s %16.1f (n=%d)" % (short(k, 60), c, val, cnt))
             per.setdefault(k, {})[c] = val
         for k, cs in per.items():
             if cs.get("SQ_BUSY_CU_CYCLES"):
                 text.append("  -> MFMA busy = SQ_VALU_MFMA_BUSY_CYCLES / (4 SIMDs x SQ_BUSY_CU_CYCLES) = %.1f %%  (%s)" % (
-                    100.0 * cs.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0) / (4.0 * cs["SQ_BUSY_CU_CYCLES"]), k[k.find("vbr_spmm"):][:50]))
+                    100.0 * cs.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0) / (4.0 * cs["SQ_BUSY_CU_CYCLES"]), short(k, 50)))
         # the load path: how busy the texture-address unit is (every direct-to-LDS load goes through it)
         ctrs = ["TA_BUSY_avr", "SQ_BUSY_CU_CYCLES", "SQ_INSTS_VMEM_RD", "SQ_WAIT_ANY", "SQ_WAVE_CYCLES"]
         run(["rocprofv3", "--pmc"] + ctrs + ["-d", os.path.join(out_dir, "ta"), "-o", "p", "--"] + bench + pmc_tail[:-1],
             os.path.join(out_dir, "ta.err"), 180)
         con = sqlite3.connect(os.path.join(out_dir, "ta", "p_results.db"))
         q = con.execute("select kernel_name, counter_name, avg(value), count(*) from counters_collection "
-                        "where kernel_name like '%vbr_spmm%' group by kernel_name, counter_name").fetchall()
+                        "where %s group by kernel_name, counter_name" % MULTIPLY.replace("name", "kernel_name")).fetchall()
         text += ["", "## load path (per dispatch, average): rocprofv3 --pmc %s -d <out>/ta -o p -- %s %s" % (
             " ".join(ctrs), shown, " ".join(pmc_tail[:-1]))]
         per = {}
         for k, c, val, cnt in q:
-            text.append("  %-60s %-28s %16.1f (n=%d)" % (k[k.find("vbr_spmm"):][:60], c, val, cnt))
+            text.append("  %-60s %-28s %16.1f (n=%d)" % (short(k, 60), c, val, cnt))
             per.setdefault(k, {})[c] = val
         for k, cs in per.items():
             if cs.get("SQ_BUSY_CU_CYCLES") and cs.get("SQ_INSTS_VMEM_RD"):
@@ -161,7 +168,7 @@ def main() -> int:
                             "%.1f kernel cycles per vector-memory load instruction and CU; waves waiting %.0f %% of their time  (%s)" % (
                                 100.0 * cs.get("TA_BUSY_avr", 0.0) / per_cu, cs.get("TA_BUSY_avr", 0.0) * 256.0 / cs["SQ_INSTS_VMEM_RD"],
                                 cs["SQ_BUSY_CU_CYCLES"] / cs["SQ_INSTS_VMEM_RD"],
-                                100.0 * cs.get("SQ_WAIT_ANY", 0.0) / max(1.0, cs.get("SQ_WAVE_CYCLES", 1.0)), k[k.find("vbr_spmm"):][:50]))
+                                100.0 * cs.get("SQ_WAIT_ANY", 0.0) / max(1.0, cs.get("SQ_WAVE_CYCLES", 1.0)), short(k, 50)))
     with open(os.path.join(out_dir, "summary.txt"), "w") as f:
         f.write("\n".join(text) + "\n")
     print("\n".join(text))
