@@ -1,7 +1,7 @@
 """Collect the rocprofv3 evidence behind one ``bench.py`` line and write the short text summary
 that is kept under ``profiles/``.
 
-    python -m paper_2202_05868_amd.rocprof_summary --workload c4 --out gpurun_out/prof_c4
+    python -m paper_2202_05868_amd.rocprof_summary --workload c4 --out /tmp/prof_c4
 
 Runs, one after the other, each as its own process and under its own time limit:
 
