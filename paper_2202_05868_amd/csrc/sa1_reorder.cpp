@@ -376,7 +376,9 @@ private:
         const int64_t lx = q_.len(seed), lam = std::min(limit_of(lx), q_.KB), d = lam - lx;
         if (lx == 0 || tau_ >= 1.0) return;               // identical patterns share a class already
         // U <= I / tau <= lx / tau for a class that passes against x; one more, the quotient being rounded
-        const int64_t d_first = std::min(d, (int64_t)((double)lx / tau_) + 1 - lx);
+        // (compared before it becomes an integer: next to tau = 0 it is beyond them all)
+        const double most = (double)lx / tau_;
+        const int64_t d_first = most < (double)(lx + d) ? (int64_t)most + 1 - lx : d;
         if (d_first < d) {
             bool any = false;
             outside_at_most(seed, d_first, s, [&](int32_t, int64_t I, int64_t U) { any |= I >= need_[U]; });

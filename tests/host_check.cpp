@@ -139,6 +139,11 @@ int main()
             const Csr a = make(rng, 1 + rng.below(400), 1 + rng.below(40), col_block, 0.05 + 0.3 * rng.uni(), 1 + (int)rng.below(30));
             for (double tau : taus) check_matrix(a, col_block, tau, true);
         }
+    // thresholds next to zero, where the blocks of a row over the threshold exceed every integer
+    for (int trial = 0; trial < 3; ++trial) {
+        const Csr a = make(rng, 60 + rng.below(100), 20, 2, 0.15, 90);
+        for (double tau : {5e-324, 1e-300, 1e-20, 1e-18}) check_matrix(a, 2, tau, true);
+    }
     // thousands of short groups: the panel packing; tall groups beside them
     {
         const Csr a = make(rng, 6000, 40, 8, 0.08, 3000);

@@ -156,6 +156,20 @@ def test_reorder_by_bit_set_scan_and_by_lists_at_the_word_counts_of_the_scan(mon
         assert np.array_equal(perm, p0) and np.array_equal(rg, g0), tau
 
 
+@pytest.mark.parametrize("threads", ["1", "3"])
+@pytest.mark.parametrize("tau", [5e-324, 1e-300, 1e-20, 1e-18, 1e-17])
+def test_reorder_at_thresholds_next_to_zero(monkeypatch, threads, tau):
+    # blocks of a row divided by the threshold exceed every integer; any block in common is similarity enough, and
+    # only the merge limit decides
+    monkeypatch.setenv("VBR_SA1_THREADS", threads)
+    for n_rows, n_blocks, density in [(50, 20, 0.15), (200, 64, 0.15), (120, 300, 0.02), (60, 30, 0.6)]:
+        csr = random_csr(np.random.default_rng(3), n_rows, 2 * n_blocks, density / 2)
+        perm, rg = assert_same_blocking(csr, 2, tau)
+        curve = binding.sa1_blocking_curve(csr, 2, [tau], 8)
+        point = oracle.blocking_curve(csr, 2, [tau], 8)["points"][0]
+        assert all(curve[k][0] == point[k] for k in ("n_groups", "n_blocks", "stored_elems", "sum_heights"))
+
+
 @pytest.mark.parametrize("name,scale,noise", [("c1", 1.0, True), ("c1", 1.0, False), ("c2", 0.25, True),
                                                ("c3", 0.125, True), ("c4", 0.125, True), ("c5", 0.0625, True)])
 def test_workloads_small_scale_bit_exact(name, scale, noise):
