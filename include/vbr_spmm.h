@@ -130,13 +130,23 @@ int vbr_upload(vbr_t *v, void *buf_dev, void *hip_stream);
  * byte offsets; else VBR_EUNSUPPORTED); B itself may be larger than 4 GiB.  Products are exact, sums
  * are fp32 on the matrix units.
  * B and C must not overlap each other or the uploaded buffer.
- * Non-finite values: the zero fill-in of a stored block is multiplied like any other value, so a
- * NaN or Inf in B row k reaches every C row whose group stores the column block of k (the
- * format's semantics).  For groups lower than 16 rows, which are multiplied in slabs of 16 rows
- * cut across group boundaries, it reaches the rows of the slabs that hold such a group when the
- * slabs share whole column blocks (panels), and only the rows of the slabs one of whose rows has
- * an entry in column k itself when they gather single columns.  B rows of column blocks that no
- * group stores are never read.
+ * Non-finite values: fill-in zeros are multiplied like any other value, so a NaN or Inf in row k of B
+ * reaches the C rows that have an entry in column k and, depending on how rows are packed, rows that
+ * have none:
+ *   block tiles (groups of 16 rows or more)  all rows of every group that stores the column block of k
+ *                  (the format's semantics);
+ *   column-gathered tiles  all rows of every tile, at most 64, one of whose rows has an entry in column k.
+ *                  Groups lower than 16 rows share tiles with other groups.  A taller group is packed so when
+ *                  its blocks are mostly fill-in, when it has far more K-steps than the others, or when the block
+ *                  width is no multiple of 8; it then has tiles of its own, except in matrices whose rows are
+ *                  packed by falling length (graphs with hubs): there its rows stand among those of other groups,
+ *                  and may be reached though the group does not store the block;
+ *   panels (128 rows of groups lower than 16 rows, in slabs of 16)  all rows of every slab that stores a
+ *                  column block of the same K-step: 32 consecutive rows of the concatenation of the blocks
+ *                  the panel's groups store, that is the block of k itself and, where col_block is no multiple
+ *                  of 32, blocks next to it in that list;
+ *   entry rows     no other row.
+ * vbr_get_launches says which of these a matrix has.  B rows of column blocks that no group stores are never read.
  */
 int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C_dev, int64_t ldc,
              int64_t N, void *hip_stream);

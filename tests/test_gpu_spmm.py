@@ -367,6 +367,81 @@ def test_b_rows_no_block_touches_never_reach_c(col_block, short):
     check_c(c, c_ref, s, "poisoned B rows, cb=%d" % col_block)
 
 
+def one_row_with_column(kind):
+    """A matrix packed as ``kind`` says, its partition and block width, and a column k that one row alone has an entry in;
+    then the rows that NaN in row k of B must reach at most: a number of rows, or the rows themselves."""
+    rng = np.random.default_rng(17)
+    if kind == "gathered":              # single-row groups in clusters over the same columns: tiles of 64 rows
+        m, cols, cb = 1100, 2048, 16
+        rows = [(128 * (i // 70 % 15) + rng.choice(128, size=50, replace=False)).tolist() for i in range(m)]
+        k, limit = cols - 1, 64
+        rows[500].append(k)
+        perm, rg = np.arange(m, dtype=np.int32), np.arange(m + 1, dtype=np.int32)
+    elif kind == "gathered by length":  # a row's columns are those of the next longer one; the rows of five tall groups stand among the others
+        cols, cb, low = 4096, 16, 1500
+        order = rng.permutation(cols)
+        lens = np.concatenate([(100 * rng.random(low) ** 6 + 1).astype(int), rng.integers(150, 250, size=100)])
+        lens[77] = 300
+        rows = [order[:n].tolist() for n in lens]
+        k, limit = int(order[299]), 64
+        perm = np.arange(low + 100, dtype=np.int32)
+        rg = np.concatenate([np.arange(low + 1), low + 20 * np.arange(1, 6)]).astype(np.int32)
+    elif kind.startswith("panels"):     # a K-step is one block of 32 columns, or two of 16
+        cb = int(kind.split()[1])
+        m, cols = 6000, 14 * cb
+        rows = [np.nonzero(rng.random(13 * cb) < 0.2)[0].tolist() for _ in range(m)]
+        k, limit = 13 * cb + 3, 16 if cb == 32 else 128
+        rows[1234].append(k)
+        perm, rg = np.arange(m, dtype=np.int32), np.arange(m + 1, dtype=np.int32)
+    elif kind == "blocks":              # groups of 40 rows, blocks half full: every row of the group, no other
+        m, cols, cb = 400, 1024, 16
+        blocks = [rng.choice(60, size=12, replace=False) for _ in range(10)]
+        rows = [[int(c) for b in blocks[i // 40] for c in range(16 * b, 16 * b + 16) if rng.random() < 0.5] for i in range(m)]
+        k, limit = cols - 5, np.arange(120, 160)
+        rows[130].append(k)
+        perm, rg = np.arange(m, dtype=np.int32), np.arange(0, m + 1, 40, dtype=np.int32)
+    else:                               # entry rows: the row itself, no other
+        m, cols, cb = 9000, 6400, 32
+        rows = [rng.choice(cols - 1, size=12, replace=False).tolist() for _ in range(m)]
+        k, limit = cols - 1, np.array([4321])
+        rows[4321].append(k)
+        perm, rg = np.arange(m, dtype=np.int32), np.arange(m + 1, dtype=np.int32)
+    return csr_from_rows(rows, cols, rng), perm, rg, cb, k, limit
+
+
+@pytest.mark.parametrize("kind,kernel", [("gathered", "vbr_spmm_kernel<4 slabs, column-gathered>"), ("gathered by length", "vbr_spmm_kernel<4 slabs, column-gathered>"),
+                                         ("panels 16", "vbr_spmm_panel_kernel"), ("panels 32", "vbr_spmm_panel_kernel"),
+                                         ("blocks", "vbr_spmm_kernel<4 slabs>"), ("entries", "entry_rows_kernel")])
+def test_rows_that_a_nan_in_b_reaches(kind, kernel):
+    # what the header says about non-finite values, packing by packing: the row that has an entry in that column, and
+    # of the others at most those that share its tile, panel slab or group; all the rest is right to the last element
+    csr, perm, rg, cb, k, limit = one_row_with_column(kind)
+    rows = np.repeat(np.arange(csr["n_rows"]), np.diff(csr["row_ptr"]))
+    own = rows[csr["col_idx"] == k]
+    assert own.size == 1
+    clean = synth.dense_rhs(np.random.default_rng(3), csr["n_cols"], 72, "f16")
+    bits = clean.copy()
+    bits[k] = 0x7E00
+    c, v = gpu_spmm(csr, perm, rg, cb, bits)
+    assert v.launches(72)[0]["kernel"] == kernel
+    hit = np.isnan(c).any(axis=1)
+    assert np.isnan(c[hit]).all() and hit[own[0]]
+    reached = np.nonzero(hit)[0]
+    if isinstance(limit, int):
+        assert reached.size <= limit, reached.size
+    else:
+        assert np.array_equal(reached, limit)
+    if kind.startswith("gathered") or kind == "panels 16":
+        assert reached.size > 16                     # a tile is not one slab, nor is what a K-step of two blocks reaches ...
+    if kind == "gathered by length":
+        assert (reached >= 1500).any()               # ... nor only of low groups: these have other blocks only
+        group = np.searchsorted(rg, reached, side="right") - 1
+        stored = {int(np.searchsorted(rg, r, side="right") - 1) for r in rows[csr["col_idx"] // cb == k // cb]}
+        assert any(int(g) not in stored for g in group[reached >= 1500])
+    c_ref, s = oracle.spmm(csr, clean)
+    check_c(c[~hit], c_ref[~hit], s[~hit], "rows a NaN in B does not reach, " + kind)
+
+
 def test_runs_on_the_given_stream_and_in_a_captured_graph():
     # vbr_spmm only enqueues kernels on the stream it is given (no allocation, no memset, no
     # synchronisation), so it can run on a side stream and be captured into a graph; every replay
