@@ -583,6 +583,17 @@ constexpr int kStagesTall = 3;  // the same for block tiles of 5 to 8 slabs (80 
 constexpr int kStagesFew = 4;   // for tiles of 1 and 2 slabs in a launch whose workgroups are all resident with two on a CU
 constexpr int kADistance = 3;   // K-steps the A fragments are requested ahead (more than the ring of B panels has slots)
 constexpr int a_distance(int stages) { return stages > kADistance ? stages : kADistance; }
+// Tiles of two slabs request their fragments one K-step later, which makes the ring 2 KiB smaller and, with the lists, lets four
+// workgroups be resident on a CU instead of three: 256 groups of 32 rows, 26 K-steps, N = 1024 (1024 workgroups): 36.3 -> 26.6 us,
+// 60 K-steps, N = 4096: 218 -> 201; launches that were resident before take the same (768 workgroups: 21.4 and 21.1).
+constexpr int kADistanceTwo = 2;
+constexpr int kLdsBytes = 160 * 1024;
+static_assert(4 * tile_lds_bytes<1, kStages, kADistance, true>() <= kLdsBytes && 4 * tile_lds_bytes<1, kStages, kADistance, false>() <= kLdsBytes &&
+                  4 * tile_lds_bytes<2, kStages, kADistanceTwo, true>() <= kLdsBytes && 4 * tile_lds_bytes<2, kStages, kADistanceTwo, false>() <= kLdsBytes,
+              "four workgroups of one- and two-slab tiles on a CU");
+static_assert(3 * tile_lds_bytes<4, kStages, kADistance, true>() <= kLdsBytes, "three of gathered tiles of 3 to 4 slabs");
+static_assert(2 * tile_lds_bytes<4, kStagesTall, kADistance, false>() <= kLdsBytes && 2 * tile_lds_bytes<8, kStagesTall, kADistance, false>() <= kLdsBytes,
+              "two of taller block tiles");
 
 // Measured on the 16-row workload: two ring slots and four resident workgroups per CU (36 KiB of
 // LDS each) beat deeper rings with fewer workgroups; the gather is bound by how many independent
@@ -886,7 +897,7 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             kernel = L.split ? vbr_spmm_split_kernel<DT, 1, true> : few ? vbr_spmm_kernel<DT, 1, kStagesFew, kStagesFew, true> : vbr_spmm_kernel<DT, 1, kStages, kADistance, true>;
             break;
         case VBR_LAUNCH_GATHER_2:
-            kernel = L.split ? vbr_spmm_split_kernel<DT, 2, true> : few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew, true> : vbr_spmm_kernel<DT, 2, kStages, kADistance, true>;
+            kernel = L.split ? vbr_spmm_split_kernel<DT, 2, true> : few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew, true> : vbr_spmm_kernel<DT, 2, kStages, kADistanceTwo, true>;
             break;
         case VBR_LAUNCH_GATHER_4:
             kernel = L.split ? vbr_spmm_split_kernel<DT, 4, true> : few ? vbr_spmm_kernel<DT, 4, kStagesTall, kADistance, true> : vbr_spmm_kernel<DT, 4, kStages, kADistance, true>;
@@ -895,7 +906,7 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             kernel = L.split ? vbr_spmm_split_kernel<DT, 1, false> : few ? vbr_spmm_kernel<DT, 1, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 1, kStages, kADistance>;
             break;
         case VBR_LAUNCH_TILE_2:
-            kernel = L.split ? vbr_spmm_split_kernel<DT, 2, false> : few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 2, kStages, kADistance>;
+            kernel = L.split ? vbr_spmm_split_kernel<DT, 2, false> : few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 2, kStages, kADistanceTwo>;
             break;
         case VBR_LAUNCH_TILE_4:
             kernel = L.split ? vbr_spmm_split_kernel<DT, 4, false> : vbr_spmm_kernel<DT, 4, kStagesTall, kADistance>;

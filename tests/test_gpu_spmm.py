@@ -209,6 +209,31 @@ def test_few_workgroups_with_long_lists_split_their_k_steps(heights, col_block, 
     check_c(c, c_ref, s, "split K-steps")
 
 
+@pytest.mark.parametrize("col_block", [32, 4])
+@pytest.mark.parametrize("n_ks,groups,n,dtype", [(1, 5, 264, "f16"), (2, 5, 256, "bf16"), (3, 5, 264, "f16"), (4, 5, 8, "f16"), (7, 5, 264, "bf16"), (26, 131, 1032, "f16")])
+def test_two_slab_tiles_at_the_lengths_of_their_rings(col_block, n_ks, groups, n, dtype):
+    # block tiles and column-gathered ones of 17 to 32 rows, lists shorter than the rings of B rows and fragments up to long
+    # ones in more workgroups than are split or take deeper rings
+    rng = np.random.default_rng(n_ks)
+    heights = [32, 17, 25, 31, 32] * (groups // 5) + [20] * (groups % 5)
+    kb = 1024 // col_block
+    rows = []
+    for h in heights:
+        cols = np.sort((rng.choice(kb, size=n_ks * 32 // col_block, replace=False)[:, None] * col_block + np.arange(col_block)).reshape(-1))
+        rows += [cols.tolist() for _ in range(h)]
+    csr = csr_from_rows(rows, 1024, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, 1024, n, dtype)
+    perm, rg = rng.permutation(len(rows)).astype(np.int32), np.cumsum([0] + heights).astype(np.int32)
+    inv = np.argsort(perm)
+    csr = synth.permute_rows(csr, inv)               # row perm[i] of the permuted matrix is row i of the groups
+    c, v = gpu_spmm(csr, perm, rg, col_block, bits)
+    assert [p["kernel"] for p in v.launches(n)] == ["vbr_spmm_kernel<2 slabs%s>" % (", column-gathered" if col_block == 4 else "")]
+    assert set(v.tile_ksteps().tolist()) == {n_ks}
+    index_bit_exact(v, csr, perm, rg, col_block)
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "two slabs, %d K-steps" % n_ks)
+
+
 @pytest.mark.parametrize("tail", [1, 15, 16, 33, 63, 64])
 def test_slabs_of_low_rows_that_share_columns_form_taller_tiles(tail):
     # 1024 + tail single-row groups in clusters over the same columns: tiles of 1 to 4 slabs, the last one partial
