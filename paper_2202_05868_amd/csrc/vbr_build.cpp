@@ -1315,9 +1315,22 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
     if (T > 0) {
         const bool one_kind = classes == 1 && (T == v->n_work || last == kClasses - 1);
         // Tiles of up to four slabs with long lists whose workgroups leave CUs idle: four workgroups of 64 columns each instead, whose
-        // waves split the K-steps (16 x 16 blocks at 12 %, 1024 x 16000, N = 512, 128 workgroups: 26 -> 12 us; at 8 %, 1024 x 4096: 9.4 -> 5.6;
-        // no gain beyond one workgroup per CU, nor, 64 columns lying in two lines, at half of that where rows of B begin inside a line).
-        const bool split = T * Qt <= (aligned ? 320 : 128) && v->class_count[3] < T && v->dev_tiles[0].n_ks >= kSplitSteps;
+        // waves split the K-steps.  Two of these fit on a CU, and per K-step they take 4 B loads and a fragment per slab for 64
+        // columns where the others take 16 and one per slab for 256, so the gain ends the sooner the taller the tiles are: at 300 workgroups
+        // (before splitting) of one slab, 192 of two, 128 of three or four, each of them 1/300, 1/192 and 1/128 of what may be split.  Not
+        // split and split, 60 K-steps of 32-column blocks, N = 512: one slab, 256 workgroups 22.9 and 20.8 us, 300: 26.9 and 25.6 (13
+        // K-steps: 10.0 and 9.5; 26, 320: 14.4 and 14.9); two slabs, 192: 24.7 and 21.3, 256: 25.0 and 27.0; four, 128: 25.7 and 22.8,
+        // 136: 25.9 and 33.5.  Where rows of B begin inside a line 64 columns lie in two: 168, 135 and 112 (26 K-steps, N = 504: one slab,
+        // 168: 12.5 and 11.5, 192: 12.6 and 12.7; two, 128: 13.4 and 10.4, 192: 13.7 and 15.7; four, 112: 14.6 and 13.5, 192: 15.2 and 23.1).
+        // Tiles of more slabs are not split; where one of them takes longest, splitting the others brings nothing (heights 1 to 100, N = 1000,
+        // 80 workgroups: 13.9 and 14.9).  A deep tile is split already.
+        static constexpr int64_t share_of_class[2][kClasses] = {{57, 71, 85, 100, 12, 57, 71, 85}, {32, 50, 75, 100, 12, 32, 50, 75}};   // in 9600ths
+        int64_t shares = 0, splittable = 0;
+        for (int c = 0; c < kClasses; ++c) {
+            shares += share_of_class[aligned][c] * v->class_count[c] * Qt;
+            if (c != 3 && c != kClassDeep) splittable += v->class_count[c];
+        }
+        const bool split = shares <= 9600 && splittable > 0 && v->dev_tiles[0].n_ks >= kSplitSteps && v->dev_tiles[0].n_slabs <= 4;
         const int32_t kind = one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED;
         const int64_t grid = !split ? grid_size(T, Qt) : kind == VBR_LAUNCH_TILE_MIXED ? grid_size(4 * (int64_t)T, Qt) : grid_size(T, (N + kDeepN - 1) / kDeepN);
         out[n++] = Launch{kind, 0, T, grid, split};

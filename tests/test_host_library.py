@@ -342,3 +342,22 @@ def test_launch_plan_lists_what_a_call_issues():
     plan = v.launches(256)
     assert [p["kernel"] for p in plan] == ["vbr_spmm_kernel<1 slab, column-gathered>"] and plan[0]["tiles"] == 6000 // 16
     v.audit()
+
+
+@pytest.mark.parametrize("height,n,most", [(16, 256, 300), (32, 256, 192), (64, 256, 128), (50, 256, 128), (16, 248, 168), (32, 248, 135), (64, 248, 112)])
+def test_launches_are_split_up_to_a_number_of_workgroups_that_falls_with_the_height_of_the_tiles(height, n, most):
+    # block tiles of 13 K-steps, one column tile: four workgroups each up to that number (two of the split kernel fit on a CU), one beyond
+    rows = [list(range(416))] * height
+    for groups, split in ((most, True), (most + 1, False)):
+        csr = csr_from_rows(rows * groups, 416)
+        v = binding.vbr_build(csr, np.arange(height * groups, dtype=np.int32), np.arange(0, height * groups + 1, height, dtype=np.int32), 32)
+        plan = v.launches(n)
+        assert len(plan) == 1 and plan[0]["tiles"] == groups
+        assert (plan[0]["workgroups"] >= 4 * groups) == split, plan
+
+
+def test_launches_are_not_split_where_a_tile_that_cannot_be_takes_longest():
+    csr = csr_from_rows([list(range(416))] * 180, 416)
+    rg = np.array([0, 100, 120, 140, 160, 180], dtype=np.int32)         # one group of seven slabs, four of two
+    v = binding.vbr_build(csr, np.arange(180, dtype=np.int32), rg, 32)
+    assert [(p["tiles"], p["workgroups"]) for p in v.launches(256)] == [(5, 8)]
