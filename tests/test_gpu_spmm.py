@@ -234,6 +234,21 @@ def test_two_slab_tiles_at_the_lengths_of_their_rings(col_block, n_ks, groups, n
     check_c(c, c_ref, s, "two slabs, %d K-steps" % n_ks)
 
 
+@pytest.mark.parametrize("n", [8, 24, 56, 64, 72, 264, 312, 320])
+@pytest.mark.parametrize("heights,col_block", [([128, 70, 100], 16), ([128, 70, 40, 18, 33, 16, 3, 9, 2], 16), ([60, 20, 7], 3)])
+def test_column_tiles_of_fewer_than_64_columns(heights, col_block, n):
+    # the only or the last column tile narrower than what a wave turns round in LDS, exactly as wide, and wider: block tiles of
+    # every height, gathered ones, full and partial slabs, nothing written beside the N columns
+    rng = np.random.default_rng(n)
+    m = sum(heights)
+    csr = random_csr(rng, m, 48 * col_block, 0.1)
+    bits = synth.dense_rhs(rng, 48 * col_block, n, "f16")
+    perm, rg = rng.permutation(m).astype(np.int32), np.cumsum([0] + heights).astype(np.int32)
+    c, v = gpu_spmm(csr, perm, rg, col_block, bits, ldb_pad=8, ldc_pad=12)
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "N = %d" % n)
+
+
 @pytest.mark.parametrize("tail", [1, 15, 16, 33, 63, 64])
 def test_slabs_of_low_rows_that_share_columns_form_taller_tiles(tail):
     # 1024 + tail single-row groups in clusters over the same columns: tiles of 1 to 4 slabs, the last one partial
