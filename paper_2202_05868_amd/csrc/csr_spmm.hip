@@ -244,9 +244,9 @@ extern "C" int csr_spmm_create(const vbr_csr_t *csr, csr_dev_t **out)
 {
     if (!csr || !out) return VBR_EINVAL;
     *out = nullptr;
-    const int rc = vbrk::validate_csr(csr, true);
-    if (rc != VBR_OK) return rc;
     try {
+        const int rc = vbrk::validate_csr(csr, true);
+        if (rc != VBR_OK) return rc;
         std::unique_ptr<csr_dev> h(new csr_dev());
         h->n_rows = csr->n_rows;
         h->n_cols = csr->n_cols;

@@ -580,10 +580,10 @@ extern "C" int sa1_reorder(const vbr_csr_t *csr, int32_t col_block, double tau, 
 {
     if (!csr || !perm || !row_groups || !n_groups) return VBR_EINVAL;
     if (col_block <= 0 || !(tau >= 0.0 && tau <= 1.0)) return VBR_EINVAL;
-    int rc = vbrk::validate_csr(csr, false);
-    if (rc != VBR_OK) return rc;
-    if (csr->n_cols % col_block != 0) return VBR_EINVAL;
     try {
+        const int rc = vbrk::validate_csr(csr, false);
+        if (rc != VBR_OK) return rc;
+        if (csr->n_cols % col_block != 0) return VBR_EINVAL;
         return vbrk::sa1_reorder_impl(csr, col_block, tau, perm, row_groups, n_groups);
     } catch (const std::bad_alloc &) {
         return VBR_ENOMEM;
@@ -599,10 +599,10 @@ extern "C" int sa1_blocking_curve(const vbr_csr_t *csr, int32_t col_block, const
     if (!csr || !taus || n_taus <= 0 || col_block <= 0 || target_height <= 0) return VBR_EINVAL;
     for (int32_t i = 0; i < n_taus; ++i)
         if (!(taus[i] >= 0.0 && taus[i] <= 1.0)) return VBR_EINVAL;
-    int rc = vbrk::validate_csr(csr, false);
-    if (rc != VBR_OK) return rc;
-    if (csr->n_cols % col_block != 0) return VBR_EINVAL;
     try {
+        const int rc = vbrk::validate_csr(csr, false);
+        if (rc != VBR_OK) return rc;
+        if (csr->n_cols % col_block != 0) return VBR_EINVAL;
         // The quotient matrix is the same for every threshold; the thresholds are independent of each other
         // and are dealt to the threads.  A stored block of group g has the group's height, and the group's
         // pattern lists its blocks, so the counts follow from the grouping of the classes alone.

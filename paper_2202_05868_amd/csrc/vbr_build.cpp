@@ -988,16 +988,16 @@ extern "C" int vbr_build(const vbr_csr_t *csr, const int32_t *perm, const int32_
 {
     if (!csr || !out || n_groups < 0 || col_block <= 0) return VBR_EINVAL;
     *out = nullptr;
-    int rc = vbrk::validate_csr(csr, true);
-    if (rc != VBR_OK) return rc;
-    if (csr->n_cols % col_block != 0) return VBR_EINVAL;
-    const int64_t M = csr->n_rows;
-    if ((M > 0 && (!perm || !row_groups)) || !row_groups) return VBR_EINVAL;
-    if (n_groups > M || (M > 0 && n_groups == 0)) return VBR_EINVAL;
-    if (row_groups[0] != 0 || row_groups[n_groups] != M) return VBR_EINVAL;
-    for (int32_t g = 0; g < n_groups; ++g)
-        if (row_groups[g + 1] <= row_groups[g]) return VBR_EINVAL;
     try {
+        int rc = vbrk::validate_csr(csr, true);
+        if (rc != VBR_OK) return rc;
+        if (csr->n_cols % col_block != 0) return VBR_EINVAL;
+        const int64_t M = csr->n_rows;
+        if ((M > 0 && (!perm || !row_groups)) || !row_groups) return VBR_EINVAL;
+        if (n_groups > M || (M > 0 && n_groups == 0)) return VBR_EINVAL;
+        if (row_groups[0] != 0 || row_groups[n_groups] != M) return VBR_EINVAL;
+        for (int32_t g = 0; g < n_groups; ++g)
+            if (row_groups[g + 1] <= row_groups[g]) return VBR_EINVAL;
         std::vector<uint8_t> seen((size_t)M, 0);
         for (int64_t i = 0; i < M; ++i) {
             if (perm[i] < 0 || perm[i] >= M || seen[perm[i]]) return VBR_EINVAL;   // not a bijection

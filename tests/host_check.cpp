@@ -8,9 +8,28 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "vbr_spmm.h"
+
+// Allocations of the thread that sets it: as many succeed as it says, then they fail (negative: all succeed).
+static thread_local long g_allocations_left = -1;
+static void *allocate(std::size_t n)
+{
+    if (g_allocations_left == 0) return nullptr;
+    if (g_allocations_left > 0) --g_allocations_left;
+    return std::malloc(n ? n : 1);
+}
+void *operator new(std::size_t n)
+{
+    if (void *p = allocate(n)) return p;
+    throw std::bad_alloc();
+}
+void *operator new(std::size_t n, const std::nothrow_t &) noexcept { return allocate(n); }
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, std::size_t) noexcept { std::free(p); }
+void operator delete(void *p, const std::nothrow_t &) noexcept { std::free(p); }
 
 extern "C" {
 int oracle_sa1(int64_t n_rows, int64_t n_cols, const int64_t *row_ptr, const int32_t *col_idx, int32_t col_block,
@@ -127,6 +146,49 @@ void check_matrix(const Csr &a, int col_block, double tau, bool all_blocks)
     vbr_free(v);
 }
 
+// Every call with the first 0, 1, 2 ... of its allocations succeeding, up to `most` or until it gets all it asks for: it
+// reports the failure, and nothing is thrown through the C interface.
+template <class F>
+void check_out_of_memory(F call, long most)
+{
+    ++g_cases;
+    for (long n = 0; n < most; ++n) {
+        int rc = 1;
+        bool thrown = false;
+        g_allocations_left = n;
+        try {
+            rc = call();
+        } catch (...) {
+            thrown = true;
+        }
+        g_allocations_left = -1;
+        REQUIRE(!thrown);
+        if (rc == VBR_OK) return;
+        REQUIRE(rc == VBR_ENOMEM);
+    }
+    REQUIRE(most < 100);
+}
+
+void check_out_of_memory(const Csr &a, int col_block, long most)
+{
+    const vbr_csr_t c = a.view();
+    std::vector<int32_t> perm((size_t)a.m), rg((size_t)a.m + 1);
+    int32_t G = 0;
+    REQUIRE(sa1_reorder(&c, col_block, 0.5, perm.data(), rg.data(), &G) == VBR_OK);
+    std::vector<int32_t> perm1((size_t)a.m), rg1((size_t)a.m + 1);
+    int32_t G1 = 0, sel = 0;
+    const double ts[] = {0.2, 0.6};
+    check_out_of_memory([&] { return sa1_reorder(&c, col_block, 0.5, perm1.data(), rg1.data(), &G1); }, most);
+    check_out_of_memory([&] { return sa1_blocking_curve(&c, col_block, ts, 2, 8, nullptr, nullptr, nullptr, nullptr, &sel); }, most);
+    check_out_of_memory([&] {
+        vbr_t *v = nullptr;
+        const int rc = vbr_build(&c, perm.data(), rg.data(), G, col_block, &v);
+        if (rc != VBR_OK && v != nullptr) return 1;
+        vbr_free(v);
+        return rc;
+    }, most);
+}
+
 }  // namespace
 
 int main()
@@ -174,6 +236,17 @@ int main()
         REQUIRE(sa1_reorder(&c, 3, 0.5, perm.data(), rg.data(), &sel) == VBR_EINVAL);            // 80 % 3 != 0
         REQUIRE(vbr_audit(nullptr) == VBR_EINVAL);
         ++g_cases;
+    }
+    // memory that runs out: at every allocation of a small matrix, and at the first ones of a matrix whose check takes threads
+    {
+        check_out_of_memory(make(rng, 90, 20, 8, 0.2, 40), 8, 100000);
+        Csr a;
+        a.m = 512;
+        a.k = 4096;
+        for (int64_t i = 0; i <= a.m; ++i) a.row_ptr.push_back(i * a.k);
+        for (int64_t i = 0; i < a.m * a.k; ++i) a.col.push_back((int32_t)(i % a.k));
+        a.val.assign(a.col.size(), 0x3c00);
+        check_out_of_memory(a, 64, 4);
     }
     std::printf("host_check ok: %d cases\n", g_cases);
     return 0;
