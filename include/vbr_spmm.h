@@ -12,8 +12,8 @@
  *   vbr_build     row partition + column partition -> variable-block-row matrix that keeps
  *                 only the nonzero blocks, zero-filled (section 2, section 3.1 last paragraph).
  *   vbr_spmm      C = A.B, every stored block multiplied as a small dense product on the
- *                 matrix units (section 4.4.1), in one launch per kernel class the matrix
- *                 needs (at most nine: see vbr_get_launches below).
+ *                 matrix units (section 4.4.1), in one to three launches (see vbr_get_launches
+ *                 below).
  *
  * sa1_reorder and vbr_build are deterministic integer host code.  vbr_spmm runs on the GPU.
  * All pointers are HOST pointers unless the name ends in _dev.  Nothing is retained from the
@@ -152,13 +152,16 @@ int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C_dev, int64
              int64_t N, void *hip_stream);
 
 /*
- * The kernel launches one vbr_spmm call with dense width N issues, in issue order (for reporting;
- * vbr_spmm itself launches from the same plan).  Rows of groups lower than 16 rows are multiplied
- * 128 at a time, by the panel kernel (their slabs of 16 rows share the B rows of the union of their
- * column blocks) or by the tile kernel on column-gathered tiles of 1 to 4 slabs (every tile loads exactly the
- * B rows of the columns its rows touch), whichever packing needs fewer loads; the other groups by the tile
- * kernel, on whole column blocks or, where the blocks are mostly fill-in, on the columns the rows
- * of a tile touch (VBR_LAUNCH_GATHER_*).  A gathered tile with far more columns than the others is deep: four
+ * The kernel launches one vbr_spmm call with dense width N issues, in issue order (for reporting), for a B
+ * whose rows follow each other without padding from a 128-byte aligned address on (ldb = N).  vbr_spmm
+ * plans likewise with the ldb and the address it is given: with rows of B that begin inside a cache line where N is a
+ * multiple of 64, or on one where it is not, the launches, their kernels and tiles are the same, the grid sizes
+ * may differ (whether a launch is split over the K-steps, how many columns a wave of the entry-row kernel takes).
+ * Rows of groups lower than 16 rows stand in a list of their own.  128 of them may be a panel (their slabs of 16 rows
+ * share the B rows of the union of their column blocks), where that needs fewer loads; the others form column-gathered
+ * tiles of 1 to 4 slabs (every tile loads exactly the B rows of the columns its rows touch).  The other groups are
+ * multiplied by the tile kernel too, on whole column blocks or, where the blocks are mostly fill-in, on the columns
+ * the rows of a tile touch (VBR_LAUNCH_GATHER_*).  A gathered tile with far more columns than the others is deep: four
  * workgroups per 256 columns, whose waves split its columns.  Tiles of one class (height, packing) are one launch
  * of the kernel for it, tiles of several classes one launch of the mixed kernel; many tiles without
  * an entry have a launch of their own behind it; a large matrix in whose rows the blocking found nothing to share is
@@ -171,18 +174,22 @@ enum {
     VBR_LAUNCH_PANEL = 0, VBR_LAUNCH_TILE_1 = 1, VBR_LAUNCH_TILE_2 = 2, VBR_LAUNCH_TILE_4 = 3,
     VBR_LAUNCH_TILE_8 = 4, VBR_LAUNCH_TILE_MIXED = 5,
     VBR_LAUNCH_GATHER_1 = 6, VBR_LAUNCH_GATHER_2 = 7, VBR_LAUNCH_GATHER_4 = 8,
-    VBR_LAUNCH_ENTRIES = 9
+    VBR_LAUNCH_ENTRIES = 10     /* 9 was gathered tiles of 8 slabs, which are built no more */
 };
 int vbr_get_launches(const vbr_t *v, int64_t N, int32_t *n_launches, int32_t *kinds, int64_t *tiles,
                      int64_t *workgroups);
 
-/* Number of workgroup tiles and K-steps of the schedule (for reporting). */
+/*
+ * Number of workgroup tiles and panels, and of K-steps, of the schedule, and of packed 16-bit values (for reporting).  A
+ * matrix kept as entry rows (VBR_LAUNCH_ENTRIES) has none of either: n_tiles is its rows, n_ksteps 0.
+ */
 int vbr_get_schedule(const vbr_t *v, int64_t *n_tiles, int64_t *n_ksteps, int64_t *packed_elems);
 
 /*
  * K-steps (32 gathered B rows each) every workgroup tile walks, for judging the balance of the
- * schedule: the tiles in launch order of their classes, then the column-gathered slabs, then the
- * panels.  Returns their number; fills out[0 .. min(number, cap) - 1] when out is not NULL.
+ * schedule: the block tiles group by group, then the column-gathered tiles in the order of their rows, then the
+ * panels (not in launch order, and a deep tile once).  Returns their number, 0 for a matrix kept as entry rows; fills
+ * out[0 .. min(number, cap) - 1] when out is not NULL.
  */
 int64_t vbr_get_tile_ksteps(const vbr_t *v, int64_t *out, int64_t cap);
 

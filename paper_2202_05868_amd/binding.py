@@ -213,10 +213,11 @@ class Vbr:
     LAUNCH_KINDS = ("vbr_spmm_panel_kernel", "vbr_spmm_kernel<1 slab>", "vbr_spmm_kernel<2 slabs>",
                     "vbr_spmm_kernel<4 slabs>", "vbr_spmm_kernel<8 slabs>", "vbr_spmm_mixed_kernel",
                     "vbr_spmm_kernel<1 slab, column-gathered>", "vbr_spmm_kernel<2 slabs, column-gathered>",
-                    "vbr_spmm_kernel<4 slabs, column-gathered>", "entry_rows_kernel")
+                    "vbr_spmm_kernel<4 slabs, column-gathered>", None, "entry_rows_kernel")     # 9: no kernel any more
 
     def launches(self, n: int) -> list:
-        """The kernel launches one ``spmm`` with dense width ``n`` issues, from the library's plan."""
+        """The kernel launches one ``spmm`` with a B of shape [K, n], rows not padded, issues, from the library's plan (with padded
+        rows or a slice the grid sizes may differ)."""
         kinds = np.zeros(16, dtype=np.int32)
         tiles = np.zeros(16, dtype=np.int64)
         wgs = np.zeros(16, dtype=np.int64)
@@ -236,7 +237,7 @@ class Vbr:
         return out
 
     def tile_ksteps(self) -> np.ndarray:
-        """K-steps of every workgroup tile of the schedule (tiles, column-gathered slabs, panels)."""
+        """K-steps of every workgroup tile of the schedule (block tiles, column-gathered tiles, panels); none for a matrix kept as entry rows."""
         n = int(_lib.vbr_get_tile_ksteps(self._h, None, 0))
         out = np.zeros(max(n, 1), dtype=np.int64)
         _lib.vbr_get_tile_ksteps(self._h, out.ctypes.data_as(ctypes.c_void_p), n)

@@ -344,6 +344,18 @@ def test_launch_plan_lists_what_a_call_issues():
     v.audit()
 
 
+
+def test_a_matrix_kept_as_entry_rows_reports_its_rows_and_no_tiles():
+    csr = csr_from_rows([[int(c)] for c in np.random.default_rng(2).integers(0, 16384, size=9000)], n_cols=16384)
+    v = binding.vbr_build(csr, np.arange(9000, dtype=np.int32), np.arange(9001, dtype=np.int32), 16)
+    assert [(p["kernel"], p["tiles"]) for p in v.launches(256)] == [("entry_rows_kernel", 9000)]
+    assert v.schedule()["n_tiles"] == 9000 and v.schedule()["n_ksteps"] == 0
+    assert v.tile_ksteps().size == 0
+    kinds, n = np.zeros(3, dtype=np.int32), ctypes.c_int32()
+    assert binding._lib.vbr_get_launches(v._h, 256, ctypes.byref(n), kinds.ctypes.data_as(ctypes.c_void_p), None, None) == 0
+    assert n.value == 1 and kinds[0] == 10               # a code no other kernel ever had
+
+
 @pytest.mark.parametrize("height,n,most", [(16, 256, 300), (32, 256, 192), (64, 256, 128), (50, 256, 128), (16, 248, 168), (32, 248, 135), (64, 248, 112)])
 def test_launches_are_split_up_to_a_number_of_workgroups_that_falls_with_the_height_of_the_tiles(height, n, most):
     # block tiles of 13 K-steps, one column tile: four workgroups each up to that number (two of the split kernel fit on a CU), one beyond
