@@ -967,7 +967,7 @@ void Builder::schedule()
 void Builder::lay_out()
 {
     DeviceLayout &L = v->lay;
-    L.zeros_off = 0;                   // 256 zero bytes the kernel reads for padding
+    L.zeros_off = 0;                   // 256 zero bytes the panel kernel reads for padding
     L.tiles_off = 256;
     L.krow_off = align_up(L.tiles_off + (int64_t)v->dev_tiles.size() * (int64_t)sizeof(TileDesc), 256);
     L.perm_off = align_up(L.krow_off + (int64_t)v->krow.size() * 4, 256);

@@ -23,12 +23,13 @@ constexpr int kTileN = 256;         // C columns per workgroup of the tile kerne
 constexpr int kPanelN = 128;        // C columns per workgroup of the panel kernel
 constexpr int kXcd = 8;             // L2 domains; workgroup i runs on domain i % 8
 
-// One workgroup tile: up to kMaxSlabs slabs of ONE row group, walked over the group's K-steps.
+// One workgroup tile: up to kMaxSlabs slabs of ONE row group, walked over the group's K-steps (a block tile), or up to
+// kMaxGatherSlabs slabs of the row list, walked over the columns its rows touch (a column-gathered tile).
 struct TileDesc {
-    int32_t ks_begin;    // first K-step of the tile's group (global K-step number)
-    int32_t n_ks;        // K-steps of the group
+    int32_t ks_begin;    // first K-step of the tile's group (global K-step number); gathered: of the tile, in gcol
+    int32_t n_ks;        // K-steps of the group; gathered: of the tile
     int64_t a_off;       // first value of the tile, in units of 8 values (16 bytes)
-    int32_t row_begin;   // position in perm of the tile's first row
+    int32_t row_begin;   // position in perm of the tile's first row; gathered: in prow
     int32_t n_rows;      // rows of the tile, 1 .. 16 * n_slabs
     int32_t n_slabs;     // ceil(n_rows / 16)
     int32_t group;       // row group the tile belongs to; column-gathered tiles: kTileGathered, or kTileDeep less the quarter

@@ -1,5 +1,5 @@
 // vbr_spmm on gfx950: C = A.B with A in packed VBR form (section 4.4.1 of the paper: every stored
-// block is multiplied as a dense product on the matrix units).  Three kernels share one scheme: a
+// block is multiplied as a dense product on the matrix units).  The kernels share one scheme: a
 // workgroup owns some slabs of 16 rows and a column tile of C, walks a list of K-steps of 32 B rows,
 // brings the gathered B rows and the A fragments into rings of LDS slots with 128-bit direct-to-LDS
 // loads, and issues v_mfma_f32_16x16x32 on them.
@@ -8,7 +8,8 @@
 //                  rows of low groups, and of tall groups whose blocks are mostly fill-in
 //   deep tiles     gathered tiles with very many columns: the waves of a workgroup split the K-steps
 //   panel kernel   8 slabs of low groups x 128 columns walking the union of their column blocks
-// All tiles of a matrix are one launch.
+//   mixed kernel   tiles of several of these classes in one launch
+// Matrices whose rows share nothing are multiplied by the kernel in csr_spmm.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -50,7 +51,6 @@ struct Params {
     const int32_t *prow;      // ... and the list of the low rows their row positions refer to
     int32_t b_fits24;         // the rows of B the matrix can touch span less than 4 GiB, their number and length in bytes less than 2^24
     const uint16_t *vals;
-    const uint16_t *zeros;    // 256 zero bytes: source of padding rows, padding lanes and columns >= N
     const uint16_t *B;
     float *C;
     int64_t ldb, ldc;
@@ -135,9 +135,9 @@ constexpr bool has_lists() { return GATHER || S < 8; }
 template <int S, int NS, int DA, bool GATHER>
 constexpr int tile_lds_bytes() { return NS * kPanelBytes + (DA + 1) * S * kFragBytes + (has_lists<S, GATHER>() ? kListBytes : 0); }
 
-// GATHER: the tile is a slab of rows of low row groups whose K dimension is the list of the single
-// COLUMNS its rows touch (one gather entry per B row, krow = that list) instead of whole column
-// blocks: the fill-in columns of the blocks, which hold nothing but zeros, are never loaded.
+// GATHER: the tile is up to four slabs of the row list (prow: rows of low groups, and of taller ones whose blocks are mostly
+// fill-in), and its K dimension the list of the single COLUMNS its rows touch (gcol, one entry per B row) instead of
+// whole column blocks: the fill-in columns of the blocks, which hold nothing but zeros, are never loaded.
 template <int DT, int S, int NS, int DA, bool GATHER = false>
 __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, const int ntile, unsigned char *smem)
 {
@@ -681,7 +681,7 @@ struct PanelParams {
     const int32_t *prow;
     const uint16_t *vals;
     const uint16_t *zfrag;    // 1 KiB of zeros (behind the last fragment): source of the filler loads
-    const uint16_t *zeros;
+    const uint16_t *zeros;    // 256 zero bytes: source of the padding rows of a K-step
     const uint16_t *B;
     float *C;
     int64_t ldb, ldc;
@@ -995,7 +995,6 @@ extern "C" int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C
     p.krow = reinterpret_cast<const int32_t *>(d + v->lay.krow_off);
     p.perm = reinterpret_cast<const int32_t *>(d + v->lay.perm_off);
     p.vals = reinterpret_cast<const uint16_t *>(d + v->lay.vals_off);
-    p.zeros = reinterpret_cast<const uint16_t *>(d + v->lay.zeros_off);
     p.B = static_cast<const uint16_t *>(B_dev);
     p.C = C_dev;
     p.ldb = ldb;
@@ -1010,7 +1009,7 @@ extern "C" int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C
     pp.zfrag = p.vals + (v->vals.size() - vbrk::kFragElems);
     pp.prow = reinterpret_cast<const int32_t *>(d + v->lay.prow_off);
     pp.vals = p.vals;
-    pp.zeros = p.zeros;
+    pp.zeros = reinterpret_cast<const uint16_t *>(d + v->lay.zeros_off);
     pp.B = p.B;
     pp.C = C_dev;
     pp.ldb = ldb;

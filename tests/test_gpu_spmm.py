@@ -522,11 +522,10 @@ def test_runs_on_the_given_stream_and_in_a_captured_graph():
         check_c(c_graph.cpu().numpy().astype(np.float64), c_ref, s_ref, "graph replay %d" % rep)
 
 
-def test_forked_launches_keep_the_order_of_the_callers_stream_and_replay_in_a_graph():
-    # a multiply of several launches spreads them over the handle's own streams between an event
-    # recorded on the caller's stream and waits of the caller's stream: work queued before the call
+def test_calls_of_several_launches_keep_the_order_of_the_callers_stream_and_replay_in_a_graph():
+    # the launches of a multiply follow each other on the caller's stream: work queued before the call
     # (the NaN fill) must be over before any launch writes, work queued after it (the clone) must
-    # see every row; a captured graph must carry the same fork and join
+    # see every row; a captured graph must carry all of them
     import torch
     rng = np.random.default_rng(61)
     w = synth.workload("rmat")
@@ -547,7 +546,7 @@ def test_forked_launches_keep_the_order_of_the_callers_stream_and_replay_in_a_gr
             v.spmm(b, c)
             results.append(c.clone())
     side.synchronize()
-    check_c(results[0].cpu().numpy().astype(np.float64), c_ref, s_ref, "forked launches, first call")
+    check_c(results[0].cpu().numpy().astype(np.float64), c_ref, s_ref, "several launches, first call")
     for i, r in enumerate(results[1:]):
         assert torch.equal(r, results[0]), "call %d differs from the first" % (i + 1)
 
@@ -571,8 +570,8 @@ def test_forked_launches_keep_the_order_of_the_callers_stream_and_replay_in_a_gr
 
 
 def test_two_handles_on_two_streams_at_the_same_time():
-    # every handle has its own side streams and events, so two multiplies of several launches each
-    # may be in flight at once from different caller streams
+    # a handle is only read by a multiply and shares nothing with other handles, so two multiplies of several launches
+    # each may be in flight at once from different caller streams
     import torch
     rng = np.random.default_rng(62)
     w = synth.workload("rmat")
