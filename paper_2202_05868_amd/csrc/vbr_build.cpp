@@ -49,13 +49,13 @@ constexpr int64_t kBlockStepNs[4] = {190, 215, 300, 370};
 constexpr int64_t kGatherStepNs[kMaxGatherSlabs] = {240, 255, 280, 300};
 constexpr int64_t kDeepStepNs[kMaxDeepSlabs] = {290, 350};
 constexpr int64_t kEntryPs = 7000, kEntryRowPs = 15000;      // the same for entry rows, in picoseconds per entry and per row
-constexpr int64_t kEntriesMinRows = 8192;
+constexpr int64_t kEntriesMinRows = 8192;    // not where the two cross: see entries_cost_less
 constexpr int64_t kTileStartSteps = 4;
 constexpr int64_t kDeepSteps = 32;           // no tile of fewer K-steps is deep
 constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: height costs workgroups, and there are few
-constexpr int64_t kShortSteps = 8, kShortMinSlabs = 512;
+constexpr int64_t kShortSteps = 8, kShortMinSlabs = 512;     // these three lines: see cut_into_tiles
 constexpr int64_t kSmallSteps = 1152, kFewTiles = 96;
-constexpr int64_t kEmptyApart = 512;         // workgroups
+constexpr int64_t kEmptyApart = 512;         // workgroups: see plan_launches
 constexpr int64_t kSegmentSlabs = 64;        // the cutting of the slab list into tiles is optimised over stretches of this length
 
 inline int64_t gather_cost(int64_t cols, int n_slabs, int64_t deep_steps)
@@ -67,7 +67,9 @@ inline int64_t gather_cost(int64_t cols, int n_slabs, int64_t deep_steps)
 }
 
 // K-steps from which on a tile is deep, for a matrix of `total` K-steps: the share of one of 768 resident workgroups at
-// N = 2048.
+// N = 2048.  N is not known here; the line holds for the others too.  Graph of 16384 nodes, 64 edges a node, half of it, this and
+// twice as much: N = 256 36.8, 34.0, 59.3 us; N = 1024 67, 52, 67; N = 2048 106, 94, 109; N = 4096 225, 202, 216; of 8192 nodes and 64
+// edges, N = 256 20.0, 19.9, 28.1; with fewer edges the three are within 4 %.
 inline int64_t deep_from(int64_t total) { return std::max<int64_t>(kDeepSteps, total * 8 / 768); }
 
 // What a thread needs to count and look up the columns and column blocks of a few rows.
@@ -319,8 +321,11 @@ Builder::Kind Builder::kind_of(Scratch &s, int64_t r0, int64_t r1, int64_t n_blo
 
 // Entries that share no B rows gain nothing from the matrix unit: a tile loads as many B rows as it has entries, and 16 values
 // of fragment for every one of them.  Then the whole matrix is kept as rows of entries (one kernel, one launch).  The tiles
-// are priced at tiles of 1 or of 4 slabs in the order of the blocking, or of falling length.  Unstructured matrices, 5e-4 of
-// the entries, N = 256: 32768 rows 33 -> 25 us, 8192 rows 9.2 -> 5.9; below some thousand rows both take what a launch takes.
+// are priced at tiles of 1 or of 4 slabs in the order of the blocking, or of falling length.  Unstructured matrices of 16
+// entries a row, as entries and as tiles, N = 64, 256, 1024: 32768 rows, N = 256 25 and 33 us; 12288 rows 6.0 and 8.2, 9.4 and 11.3,
+// 28.9 and 36.2; 8192: 5.9 and 7.8, 7.0 and 9.1, 18.9 and 23.6; 4096: 5.8 and 7.6, 5.9 and 8.1, 10.7 and 12.5; 2048: 5.8 and 6.0, 5.9
+// and 7.4, 6.9 and 7.4; of 4 a row: 8192 5.8 and 8.1, 5.9 and 8.6, 13.2 and 13.6; 2048 5.9 and 5.7, 5.8 and 6.0, 5.9 and 6.2.  So
+// kEntriesMinRows is not where the two cross, which they do between 1024 and 2048 rows: below it a matrix keeps its tiles all the same.
 bool Builder::entries_cost_less()
 {
     if (M < kEntriesMinRows) return false;
@@ -764,11 +769,20 @@ void Builder::append_gathered_groups()
 // The cut of least estimated time is found stretch by stretch.
 //   - Slabs of low rows are joined only where that saves at least a seventh of the gathered rows (joining slabs that
 //     share nothing would make fewer, longer workgroups) and there are kMergeMinSlabs of them; or where the tile stays
-//     short, so that starting and storing are most of its time, and there are enough of them to fill the chip still.
+//     short, so that starting and storing are most of its time, and there are enough of them to fill the chip still: graph
+//     of 16384 nodes, 32 edges a node, N = 1024 49.6 -> 39.0 us, 8 edges 30.9 -> 25.5, N = 512 and 2048 within 3 %.  Lists of up to 16
+//     K-steps instead of 8: within 2 %, but 8 edges, N = 2048 51 -> 46; from 64 slabs on instead of 512: within 4 %, but 98 edges,
+//     N = 1024 70 -> 63.
 //   - A tile of more K-steps than a resident workgroup's share of the whole (at N = 2048) would still be at it when the
 //     rest is done.  It is "deep": the waves of a workgroup split its K-steps, and four workgroups its 256 columns.
-//     In a matrix too small to fill the chip every longer tile is, and not higher than two slabs (1024 x 1024 with 286 groups,
-//     N = 256: 8.2 -> 6.4 us; 2048 x 2048 with 631, N = 128: 15.0 -> 7.7).
+//     In a matrix too small to fill the chip every longer tile is (kSmallSteps: the matrix's K-steps), and not higher than two slabs
+//     either (kFewTiles: its tiles before that; 1024 x 1024 with 286 groups, N = 256: 8.2 -> 6.4 us).  Without and with kSmallSteps: 1536
+//     x 1536, 32-column blocks, N = 1024 8.6 and 7.4; 4000 rows in groups of 1 to 100, N = 1024 9.2 and 7.8; 3072 x 3072, N = 512 9.8 and
+//     12.1.  Without and with kFewTiles, 64-column blocks at 10 %, N = 256, 512, 1024: 2048 x 2048 8.3 and 7.7, 9.1 and 7.9, 15.4 and 8.6;
+//     3072 9.8 and 7.9, 15.4 and 10.1, 16.7 and 16.3; 4096 9.8 and 10.0, 14.0 and 13.7, 15.9 and 20.0 (blocks at 5 %: 9.0 and 8.5, 12.3 and
+//     9.0, 13.8 and 10.0); 6144 11.7 and 12.7, 14.5 and 20.2, 18.0 and 29.9.  The line at 96 tiles is right where B is narrow or the lists
+//     are short; long lists against a wide B would have it at 48: the number of workgroups, and with it N, is what counts, and N is
+//     not known here.
 void Builder::cut_into_tiles()
 {
     const int64_t n_slabs = ((int64_t)v->prow.size() + kSlabRows - 1) / kSlabRows;
@@ -1243,9 +1257,15 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     // wide ones fetch and store B and C in longer pieces, which is what counts once they come from memory.  Measured with 64 / 128
     // / 256 columns: 32768 x 32768, 16 entries a row, N = 256: 28.8 / 32 / 38 us; graph of 16384 nodes, N = 256: 22 / 26 / 37,
     // N = 4096: 358 / 253 / 208, of 4096 nodes, N = 2048: 33 / 29 / 34; 224 entries a row, N = 512: 213 / 185 / 213, 388, N = 1024:
-    // 365 / 270 / 241; 32768 rows of 16 entries and none long, N = 512: 46 / 57 / 72, N = 1024: 88 / 109 / 140.  Rows of B that start
-    // inside a cache line lie in one line more, which 64 columns pay twice and 128 half: then 128 only where rows are short and three
-    // lines of every row of B come near the L2 (16384 rows of 5 entries, N = 1000: 31 us, with 256 columns 36; 32352 of 24, N = 632: 194, 152).
+    // 365 / 270 / 241; 32768 rows of 16 entries and none long, N = 512: 46 / 57 / 72, N = 1024: 88 / 109 / 140.
+    // 256 columns from nnz N = 2^29 and N = 1024 on, with 128 and 256 columns: graph of 16384 nodes, N = 4096, 8 edges a node (2^28.8) 99 and
+    // 117, 32 (2^30.7) 196 and 192; N = 2048, 32 (2^29.7) 91 and 96; of 8192 nodes, N = 4096, 16 (2^28.9) 62 and 73, 64 (2^30.6) 141 and 130;
+    // the crossing lies between 2^29 and 2^30, and it is one of rows with hubs: 32768 rows of 33 entries, N = 1024 (2^30) 197 and 252.
+    // Rows of B that start inside a cache line lie in one line more, which 64 columns pay twice and 128 half: then 128 only where rows are
+    // short and B has at most 16384 rows.  With 128 and 256 columns, 5 to 10 entries a row, N = 136, 264, 632, 1000: 16384 rows 8.7 and
+    // 7.7, 11.9 and 14.0, 25.8 and 24.0, 30.5 and 35.3; 20000: 10.7 and 9.3, 15.9 and 18.2, 36.8 and 33.5, 44.6 and 50.0; 32768: 21.3
+    // and 16.8, 37.5 and 41.6, 96.8 and 80.8, 118 and 122.  What decides is how evenly the column tiles fall on the eight L2 domains
+    // (N = 264: three or two of them, N = 632: five or three); the line in the rows of B only follows which of these were met.
     const bool all_short = M > 0 && start[1] <= kEntryLongRow && nnz <= 32 * M;
     if (N <= 64 || (aligned && (N <= 256 || all_short))) L.lanes = 8;
     else if (aligned) L.lanes = N >= 1024 && nnz * N >= ((int64_t)1 << 29) ? 32 : 16;
@@ -1291,7 +1311,9 @@ static int64_t grid_size(int64_t T, int64_t Q)
 // another.  Measured against launches side by side on streams of their own, and one behind the other: row groups of 16 to 128
 // rows, N = 4096: 169 and 155 -> 137 us; graph of 16384 nodes, N = 4096: 192 and 195 -> 181; of 4096 nodes, N = 2048: 41 and
 // 24 -> 20.  Only tiles without a K-step, if there are many, have a launch of their own behind the others: they just
-// store zeros, and the kernel for them needs no more than that.
+// store zeros, and the kernel for them needs no more than that.  (Their workgroups in the launch of the others, behind those, take
+// less: graph of 16384 nodes, N = 4096, 8, 32 and 64 edges a node 96, 146, 202 us apart and 91, 137, 195 together; N = 2048, 8 edges 51
+// and 47; of 8192 nodes, N = 4096, 8 edges 44.9 and 40.1.  Below kEmptyApart a launch of its own takes 4 us more.)
 int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUNCHES])
 {
     int n = 0;

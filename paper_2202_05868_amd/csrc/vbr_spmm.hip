@@ -608,7 +608,7 @@ static_assert(3 * tile_lds_bytes<4, kStages, kADistance, true>() <= kLdsBytes, "
 static_assert(2 * tile_lds_bytes<4, kStagesTall, kADistance, false>() <= kLdsBytes && 2 * tile_lds_bytes<8, kStagesTall, kADistance, false>() <= kLdsBytes,
               "two of taller block tiles");
 
-// Measured on the 16-row workload: two ring slots and four resident workgroups per CU (36 KiB of
+// Measured on the 16-row workload: two ring slots and four resident workgroups per CU (38 KiB of
 // LDS each) beat deeper rings with fewer workgroups; the gather is bound by how many independent
 // instruction streams feed the texture-address unit, not by the depth of any one of them.
 template <int DT, int S, int NS, int DA, bool GATHER = false>
@@ -892,9 +892,10 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             continue;
         }
         // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are
-        // resident then and their lists are long (16 x 16 blocks at 12 %, 2048 x 8192, N = 1024: 20.3 -> 18.4 us; a 1024 x 1024 matrix
-        // of at most 19 K-steps a tile: 8.2 -> 8.9).  With deep tiles, whose chain is the longest, up to three rounds
-        // (graph of 16384 nodes: N = 512 47 -> 34 us, N = 2048 70 -> 78).
+        // resident then, 512 of them, and their lists are long.  Two slots and four, one slab, 512 workgroups: 6 K-steps 7.7 and 8.1 us,
+        // 13: 10.7 and 10.5, 19: 12.9 and 12.2, 26: 15.8 and 14.7, 60: 29.7 and 27.4; 576 workgroups, 26: 17.1 and 23.9.  With deep
+        // tiles, whose chain is the longest, up to three rounds of 512 (graphs of 4096 to 16384 nodes, 360 to 1448 workgroups: 13.1 and 9.7,
+        // 42.4 and 32.2, 63 and 52; 1744: 22.1 and 24.8, 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
         const int64_t workgroups = (int64_t)p.n_tiles * p.n_ntiles;
         const bool few = L.split ? true : v->class_count[kClassDeep] > 0 ? workgroups <= 1536 : workgroups <= 512 && v->dev_tiles[0].n_ks >= 24;
         void (*kernel)(Params) = nullptr;
