@@ -138,7 +138,8 @@ constexpr int tile_lds_bytes() { return NS * kPanelBytes + (DA + 1) * S * kFragB
 // GATHER: the tile is up to four slabs of the row list (prow: rows of low groups, and of taller ones whose blocks are mostly
 // fill-in), and its K dimension the list of the single COLUMNS its rows touch (gcol, one entry per B row) instead of
 // whole column blocks: the fill-in columns of the blocks, which hold nothing but zeros, are never loaded.
-template <int DT, int S, int NS, int DA, bool GATHER = false>
+// NARROW: narrow column tiles have a way of their own to C (at the end).
+template <int DT, int S, int NS, int DA, bool GATHER = false, bool NARROW = (S > 4)>
 __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, const int ntile, unsigned char *smem)
 {
     static_assert(NS >= 2 && DA >= NS, "A must be requested before the B panel of its K-step");
@@ -397,8 +398,10 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
     // 16 rows x 272 bytes: no bank conflicts) and stores 4 rows x 256 bytes at a time, around the caches' write
     // allocation.  That graph: 260 -> 222 us; 8192 x 8192 with 700 000 stored entries, N = 2048: 23.1 -> 18.7 us;
     // 16384 x 16384 with row groups of 16 to 128 rows, N = 512: 26.4 -> 23.5 us.
-    // In a column tile of fewer than 64 columns there is little to write, and the way through LDS, slab after slab, is what
-    // counts: stored straight (eight slabs, 4 K-steps, N = 8: 7.5 and 5.3 us; N = 24: 7.6 and 5.6).
+    // In a column tile of up to 128 columns there is little to write, and the way through LDS, slab after slab, is what counts
+    // with 5 to 8 slabs: stored straight (24 tiles, 4 K-steps, N = 8: 7.5 and 5.9 us, N = 72: 7.7 and 6.0, N = 128: 7.7 and 6.6; 200
+    // tiles, 8 K-steps, N = 64: 9.9 and 8.2, N = 128: 10.0 and 9.5, N = 160: 10.2 and 10.4; up to 4 slabs both take the same;
+    // in the mixed kernel with tiles of up to 8 those of 4 have it too, without which its code runs 1 % slower at any N).
     int32_t orig[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -406,16 +409,17 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
         orig[s] = rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
     }
     if (n_ks > 0) __syncthreads();                  // the rings are read no more
-    if (__builtin_expect(p.N - n0 < kWaveN, 0)) {
-        if (wave > 0) return;
+    if constexpr (NARROW) {
+        if (__builtin_expect(p.N - n0 <= kTileN / 2, 0)) {
 #pragma unroll
-        for (int s = 0; s < S; ++s)
+            for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                const int n = n0 + 16 * f + 4 * q;
-                if (orig[s] >= 0 && n < p.N) __builtin_nontemporal_store(acc[s][f], reinterpret_cast<float4v *>(p.C + orig[s] * p.ldc + n));
-            }
-        return;
+                for (int f = 0; f < 4; ++f) {
+                    const int n = n0 + wave * kWaveN + 16 * f + 4 * q;
+                    if (orig[s] >= 0 && n < p.N) __builtin_nontemporal_store(acc[s][f], reinterpret_cast<float4v *>(p.C + orig[s] * p.ldc + n));
+                }
+            return;
+        }
     }
     constexpr int kOutRow = kWaveN * 4 + 16;
     static_assert(4 * kSlabRows * kOutRow <= tile_lds_bytes<S, NS, DA, GATHER>(), "the turned slabs of the four waves fit the rings");
@@ -656,10 +660,10 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
     } else if (td.group == kTileGathered) {
         if (td.n_slabs <= 1) tile_body<DT, 1, NS1, DA1, true>(p, td, ntile, smem);
         else if (td.n_slabs <= 2) tile_body<DT, 2, NS1, DA1, true>(p, td, ntile, smem);
-        else tile_body<DT, 4, NSG, kADistance, true>(p, td, ntile, smem);
+        else tile_body<DT, 4, NSG, kADistance, true, MAXS == 8>(p, td, ntile, smem);
     } else if (td.n_slabs <= 1) tile_body<DT, 1, NS1, DA1>(p, td, ntile, smem);
     else if (td.n_slabs <= 2) tile_body<DT, 2, NS1, DA1>(p, td, ntile, smem);
-    else if (MAXS == 4 || td.n_slabs <= 4) tile_body<DT, 4, NS4, kADistance>(p, td, ntile, smem);
+    else if (MAXS == 4 || td.n_slabs <= 4) tile_body<DT, 4, NS4, kADistance, false, MAXS == 8>(p, td, ntile, smem);
     else if constexpr (MAXS == 8) tile_body<DT, 8, NS8, kADistance>(p, td, ntile, smem);
 }
 

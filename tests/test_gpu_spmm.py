@@ -234,11 +234,11 @@ def test_two_slab_tiles_at_the_lengths_of_their_rings(col_block, n_ks, groups, n
     check_c(c, c_ref, s, "two slabs, %d K-steps" % n_ks)
 
 
-@pytest.mark.parametrize("n", [8, 24, 56, 64, 72, 264, 312, 320])
+@pytest.mark.parametrize("n", [8, 24, 64, 72, 120, 128, 136, 264, 384, 392])
 @pytest.mark.parametrize("heights,col_block", [([128, 70, 100], 16), ([128, 70, 40, 18, 33, 16, 3, 9, 2], 16), ([60, 20, 7], 3)])
-def test_column_tiles_of_fewer_than_64_columns(heights, col_block, n):
-    # the only or the last column tile narrower than what a wave turns round in LDS, exactly as wide, and wider: block tiles of
-    # every height, gathered ones, full and partial slabs, nothing written beside the N columns
+def test_narrow_column_tiles(heights, col_block, n):
+    # the only or the last column tile around the width up to which tall tiles are stored without the way through LDS: block
+    # tiles of every height, gathered ones, full and partial slabs, nothing written beside the N columns
     rng = np.random.default_rng(n)
     m = sum(heights)
     csr = random_csr(rng, m, 48 * col_block, 0.1)
