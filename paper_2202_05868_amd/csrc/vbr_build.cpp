@@ -56,6 +56,7 @@ constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: hei
 constexpr int64_t kShortSteps = 8, kShortMinSlabs = 512;     // these three lines: see cut_into_tiles
 constexpr int64_t kSmallSteps = 1152, kFewTiles = 96;
 constexpr int64_t kEmptyApart = 512;         // workgroups: see plan_launches
+constexpr int64_t kTwoOnACu = 512;           // workgroups that are resident with two on a CU
 constexpr int64_t kSegmentSlabs = 64;        // the cutting of the slab list into tiles is optimised over stretches of this length
 
 inline int64_t gather_cost(int64_t cols, int n_slabs, int64_t deep_steps)
@@ -1355,7 +1356,15 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         const bool split = shares <= 9600 && splittable > 0 && v->dev_tiles[0].n_ks >= kSplitSteps && v->dev_tiles[0].n_slabs <= 4;
         const int32_t kind = one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED;
         const int64_t grid = !split ? grid_size(T, Qt) : kind == VBR_LAUNCH_TILE_MIXED ? grid_size(4 * (int64_t)T, Qt) : grid_size(T, (N + kDeepN - 1) / kDeepN);
-        out[n++] = Launch{kind, 0, T, grid, split};
+        // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are
+        // resident then and their lists are long.  An L2 domain holds 64, and the busiest has an eighth of the grid: column tiles whose
+        // number does not divide by eight do not fall evenly (82 tiles of 41 K-steps, N = 1352, 492 workgroups, 82 of them on one domain:
+        // 31.5 us, with two slots 26.8).  Two slots and four, one slab, 512 workgroups: 6 K-steps 7.7 and 8.1 us, 13: 10.7 and 10.5, 19:
+        // 12.9 and 12.2, 26: 15.8 and 14.7, 60: 29.7 and 27.4; 576 workgroups, 26: 17.1 and 23.9.  With deep tiles, whose chain is the
+        // longest, up to three rounds (graphs of 4096 to 16384 nodes, 360 to 1448 workgroups: 13.1 and 9.7, 42.4 and 32.2, 63 and 52;
+        // 1744: 22.1 and 24.8, 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
+        const bool few = split || (v->class_count[kClassDeep] > 0 ? grid <= 3 * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= 24);
+        out[n++] = Launch{kind, 0, T, grid, split, few};
     }
     if (T < T_all) out[n++] = Launch{VBR_LAUNCH_GATHER_4, T, T_all - T, grid_size(T_all - T, Qt)};
     return n;

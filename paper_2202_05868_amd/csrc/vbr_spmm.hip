@@ -895,13 +895,7 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
             continue;
         }
-        // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are
-        // resident then, 512 of them, and their lists are long.  Two slots and four, one slab, 512 workgroups: 6 K-steps 7.7 and 8.1 us,
-        // 13: 10.7 and 10.5, 19: 12.9 and 12.2, 26: 15.8 and 14.7, 60: 29.7 and 27.4; 576 workgroups, 26: 17.1 and 23.9.  With deep
-        // tiles, whose chain is the longest, up to three rounds of 512 (graphs of 4096 to 16384 nodes, 360 to 1448 workgroups: 13.1 and 9.7,
-        // 42.4 and 32.2, 63 and 52; 1744: 22.1 and 24.8, 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
-        const int64_t workgroups = (int64_t)p.n_tiles * p.n_ntiles;
-        const bool few = L.split ? true : v->class_count[kClassDeep] > 0 ? workgroups <= 1536 : workgroups <= 512 && v->dev_tiles[0].n_ks >= 24;
+        const bool few = L.few;
         void (*kernel)(Params) = nullptr;
         p.split = L.split && L.kind == VBR_LAUNCH_TILE_MIXED;
         if (p.split) p.n_tiles *= 4;

@@ -11,7 +11,7 @@
 #include <new>
 #include <vector>
 
-#include "vbr_spmm.h"
+#include "vbr_host.h"
 
 // Allocations of the thread that sets it: as many succeed as it says, then they fail (negative: all succeed).
 static thread_local long g_allocations_left = -1;
@@ -146,6 +146,39 @@ void check_matrix(const Csr &a, int col_block, double tau, bool all_blocks)
     vbr_free(v);
 }
 
+// `groups` groups of `rows` rows that all hold the first n_ks * 32 columns, in blocks of 32
+vbr_t *stack(int groups, int rows, int n_ks)
+{
+    Csr a;
+    a.m = (int64_t)groups * rows;
+    a.k = 32 * n_ks;
+    for (int64_t i = 0; i <= a.m; ++i) a.row_ptr.push_back(i * a.k);
+    for (int64_t i = 0; i < a.m * a.k; ++i) a.col.push_back((int32_t)(i % a.k));
+    a.val.assign(a.col.size(), 0x3c00);
+    std::vector<int32_t> perm, rg;
+    for (int64_t i = 0; i < a.m; ++i) perm.push_back((int32_t)i);
+    for (int g = 0; g <= groups; ++g) rg.push_back(g * rows);
+    const vbr_csr_t c = a.view();
+    vbr_t *v = nullptr;
+    REQUIRE(vbr_build(&c, perm.data(), rg.data(), groups, 32, &v) == VBR_OK);
+    return v;
+}
+
+// Launches that are planned with two workgroups on a CU: 64 on each of the eight L2 domains, and the busiest counts.
+void check_plan()
+{
+    ++g_cases;
+    struct { int groups; int64_t N; bool few; } const cases[] = {{82, 1024, true},  {82, 1280, false}, {82, 1352, false}, {64, 1352, true},
+                                                                 {65, 1352, false}, {64, 2048, true},  {65, 2048, false}, {64, 2056, false}};
+    for (const auto &x : cases) {
+        vbr_t *v = stack(x.groups, 16, 41);
+        vbrk::Launch plan[VBR_MAX_LAUNCHES];
+        REQUIRE(vbrk::plan_launches(v, x.N, x.N % 64 == 0, plan) == 1 && !plan[0].split);
+        REQUIRE(plan[0].few == x.few);
+        vbr_free(v);
+    }
+}
+
 // Every call with the first 0, 1, 2 ... of its allocations succeeding, up to `most` or until it gets all it asks for: it
 // reports the failure, and nothing is thrown through the C interface.
 template <class F>
@@ -237,6 +270,7 @@ int main()
         REQUIRE(vbr_audit(nullptr) == VBR_EINVAL);
         ++g_cases;
     }
+    check_plan();
     // memory that runs out: at every allocation of a small matrix, and at the first ones of a matrix whose check takes threads
     {
         check_out_of_memory(make(rng, 90, 20, 8, 0.2, 40), 8, 100000);
