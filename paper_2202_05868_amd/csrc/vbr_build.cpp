@@ -1340,7 +1340,7 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         // Tiles of up to four slabs with long lists whose workgroups leave CUs idle: four workgroups of 64 columns each instead, whose
         // waves split the K-steps.  Two of these fit on a CU, and per K-step they take 4 B loads and a fragment per slab for 64
         // columns where the others take 16 and one per slab for 256, so the gain ends the sooner the taller the tiles are: at 300 workgroups
-        // (before splitting) of one slab, 192 of two, 128 of three or four, each of them 1/300, 1/192 and 1/128 of what may be split.  Not
+        // (before splitting) of one slab, 192 of two, 128 of three or four, each of them 1/300, 1/192 and 1/128 of what may be split, N being 512.  Not
         // split and split, 60 K-steps of 32-column blocks, N = 512: one slab, 256 workgroups 22.9 and 20.8 us, 300: 26.9 and 25.6 (13
         // K-steps: 10.0 and 9.5; 26, 320: 14.4 and 14.9); two slabs, 192: 24.7 and 21.3, 256: 25.0 and 27.0; four, 128: 25.7 and 22.8,
         // 136: 25.9 and 33.5.  Where rows of B begin inside a line 64 columns lie in two: 168, 135 and 112 (26 K-steps, N = 504: one slab,
@@ -1350,10 +1350,17 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         static constexpr int64_t share_of_class[2][kClasses] = {{57, 71, 85, 100, 12, 57, 71, 85}, {32, 50, 75, 100, 12, 32, 50, 75}};   // in 9600ths
         int64_t shares = 0, splittable = 0;
         for (int c = 0; c < kClasses; ++c) {
-            shares += share_of_class[aligned][c] * v->class_count[c] * Qt;
+            shares += share_of_class[aligned][c] * v->class_count[c];
             if (c != 3 && c != kClassDeep) splittable += v->class_count[c];
         }
-        const bool split = shares <= 9600 && splittable > 0 && v->dev_tiles[0].n_ks >= kSplitSteps && v->dev_tiles[0].n_slabs <= 4;
+        // The numbers above are those of N = 512, where every domain has one of the eight 64-column workgroups of a tile.  For other N: what the
+        // busiest has (a workgroup of the mixed kernel beyond the last column ends at once; 6368 x 5792, 32-column blocks, N = 80, 150 tiles:
+        // not split 15.3 us, split, two workgroups a tile, 9.5; tiles of 64 rows, 31 K-steps, N = 72: 160 tiles 15.6 and 11.8, 225 15.8 and 13.3, 300
+        // 18.0 and 20.7).
+        const int64_t Qd = (N + kDeepN - 1) / kDeepN;
+        auto busiest = [](int64_t n, int64_t Q) { return Q >= kXcd ? 8 * n * ((Q + kXcd - 1) / kXcd) : 8 * n / (kXcd / Q); };      // in eighths
+        const int64_t of_tile = one_kind ? busiest(1, Qd) : Qt == 1 ? Qd : busiest(4, Qt);
+        const bool split = shares * of_tile <= 8 * 4800 && splittable > 0 && v->dev_tiles[0].n_ks >= kSplitSteps && v->dev_tiles[0].n_slabs <= 4;
         const int32_t kind = one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED;
         const int64_t grid = !split ? grid_size(T, Qt) : kind == VBR_LAUNCH_TILE_MIXED ? grid_size(4 * (int64_t)T, Qt) : grid_size(T, (N + kDeepN - 1) / kDeepN);
         // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are

@@ -356,16 +356,34 @@ def test_a_matrix_kept_as_entry_rows_reports_its_rows_and_no_tiles():
     assert n.value == 1 and kinds[0] == 10               # a code no other kernel ever had
 
 
-@pytest.mark.parametrize("height,n,most", [(16, 256, 300), (32, 256, 192), (64, 256, 128), (50, 256, 128), (16, 248, 168), (32, 248, 135), (64, 248, 112)])
+def full_csr(n_rows, n_cols):
+    """Every entry stored: for plans, which look at the pattern alone."""
+    return dict(n_rows=n_rows, n_cols=n_cols, nnz=n_rows * n_cols, row_ptr=np.arange(n_rows + 1, dtype=np.int64) * n_cols,
+                col_idx=np.tile(np.arange(n_cols, dtype=np.int32), n_rows), vals=np.full(n_rows * n_cols, 0x3c00, dtype=np.uint16), dtype="f16")
+
+
+@pytest.mark.parametrize("height,n,most", [(16, 256, 300), (32, 256, 192), (64, 256, 128), (50, 256, 128), (16, 248, 168), (32, 248, 135), (64, 248, 112),
+                                           (64, 512, 64), (64, 576, 32), (64, 64, 512), (64, 128, 256), (64, 72, 225), (32, 192, 192)])
 def test_launches_are_split_up_to_a_number_of_workgroups_that_falls_with_the_height_of_the_tiles(height, n, most):
-    # block tiles of 13 K-steps, one column tile: four workgroups each up to that number (two of the split kernel fit on a CU), one beyond
-    rows = [list(range(416))] * height
+    # block tiles of 12 K-steps: a workgroup for every 64 columns up to that number of tiles (64 of these four-slab workgroups fit on
+    # an L2 domain, and the busiest counts), one for every 256 beyond
     for groups, split in ((most, True), (most + 1, False)):
-        csr = csr_from_rows(rows * groups, 416)
+        csr = full_csr(height * groups, 384)
         v = binding.vbr_build(csr, np.arange(height * groups, dtype=np.int32), np.arange(0, height * groups + 1, height, dtype=np.int32), 32)
         plan = v.launches(n)
-        assert len(plan) == 1 and plan[0]["tiles"] == groups
-        assert (plan[0]["workgroups"] >= 4 * groups) == split, plan
+        domains = lambda q: 8 * groups * -(-q // 8) if q >= 8 else 8 * -(-groups // (8 // q))
+        assert [p["workgroups"] for p in plan] == [domains(-(-n // 64) if split else -(-n // 256))], (groups, plan)
+
+
+@pytest.mark.parametrize("n,most", [(80, 226), (256, 128), (264, 56)])
+def test_mixed_launches_are_split_by_the_workgroups_that_have_columns(n, most):
+    # the same with tiles of two heights in one launch, four workgroups a column tile, of which those beyond the last column end at once
+    for groups, split in ((most, True), (most + 1, False)):
+        rg = np.concatenate([[0], [16], 16 + 64 * np.arange(1, groups)]).astype(np.int32)
+        v = binding.vbr_build(full_csr(int(rg[-1]), 384), np.arange(rg[-1], dtype=np.int32), rg, 32)
+        plan = v.launches(n)
+        assert len(plan) == 1 and plan[0]["kernel"] == "vbr_spmm_mixed_kernel"
+        assert (plan[0]["workgroups"] > 2 * groups * -(-n // 256)) == split, (groups, plan)
 
 
 def test_launches_are_not_split_where_a_tile_that_cannot_be_takes_longest():
