@@ -1250,6 +1250,31 @@ void make_entry_rows(const vbr_csr_t *csr, Team &team, int64_t tail, EntryRows &
     });
 }
 
+// Cache lines an entry of A costs the busiest L2 domain, rows of B beginning inside lines: every column tile that falls on
+// the domain brings the lines its piece of a row lies in, a tile shared by several domains a part of them.  Where all rows are short
+// no two of them share much of B, and a part of B that outgrows the domain's 4 MB comes from farther away, the more of it the larger it is: 15 %
+// more for every megabyte beyond, until hardly any is left.  Found on 125 unaligned products of all kinds of matrices, B of 1000 to 32000 rows, N = 72 to
+// 3816: what the rule takes is on average 0.5 % slower than the faster of the two and 5 % at most but once; always 256 columns, and 128 only
+// for short rows and up to 16384 rows of B, was 4 %, and up to 39.  With 128 and 256 columns: 32416 rows of B, 23 entries a row, N = 312
+// 69 and 85 us; 20448, 8, N = 296 19.3 and 23.1; 18720, 6, N = 352 14.7 and 17.3; 12320, 3, N = 688 15.9 and 15.3; 5936, 875, N = 3040 351 and
+// 430; 16048, 1939, N = 3752 1662 and 1508; 5184, 137, N = 696 117 and 84; graph of 16384 nodes, N = 1672 68 and 60.
+static double entry_row_lines(int lanes, int64_t N, int64_t n_cols, bool all_short)
+{
+    const int64_t width = 8 * lanes, Q = (N + width - 1) / width;
+    auto lines_of = [&](int64_t columns) {
+        const double lines = (double)((2 * columns + 127) / 128 + 1);
+        return all_short ? lines * std::min(2.25, 1.0 + 0.15 * std::max(0.0, (double)n_cols * lines * 128e-6 - 4.0)) : lines;
+    };
+    const double full = lines_of(std::min(width, N)), last = lines_of(N - (Q - 1) * width);
+    if (Q >= kXcd) {                                                // of the first domain, the last of them maybe the narrow tile
+        const int64_t rounds = (Q + kXcd - 1) / kXcd;
+        return Q % kXcd == 1 ? (double)(rounds - 1) * full + last : (double)rounds * full;
+    }
+    double busiest = 0;
+    for (int64_t t = 0; t < Q; ++t) busiest = std::max(busiest, (t + 1 < Q ? full : last) / (double)((kXcd - t + Q - 1) / Q));
+    return busiest;
+}
+
 EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned)
 {
     const int64_t M = (int64_t)start.size() - 1, nnz = start[(size_t)M];
@@ -1262,15 +1287,15 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     // 256 columns from nnz N = 2^29 and N = 1024 on, with 128 and 256 columns: graph of 16384 nodes, N = 4096, 8 edges a node (2^28.8) 99 and
     // 117, 32 (2^30.7) 196 and 192; N = 2048, 32 (2^29.7) 91 and 96; of 8192 nodes, N = 4096, 16 (2^28.9) 62 and 73, 64 (2^30.6) 141 and 130;
     // the crossing lies between 2^29 and 2^30, and it is one of rows with hubs: 32768 rows of 33 entries, N = 1024 (2^30) 197 and 252.
-    // Rows of B that start inside a cache line lie in one line more, which 64 columns pay twice and 128 half: then 128 only where rows are
-    // short and B has at most 16384 rows.  With 128 and 256 columns, 5 to 10 entries a row, N = 136, 264, 632, 1000: 16384 rows 8.7 and
-    // 7.7, 11.9 and 14.0, 25.8 and 24.0, 30.5 and 35.3; 20000: 10.7 and 9.3, 15.9 and 18.2, 36.8 and 33.5, 44.6 and 50.0; 32768: 21.3
-    // and 16.8, 37.5 and 41.6, 96.8 and 80.8, 118 and 122.  What decides is how evenly the column tiles fall on the eight L2 domains
-    // (N = 264: three or two of them, N = 632: five or three); the line in the rows of B only follows which of these were met.
+    // Rows of B that start inside a cache line lie in one line more, which 64 columns pay twice and 128 half.  Then it is one tile where 256
+    // columns hold it (with 128 and 256: 28256 rows of B, 14 entries a row, N = 152 23.3 and 18.9 us; 22528, 13, N = 216 21.2 and 20.4), but
+    // for short rows and widths between, where two tiles stay in the L2 (15968, 11, N = 240 12.4 and 13.6); else 256 where that brings clearly
+    // fewer lines.
     const bool all_short = M > 0 && start[1] <= kEntryLongRow && nnz <= 32 * M;
     if (N <= 64 || (aligned && (N <= 256 || all_short))) L.lanes = 8;
     else if (aligned) L.lanes = N >= 1024 && nnz * N >= ((int64_t)1 << 29) ? 32 : 16;
-    else L.lanes = N > 128 && !(all_short && n_cols <= 16384) ? 32 : 16;
+    else if (N <= 256) L.lanes = N > 128 && (N <= 192 || !all_short || n_cols > 16384) ? 32 : 16;
+    else L.lanes = 1.1 * entry_row_lines(32, N, n_cols, all_short) < entry_row_lines(16, N, n_cols, all_short) ? 32 : 16;
     const int64_t Q = (N + 8 * L.lanes - 1) / (8 * L.lanes);
     // A workgroup for a row costs its barrier and the fourfold sum; it pays where one wave would still be at the row when
     // the rest is done, i.e. beyond the share of all entries that one of 4096 waves takes (graph, N = 256: 66 -> 26 us;

@@ -179,6 +179,24 @@ void check_plan()
     }
 }
 
+// Lanes of a row of entries: 8 (64 columns) where rows of B begin on a cache line, else 128 or 256 columns by how many lines the
+// busiest L2 domain has to bring.
+void check_entry_plan()
+{
+    ++g_cases;
+    struct { int64_t len, n_cols, N; int lanes; } const cases[] = {
+        {5, 16384, 64, 8},    {5, 16384, 256, 8},   {5, 16384, 512, 8},   {5, 16384, 72, 16},   {5, 16384, 136, 32}, {5, 16384, 240, 16}, {5, 32768, 240, 32},
+        {5, 16384, 264, 16},  {5, 32768, 296, 16},  {5, 16384, 632, 32},  {5, 32768, 680, 32},  {5, 16384, 1000, 16}, {5, 16384, 2056, 16},
+        {500, 5936, 3032, 16}, {500, 16048, 3752, 32}, {500, 16384, 240, 32}, {500, 5184, 696, 32}, {500, 5184, 136, 32}};
+    for (const auto &x : cases) {
+        std::vector<int64_t> start;
+        for (int64_t i = 0; i <= 9000; ++i) start.push_back(i * x.len);
+        const vbrk::EntryLaunch L = vbrk::plan_entry_rows(start, x.n_cols, x.N, x.N % 64 == 0);
+        if (L.lanes != x.lanes) std::fprintf(stderr, "%lld entries a row, %lld rows of B, N = %lld: %d lanes\n", (long long)x.len, (long long)x.n_cols, (long long)x.N, L.lanes);
+        REQUIRE(L.lanes == x.lanes && L.grid >= 8 && L.waves >= 9000 * x.lanes / 64);
+    }
+}
+
 // Every call with the first 0, 1, 2 ... of its allocations succeeding, up to `most` or until it gets all it asks for: it
 // reports the failure, and nothing is thrown through the C interface.
 template <class F>
@@ -271,6 +289,7 @@ int main()
         ++g_cases;
     }
     check_plan();
+    check_entry_plan();
     // memory that runs out: at every allocation of a small matrix, and at the first ones of a matrix whose check takes threads
     {
         check_out_of_memory(make(rng, 90, 20, 8, 0.2, 40), 8, 100000);
