@@ -35,6 +35,11 @@ inline int tile_class(const TileDesc &td)
 constexpr int kPanelSlabs = 8;
 constexpr int64_t kPanelMinRows = 4096;
 inline bool use_panels(int lg_gran, int64_t short_rows) { return lg_gran >= 3 && short_rows >= kPanelMinRows; }
+// Panels are a launch of their own, which the others wait for: a few of them, one workgroup each for up to 64 K-steps, are not worth it
+// (7680 x 1856, 64-column blocks, N = 120, one panel among 250 tiles 41 us, all tiles 12.6; 6272 x 1984, N = 160, 17 panels 43 and 23; 6912 x
+// 1920, N = 72, 17 panels 42 and 15).  (Against gathered tiles of up to 64 rows many of them are not the faster ones either: 6000 rows of 12
+// 8-column blocks, N = 512, 47 panels 12.3 us, as tiles 6.2.)
+constexpr int64_t kPanelMinCount = 20;
 // Load instructions per K-step and 256 columns of C: a panel brings 32 B rows x 128 columns (8 loads)
 // and up to 8 fragments (8 loads) per 128 columns; a one-slab tile 32 B rows x 256 columns (16 loads)
 // and one fragment.  The direct-to-LDS load instruction is the unit of cost of both kernels.
@@ -652,6 +657,7 @@ void Builder::choose_panels()
         const int64_t steps = steps_of((int64_t)blocks.size() * cb);
         panel[(size_t)c] = steps > 0 && steps <= kPanelMaxSteps && cost_gather >= steps * kPanelStepCost;
     });
+    if (std::count(panel.begin(), panel.end(), (uint8_t)1) < kPanelMinCount) return;
     int32_t n = 0;
     for (int64_t c = 0; c < n_chunks; ++c)
         if (panel[(size_t)c]) v->chunk_panel[(size_t)c] = n++;

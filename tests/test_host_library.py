@@ -345,6 +345,19 @@ def test_launch_plan_lists_what_a_call_issues():
 
 
 
+@pytest.mark.parametrize("dense_rows,panels", [(128 * 10, False), (128 * 24, True)])
+def test_a_few_panels_are_not_worth_a_launch_of_their_own(dense_rows, panels):
+    # single-row groups over the same 6 column blocks, whose panels need fewer loads than tiles, among rows of two entries anywhere
+    rng = np.random.default_rng(8)
+    cols = np.concatenate([np.arange(b * 16, b * 16 + 16) for b in (3, 70, 200, 511, 800, 1023)])
+    rows = [rng.choice(cols, size=40, replace=False).tolist() for _ in range(dense_rows)]
+    rows += [rng.integers(0, 16384, size=2).tolist() for _ in range(6144 - dense_rows)]
+    v = binding.vbr_build(csr_from_rows(rows, 16384), np.arange(6144, dtype=np.int32), np.arange(6145, dtype=np.int32), 16)
+    v.audit()
+    plan = v.launches(256)
+    assert (plan[0]["kernel"] == "vbr_spmm_panel_kernel") == panels and len(plan) == 1 + panels
+
+
 def test_a_matrix_kept_as_entry_rows_reports_its_rows_and_no_tiles():
     csr = csr_from_rows([[int(c)] for c in np.random.default_rng(2).integers(0, 16384, size=9000)], n_cols=16384)
     v = binding.vbr_build(csr, np.arange(9000, dtype=np.int32), np.arange(9001, dtype=np.int32), 16)
