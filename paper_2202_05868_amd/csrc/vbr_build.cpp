@@ -982,6 +982,7 @@ void Builder::schedule()
         if (it.td.n_ks == 0) continue;
         v->n_work = (int32_t)v->dev_tiles.size();
         v->class_count[tile_class(it.td)]++;
+        if (it.td.n_ks >= kSplitSteps) v->long_count[tile_class(it.td)]++;
     }
 }
 
@@ -1381,7 +1382,10 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         static constexpr int64_t share_of_class[2][kClasses] = {{57, 71, 85, 100, 12, 57, 71, 85}, {32, 50, 75, 100, 12, 32, 50, 75}};   // in 9600ths
         int64_t shares = 0, splittable = 0;
         for (int c = 0; c < kClasses; ++c) {
-            shares += share_of_class[aligned][c] * v->class_count[c];
+            // the mixed kernel leaves tiles of short lists whole, one workgroup of the four (30 tiles of 64 rows and 30 K-steps among 250 of 5
+            // K-steps, N = 72: 15.2 us with all of them counted, not split, and 9.3; N = 256: 16.1 and 10.5)
+            const int64_t whole = one_kind ? 0 : v->class_count[c] - v->long_count[c];
+            shares += share_of_class[aligned][c] * (v->class_count[c] - whole) + share_of_class[aligned][c] * whole / 4;
             if (c != 3 && c != kClassDeep) splittable += v->class_count[c];
         }
         // The numbers above are those of N = 512, where every domain has one of the eight 64-column workgroups of a tile.  For other N: what the

@@ -399,6 +399,19 @@ def test_mixed_launches_are_split_by_the_workgroups_that_have_columns(n, most):
         assert (plan[0]["workgroups"] > 2 * groups * -(-n // 256)) == split, (groups, plan)
 
 
+@pytest.mark.parametrize("long_groups,split", [(30, True), (120, False)])
+def test_tiles_of_short_lists_hardly_count_for_the_split(long_groups, split):
+    # tiles of 64 rows and 12 K-steps among 250 of 32 rows and one K-step, N = 248
+    rows = long_groups * 64 + 250 * 32
+    lens = np.where(np.arange(rows) < long_groups * 64, 384, 32)
+    row_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    col = (np.arange(row_ptr[-1]) - np.repeat(row_ptr[:-1], lens)).astype(np.int32)
+    csr = dict(n_rows=rows, n_cols=384, nnz=int(row_ptr[-1]), row_ptr=row_ptr, col_idx=col, vals=np.full(col.size, 0x3c00, dtype=np.uint16), dtype="f16")
+    rg = np.concatenate([64 * np.arange(long_groups + 1), 64 * long_groups + 32 * np.arange(1, 251)]).astype(np.int32)
+    plan = binding.vbr_build(csr, np.arange(rows, dtype=np.int32), rg, 32).launches(248)
+    assert len(plan) == 1 and (plan[0]["workgroups"] >= 4 * (long_groups + 250)) == split, plan
+
+
 def test_launches_are_not_split_where_a_tile_that_cannot_be_takes_longest():
     csr = csr_from_rows([list(range(416))] * 180, 416)
     rg = np.array([0, 100, 120, 140, 160, 180], dtype=np.int32)         # one group of seven slabs, four of two
