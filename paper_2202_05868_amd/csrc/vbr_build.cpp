@@ -1403,9 +1403,10 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         // number does not divide by eight do not fall evenly (82 tiles of 41 K-steps, N = 1352, 492 workgroups, 82 of them on one domain:
         // 31.5 us, with two slots 26.8).  Two slots and four, one slab, 512 workgroups: 6 K-steps 7.7 and 8.1 us, 13: 10.7 and 10.5, 19:
         // 12.9 and 12.2, 26: 15.8 and 14.7, 60: 29.7 and 27.4; 576 workgroups, 26: 17.1 and 23.9.  With deep tiles, whose chain is the
-        // longest, up to three rounds (graphs of 4096 to 16384 nodes, 360 to 1448 workgroups: 13.1 and 9.7, 42.4 and 32.2, 63 and 52;
-        // 1744: 22.1 and 24.8, 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
-        const bool few = split || (v->class_count[kClassDeep] > 0 ? grid <= 3 * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= 24);
+        // longest, up to three rounds, and all workgroups count, since the short ones fill up what is free beside the long (graphs of 4096 to
+        // 16384 nodes, 360 to 1448 workgroups: 13.1 and 9.7, 42.4 and 32.2, 63 and 52; N = 592, 1416 of them, 236 on the busiest domain: 33.2
+        // and 24.5; 1744: 22.1 and 24.8, 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
+        const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= 3 * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= 24);
         out[n++] = Launch{kind, 0, T, grid, split, few};
     }
     if (T < T_all) out[n++] = Launch{VBR_LAUNCH_GATHER_4, T, T_all - T, grid_size(T_all - T, Qt)};
