@@ -1369,33 +1369,38 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
     // (tiles without a K-step are gathered ones of up to 4 slabs: that kernel takes them, and the mixed one)
     if (T > 0) {
         const bool one_kind = classes == 1 && (T == v->n_work || last == kClasses - 1);
-        // Tiles of up to four slabs with long lists whose workgroups leave CUs idle: four workgroups of 64 columns each instead, whose
-        // waves split the K-steps.  Two of these fit on a CU, and per K-step they take 4 B loads and a fragment per slab for 64
-        // columns where the others take 16 and one per slab for 256, so the gain ends the sooner the taller the tiles are: at 300 workgroups
-        // (before splitting) of one slab, 192 of two, 128 of three or four, each of them 1/300, 1/192 and 1/128 of what may be split, N being 512.  Not
-        // split and split, 60 K-steps of 32-column blocks, N = 512: one slab, 256 workgroups 22.9 and 20.8 us, 300: 26.9 and 25.6 (13
-        // K-steps: 10.0 and 9.5; 26, 320: 14.4 and 14.9); two slabs, 192: 24.7 and 21.3, 256: 25.0 and 27.0; four, 128: 25.7 and 22.8,
-        // 136: 25.9 and 33.5.  Where rows of B begin inside a line 64 columns lie in two: 168, 135 and 112 (26 K-steps, N = 504: one slab,
-        // 168: 12.5 and 11.5, 192: 12.6 and 12.7; two, 128: 13.4 and 10.4, 192: 13.7 and 15.7; four, 112: 14.6 and 13.5, 192: 15.2 and 23.1).
-        // Tiles of more slabs are not split; where one of them takes longest, splitting the others brings nothing (heights 1 to 100, N = 1000,
-        // 80 workgroups: 13.9 and 14.9).  A deep tile is split already.
-        static constexpr int64_t share_of_class[2][kClasses] = {{57, 71, 85, 100, 12, 57, 71, 85}, {32, 50, 75, 100, 12, 32, 50, 75}};   // in 9600ths
-        int64_t shares = 0, splittable = 0;
+        // Tiles of up to four slabs with long lists whose workgroups leave CUs idle: four workgroups of 64 columns each instead, whose waves split
+        // the K-steps.  Two of these fit on a CU, 64 on an L2 domain, and per K-step they take 4 B loads and a fragment per slab for 64 columns
+        // where the others take 16 and one per slab for 256, so the gain ends the sooner the taller the tiles are.  With one of a tile's eight
+        // workgroups on every domain (N = 512; not split and split, 60 K-steps of 32-column blocks): one slab, 128 tiles 22.9 and 20.8 us, 150:
+        // 26.9 and 25.6 (13 K-steps: 10.0 and 9.5; 26, 160: 14.4 and 14.9); two slabs, 104: 24.8 and 25.2 (23: 14.2 and 13.4; 40: 17.9 and 19.1),
+        // 128: 25.0 and 27.0; four, 64: 25.7 and 22.8, 68: 25.9 and 33.5, the 64 that are resident being the end.  Where rows of B begin inside a
+        // line, 64 columns lie in two (26 K-steps, N = 504): one slab, 84: 12.5 and 11.5, 96: 12.6 and 12.7; two, 64: 13.4 and 10.4, 96: 13.7 and
+        // 15.7; four, 56: 14.6 and 13.5, 96: 15.2 and 23.1.  With nine to twelve workgroups a tile the first domains have two and the others one:
+        // what is resident counts on those (four slabs, 23 K-steps, N = 640, 30 tiles 12.7 and 9.5, 36: 12.9 and 14.7), but lower tiles gain as
+        // long as the domains have less on the whole (two slabs, 64: 14.5 and 11.8, with 40 K-steps 17.8 and 17.9, 80: 14.4 and 15.6; one, 75: 13.5
+        // and 11.8, 100: 14.1 and 15.5). With few columns a tile has fewer workgroups (6368 x 5792, 32-column blocks, N = 80, 150 tiles: not split
+        // 15.3 us, split, two a tile, 9.5; tiles of 64 rows, 31 K-steps, N = 72: 160 tiles 15.6 and 11.8, 225 15.8 and 13.3, 300 18.0 and 20.7).
+        // Tiles of more slabs are not split; where one of them takes longest, splitting the others brings nothing (heights 1 to 100, N = 1000, 80
+        // workgroups: 13.9 and 14.9).  A deep tile is split already.
+        // Shares of what may be split: per tile, in 4800ths, for one of its workgroups on every domain.
+        static constexpr int64_t share_of_class[2][kClasses] = {{48, 64, 75, 100, 12, 48, 64, 75}, {32, 46, 75, 100, 12, 32, 46, 75}};
+        // workgroups of a tile on the busiest domain and on all of them, in eighths (one of the mixed kernel beyond the last column ends at once)
+        const int64_t Qd = (N + kDeepN - 1) / kDeepN;
+        auto busiest = [](int64_t n, int64_t Q) { return Q >= kXcd ? 8 * n * ((Q + kXcd - 1) / kXcd) : 8 * n / (kXcd / Q); };
+        const int64_t most = one_kind ? busiest(1, Qd) : Qt == 1 ? Qd : busiest(4, Qt);
+        int64_t load = 0, splittable = 0;
         for (int c = 0; c < kClasses; ++c) {
-            // the mixed kernel leaves tiles of short lists whole, one workgroup of the four (30 tiles of 64 rows and 30 K-steps among 250 of 5
-            // K-steps, N = 72: 15.2 us with all of them counted, not split, and 9.3; N = 256: 16.1 and 10.5)
-            const int64_t whole = one_kind ? 0 : v->class_count[c] - v->long_count[c];
-            shares += share_of_class[aligned][c] * (v->class_count[c] - whole) + share_of_class[aligned][c] * whole / 4;
+            // Tiles of short lists take a quarter: their workgroups are soon over, and the mixed kernel leaves them whole, one of the four (30 tiles of
+            // 64 rows and 30 K-steps among 250 of 32 rows and 5 K-steps, N = 72: not split, all counted, 15.2 us and 9.3; one kernel, N = 256: 10
+            // tiles of 30 K-steps among 250 of 3 or 9, two slabs, 14.5 and 8.1, 14.7 and 9.7; 40 among 400, one slab, 13.5 and 9.3, 13.5 and 11.3;
+            // 40 among 160, four slabs, 15.1 and 10.4, 15.1 and 13.2).
+            const int64_t share = share_of_class[aligned][c] * v->long_count[c] + share_of_class[aligned][c] * (v->class_count[c] - v->long_count[c]) / 4;
+            const bool low = c < 2 || c == kClassGather || c == kClassGather + 1;
+            load += share * (most + (low ? Qd : most));
             if (c != 3 && c != kClassDeep) splittable += v->class_count[c];
         }
-        // The numbers above are those of N = 512, where every domain has one of the eight 64-column workgroups of a tile.  For other N: what the
-        // busiest has (a workgroup of the mixed kernel beyond the last column ends at once; 6368 x 5792, 32-column blocks, N = 80, 150 tiles:
-        // not split 15.3 us, split, two workgroups a tile, 9.5; tiles of 64 rows, 31 K-steps, N = 72: 160 tiles 15.6 and 11.8, 225 15.8 and 13.3, 300
-        // 18.0 and 20.7).
-        const int64_t Qd = (N + kDeepN - 1) / kDeepN;
-        auto busiest = [](int64_t n, int64_t Q) { return Q >= kXcd ? 8 * n * ((Q + kXcd - 1) / kXcd) : 8 * n / (kXcd / Q); };      // in eighths
-        const int64_t of_tile = one_kind ? busiest(1, Qd) : Qt == 1 ? Qd : busiest(4, Qt);
-        const bool split = shares * of_tile <= 8 * 4800 && splittable > 0 && v->dev_tiles[0].n_ks >= kSplitSteps && v->dev_tiles[0].n_slabs <= 4;
+        const bool split = load <= 16 * 4800 && splittable > 0 && v->dev_tiles[0].n_ks >= kSplitSteps && v->dev_tiles[0].n_slabs <= 4;
         const int32_t kind = one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED;
         const int64_t grid = !split ? grid_size(T, Qt) : kind == VBR_LAUNCH_TILE_MIXED ? grid_size(4 * (int64_t)T, Qt) : grid_size(T, (N + kDeepN - 1) / kDeepN);
         // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are
