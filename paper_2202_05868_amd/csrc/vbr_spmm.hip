@@ -160,6 +160,14 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
     const int n_ks = td.n_ks;
     const int q = lane >> 4, s16 = lane & 15;
 
+    // C rows of the tile, lane l of register i that of row 64 i + l: requested first and used last.
+    int32_t c_rows[(S + 3) / 4];
+#pragma unroll
+    for (int i = 0; i < (S + 3) / 4; ++i) {
+        const int rr = 64 * i + lane;
+        c_rows[i] = rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
+    }
+
     float4v acc[S][4];
 #pragma unroll
     for (int s = 0; s < S; ++s)
@@ -402,22 +410,18 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
     // with 5 to 8 slabs: stored straight (24 tiles, 4 K-steps, N = 8: 7.5 and 5.9 us, N = 72: 7.7 and 6.0, N = 128: 7.7 and 6.6; 200
     // tiles, 8 K-steps, N = 64: 9.9 and 8.2, N = 128: 10.0 and 9.5, N = 160: 10.2 and 10.4; up to 4 slabs both take the same;
     // in the mixed kernel with tiles of up to 8 those of 4 have it too, without which its code runs 1 % slower at any N).
-    int32_t orig[S];
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-        const int rr = s * kSlabRows + s16;
-        orig[s] = rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
-    }
     if (n_ks > 0) __syncthreads();                  // the rings are read no more
     if constexpr (NARROW) {
         if (__builtin_expect(p.N - n0 <= kTileN / 2, 0)) {
 #pragma unroll
-            for (int s = 0; s < S; ++s)
+            for (int s = 0; s < S; ++s) {
+                const int32_t row = __shfl(c_rows[s / 4], (s & 3) * kSlabRows + s16);
 #pragma unroll
                 for (int f = 0; f < 4; ++f) {
                     const int n = n0 + wave * kWaveN + 16 * f + 4 * q;
-                    if (orig[s] >= 0 && n < p.N) __builtin_nontemporal_store(acc[s][f], reinterpret_cast<float4v *>(p.C + orig[s] * p.ldc + n));
+                    if (row >= 0 && n < p.N) __builtin_nontemporal_store(acc[s][f], reinterpret_cast<float4v *>(p.C + row * p.ldc + n));
                 }
+            }
             return;
         }
     }
@@ -431,7 +435,7 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float4v x = *(lds_float4_ptr)(out + (4 * i + q) * kOutRow + s16 * 16);
-            const int32_t row = __shfl(orig[s], 4 * i + q);
+            const int32_t row = __shfl(c_rows[s / 4], (s & 3) * kSlabRows + 4 * i + q);
             const int n = n0 + wave * kWaveN + 4 * s16;
             // a position of the low-row list may be padding (-1)
             if (row >= 0 && n < p.N) __builtin_nontemporal_store(x, reinterpret_cast<float4v *>(p.C + row * p.ldc + n));
@@ -463,6 +467,8 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
     const uint32_t base = (uint32_t)(uintptr_t)mine;             // [B slots][A slots][list slots]
     const lds_u8_ptr lists = mine + SLOTS * (kB + kA);
     const int n_ks = td.n_ks;
+    // C row of row `lane` of the tile: requested first and used last
+    const int32_t c_row = lane < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + lane] : -1;
 
     float4v acc[S][4];
 #pragma unroll
@@ -560,12 +566,6 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
         wait_vmcnt<0>();
     }
 
-    int32_t orig[S];
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-        const int rr = s * kSlabRows + 4 * wave + q;                           // this lane's row when the sums are stored
-        orig[s] = rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
-    }
     constexpr int kOutRow = kDeepN * 4 + 16, kOutSlab = kSlabRows * kOutRow;
     __syncthreads();                                                           // nobody reads the rings any more
     const lds_u8_ptr out = sm + wave * S * kOutSlab;
@@ -581,7 +581,8 @@ __device__ __forceinline__ void deep_body(const Params &p, const TileDesc td, co
 #pragma unroll
         for (int w = 1; w < 4; ++w) x += *(lds_float4_ptr)(at + w * S * kOutSlab);
         const int n = n0 + 4 * s16;
-        if (orig[s] >= 0 && n < p.N) __builtin_nontemporal_store(x, reinterpret_cast<float4v *>(p.C + orig[s] * p.ldc + n));
+        const int32_t row = __shfl(c_row, s * kSlabRows + 4 * wave + q);
+        if (row >= 0 && n < p.N) __builtin_nontemporal_store(x, reinterpret_cast<float4v *>(p.C + row * p.ldc + n));
     }
 }
 
