@@ -1389,7 +1389,7 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         const int64_t Qd = (N + kDeepN - 1) / kDeepN;
         auto busiest = [](int64_t n, int64_t Q) { return Q >= kXcd ? 8 * n * ((Q + kXcd - 1) / kXcd) : 8 * n / (kXcd / Q); };
         const int64_t most = one_kind ? busiest(1, Qd) : Qt == 1 ? Qd : busiest(4, Qt);
-        int64_t load = 0, splittable = 0;
+        int64_t load = 0, resident = 0, splittable = 0;
         for (int c = 0; c < kClasses; ++c) {
             // Tiles of short lists take a quarter: their workgroups are soon over, and the mixed kernel leaves them whole, one of the four (30 tiles of
             // 64 rows and 30 K-steps among 250 of 32 rows and 5 K-steps, N = 72: not split, all counted, 15.2 us and 9.3; one kernel, N = 256: 10
@@ -1398,9 +1398,16 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
             const int64_t share = share_of_class[aligned][c] * v->long_count[c] + share_of_class[aligned][c] * (v->class_count[c] - v->long_count[c]) / 4;
             const bool low = c < 2 || c == kClassGather || c == kClassGather + 1;
             load += share * (most + (low ? Qd : most));
+            resident += (c == kClassDeep ? v->class_count[c] / 4 : v->class_count[c]) * most;
             if (c != 3 && c != kClassDeep) splittable += v->class_count[c];
         }
-        const bool split = load <= 16 * 4800 && splittable > 0 && v->dev_tiles[0].n_ks >= kSplitSteps && v->dev_tiles[0].n_slabs <= 4;
+        // Lists of four K-steps and more gain whatever the height of the tiles, as long as two workgroups on a CU hold all that result, 64 on a
+        // domain.  Not split and split, column blocks of 32 at N = 512 (kernel time; a call from the host takes longer than most of these): one slab, 64
+        // tiles of 4 K-steps 5.1 and 3.4 us, 6: 6.0 and 3.7, 10: 7.8 and 4.3; 16 tiles of 10: 7.8 and 3.4; two slabs, 64 tiles, 4: 5.5 and 4.5, 10: 8.2 and
+        // 5.2; four, 4: 5.9 and 5.6, 10: 7.8 and 6.9.  Beyond, 96 tiles, 10 K-steps: 7.5 and 6.0, 8.0 and 7.1, 8.0 and 12.2; 4: 5.1 and 5.2, 5.5 and 6.3,
+        // 6.0 and 8.1; 128: 7.2 and 6.7, 7.7 and 8.1, 8.5 and 14.1.
+        const int32_t longest = v->dev_tiles[0].n_slabs <= 4 && splittable > 0 ? v->dev_tiles[0].n_ks : 0;
+        const int32_t split = longest >= kSplitSteps && load <= 16 * 4800 ? kSplitSteps : longest >= kSplitShort && resident <= 8 * 64 ? kSplitShort : 0;
         const int32_t kind = one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED;
         const int64_t grid = !split ? grid_size(T, Qt) : kind == VBR_LAUNCH_TILE_MIXED ? grid_size(4 * (int64_t)T, Qt) : grid_size(T, (N + kDeepN - 1) / kDeepN);
         // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are

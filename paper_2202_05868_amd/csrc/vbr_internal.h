@@ -17,9 +17,9 @@ constexpr int kMaxSlabs = 8;        // slabs per workgroup tile (128 rows)
 constexpr int kFragElems = kSlabRows * kStepK;   // 512 16-bit values = 1 KiB per (slab, K-step)
 constexpr int kMaxGatherSlabs = 4;  // slabs per column-gathered tile (64 rows) ...
 constexpr int kMaxDeepSlabs = 2;    // ... and per deep one (32 rows)
-constexpr int kSplitSteps = 12;     // K-steps from which on a tile is split over K in launches of few workgroups (not split and split, 128
-                                    // workgroups of one slab: 12 K-steps 9.0 and 5.8 us, 8: 7.1 and 5.7, 6: 6.1 and 5.8, 4: the same;
-                                    // gathered, two slabs, 240 workgroups: 10 K-steps 9.0 and 9.0, 8: 7.9 and 8.3, 6: 6.9 and 8.1)
+constexpr int kSplitSteps = 12;     // K-steps from which on a tile is split over K in launches of few workgroups, while those that result may be more than two on
+                                    // a CU (gathered, two slabs, 240 workgroups, not split and split: 10 K-steps 9.0 and 9.0 us, 8: 7.9 and 8.3, 6: 6.9 and 8.1) ...
+constexpr int kSplitShort = 4;      // ... and where two on a CU hold them all: see plan_launches
 constexpr int kDeepN = 64;          // C columns per workgroup of a deep tile, and of a split launch
 constexpr int kTileN = 256;         // C columns per workgroup of the tile kernel
 constexpr int kPanelN = 128;        // C columns per workgroup of the panel kernel

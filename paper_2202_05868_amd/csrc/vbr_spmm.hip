@@ -58,7 +58,7 @@ struct Params {
     int32_t lg_gran;
     int32_t n_tiles;          // T
     int32_t n_ntiles;         // Q = ceil(N / 256), of the split kernel ceil(N / 64)
-    int32_t split;            // mixed kernel: n_tiles is four times the tiles, see there
+    int32_t split;            // mixed kernel: K-steps from which on tiles are split, n_tiles is four times the tiles, see there; 0: none are
 };
 
 template <int DT>
@@ -647,7 +647,7 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
         const int n0 = ntile * kTileN + (kTileDeep - td.group) * kDeepN;
         if (td.n_slabs <= 1) deep_body<DT, 1, SLOTS>(p, td, n0, smem);
         else deep_body<DT, 2, SLOTS>(p, td, n0, smem);
-    } else if (RING > kStages && p.split && td.n_slabs <= 4 && td.n_ks >= kSplitSteps) {
+    } else if (RING > kStages && p.split && td.n_slabs <= 4 && td.n_ks >= p.split) {
         const int n0 = ntile * kTileN + quarter * kDeepN;
         const bool gathered = td.group == kTileGathered;
         if (gathered && td.n_slabs <= 1) deep_body<DT, 1, SLOTS>(p, td, n0, smem);
@@ -898,7 +898,7 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
         }
         const bool few = L.few;
         void (*kernel)(Params) = nullptr;
-        p.split = L.split && L.kind == VBR_LAUNCH_TILE_MIXED;
+        p.split = L.kind == VBR_LAUNCH_TILE_MIXED ? L.split : 0;
         if (p.split) p.n_tiles *= 4;
         else if (L.split) p.n_ntiles = (p.N + kDeepN - 1) / kDeepN;
         switch (L.kind) {

@@ -209,6 +209,27 @@ def test_few_workgroups_with_long_lists_split_their_k_steps(heights, col_block, 
     check_c(c, c_ref, s, "split K-steps")
 
 
+@pytest.mark.parametrize("n_ks,n,ldb_pad", [(4, 8, 0), (4, 256, 8), (5, 72, 0), (7, 520, 0), (11, 64, 16)])
+@pytest.mark.parametrize("heights,col_block", [([16, 9, 16], 32), ([32, 17, 20], 4), ([64, 33, 50], 8), ([64, 16, 5, 30, 3], 32)])
+def test_few_workgroups_with_short_lists_split_their_k_steps(heights, col_block, n_ks, n, ldb_pad):
+    # one to four slabs, block tiles and gathered ones, then several classes in one launch: from as many K-steps as a workgroup has
+    # waves on up to the last before tiles are split in larger launches too
+    rng = np.random.default_rng(n_ks)
+    kb = 1024 // col_block
+    rows = []
+    for h in heights:
+        cols = np.sort((rng.choice(kb, size=n_ks * 32 // col_block, replace=False)[:, None] * col_block + np.arange(col_block)).reshape(-1))
+        rows += [cols.tolist() for _ in range(h)]
+    csr = csr_from_rows(rows, 1024, rng)
+    bits = synth.dense_rhs(rng, 1024, n, "f16")
+    rg = np.cumsum([0] + heights).astype(np.int32)
+    c, v = gpu_spmm(csr, np.arange(len(rows), dtype=np.int32), rg, col_block, bits, ldb_pad=ldb_pad, ldc_pad=4)
+    plan = v.launches(n)
+    assert len(plan) == 1 and plan[0]["workgroups"] >= plan[0]["tiles"] * -(-n // 64) and v.tile_ksteps().max() >= n_ks
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "short lists")
+
+
 @pytest.mark.parametrize("col_block", [32, 4])
 @pytest.mark.parametrize("n_ks,groups,n,dtype", [(1, 5, 264, "f16"), (2, 5, 256, "bf16"), (3, 5, 264, "f16"), (4, 5, 8, "f16"), (7, 5, 264, "bf16"), (26, 131, 1032, "f16")])
 def test_two_slab_tiles_at_the_lengths_of_their_rings(col_block, n_ks, groups, n, dtype):

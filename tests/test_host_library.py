@@ -388,6 +388,16 @@ def test_launches_are_split_up_to_a_number_of_workgroups_that_falls_with_the_hei
         assert [p["workgroups"] for p in plan] == [domains(-(-n // 64) if split else -(-n // 256))], (groups, plan)
 
 
+@pytest.mark.parametrize("n_ks,height,n,most", [(4, 16, 512, 64), (11, 32, 512, 64), (4, 64, 256, 128), (11, 64, 576, 32), (8, 16, 72, 256), (3, 16, 512, 0)])
+def test_launches_of_short_lists_are_split_while_two_workgroups_on_a_cu_hold_them(n_ks, height, n, most):
+    for groups, split in ((max(most, 1), most > 0), (most + 1, False)):
+        csr = full_csr(height * groups, 32 * n_ks)
+        v = binding.vbr_build(csr, np.arange(height * groups, dtype=np.int32), np.arange(0, height * groups + 1, height, dtype=np.int32), 32)
+        plan = v.launches(n)
+        domains = lambda q: 8 * groups * -(-q // 8) if q >= 8 else 8 * -(-groups // (8 // q))
+        assert [p["workgroups"] for p in plan] == [domains(-(-n // 64) if split else -(-n // 256))], (groups, plan)
+
+
 @pytest.mark.parametrize("n,most", [(80, 256), (256, 128), (264, 64)])
 def test_mixed_launches_are_split_by_the_workgroups_that_have_columns(n, most):
     # the same with tiles of two heights in one launch, four workgroups a column tile, of which those beyond the last column end at once
