@@ -61,7 +61,7 @@ constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: hei
 constexpr int64_t kShortSteps = 8, kShortMinSlabs = 512;     // these three lines: see cut_into_tiles
 constexpr int64_t kSmallSteps = 1152, kFewTiles = 96;
 constexpr int64_t kEmptyApart = 512;         // workgroups: see plan_launches
-constexpr int64_t kTwoOnACu = 512;           // workgroups that are resident with two on a CU
+constexpr int64_t kTwoOnACu = 512, kThreeOnACu = 768;      // workgroups that are resident with two and three on a CU
 constexpr int64_t kSegmentSlabs = 64;        // the cutting of the slab list into tiles is optimised over stretches of this length
 
 inline int64_t gather_cost(int64_t cols, int n_slabs, int64_t deep_steps)
@@ -1409,7 +1409,6 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         const int32_t longest = v->dev_tiles[0].n_slabs <= 4 && splittable > 0 ? v->dev_tiles[0].n_ks : 0;
         const int32_t split = longest >= kSplitSteps && load <= 16 * 4800 ? kSplitSteps : longest >= kSplitShort && resident <= 8 * 64 ? kSplitShort : 0;
         const int32_t kind = one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED;
-        const int64_t grid = !split ? grid_size(T, Qt) : kind == VBR_LAUNCH_TILE_MIXED ? grid_size(4 * (int64_t)T, Qt) : grid_size(T, (N + kDeepN - 1) / kDeepN);
         // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are
         // resident then and their lists are long.  An L2 domain holds 64, and the busiest has an eighth of the grid: column tiles whose
         // number does not divide by eight do not fall evenly (82 tiles of 41 K-steps, N = 1352, 492 workgroups, 82 of them on one domain:
@@ -1418,8 +1417,31 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         // longest, up to three rounds, and all workgroups count, since the short ones fill up what is free beside the long (graphs of 4096 to
         // 16384 nodes, 360 to 1448 workgroups: 13.1 and 9.7, 42.4 and 32.2, 63 and 52; N = 592, 1416 of them, 236 on the busiest domain: 33.2
         // and 24.5; 1744: 22.1 and 24.8, 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
-        const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= 3 * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= 24);
-        out[n++] = Launch{kind, 0, T, grid, split, few};
+        const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= 3 * kTwoOnACu : grid_size(T, Qt) <= kTwoOnACu && v->dev_tiles[0].n_ks >= 24);
+        Launch L{kind, 0, T, 0, split, few};
+        if (kind == VBR_LAUNCH_TILE_MIXED) {
+            L.whole = split ? 0 : T;
+            // A last round of few workgroups takes as long as a full one.  Where an L2 domain has up to a quarter more than it holds at once (or
+            // than it holds in two, three .. rounds), the last tiles, the shortest, are split: their workgroups are over in a third of the time.  Not
+            // split and split, groups of 16 to 128 rows (64 workgroups at once), N = 512: 66 on a domain, 10 K-steps 17.8 and 15.2 us, 20: 25.4 and
+            // 19.7; 70: 18.7 and 16.2, 25.8 and 22.1; 76: 19.8 and 19.1, 28.2 and 25.5; 84: 20.8 and 21.0, 29.6 and 28.6; 94: 23.4 and 24.2; 132: 32.1
+            // and 30.1; 140: 32.7 and 31.2; 152: 33.8 and 34.4; 198: 43.3 and 41.4; groups of up to 64 rows (96 at once): 98: 18.7 and 16.0, 28.1 and
+            // 22.5; 108: 20.4 and 17.9; 116: 21.4 and 19.4; 126: 21.9 and 22.0; 216: 34.2 and 33.2; N = 256, 1024, 2048 alike.  With more than eight
+            // column tiles a domain has several of them, one behind the other, and the rounds are many: these stay whole.
+            if (!split && Qt <= kXcd) {
+                const int64_t members = kXcd / Qt, at_once = (few || v->class_count[3] > 0 ? kTwoOnACu : kThreeOnACu) / kXcd;
+                const int64_t here = (T + members - 1) / members, over = here > at_once ? here % at_once : 0;
+                const TileDesc &first = v->dev_tiles[(size_t)std::max<int64_t>(T - over * members, 0)];
+                if (over > 0 && 4 * over <= at_once && T > over * members && first.group > kTileDeep && first.n_slabs <= split_slabs(few) && first.n_ks >= kSplitShort) {
+                    L.whole = (int32_t)(T - over * members);
+                    L.split = kSplitShort;
+                }
+            }
+            L.grid = grid_size(L.whole + 4 * (int64_t)(T - L.whole), Qt);
+        } else {
+            L.grid = grid_size(T, split ? Qd : Qt);
+        }
+        out[n++] = L;
     }
     if (T < T_all) out[n++] = Launch{VBR_LAUNCH_GATHER_4, T, T_all - T, grid_size(T_all - T, Qt)};
     return n;

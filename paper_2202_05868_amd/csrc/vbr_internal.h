@@ -20,6 +20,8 @@ constexpr int kMaxDeepSlabs = 2;    // ... and per deep one (32 rows)
 constexpr int kSplitSteps = 12;     // K-steps from which on a tile is split over K in launches of few workgroups, while those that result may be more than two on
                                     // a CU (gathered, two slabs, 240 workgroups, not split and split: 10 K-steps 9.0 and 9.0 us, 8: 7.9 and 8.3, 6: 6.9 and 8.1) ...
 constexpr int kSplitShort = 4;      // ... and where two on a CU hold them all: see plan_launches
+// slabs of the tallest tile that can be split in a launch of the mixed kernel, with deeper rings (two workgroups on a CU) and without
+constexpr int split_slabs(bool few) { return few ? 4 : 2; }
 constexpr int kDeepN = 64;          // C columns per workgroup of a deep tile, and of a split launch
 constexpr int kTileN = 256;         // C columns per workgroup of the tile kernel
 constexpr int kPanelN = 128;        // C columns per workgroup of the panel kernel

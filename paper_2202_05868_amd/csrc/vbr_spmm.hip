@@ -58,7 +58,8 @@ struct Params {
     int32_t lg_gran;
     int32_t n_tiles;          // T
     int32_t n_ntiles;         // Q = ceil(N / 256), of the split kernel ceil(N / 64)
-    int32_t split;            // mixed kernel: K-steps from which on tiles are split, n_tiles is four times the tiles, see there; 0: none are
+    int32_t whole, rest;      // mixed kernel: tiles with one workgroup a column tile, and behind them tiles with four, see there ...
+    int32_t split;            // ... and from how many K-steps on these are split
 };
 
 template <int DT>
@@ -639,23 +640,27 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
     __shared__ __attribute__((aligned(1024))) unsigned char smem[std::max(k8, std::max(k4, kLow))];
     int tile, ntile;
     if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
-    // in a split launch every tile has four workgroups a column tile: quarters of it for the long ones, the others use the first
-    const int T = p.split ? p.n_tiles / 4 : p.n_tiles, quarter = tile / T;
-    const TileDesc td = p.tiles[tile - quarter * T];
+    // the last tiles, in a split launch all of them, have four workgroups a column tile: quarters of it for those that are split, the
+    // others use the first
+    const bool four = tile >= p.whole;
+    const int quarter = four ? (tile - p.whole) / p.rest : 0;
+    const TileDesc td = p.tiles[tile - quarter * p.rest];
     if (td.group <= kTileDeep) {
         if (quarter != 0) return;
         const int n0 = ntile * kTileN + (kTileDeep - td.group) * kDeepN;
         if (td.n_slabs <= 1) deep_body<DT, 1, SLOTS>(p, td, n0, smem);
         else deep_body<DT, 2, SLOTS>(p, td, n0, smem);
-    } else if (RING > kStages && p.split && td.n_slabs <= 4 && td.n_ks >= p.split) {
+    } else if (four && td.n_slabs <= split_slabs(RING > kStages) && td.n_ks >= p.split) {
         const int n0 = ntile * kTileN + quarter * kDeepN;
         const bool gathered = td.group == kTileGathered;
         if (gathered && td.n_slabs <= 1) deep_body<DT, 1, SLOTS>(p, td, n0, smem);
         else if (gathered && td.n_slabs <= 2) deep_body<DT, 2, SLOTS>(p, td, n0, smem);
-        else if (gathered) deep_body<DT, 4, 2>(p, td, n0, smem);
         else if (td.n_slabs <= 1) deep_body<DT, 1, SLOTS, false>(p, td, n0, smem);
         else if (td.n_slabs <= 2) deep_body<DT, 2, SLOTS, false>(p, td, n0, smem);
-        else deep_body<DT, 4, 2, false>(p, td, n0, smem);
+        else if constexpr (RING > kStages) {
+            if (gathered) deep_body<DT, 4, 2>(p, td, n0, smem);
+            else deep_body<DT, 4, 2, false>(p, td, n0, smem);
+        }
     } else if (quarter != 0) {
         return;
     } else if (td.group == kTileGathered) {
@@ -898,9 +903,14 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
         }
         const bool few = L.few;
         void (*kernel)(Params) = nullptr;
-        p.split = L.kind == VBR_LAUNCH_TILE_MIXED ? L.split : 0;
-        if (p.split) p.n_tiles *= 4;
-        else if (L.split) p.n_ntiles = (p.N + kDeepN - 1) / kDeepN;
+        if (L.kind == VBR_LAUNCH_TILE_MIXED) {
+            p.whole = L.whole;
+            p.rest = L.n_tiles - L.whole;
+            p.split = L.split;
+            p.n_tiles = p.whole + 4 * p.rest;
+        } else if (L.split) {
+            p.n_ntiles = (p.N + kDeepN - 1) / kDeepN;
+        }
         switch (L.kind) {
         case VBR_LAUNCH_TILE_MIXED:
             if (v->class_count[3] > 0) kernel = few ? vbr_spmm_mixed_kernel<DT, 8, kStagesFew, 3> : vbr_spmm_mixed_kernel<DT, 8, kStages, 2>;

@@ -230,6 +230,30 @@ def test_few_workgroups_with_short_lists_split_their_k_steps(heights, col_block,
     check_c(c, c_ref, s, "short lists")
 
 
+@pytest.mark.parametrize("heights,col_block,n,dtype,most", [([128] * 10 + [40] * 26 + [16] * 29, 32, 2048, "f16", 64), ([100] * 5 + [30] * 50 + [16] * 14, 32, 1800, "bf16", 64),
+                                                            ([64] * 10 + [32, 17] * 24 + [16] * 42, 4, 2040, "f16", 96), ([64] * 50 + [30, 9] * 20 + [16] * 20, 16, 1992, "f16", 96)])
+def test_the_last_tiles_of_a_launch_that_does_not_fit_are_split(heights, col_block, n, dtype, most):
+    # eight column tiles, one a domain, and a few tiles more than a domain holds at once: the shortest ones, of one and two slabs, block
+    # tiles and gathered ones, have four workgroups each; a ragged last column tile, whose last quarters have no columns
+    rng = np.random.default_rng(len(heights))
+    kb = 512 // col_block
+    rows = []
+    for i, h in enumerate(heights):
+        n_ks = 7 if h > 16 else 4 + i % 3
+        cols = np.sort((rng.choice(kb, size=n_ks * 32 // col_block, replace=False)[:, None] * col_block + np.arange(col_block)).reshape(-1))
+        rows += [cols.tolist() for _ in range(h)]
+    csr = csr_from_rows(rows, 512, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, 512, n, dtype)
+    rg = np.cumsum([0] + heights).astype(np.int32)
+    c, v = gpu_spmm(csr, np.arange(len(rows), dtype=np.int32), rg, col_block, bits, ldc_pad=4)
+    plan = v.launches(n)
+    tiles = plan[0]["tiles"]
+    assert len(plan) == 1 and plan[0]["kernel"] == "vbr_spmm_mixed_kernel" and most < tiles <= most + most // 4
+    assert plan[0]["workgroups"] == 8 * (most + 4 * (tiles - most))
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "the last tiles split")
+
+
 @pytest.mark.parametrize("col_block", [32, 4])
 @pytest.mark.parametrize("n_ks,groups,n,dtype", [(1, 5, 264, "f16"), (2, 5, 256, "bf16"), (3, 5, 264, "f16"), (4, 5, 8, "f16"), (7, 5, 264, "bf16"), (26, 131, 1032, "f16")])
 def test_two_slab_tiles_at_the_lengths_of_their_rings(col_block, n_ks, groups, n, dtype):
