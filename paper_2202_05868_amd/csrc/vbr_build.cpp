@@ -1298,8 +1298,14 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     // columns hold it (with 128 and 256: 28256 rows of B, 14 entries a row, N = 152 23.3 and 18.9 us; 22528, 13, N = 216 21.2 and 20.4), but
     // for short rows and widths between, where two tiles stay in the L2 (15968, 11, N = 240 12.4 and 13.6); else 256 where that brings clearly
     // fewer lines.
+    // Short rows against B of more than 256 columns: 128 of them as long as that part of B, 4 MB for 16384 rows, stays in the L2 of a domain, or
+    // each of its rows is used but a few times (with 64 and 128 columns, 2, 5 and 8 entries in 10000: 8192 rows of B, N = 384 7.0 and 6.4 us, 7.9 and 7.2,
+    // 8.2 and 7.9, N = 512 the same, N = 1024 11.8 and 10.6, 13.3 and 11.3, 14.3 and 12.4; 16384, N = 384 13.0 and 11.5, 14.9 and 14.6, 17.1 and 17.3, N =
+    // 1024 23.6 and 19.8, 29.0 and 26.1, 35.1 and 33.0; 23008, N = 512 18.5 and 18.6, 24.8 and 27.4, 31.9 and 36.6, N = 1024 34.6 and 31.8, 46.8 and 49.4,
+    // 60.3 and 67.8; 32768, 16 entries a row, N = 512 48 and 57).
     const bool all_short = M > 0 && start[1] <= kEntryLongRow && nnz <= 32 * M;
-    if (N <= 64 || (aligned && (N <= 256 || all_short))) L.lanes = 8;
+    const bool wide = n_cols <= 16384 || (N > 512 && n_cols <= 24576 && nnz <= 8 * M);
+    if (N <= 64 || (aligned && (N <= 256 || (all_short && !wide)))) L.lanes = 8;
     else if (aligned) L.lanes = N >= 1024 && nnz * N >= ((int64_t)1 << 29) ? 32 : 16;
     else if (N <= 256) L.lanes = N > 128 && (N <= 192 || !all_short || n_cols > 16384) ? 32 : 16;
     else L.lanes = 1.1 * entry_row_lines(32, N, n_cols, all_short) < entry_row_lines(16, N, n_cols, all_short) ? 32 : 16;
