@@ -1298,13 +1298,15 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     // columns hold it (with 128 and 256: 28256 rows of B, 14 entries a row, N = 152 23.3 and 18.9 us; 22528, 13, N = 216 21.2 and 20.4), but
     // for short rows and widths between, where two tiles stay in the L2 (15968, 11, N = 240 12.4 and 13.6); else 256 where that brings clearly
     // fewer lines.
-    // Short rows against B of more than 256 columns: 128 of them as long as that part of B, 4 MB for 16384 rows, stays in the L2 of a domain, or
-    // each of its rows is used but a few times (with 64 and 128 columns, 2, 5 and 8 entries in 10000: 8192 rows of B, N = 384 7.0 and 6.4 us, 7.9 and 7.2,
-    // 8.2 and 7.9, N = 512 the same, N = 1024 11.8 and 10.6, 13.3 and 11.3, 14.3 and 12.4; 16384, N = 384 13.0 and 11.5, 14.9 and 14.6, 17.1 and 17.3, N =
-    // 1024 23.6 and 19.8, 29.0 and 26.1, 35.1 and 33.0; 23008, N = 512 18.5 and 18.6, 24.8 and 27.4, 31.9 and 36.6, N = 1024 34.6 and 31.8, 46.8 and 49.4,
-    // 60.3 and 67.8; 32768, 16 entries a row, N = 512 48 and 57).
+    // Short rows against an aligned B of more than 256 columns: 128 of them as long as that part of B, 4 MB for 16384 rows, stays in the L2 of a domain,
+    // or each of its rows is used but a few times (with 64 and 128 columns, 2, 5 and 8 entries in 10000: 8192 rows of B, N = 384 7.1 and 6.4 us, 8.0 and
+    // 7.2, 8.3 and 7.9, N = 1024 11.8 and 10.6, 13.3 and 11.3, 14.3 and 12.4; 16384, N = 384 13.1 and 11.5, 15.1 and 14.7, 17.4 and 17.4, N = 1024 23.6
+    // and 19.8, 29.0 and 26.1, 35.1 and 33.0; 23008, N = 384 18.5 and 17.4, 23.2 and 24.8, 28.8 and 31.7, N = 1024 34.6 and 31.8, 46.8 and 49.4, 60.3 and
+    // 67.8; 32768, N = 384 26.8 and 29.8, 39.6 and 50.2). At N = 320 five tiles of 64 columns leave three domains half idle and three of 128
+    // do not (8192: 7.8 and 6.4; 32768: 26.5 and 22.2, 49.0 and 48.8); at N = 512 the eight of 64 are one for every domain, and 128 columns gain little
+    // (8192: 8.0 and 7.7, 16384: 15.7 and 15.7, 18.9 and 19.2).
     const bool all_short = M > 0 && start[1] <= kEntryLongRow && nnz <= 32 * M;
-    const bool wide = n_cols <= 16384 || (N > 512 && n_cols <= 24576 && nnz <= 8 * M);
+    const bool wide = N <= 320 || (N != 512 && n_cols <= 16384) || (N > 512 && n_cols <= 24576 && nnz <= 8 * M);
     if (N <= 64 || (aligned && (N <= 256 || (all_short && !wide)))) L.lanes = 8;
     else if (aligned) L.lanes = N >= 1024 && nnz * N >= ((int64_t)1 << 29) ? 32 : 16;
     else if (N <= 256) L.lanes = N > 128 && (N <= 192 || !all_short || n_cols > 16384) ? 32 : 16;
