@@ -224,7 +224,8 @@ class Vbr:
     LAUNCH_KINDS = ("vbr_spmm_panel_kernel", "vbr_spmm_kernel<1 slab>", "vbr_spmm_kernel<2 slabs>",
                     "vbr_spmm_kernel<4 slabs>", "vbr_spmm_kernel<8 slabs>", "vbr_spmm_mixed_kernel",
                     "vbr_spmm_kernel<1 slab, column-gathered>", "vbr_spmm_kernel<2 slabs, column-gathered>",
-                    "vbr_spmm_kernel<4 slabs, column-gathered>", None, "entry_rows_kernel")     # 9: no kernel any more
+                    "vbr_spmm_kernel<4 slabs, column-gathered>", None, "entry_rows_kernel",           # 9: no kernel any more
+                    "vbr_spmm_zero_rows_kernel")
 
     def launches(self, n: int) -> list:
         """The kernel launches one ``spmm`` with a B of shape [K, n], rows not padded, issues, from the library's plan (with padded

@@ -1351,10 +1351,11 @@ static int64_t grid_size(int64_t T, int64_t Q)
 // One launch for all of them, not one per class: the classes' tails fill each other's gaps, and no launch waits for
 // another.  Measured against launches side by side on streams of their own, and one behind the other: row groups of 16 to 128
 // rows, N = 4096: 169 and 155 -> 137 us; graph of 16384 nodes, N = 4096: 192 and 195 -> 181; of 4096 nodes, N = 2048: 41 and
-// 24 -> 20.  Only tiles without a K-step, if there are many, have a launch of their own behind the others: they just
-// store zeros, and the kernel for them needs no more than that.  (Their workgroups in the launch of the others, behind those, take
-// less: graph of 16384 nodes, N = 4096, 8, 32 and 64 edges a node 96, 146, 202 us apart and 91, 137, 195 together; N = 2048, 8 edges 51
-// and 47; of 8192 nodes, N = 4096, 8 edges 44.9 and 40.1.  Below kEmptyApart a launch of its own takes 4 us more.)
+// 24 -> 20.  Tiles without a K-step run behind the others, where their stores fill what those leave free; only where they are many, but
+// less than a quarter of the others, the two ways take the same and they have a launch of the kernel that just stores zeros (in the
+// launch of the others and apart: graphs of 16384 nodes, 8 edges a node, more than a quarter, N = 4096 79 and 85 us, N = 2048 41 and
+// 48; of 8192 nodes, N = 4096 39 and 45; less: 32 edges, N = 4096 149 and 152, N = 3000 154 and 151, 64 edges, N = 4096 194 and 197.  With
+// few of them a launch of its own takes 3 us more).
 int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUNCHES])
 {
     int n = 0;
@@ -1372,9 +1373,9 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
     for (int c = 0; c < kClasses; ++c)
         if (v->class_count[c] > 0) { ++classes; last = c; }
     const int32_t T_all = (int32_t)v->dev_tiles.size(), T_empty = T_all - v->n_work;
-    const bool apart = T_empty * Qt >= kEmptyApart;
+    const bool apart = T_empty * Qt >= kEmptyApart && 4 * T_empty < v->n_work;
     const int32_t T = apart || v->n_work == 0 ? v->n_work : T_all;
-    // (tiles without a K-step are gathered ones of up to 4 slabs: that kernel takes them, and the mixed one)
+    // (tiles without a K-step are gathered ones of up to 4 slabs: the kernel of these takes them too, and the mixed one)
     if (T > 0) {
         const bool one_kind = classes == 1 && (T == v->n_work || last == kClasses - 1);
         // Tiles of up to four slabs with long lists whose workgroups leave CUs idle: four workgroups of 64 columns each instead, whose waves split
@@ -1451,7 +1452,7 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         }
         out[n++] = L;
     }
-    if (T < T_all) out[n++] = Launch{VBR_LAUNCH_GATHER_4, T, T_all - T, grid_size(T_all - T, Qt)};
+    if (T < T_all) out[n++] = Launch{VBR_LAUNCH_ZERO_ROWS, T, T_all - T, (int64_t)(T_all - T) * kMaxGatherSlabs * ((N + kZeroN - 1) / kZeroN)};
     return n;
 }
 

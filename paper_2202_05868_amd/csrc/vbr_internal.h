@@ -25,6 +25,7 @@ constexpr int split_slabs(bool few) { return few ? 4 : 2; }
 constexpr int kDeepN = 64;          // C columns per workgroup of a deep tile, and of a split launch
 constexpr int kTileN = 256;         // C columns per workgroup of the tile kernel
 constexpr int kPanelN = 128;        // C columns per workgroup of the panel kernel
+constexpr int kZeroN = 1024;        // C columns per workgroup of the kernel that stores zeros
 constexpr int kXcd = 8;             // L2 domains; workgroup i runs on domain i % 8
 
 // One workgroup tile: up to kMaxSlabs slabs of ONE row group, walked over the group's K-steps (a block tile), or up to

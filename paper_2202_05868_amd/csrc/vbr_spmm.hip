@@ -685,6 +685,24 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_split_kernel(const Params p
     deep_body<DT, S, SLOTS, GATHER>(p, p.tiles[tile], ntile * kDeepN, smem);
 }
 
+// C rows of tiles without a K-step, the rows of A without entries: zeros.  Bound by what the memory takes, so a workgroup writes whole
+// pieces of 4 KiB, one of each of 16 rows (3886 rows of a graph, N = 4096, behind the launch of its other tiles: 27 us in the kernel of the gathered
+// tiles, which turns its zeros in LDS like any other result, 25 here; N = 3000: 22 and 17).
+__global__ void __launch_bounds__(kThreads) vbr_spmm_zero_rows_kernel(const Params p)
+{
+    static_assert(kZeroN == 4 * kThreads, "a lane writes four columns");
+    const int chunk = blockIdx.x % p.n_ntiles, part = blockIdx.x / p.n_ntiles;
+    const TileDesc td = p.tiles[part / kMaxGatherSlabs];
+    const int r0 = part % kMaxGatherSlabs * kSlabRows, n = chunk * kZeroN + 4 * threadIdx.x;
+    if (n >= p.N) return;
+    const const_i32_ptr rows = (const_i32_ptr)p.prow + td.row_begin + r0;
+#pragma unroll
+    for (int i = 0; i < kSlabRows; ++i) {
+        const int64_t row = r0 + i < td.n_rows ? rows[i] : -1;          // a position of the row list may be padding (-1), too
+        if (row >= 0) __builtin_nontemporal_store(float4v{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<float4v *>(p.C + row * p.ldc + n));
+    }
+}
+
 struct PanelParams {
     const PanelDesc *panels;
     const int32_t *pk_meta;   // K-step stream: records {mask, first B row of each granule}
@@ -933,6 +951,10 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
             break;
         case VBR_LAUNCH_TILE_4:
             kernel = L.split ? vbr_spmm_split_kernel<DT, 4, false> : vbr_spmm_kernel<DT, 4, kStagesTall, kADistance>;
+            break;
+        case VBR_LAUNCH_ZERO_ROWS:
+            kernel = vbr_spmm_zero_rows_kernel;
+            p.n_ntiles = (p.N + kZeroN - 1) / kZeroN;
             break;
         default:
             kernel = vbr_spmm_kernel<DT, 8, kStagesTall, kADistance>;

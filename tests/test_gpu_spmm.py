@@ -380,6 +380,24 @@ def test_leading_dimensions_and_overwrite():
     check_c(c, c_ref, s, "padded leading dimensions")
 
 
+@pytest.mark.parametrize("groups,empty,n,kernels", [(70, 1015, 8200, ["vbr_spmm_kernel<1 slab>", "vbr_spmm_zero_rows_kernel"]), (70, 1201, 8200, ["vbr_spmm_mixed_kernel"]),
+                                                    (0, 37, 264, ["vbr_spmm_zero_rows_kernel"]), (0, 100, 8, ["vbr_spmm_zero_rows_kernel"])])
+def test_tiles_without_entries(groups, empty, n, kernels):
+    # in a launch of their own up to a quarter of the others, beyond in the launch of these; nothing but them; the last piece of a row of 8
+    # columns, the last rows of a slab and of a tile missing
+    rng = np.random.default_rng(empty)
+    rows = [[int(16 * (g % 4)) + i for i in range(16)] for g in range(groups) for _ in range(16)] + [[]] * empty
+    csr = csr_from_rows(rows, 64, rng)
+    bits = synth.dense_rhs(rng, 64, n, "f16")
+    rg = np.append(16 * np.arange(groups + 1), 16 * groups + empty).astype(np.int32)
+    order = rng.permutation(len(rows)).astype(np.int32)
+    csr = synth.permute_rows(csr, np.argsort(order))
+    c, v = gpu_spmm(csr, order, rg, 16, bits, ldc_pad=4)
+    assert [p["kernel"] for p in v.launches(n)] == kernels
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "tiles without entries")
+
+
 def test_empty_rows_get_zeros_and_single_dense_block_is_a_gemm():
     rng = np.random.default_rng(7)
     csr = csr_from_rows([[], [1, 40], [], [2], []], n_cols=64, rng=rng)
