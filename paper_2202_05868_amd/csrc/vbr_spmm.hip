@@ -112,10 +112,21 @@ __device__ __forceinline__ void wait_vmcnt()
 // multiple of 8, full column tile, no padding rows in the K-step) is kept to a handful of scalar
 // instructions per 1 KiB load; everything else takes the general path.
 // Workgroup -> (tile, column tile).  Workgroups are dealt to the 8 L2 domains round-robin; a
-// domain keeps to few column tiles so that the B columns it gathers stay in its L2.
+// domain keeps to few column tiles so that the B columns it gathers stay in its L2, and takes one after the other: every eighth, or (BESIDE)
+// such that lie side by side.  Tiles of one slab, which load the most of B for what they multiply, are faster with the latter, where the pieces
+// of a row of B that the domains read at a time lie farther apart (16 x 16 blocks, 4096 x 16384, N = 4096 160 and
+// 156 us; 3072 x 16384, N = 2560 155 and 143; 4096 x 12000, N = 3584 120 and 116; 4096 x 16384, N = 3328 152.6 and 153.4); taller ones are
+// not (64 x 64 blocks at 40 %, N = 8192 471 and 477; 6144 x 6144 at 10 %, N = 6184 90 and 93).
+template <bool BESIDE = false>
 __device__ __forceinline__ bool map_workgroup(int T, int Q, int &tile, int &ntile)
 {
     const int x = blockIdx.x & (kXcd - 1), j = blockIdx.x >> 3;
+    if (BESIDE && Q >= kXcd) {
+        const int own = Q / kXcd, few = kXcd - Q % kXcd, round = j / T;        // domains 0 .. few-1 have `own` column tiles, the others one more
+        tile = j - round * T;
+        ntile = own * x + (x > few ? x - few : 0) + round;
+        return round < own + (x >= few ? 1 : 0);
+    }
     if (Q >= kXcd) {
         ntile = x + kXcd * (j / T);
         tile = j % T;
@@ -622,7 +633,7 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_kernel(const Params p)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<S, NS, DA, GATHER>()];
     int tile, ntile;
-    if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
+    if (!map_workgroup<S == 1 && !GATHER>(p.n_tiles, p.n_ntiles, tile, ntile)) return;
     tile_body<DT, S, NS, DA, GATHER>(p, p.tiles[tile], ntile, smem);
 }
 

@@ -380,6 +380,20 @@ def test_leading_dimensions_and_overwrite():
     check_c(c, c_ref, s, "padded leading dimensions")
 
 
+@pytest.mark.parametrize("n", [2048, 2056, 2312, 3592, 4096, 4104])
+def test_one_slab_tiles_over_eight_to_seventeen_column_tiles(n):
+    # every tile meets every column tile once, however many of these a domain has
+    rng = np.random.default_rng(n)
+    rows = [[16 * int(b) + i for b in np.sort(rng.choice(40, size=6 + t % 5, replace=False)) for i in range(16)] for t in range(43) for _ in range(16)]
+    csr = csr_from_rows(rows, 640, rng)
+    bits = synth.dense_rhs(rng, 640, n, "f16")
+    c, v = gpu_spmm(csr, np.arange(688, dtype=np.int32), np.arange(0, 689, 16, dtype=np.int32), 16, bits)
+    q = -(-n // 256)
+    assert [(p["kernel"], p["workgroups"]) for p in v.launches(n)] == [("vbr_spmm_kernel<1 slab>", 8 * -(-q // 8) * 43)]
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "column tiles")
+
+
 @pytest.mark.parametrize("groups,empty,n,kernels", [(70, 1015, 8200, ["vbr_spmm_kernel<1 slab>", "vbr_spmm_zero_rows_kernel"]), (70, 1201, 8200, ["vbr_spmm_mixed_kernel"]),
                                                     (0, 37, 264, ["vbr_spmm_zero_rows_kernel"]), (0, 100, 8, ["vbr_spmm_zero_rows_kernel"])])
 def test_tiles_without_entries(groups, empty, n, kernels):
