@@ -1418,15 +1418,19 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         const int32_t longest = v->dev_tiles[0].n_slabs <= 4 && splittable > 0 ? v->dev_tiles[0].n_ks : 0;
         const int32_t split = longest >= kSplitSteps && load <= 16 * 4800 ? kSplitSteps : longest >= kSplitShort && resident <= 8 * 64 ? kSplitShort : 0;
         const int32_t kind = one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED;
-        // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are
-        // resident then and their lists are long.  An L2 domain holds 64, and the busiest has an eighth of the grid: column tiles whose
-        // number does not divide by eight do not fall evenly (82 tiles of 41 K-steps, N = 1352, 492 workgroups, 82 of them on one domain:
-        // 31.5 us, with two slots 26.8).  Two slots and four, one slab, 512 workgroups: 6 K-steps 7.7 and 8.1 us, 13: 10.7 and 10.5, 19:
-        // 12.9 and 12.2, 26: 15.8 and 14.7, 60: 29.7 and 27.4; 576 workgroups, 26: 17.1 and 23.9.  With deep tiles, whose chain is the
-        // longest, up to three rounds, and all workgroups count, since the short ones fill up what is free beside the long (graphs of 4096 to
-        // 16384 nodes, 360 to 1448 workgroups: 13.1 and 9.7, 42.4 and 32.2, 63 and 52; N = 592, 1416 of them, 236 on the busiest domain: 33.2
-        // and 24.5; 1744: 22.1 and 24.8, 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
-        const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= 3 * kTwoOnACu : grid_size(T, Qt) <= kTwoOnACu && v->dev_tiles[0].n_ks >= 24);
+        // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are resident then
+        // and their lists are long.  An L2 domain holds 64, and the busiest has an eighth of the grid: column tiles whose number does not divide by
+        // eight do not fall evenly (82 tiles of 41 K-steps, N = 1352, 492 workgroups, 82 of them on one domain: 31.5 us, with two slots 26.8).  Two
+        // slots and four, one slab, 512 workgroups: 6 K-steps 7.7 and 8.1 us, 13: 10.7 and 10.5, 19: 12.9 and 12.2, 26: 15.8 and 14.7, 60: 29.7 and
+        // 27.4; 576 workgroups, 26: 17.1 and 23.9.  Where the grid leaves a workgroup a CU of its own nothing hides its chain, and short lists gain
+        // too.  Groups of 16 to 32 rows, 240 workgroups, N = 512: 4 K-steps 5.7 and 5.7, 5: 6.6 and 6.3, 7: 7.6 and 7.1, 11: 9.1 and 8.5; N = 2048:
+        // 5: 6.6 and 6.3, 11: 10.9 and 8.6, 16: 14.6 and 11.1; 320 workgroups, N = 512: 11: 9.7 and 9.6, 16: 11.8 and 11.3, 18: 12.8 and 12.0; groups
+        // of 32 to 48 rows: 16: 12.8 and 13.0, 18: 13.7 and 13.5, 23: 15.4 and 14.9.  With deep tiles, whose chain is the longest, up to three
+        // rounds, and all workgroups count, since the short ones fill up what is free beside the long (graphs of 4096 to 16384 nodes, 360 to 1448
+        // workgroups: 13.1 and 9.7, 42.4 and 32.2, 63 and 52; N = 592, 1416 of them, 236 on the busiest domain: 33.2 and 24.5; 1744: 22.1 and 24.8,
+        // 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
+        const int64_t grid = grid_size(T, Qt);
+        const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= 3 * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= (grid <= kTwoOnACu / 2 ? 5 : 18));
         Launch L{kind, 0, T, 0, split, few};
         if (kind == VBR_LAUNCH_TILE_MIXED) {
             L.whole = split ? 0 : T;

@@ -177,6 +177,16 @@ void check_plan()
         REQUIRE(plan[0].few == x.few);
         vbr_free(v);
     }
+    // shorter lists: from 5 K-steps on where every workgroup has a CU, from 18 where two share one; not split, more than 64 on a domain
+    struct { int groups, n_ks; int64_t N; bool few; } const lists[] = {{32, 5, 2048, true}, {32, 4, 2048, false}, {33, 17, 2048, false}, {33, 18, 2048, true},
+                                                                       {64, 18, 2048, true}, {65, 18, 2048, false}, {65, 5, 2048, false}};
+    for (const auto &x : lists) {
+        vbr_t *v = stack(x.groups, 64, x.n_ks);
+        vbrk::Launch plan[VBR_MAX_LAUNCHES];
+        REQUIRE(vbrk::plan_launches(v, x.N, true, plan) == 1 && !plan[0].split);
+        REQUIRE(plan[0].few == x.few);
+        vbr_free(v);
+    }
 }
 
 // Lanes of a row of entries: 8 (64 columns) where rows of B begin on a cache line, else 128 or 256 columns by how many lines the

@@ -254,6 +254,28 @@ def test_the_last_tiles_of_a_launch_that_does_not_fit_are_split(heights, col_blo
     check_c(c, c_ref, s, "the last tiles split")
 
 
+@pytest.mark.parametrize("n_ks", [5, 6, 8])
+@pytest.mark.parametrize("heights,col_block,n", [([32] * 30, 32, 1800), ([16] * 32, 4, 2048), ([32, 20] * 14, 8, 2040), ([64, 100, 16] * 9, 16, 2048), ([30, 9] * 15, 4, 1992)])
+def test_lists_about_as_long_as_the_deeper_rings(heights, col_block, n_ks, n):
+    # at most one workgroup on a CU and too many to be split: one and two slabs alone, then with four and eight in one launch, block tiles and
+    # gathered ones; every third group's list is shorter than the rings
+    rng = np.random.default_rng(n_ks)
+    kb = 512 // col_block
+    rows = []
+    for i, h in enumerate(heights):
+        ks = n_ks if i % 3 else 1 + i % 4
+        cols = np.sort((rng.choice(kb, size=ks * 32 // col_block, replace=False)[:, None] * col_block + np.arange(col_block)).reshape(-1))
+        rows += [cols.tolist() for _ in range(h)]
+    csr = csr_from_rows(rows, 512, rng)
+    bits = synth.dense_rhs(rng, 512, n, "f16")
+    rg = np.cumsum([0] + heights).astype(np.int32)
+    c, v = gpu_spmm(csr, np.arange(len(rows), dtype=np.int32), rg, col_block, bits, ldc_pad=4)
+    plan = v.launches(n)
+    assert len(plan) == 1 and plan[0]["workgroups"] <= 256 and v.tile_ksteps().max() >= n_ks
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "deeper rings")
+
+
 @pytest.mark.parametrize("col_block", [32, 4])
 @pytest.mark.parametrize("n_ks,groups,n,dtype", [(1, 5, 264, "f16"), (2, 5, 256, "bf16"), (3, 5, 264, "f16"), (4, 5, 8, "f16"), (7, 5, 264, "bf16"), (26, 131, 1032, "f16")])
 def test_two_slab_tiles_at_the_lengths_of_their_rings(col_block, n_ks, groups, n, dtype):
