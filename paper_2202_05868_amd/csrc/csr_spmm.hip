@@ -36,6 +36,7 @@ struct EntryParams {
     int64_t ldb, ldc;
     uint32_t b_bytes;                // bytes from B's first element to the end of its last row (WIDE: not used)
     int32_t n_rows, n_huge, n_long, N, n_waves, n_ntiles;
+    bool even;
 };
 
 template <int DT>
@@ -80,17 +81,10 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
     const int lane = threadIdx.x & 63, g = lane / (64 / kGroups), s16 = lane & 15, chunk0 = lane % LANES;
     // workgroup -> (column tile, four waves' rows): workgroups are dealt to the 8 L2 domains round-robin
     const int T = (p.n_waves + 3) / 4, Q = p.n_ntiles;
-    const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
     int ntile, tile;
-    if (Q >= 8) {
-        ntile = x + 8 * (j / T);
-        tile = j % T;
-    } else {
-        ntile = x % Q;
-        tile = x / Q + ((8 - ntile + Q - 1) / Q) * j;
-    }
+    if (!map_workgroup<false, true>(blockIdx.x, T, Q, p.even, tile, ntile)) return;
     const int in_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = tile * 4 + in_wg;
-    if (ntile >= Q || tile >= T || wave >= p.n_waves) return;
+    if (wave >= p.n_waves) return;
     // parts: the groups of lanes that share a row; part: this group's number among them
     const bool huge = tile < p.n_huge, whole = !huge && wave < 4 * p.n_huge + p.n_long;
     const int parts = huge ? 4 * kGroups : whole ? kGroups : 1, part = huge ? in_wg * kGroups + g : whole ? g : 0;
@@ -222,6 +216,7 @@ int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &r
     p.n_rows = (int32_t)n_rows;
     p.N = (int32_t)N;
     p.n_ntiles = (int32_t)((N + 8 * L.lanes - 1) / (8 * L.lanes));
+    p.even = L.even;
     p.n_huge = L.n_huge;
     p.n_long = L.n_long;
     p.n_waves = (int32_t)L.waves;

@@ -1257,8 +1257,8 @@ void make_entry_rows(const vbr_csr_t *csr, Team &team, int64_t tail, EntryRows &
     });
 }
 
-// Cache lines an entry of A costs the busiest L2 domain, rows of B beginning inside lines: every column tile that falls on
-// the domain brings the lines its piece of a row lies in, a tile shared by several domains a part of them.  Where all rows are short
+// Cache lines an entry of A costs the busiest L2 domain, rows of B beginning inside lines, as if column tiles fell on the domains whole: every one
+// that falls on the domain brings the lines its piece of a row lies in, a tile shared by several domains a part of them.  Where all rows are short
 // no two of them share much of B, and a part of B that outgrows the domain's 4 MB comes from farther away, the more of it the larger it is: 15 %
 // more for every megabyte beyond, until hardly any is left.  Found on 125 unaligned products of all kinds of matrices, B of 1000 to 32000 rows, N = 72 to
 // 3816: what the rule takes is on average 0.5 % slower than the faster of the two and 5 % at most but once; always 256 columns, and 128 only
@@ -1280,6 +1280,32 @@ static double entry_row_lines(int lanes, int64_t N, int64_t n_cols, bool all_sho
     double busiest = 0;
     for (int64_t t = 0; t < Q; ++t) busiest = std::max(busiest, (t + 1 < Q ? full : last) / (double)((kXcd - t + Q - 1) / Q));
     return busiest;
+}
+
+// Workgroups of a launch over T row tiles and Q column tiles, by either way of map_workgroup.
+static int64_t grid_size(int64_t T, int64_t Q, bool even = false)
+{
+    if (even) {
+        const int64_t rest = Q % kXcd, each = rest & -rest, shares = kXcd / each;
+        return kXcd * (Q / kXcd * T + rest / each * ((T + shares - 1) / shares));
+    }
+    if (Q >= kXcd) return (int64_t)kXcd * ((Q + kXcd - 1) / kXcd) * T;
+    return (int64_t)kXcd * ((T + (kXcd / Q) - 1) / (kXcd / Q));
+}
+
+// Are the column tiles cut in even shares?  Then a domain meets up to two of those left over and brings parts of B that others bring too, so the
+// busiest domain has to get clearly shorter, and a CU of it a workgroup less.  Whole tiles and shares: 16 x 16 blocks, 4096 x 8192, five column
+// tiles 40.7 and 38.4 us, nine 81.9 and 62.1, 19: 113.7 and 100.1; 64 x 64 blocks at 30 %, 8192 x 8192, five 58.9 and 53.0, nine 108.6 and 87.7, 11:
+// 113 and 100; graph of 16384 nodes, five 67.3 and 65.1, ten 125.8 and 116.4, of 8192 nodes 26.7 and 19.7, 43.9 and 42.6; groups of 50 rows, 5003
+// x 4104, five 23.6 and 15.8; panels of 6000 rows, nine 19.9 and 15.0; entry rows, 16384 x 16384, 8 entries a row, five 23.6 and 18.8, nine 43.5 and
+// 30.9.  Where the busiest has little more than the others: 14 column tiles 82.4 and 81.5, 120.1 and 118.8, seven 62.4 and 64.7, 65.9 and 67.1, 22:
+// 121.5 and 120.4, 181.9 and 183.2; three, where whole tiles have two or three domains each, 34.5 and 37.0, entry rows 15.4 and 16.8.  One round of
+// workgroups, 60 tiles, five: 15.1 and 17.1, six: 16.5 and 16.8; 40 tiles, six, 40 and 30 on a domain of 32 CUs: 16.3 and 13.1.
+static bool even_columns(int64_t T, int64_t Q)
+{
+    if (Q <= 4 || Q == 7 || Q % kXcd == 0) return false;
+    const int64_t whole = grid_size(T, Q), shares = grid_size(T, Q, true), cus = kTwoOnACu / 2;
+    return 8 * whole >= 9 * shares && (whole + cus - 1) / cus > (shares + cus - 1) / cus;
 }
 
 EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned)
@@ -1329,7 +1355,8 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     const int64_t groups = 64 / std::max(L.lanes, 16), sets = (M - L.n_huge - L.n_long + groups - 1) / groups;
     L.waves = 4 * (int64_t)L.n_huge + L.n_long + sets;
     const int64_t T = (L.waves + 3) / 4;
-    L.grid = Q >= 8 ? 8 * ((Q + 7) / 8) * T : 8 * ((T + 8 / Q - 1) / (8 / Q));
+    L.even = even_columns(T, Q);
+    L.grid = grid_size(T, Q, L.even);
     return L;
 }
 
@@ -1338,14 +1365,6 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
 extern "C" int64_t vbr_device_bytes(const vbr_t *v) { return v ? v->lay.total : 0; }
 
 namespace vbrk {
-
-// Workgroups of a launch over T row tiles and Q column tiles: workgroups are dealt to the L2
-// domains round-robin, and a domain keeps to few column tiles (the kernels undo this map).
-static int64_t grid_size(int64_t T, int64_t Q)
-{
-    if (Q >= kXcd) return (int64_t)kXcd * ((Q + kXcd - 1) / kXcd) * T;
-    return (int64_t)kXcd * ((T + (kXcd / Q) - 1) / (kXcd / Q));
-}
 
 // The panels, then the tiles: one launch of the kernel of their class, or of the mixed kernel if there are several.
 // One launch for all of them, not one per class: the classes' tails fill each other's gaps, and no launch waits for
@@ -1365,8 +1384,11 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         return n;
     }
     const int64_t Qt = (N + kTileN - 1) / kTileN, Qp = (N + kPanelN - 1) / kPanelN;
-    if (!v->panels.empty())
-        out[n++] = Launch{VBR_LAUNCH_PANEL, 0, (int32_t)v->panels.size(), grid_size((int64_t)v->panels.size(), Qp)};
+    if (!v->panels.empty()) {
+        const int64_t P = (int64_t)v->panels.size();
+        const bool even = even_columns(P, Qp);
+        out[n++] = Launch{VBR_LAUNCH_PANEL, 0, (int32_t)P, grid_size(P, Qp, even), 0, false, 0, even};
+    }
     static const int32_t kind_of_class[kClasses] = {VBR_LAUNCH_TILE_1, VBR_LAUNCH_TILE_2, VBR_LAUNCH_TILE_4, VBR_LAUNCH_TILE_8, VBR_LAUNCH_TILE_MIXED,
                                                     VBR_LAUNCH_GATHER_1, VBR_LAUNCH_GATHER_2, VBR_LAUNCH_GATHER_4};
     int classes = 0, last = 0;
@@ -1429,9 +1451,9 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         // rounds, and all workgroups count, since the short ones fill up what is free beside the long (graphs of 4096 to 16384 nodes, 360 to 1448
         // workgroups: 13.1 and 9.7, 42.4 and 32.2, 63 and 52; N = 592, 1416 of them, 236 on the busiest domain: 33.2 and 24.5; 1744: 22.1 and 24.8,
         // 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
-        const int64_t grid = grid_size(T, Qt);
+        const int64_t grid = grid_size(T, Qt);             // as if of whole column tiles
         const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= 3 * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= (grid <= kTwoOnACu / 2 ? 5 : 18));
-        Launch L{kind, 0, T, 0, split, few};
+        Launch L{kind, 0, T, 0, split, few, 0, !split && even_columns(T, Qt)};
         if (kind == VBR_LAUNCH_TILE_MIXED) {
             L.whole = split ? 0 : T;
             // A last round of few workgroups takes as long as a full one.  Where an L2 domain has up to a quarter more than it holds at once (or
@@ -1443,16 +1465,17 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
             // column tiles a domain has several of them, one behind the other, and the rounds are many: these stay whole.
             if (!split && Qt <= kXcd) {
                 const int64_t members = kXcd / Qt, at_once = (few || v->class_count[3] > 0 ? kTwoOnACu : kThreeOnACu) / kXcd;
-                const int64_t here = (T + members - 1) / members, over = here > at_once ? here % at_once : 0;
-                const TileDesc &first = v->dev_tiles[(size_t)std::max<int64_t>(T - over * members, 0)];
-                if (over > 0 && 4 * over <= at_once && T > over * members && first.group > kTileDeep && first.n_slabs <= split_slabs(few) && first.n_ks >= kSplitShort) {
-                    L.whole = (int32_t)(T - over * members);
+                const int64_t here = L.even ? grid_size(T, Qt, true) / kXcd : (T + members - 1) / members, over = here > at_once ? here % at_once : 0;
+                const int64_t last = L.even ? (kXcd * over + Qt - 1) / Qt : over * members;
+                const TileDesc &first = v->dev_tiles[(size_t)std::max<int64_t>(T - last, 0)];
+                if (over > 0 && 4 * over <= at_once && T > last && first.group > kTileDeep && first.n_slabs <= split_slabs(few) && first.n_ks >= kSplitShort) {
+                    L.whole = (int32_t)(T - last);
                     L.split = kSplitShort;
                 }
             }
-            L.grid = grid_size(L.whole + 4 * (int64_t)(T - L.whole), Qt);
+            L.grid = grid_size(L.whole + 4 * (int64_t)(T - L.whole), Qt, L.even);
         } else {
-            L.grid = grid_size(T, split ? Qd : Qt);
+            L.grid = grid_size(T, split ? Qd : Qt, L.even);
         }
         out[n++] = L;
     }

@@ -16,7 +16,7 @@ int sa1_reorder_impl(const vbr_csr_t *csr, int32_t col_block, double tau, int32_
 // kernel, first tile and number of tiles (or panels) of the launch, grid size; split: 64 columns of C a workgroup,
 // whose waves split the K-steps; few: rings of four slots.  aligned: rows of B begin on a cache line.
 // split: 0, or the K-steps from which on its tiles are split, of the mixed kernel those from number `whole` on
-struct Launch { int32_t kind; int32_t first_tile, n_tiles; int64_t grid; int32_t split = 0; bool few = false; int32_t whole = 0; };
+struct Launch { int32_t kind; int32_t first_tile, n_tiles; int64_t grid; int32_t split = 0; bool few = false; int32_t whole = 0; bool even = false; };
 int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUNCHES]);
 
 constexpr int kEntryLongRow = 256;     // entries beyond which a row gets a wave of its own ...
@@ -31,7 +31,7 @@ struct EntryRowsDev {
     const int32_t *row, *col;
     const uint16_t *val;
 };
-struct EntryLaunch { int32_t lanes, n_huge, n_long; int64_t waves, grid; };
+struct EntryLaunch { int32_t lanes, n_huge, n_long; int64_t waves, grid; bool even; };
 // the launch for dense width N; aligned: rows of B begin on a cache line
 EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned);
 int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &rows, int64_t n_rows, int64_t n_cols,

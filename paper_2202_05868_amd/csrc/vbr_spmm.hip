@@ -58,6 +58,7 @@ struct Params {
     int32_t lg_gran;
     int32_t n_tiles;          // T
     int32_t n_ntiles;         // Q = ceil(N / 256), of the split kernel ceil(N / 64)
+    bool even;                // see map_workgroup
     int32_t whole, rest;      // mixed kernel: tiles with one workgroup a column tile, and behind them tiles with four, see there ...
     int32_t split;            // ... and from how many K-steps on these are split
 };
@@ -111,33 +112,6 @@ __device__ __forceinline__ void wait_vmcnt()
 // The loop is bound by the instructions a wave needs per K-step, so the common case (block width a
 // multiple of 8, full column tile, no padding rows in the K-step) is kept to a handful of scalar
 // instructions per 1 KiB load; everything else takes the general path.
-// Workgroup -> (tile, column tile).  Workgroups are dealt to the 8 L2 domains round-robin; a
-// domain keeps to few column tiles so that the B columns it gathers stay in its L2, and takes one after the other: every eighth, or (BESIDE)
-// such that lie side by side.  Tiles of one slab, which load the most of B for what they multiply, are faster with the latter, where the pieces
-// of a row of B that the domains read at a time lie farther apart (16 x 16 blocks, 4096 x 16384, N = 4096 160 and
-// 156 us; 3072 x 16384, N = 2560 155 and 143; 4096 x 12000, N = 3584 120 and 116; 4096 x 16384, N = 3328 152.6 and 153.4); taller ones are
-// not (64 x 64 blocks at 40 %, N = 8192 471 and 477; 6144 x 6144 at 10 %, N = 6184 90 and 93).
-template <bool BESIDE = false>
-__device__ __forceinline__ bool map_workgroup(int T, int Q, int &tile, int &ntile)
-{
-    const int x = blockIdx.x & (kXcd - 1), j = blockIdx.x >> 3;
-    if (BESIDE && Q >= kXcd) {
-        const int own = Q / kXcd, few = kXcd - Q % kXcd, round = j / T;        // domains 0 .. few-1 have `own` column tiles, the others one more
-        tile = j - round * T;
-        ntile = own * x + (x > few ? x - few : 0) + round;
-        return round < own + (x >= few ? 1 : 0);
-    }
-    if (Q >= kXcd) {
-        ntile = x + kXcd * (j / T);
-        tile = j % T;
-        return ntile < Q;
-    }
-    ntile = x % Q;
-    const int member = x / Q, members = (kXcd - ntile + Q - 1) / Q;
-    tile = member + members * j;
-    return tile < T;
-}
-
 // B rows of the next K-steps, in LDS: one load of a wave brings those of 8 K-steps of a gathered tile (8 columns each) or of
 // 64 of a block tile (one granule each); two such lists for each of the 4 waves.
 constexpr int kListBytes = 2 * 4 * 64 * 4;
@@ -633,7 +607,7 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_kernel(const Params p)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<S, NS, DA, GATHER>()];
     int tile, ntile;
-    if (!map_workgroup<S == 1 && !GATHER>(p.n_tiles, p.n_ntiles, tile, ntile)) return;
+    if (!map_workgroup<S == 1 && !GATHER>(blockIdx.x, p.n_tiles, p.n_ntiles, p.even, tile, ntile)) return;
     tile_body<DT, S, NS, DA, GATHER>(p, p.tiles[tile], ntile, smem);
 }
 
@@ -650,7 +624,7 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
     constexpr int k8 = MAXS == 8 ? tile_lds_bytes<8, NS8, kADistance, false>() : 0;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[std::max(k8, std::max(k4, kLow))];
     int tile, ntile;
-    if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
+    if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.even, tile, ntile)) return;
     // the last tiles, in a split launch all of them, have four workgroups a column tile: quarters of it for those that are split, the
     // others use the first
     const bool four = tile >= p.whole;
@@ -692,7 +666,7 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_split_kernel(const Params p
     constexpr int SLOTS = S <= 2 ? 3 : 2;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[deep_lds_bytes<S, SLOTS>()];
     int tile, ntile;
-    if (!map_workgroup(p.n_tiles, p.n_ntiles, tile, ntile)) return;
+    if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.even, tile, ntile)) return;
     deep_body<DT, S, SLOTS, GATHER>(p, p.tiles[tile], ntile * kDeepN, smem);
 }
 
@@ -728,6 +702,7 @@ struct PanelParams {
     int32_t lg_gran;          // >= 3
     int32_t n_panels;         // T
     int32_t n_ntiles;         // Q = ceil(N / 128)
+    bool even;
 };
 
 // Panel kernel: one workgroup (8 waves) owns R slabs (R * 16 rows of short row groups, whatever
@@ -759,7 +734,7 @@ __global__ void __launch_bounds__(kPanelThreads) vbr_spmm_panel_kernel(const Pan
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kBRing + NAS * kAStage + 2 * kFragBytes];
 
     int tile, ntile;
-    if (!map_workgroup(p.n_panels, p.n_ntiles, tile, ntile)) return;
+    if (!map_workgroup(blockIdx.x, p.n_panels, p.n_ntiles, p.even, tile, ntile)) return;
     const PanelDesc pd = p.panels[tile];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -912,7 +887,7 @@ __global__ void __launch_bounds__(kPanelThreads) vbr_spmm_panel_kernel(const Pan
 
 
 template <int DT>
-int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStream_t stream)
+int launch_all(const vbr *v, const Params &base, PanelParams pp, hipStream_t stream)
 {
     Launch plan[VBR_MAX_LAUNCHES];
     const int n = plan_launches(v, base.N, base.ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(base.B) & 127) == 0, plan);
@@ -923,8 +898,10 @@ int launch_all(const vbr *v, const Params &base, const PanelParams &pp, hipStrea
         Params p = base;
         p.tiles = base.tiles + L.first_tile;
         p.n_tiles = L.n_tiles;
+        p.even = L.even;
         const dim3 grid((unsigned)L.grid);
         if (L.kind == VBR_LAUNCH_PANEL) {
+            pp.even = L.even;
             hipLaunchKernelGGL((vbr_spmm_panel_kernel<DT, 8, 4, 3>), grid, dim3(kPanelThreads), 0, stream, pp);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }

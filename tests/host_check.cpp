@@ -4,6 +4,7 @@
 // library with the oracle bit for bit and runs the audit of everything the kernels would index, so
 // that an out-of-bounds access, an overflow or a leak in 500 lines of hand index arithmetic shows up
 // on the CPU.  Test infrastructure: built and run by tests/test_host_sanitizers.py.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -189,6 +190,30 @@ void check_plan()
     }
 }
 
+// Every tile meets every column tile once, whatever the way the workgroups are dealt, and cut in shares no domain has many more than an eighth.
+template <bool BESIDE, bool IN_TURN>
+void check_map()
+{
+    ++g_cases;
+    for (int Q = 1; Q <= 34; ++Q)
+        for (int T : {1, 2, 3, 5, 7, 8, 9, 12, 16, 31, 40, 77, 130})
+            for (bool even : {false, true}) {
+                const int rest = Q % 8, each = rest & -rest;
+                if (even && rest == 0) continue;
+                const int domain = even ? Q / 8 * T + rest / each * ((T * each + 7) / 8) : Q >= 8 ? (Q + 7) / 8 * T : (T + 8 / Q - 1) / (8 / Q);
+                std::vector<int> seen((size_t)T * Q), load(8);
+                int tile = 0, ntile = 0;
+                for (int b = 0; b < 8 * domain; ++b)
+                    if (vbrk::map_workgroup<BESIDE, IN_TURN>(b, T, Q, even, tile, ntile)) {
+                        REQUIRE(tile >= 0 && tile < T && ntile >= 0 && ntile < Q);
+                        ++seen[(size_t)tile * Q + ntile];
+                        ++load[b % 8];
+                    }
+                REQUIRE(std::count(seen.begin(), seen.end(), 1) == (long)seen.size());
+                if (even) REQUIRE(8 * *std::max_element(load.begin(), load.end()) <= T * Q + 8 * 7);
+            }
+}
+
 // Lanes of a row of entries: 8 (64 columns) where rows of B begin on a cache line, else 128 or 256 columns by how many lines the
 // busiest L2 domain has to bring.
 void check_entry_plan()
@@ -299,6 +324,9 @@ int main()
         ++g_cases;
     }
     check_plan();
+    check_map<false, false>();
+    check_map<true, false>();
+    check_map<false, true>();
     check_entry_plan();
     // memory that runs out: at every allocation of a small matrix, and at the first ones of a matrix whose check takes threads
     {

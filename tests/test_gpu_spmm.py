@@ -411,9 +411,34 @@ def test_one_slab_tiles_over_eight_to_seventeen_column_tiles(n):
     bits = synth.dense_rhs(rng, 640, n, "f16")
     c, v = gpu_spmm(csr, np.arange(688, dtype=np.int32), np.arange(0, 689, 16, dtype=np.int32), 16, bits)
     q = -(-n // 256)
-    assert [(p["kernel"], p["workgroups"]) for p in v.launches(n)] == [("vbr_spmm_kernel<1 slab>", 8 * -(-q // 8) * 43)]
+    assert [(p["kernel"], p["workgroups"]) for p in v.launches(n)] == [("vbr_spmm_kernel<1 slab>", 8 * {8: 43, 9: 49, 10: 54, 15: 86, 16: 86, 17: 92}[q])]
     c_ref, s = oracle.spmm(csr, bits)
     check_c(c, c_ref, s, "column tiles")
+
+
+@pytest.mark.parametrize("kind,n,workgroups", [("mixed", 1096, 5 * 10), ("mixed", 1536, 3 * 20), ("mixed", 2304, 77 + 10), ("panel", 640, 5 * 6), ("panel", 1160, 47 + 12),
+                                               ("entries", 1216, 563 + 141), ("entries", 1096, 563 + 71)])
+def test_column_tiles_that_the_domains_share(kind, n, workgroups):
+    # five, six, nine and ten column tiles, not all of them full: mixed tiles, panels and rows of entries
+    rng = np.random.default_rng(n)
+    if kind == "mixed":
+        heights = [64, 30, 9, 16, 33, 48, 16] * 11
+        rows = []
+        for i, h in enumerate(heights):
+            cols = np.sort((rng.choice(24, size=5 + i % 4, replace=False)[:, None] * 32 + np.arange(32)).reshape(-1))
+            rows += [cols.tolist() for _ in range(h)]
+        csr, rg = csr_from_rows(rows, 768, rng), np.cumsum([0] + heights).astype(np.int32)
+    elif kind == "panel":
+        csr = random_csr(rng, 6000, 64, 0.2)
+        rg = np.arange(6001, dtype=np.int32)
+    else:
+        csr = csr_from_rows([np.unique(rng.integers(0, 12000, size=1 + i % 5)).tolist() for i in range(9000)], 12000, rng)
+        rg = np.arange(9001, dtype=np.int32)
+    bits = synth.dense_rhs(rng, csr["n_cols"], n, "f16")
+    c, v = gpu_spmm(csr, np.arange(csr["n_rows"], dtype=np.int32), rg, 16 if kind != "mixed" else 32, bits, ldc_pad=4)
+    assert v.launches(n)[0]["workgroups"] == 8 * workgroups, v.launches(n)
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "shared column tiles")
 
 
 @pytest.mark.parametrize("groups,empty,n,kernels", [(70, 1015, 8200, ["vbr_spmm_kernel<1 slab>", "vbr_spmm_zero_rows_kernel"]), (70, 1201, 8200, ["vbr_spmm_mixed_kernel"]),
