@@ -1328,15 +1328,38 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     // or each of its rows is used but a few times (with 64 and 128 columns, 2, 5 and 8 entries in 10000: 8192 rows of B, N = 384 7.1 and 6.4 us, 8.0 and
     // 7.2, 8.3 and 7.9, N = 1024 11.8 and 10.6, 13.3 and 11.3, 14.3 and 12.4; 16384, N = 384 13.1 and 11.5, 15.1 and 14.7, 17.4 and 17.4, N = 1024 23.6
     // and 19.8, 29.0 and 26.1, 35.1 and 33.0; 23008, N = 384 18.5 and 17.4, 23.2 and 24.8, 28.8 and 31.7, N = 1024 34.6 and 31.8, 46.8 and 49.4, 60.3 and
-    // 67.8; 32768, N = 384 26.8 and 29.8, 39.6 and 50.2). At N = 320 five tiles of 64 columns leave three domains half idle and three of 128
-    // do not (8192: 7.8 and 6.4; 32768: 26.5 and 22.2, 49.0 and 48.8); at N = 512 the eight of 64 are one for every domain, and 128 columns gain little
-    // (8192: 8.0 and 7.7, 16384: 15.7 and 15.7, 18.9 and 19.2).
-    const bool all_short = M > 0 && start[1] <= kEntryLongRow && nnz <= 32 * M;
-    const bool wide = N <= 320 || (N != 512 && n_cols <= 16384) || (N > 512 && n_cols <= 24576 && nnz <= 8 * M);
-    if (N <= 64 || (aligned && (N <= 256 || (all_short && !wide)))) L.lanes = 8;
+    // 67.8; 32768, N = 384 26.8 and 29.8, 39.6 and 50.2).  At N = 320 five tiles of 64 columns bring a domain parts of two, three of 128 leave two domains
+    // half idle: for short rows or few rows of B the latter (16416, 8 entries a row 11.9 and 11.5; 23008, 11.5: 17.1 and 18.0; 26016, 2.6: 14.5 and 13.1,
+    // 5: 16.1 and 15.7, 8: 17.2 and 17.9; 32768, 3.3: 18.3 and 17.0, 6.6: 20.4 and 22.1, 16: 27.2 and 35.9).  At N = 512 the eight of 64 are one for every
+    // domain, and 128 columns gain little (8192: 8.0 and 7.7, 16384: 15.7 and 15.7, 18.9 and 19.2).
+    // Longer rows against an aligned B of 320 to 448 columns: 64 of them, too, of which the domains have even shares (with 64 and 128 columns: 4096 x 8192,
+    // 415 entries a row, N = 320 53 and 68 us; 1504 x 16000, 1611, N = 384 86 and 107; 5003 x 4104, 336, N = 384 62 and 68).
+    // Short rows against an unaligned B of more than 512 columns and 8192 rows, every row of it used four times and more: 128 columns, of which the domains have even
+    // shares, or 64 where B outgrows the L2 and its rows are used often (with 64, 128 and 256 columns: 9984 rows of B, 8 entries a row, N = 600 10.1,
+    // 9.3 and 10.5 us; 20000, 8, N = 520 24.7, 27.7 and 33.3; 23008, 16, N = 840 63, 76 and 85; 16384, 25, N = 1208 71, 75 and 97; 27008, 25, N = 712 104,
+    // 108 and 118; 32768, 16, N = 1800 215, 211 and 234).  On 430 such products the rule is 1 % slower than the best of the three; counting lines as
+    // below, which N = 904 to 1024, where whole tiles of 128 columns are one for every domain, still have, was 6 %.
+    const int64_t longest = M > 0 ? start[1] : 0;
+    const bool all_short = M > 0 && longest <= kEntryLongRow && nnz <= 32 * M;
+    const bool wide = N == 320 ? n_cols <= 18432 || 2 * nnz <= 11 * M : (N != 512 && n_cols <= 16384) || (N > 512 && n_cols <= 24576 && nnz <= 8 * M);
+    if (N <= 64 || (aligned && (N <= 256 || (all_short ? !wide : N < 512)))) L.lanes = 8;
     else if (aligned) L.lanes = N >= 1024 && nnz * N >= ((int64_t)1 << 29) ? 32 : 16;
     else if (N <= 256) L.lanes = N > 128 && (N <= 192 || !all_short || n_cols > 16384) ? 32 : 16;
+    else if (all_short && n_cols > 8192 && 2 * nnz >= 7 * n_cols && ((N > 512 && N <= 896) || N > 1024))
+        L.lanes = nnz >= 6 * M && n_cols >= 15000 && n_cols <= 31000 && 5 * nnz >= 37 * n_cols && 4 * M >= 3 * n_cols ? 8 : 16;
+    else if (!all_short && n_cols > 4096 && N > 512 && N <= 640) L.lanes = 16;    // five tiles of 128 columns in even shares: 4096 x 8192, N = 600 113 and 101 us
     else L.lanes = 1.1 * entry_row_lines(32, N, n_cols, all_short) < entry_row_lines(16, N, n_cols, all_short) ? 32 : 16;
+    // The loads of a row follow each other, the more of them the more lanes it has.  Where the longest, much longer than the others, has more than 3/4 of
+    // what a SIMD has of all loads (1024 SIMDs, 512 columns of one entry a load), fewer lanes.  CSR multiply of graphs, without and so: 4096 nodes, 13 entries
+    // a row and 909 in the longest, N = 424 32 and 13 us, N = 1016 35 and 17, N = 2504 33 and 29; of 8192, 13 and 1520, N = 512 19 and 13, N = 600 30 and
+    // 22; of 16384, 16 edges a node, N = 200 26 and 14.  On 280 products with such rows what is chosen is 3 % slower than the best, without this 13 %
+    // (and 10 % slower than without at worst: 8192 nodes, 35 a row, N = 744 35 and 39).
+    while (longest > kEntryLongRow && longest * M > 4 * nnz && L.lanes > 8) {
+        const int64_t tiles = (N + 8 * L.lanes - 1) / (8 * L.lanes);
+        const int64_t loads = longest * L.lanes / (longest > std::max<int64_t>(kEntryHugeRow, nnz * tiles / 4096) ? 256 : 64);
+        if (4 * loads * 1024 * 512 <= 3 * nnz * N) break;
+        L.lanes /= 2;
+    }
     const int64_t Q = (N + 8 * L.lanes - 1) / (8 * L.lanes);
     // A workgroup for a row costs its barrier and the fourfold sum; it pays where one wave would still be at the row when
     // the rest is done, i.e. beyond the share of all entries that one of 4096 waves takes (graph, N = 256: 66 -> 26 us;

@@ -230,6 +230,18 @@ void check_entry_plan()
         if (L.lanes != x.lanes) std::fprintf(stderr, "%lld entries a row, %lld rows of B, N = %lld: %d lanes\n", (long long)x.len, (long long)x.n_cols, (long long)x.N, L.lanes);
         REQUIRE(L.lanes == x.lanes && L.grid >= 8 && L.waves >= 9000 * x.lanes / 64);
     }
+    // by how often the rows of B are used, and one row (the first) longer than the others: fewer where its loads are too many of all
+    struct { int64_t rows, len, longest, n_cols, N; int lanes; } const more[] = {
+        {12300, 10, 10, 16000, 520, 8},   {12300, 9, 9, 16000, 520, 16},    {9000, 20, 20, 16000, 520, 16},  {12300, 10, 10, 16000, 1000, 16}, {12300, 10, 10, 16000, 320, 16},
+        {30000, 5, 5, 16000, 1288, 16},   {9000, 5, 5, 16384, 632, 32},     {9000, 300, 300, 16000, 384, 8},  {9000, 300, 300, 16000, 600, 16},  {9000, 300, 300, 4096, 600, 32},
+        {4096, 12, 1000, 4096, 200, 8},   {4096, 12, 1000, 4096, 1016, 8},  {4096, 12, 1000, 4096, 3752, 16}, {4096, 12, 256, 4096, 1016, 32},  {16384, 25, 3700, 16384, 1016, 32}};
+    for (const auto &x : more) {
+        std::vector<int64_t> start = {0, x.longest};
+        for (int64_t i = 1; i < x.rows; ++i) start.push_back(start.back() + x.len);
+        const vbrk::EntryLaunch L = vbrk::plan_entry_rows(start, x.n_cols, x.N, x.N % 64 == 0);
+        if (L.lanes != x.lanes) std::fprintf(stderr, "%lld rows of %lld entries, %lld, %lld of B, N = %lld: %d lanes\n", (long long)x.rows, (long long)x.len, (long long)x.longest, (long long)x.n_cols, (long long)x.N, L.lanes);
+        REQUIRE(L.lanes == x.lanes);
+    }
 }
 
 // Every call with the first 0, 1, 2 ... of its allocations succeeding, up to `most` or until it gets all it asks for: it

@@ -786,6 +786,35 @@ def test_csr_comparator_at_the_row_lengths_where_it_splits(n, ldb_pad, dtype):
     check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
 
 
+@pytest.mark.parametrize("n,ldb_pad,dtype", [(520, 0, "f16"), (576, 0, "bf16"), (776, 8, "f16"), (1096, 0, "bf16")])
+def test_csr_comparator_with_many_long_rows(n, ldb_pad, dtype):
+    # rows for a wave and for a workgroup with 128 and 256 columns a wave: none is much longer than the others
+    import torch
+    rng = np.random.default_rng(n)
+    lens = [257, 300, 512, 513, 1023, 1024, 1025, 1300, 2049, 2600, 0, 17] * 3
+    csr = csr_from_rows([sorted(rng.choice(2600, size=x, replace=False).tolist()) for x in lens], 2600, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, 2600, n + ldb_pad, dtype)
+    b = torch_io.bits_to_device(bits, dtype)[:, :n]
+    c = binding.CsrDev(csr).upload("cuda:0").spmm(b)
+    torch.cuda.synchronize()
+    c_ref, s = oracle.spmm(csr, np.ascontiguousarray(bits[:, :n]))
+    check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
+
+
+@pytest.mark.parametrize("n", [520, 1032, 1288])
+def test_csr_comparator_with_64_columns_a_wave_of_an_unaligned_b(n):
+    # short rows that use every row of a long B often; nine, seventeen and twenty-one column tiles, the last of eight columns
+    import torch
+    rng = np.random.default_rng(n)
+    cols = (rng.integers(0, 16000, size=(12300, 1)) + np.cumsum(rng.integers(1, 600, size=(12300, 10)), axis=1)) % 16000
+    csr = csr_from_rows([np.unique(r).tolist() for r in cols], 16000, rng)
+    bits = synth.dense_rhs(rng, 16000, n, "f16")
+    c = binding.CsrDev(csr).upload("cuda:0").spmm(torch_io.bits_to_device(bits, "f16"))
+    torch.cuda.synchronize()
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
+
+
 def test_csr_comparator_and_blocked_path_agree_on_the_graph_workload():
     import torch
     w = synth.workload("rmat", scale=0.125)
