@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
     // workgroup -> (column tile, four waves' rows): workgroups are dealt to the 8 L2 domains round-robin
     const int T = (p.n_waves + 3) / 4, Q = p.n_ntiles;
     int ntile, tile;
-    if (!map_workgroup<false, true>(blockIdx.x, T, Q, p.even, tile, ntile)) return;
+    if (!map_workgroup<true>(blockIdx.x, T, Q, p.even, tile, ntile)) return;
     const int in_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = tile * 4 + in_wg;
     if (wave >= p.n_waves) return;
     // parts: the groups of lanes that share a row; part: this group's number among them

@@ -35,17 +35,15 @@ constexpr int kXcd = 8;             // L2 domains; workgroup i runs on domain i 
 #endif
 
 // Workgroup -> (one of T tiles, one of Q column tiles); false: nothing to do.  Workgroups are dealt to the 8 L2 domains round-robin; a
-// domain keeps to few column tiles so that the B columns it gathers stay in its L2, and takes one after the other: every eighth, or (BESIDE)
-// such that lie side by side.  Tiles of one slab, which load the most of B for what they multiply, are faster with the latter, where the pieces
-// of a row of B that the domains read at a time lie farther apart (16 x 16 blocks, 4096 x 16384, N = 4096 160 and 156 us); taller ones are not
-// (64 x 64 blocks at 40 %, N = 8192 471 and 477; 6144 x 6144 at 10 %, N = 6184 90 and 93).
+// domain keeps to few column tiles, every eighth, so that the B columns it gathers stay in its L2, and takes one after the other.  (Column tiles
+// side by side on a domain: 16 x 16 blocks, 4096 x 16384, N = 4096 165.4 and 165.3 us among other calls, 64 x 64 blocks at 40 %, N = 8192 471 and 477.)
 // The column tiles left over when every domain has as many: a domain takes one or none, with fewer than 8 column tiles in all several domains
 // share one as long as there are domains.  Five or nine column tiles leave most domains half idle that way; `even` cuts each that is left over in
 // shares, 8 or 4 of its tiles' workgroups in turn, so that all domains have the same number, of two column tiles at most (what it gains and
 // where: even_columns).  A domain with parts of two takes the workgroups in the order of the tiles, the longest first, or (IN_TURN) one column
 // tile after the other, which is better for rows of entries, many short workgroups that live on what is in the L2 (16384 x 16384, 8 entries a
 // row, N = 640 22.9 and 21.2 us, N = 712 32.3 and 30.5) and worse for tiles (graph of 16384 nodes, N = 1200 65.5 and 78).
-template <bool BESIDE = false, bool IN_TURN = false>
+template <bool IN_TURN = false>
 VBRK_HOST_DEVICE bool map_workgroup(uint32_t block, uint32_t T, uint32_t Q, bool even, int &tile, int &ntile)
 {
     const uint32_t x = block % kXcd, own = Q / kXcd, rest = Q % kXcd;
@@ -53,7 +51,7 @@ VBRK_HOST_DEVICE bool map_workgroup(uint32_t block, uint32_t T, uint32_t Q, bool
     if (Q >= kXcd) {
         const uint32_t round = j / T;
         tile = (int)(j - round * T);
-        ntile = (int)(BESIDE && round < own ? own * x + round : x + kXcd * round);
+        ntile = (int)(x + kXcd * round);
         if (!even || round < own) return (uint32_t)ntile < Q;
         j -= own * T;
     } else if (!even) {

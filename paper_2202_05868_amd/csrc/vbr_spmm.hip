@@ -607,7 +607,7 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_kernel(const Params p)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<S, NS, DA, GATHER>()];
     int tile, ntile;
-    if (!map_workgroup<S == 1 && !GATHER>(blockIdx.x, p.n_tiles, p.n_ntiles, p.even, tile, ntile)) return;
+    if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.even, tile, ntile)) return;
     tile_body<DT, S, NS, DA, GATHER>(p, p.tiles[tile], ntile, smem);
 }
 

@@ -191,7 +191,7 @@ void check_plan()
 }
 
 // Every tile meets every column tile once, whatever the way the workgroups are dealt, and cut in shares no domain has many more than an eighth.
-template <bool BESIDE, bool IN_TURN>
+template <bool IN_TURN>
 void check_map()
 {
     ++g_cases;
@@ -204,7 +204,7 @@ void check_map()
                 std::vector<int> seen((size_t)T * Q), load(8);
                 int tile = 0, ntile = 0;
                 for (int b = 0; b < 8 * domain; ++b)
-                    if (vbrk::map_workgroup<BESIDE, IN_TURN>(b, T, Q, even, tile, ntile)) {
+                    if (vbrk::map_workgroup<IN_TURN>(b, T, Q, even, tile, ntile)) {
                         REQUIRE(tile >= 0 && tile < T && ntile >= 0 && ntile < Q);
                         ++seen[(size_t)tile * Q + ntile];
                         ++load[b % 8];
@@ -336,9 +336,8 @@ int main()
         ++g_cases;
     }
     check_plan();
-    check_map<false, false>();
-    check_map<true, false>();
-    check_map<false, true>();
+    check_map<false>();
+    check_map<true>();
     check_entry_plan();
     // memory that runs out: at every allocation of a small matrix, and at the first ones of a matrix whose check takes threads
     {
