@@ -36,7 +36,7 @@ struct EntryParams {
     int64_t ldb, ldc;
     uint32_t b_bytes;                // bytes from B's first element to the end of its last row (WIDE: not used)
     int32_t n_rows, n_huge, n_long, N, n_waves, n_ntiles;
-    bool even;
+    ColumnMap map;
 };
 
 template <int DT>
@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
     // workgroup -> (column tile, four waves' rows): workgroups are dealt to the 8 L2 domains round-robin
     const int T = (p.n_waves + 3) / 4, Q = p.n_ntiles;
     int ntile, tile;
-    if (!map_workgroup<true>(blockIdx.x, T, Q, p.even, tile, ntile)) return;
+    if (!map_workgroup<true>(blockIdx.x, T, Q, p.map, tile, ntile)) return;
     const int in_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = tile * 4 + in_wg;
     if (wave >= p.n_waves) return;
     // parts: the groups of lanes that share a row; part: this group's number among them
@@ -216,7 +216,7 @@ int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &r
     p.n_rows = (int32_t)n_rows;
     p.N = (int32_t)N;
     p.n_ntiles = (int32_t)((N + 8 * L.lanes - 1) / (8 * L.lanes));
-    p.even = L.even;
+    p.map = column_map((uint32_t)p.n_ntiles, L.even);
     p.n_huge = L.n_huge;
     p.n_long = L.n_long;
     p.n_waves = (int32_t)L.waves;

@@ -34,6 +34,22 @@ constexpr int kXcd = 8;             // L2 domains; workgroup i runs on domain i 
 #define VBRK_HOST_DEVICE inline
 #endif
 
+// What map_workgroup needs to know of a launch beside T and Q: the way column tiles are dealt, and for fewer than 8 of them, whole, four bits a
+// domain each: its column tile, its number among the domains of that, and how many these are.  (Every wave divided for them: entry rows of 16384 x
+// 16384, 8 entries a row, N = 8 4.2 and now 4.0 us, N = 256 9.5 and 9.3; 1024 rows in groups of 32, N = 256 4.6 and 4.5.)
+struct ColumnMap { uint32_t even, ntile, member, members; };
+inline ColumnMap column_map(uint32_t Q, bool even)
+{
+    ColumnMap m{even, 0, 0, 0};
+    for (uint32_t x = 0; x < kXcd && Q < kXcd; ++x) {
+        const uint32_t ntile = x % Q;
+        m.ntile |= ntile << (4 * x);
+        m.member |= x / Q << (4 * x);
+        m.members |= (kXcd - ntile + Q - 1) / Q << (4 * x);
+    }
+    return m;
+}
+
 // Workgroup -> (one of T tiles, one of Q column tiles); false: nothing to do.  Workgroups are dealt to the 8 L2 domains round-robin; a
 // domain keeps to few column tiles, every eighth, so that the B columns it gathers stay in its L2, and takes one after the other.  (Column tiles
 // side by side on a domain: 16 x 16 blocks, 4096 x 16384, N = 4096 165.4 and 165.3 us among other calls, 64 x 64 blocks at 40 %, N = 8192 471 and 477.)
@@ -44,7 +60,7 @@ constexpr int kXcd = 8;             // L2 domains; workgroup i runs on domain i 
 // tile after the other, which is better for rows of entries, many short workgroups that live on what is in the L2 (16384 x 16384, 8 entries a
 // row, N = 640 22.9 and 21.2 us, N = 712 32.3 and 30.5) and worse for tiles (graph of 16384 nodes, N = 1200 65.5 and 78).
 template <bool IN_TURN = false>
-VBRK_HOST_DEVICE bool map_workgroup(uint32_t block, uint32_t T, uint32_t Q, bool even, int &tile, int &ntile)
+VBRK_HOST_DEVICE bool map_workgroup(uint32_t block, uint32_t T, uint32_t Q, const ColumnMap &m, int &tile, int &ntile)
 {
     const uint32_t x = block % kXcd, own = Q / kXcd, rest = Q % kXcd;
     uint32_t j = block / kXcd;
@@ -52,12 +68,11 @@ VBRK_HOST_DEVICE bool map_workgroup(uint32_t block, uint32_t T, uint32_t Q, bool
         const uint32_t round = j / T;
         tile = (int)(j - round * T);
         ntile = (int)(x + kXcd * round);
-        if (!even || round < own) return (uint32_t)ntile < Q;
+        if (!m.even || round < own) return (uint32_t)ntile < Q;
         j -= own * T;
-    } else if (!even) {
-        const uint32_t member = x / Q;
-        ntile = (int)(x - member * Q);
-        tile = (int)(member + (kXcd - ntile + Q - 1) / Q * j);
+    } else if (!m.even) {
+        ntile = (int)(m.ntile >> (4 * x) & 15);
+        tile = (int)((m.member >> (4 * x) & 15) + (m.members >> (4 * x) & 15) * j);
         return (uint32_t)tile < T;
     }
     const uint32_t lg = rest & 1 ? 0 : rest & 2 ? 1 : 2, shares = kXcd >> lg, n = rest >> lg;      // of a column tile, and how many of them a domain has

@@ -58,7 +58,7 @@ struct Params {
     int32_t lg_gran;
     int32_t n_tiles;          // T
     int32_t n_ntiles;         // Q = ceil(N / 256), of the split kernel ceil(N / 64)
-    bool even;                // see map_workgroup
+    ColumnMap map;
     int32_t whole, rest;      // mixed kernel: tiles with one workgroup a column tile, and behind them tiles with four, see there ...
     int32_t split;            // ... and from how many K-steps on these are split
 };
@@ -353,6 +353,9 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
             issue_a(DA - NS + 1 + t, DA - NS + 1 + t);
         }
         int bslot = 0, aslot = 0;
+        // With deep rings and one slab few waves are on a CU and the fetch of the short loop's instructions shows, 32 bytes at a time: begun 16 bytes into
+        // such a piece, 1712 x 9184 in 16 x 16 blocks, N = 952 takes 18.7 us, at 0 19.3, at 4 and 8 19.8, at 12 19.1.  The other kernels take the same.
+        if constexpr (S == 1 && NS > 2) asm volatile(".p2align 5\n\t.rept 4\n\ts_nop 0\n\t.endr" ::: "memory");
         for (int ks = 0; ks < n_ks; ++ks) {
             // The last iterations issue nothing for K-steps past the end (a short tile would spend a
             // tenth of its loads there); from the first iteration whose predecessors left loads out,
@@ -607,7 +610,7 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_kernel(const Params p)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds_bytes<S, NS, DA, GATHER>()];
     int tile, ntile;
-    if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.even, tile, ntile)) return;
+    if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.map, tile, ntile)) return;
     tile_body<DT, S, NS, DA, GATHER>(p, p.tiles[tile], ntile, smem);
 }
 
@@ -624,7 +627,7 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
     constexpr int k8 = MAXS == 8 ? tile_lds_bytes<8, NS8, kADistance, false>() : 0;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[std::max(k8, std::max(k4, kLow))];
     int tile, ntile;
-    if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.even, tile, ntile)) return;
+    if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.map, tile, ntile)) return;
     // the last tiles, in a split launch all of them, have four workgroups a column tile: quarters of it for those that are split, the
     // others use the first
     const bool four = tile >= p.whole;
@@ -666,7 +669,7 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_split_kernel(const Params p
     constexpr int SLOTS = S <= 2 ? 3 : 2;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[deep_lds_bytes<S, SLOTS>()];
     int tile, ntile;
-    if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.even, tile, ntile)) return;
+    if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.map, tile, ntile)) return;
     deep_body<DT, S, SLOTS, GATHER>(p, p.tiles[tile], ntile * kDeepN, smem);
 }
 
@@ -702,7 +705,7 @@ struct PanelParams {
     int32_t lg_gran;          // >= 3
     int32_t n_panels;         // T
     int32_t n_ntiles;         // Q = ceil(N / 128)
-    bool even;
+    ColumnMap map;
 };
 
 // Panel kernel: one workgroup (8 waves) owns R slabs (R * 16 rows of short row groups, whatever
@@ -734,7 +737,7 @@ __global__ void __launch_bounds__(kPanelThreads) vbr_spmm_panel_kernel(const Pan
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kBRing + NAS * kAStage + 2 * kFragBytes];
 
     int tile, ntile;
-    if (!map_workgroup(blockIdx.x, p.n_panels, p.n_ntiles, p.even, tile, ntile)) return;
+    if (!map_workgroup(blockIdx.x, p.n_panels, p.n_ntiles, p.map, tile, ntile)) return;
     const PanelDesc pd = p.panels[tile];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -898,10 +901,9 @@ int launch_all(const vbr *v, const Params &base, PanelParams pp, hipStream_t str
         Params p = base;
         p.tiles = base.tiles + L.first_tile;
         p.n_tiles = L.n_tiles;
-        p.even = L.even;
         const dim3 grid((unsigned)L.grid);
         if (L.kind == VBR_LAUNCH_PANEL) {
-            pp.even = L.even;
+            pp.map = column_map((uint32_t)pp.n_ntiles, L.even);
             hipLaunchKernelGGL((vbr_spmm_panel_kernel<DT, 8, 4, 3>), grid, dim3(kPanelThreads), 0, stream, pp);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
@@ -948,6 +950,7 @@ int launch_all(const vbr *v, const Params &base, PanelParams pp, hipStream_t str
             kernel = vbr_spmm_kernel<DT, 8, kStagesTall, kADistance>;
             break;
         }
+        p.map = column_map((uint32_t)p.n_ntiles, L.even);
         hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }

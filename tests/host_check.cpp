@@ -203,8 +203,9 @@ void check_map()
                 const int domain = even ? Q / 8 * T + rest / each * ((T * each + 7) / 8) : Q >= 8 ? (Q + 7) / 8 * T : (T + 8 / Q - 1) / (8 / Q);
                 std::vector<int> seen((size_t)T * Q), load(8);
                 int tile = 0, ntile = 0;
+                const vbrk::ColumnMap map = vbrk::column_map(Q, even);
                 for (int b = 0; b < 8 * domain; ++b)
-                    if (vbrk::map_workgroup<IN_TURN>(b, T, Q, even, tile, ntile)) {
+                    if (vbrk::map_workgroup<IN_TURN>(b, T, Q, map, tile, ntile)) {
                         REQUIRE(tile >= 0 && tile < T && ntile >= 0 && ntile < Q);
                         ++seen[(size_t)tile * Q + ntile];
                         ++load[b % 8];
