@@ -146,12 +146,15 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
     const int n_ks = td.n_ks;
     const int q = lane >> 4, s16 = lane & 15;
 
-    // C rows of the tile, lane l of register i that of row 64 i + l: requested first and used last.
+    // C rows of the tile, lane l of register i that of row 64 i + l: requested first and used last.  A narrow column tile (see its stores) asks for
+    // them when it stores: handed round from here they took longer (row groups of 1 to 100 rows, in a graph of calls, N = 72 5.7 and 5.4 us, N = 8
+    // 9.3 and 9.0, N = 40 7.5 and 7.2), and the kernels that have both are faster at other N, too (N = 264 7.2 and 6.9, N = 672 8.5 and 8.1).
+    const bool narrow = NARROW && p.N - n0 <= kTileN / 2;
     int32_t c_rows[(S + 3) / 4];
 #pragma unroll
     for (int i = 0; i < (S + 3) / 4; ++i) {
         const int rr = 64 * i + lane;
-        c_rows[i] = rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
+        c_rows[i] = !narrow && rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
     }
 
     float4v acc[S][4];
@@ -401,16 +404,20 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
     // in the mixed kernel with tiles of up to 8 those of 4 have it too, without which its code runs 1 % slower at any N).
     if (n_ks > 0) __syncthreads();                  // the rings are read no more
     if constexpr (NARROW) {
-        if (__builtin_expect(p.N - n0 <= kTileN / 2, 0)) {
+        if (__builtin_expect(narrow, 0)) {
+            int32_t row[S];
 #pragma unroll
             for (int s = 0; s < S; ++s) {
-                const int32_t row = __shfl(c_rows[s / 4], (s & 3) * kSlabRows + s16);
+                const int rr = s * kSlabRows + s16;
+                row[s] = rr < td.n_rows ? (GATHER ? p.prow : p.perm)[td.row_begin + rr] : -1;
+            }
+#pragma unroll
+            for (int s = 0; s < S; ++s)
 #pragma unroll
                 for (int f = 0; f < 4; ++f) {
                     const int n = n0 + wave * kWaveN + 16 * f + 4 * q;
-                    if (row >= 0 && n < p.N) __builtin_nontemporal_store(acc[s][f], reinterpret_cast<float4v *>(p.C + row * p.ldc + n));
+                    if (row[s] >= 0 && n < p.N) __builtin_nontemporal_store(acc[s][f], reinterpret_cast<float4v *>(p.C + row[s] * p.ldc + n));
                 }
-            }
             return;
         }
     }
