@@ -1476,7 +1476,13 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         // 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
         const int64_t grid = grid_size(T, Qt);             // as if of whole column tiles
         const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= 3 * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= (grid <= kTwoOnACu / 2 ? 5 : 18));
-        Launch L{kind, 0, T, 0, split, few, 0, !split && even_columns(T, Qt)};
+        // Six column tiles, the last of them narrow: the domains that would get most of it have little to do, and the others parts of two column tiles for
+        // little less than a whole one.  Whole and shares, 72 columns in the last: 16 x 16 blocks, 3760 x 14592 61.5 and 64.3 us; 64 x 64 blocks, 8192 x 8192 41.1
+        // and 43.5; graph of 16384 nodes 54.8 and 58.8; all 256: 60.1 and 59.0, 38.0 and 38.3, 48.5 and 49.3.  Tiles of 5 to 8 slabs, which are fewer and of
+        // many lengths, gain all the same (row groups of 16 to 128 rows 72.4 and 64.9, of 1 to 100 rows 22.9 and 21.4), and so do five and nine column tiles
+        // (80 columns in the last of five: 61.4 and 55.8, 37.7 and 36.8, 58.6 and 45.3; 24 of nine: 109 and 74, 75.7 and 63.3, 101 and 98).
+        const bool narrow_sixth = Qt == 6 && N - 5 * kTileN <= kTileN / 2 && v->class_count[3] == 0;
+        Launch L{kind, 0, T, 0, split, few, 0, !split && !narrow_sixth && even_columns(T, Qt)};
         if (kind == VBR_LAUNCH_TILE_MIXED) {
             L.whole = split ? 0 : T;
             // A last round of few workgroups takes as long as a full one.  Where an L2 domain has up to a quarter more than it holds at once (or

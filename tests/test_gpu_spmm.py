@@ -416,7 +416,7 @@ def test_one_slab_tiles_over_eight_to_seventeen_column_tiles(n):
     check_c(c, c_ref, s, "column tiles")
 
 
-@pytest.mark.parametrize("kind,n,workgroups", [("mixed", 1096, 5 * 10), ("mixed", 1536, 3 * 20), ("mixed", 2304, 77 + 10), ("panel", 640, 5 * 6), ("panel", 1160, 47 + 12),
+@pytest.mark.parametrize("kind,n,workgroups", [("mixed", 1096, 5 * 10), ("mixed", 1536, 3 * 20), ("mixed", 1408, 77), ("mixed", 1416, 3 * 20), ("mixed", 2304, 77 + 10), ("panel", 640, 5 * 6), ("panel", 1160, 47 + 12),
                                                ("entries", 1216, 563 + 141), ("entries", 1096, 563 + 71)])
 def test_column_tiles_that_the_domains_share(kind, n, workgroups):
     # five, six, nine and ten column tiles, not all of them full: mixed tiles, panels and rows of entries
