@@ -1410,7 +1410,7 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
     if (!v->panels.empty()) {
         const int64_t P = (int64_t)v->panels.size();
         const bool even = even_columns(P, Qp);
-        out[n++] = Launch{VBR_LAUNCH_PANEL, 0, (int32_t)P, grid_size(P, Qp, even), 0, false, 0, even};
+        out[n++] = Launch{VBR_LAUNCH_PANEL, 0, (int32_t)P, grid_size(P, Qp, even), 0, false, 0, 0, even};
     }
     static const int32_t kind_of_class[kClasses] = {VBR_LAUNCH_TILE_1, VBR_LAUNCH_TILE_2, VBR_LAUNCH_TILE_4, VBR_LAUNCH_TILE_8, VBR_LAUNCH_TILE_MIXED,
                                                     VBR_LAUNCH_GATHER_1, VBR_LAUNCH_GATHER_2, VBR_LAUNCH_GATHER_4};
@@ -1482,27 +1482,31 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         // many lengths, gain all the same (row groups of 16 to 128 rows 72.4 and 64.9, of 1 to 100 rows 22.9 and 21.4), and so do five and nine column tiles
         // (80 columns in the last of five: 61.4 and 55.8, 37.7 and 36.8, 58.6 and 45.3; 24 of nine: 109 and 74, 75.7 and 63.3, 101 and 98).
         const bool narrow_sixth = Qt == 6 && N - 5 * kTileN <= kTileN / 2 && v->class_count[3] == 0;
-        Launch L{kind, 0, T, 0, split, few, 0, !split && !narrow_sixth && even_columns(T, Qt)};
+        Launch L{kind, 0, T, 0, split, few, 0, 0, !split && !narrow_sixth && even_columns(T, Qt)};
         if (kind == VBR_LAUNCH_TILE_MIXED) {
             L.whole = split ? 0 : T;
+            L.rest = split ? v->n_work : 0;
             // A last round of few workgroups takes as long as a full one.  Where an L2 domain has up to a quarter more than it holds at once (or
             // than it holds in two, three .. rounds), the last tiles, the shortest, are split: their workgroups are over in a third of the time.  Not
             // split and split, groups of 16 to 128 rows (64 workgroups at once), N = 512: 66 on a domain, 10 K-steps 17.8 and 15.2 us, 20: 25.4 and
             // 19.7; 70: 18.7 and 16.2, 25.8 and 22.1; 76: 19.8 and 19.1, 28.2 and 25.5; 84: 20.8 and 21.0, 29.6 and 28.6; 94: 23.4 and 24.2; 132: 32.1
             // and 30.1; 140: 32.7 and 31.2; 152: 33.8 and 34.4; 198: 43.3 and 41.4; groups of up to 64 rows (96 at once): 98: 18.7 and 16.0, 28.1 and
             // 22.5; 108: 20.4 and 17.9; 116: 21.4 and 19.4; 126: 21.9 and 22.0; 216: 34.2 and 33.2; N = 256, 1024, 2048 alike.  With more than eight
-            // column tiles a domain has several of them, one behind the other, and the rounds are many: these stay whole.
+            // column tiles a domain has several of them, one behind the other, and the rounds are many: these stay whole.  Tiles without a K-step do not
+            // count: they run behind the others and are over at once (66 tiles of 16 to 128 rows and 20 of them, N = 2048, counted and not, 10 K-steps
+            // 18.1 and 15.7, 20: 26.7 and 20.8; 76 and 7: 26.9 and 23.6; 114 of up to 64 rows and 22, 10: 20.5 and 18.1).
             if (!split && Qt <= kXcd) {
-                const int64_t members = kXcd / Qt, at_once = (few || v->class_count[3] > 0 ? kTwoOnACu : kThreeOnACu) / kXcd;
-                const int64_t here = L.even ? grid_size(T, Qt, true) / kXcd : (T + members - 1) / members, over = here > at_once ? here % at_once : 0;
+                const int64_t work = v->n_work, members = kXcd / Qt, at_once = (few || v->class_count[3] > 0 ? kTwoOnACu : kThreeOnACu) / kXcd;
+                const int64_t here = L.even ? grid_size(work, Qt, true) / kXcd : (work + members - 1) / members, over = here > at_once ? here % at_once : 0;
                 const int64_t last = L.even ? (kXcd * over + Qt - 1) / Qt : over * members;
-                const TileDesc &first = v->dev_tiles[(size_t)std::max<int64_t>(T - last, 0)];
-                if (over > 0 && 4 * over <= at_once && T > last && first.group > kTileDeep && first.n_slabs <= split_slabs(few) && first.n_ks >= kSplitShort) {
-                    L.whole = (int32_t)(T - last);
+                const TileDesc &first = v->dev_tiles[(size_t)std::max<int64_t>(work - last, 0)];
+                if (over > 0 && 4 * over <= at_once && work > last && first.group > kTileDeep && first.n_slabs <= split_slabs(few) && first.n_ks >= kSplitShort) {
+                    L.whole = (int32_t)(work - last);
+                    L.rest = (int32_t)last;
                     L.split = kSplitShort;
                 }
             }
-            L.grid = grid_size(L.whole + 4 * (int64_t)(T - L.whole), Qt, L.even);
+            L.grid = grid_size(T + 3 * (int64_t)L.rest, Qt, L.even);
         } else {
             L.grid = grid_size(T, split ? Qd : Qt, L.even);
         }

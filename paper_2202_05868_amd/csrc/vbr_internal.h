@@ -99,6 +99,20 @@ VBRK_HOST_DEVICE bool map_workgroup(uint32_t block, uint32_t T, uint32_t Q, cons
     return (uint32_t)tile < T;
 }
 
+// Number of a workgroup among those of a column tile -> the tile, and the quarter of the column tile if the tile has four workgroups (true): of the
+// tiles of a mixed launch the first `whole` have one, `rest` have four, those of the first quarter before those of the second, and the others,
+// tiles without a K-step, have one.  (Without tiles that have four, `whole` is all of them.)
+VBRK_HOST_DEVICE bool split_tile(int &tile, int whole, int rest, int &quarter)
+{
+    quarter = 0;
+    if (tile < whole) return false;
+    const int q = (tile - whole) / rest;
+    tile -= rest * (q < 3 ? q : 3);
+    if (q > 3) return false;
+    quarter = q;
+    return true;
+}
+
 // One workgroup tile: up to kMaxSlabs slabs of ONE row group, walked over the group's K-steps (a block tile), or up to
 // kMaxGatherSlabs slabs of the row list, walked over the columns its rows touch (a column-gathered tile).
 struct TileDesc {

@@ -59,7 +59,7 @@ struct Params {
     int32_t n_tiles;          // T
     int32_t n_ntiles;         // Q = ceil(N / 256), of the split kernel ceil(N / 64)
     ColumnMap map;
-    int32_t whole, rest;      // mixed kernel: tiles with one workgroup a column tile, and behind them tiles with four, see there ...
+    int32_t whole, rest;      // mixed kernel: tiles with one workgroup a column tile, and behind them some with four, see there ...
     int32_t split;            // ... and from how many K-steps on these are split
 };
 
@@ -635,11 +635,10 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_mixed_kernel(const Params p
     __shared__ __attribute__((aligned(1024))) unsigned char smem[std::max(k8, std::max(k4, kLow))];
     int tile, ntile;
     if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.map, tile, ntile)) return;
-    // the last tiles, in a split launch all of them, have four workgroups a column tile: quarters of it for those that are split, the
-    // others use the first
-    const bool four = tile >= p.whole;
-    const int quarter = four ? (tile - p.whole) / p.rest : 0;
-    const TileDesc td = p.tiles[tile - quarter * p.rest];
+    // quarters of a column tile for the tiles that are split; of those that have four workgroups and are not, the first takes all of it
+    int quarter;
+    const bool four = split_tile(tile, p.whole, p.rest, quarter);
+    const TileDesc td = p.tiles[tile];
     if (td.group <= kTileDeep) {
         if (quarter != 0) return;
         const int n0 = ntile * kTileN + (kTileDeep - td.group) * kDeepN;
@@ -920,9 +919,9 @@ int launch_all(const vbr *v, const Params &base, PanelParams pp, hipStream_t str
         void (*kernel)(Params) = nullptr;
         if (L.kind == VBR_LAUNCH_TILE_MIXED) {
             p.whole = L.whole;
-            p.rest = L.n_tiles - L.whole;
+            p.rest = L.rest;
             p.split = L.split;
-            p.n_tiles = p.whole + 4 * p.rest;
+            p.n_tiles = L.n_tiles + 3 * p.rest;
         } else if (L.split) {
             p.n_ntiles = (p.N + kDeepN - 1) / kDeepN;
         }

@@ -215,6 +215,29 @@ void check_map()
             }
 }
 
+// The workgroups of a column tile of a mixed launch: one for a tile, or one for each of its four quarters.
+void check_split_tile()
+{
+    ++g_cases;
+    for (int whole : {0, 1, 5, 40})
+        for (int rest : {0, 1, 3, 17})
+            for (int behind : {0, 1, 9}) {
+                if (whole + rest + behind == 0 || (rest == 0 && behind > 0)) continue;
+                std::vector<int> one((size_t)(whole + rest + behind)), quarters(one.size());
+                for (int w = 0; w < whole + 4 * rest + behind; ++w) {
+                    int tile = w, quarter = -1;
+                    const bool four = vbrk::split_tile(tile, whole, rest, quarter);
+                    REQUIRE(tile >= 0 && tile < (int)one.size() && four == (tile >= whole && tile < whole + rest) && quarter >= 0 && quarter < (four ? 4 : 1));
+                    if (four) quarters[(size_t)tile] |= 1 << quarter;
+                    ++one[(size_t)tile];
+                }
+                for (int t = 0; t < (int)one.size(); ++t) {
+                    const bool four = t >= whole && t < whole + rest;
+                    REQUIRE(one[(size_t)t] == (four ? 4 : 1) && quarters[(size_t)t] == (four ? 15 : 0));
+                }
+            }
+}
+
 // Lanes of a row of entries: 8 (64 columns) where rows of B begin on a cache line, else 128 or 256 columns by how many lines the
 // busiest L2 domain has to bring.
 void check_entry_plan()
@@ -339,6 +362,7 @@ int main()
     check_plan();
     check_map<false>();
     check_map<true>();
+    check_split_tile();
     check_entry_plan();
     // memory that runs out: at every allocation of a small matrix, and at the first ones of a matrix whose check takes threads
     {

@@ -254,6 +254,29 @@ def test_the_last_tiles_of_a_launch_that_does_not_fit_are_split(heights, col_blo
     check_c(c, c_ref, s, "the last tiles split")
 
 
+@pytest.mark.parametrize("tiles,n,split,empty", [(259, 504, 4, 0), (131, 760, 4, 700), (100, 1272, 2, 0), (100, 1280, 2, 640), (97, 1536, 15, 33), (66, 2040, 2, 1000)])
+def test_the_last_tiles_are_split_over_fewer_column_tiles_and_before_tiles_without_entries(tiles, n, split, empty):
+    # two, three, and five and six column tiles that the domains share; rows without entries behind them, whose tiles have one workgroup
+    rng = np.random.default_rng(tiles)
+    rows = []
+    for t in range(tiles):
+        cols = np.sort((rng.choice(16, size=4 + t % 3, replace=False)[:, None] * 32 + np.arange(32)).reshape(-1))
+        rows += [cols.tolist() for _ in range(128 if t < 10 else 30 if t % 2 else 16)]
+    rg = np.cumsum([0] + [128 if t < 10 else 30 if t % 2 else 16 for t in range(tiles)] + ([empty] if empty else [])).astype(np.int32)
+    rows += [[]] * empty
+    csr = csr_from_rows(rows, 512, rng)
+    order = rng.permutation(len(rows)).astype(np.int32)
+    csr = synth.permute_rows(csr, np.argsort(order))
+    bits = synth.dense_rhs(rng, 512, n, "f16")
+    c, v = gpu_spmm(csr, order, rg, 32, bits, ldc_pad=4)
+    plan = v.launches(n)
+    q, t = -(-n // 256), tiles + -(-empty // 64) + 3 * split
+    domain = {8: t, 2: -(-t // 4), 3: -(-t // 2), 5: 5 * -(-t // 8), 6: 3 * -(-t // 4)}[q]
+    assert [(p["kernel"], p["workgroups"]) for p in plan] == [("vbr_spmm_mixed_kernel", 8 * domain)]
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "the last tiles split, %d column tiles" % q)
+
+
 @pytest.mark.parametrize("n_ks", [5, 6, 8])
 @pytest.mark.parametrize("heights,col_block,n", [([32] * 30, 32, 1800), ([16] * 32, 4, 2048), ([32, 20] * 14, 8, 2040), ([64, 100, 16] * 9, 16, 2048), ([30, 9] * 15, 4, 1992)])
 def test_lists_about_as_long_as_the_deeper_rings(heights, col_block, n_ks, n):

@@ -428,3 +428,24 @@ def test_launches_are_not_split_where_a_tile_that_cannot_be_takes_longest():
     rg = np.array([0, 100, 120, 140, 160, 180], dtype=np.int32)         # one group of seven slabs, four of two
     v = binding.vbr_build(csr, np.arange(180, dtype=np.int32), rg, 32)
     assert [(p["tiles"], p["workgroups"]) for p in v.launches(256)] == [(5, 8)]
+
+
+def mixed_heights_and_empty_rows(tiles, n_ks, empty):
+    """Row groups of 16 and 128 rows that hold n_ks K-steps of 32 columns, then rows without entries."""
+    heights = [128] * 10 + [16] * (tiles - 10)
+    full = full_csr(sum(heights), 32 * n_ks)
+    csr = dict(full, n_rows=full["n_rows"] + empty, row_ptr=np.concatenate([full["row_ptr"], np.full(empty, full["nnz"], dtype=np.int64)]))
+    rg = np.cumsum([0] + heights + ([empty] if empty else [])).astype(np.int32)
+    return binding.vbr_build(csr, np.arange(csr["n_rows"], dtype=np.int32), rg, 32)
+
+
+@pytest.mark.parametrize("tiles,n,split", [(66, 2048, 2), (80, 2048, 16), (81, 2048, 0), (64, 2048, 0), (258, 512, 4), (130, 768, 2), (100, 1280, 2), (97, 1536, 15)])
+@pytest.mark.parametrize("empty_tiles", [0, 20])
+def test_the_last_tiles_are_split_by_the_tiles_with_entries_on_a_domain(tiles, n, split, empty_tiles):
+    # 64 workgroups of such tiles at once on a domain; of eight, two, three, and five and six column tiles, which the domains share; tiles
+    # without a K-step run behind the others and do not count
+    v = mixed_heights_and_empty_rows(tiles, 4, 64 * empty_tiles)
+    plan = v.launches(n)
+    q, t = n // 256, tiles + empty_tiles + 3 * split
+    whole = {8: t, 2: -(-t // 4), 3: -(-t // 2), 5: 5 * -(-t // 8), 6: 3 * -(-t // 4)}[q]
+    assert [(p["kernel"], p["tiles"], p["workgroups"]) for p in plan] == [("vbr_spmm_mixed_kernel", tiles + empty_tiles, 8 * whole)]
