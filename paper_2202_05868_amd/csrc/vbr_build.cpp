@@ -1393,11 +1393,18 @@ namespace vbrk {
 // One launch for all of them, not one per class: the classes' tails fill each other's gaps, and no launch waits for
 // another.  Measured against launches side by side on streams of their own, and one behind the other: row groups of 16 to 128
 // rows, N = 4096: 169 and 155 -> 137 us; graph of 16384 nodes, N = 4096: 192 and 195 -> 181; of 4096 nodes, N = 2048: 41 and
-// 24 -> 20.  Tiles without a K-step run behind the others, where their stores fill what those leave free; only where they are many, but
-// less than a quarter of the others, the two ways take the same and they have a launch of the kernel that just stores zeros (in the
-// launch of the others and apart: graphs of 16384 nodes, 8 edges a node, more than a quarter, N = 4096 79 and 85 us, N = 2048 41 and
-// 48; of 8192 nodes, N = 4096 39 and 45; less: 32 edges, N = 4096 149 and 152, N = 3000 154 and 151, 64 edges, N = 4096 194 and 197.  With
-// few of them a launch of its own takes 3 us more).
+// 24 -> 20.
+// Tiles without a K-step run behind the others, where their stores fill what those leave free.  The kernels of one and two slabs, of which more
+// workgroups fit on a CU than of the mixed one, take them themselves (mixed, apart and so: 512 tiles of 16 rows, 40 K-steps, N = 4096, a quarter of the rows
+// empty 241, 223 and 217 us, half 249, 239 and 229; 16 K-steps, N = 1024, a quarter 32.1, 31.4 and 29.0, 70 % 41.2, 45.2 and 42.7; 400 of 32 rows, 16
+// K-steps, N = 4096, half 143, 149 and 134; on average 10 % less than mixed and 20 % less than apart).  Launches that are split over K stay mixed (two
+// slabs, 40 K-steps, N = 256, 128 tiles mixed 9.7 and own kernel 11.2; 16: 7.6 and 5.9), and so do tall tiles, for which the mixed kernel is as good
+// as their own (64 and 128 rows, 2 to 70 % empty: 0.3 and 1.3 % slower on average; 40 tiles of 64 rows, 40 K-steps, N = 4096 34.8 and 45.7), and tiles of a
+// single K-step, which mostly store (70 tiles, N = 8200, 16 without a K-step: mixed 23.2, apart 23.5, own kernel 21.9).  Only where those without a K-step
+// are many, but less than a quarter of the others, the two ways take nearly the same and they have a launch of the kernel that just stores zeros (in the
+// launch of the others and apart: graphs of 16384 nodes, 32 edges a node, N = 4096 176 and 177, N = 3000 147 and 148, 64 edges 217 and 221, 198 and
+// 196, of 8192 nodes, 16 edges, N = 4096 48 and 53; more than a quarter: 16384 nodes, 8 edges, N = 4096 94 and 101, N = 2048 44 and 49.  With few of them
+// a launch of its own takes 3 us more).
 int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUNCHES])
 {
     int n = 0;
@@ -1418,9 +1425,11 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
     for (int c = 0; c < kClasses; ++c)
         if (v->class_count[c] > 0) { ++classes; last = c; }
     const int32_t T_all = (int32_t)v->dev_tiles.size(), T_empty = T_all - v->n_work;
-    const bool apart = T_empty * Qt >= kEmptyApart && 4 * T_empty < v->n_work;
+    const bool low_class = classes == 1 && (last < 2 || last == kClassGather || last == kClassGather + 1);
+    const bool keeps_kernel = low_class && v->dev_tiles[0].n_ks > 1;
+    const bool apart = !keeps_kernel && T_empty * Qt >= kEmptyApart && 4 * T_empty < v->n_work;
     const int32_t T = apart || v->n_work == 0 ? v->n_work : T_all;
-    // (tiles without a K-step are gathered ones of up to 4 slabs: the kernel of these takes them too, and the mixed one)
+    // (tiles without a K-step are gathered ones of up to 4 slabs: the kernel of these is the kernel of their class, and the mixed one takes them, too)
     if (T > 0) {
         const bool one_kind = classes == 1 && (T == v->n_work || last == kClasses - 1);
         // Tiles of up to four slabs with long lists whose workgroups leave CUs idle: four workgroups of 64 columns each instead, whose waves split
@@ -1462,7 +1471,7 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         // 6.0 and 8.1; 128: 7.2 and 6.7, 7.7 and 8.1, 8.5 and 14.1.
         const int32_t longest = v->dev_tiles[0].n_slabs <= 4 && splittable > 0 ? v->dev_tiles[0].n_ks : 0;
         const int32_t split = longest >= kSplitSteps && load <= 16 * 4800 ? kSplitSteps : longest >= kSplitShort && resident <= 8 * 64 ? kSplitShort : 0;
-        const int32_t kind = one_kind ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED;
+        const int32_t kind = one_kind || (keeps_kernel && !split) ? kind_of_class[last] : VBR_LAUNCH_TILE_MIXED;
         // Deeper rings allow only two workgroups on a CU and shorten the chain of K-steps of each: worth it where all workgroups are resident then
         // and their lists are long.  An L2 domain holds 64, and the busiest has an eighth of the grid: column tiles whose number does not divide by
         // eight do not fall evenly (82 tiles of 41 K-steps, N = 1352, 492 workgroups, 82 of them on one domain: 31.5 us, with two slots 26.8).  Two

@@ -482,6 +482,31 @@ def test_tiles_without_entries(groups, empty, n, kernels):
     check_c(c, c_ref, s, "tiles without entries")
 
 
+@pytest.mark.parametrize("height,col_block,tiles,n_ks,n,empty", [(16, 32, 70, 2, 264, 1), (16, 32, 300, 3, 8, 63), (32, 32, 70, 3, 2056, 64), (25, 4, 70, 2, 1032, 65), (16, 4, 70, 3, 520, 200),
+                                                                 (16, 32, 40, 20, 1800, 130), (32, 32, 300, 5, 1032, 1500), (60, 4, 40, 3, 1032, 70), (50, 32, 40, 3, 264, 70)])
+def test_rows_without_entries_beside_tiles_of_one_class(height, col_block, tiles, n_ks, n, empty):
+    # in the kernel of one and two slabs, block tiles and gathered ones, shallow rings and deep ones; of gathered tiles of four slabs; the mixed one
+    rng = np.random.default_rng(empty)
+    kb = 1024 // col_block
+    rows = []
+    for t in range(tiles):
+        cols = np.sort((rng.choice(kb, size=n_ks * 32 // col_block, replace=False)[:, None] * col_block + np.arange(col_block)).reshape(-1))
+        rows += [cols.tolist() for _ in range(height)]
+    rows += [[]] * empty
+    csr = csr_from_rows(rows, 1024, rng)
+    bits = synth.dense_rhs(rng, 1024, n, "f16")
+    rg = np.append(height * np.arange(tiles + 1), height * tiles + empty).astype(np.int32)
+    order = rng.permutation(len(rows)).astype(np.int32)
+    csr = synth.permute_rows(csr, np.argsort(order))
+    c, v = gpu_spmm(csr, order, rg, col_block, bits, ldc_pad=4)
+    slabs = {16: "1 slab", 25: "2 slabs", 32: "2 slabs", 60: "4 slabs"}.get(height)
+    kernel = "vbr_spmm_kernel<%s%s>" % (slabs, ", column-gathered" if col_block == 4 else "") if slabs else "vbr_spmm_mixed_kernel"
+    assert [(p["kernel"], p["tiles"]) for p in v.launches(n)] == [(kernel, tiles + -(-empty // 64))]
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "empty rows beside %s" % kernel)
+    assert np.all(c[order[height * tiles:]] == 0.0)
+
+
 def test_empty_rows_get_zeros_and_single_dense_block_is_a_gemm():
     rng = np.random.default_rng(7)
     csr = csr_from_rows([[], [1, 40], [], [2], []], n_cols=64, rng=rng)

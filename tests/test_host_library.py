@@ -449,3 +449,21 @@ def test_the_last_tiles_are_split_by_the_tiles_with_entries_on_a_domain(tiles, n
     q, t = n // 256, tiles + empty_tiles + 3 * split
     whole = {8: t, 2: -(-t // 4), 3: -(-t // 2), 5: 5 * -(-t // 8), 6: 3 * -(-t // 4)}[q]
     assert [(p["kernel"], p["tiles"], p["workgroups"]) for p in plan] == [("vbr_spmm_mixed_kernel", tiles + empty_tiles, 8 * whole)]
+
+
+@pytest.mark.parametrize("height,col_block,tiles,n_ks,n,empty,kernels", [
+    (16, 32, 128, 16, 4096, 2048, ["vbr_spmm_kernel<1 slab>"]), (32, 32, 128, 16, 4096, 2048, ["vbr_spmm_kernel<2 slabs>"]), (16, 32, 600, 3, 512, 1, ["vbr_spmm_kernel<1 slab>"]),
+    (16, 4, 512, 3, 1024, 900, ["vbr_spmm_kernel<1 slab, column-gathered>"]), (30, 4, 300, 3, 1024, 9000, ["vbr_spmm_kernel<2 slabs, column-gathered>"]),
+    (60, 4, 100, 3, 4096, 1700, ["vbr_spmm_kernel<4 slabs, column-gathered>"]),
+    # taller ones run as well in the mixed kernel, and those that are split run in it as they did; lists of one K-step keep their routes
+    (64, 32, 100, 3, 8192, 1700, ["vbr_spmm_mixed_kernel"]), (128, 32, 64, 3, 8192, 1100, ["vbr_spmm_mixed_kernel"]), (16, 32, 60, 16, 256, 64, ["vbr_spmm_mixed_kernel"]),
+    (16, 32, 128, 1, 4096, 1900, ["vbr_spmm_mixed_kernel"]), (16, 32, 140, 1, 4096, 2048, ["vbr_spmm_kernel<1 slab>", "vbr_spmm_zero_rows_kernel"])])
+def test_one_class_of_low_tiles_keeps_its_kernel_beside_tiles_without_entries(height, col_block, tiles, n_ks, n, empty, kernels):
+    cols = 32 * n_ks // col_block * col_block
+    full = full_csr(height * tiles, cols)
+    csr = dict(full, n_rows=full["n_rows"] + empty, row_ptr=np.concatenate([full["row_ptr"], np.full(empty, full["nnz"], dtype=np.int64)]))
+    rg = np.append(height * np.arange(tiles + 1), height * tiles + empty).astype(np.int32)
+    v = binding.vbr_build(csr, np.arange(csr["n_rows"], dtype=np.int32), rg, col_block)
+    v.audit()
+    plan = v.launches(n)
+    assert [p["kernel"] for p in plan] == kernels and sum(p["tiles"] for p in plan) == tiles + -(-empty // 64)
