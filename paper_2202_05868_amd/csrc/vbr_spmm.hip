@@ -356,9 +356,6 @@ __device__ __forceinline__ void tile_body(const Params &p, const TileDesc td, co
             issue_a(DA - NS + 1 + t, DA - NS + 1 + t);
         }
         int bslot = 0, aslot = 0;
-        // With deep rings and one slab few waves are on a CU and the fetch of the short loop's instructions shows, 32 bytes at a time: begun 16 bytes into
-        // such a piece, 1712 x 9184 in 16 x 16 blocks, N = 952 takes 18.7 us, at 0 19.3, at 4 and 8 19.8, at 12 19.1.  The other kernels take the same.
-        if constexpr (S == 1 && NS > 2) asm volatile(".p2align 5\n\t.rept 4\n\ts_nop 0\n\t.endr" ::: "memory");
         for (int ks = 0; ks < n_ks; ++ks) {
             // The last iterations issue nothing for K-steps past the end (a short tile would spend a
             // tenth of its loads there); from the first iteration whose predecessors left loads out,

@@ -7,6 +7,8 @@ bit.  Also: the library loads and exports every symbol the header declares, and 
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -467,3 +469,27 @@ def test_one_class_of_low_tiles_keeps_its_kernel_beside_tiles_without_entries(he
     v.audit()
     plan = v.launches(n)
     assert [p["kernel"] for p in plan] == kernels and sum(p["tiles"] for p in plan) == tiles + -(-empty // 64)
+
+
+def test_the_loop_of_one_slab_tiles_with_deep_rings_begins_on_a_fetch_boundary(tmp_path):
+    # of the built library's own kernels: the innermost loop around the products, 32-byte pieces
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no llvm-objdump")
+    lib = shutil.copy(binding.LIB_PATH, tmp_path)
+    subprocess.run([objdump, "--offloading", lib], cwd=tmp_path, check=True, stdout=subprocess.DEVNULL)
+    found = 0
+    for part in sorted(tmp_path.glob("*gfx950*")):
+        text = subprocess.run([objdump, "-d", str(part)], check=True, capture_output=True, text=True).stdout
+        for name, body in re.findall(r"^[0-9a-f]+ <(\S*15vbr_spmm_kernelILi[01]ELi1ELi4E\S*)>:\n((?:.+\n)+)", text, re.M):
+            code = [(int(m.group(2), 16), m.group(1), line) for line in body.splitlines() for m in [re.match(r"\s*(\S+).*// ([0-9A-F]+):", line)] if m]
+            products = [address for address, op, _ in code if "mfma" in op]
+            begins = []
+            for address, op, line in code:
+                to = re.search(r"\+0x([0-9a-f]+)>", line) if op.startswith(("s_branch", "s_cbranch")) else None
+                begin = code[0][0] + int(to.group(1), 16) if to else address + 1
+                if any(begin <= x <= address for x in products):
+                    begins.append(begin)
+            assert max(begins) % 32 == 0, (name, [x % 32 for x in begins])
+            found += 1
+    assert found == 4
