@@ -1257,31 +1257,6 @@ void make_entry_rows(const vbr_csr_t *csr, Team &team, int64_t tail, EntryRows &
     });
 }
 
-// Cache lines an entry of A costs the busiest L2 domain, rows of B beginning inside lines, as if column tiles fell on the domains whole: every one
-// that falls on the domain brings the lines its piece of a row lies in, a tile shared by several domains a part of them.  Where all rows are short
-// no two of them share much of B, and a part of B that outgrows the domain's 4 MB comes from farther away, the more of it the larger it is: 15 %
-// more for every megabyte beyond, until hardly any is left.  Found on 125 unaligned products of all kinds of matrices, B of 1000 to 32000 rows, N = 72 to
-// 3816: what the rule takes is on average 0.5 % slower than the faster of the two and 5 % at most but once; always 256 columns, and 128 only
-// for short rows and up to 16384 rows of B, was 4 %, and up to 39.  With 128 and 256 columns: 32416 rows of B, 23 entries a row, N = 312
-// 69 and 85 us; 20448, 8, N = 296 19.3 and 23.1; 18720, 6, N = 352 14.7 and 17.3; 12320, 3, N = 688 15.9 and 15.3; 5936, 875, N = 3040 351 and
-// 430; 16048, 1939, N = 3752 1662 and 1508; 5184, 137, N = 696 117 and 84; graph of 16384 nodes, N = 1672 68 and 60.
-static double entry_row_lines(int lanes, int64_t N, int64_t n_cols, bool all_short)
-{
-    const int64_t width = 8 * lanes, Q = (N + width - 1) / width;
-    auto lines_of = [&](int64_t columns) {
-        const double lines = (double)((2 * columns + 127) / 128 + 1);
-        return all_short ? lines * std::min(2.25, 1.0 + 0.15 * std::max(0.0, (double)n_cols * lines * 128e-6 - 4.0)) : lines;
-    };
-    const double full = lines_of(std::min(width, N)), last = lines_of(N - (Q - 1) * width);
-    if (Q >= kXcd) {                                                // of the first domain, the last of them maybe the narrow tile
-        const int64_t rounds = (Q + kXcd - 1) / kXcd;
-        return Q % kXcd == 1 ? (double)(rounds - 1) * full + last : (double)rounds * full;
-    }
-    double busiest = 0;
-    for (int64_t t = 0; t < Q; ++t) busiest = std::max(busiest, (t + 1 < Q ? full : last) / (double)((kXcd - t + Q - 1) / Q));
-    return busiest;
-}
-
 // Workgroups of a launch over T row tiles and Q column tiles, by either way of map_workgroup.
 static int64_t grid_size(int64_t T, int64_t Q, bool even = false)
 {
@@ -1312,52 +1287,36 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
 {
     const int64_t M = (int64_t)start.size() - 1, nnz = start[(size_t)M];
     EntryLaunch L;
-    // Lanes a row, i.e. columns a wave (8 per lane): narrow tiles keep the B that a tile touches smallest and give many waves,
-    // wide ones fetch and store B and C in longer pieces, which is what counts once they come from memory.  Measured with 64 / 128
-    // / 256 columns: 32768 x 32768, 16 entries a row, N = 256: 28.8 / 32 / 38 us; graph of 16384 nodes, N = 256: 22 / 26 / 37,
-    // N = 4096: 358 / 253 / 208, of 4096 nodes, N = 2048: 33 / 29 / 34; 224 entries a row, N = 512: 213 / 185 / 213, 388, N = 1024:
-    // 365 / 270 / 241; 32768 rows of 16 entries and none long, N = 512: 46 / 57 / 72, N = 1024: 88 / 109 / 140.
-    // 256 columns from nnz N = 2^29 and N = 1024 on, with 128 and 256 columns: graph of 16384 nodes, N = 4096, 8 edges a node (2^28.8) 99 and
-    // 117, 32 (2^30.7) 196 and 192; N = 2048, 32 (2^29.7) 91 and 96; of 8192 nodes, N = 4096, 16 (2^28.9) 62 and 73, 64 (2^30.6) 141 and 130;
-    // the crossing lies between 2^29 and 2^30, and it is one of rows with hubs: 32768 rows of 33 entries, N = 1024 (2^30) 197 and 252.
-    // Rows of B that start inside a cache line lie in one line more, which 64 columns pay twice and 128 half.  Then it is one tile where 256
-    // columns hold it (with 128 and 256: 28256 rows of B, 14 entries a row, N = 152 23.3 and 18.9 us; 22528, 13, N = 216 21.2 and 20.4), but
-    // for short rows and widths between, where two tiles stay in the L2 (15968, 11, N = 240 12.4 and 13.6); else 256 where that brings clearly
-    // fewer lines.
-    // Short rows against an aligned B of more than 256 columns: 128 of them as long as that part of B, 4 MB for 16384 rows, stays in the L2 of a domain,
-    // or each of its rows is used but a few times (with 64 and 128 columns, 2, 5 and 8 entries in 10000: 8192 rows of B, N = 384 7.1 and 6.4 us, 8.0 and
-    // 7.2, 8.3 and 7.9, N = 1024 11.8 and 10.6, 13.3 and 11.3, 14.3 and 12.4; 16384, N = 384 13.1 and 11.5, 15.1 and 14.7, 17.4 and 17.4, N = 1024 23.6
-    // and 19.8, 29.0 and 26.1, 35.1 and 33.0; 23008, N = 384 18.5 and 17.4, 23.2 and 24.8, 28.8 and 31.7, N = 1024 34.6 and 31.8, 46.8 and 49.4, 60.3 and
-    // 67.8; 32768, N = 384 26.8 and 29.8, 39.6 and 50.2).  At N = 320 five tiles of 64 columns bring a domain parts of two, three of 128 leave two domains
-    // half idle: for short rows or few rows of B the latter (16416, 8 entries a row 11.9 and 11.5; 23008, 11.5: 17.1 and 18.0; 26016, 2.6: 14.5 and 13.1,
-    // 5: 16.1 and 15.7, 8: 17.2 and 17.9; 32768, 3.3: 18.3 and 17.0, 6.6: 20.4 and 22.1, 16: 27.2 and 35.9).  At N = 512 the eight of 64 are one for every
-    // domain, and 128 columns gain little (8192: 8.0 and 7.7, 16384: 15.7 and 15.7, 18.9 and 19.2).
-    // Longer rows against an aligned B of 320 to 448 columns: 64 of them, too, of which the domains have even shares (with 64 and 128 columns: 4096 x 8192,
-    // 415 entries a row, N = 320 53 and 68 us; 1504 x 16000, 1611, N = 384 86 and 107; 5003 x 4104, 336, N = 384 62 and 68).
-    // Short rows against an unaligned B of more than 512 columns and 8192 rows, every row of it used four times and more: 128 columns, of which the domains have even
-    // shares, or 64 where B outgrows the L2 and its rows are used often (with 64, 128 and 256 columns: 9984 rows of B, 8 entries a row, N = 600 10.1,
-    // 9.3 and 10.5 us; 20000, 8, N = 520 24.7, 27.7 and 33.3; 23008, 16, N = 840 63, 76 and 85; 16384, 25, N = 1208 71, 75 and 97; 27008, 25, N = 712 104,
-    // 108 and 118; 32768, 16, N = 1800 215, 211 and 234).  On 430 such products the rule is 1 % slower than the best of the three; counting lines as
-    // below, which N = 904 to 1024, where whole tiles of 128 columns are one for every domain, still have, was 6 %.
-    const int64_t longest = M > 0 ? start[1] : 0;
-    const bool all_short = M > 0 && longest <= kEntryLongRow && nnz <= 32 * M;
-    const bool wide = N == 320 ? n_cols <= 18432 || 2 * nnz <= 11 * M : (N != 512 && n_cols <= 16384) || (N > 512 && n_cols <= 24576 && nnz <= 8 * M);
-    if (N <= 64 || (aligned && (N <= 256 || (all_short ? !wide : N < 512)))) L.lanes = 8;
-    else if (aligned) L.lanes = N >= 1024 && nnz * N >= ((int64_t)1 << 29) ? 32 : 16;
-    else if (N <= 256) L.lanes = N > 128 && (N <= 192 || !all_short || n_cols > 16384) ? 32 : 16;
-    else if (all_short && n_cols > 8192 && 2 * nnz >= 7 * n_cols && ((N > 512 && N <= 896) || N > 1024))
-        L.lanes = nnz >= 6 * M && n_cols >= 15000 && n_cols <= 31000 && 5 * nnz >= 37 * n_cols && 4 * M >= 3 * n_cols ? 8 : 16;
-    else if (!all_short && n_cols > 4096 && N > 512 && N <= 640) L.lanes = 16;    // five tiles of 128 columns in even shares: 4096 x 8192, N = 600 113 and 101 us
-    else L.lanes = 1.1 * entry_row_lines(32, N, n_cols, all_short) < entry_row_lines(16, N, n_cols, all_short) ? 32 : 16;
-    // The loads of a row follow each other, the more of them the more lanes it has.  Where the longest, much longer than the others, has more than 3/4 of
-    // what a SIMD has of all loads (1024 SIMDs, 512 columns of one entry a load), fewer lanes.  CSR multiply of graphs, without and so: 4096 nodes, 13 entries
-    // a row and 909 in the longest, N = 424 32 and 13 us, N = 1016 35 and 17, N = 2504 33 and 29; of 8192, 13 and 1520, N = 512 19 and 13, N = 600 30 and
-    // 22; of 16384, 16 edges a node, N = 200 26 and 14.  On 280 products with such rows what is chosen is 3 % slower than the best, without this 13 %
-    // (and 10 % slower than without at worst: 8192 nodes, 35 a row, N = 744 35 and 39).
-    while (longest > kEntryLongRow && longest * M > 4 * nnz && L.lanes > 8) {
+    // Columns a wave.  What counts is whether a part of B that wide stays in the 4 MB of a domain's L2 and how often its rows are used, how the column
+    // tiles fall on the domains, and where rows of B begin inside cache lines the pieces that lie in one line more: 2 lines for 64 columns, 3 for 128, 5
+    // for 256; wider ones also ask for the rows and entries of A less often.  Found on 8100 products, uniform matrices, graphs and blocks, 1000 to 33000
+    // rows of A and of B, 2 to 2000 entries a row, N = 72 to 4096; what is taken is 1.2 % slower than the best of the three on average, more than 14 %
+    // for one in fifty.  Times for 64, 128 and 256 columns in us; rows of A x of B, entries a row:
+    //  - unaligned, up to 256: one column tile (20368 x 2496, 309, N = 80: 97, 70, 108; 23728 x 23712, 15, N = 136: 17.6, 18.4, 14.9; 24112 x 24096,
+    //    134, N = 144: 94, 99, 73);
+    //  - 128 columns of B do not stay, and each of its rows is used five times and more: 64 (aligned 22968 x 22944, 19, N = 512: 32.7, 37.3, 53.4;
+    //    24272 x 24256, 98, N = 696: 165, 221, 313; unaligned 23720 x 23712, 26, N = 1760: 187, 225, 311; used 3 times: 24104 x 24096, 3, N = 2080: 98.8,
+    //    86.7, 86.6; unaligned, N = 264 to 512, the two take the same);
+    //  - aligned, up to 256, short rows: 64 (on average 5 % less than 128).  Long rows, N = 264 to 448: 64, of which the domains have even shares (20064
+    //    x 8320, 352, N = 312: 200, 242, 268; 6832 x 11584, 648, N = 480: 255, 192, 191);
+    //  - long rows, as many column tiles of 256 for every domain: 256 (graph of 8192 nodes, 33, N = 1936: 79, 66, 56; 16384, 20, N = 4016: 239, 191, 181;
+    //    nine of them, 16384, 28, N = 2272: 166, 133, 136), and unaligned where 256 stay (2072 x 2048, 278, N = 2552: 179, 143, 123);
+    //  - else 128 (27456 x 4864, 6, aligned, N = 304: 15.5, 13.1, 17.1; 23656 x 4576, 7, unaligned, N = 744: 32.0, 27.7, 35.3).
+    const int64_t longest = M > 0 ? start[1] : 0, work = nnz * N, l2 = 4 << 20, tiles64 = (N + 63) / 64, tiles256 = (N + 255) / 256;
+    const bool all_short = longest <= kEntryLongRow && nnz <= 32 * M, stays = n_cols * 256 <= l2, often = nnz >= 5 * n_cols;
+    if (N <= 64) L.lanes = 8;
+    else if (!aligned && N <= 256) L.lanes = N <= 128 ? 16 : 32;
+    else if (!stays && often && (aligned || N > 512)) L.lanes = 8;
+    else if (aligned && (all_short ? tiles64 <= 4 : tiles64 > 4 && tiles64 < 8)) L.lanes = 8;
+    else if (!all_short && ((tiles256 % kXcd == 0 && work >= (int64_t)1 << 28) || (!aligned && n_cols * 640 <= l2 && work >= (int64_t)1 << 29))) L.lanes = 32;
+    else L.lanes = 16;
+    // The loads of a row follow each other, the more of them the more lanes it has: fewer lanes where the longest row has more than half of what a
+    // SIMD has of all loads (1024 SIMDs, 512 columns of one entry a load; graph of 16384 nodes, 7 entries a row and 1610 in the longest, aligned, N =
+    // 480: 15, 23, 33 us; of 4096 nodes, 12 and 1000, N = 200: 11, 17, 35; 2816 x 2816, 210 and 261, N = 80: 10.7, 14.3, 16.8).
+    while (L.lanes > 8 && !all_short) {
         const int64_t tiles = (N + 8 * L.lanes - 1) / (8 * L.lanes);
-        const int64_t loads = longest * L.lanes / (longest > std::max<int64_t>(kEntryHugeRow, nnz * tiles / 4096) ? 256 : 64);
-        if (4 * loads * 1024 * 512 <= 3 * nnz * N) break;
+        const int64_t loads = longest <= kEntryLongRow ? longest : longest * L.lanes / (longest > std::max<int64_t>(kEntryHugeRow, nnz * tiles / 4096) ? 256 : 64);
+        if (2 * loads * 1024 * 512 <= work) break;
         L.lanes /= 2;
     }
     const int64_t Q = (N + 8 * L.lanes - 1) / (8 * L.lanes);

@@ -863,6 +863,36 @@ def test_csr_comparator_with_64_columns_a_wave_of_an_unaligned_b(n):
     check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
 
 
+@pytest.mark.parametrize("n,ldb_pad,dtype", [(200, 0, "f16"), (520, 0, "bf16"), (584, 0, "f16"), (1096, 0, "f16"), (1848, 8, "f16")])
+def test_csr_comparator_with_long_rows_in_wide_waves(n, ldb_pad, dtype):
+    # so many entries that 128 and 256 columns a wave are taken: rows for 16 and 32 lanes, for a wave and for a workgroup; rows of B inside and (N = 1848)
+    # on cache lines
+    import torch
+    rng = np.random.default_rng(n)
+    lens = ([257, 300, 512, 513, 1023, 1024, 1025, 1100, 0, 17, 256, 255] + [600] * 30) * 30
+    csr = csr_from_rows([sorted(rng.choice(2600, size=x, replace=False).tolist()) for x in lens], 2600, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, 2600, n + ldb_pad, dtype)
+    b = torch_io.bits_to_device(bits, dtype)[:, :n]
+    c = binding.CsrDev(csr).upload("cuda:0").spmm(b)
+    torch.cuda.synchronize()
+    c_ref, s = oracle.spmm(csr, np.ascontiguousarray(bits[:, :n]))
+    check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
+
+
+@pytest.mark.parametrize("n,ldb_pad", [(520, 0), (1032, 0), (512, 0), (296, 24)])
+def test_csr_comparator_with_64_columns_a_wave_of_a_long_b(n, ldb_pad):
+    # short rows that use every row of a B that does not stay in an L2 often; rows of B inside cache lines and on them
+    import torch
+    rng = np.random.default_rng(n)
+    cols = (rng.integers(0, 17000, size=(12300, 1)) + np.cumsum(rng.integers(1, 600, size=(12300, 10)), axis=1)) % 17000
+    csr = csr_from_rows([np.unique(r).tolist() for r in cols], 17000, rng)
+    bits = synth.dense_rhs(rng, 17000, n + ldb_pad, "f16")
+    c = binding.CsrDev(csr).upload("cuda:0").spmm(torch_io.bits_to_device(bits, "f16")[:, :n])
+    torch.cuda.synchronize()
+    c_ref, s = oracle.spmm(csr, np.ascontiguousarray(bits[:, :n]))
+    check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
+
+
 def test_csr_comparator_and_blocked_path_agree_on_the_graph_workload():
     import torch
     w = synth.workload("rmat", scale=0.125)
