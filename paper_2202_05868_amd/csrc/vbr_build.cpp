@@ -1293,7 +1293,7 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     // rows of A and of B, 2 to 2000 entries a row, N = 72 to 4096; what is taken is 1.2 % slower than the best of the three on average, more than 14 %
     // for one in fifty.  Times for 64, 128 and 256 columns in us; rows of A x of B, entries a row:
     //  - unaligned, up to 256: one column tile (20368 x 2496, 309, N = 80: 97, 70, 108; 23728 x 23712, 15, N = 136: 17.6, 18.4, 14.9; 24112 x 24096,
-    //    134, N = 144: 94, 99, 73);
+    //    134, N = 144: 94, 99, 73), but two for short rows where both are nearly full (15328 x 15328, 6, N = 240: 128 columns 9.8, 256 10.6);
     //  - 128 columns of B do not stay, and each of its rows is used five times and more: 64 (aligned 22968 x 22944, 19, N = 512: 32.7, 37.3, 53.4;
     //    24272 x 24256, 98, N = 696: 165, 221, 313; unaligned 23720 x 23712, 26, N = 1760: 187, 225, 311; used 3 times: 24104 x 24096, 3, N = 2080: 98.8,
     //    86.7, 86.6; unaligned, N = 264 to 512, the two take the same);
@@ -1305,7 +1305,7 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     const int64_t longest = M > 0 ? start[1] : 0, work = nnz * N, l2 = 4 << 20, tiles64 = (N + 63) / 64, tiles256 = (N + 255) / 256;
     const bool all_short = longest <= kEntryLongRow && nnz <= 32 * M, stays = n_cols * 256 <= l2, often = nnz >= 5 * n_cols;
     if (N <= 64) L.lanes = 8;
-    else if (!aligned && N <= 256) L.lanes = N <= 128 ? 16 : 32;
+    else if (!aligned && N <= 256) L.lanes = N <= 128 || (all_short && N > 192) ? 16 : 32;
     else if (!stays && often && (aligned || N > 512)) L.lanes = 8;
     else if (aligned && (all_short ? tiles64 <= 4 : tiles64 > 4 && tiles64 < 8)) L.lanes = 8;
     else if (!all_short && ((tiles256 % kXcd == 0 && work >= (int64_t)1 << 28) || (!aligned && n_cols * 640 <= l2 && work >= (int64_t)1 << 29))) L.lanes = 32;

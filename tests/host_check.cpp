@@ -244,7 +244,7 @@ void check_entry_plan()
 {
     ++g_cases;
     struct { int64_t len, n_cols, N; int lanes; } const cases[] = {
-        {5, 16384, 64, 8},    {5, 16384, 256, 8},   {5, 16384, 512, 16},   {5, 16384, 72, 16},   {5, 16384, 136, 32}, {5, 16384, 240, 32}, {5, 32768, 240, 32},
+        {5, 16384, 64, 8},    {5, 16384, 256, 8},   {5, 16384, 512, 16},   {5, 16384, 72, 16},   {5, 16384, 136, 32}, {5, 16384, 240, 16}, {5, 32768, 240, 16},
         {5, 16384, 264, 16},  {5, 32768, 296, 16},  {5, 16384, 632, 16},  {5, 32768, 680, 16},  {5, 16384, 1000, 16}, {5, 16384, 2056, 16},
         {500, 5936, 3032, 32}, {500, 16048, 3752, 16}, {500, 16384, 240, 32}, {500, 5184, 696, 32}, {500, 5184, 136, 32}};
     for (const auto &x : cases) {
@@ -270,7 +270,7 @@ void check_entry_plan()
     struct { int64_t rows, len, longest, n_cols, first_N, last_N; bool aligned; int lanes; } const widths[] = {
         {16384, 5, 5, 16384, 72, 256, true, 8},     {20000, 5, 5, 20000, 264, 320, true, 8},   {20000, 5, 5, 20000, 456, 512, true, 8},  {20000, 4, 4, 20000, 264, 1024, true, 16},
         {16384, 5, 5, 16384, 264, 320, true, 16},   {16384, 5, 5, 16384, 456, 512, true, 16},  {5003, 336, 336, 5000, 264, 448, true, 8}, {5003, 336, 336, 5000, 456, 512, true, 16},
-        {20000, 5, 5, 20000, 264, 512, false, 16},  {20000, 5, 5, 20000, 520, 1024, false, 8}, {16384, 5, 5, 16384, 520, 1024, false, 16}, {16384, 30, 30, 16384, 136, 256, false, 32},
+        {20000, 5, 5, 20000, 264, 512, false, 16},  {20000, 5, 5, 20000, 520, 1024, false, 8}, {16384, 5, 5, 16384, 520, 1024, false, 16}, {16384, 30, 30, 16384, 136, 192, false, 32}, {16384, 30, 30, 16384, 200, 256, false, 16},
         {1250, 600, 1100, 2600, 200, 256, false, 32}, {1250, 600, 1100, 2600, 520, 584, false, 16}, {1250, 600, 1100, 2600, 1096, 1160, false, 32}, {1250, 600, 1100, 2600, 1800, 2048, true, 32}};
     for (const auto &x : widths)
         for (int64_t N = x.first_N; N <= x.last_N; N += 8) {
