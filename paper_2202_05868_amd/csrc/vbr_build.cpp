@@ -61,7 +61,7 @@ constexpr int64_t kMergeMinSlabs = 64;       // fewer low slabs stay single: hei
 constexpr int64_t kShortSteps = 8, kShortMinSlabs = 512;     // these three lines: see cut_into_tiles
 constexpr int64_t kSmallSteps = 1152, kFewTiles = 96;
 constexpr int64_t kEmptyApart = 512;         // workgroups: see plan_launches
-constexpr int64_t kTwoOnACu = 512, kThreeOnACu = 768;      // workgroups that are resident with two and three on a CU
+constexpr int64_t kTwoOnACu = 512, kThreeOnACu = 768, kFourOnACu = 1024;      // workgroups that are resident with two, three and four on a CU
 constexpr int64_t kSegmentSlabs = 64;        // the cutting of the slab list into tiles is optimised over stretches of this length
 
 inline int64_t gather_cost(int64_t cols, int n_slabs, int64_t deep_steps)
@@ -1444,12 +1444,19 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         // 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
         const int64_t grid = grid_size(T, Qt);             // as if of whole column tiles
         const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= 3 * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= (grid <= kTwoOnACu / 2 ? 5 : 18));
+        // workgroups an L2 domain holds at once
+        const int64_t at_once = (few || v->class_count[3] > 0 || kind == VBR_LAUNCH_TILE_4 ? kTwoOnACu : kind == VBR_LAUNCH_TILE_MIXED || kind == VBR_LAUNCH_GATHER_4 ? kThreeOnACu
+                                                                                                                                                                  : kFourOnACu) / kXcd;
         // Six column tiles, the last of them narrow: the domains that would get most of it have little to do, and the others parts of two column tiles for
-        // little less than a whole one.  Whole and shares, 72 columns in the last: 16 x 16 blocks, 3760 x 14592 61.5 and 64.3 us; 64 x 64 blocks, 8192 x 8192 41.1
-        // and 43.5; graph of 16384 nodes 54.8 and 58.8; all 256: 60.1 and 59.0, 38.0 and 38.3, 48.5 and 49.3.  Tiles of 5 to 8 slabs, which are fewer and of
-        // many lengths, gain all the same (row groups of 16 to 128 rows 72.4 and 64.9, of 1 to 100 rows 22.9 and 21.4), and so do five and nine column tiles
-        // (80 columns in the last of five: 61.4 and 55.8, 37.7 and 36.8, 58.6 and 45.3; 24 of nine: 109 and 74, 75.7 and 63.3, 101 and 98).
-        const bool narrow_sixth = Qt == 6 && N - 5 * kTileN <= kTileN / 2 && v->class_count[3] == 0;
+        // little less than a whole one, which they only take for a round of workgroups less (a sixteenth of a round more is none).  Whole and shares, 72
+        // columns in the last, one-slab tiles of 16 x 16 blocks, 128 at once: 235 of them on a domain whole, 177 in shares 62.1 and 66.1 us; 256, 192: 45.1
+        // and 47.5; 200, 150: 42.4 and 42.8; a round less: 170, 129: 40.2 and 31.8; graph of 4096 nodes, 229, 174 (64): 26.1 and 21.7; of 16384 nodes, 64
+        // edges a node, 361, 273 (96): 98.5 and 90.6, 16 edges, 356, 267: 57.3 and 60.0; all 256 columns: 55.1 and 57.2, 41.4 and 41.4, 35.9 and 29.2,
+        // 23.9 and 19.4, 88.1 and 78.3, 51.5 and 49.4.  Tiles of 5 to 8 slabs, which are fewer and of many lengths, gain all the same (row groups of 16 to
+        // 128 rows 75.2 and 68.5, of 1 to 100 rows 23.3 and 20.1), and so do five and nine column tiles (80 columns in the last of five: 61.4 and 55.8, 37.7
+        // and 36.8, 58.6 and 45.3; 72 of nine: 106 and 81, 102.8 and 102.7, 50.3 and 41.4).
+        auto rounds = [&](bool even) { return std::max<int64_t>((grid_size(T, Qt, even) / kXcd - at_once / 16 + at_once - 1) / at_once, 1); };
+        const bool narrow_sixth = Qt == 6 && N - 5 * kTileN <= kTileN / 2 && v->class_count[3] == 0 && rounds(false) == rounds(true);
         Launch L{kind, 0, T, 0, split, few, 0, 0, !split && !narrow_sixth && even_columns(T, Qt)};
         if (kind == VBR_LAUNCH_TILE_MIXED) {
             L.whole = split ? 0 : T;
@@ -1464,7 +1471,7 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
             // count: they run behind the others and are over at once (66 tiles of 16 to 128 rows and 20 of them, N = 2048, counted and not, 10 K-steps
             // 18.1 and 15.7, 20: 26.7 and 20.8; 76 and 7: 26.9 and 23.6; 114 of up to 64 rows and 22, 10: 20.5 and 18.1).
             if (!split && Qt <= kXcd) {
-                const int64_t work = v->n_work, members = kXcd / Qt, at_once = (few || v->class_count[3] > 0 ? kTwoOnACu : kThreeOnACu) / kXcd;
+                const int64_t work = v->n_work, members = kXcd / Qt;
                 const int64_t here = L.even ? grid_size(work, Qt, true) / kXcd : (work + members - 1) / members, over = here > at_once ? here % at_once : 0;
                 const int64_t last = L.even ? (kXcd * over + Qt - 1) / Qt : over * members;
                 const TileDesc &first = v->dev_tiles[(size_t)std::max<int64_t>(work - last, 0)];

@@ -493,3 +493,11 @@ def test_the_loop_of_one_slab_tiles_with_deep_rings_begins_on_a_fetch_boundary(t
             assert max(begins) % 32 == 0, (name, [x % 32 for x in begins])
             found += 1
     assert found == 4
+
+
+@pytest.mark.parametrize("height,groups,n,domain", [(16, 170, 1352, 129), (16, 170, 1408, 129), (16, 235, 1352, 235), (16, 256, 1288, 256), (16, 235, 1416, 177), (64, 135, 1352, 102), (64, 100, 1352, 100)])
+def test_six_column_tiles_with_a_narrow_last_one_are_shared_where_that_saves_a_round(height, groups, n, domain):
+    # 128 workgroups of one-slab tiles at once on a domain, 64 of four-slab ones; up to 128 columns in the last
+    csr = full_csr(height * groups, 96)
+    v = binding.vbr_build(csr, np.arange(height * groups, dtype=np.int32), np.arange(0, height * groups + 1, height, dtype=np.int32), 32)
+    assert [p["workgroups"] for p in v.launches(n)] == [8 * domain]
