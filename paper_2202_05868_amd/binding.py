@@ -150,6 +150,7 @@ def _operands(what: str, dtype: str, n_rows: int, n_cols: int, dev_buf, b, c):
 
 
 def _check_operands(what: str, dtype: str, n_rows: int, n_cols: int, dev_buf, b, c):
+    """The checks without a multiply behind them."""
     return _operands(what, dtype, n_rows, n_cols, dev_buf, b, c)[0]
 
 

@@ -1257,17 +1257,6 @@ void make_entry_rows(const vbr_csr_t *csr, Team &team, int64_t tail, EntryRows &
     });
 }
 
-// Workgroups of a launch over T row tiles and Q column tiles, by either way of map_workgroup.
-static int64_t grid_size(int64_t T, int64_t Q, bool even = false)
-{
-    if (even) {
-        const int64_t rest = Q % kXcd, each = rest & -rest, shares = kXcd / each;
-        return kXcd * (Q / kXcd * T + rest / each * ((T + shares - 1) / shares));
-    }
-    if (Q >= kXcd) return (int64_t)kXcd * ((Q + kXcd - 1) / kXcd) * T;
-    return (int64_t)kXcd * ((T + (kXcd / Q) - 1) / (kXcd / Q));
-}
-
 // Are the column tiles cut in even shares?  Then a domain meets up to two of those left over and brings parts of B that others bring too, so the
 // busiest domain has to get clearly shorter, and a CU of it a workgroup less.  Whole tiles and shares: 16 x 16 blocks, 4096 x 8192, five column
 // tiles 40.7 and 38.4 us, nine 81.9 and 62.1, 19: 113.7 and 100.1; 64 x 64 blocks at 30 %, 8192 x 8192, five 58.9 and 53.0, nine 108.6 and 87.7, 11:

@@ -99,6 +99,17 @@ VBRK_HOST_DEVICE bool map_workgroup(uint32_t block, uint32_t T, uint32_t Q, cons
     return (uint32_t)tile < T;
 }
 
+// Workgroups of a launch over T row tiles and Q column tiles, by either way of map_workgroup.
+inline int64_t grid_size(int64_t T, int64_t Q, bool even = false)
+{
+    if (even) {
+        const int64_t rest = Q % kXcd, each = rest & -rest, shares = kXcd / each;
+        return kXcd * (Q / kXcd * T + rest / each * ((T + shares - 1) / shares));
+    }
+    if (Q >= kXcd) return (int64_t)kXcd * ((Q + kXcd - 1) / kXcd) * T;
+    return (int64_t)kXcd * ((T + (kXcd / Q) - 1) / (kXcd / Q));
+}
+
 // Number of a workgroup among those of a column tile -> the tile, and the quarter of the column tile if the tile has four workgroups (true): of the
 // tiles of a mixed launch the first `whole` have one, `rest` have four, those of the first quarter before those of the second, and the others,
 // tiles without a K-step, have one.  (Without tiles that have four, `whole` is all of them.)

@@ -190,6 +190,41 @@ void check_plan()
     }
 }
 
+// Short lists are split, whatever the grid is rounded up to: the plans of a few tiles of one height and of two.
+void check_short_lists()
+{
+    ++g_cases;
+    for (int rows : {16, 32, 64})
+        for (int n_ks : {3, 4, 5, 7, 11, 12})
+            for (int64_t N : {8, 64, 72, 256, 520}) {
+                vbr_t *v = stack(3, rows, n_ks);
+                vbrk::Launch plan[VBR_MAX_LAUNCHES];
+                REQUIRE(vbrk::plan_launches(v, N, N % 64 == 0, plan) == 1);
+                REQUIRE(plan[0].split == (n_ks < 4 ? 0 : n_ks < 12 ? vbrk::kSplitShort : vbrk::kSplitSteps));
+                REQUIRE(plan[0].grid == vbrk::grid_size(3, plan[0].split ? (N + 63) / 64 : (N + 255) / 256));
+                vbr_free(v);
+            }
+    const std::vector<int32_t> rg = {0, 64, 80, 85, 115, 118};
+    Csr a;
+    a.m = 118;
+    a.k = 160;
+    for (int64_t i = 0; i <= a.m; ++i) a.row_ptr.push_back(i * a.k);
+    for (int64_t i = 0; i < a.m * a.k; ++i) a.col.push_back((int32_t)(i % a.k));
+    a.val.assign(a.col.size(), 0x3c00);
+    std::vector<int32_t> perm;
+    for (int32_t i = 0; i < 118; ++i) perm.push_back(i);
+    const vbr_csr_t c = a.view();
+    vbr_t *v = nullptr;
+    REQUIRE(vbr_build(&c, perm.data(), rg.data(), 5, 32, &v) == VBR_OK);
+    for (int64_t N : {8, 64, 72, 256, 520}) {
+        vbrk::Launch plan[VBR_MAX_LAUNCHES];
+        REQUIRE(vbrk::plan_launches(v, N, N % 64 == 0, plan) == 1 && plan[0].kind == VBR_LAUNCH_TILE_MIXED);
+        REQUIRE(plan[0].split == vbrk::kSplitShort && plan[0].whole == 0 && plan[0].rest == plan[0].n_tiles);
+        REQUIRE(plan[0].grid == vbrk::grid_size(4 * (int64_t)plan[0].n_tiles, (N + 255) / 256));
+    }
+    vbr_free(v);
+}
+
 // Every tile meets every column tile once, whatever the way the workgroups are dealt, and cut in shares no domain has many more than an eighth.
 template <bool IN_TURN>
 void check_map()
@@ -201,6 +236,7 @@ void check_map()
                 const int rest = Q % 8, each = rest & -rest;
                 if (even && rest == 0) continue;
                 const int domain = even ? Q / 8 * T + rest / each * ((T * each + 7) / 8) : Q >= 8 ? (Q + 7) / 8 * T : (T + 8 / Q - 1) / (8 / Q);
+                REQUIRE(vbrk::grid_size(T, Q, even) == 8 * domain);
                 std::vector<int> seen((size_t)T * Q), load(8);
                 int tile = 0, ntile = 0;
                 const vbrk::ColumnMap map = vbrk::column_map(Q, even);
@@ -374,6 +410,7 @@ int main()
         ++g_cases;
     }
     check_plan();
+    check_short_lists();
     check_map<false>();
     check_map<true>();
     check_split_tile();
