@@ -863,7 +863,7 @@ def test_csr_comparator_with_64_columns_a_wave_of_an_unaligned_b(n):
     check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
 
 
-@pytest.mark.parametrize("n,ldb_pad,dtype", [(200, 0, "f16"), (520, 0, "bf16"), (584, 0, "f16"), (1096, 0, "f16"), (1848, 8, "f16")])
+@pytest.mark.parametrize("n,ldb_pad,dtype", [(200, 0, "f16"), (456, 0, "f16"), (520, 0, "bf16"), (1096, 0, "f16"), (1848, 8, "f16")])
 def test_csr_comparator_with_long_rows_in_wide_waves(n, ldb_pad, dtype):
     # so many entries that 128 and 256 columns a wave are taken: rows for 16 and 32 lanes, for a wave and for a workgroup; rows of B inside and (N = 1848)
     # on cache lines
