@@ -1282,7 +1282,8 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     // rows of A and of B, 2 to 2000 entries a row, N = 72 to 8192; what is taken is 1.3 % slower than the best of the three on average, more than 14 %
     // for one in fifty, and the same on 4100 others.  Times for 64, 128 and 256 columns in us; rows of A x of B, entries a row:
     //  - unaligned, up to 256: one column tile (20368 x 2496, 309, N = 80: 97, 70, 108; 23728 x 23712, 15, N = 136: 17.6, 18.4, 14.9; 24112 x 24096,
-    //    134, N = 144: 94, 99, 73), but two for short rows where both are nearly full (15328 x 15328, 6, N = 240: 128 columns 9.8, 256 10.6);
+    //    134, N = 144: 94, 99, 73), but two for short rows where the second is three quarters full (15328 x 15328, 6, N = 240: 128 columns 9.8, 256
+    //    10.6; 26016 x 26016, 21, N = 216: 35.0 and 32.7);
     //  - 128 columns of B do not stay, and each of its rows is used five times and more: 64 (aligned 22968 x 22944, 19, N = 512: 32.7, 37.3, 53.4;
     //    24272 x 24256, 98, N = 696: 165, 221, 313; unaligned 23720 x 23712, 26, N = 1760: 187, 225, 311), but not where the two take the same or 64
     //    take more: aligned beyond 1024 columns (24240 x 24224, 5, N = 2048: 124, 100, 98), unaligned up to 512, or used less (24104 x 24096, 3, N =
@@ -1290,9 +1291,9 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     //  - aligned, up to 256: 64 (on average 5 % less than 128 for short rows, 4 to 40 % for long ones), but for long rows from 2^27 products on, where
     //    128 take up to 10 % less.  Long rows, N = 264 to 448: 64, of which the domains have even shares (20064 x 8320, 352, N = 312: 200, 242, 268;
     //    6832 x 11584, 648, N = 480: 255, 192, 191);
-    //  - long rows, as many column tiles of 256 for every domain, and entries enough for their waves: 256 (graph of 8192 nodes, 33, N = 1936: 79, 66, 56;
-    //    16384, 20, N = 4016: 239, 191, 181; nine of them, 16384, 28, N = 2272: 166, 133, 136; 120000 entries, 16384, 7, N = 4096: 128 columns 103, 256
-    //    116);
+    //  - long rows, as many column tiles of 256 for every domain (unaligned, one fewer, too), and entries enough for their waves: 256 (graph of 8192 nodes,
+    //    33, N = 1936: 79, 66, 56; 16384, 20, N = 4016: 239, 191, 181; 4096, 45, N = 1832: 54, 49, 36; 8192, 31, N = 1640: 67, 63, 52; two fewer 4096, 23, N =
+    //    3432: 52, 48, 56; one more 16384, 28, N = 2272: 166, 133, 136; 120000 entries, aligned, 16384, 7, N = 4096: 128 columns 103, 256 116);
     //  - long rows, unaligned, none much longer than the others, of a B of which 128 columns stay: 256 take 5 to 10 % less beyond 384 columns (8560 x 6304,
     //    210, N = 648: 168, 142, 118; 2072 x 2048, 278, N = 2552: 179, 143, 123), but as much or up to 15 % more for 5, 9 and, nearly full, 6 column tiles of
     //    128 (N = 520 to 640, 1032 to 1152 and 712 to 768); with one much longer than the others they take 10 % more;
@@ -1301,21 +1302,21 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     const bool all_short = longest <= kEntryLongRow && nnz <= 32 * M, stays = n_cols * 256 <= 4 << 20, often = nnz >= 5 * n_cols;
     const bool alike = longest * M <= 4 * nnz, many = work >= (int64_t)1 << 27;
     if (N <= 64) L.lanes = 8;
-    else if (!aligned && N <= 256) L.lanes = N <= 128 || (all_short && N > 192) ? 16 : 32;
+    else if (!aligned && N <= 256) L.lanes = N <= 128 || (all_short && N >= 224) ? 16 : 32;
     else if (!stays && often && (aligned ? N <= 1024 : N > 512)) L.lanes = 8;
     else if (aligned && (tiles64 <= 4 ? all_short || !many : tiles64 < 8 && !all_short)) L.lanes = 8;
-    else if (!all_short && tiles256 % kXcd == 0 && nnz >= 3 << 16) L.lanes = 32;
+    else if (!all_short && (tiles256 % kXcd == 0 || (!aligned && tiles256 % kXcd == kXcd - 1)) && nnz >= (aligned ? 3 << 16 : 1 << 17)) L.lanes = 32;
     else if (!all_short && !aligned && alike && stays && many && N > 384 && tiles128 != 5 && tiles64 != 12 && tiles128 != 9) L.lanes = 32;
     else L.lanes = 16;
     // The loads of a row follow each other, the more of them the more lanes it has: fewer lanes where the longest row has too many of the loads of a SIMD
     // (1024 SIMDs, 512 columns of one entry a load; graph of 16384 nodes, 7 entries a row and 1610 in the longest, aligned, N = 480: 15, 23, 33 us; of
     // 4096 nodes, 12 and 1000, N = 200: 11, 17, 35; 2816 x 2816, 210 and 261, N = 80: 10.7, 14.3, 16.8).  128 and 64 columns take the same, aligned, where
-    // it has 0.4 of them; unaligned, where 64 columns bring more lines, where it has 0.6 of them, or 1.2 if the others are hardly shorter.
-    const int64_t fifths = aligned ? 2 : alike ? 6 : 3;
+    // it has 0.4 of them; unaligned, where 64 columns bring more lines, where it has half of them, or 1.2 if the others are hardly shorter.
+    const int64_t tenths = aligned ? 4 : alike ? 12 : 5;
     while (L.lanes > 8 && !all_short) {
         const int64_t tiles = (N + 8 * L.lanes - 1) / (8 * L.lanes);
         const int64_t loads = longest <= kEntryLongRow ? longest : longest * L.lanes / (longest > std::max<int64_t>(kEntryHugeRow, nnz * tiles / 4096) ? 256 : 64);
-        if (5 * loads * 1024 * 512 <= fifths * work) break;
+        if (10 * loads * 1024 * 512 <= tenths * work) break;
         L.lanes /= 2;
     }
     const int64_t Q = (N + 8 * L.lanes - 1) / (8 * L.lanes);

@@ -306,8 +306,9 @@ void check_entry_plan()
     struct { int64_t rows, len, longest, n_cols, first_N, last_N; bool aligned; int lanes; } const widths[] = {
         {16384, 5, 5, 16384, 72, 256, true, 8},     {20000, 5, 5, 20000, 264, 320, true, 8},   {20000, 5, 5, 20000, 456, 512, true, 8},  {20000, 4, 4, 20000, 264, 1024, true, 16},
         {16384, 5, 5, 16384, 264, 320, true, 16},   {16384, 5, 5, 16384, 456, 512, true, 16},  {5003, 336, 336, 5000, 264, 448, true, 8}, {5003, 336, 336, 5000, 456, 512, true, 16},
-        {20000, 5, 5, 20000, 264, 512, false, 16},  {20000, 5, 5, 20000, 520, 1024, false, 8}, {16384, 5, 5, 16384, 520, 1024, false, 16}, {16384, 30, 30, 16384, 136, 192, false, 32}, {16384, 30, 30, 16384, 200, 256, false, 16},
-        {1250, 600, 1100, 2600, 200, 256, false, 32}, {1250, 600, 1100, 2600, 520, 584, false, 16}, {1250, 600, 1100, 2600, 392, 512, false, 32}, {1250, 600, 1100, 2600, 1032, 1152, false, 16}, {1250, 600, 1100, 2600, 1160, 1280, false, 32}, {1250, 600, 1100, 2600, 1800, 2048, true, 32}};
+        {20000, 5, 5, 20000, 264, 512, false, 16},  {20000, 5, 5, 20000, 520, 1024, false, 8}, {16384, 5, 5, 16384, 520, 1024, false, 16}, {16384, 30, 30, 16384, 136, 216, false, 32}, {16384, 30, 30, 16384, 224, 256, false, 16},
+        {1250, 600, 1100, 2600, 200, 256, false, 32}, {1250, 600, 1100, 2600, 520, 584, false, 16}, {1250, 600, 1100, 2600, 392, 512, false, 32}, {1250, 600, 1100, 2600, 1032, 1152, false, 16}, {1250, 600, 1100, 2600, 1160, 1280, false, 32}, {1250, 600, 1100, 2600, 1800, 2048, true, 32},
+        {4096, 45, 1800, 4096, 1288, 1528, false, 16}, {4096, 45, 1800, 4096, 1544, 2040, false, 32}, {4096, 45, 1800, 4096, 2056, 2304, false, 16}};
     for (const auto &x : widths)
         for (int64_t N = x.first_N; N <= x.last_N; N += 8) {
             std::vector<int64_t> start = {0, x.longest};
