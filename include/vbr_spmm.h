@@ -163,8 +163,8 @@ int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C_dev, int64
  * multiplied by the tile kernel too, on whole column blocks or, where the blocks are mostly fill-in, on the columns
  * the rows of a tile touch (VBR_LAUNCH_GATHER_*).  A gathered tile with far more columns than the others is deep: four
  * workgroups per 256 columns, whose waves split its columns.  Tiles of one class (height, packing) are one launch
- * of the kernel for it, tiles of several classes one launch of the mixed kernel; tiles without an entry may have a launch
- * of their own behind it, which stores zeros (VBR_LAUNCH_ZERO_ROWS); a large matrix in whose rows the blocking found nothing to share is
+ * of the kernel for it, tiles of several classes one launch of the mixed kernel; tiles without an entry are part of it (a
+ * launch of 1- and 2-slab tiles keeps its kernel, others are mixed then) or have a launch of their own behind it, which stores zeros (VBR_LAUNCH_ZERO_ROWS); a large matrix in whose rows the blocking found nothing to share is
  * multiplied entry by entry (VBR_LAUNCH_ENTRIES, tiles = its rows): between 0 and VBR_MAX_LAUNCHES launches.  kinds / tiles /
  * workgroups (each room for VBR_MAX_LAUNCHES entries, any may be NULL) receive the kernel, the number of row tiles (a deep
  * tile counts four times) or panels, and the grid size of each launch.

@@ -36,7 +36,7 @@ constexpr int kXcd = 8;             // L2 domains; workgroup i runs on domain i 
 
 // What map_workgroup needs to know of a launch beside T and Q: the way column tiles are dealt, and for fewer than 8 of them, whole, four bits a
 // domain each: its column tile, its number among the domains of that, and how many these are.  (Every wave divided for them: entry rows of 16384 x
-// 16384, 8 entries a row, N = 8 4.2 and now 4.0 us, N = 256 9.5 and 9.3; 1024 rows in groups of 32, N = 256 4.6 and 4.5.)
+// 16384, 8 entries a row, N = 8 4.2 and now 4.0 us, N = 256 9.5 and 9.3; 1024 rows in groups of 32, N = 256 4.6 and 4.4.)
 struct ColumnMap { uint32_t even, ntile, member, members; };
 inline ColumnMap column_map(uint32_t Q, bool even)
 {
