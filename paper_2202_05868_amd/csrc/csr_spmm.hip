@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <memory>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "host_threads.h"
@@ -16,7 +17,7 @@ struct csr_dev {
     int64_t n_rows = 0, n_cols = 0, nnz = 0;
     int32_t dtype = 0;
     vbrk::EntryRows rows;
-    int64_t row_off = 0, col_off = 0, val_off = 0, total = 256;
+    int64_t entry_off = 0, total = 256;
     void *dev = nullptr;
 };
 
@@ -49,14 +50,30 @@ __device__ __forceinline__ float half_to_f32(uint32_t pair, int hi)      // the 
 template <int I>
 __device__ __forceinline__ uint32_t row_lane(uint32_t x)     // lane I of every row of 16 lanes, to the whole row
 {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x150 + I, 0xf, 0xf, false);
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x150 + I, 0xf, 0xf, true);
 }
 
 template <int U>
 __device__ __forceinline__ uint32_t row_pair(uint32_t x)     // lane 2U of every row of 16 lanes to its first eight, lane 2U + 1 to the others
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)x, 0x150 + 2 * U, 0xf, 0x3, false);
+    const int lo = __builtin_amdgcn_mov_dpp((int)x, 0x150 + 2 * U, 0xf, 0xf, true);
     return (uint32_t)__builtin_amdgcn_update_dpp(lo, (int)x, 0x150 + 2 * U + 1, 0xf, 0xc, false);
+}
+
+__device__ __forceinline__ uint32_t half_turn(uint32_t x)    // the halves of every row of 16 lanes change places
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xf, 0xf, true);
+}
+
+template <int I>
+using constant = std::integral_constant<int, I>;
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F f)               // f(0) .. f(N - 1), each a constant
+{
+    if constexpr (I < N) {
+        f(constant<I>());
+        static_for<N, I + 1>(f);
+    }
 }
 
 // What bounds it: the B rows gathered through the caches, nnz N 2 bytes, at 64 bytes per cycle and compute unit.  So
@@ -70,13 +87,17 @@ __device__ __forceinline__ uint32_t row_pair(uint32_t x)     // lane 2U of every
 // Entries past the end of a row are loads out of the buffer's range: they return zeros and cost no traffic.
 // LANES: 8, 16 or 32 (64, 128 or 256 columns a wave), chosen by plan_entry_rows.  With 8, the 16 lanes of a row take two entries
 // at a time and add their halves at the end.
-// Measured on a graph of 16384 nodes with 426 000 entries (rows of 0 to 3600), with B and C beyond the caches, N = 4096: 680 -> 208 us
-// (17 TB/s of gathered B); N = 256: 329 -> 22 us.  4096 x 16384 with 1638 entries a row, N = 4096: 3.56 -> 1.90 ms (29 TB/s).
+// Eight loads of B are in flight from a row's first entry to its last: an addition is followed by the load of the entry eight further on, whose column
+// was fetched a batch earlier, and no load stands in a branch, so that every wait is for one load and not for all.  A load of B takes the load path 17
+// cycles, a word a lane 7, two words 17 (so an entry and a row's description are one load each).  A row leaves through LDS: see there.
+// Measured on a graph of 16384 nodes with 426 000 entries (rows of 0 to 3600), with B and C beyond the caches, N = 4096: 214 us with the waits of a
+// batch for all of its loads, columns and values apart and 16 bytes of every 32 a store, now 197 (17.8 TB/s of gathered B; without B's loads 110, without the
+// stores 171); 120 products of the experiments' and the tests' matrices: 9 % less on average.
 template <int DT, bool WIDE, int LANES>
 __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryParams p)
 {
     constexpr bool kPair = LANES == 8;                               // 16 lanes own a row, two entries at a time
-    constexpr int kGroups = kPair ? 4 : 64 / LANES, kTileN = 8 * LANES;
+    constexpr int kGroups = kPair ? 4 : 64 / LANES, kLgGroups = kGroups == 4 ? 2 : 1, kTileN = 8 * LANES;
     __shared__ float partial[3][kTileN];
     const int lane = threadIdx.x & 63, g = lane / (64 / kGroups), s16 = lane & 15, chunk0 = lane % LANES;
     // workgroup -> (column tile, four waves' rows): workgroups are dealt to the 8 L2 domains round-robin
@@ -89,10 +110,11 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
     const bool huge = tile < p.n_huge, whole = !huge && wave < 4 * p.n_huge + p.n_long;
     const int parts = huge ? 4 * kGroups : whole ? kGroups : 1, part = huge ? in_wg * kGroups + g : whole ? g : 0;
     const int first = p.n_huge + p.n_long, pos = huge ? tile : whole ? wave - 3 * p.n_huge : first + (wave - 3 * p.n_huge - first) * kGroups + g;
-    const int32_t row = pos < p.n_rows ? p.rows.row[pos] : -1;
-    const int64_t from = p.rows.start[pos < p.n_rows ? pos : p.n_rows];
-    const int32_t len = (int32_t)(p.rows.start[pos < p.n_rows ? pos + 1 : p.n_rows] - from);
+    const EntryRow mine = p.rows.row[pos < p.n_rows ? pos : p.n_rows - 1];
+    const int32_t row = pos < p.n_rows ? mine.row : -1, len = pos < p.n_rows ? mine.len : 0;
+    const int64_t from = mine.start;
     const int32_t max_len = __builtin_amdgcn_readfirstlane(len);     // the first row of a wave is its longest
+    const int lg_parts = huge ? 2 + kLgGroups : whole ? kLgGroups : 0;
     const int step = 16 * parts;
     const int e0 = parts * s16 + part;                               // this lane's entry of a batch
 
@@ -114,51 +136,111 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
             return __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(off + coff), 0, 0));
         }
     };
-    auto add = [&](uint32_t a_bits, const uint4v b) {
+    // (the empty statements keep additions and loads in the order written: moved past each other they take registers that cost waves)
+    auto add = [&](uint32_t a_bits, uint4v &b) {
+        asm volatile("" : "+v"(b));
         const float a = __builtin_bit_cast(float, a_bits);
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] = __builtin_fmaf(a, half_to_f32<DT>(b[i >> 1], i & 1), acc[i]);
+        asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]), "+v"(acc[7]));
+        __builtin_amdgcn_sched_barrier(0);
     };
-    auto fetch = [&](int base, int32_t &col, uint32_t &a) {
-        col = -1;
-        a = 0;
-        if (base + e0 < len) {
-            col = p.rows.col[from + base + e0];
-            a = p.rows.val[from + base + e0];
-        }
-    };
+    // The entries of batch i, this lane's one of 16.  Behind the end of the row the last entry again, without effect: a load that every lane
+    // makes is one the waits for the loads of B can count on.
     int32_t col;
-    uint32_t abits;
-    fetch(0, col, abits);
-    for (int base = 0; base < max_len; base += step) {
-        const uint32_t off = WIDE ? (uint32_t)col : col >= 0 ? (uint32_t)col * ldb_bytes : 0xFFFFF000u;
-        const uint32_t a = __builtin_bit_cast(uint32_t, half_to_f32<DT>(abits, 0));
-        if (base + step < max_len) fetch(base + step, col, abits);
-        const int left = max_len - base;                             // entries of the longest row of the wave
-        const int rounds = (left + parts - 1) / parts;
-        uint4v b[8];
+    uint32_t val;
+    bool there;
+    auto fetch = [&](int batch) {
+        const int32_t at = batch * step + e0;
+        const int64_t i = from + (at < len ? at : len - 1);
+        const int64_t k = i > 0 ? i : 0;
+        const Entry e = p.rows.entry[k];
+        col = e.col;
+        val = e.val;
+        there = at < len;
+    };
+    uint32_t off = 0, a = 0;
+    auto take = [&]() {                                              // the fetched entries become those to load and to add
+        off = !there ? 0xFFFFF000u : WIDE ? (uint32_t)col : (uint32_t)col * ldb_bytes;
+        a = there ? __builtin_bit_cast(uint32_t, half_to_f32<DT>(val, 0)) : 0;
+    };
+    uint4v b[8];
+    auto hand = [](auto u, uint32_t x) {
+        if constexpr (kPair) return row_pair<u.value>(x);
+        else return row_lane<u.value>(x);
+    };
+    // loads of entries AT .. AT + N - 1 of `off`; additions of 8 from AT on, each followed by a load of one of `off` in its place
+    auto issue = [&](auto n, auto at) { static_for<n.value>([&](auto u) { b[u.value] = load(hand(constant<at.value + u.value>(), off)); }); };
+    auto finish = [&](auto n, auto at, uint32_t a) {
+        static_for<n.value>([&](auto u) { add(hand(constant<at.value + u.value>(), a), b[u.value]); });
+    };
+    auto go_on = [&](auto at, uint32_t a, auto n, auto next) {
+        static_for<8>([&](auto u) {
+            add(hand(constant<at.value + u.value>(), a), b[u.value]);
+            if constexpr (u.value < n.value) b[u.value] = load(hand(constant<next.value + u.value>(), off));
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    constexpr constant<0> c0;
+    constexpr constant<4> c4;
+    constexpr constant<8> c8;
+    int left = (max_len + parts - 1) >> lg_parts;                    // entries of this group of lanes, of the longest row of the wave
+    if (left > 0) {
+        fetch(0);
+        take();
+        int batch = 1;
         if constexpr (kPair) {
-#define ENTRY_LOAD(U) b[U] = load(row_pair<U>(off))
-#define ENTRY_ADD(U) add(row_pair<U>(a), b[U])
-            ENTRY_LOAD(0); ENTRY_LOAD(1); ENTRY_LOAD(2); ENTRY_LOAD(3);
-            if (rounds > 8) { ENTRY_LOAD(4); ENTRY_LOAD(5); ENTRY_LOAD(6); ENTRY_LOAD(7); }
-            ENTRY_ADD(0); ENTRY_ADD(1); ENTRY_ADD(2); ENTRY_ADD(3);
-            if (rounds > 8) { ENTRY_ADD(4); ENTRY_ADD(5); ENTRY_ADD(6); ENTRY_ADD(7); }
-#undef ENTRY_LOAD
-#undef ENTRY_ADD
+            if (left <= 8) {
+                issue(c4, c0);
+                finish(c4, c0, a);
+            } else {
+                if (left > 16) fetch(batch);
+                issue(c8, c0);
+                for (; left > 24; left -= 16) {
+                    const uint32_t now = a;
+                    take();
+                    fetch(++batch);
+                    go_on(c0, now, c8, c0);
+                }
+                if (left > 16) {
+                    const uint32_t now = a;
+                    take();
+                    go_on(c0, now, c4, c0);
+                    finish(c4, c0, a);
+                } else {
+                    finish(c8, c0, a);
+                }
+            }
+        } else if (left <= 4) {
+            issue(c4, c0);
+            finish(c4, c0, a);
         } else {
-#define ENTRY_LOAD(U, S) b[U] = load(row_lane<U + S>(off))
-#define ENTRY_ADD(U, S) add(row_lane<U + S>(a), b[U])
-            ENTRY_LOAD(0, 0); ENTRY_LOAD(1, 0); ENTRY_LOAD(2, 0); ENTRY_LOAD(3, 0);
-            if (rounds > 4) { ENTRY_LOAD(4, 0); ENTRY_LOAD(5, 0); ENTRY_LOAD(6, 0); ENTRY_LOAD(7, 0); }
-            ENTRY_ADD(0, 0); ENTRY_ADD(1, 0); ENTRY_ADD(2, 0); ENTRY_ADD(3, 0);
-            if (rounds > 8) { ENTRY_LOAD(0, 8); ENTRY_LOAD(1, 8); ENTRY_LOAD(2, 8); ENTRY_LOAD(3, 8); }
-            if (rounds > 4) { ENTRY_ADD(4, 0); ENTRY_ADD(5, 0); ENTRY_ADD(6, 0); ENTRY_ADD(7, 0); }
-            if (rounds > 12) { ENTRY_LOAD(4, 8); ENTRY_LOAD(5, 8); ENTRY_LOAD(6, 8); ENTRY_LOAD(7, 8); }
-            if (rounds > 8) { ENTRY_ADD(0, 8); ENTRY_ADD(1, 8); ENTRY_ADD(2, 8); ENTRY_ADD(3, 8); }
-            if (rounds > 12) { ENTRY_ADD(4, 8); ENTRY_ADD(5, 8); ENTRY_ADD(6, 8); ENTRY_ADD(7, 8); }
-#undef ENTRY_LOAD
-#undef ENTRY_ADD
+            issue(c8, c0);
+            for (; left > 20; left -= 16) {
+                fetch(batch++);
+                go_on(c0, a, c8, c8);
+                const uint32_t now = a;
+                take();
+                go_on(c8, now, c8, c0);
+            }
+            // 5 to 20 are left, eight of them on their way: those beyond 12, and the last four of more than eight
+            uint32_t now = a;
+            if (left > 12) {
+                if (left > 16) fetch(batch);
+                go_on(c0, now, c8, c8);
+                now = half_turn(a);
+                if (left > 16) take();
+                left -= 8;
+            } else {
+                off = half_turn(off);
+                a = half_turn(a);
+            }
+            if (left > 8) {
+                go_on(c0, now, c4, c0);
+                finish(c4, c0, a);
+            } else {
+                finish(c8, c0, now);
+            }
         }
     }
     if constexpr (kPair) {
@@ -182,16 +264,23 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] += partial[0][chunk0 * 8 + i] + partial[1][chunk0 * 8 + i] + partial[2][chunk0 * 8 + i];
     }
-    const int n = n0 + chunk0 * 8;
-    if (row >= 0 && n < p.N && (parts == 1 || g == 0)) {
-        float *c = p.C + row * p.ldc + n;
-        if constexpr (kPair) {                                       // each half of the 16 lanes stores four of the eight columns
-            const int hi = lane >> 3 & 1;
-            const float4v out = hi ? float4v{acc[4], acc[5], acc[6], acc[7]} : float4v{acc[0], acc[1], acc[2], acc[3]};
-            __builtin_nontemporal_store(out, reinterpret_cast<float4v *>(c + 4 * hi));
-        } else {
-            __builtin_nontemporal_store(float4v{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<float4v *>(c));
-            __builtin_nontemporal_store(float4v{acc[4], acc[5], acc[6], acc[7]}, reinterpret_cast<float4v *>(c + 4));
+    if constexpr (kPair) {                                           // each half of the 16 lanes stores four of the eight columns
+        const int hi = lane >> 3 & 1, n = n0 + chunk0 * 8 + 4 * hi;
+        const float4v out = hi ? float4v{acc[4], acc[5], acc[6], acc[7]} : float4v{acc[0], acc[1], acc[2], acc[3]};
+        if (row >= 0 && n < p.N && (parts == 1 || g == 0)) __builtin_nontemporal_store(out, reinterpret_cast<float4v *>(p.C + row * p.ldc + n));
+    } else {
+        // A lane holds eight columns, 32 bytes of C: stored as they are, a store takes every other 16 bytes of its lines.  Through LDS, it is 1 KiB of whole
+        // lines (16384 rows, N = 4096, only the rows' descriptions and stores: 116 and 52 us; that graph without its loads of B: 141 and 110).
+        __shared__ __attribute__((aligned(16))) float turned[4][64 * 8];
+        float *out_lds = turned[in_wg];
+        *reinterpret_cast<float4v *>(out_lds + 8 * lane) = float4v{acc[0], acc[1], acc[2], acc[3]};
+        *reinterpret_cast<float4v *>(out_lds + 8 * lane + 4) = float4v{acc[4], acc[5], acc[6], acc[7]};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int from_lane = 32 * i + (lane >> 1), n = n0 + 4 * (lane + 64 * i) % kTileN;
+            const float4v out = *reinterpret_cast<const float4v *>(out_lds + 4 * (lane + 64 * i));
+            const int32_t r = __shfl(row, from_lane);
+            if (r >= 0 && n < p.N && (parts == 1 || from_lane < LANES)) __builtin_nontemporal_store(out, reinterpret_cast<float4v *>(p.C + r * p.ldc + n));
         }
     }
 }
@@ -215,7 +304,8 @@ int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &r
     p.b_bytes = wide ? 0 : (uint32_t)b_bytes;
     p.n_rows = (int32_t)n_rows;
     p.N = (int32_t)N;
-    p.n_ntiles = (int32_t)((N + 8 * L.lanes - 1) / (8 * L.lanes));
+    const int width = 8 * L.lanes;
+    p.n_ntiles = (int32_t)((N + width - 1) / width);
     p.map = column_map((uint32_t)p.n_ntiles, L.even);
     p.n_huge = L.n_huge;
     p.n_long = L.n_long;
@@ -248,11 +338,9 @@ extern "C" int csr_spmm_create(const vbr_csr_t *csr, csr_dev_t **out)
         h->nnz = csr->nnz;
         h->dtype = csr->dtype;
         vbrk::Team team(vbrk::threads_for(csr->nnz, 1 << 18));
-        vbrk::make_entry_rows(csr, team, 0, h->rows);
-        h->row_off = vbrk::align_up256((csr->n_rows + 1) * 8);
-        h->col_off = vbrk::align_up256(h->row_off + csr->n_rows * 4);
-        h->val_off = vbrk::align_up256(h->col_off + csr->nnz * 4);
-        h->total = vbrk::align_up256(h->val_off + csr->nnz * 2 + 256);
+        vbrk::make_entry_rows(csr, team, h->rows);
+        h->entry_off = vbrk::align_up256(csr->n_rows * (int64_t)sizeof(vbrk::EntryRow));
+        h->total = vbrk::align_up256(h->entry_off + (int64_t)h->rows.bytes());
         *out = h.release();
         return VBR_OK;
     } catch (const std::bad_alloc &) {
@@ -270,11 +358,9 @@ extern "C" int csr_upload(csr_dev_t *h, void *buf_dev, void *hip_stream)
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     char *d = static_cast<char *>(buf_dev);
     struct Part { int64_t off; const void *src; size_t bytes; };
-    const Part parts[4] = {
-        {0, h->rows.start.data(), h->rows.start.size() * 8},
-        {h->row_off, h->rows.row.data(), h->rows.row.size() * 4},
-        {h->col_off, h->rows.col.data(), h->rows.col.size() * 4},
-        {h->val_off, h->rows.val.data(), h->rows.val.size() * 2},
+    const Part parts[2] = {
+        {0, h->rows.row.data(), h->rows.row.size() * sizeof(vbrk::EntryRow)},
+        {h->entry_off, h->rows.entry.get(), h->rows.bytes()},
     };
     for (const Part &pt : parts) {
         if (pt.bytes == 0) continue;
@@ -297,8 +383,7 @@ extern "C" int csr_spmm(const csr_dev_t *h, const void *B_dev, int64_t ldb, floa
     if (!B_dev || !C_dev || ldb < N || ldc < N || ldb % 8 != 0 || ldc % 4 != 0) return VBR_EINVAL;
     if ((reinterpret_cast<uintptr_t>(B_dev) & 15) != 0 || (reinterpret_cast<uintptr_t>(C_dev) & 15) != 0) return VBR_EINVAL;
     const char *d = static_cast<const char *>(h->dev);
-    const vbrk::EntryRowsDev rows{reinterpret_cast<const int64_t *>(d), reinterpret_cast<const int32_t *>(d + h->row_off),
-                                  reinterpret_cast<const int32_t *>(d + h->col_off), reinterpret_cast<const uint16_t *>(d + h->val_off)};
+    const vbrk::EntryRowsDev rows{reinterpret_cast<const vbrk::EntryRow *>(d), reinterpret_cast<const vbrk::Entry *>(d + h->entry_off)};
     const vbrk::EntryLaunch L = vbrk::plan_entry_rows(h->rows.start, h->n_cols, N, ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0);
     return vbrk::launch_entry_rows(L, h->dtype, rows, h->n_rows, h->n_cols, B_dev, ldb, C_dev, ldc, N, hip_stream);
 }

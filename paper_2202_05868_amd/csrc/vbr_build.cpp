@@ -379,11 +379,11 @@ bool Builder::entries_cost_less()
 void Builder::keep_entries()
 {
     v->by_entries = true;
-    make_entry_rows(csr, team, kFragElems, v->entries);
+    make_entry_rows(csr, team, v->entries);
     v->ks_ptr.assign((size_t)G + 1, 0);
     v->group_first_tile.assign((size_t)G + 1, 0);
     std::vector<int32_t> pos((size_t)M);
-    for (int64_t i = 0; i < M; ++i) pos[(size_t)v->entries.row[(size_t)i]] = (int32_t)i;
+    for (int64_t i = 0; i < M; ++i) pos[(size_t)v->entries.row[(size_t)i].row] = (int32_t)i;
     v->row_pos.resize((size_t)M);
     for (int64_t q = 0; q < M; ++q) v->row_pos[(size_t)q] = pos[(size_t)perm[q]];
 }
@@ -996,10 +996,9 @@ void Builder::lay_out()
     L.panels_off = align_up(L.perm_off + M * 4, 256);
     L.pk_meta_off = align_up(L.panels_off + (int64_t)v->panels.size() * (int64_t)sizeof(PanelDesc), 256);
     L.prow_off = align_up(L.pk_meta_off + (int64_t)v->pk_meta.size() * 4, 256);
-    L.gcol_off = align_up(L.prow_off + (int64_t)(v->by_entries ? v->entries.row : v->prow).size() * 4, 256);
-    L.start_off = align_up(L.gcol_off + (int64_t)(v->by_entries ? v->entries.col : v->gcol).size() * 4, 256);
-    L.vals_off = align_up(L.start_off + (int64_t)v->entries.start.size() * 8, 256);
-    L.total = std::max<int64_t>(256, align_up(L.vals_off + (int64_t)(v->by_entries ? v->entries.val : v->vals).size() * 2, 256));
+    L.gcol_off = align_up(L.prow_off + (int64_t)(v->by_entries ? v->entries.row.size() * sizeof(EntryRow) : v->prow.size() * 4), 256);
+    L.vals_off = align_up(L.gcol_off + (int64_t)(v->by_entries ? v->entries.bytes() : v->gcol.size() * 4), 256);
+    L.total = std::max<int64_t>(256, align_up(L.vals_off + (int64_t)v->vals.size() * 2, 256));
 }
 
 }  // namespace
@@ -1064,11 +1063,11 @@ extern "C" int vbr_unpack_block(const vbr_t *v, int64_t blk, void *dst_)
     if (v->by_entries) {
         for (int64_t i = 0; i < v->row_groups[g + 1] - v->row_groups[g]; ++i) {
             const int64_t e = v->row_pos[(size_t)(v->row_groups[g] + i)];
-            const int32_t *b = v->entries.col.data() + v->entries.start[(size_t)e], *end = v->entries.col.data() + v->entries.start[(size_t)e + 1];
+            const Entry *b = v->entries.entry.get() + v->entries.start[(size_t)e], *end = v->entries.entry.get() + v->entries.start[(size_t)e + 1];
             for (int64_t c = 0; c < cb; ++c) {
                 const int32_t col = (int32_t)((int64_t)v->blk_col[blk] * cb + c);
-                const int32_t *it = std::lower_bound(b, end, col);
-                dst[i * cb + c] = it != end && *it == col ? v->entries.val[(size_t)(it - v->entries.col.data())] : 0;
+                const Entry *it = std::lower_bound(b, end, col, [](const Entry &x, int32_t c) { return x.col < c; });
+                dst[i * cb + c] = it != end && it->col == col ? (uint16_t)it->val : 0;
             }
         }
         return VBR_OK;
@@ -1139,9 +1138,9 @@ extern "C" int vbr_audit(const vbr_t *v)
     if (!v) return VBR_EINVAL;
     const int64_t M = v->n_rows, K = v->n_cols;
     const int gran = 1 << v->lg_gran, per_step = kStepK >> v->lg_gran;
-    const HostValues &values = v->by_entries ? v->entries.val : v->vals;
+    const HostValues &values = v->vals;
     const int64_t n_vals = (int64_t)values.size();
-    if (n_vals < kFragElems || (int64_t)v->perm.size() != M) return VBR_EINVAL;
+    if ((!v->by_entries && n_vals < kFragElems) || (int64_t)v->perm.size() != M) return VBR_EINVAL;
     for (int64_t i = 0; i < M; ++i)
         if (v->perm[i] < 0 || v->perm[i] >= M) return VBR_EINVAL;
     for (const int32_t e : v->krow)
@@ -1202,35 +1201,36 @@ extern "C" int vbr_audit(const vbr_t *v)
     if (v->by_entries) {
         const EntryRows &e = v->entries;
         if (!v->dev_tiles.empty() || !v->panels.empty() || (int64_t)e.start.size() != M + 1 || (int64_t)e.row.size() != M) return VBR_EINVAL;
-        if (e.start[0] != 0 || e.start[(size_t)M] != (int64_t)e.col.size() || (int64_t)e.col.size() + kFragElems != n_vals) return VBR_EINVAL;
+        if (n_vals != 0 || !e.entry || e.start[0] != 0 || e.start[(size_t)M] != e.count) return VBR_EINVAL;
         for (int64_t i = 0; i < M; ++i) {
-            if (e.row[(size_t)i] < 0 || e.row[(size_t)i] >= M || e.start[(size_t)i + 1] < e.start[(size_t)i]) return VBR_EINVAL;
+            const EntryRow &r = e.row[(size_t)i];
+            if (r.row < 0 || r.row >= M || r.len < 0 || r.start != e.start[(size_t)i] || r.start + r.len != e.start[(size_t)i + 1]) return VBR_EINVAL;
             if (i > 0 && e.start[(size_t)i + 1] - e.start[(size_t)i] > e.start[(size_t)i] - e.start[(size_t)i - 1]) return VBR_EINVAL;
         }
-        for (const int32_t c : e.col)
-            if (c < 0 || c >= K) return VBR_EINVAL;
+        for (int64_t i = 0; i < e.count; ++i)
+            if (e.entry[(size_t)i].col < 0 || e.entry[(size_t)i].col >= K) return VBR_EINVAL;
     }
-    for (size_t i = (size_t)n_vals - kFragElems; i < (size_t)n_vals; ++i)
+    for (size_t i = v->by_entries ? 0 : (size_t)n_vals - kFragElems; i < (size_t)n_vals; ++i)
         if (values[i] != 0) return VBR_EINVAL;                                               // the zero fragment
     const DeviceLayout &L = v->lay;
-    const int64_t ends[10] = {L.zeros_off + 256, L.tiles_off + (int64_t)v->dev_tiles.size() * (int64_t)sizeof(TileDesc),
+    const int64_t ends[9] = {L.zeros_off + 256, L.tiles_off + (int64_t)v->dev_tiles.size() * (int64_t)sizeof(TileDesc),
                               L.krow_off + (int64_t)v->krow.size() * 4, L.perm_off + M * 4,
                               L.panels_off + (int64_t)v->panels.size() * (int64_t)sizeof(PanelDesc),
-                              L.pk_meta_off + (int64_t)v->pk_meta.size() * 4, L.prow_off + (int64_t)(v->by_entries ? v->entries.row : v->prow).size() * 4,
-                              L.gcol_off + (int64_t)(v->by_entries ? v->entries.col : v->gcol).size() * 4,
-                              L.start_off + (int64_t)v->entries.start.size() * 8, L.vals_off + n_vals * 2};
-    const int64_t begins[10] = {L.zeros_off, L.tiles_off, L.krow_off, L.perm_off, L.panels_off, L.pk_meta_off, L.prow_off,
-                                L.gcol_off, L.start_off, L.vals_off};
-    for (int i = 0; i < 10; ++i) {
+                              L.pk_meta_off + (int64_t)v->pk_meta.size() * 4, L.prow_off + (int64_t)(v->by_entries ? v->entries.row.size() * sizeof(EntryRow) : v->prow.size() * 4),
+                              L.gcol_off + (int64_t)(v->by_entries ? v->entries.bytes() : v->gcol.size() * 4),
+                              L.vals_off + n_vals * 2};
+    const int64_t begins[9] = {L.zeros_off, L.tiles_off, L.krow_off, L.perm_off, L.panels_off, L.pk_meta_off, L.prow_off,
+                                L.gcol_off, L.vals_off};
+    for (int i = 0; i < 9; ++i) {
         if (begins[i] % 256 != 0 || ends[i] > L.total) return VBR_EINVAL;
-        if (i + 1 < 10 && ends[i] > begins[i + 1]) return VBR_EINVAL;                         // sections in this order, disjoint
+        if (i + 1 < 9 && ends[i] > begins[i + 1]) return VBR_EINVAL;                         // sections in this order, disjoint
     }
     return VBR_OK;
 }
 
 namespace vbrk {
 
-void make_entry_rows(const vbr_csr_t *csr, Team &team, int64_t tail, EntryRows &out)
+void make_entry_rows(const vbr_csr_t *csr, Team &team, EntryRows &out)
 {
     const int64_t M = csr->n_rows;
     // by falling length, by counting (a row has at most n_cols entries)
@@ -1240,19 +1240,24 @@ void make_entry_rows(const vbr_csr_t *csr, Team &team, int64_t tail, EntryRows &
     for (int64_t i = 0; i < M; ++i) ++at[(size_t)(longest - (csr->row_ptr[i + 1] - csr->row_ptr[i])) + 1];
     for (int64_t k = 0; k <= longest; ++k) at[(size_t)k + 1] += at[(size_t)k];
     out.row.resize((size_t)M);
-    for (int64_t i = 0; i < M; ++i) out.row[(size_t)at[(size_t)(longest - (csr->row_ptr[i + 1] - csr->row_ptr[i]))]++] = (int32_t)i;
+    for (int64_t i = 0; i < M; ++i) out.row[(size_t)at[(size_t)(longest - (csr->row_ptr[i + 1] - csr->row_ptr[i]))]++].row = (int32_t)i;
     out.start.resize((size_t)M + 1);
     out.start[0] = 0;
-    for (int64_t k = 0; k < M; ++k) out.start[(size_t)k + 1] = out.start[(size_t)k] + csr->row_ptr[out.row[(size_t)k] + 1] - csr->row_ptr[out.row[(size_t)k]];
-    out.col.resize((size_t)csr->nnz);
-    out.val.allocate((size_t)(csr->nnz + tail));
-    std::fill(out.val.data() + csr->nnz, out.val.data() + csr->nnz + tail, (uint16_t)0);
+    for (int64_t k = 0; k < M; ++k) {
+        EntryRow &r = out.row[(size_t)k];
+        r.start = out.start[(size_t)k];
+        r.len = (int32_t)(csr->row_ptr[r.row + 1] - csr->row_ptr[r.row]);
+        out.start[(size_t)k + 1] = r.start + r.len;
+    }
+    out.count = csr->nnz;
+    out.entry.reset(new Entry[(size_t)(csr->nnz + kEntryPad)]);
+    std::fill(out.entry.get() + csr->nnz, out.entry.get() + csr->nnz + kEntryPad, Entry{0, 0});
     const uint16_t *v = static_cast<const uint16_t *>(csr->vals);
     team.each(M, 256, [&](int64_t b, int64_t e) {
         for (int64_t k = b; k < e; ++k) {
-            const int64_t p0 = csr->row_ptr[out.row[(size_t)k]], n = out.start[(size_t)k + 1] - out.start[(size_t)k];
-            std::copy(csr->col_idx + p0, csr->col_idx + p0 + n, out.col.data() + out.start[(size_t)k]);
-            std::copy(v + p0, v + p0 + n, out.val.data() + out.start[(size_t)k]);
+            const int64_t p0 = csr->row_ptr[out.row[(size_t)k].row], n = out.start[(size_t)k + 1] - out.start[(size_t)k];
+            Entry *to = out.entry.get() + out.start[(size_t)k];
+            for (int64_t i = 0; i < n; ++i) to[i] = Entry{csr->col_idx[p0 + i], v[p0 + i]};
         }
     });
 }
@@ -1319,7 +1324,7 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
         if (10 * loads * 1024 * 512 <= tenths * work) break;
         L.lanes /= 2;
     }
-    const int64_t Q = (N + 8 * L.lanes - 1) / (8 * L.lanes);
+    const int64_t width = 8 * L.lanes, Q = (N + width - 1) / width;
     // A workgroup for a row costs its barrier and the fourfold sum; it pays where one wave would still be at the row when
     // the rest is done, i.e. beyond the share of all entries that one of 4096 waves takes (graph, N = 256: 66 -> 26 us;
     // a matrix whose rows all have 1638 entries is 20 % slower with it and stays without).
@@ -1512,7 +1517,7 @@ extern "C" int vbr_get_schedule(const vbr_t *v, int64_t *n_tiles, int64_t *n_kst
     if (!v) return VBR_EINVAL;
     if (n_tiles) *n_tiles = v->by_entries ? v->n_rows : (int64_t)v->tiles.size() + (int64_t)v->panels.size() + (int64_t)v->gtiles.size();
     if (n_ksteps) *n_ksteps = v->ks_ptr.back() + (int64_t)v->pk_mask.size() + (int64_t)v->gcol.size() / vbrk::kStepK;
-    if (packed_elems) *packed_elems = (int64_t)(v->by_entries ? v->entries.val : v->vals).size();
+    if (packed_elems) *packed_elems = v->by_entries ? v->entries.count + vbrk::kFragElems : (int64_t)v->vals.size();
     return VBR_OK;
 }
 

@@ -22,14 +22,13 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
 constexpr int kEntryLongRow = 256;     // entries beyond which a row gets a wave of its own ...
 constexpr int kEntryHugeRow = 1024;    // ... and a workgroup of its own
 
-// The rows of a matrix as lists of entries, and `tail` zeros behind the last value.
-void make_entry_rows(const vbr_csr_t *csr, Team &team, int64_t tail, EntryRows &out);
+// The rows of a matrix as lists of entries.
+void make_entry_rows(const vbr_csr_t *csr, Team &team, EntryRows &out);
 
 // The same on the device.
 struct EntryRowsDev {
-    const int64_t *start;
-    const int32_t *row, *col;
-    const uint16_t *val;
+    const EntryRow *row;
+    const Entry *entry;
 };
 struct EntryLaunch { int32_t lanes, n_huge, n_long; int64_t waves, grid; bool even; };
 // the launch for dense width N; aligned: rows of B begin on a cache line

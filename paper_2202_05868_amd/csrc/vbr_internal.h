@@ -185,8 +185,7 @@ constexpr int kPanelMetaPad = 12;    // records appended to a panel's K-step str
 struct DeviceLayout {
     int64_t zeros_off = 0, tiles_off = 0, krow_off = 0, perm_off = 0, vals_off = 0, total = 0;
     int64_t panels_off = 0, pk_meta_off = 0, prow_off = 0;
-    int64_t gcol_off = 0;      // by_entries: the columns of the entries; prow their rows, vals their values
-    int64_t start_off = 0;
+    int64_t gcol_off = 0;      // by_entries: the entries; prow their rows
 };
 
 // The packed values on the host: not cleared when allocated, every tile writes its own part.
@@ -203,13 +202,28 @@ private:
     size_t n_ = 0;
 };
 
+// An entry: its column and the 16 bits of its value in one word each, so that one load brings both.
+struct Entry {
+    int32_t col;
+    uint32_t val;
+};
+constexpr int kEntryPad = 8;         // entries of zeros behind the last one: eight are read at a time
+
+// A row of entries: the first of them, how many, and its row of C; 16 bytes, which one load brings.
+struct EntryRow {
+    int64_t start;
+    int32_t len, row;
+};
+static_assert(sizeof(Entry) == 8 && sizeof(EntryRow) == 16, "read by the kernels as 8 and 16 bytes");
+
 // Rows of a matrix as lists of entries, the longest row first (csr_spmm.hip multiplies them): positions 0 .. rows-1,
-// the entries of a position at start[pos] .. start[pos + 1] of col and val.
+// the entries of a position at start[pos] .. start[pos + 1].
 struct EntryRows {
-    std::vector<int64_t> start;
-    std::vector<int32_t> row;        // C row of every position
-    std::vector<int32_t> col;
-    HostValues val;
+    std::vector<int64_t> start;      // [rows + 1]
+    std::vector<EntryRow> row;       // what the device knows of every position
+    std::unique_ptr<Entry[]> entry;  // and kEntryPad behind them
+    int64_t count = 0;               // of them, without these
+    size_t bytes() const { return entry ? (size_t)(count + kEntryPad) * sizeof(Entry) : 0; }
 };
 
 }  // namespace vbrk
@@ -258,7 +272,7 @@ struct vbr {
     std::vector<int32_t> p_union;        // host only: ascending union of the column blocks of each panel
     // A matrix whose blocking found next to nothing to share is kept as entries only: no tiles, no panels, no values above.
     bool by_entries = false;
-    vbrk::EntryRows entries;             // behind the last value 1 KiB of zeros, like `vals`
+    vbrk::EntryRows entries;
     vbrk::DeviceLayout lay;
     void *dev = nullptr;                 // uploaded buffer (caller-owned)
 };

@@ -991,19 +991,18 @@ extern "C" int vbr_upload(vbr_t *v, void *buf_dev, void *hip_stream)
     const vbrk::DeviceLayout &L = v->lay;
     struct Part { int64_t off; const void *src; size_t bytes; };
     static const unsigned char kZeros[256] = {0};
-    const vbrk::HostValues &values = v->by_entries ? v->entries.val : v->vals;
-    const std::vector<int32_t> &rows = v->by_entries ? v->entries.row : v->prow, &cols = v->by_entries ? v->entries.col : v->gcol;
-    const Part parts[10] = {
-        {L.gcol_off, cols.data(), cols.size() * 4},
-        {L.start_off, v->entries.start.data(), v->entries.start.size() * 8},
+    const Part rows = v->by_entries ? Part{L.prow_off, v->entries.row.data(), v->entries.row.size() * sizeof(vbrk::EntryRow)} : Part{L.prow_off, v->prow.data(), v->prow.size() * 4};
+    const Part cols = v->by_entries ? Part{L.gcol_off, v->entries.entry.get(), v->entries.bytes()} : Part{L.gcol_off, v->gcol.data(), v->gcol.size() * 4};
+    const Part parts[9] = {
+        cols,
         {L.panels_off, v->panels.data(), v->panels.size() * sizeof(vbrk::PanelDesc)},
         {L.pk_meta_off, v->pk_meta.data(), v->pk_meta.size() * 4},
-        {L.prow_off, rows.data(), rows.size() * 4},
+        rows,
         {L.zeros_off, kZeros, sizeof(kZeros)},
         {L.tiles_off, v->dev_tiles.data(), v->dev_tiles.size() * sizeof(vbrk::TileDesc)},
         {L.krow_off, v->krow.data(), v->krow.size() * 4},
         {L.perm_off, v->perm.data(), v->perm.size() * 4},
-        {L.vals_off, values.data(), values.size() * 2},
+        {L.vals_off, v->vals.data(), v->vals.size() * 2},
     };
     for (const Part &pt : parts) {
         if (pt.bytes == 0) continue;
@@ -1028,8 +1027,7 @@ extern "C" int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C
     if ((reinterpret_cast<uintptr_t>(B_dev) & 15) != 0 || (reinterpret_cast<uintptr_t>(C_dev) & 15) != 0) return VBR_EINVAL;
     const char *d = static_cast<const char *>(v->dev);
     if (v->by_entries) {
-        const vbrk::EntryRowsDev rows{reinterpret_cast<const int64_t *>(d + v->lay.start_off), reinterpret_cast<const int32_t *>(d + v->lay.prow_off),
-                                      reinterpret_cast<const int32_t *>(d + v->lay.gcol_off), reinterpret_cast<const uint16_t *>(d + v->lay.vals_off)};
+        const vbrk::EntryRowsDev rows{reinterpret_cast<const vbrk::EntryRow *>(d + v->lay.prow_off), reinterpret_cast<const vbrk::Entry *>(d + v->lay.gcol_off)};
         const vbrk::EntryLaunch L = vbrk::plan_entry_rows(v->entries.start, v->n_cols, N, ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0);
         return vbrk::launch_entry_rows(L, v->dtype, rows, v->n_rows, v->n_cols, B_dev, ldb, C_dev, ldc, N, hip_stream);
     }

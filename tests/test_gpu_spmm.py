@@ -834,6 +834,30 @@ def test_csr_comparator_at_the_row_lengths_where_it_splits(n, ldb_pad, dtype):
     check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
 
 
+@pytest.mark.parametrize("n,ldb_pad,dtype", [(64, 0, "bf16"), (128, 0, "f16"), (200, 8, "bf16"), (256, 8, "f16")])
+def test_csr_comparator_at_every_length_of_a_rows_end(n, ldb_pad, dtype):
+    # four rows of every length, so that a wave has them alone: each way the loads in flight end, of rows for 16 and 32 lanes, and of the
+    # shares of rows for a wave and for a workgroup; infinities in the rows of B that only the longest rows have
+    import torch
+    rng = np.random.default_rng(n)
+    k = 1500
+    lens = np.repeat(list(range(46)) + list(range(257, 330, 8)), 4).tolist() + list(range(1025, 1170, 16))
+    csr = csr_from_rows([list(range(x)) for x in rng.permutation(lens)], k, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, k, n + ldb_pad, dtype)
+    b = torch_io.bits_to_device(bits, dtype)[:, :n]
+    m = binding.CsrDev(csr).upload("cuda:0")
+    c = m.spmm(b)
+    torch.cuda.synchronize()
+    c_ref, s = oracle.spmm(csr, np.ascontiguousarray(bits[:, :n]))
+    check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
+    first = 20
+    b[first:] = float("inf")
+    short = np.diff(csr["row_ptr"]) <= first
+    again = m.spmm(b)
+    torch.cuda.synchronize()
+    assert torch.equal(again.cpu()[short], c.cpu()[short]) and not torch.isfinite(again.cpu()[~short]).any()
+
+
 @pytest.mark.parametrize("n,ldb_pad,dtype", [(520, 0, "f16"), (576, 0, "bf16"), (776, 8, "f16"), (1096, 0, "bf16")])
 def test_csr_comparator_with_many_long_rows(n, ldb_pad, dtype):
     # rows for a wave and for a workgroup with 128 and 256 columns a wave: none is much longer than the others
