@@ -7,10 +7,10 @@
 #include <cstdint>
 #include <memory>
 #include <new>
-#include <type_traits>
 #include <vector>
 
 #include "host_threads.h"
+#include "vbr_device.h"
 #include "vbr_host.h"
 
 struct csr_dev {
@@ -47,12 +47,6 @@ __device__ __forceinline__ float half_to_f32(uint32_t pair, int hi)      // the 
     else return __builtin_bit_cast(float, hi ? pair & 0xFFFF0000u : pair << 16);
 }
 
-template <int I>
-__device__ __forceinline__ uint32_t row_lane(uint32_t x)     // lane I of every row of 16 lanes, to the whole row
-{
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x150 + I, 0xf, 0xf, true);
-}
-
 template <int U>
 __device__ __forceinline__ uint32_t row_pair(uint32_t x)     // lane 2U of every row of 16 lanes to its first eight, lane 2U + 1 to the others
 {
@@ -63,17 +57,6 @@ __device__ __forceinline__ uint32_t row_pair(uint32_t x)     // lane 2U of every
 __device__ __forceinline__ uint32_t half_turn(uint32_t x)    // the halves of every row of 16 lanes change places
 {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xf, 0xf, true);
-}
-
-template <int I>
-using constant = std::integral_constant<int, I>;
-template <int N, int I = 0, class F>
-__device__ __forceinline__ void static_for(F f)               // f(0) .. f(N - 1), each a constant
-{
-    if constexpr (I < N) {
-        f(constant<I>());
-        static_for<N, I + 1>(f);
-    }
 }
 
 // What bounds it: the B rows gathered through the caches, nnz N 2 bytes, at 64 bytes per cycle and compute unit.  So
@@ -298,9 +281,8 @@ int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &r
     p.C = C_dev;
     p.ldb = ldb;
     p.ldc = ldc;
-    // B within 4 GiB (less a page for the offset that stands for "no entry"): 32-bit offsets from its first element
-    const int64_t b_bytes = n_cols > 0 ? ((n_cols - 1) * ldb + N) * 2 : 0;
-    const bool wide = b_bytes > 0xFFFFF000ll;
+    const int64_t b_bytes = b_bytes_of(n_cols, ldb, N);              // 32-bit offsets from its first element, if they reach
+    const bool wide = b_bytes > kNearBytes;
     p.b_bytes = wide ? 0 : (uint32_t)b_bytes;
     p.n_rows = (int32_t)n_rows;
     p.N = (int32_t)N;

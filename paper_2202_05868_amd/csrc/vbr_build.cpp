@@ -1148,6 +1148,7 @@ extern "C" int vbr_audit(const vbr_t *v)
     if (v->lg_gran < 3 && !v->krow.empty()) return VBR_EINVAL;      // the kernel takes whole groups of 8 rows
     if ((int64_t)v->krow.size() % per_step != 0) return VBR_EINVAL;
     const int64_t total_ks = (int64_t)v->krow.size() / per_step;
+    if (v->lay.krow_off + ((int64_t)v->krow.size() + kWideAhead * per_step) * 4 > v->lay.total) return VBR_EINVAL;
     if (v->n_work < 0 || v->n_work > (int32_t)v->dev_tiles.size()) return VBR_EINVAL;
     int32_t count[kClasses] = {0};
     for (size_t i = 0; i < v->dev_tiles.size(); ++i) {
@@ -1277,6 +1278,27 @@ static bool even_columns(int64_t T, int64_t Q)
     return 8 * whole >= 9 * shares && (whole + cus - 1) / cus > (shares + cus - 1) / cus;
 }
 
+// Are T tiles of 3 to 4 slabs for the wide kernel?  Two of its workgroups are resident on a CU, as of the tile kernel's, 64 on an L2 domain; 64 of them take
+// 100 where 64 of the tile kernel, with half the columns, take 62, so it is ahead where both come in full rounds; but up to 32, one on a CU, take 77 and
+// 50, and a launch of a single round gains less.  So the rounds of the busiest domain are counted.  8192 x 8192, blocks of 64 x 64, 132 K-steps, tile and
+// wide kernel: N = 512 51.8 and 64.6 us, 1024 68 and 79, 1536 109 and 99, 2048 128 and 115, 3072 189 and 184, 4096 247 and 201, 6144 378 and 307, 8192 487
+// and 396; 42 K-steps: 1024 24.3 and 28.0, 2048 42.0 and 40.5, 4096 86 and 81, 8192 184 and 153; 6144 rows (96 tiles), 98 K-steps: 2048 81 and 77, 3072
+// 118 and 133, 4096 150 and 135, 8192 286 and 235; 64 tiles, 68: 4096 65.8 and 66.0, 8192 146 and 113.  Short lists mostly store: 132 tiles, N = 8192,
+// 21 K-steps 186 and 163, 11: 136 and 126, 5: 91.3 and 88.9, 3: 71.5 and 71.4; 96 tiles, 1: 42.4 and 43.0.  Tiles have to be of like length: a
+// workgroup of the wide kernel takes half as long again for a K-step, which a few long tiles would make the whole launch wait for.  Against up to 1024
+// columns it has nothing to save, A and B stay in the L2 (512 tiles of 33 rows, 5 K-steps, N = 1024: 26.8 and 30.0; 256 of 64, N = 648: 20.5 and 18.5,
+// N = 1024: 21.4 and 21.7).
+static bool wide_pays(const vbr *v, int64_t T, int64_t N)
+{
+    constexpr int64_t kHere = kTwoOnACu / kXcd;
+    auto cost = [&](int64_t columns, int64_t full, int64_t half) {
+        const int64_t Q = (N + columns - 1) / columns, n = grid_size(T, Q, even_columns(T, Q)) / kXcd, over = n % kHere;
+        return n / kHere * full + (over > kHere / 2 ? full : over > 0 ? half : 0);
+    };
+    const int32_t longest = v->dev_tiles[0].n_ks, median = v->dev_tiles[(size_t)v->n_work / 2].n_ks;
+    return N > 1024 && longest >= 4 && longest <= 2 * median && 10 * (10 + cost(kWideN, 100, 77)) <= 9 * cost(kTileN, 62, 50);
+}
+
 EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned)
 {
     const int64_t M = (int64_t)start.size() - 1, nnz = start[(size_t)M];
@@ -1369,7 +1391,7 @@ namespace vbrk {
 // launch of the others and apart: graphs of 16384 nodes, 32 edges a node, N = 4096 176 and 177, N = 3000 147 and 148, 64 edges 217 and 221, 198 and
 // 196, of 8192 nodes, 16 edges, N = 4096 48 and 53; more than a quarter: 16384 nodes, 8 edges, N = 4096 94 and 101, N = 2048 44 and 49.  With few of them
 // a launch of its own takes 3 us more).
-int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUNCHES])
+int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUNCHES], int64_t ldb)
 {
     int n = 0;
     if (v->by_entries) {
@@ -1487,6 +1509,11 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
                 }
             }
             L.grid = grid_size(T + 3 * (int64_t)L.rest, Qt, L.even);
+        } else if (kind == VBR_LAUNCH_TILE_4 && !split && wide_pays(v, T, N) && b_bytes_of(v->n_cols, ldb ? ldb : N, N) <= kNearBytes) {
+            const int64_t Qw = (N + kWideN - 1) / kWideN;
+            L.wide = true;
+            L.even = even_columns(T, Qw);
+            L.grid = grid_size(T, Qw, L.even);
         } else {
             L.grid = grid_size(T, split ? Qd : Qt, L.even);
         }

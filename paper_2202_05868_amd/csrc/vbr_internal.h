@@ -24,6 +24,8 @@ constexpr int kSplitShort = 4;      // ... and where two on a CU hold them all: 
 constexpr int split_slabs(bool few) { return few ? 4 : 2; }
 constexpr int kDeepN = 64;          // C columns per workgroup of a deep tile, and of a split launch
 constexpr int kTileN = 256;         // C columns per workgroup of the tile kernel
+constexpr int kWideN = 512;         // C columns per workgroup of the wide kernel
+constexpr int kWideAhead = 5;       // K-steps behind a tile's last whose B rows it looks up, and does not use
 constexpr int kPanelN = 128;        // C columns per workgroup of the panel kernel
 constexpr int kZeroN = 1024;        // C columns per workgroup of the kernel that stores zeros
 constexpr int kXcd = 8;             // L2 domains; workgroup i runs on domain i % 8
@@ -33,6 +35,10 @@ constexpr int kXcd = 8;             // L2 domains; workgroup i runs on domain i 
 #else
 #define VBRK_HOST_DEVICE inline
 #endif
+
+// Bytes from B's first element to the end of its last row, and the most that offsets of 32 bits reach, less a page for the offset that stands for "none".
+constexpr int64_t kNearBytes = 0xFFFFF000ll;
+inline int64_t b_bytes_of(int64_t n_cols, int64_t ldb, int64_t N) { return n_cols > 0 ? ((n_cols - 1) * ldb + N) * 2 : 0; }
 
 // What map_workgroup needs to know of a launch beside T and Q: the way column tiles are dealt, and for fewer than 8 of them, whole, four bits a
 // domain each: its column tile, its number among the domains of that, and how many these are.  (Every wave divided for them: entry rows of 16384 x

@@ -7,6 +7,7 @@
 //   gathered tiles the same kernel with K-steps = the single columns its rows touch: up to 4 slabs of the
 //                  rows of low groups, and of tall groups whose blocks are mostly fill-in
 //   deep tiles     gathered tiles with very many columns: the waves of a workgroup split the K-steps
+//   wide kernel    3 to 4 slabs of one row group x 512 columns, for long lists against a wide B: B goes to registers, A through LDS
 //   panel kernel   8 slabs of low groups x 128 columns walking the union of their column blocks
 //   mixed kernel   tiles of several of these classes in one launch
 // Matrices whose rows share nothing are multiplied by the kernel in csr_spmm.hip.
@@ -16,6 +17,7 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "vbr_device.h"
 #include "vbr_host.h"
 
 namespace vbrk {
@@ -38,7 +40,9 @@ typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4v *lds_short4_ptr;
 typedef __attribute__((address_space(3))) short8v *lds_short8_ptr;
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) float4v *lds_float4_ptr;
+typedef __attribute__((address_space(3))) uint4v *lds_uint4_ptr;
 typedef __attribute__((address_space(3))) int32_t *lds_i32_ptr;
 typedef __attribute__((address_space(3))) unsigned char *lds_u8_ptr;
 typedef __attribute__((address_space(4))) const int32_t *const_i32_ptr;
@@ -50,6 +54,7 @@ struct Params {
     const int32_t *gcol;      // column-gathered tiles: their column lists ...
     const int32_t *prow;      // ... and the list of the low rows their row positions refer to
     int32_t b_fits24;         // the rows of B the matrix can touch span less than 4 GiB, their number and length in bytes less than 2^24
+    uint32_t b_bytes;         // wide kernel: bytes from B's first element to the end of its last row
     const uint16_t *vals;
     const uint16_t *B;
     float *C;
@@ -693,6 +698,177 @@ __global__ void __launch_bounds__(kThreads) vbr_spmm_split_kernel(const Params p
     deep_body<DT, S, SLOTS, GATHER>(p, p.tiles[tile], ntile * kDeepN, smem);
 }
 
+constexpr int kWideWaveN = kWideN / 4;           // C columns per wave of the wide kernel
+
+// Block tiles of 3 to 4 slabs against a wide B.  A workgroup owns 512 columns of C, each of its four waves 128 of them and all rows.
+// In the tile kernel a wave's B columns are nobody else's and pass through LDS all the same, for the sake of the transposed read: 16 KiB
+// written and 32 KiB read per K-step, which keeps the LDS busier than the matrix unit.  Here a lane loads eight columns of eight rows of B, 8 x 8 values that
+// it turns round by itself: 32 byte permutes leave in it, for each of its columns, the eight rows that a lane of a B operand holds, so that
+// operand f is columns f, 8 + f, 16 + f ... of the wave's 128, and neither LDS nor other lanes take part.  A row of 16 lanes loads 256 bytes of a row of B.
+//   - the row of B for every load stands in a lane of the row of 16, one load for two K-steps, and is added to the lane's column by the DPP of that addition;
+//   - the fragments of A, the same for all waves, go through registers into LDS, two K-steps at a time, one slab a wave, two K-steps ahead, with one
+//     barrier; 512 columns instead of 256 also halve what is fetched of A, which comes from beyond the L2;
+//   - rows of the next K-step are requested as soon as the registers of this one's are free, before its 32 matrix instructions.
+// Bound by the load path, 36 KiB a K-step of 64 x 512 (texture-address unit 86 % busy), then by the matrix unit (59 %).
+// Blocks of 64 x 64 at 40 %, 8192 x 8192, N = 8192: 473 -> 392 us (with fragments that are always in the L2 371); at 4096 x 4096, N = 4096: 63.4 -> 58.3.
+// The same for tiles of one and two slabs is slower (16 x 16 blocks at 10 %, N = 4096: 163 and 200; 32 x 32, 102 and 107): more waves ask for more
+// parts of B at a time than stay in the L2.
+template <int DT>
+__global__ void __launch_bounds__(kThreads, 2) vbr_spmm_wide_kernel(const Params p)
+{
+    constexpr int S = 4, kBuf = 2 * S * kFragBytes, kOutSlab = kSlabRows * kWideWaveN * 4;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * kOutSlab];      // two buffers of A, then the turned slabs of the four waves
+    static_assert(2 * kBuf <= 4 * kOutSlab, "both buffers of A fit");
+    int tile, ntile;
+    if (!map_workgroup(blockIdx.x, p.n_tiles, p.n_ntiles, p.map, tile, ntile)) return;
+    const TileDesc td = p.tiles[tile];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int q = lane >> 4, s16 = lane & 15;
+    const int n0 = ntile * kWideN + wave * kWideWaveN;
+    const bool live = n0 < p.N;                      // a wave beyond the last column only brings its share of A
+    const lds_u8_ptr sm = (lds_u8_ptr)smem;
+    const int n_ks = __builtin_amdgcn_readfirstlane(td.n_ks);
+    const int32_t c_row = lane < td.n_rows ? p.perm[td.row_begin + lane] : -1;       // C row of row `lane` of the tile
+
+    float4v acc[S][8];
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int f = 0; f < 8; ++f) acc[s][f] = float4v{0.f, 0.f, 0.f, 0.f};
+
+    // A: fragments of slab `wave` (no such slab: the last again, never stored; a row that the last slab does not have: its last one).  Behind the last
+    // K-step the loads are out of range and bring zeros.
+    const int n_slabs = __builtin_amdgcn_readfirstlane(td.n_slabs);
+    const int rows_last = __builtin_amdgcn_readfirstlane(td.n_rows) - (n_slabs - 1) * kSlabRows;
+    const uint32_t a_stride = (uint32_t)(((n_slabs - 1) * kFragElems + rows_last * kStepK) * 2);
+    const int slab = wave < n_slabs ? wave : n_slabs - 1, rows = slab == n_slabs - 1 ? rows_last : kSlabRows;
+    uint32_t a_lane = (uint32_t)((slab * kFragElems + (q * rows + (s16 < rows ? s16 : rows - 1)) * 8) * 2);
+    const uint64_t a_addr = reinterpret_cast<uint64_t>(p.vals) + (uint64_t)td.a_off * 16;
+    const uint64_t a_base = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(a_addr >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a_addr);
+    const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(a_base), 0, (int)((uint32_t)n_ks * a_stride), 0x00020000);
+    uint4v stage[2];
+    auto load_a = [&]() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            stage[i] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (int)a_lane, 0, 0));
+            a_lane += a_stride;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto write_a = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) *(lds_uint4_ptr)(sm + buf * kBuf + (i * S + wave) * kFragBytes + lane * 16) = stage[i];
+    };
+    auto meet = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };      // the loads in flight go on
+
+    if (!live) {
+        load_a();
+        write_a(0);
+        load_a();
+        meet();
+        for (int k = 0, buf = 1; k < n_ks; k += 2, buf ^= 1) {
+            write_a(buf);
+            load_a();
+            meet();
+        }
+        return;
+    }
+
+    // B: lane (q, s16) loads columns 8 s16 .. 8 s16 + 7 of rows 8 q + j of the K-step in fragment order, j = 0 .. 7.  Lane j + 8 h of a row of 16 looks row j
+    // of K-step 2 i + h up for all of them.  (Up to kWideAhead K-steps past the tile's last are looked up, inside the uploaded buffer, and not used.)
+    const int last_chunk = (p.N - n0 < kWideWaveN ? p.N - n0 : kWideWaveN) / 8 - 1;
+    const uint32_t column = (uint32_t)(s16 <= last_chunk ? s16 : last_chunk) * 16;               // past column N: the last chunk again, never stored
+    const uint32_t ldb_bytes = (uint32_t)(p.ldb * 2);
+    const char *Bs = reinterpret_cast<const char *>(p.B + n0);
+    const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(Bs), 0, (int)(p.b_bytes - (uint32_t)n0 * 2), 0x00020000);
+    const int lg = p.lg_gran, kk = 16 * (q >> 1) + 4 * (q & 1) + (s16 & 3) + 8 * (s16 >> 2 & 1), in_granule = kk & ((1 << lg) - 1);
+    const int32_t *list = p.krow + ((((int64_t)td.ks_begin + (s16 >> 3)) * kStepK + kk) >> lg);
+    auto look_up = [&]() -> int32_t {
+        const int32_t r = *list;
+        list += 2 * kStepK >> lg;
+        __builtin_amdgcn_sched_barrier(0);
+        return r;
+    };
+    // the offset of this lane's row of K-step k or k + 1; past the last one: out of range, which brings zeros and costs no traffic
+    auto offset = [&](int32_t row, int k) -> uint32_t { return k + (s16 >> 3) < n_ks ? (uint32_t)(row + in_granule) * ldb_bytes : (uint32_t)kNearBytes; };
+    uint4v b[8];
+    uint32_t turned[8][4];
+    auto load_b = [&](uint32_t off) -> uint4v { return __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, (int)(off + column), 0, 0)); };
+    // (the empty statements keep rows in the order written: a wait is for two loads and not for all)
+    auto turn = [&](auto j, uint4v &lo, uint4v &hi) {
+        asm volatile("" : "+v"(lo), "+v"(hi));
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            turned[2 * w][j.value] = __builtin_amdgcn_perm(hi[w], lo[w], 0x05040100u);
+            turned[2 * w + 1][j.value] = __builtin_amdgcn_perm(hi[w], lo[w], 0x07060302u);
+        }
+        asm volatile("" : "+v"(turned[0][j.value]), "+v"(turned[1][j.value]), "+v"(turned[2][j.value]), "+v"(turned[3][j.value]), "+v"(turned[4][j.value]),
+                     "+v"(turned[5][j.value]), "+v"(turned[6][j.value]), "+v"(turned[7][j.value]));
+    };
+    // one K-step: its rows turned and, in their place, those of the next requested (half h of the offsets); its fragments at `from`
+    auto step = [&](lds_u8_ptr from, auto h, uint32_t off) {
+        short8v a[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) a[s] = *(lds_short8_ptr)(from + s * kFragBytes + lane * 16);
+        __builtin_amdgcn_s_setprio(3);
+        static_for<4>([&](auto j) {
+            turn(j, b[2 * j.value], b[2 * j.value + 1]);
+            b[2 * j.value] = load_b(row_lane<8 * h.value + 2 * j.value>(off));
+            b[2 * j.value + 1] = load_b(row_lane<8 * h.value + 2 * j.value + 1>(off));
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+        for (int f = 0; f < 8; ++f) {
+            const uint4v bf = {turned[f][0], turned[f][1], turned[f][2], turned[f][3]};
+#pragma unroll
+            for (int s = 0; s < S; ++s) acc[s][f] = mfma16x16x32<DT>(a[s], __builtin_bit_cast(short8v, bf), acc[s][f]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    uint32_t off = offset(look_up(), 0);
+    load_a();
+    static_for<8>([&](auto u) {
+        b[u.value] = load_b(row_lane<u.value>(off));
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    int32_t next = look_up();
+    write_a(0);
+    load_a();
+    meet();
+    for (int k = 0, buf = 0; k < n_ks; k += 2, buf ^= 1) {
+        step(sm + buf * kBuf, constant<1>(), off);
+        write_a(buf ^ 1);
+        off = offset(next, k + 2);
+        next = look_up();
+        step(sm + buf * kBuf + S * kFragBytes, constant<0>(), off);
+        load_a();
+        meet();                                     // the next two K-steps are there, and nobody reads these any more
+    }
+
+    // Operand f held every eighth column from f on, so a lane has eight columns in a row of each of its four C rows.  As in the tile kernel the slab is turned
+    // round in LDS (the wave's own 8 KiB) and leaves in whole lines, 2 rows x 512 bytes a store.
+    const lds_u8_ptr out = sm + wave * kOutSlab;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const lds_u8_ptr at = out + i * 2048 + lane * 32;
+            *(lds_float4_ptr)at = float4v{acc[s][0][i], acc[s][1][i], acc[s][2][i], acc[s][3][i]};
+            *(lds_float4_ptr)(at + 16) = float4v{acc[s][4][i], acc[s][5][i], acc[s][6][i], acc[s][7][i]};
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float4v x = *(lds_float4_ptr)(out + i * 2048 + h * 1024 + lane * 16);
+                const int32_t row = __shfl(c_row, s * kSlabRows + 4 * (2 * h + (lane >> 5)) + i);
+                const int n = n0 + 4 * (lane & 31);
+                if (row >= 0 && n < p.N) __builtin_nontemporal_store(x, reinterpret_cast<float4v *>(p.C + row * p.ldc + n));
+            }
+    }
+}
+
 // C rows of tiles without a K-step, the rows of A without entries: zeros.  Bound by what the memory takes, so a workgroup writes whole
 // pieces of 4 KiB, one of each of 16 rows (3886 rows of a graph, N = 4096, behind the launch of its other tiles: 27 us in the kernel of the gathered
 // tiles, which turns its zeros in LDS like any other result, 25 here; N = 3000: 22 and 17).
@@ -913,7 +1089,7 @@ template <int DT>
 int launch_all(const vbr *v, const Params &base, PanelParams pp, hipStream_t stream)
 {
     Launch plan[VBR_MAX_LAUNCHES];
-    const int n = plan_launches(v, base.N, base.ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(base.B) & 127) == 0, plan);
+    const int n = plan_launches(v, base.N, base.ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(base.B) & 127) == 0, plan, base.ldb);
     for (int i = 0; i < n; ++i)
         if (plan[i].grid > INT32_MAX) return VBR_EINVAL;
     for (int i = 0; i < n; ++i) {
@@ -938,6 +1114,8 @@ int launch_all(const vbr *v, const Params &base, PanelParams pp, hipStream_t str
             p.n_tiles = L.n_tiles + 3 * p.rest;
         } else if (L.split) {
             p.n_ntiles = (p.N + kDeepN - 1) / kDeepN;
+        } else if (L.wide) {
+            p.n_ntiles = (p.N + kWideN - 1) / kWideN;
         }
         switch (L.kind) {
         case VBR_LAUNCH_TILE_MIXED:
@@ -960,7 +1138,7 @@ int launch_all(const vbr *v, const Params &base, PanelParams pp, hipStream_t str
             kernel = L.split ? vbr_spmm_split_kernel<DT, 2, false> : few ? vbr_spmm_kernel<DT, 2, kStagesFew, kStagesFew> : vbr_spmm_kernel<DT, 2, kStages, kADistanceTwo>;
             break;
         case VBR_LAUNCH_TILE_4:
-            kernel = L.split ? vbr_spmm_split_kernel<DT, 4, false> : vbr_spmm_kernel<DT, 4, kStagesTall, kADistance>;
+            kernel = L.split ? vbr_spmm_split_kernel<DT, 4, false> : L.wide ? vbr_spmm_wide_kernel<DT> : vbr_spmm_kernel<DT, 4, kStagesTall, kADistance>;
             break;
         case VBR_LAUNCH_ZERO_ROWS:
             kernel = vbr_spmm_zero_rows_kernel;
@@ -1061,6 +1239,7 @@ extern "C" int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C
     pp.n_ntiles = (int32_t)((N + 127) / 128);
     p.gcol = reinterpret_cast<const int32_t *>(d + v->lay.gcol_off);
     p.b_fits24 = (v->n_cols * ldb * 2 + N * 2) < ((int64_t)1 << 32) && v->n_cols <= (1 << 24) && ldb * 2 < (1 << 24) ? 1 : 0;
+    p.b_bytes = (uint32_t)vbrk::b_bytes_of(v->n_cols, ldb, N);
     p.prow = pp.prow;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     return v->dtype == VBR_F16 ? vbrk::launch_all<VBR_F16>(v, p, pp, stream) : vbrk::launch_all<VBR_BF16>(v, p, pp, stream);

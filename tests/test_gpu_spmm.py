@@ -324,6 +324,34 @@ def test_two_slab_tiles_at_the_lengths_of_their_rings(col_block, n_ks, groups, n
     check_c(c, c_ref, s, "two slabs, %d K-steps" % n_ks)
 
 
+@pytest.mark.parametrize("heights,groups,col_block,n_ks,n,pad,dtype,workgroups", [
+    ([33], 128, 32, 4, 2048, 0, "f16", 512), ([64], 128, 16, 5, 1920, 0, "bf16", 512), ([64, 33, 48, 49], 128, 8, 7, 1928, 8, "f16", 512),
+    ([50, 64], 128, 24, 6, 1800, 0, "f16", 512), ([40], 128, 64, 6, 1544, 64, "f16", 512), ([35, 64], 126, 40, 9, 2040, 0, "bf16", 504),
+    ([33, 41], 192, 16, 4, 2056, 0, "f16", 960), ([61], 64, 32, 11, 4096, 0, "f16", 512)])
+def test_long_lists_against_a_wide_b(heights, groups, col_block, n_ks, n, pad, dtype, workgroups):
+    # row groups of three and four slabs with full and partial last ones, lists of an even and an odd number of K-steps with and without a partial last one,
+    # of one length and (longer than 4) of two; every granule width; the last column tile whole, with waves that have no column, and one that has 8
+    rng = np.random.default_rng(n + n_ks)
+    n_cols = 40 * 64 if col_block in (40, 64) else 72 * 32
+    r, c, row = [], [], 0
+    for g in range(groups):
+        h, blocks = heights[g % len(heights)], (n_ks - (g % 3 == 1 and n_ks > 4)) * 32 // col_block
+        cols = (np.sort(rng.choice(n_cols // col_block, size=blocks, replace=False))[:, None] * col_block + np.arange(col_block)).reshape(-1)
+        r.append(np.repeat(np.arange(row, row + h), cols.size))
+        c.append(np.tile(cols, h))
+        row += h
+    r, c = np.concatenate(r), np.concatenate(c)
+    csr = synth.csr_from_coo(row, n_cols, r, c, synth.to_bits(rng.uniform(-1, 1, size=r.size).astype(np.float32), dtype), dtype)
+    rg = np.cumsum([0] + [heights[g % len(heights)] for g in range(groups)]).astype(np.int32)
+    perm = rng.permutation(row).astype(np.int32)
+    csr = synth.permute_rows(csr, np.argsort(perm))
+    bits = synth.dense_rhs(rng, n_cols, n, dtype)
+    out, v = gpu_spmm(csr, perm, rg, col_block, bits, ldb_pad=pad, ldc_pad=pad)
+    assert [(p["kernel"], p["workgroups"]) for p in v.launches(n)] == [("vbr_spmm_kernel<4 slabs>", workgroups)]
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(out, c_ref, s, "%d K-steps, N = %d" % (n_ks, n))
+
+
 @pytest.mark.parametrize("n", [8, 24, 64, 72, 120, 128, 136, 264, 384, 392])
 @pytest.mark.parametrize("heights,col_block", [([128, 70, 100], 16), ([128, 70, 40, 18, 33, 16, 3, 9, 2], 16), ([60, 20, 7], 3)])
 def test_narrow_column_tiles(heights, col_block, n):
