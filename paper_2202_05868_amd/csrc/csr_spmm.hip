@@ -72,11 +72,14 @@ __device__ __forceinline__ uint32_t half_turn(uint32_t x)    // the halves of ev
 // at a time and add their halves at the end.
 // Eight loads of B are in flight from a row's first entry to its last: an addition is followed by the load of the entry eight further on, whose column
 // was fetched a batch earlier, and no load stands in a branch, so that every wait is for one load and not for all.  A load of B takes the load path 17
-// cycles, a word a lane 7, two words 17 (so an entry and a row's description are one load each).  A row leaves through LDS: see there.
+// cycles, a word a lane 7, two words 17: so an entry whose column fits 16 bits is one word (NEAR), any other and a row's description are one load each.
+// (Words against two words, both with eight waves a SIMD: 120 products of the cases' ranges 3 % less on average, 3648 x 4864, 253 entries a row, N = 88
+// 15.1 and 12.7 us, 32768 x 32768, 16 a row, N = 256 24.9 and 23.0.)  A row leaves through LDS: see there.
+// Up to 64 registers, eight waves a SIMD; where the compiler keeps values across a branch at a row's end it takes more.
 // Measured on a graph of 16384 nodes with 426 000 entries (rows of 0 to 3600), with B and C beyond the caches, N = 4096: 214 us with the waits of a
-// batch for all of its loads, columns and values apart and 16 bytes of every 32 a store, now 197 (17.8 TB/s of gathered B; without B's loads 110, without the
-// stores 171); 120 products of the experiments' and the tests' matrices: 9 % less on average.
-template <int DT, bool WIDE, int LANES>
+// batch for all of its loads, columns and values apart and 16 bytes of every 32 a store, 197 with entries of two words, now 194 (18.0 TB/s of gathered B,
+// texture-address unit 84 % busy).
+template <int DT, bool WIDE, int LANES, bool NEAR>
 __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryParams p)
 {
     constexpr bool kPair = LANES == 8;                               // 16 lanes own a row, two entries at a time
@@ -95,11 +98,13 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
     const int first = p.n_huge + p.n_long, pos = huge ? tile : whole ? wave - 3 * p.n_huge : first + (wave - 3 * p.n_huge - first) * kGroups + g;
     const EntryRow mine = p.rows.row[pos < p.n_rows ? pos : p.n_rows - 1];
     const int32_t row = pos < p.n_rows ? mine.row : -1, len = pos < p.n_rows ? mine.len : 0;
-    const int64_t from = mine.start;
     const int32_t max_len = __builtin_amdgcn_readfirstlane(len);     // the first row of a wave is its longest
     const int lg_parts = huge ? 2 + kLgGroups : whole ? kLgGroups : 0;
     const int step = 16 * parts;
-    const int e0 = parts * s16 + part;                               // this lane's entry of a batch
+    // this lane's entry of the first batch, and how far behind it the row's last one is; of a row without entries the place of its start counts as behind
+    const int e0 = parts * s16 + part, to_last = len - 1 - e0;
+    using Stored = std::conditional_t<NEAR, uint32_t, Entry>;
+    const Stored *first_entry = static_cast<const Stored *>(p.rows.entry) + (mine.start + (len == 0) + e0);
 
     const int n0 = ntile * kTileN;
     const int last_chunk = (p.N - n0 < kTileN ? p.N - n0 : kTileN) / 8 - 1;
@@ -121,7 +126,8 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
     };
     // (the empty statements keep additions and loads in the order written: moved past each other they take registers that cost waves)
     auto add = [&](uint32_t a_bits, uint4v &b) {
-        asm volatile("" : "+v"(b));
+        if constexpr (DT == VBR_F16) asm volatile("" ::"v"(b));
+        else asm volatile("" : "+v"(b));
         const float a = __builtin_bit_cast(float, a_bits);
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] = __builtin_fmaf(a, half_to_f32<DT>(b[i >> 1], i & 1), acc[i]);
@@ -130,22 +136,25 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
     };
     // The entries of batch i, this lane's one of 16.  Behind the end of the row the last entry again, without effect: a load that every lane
     // makes is one the waits for the loads of B can count on.
-    int32_t col;
-    uint32_t val;
+    int32_t col;                                                     // where it does not stand in the word
+    uint32_t word;
     bool there;
     auto fetch = [&](int batch) {
-        const int32_t at = batch * step + e0;
-        const int64_t i = from + (at < len ? at : len - 1);
-        const int64_t k = i > 0 ? i : 0;
-        const Entry e = p.rows.entry[k];
-        col = e.col;
-        val = e.val;
-        there = at < len;
+        const int32_t at = batch * step;
+        const Stored e = first_entry[at < to_last ? at : to_last];
+        if constexpr (NEAR) {
+            word = e;
+        } else {
+            col = e.col;
+            word = e.val;
+        }
+        there = at <= to_last;
     };
     uint32_t off = 0, a = 0;
     auto take = [&]() {                                              // the fetched entries become those to load and to add
-        off = !there ? 0xFFFFF000u : WIDE ? (uint32_t)col : (uint32_t)col * ldb_bytes;
-        a = there ? __builtin_bit_cast(uint32_t, half_to_f32<DT>(val, 0)) : 0;
+        const uint32_t c = NEAR ? word & 0xFFFFu : (uint32_t)col;
+        off = !there ? 0xFFFFF000u : WIDE ? c : c * ldb_bytes;
+        a = there ? __builtin_bit_cast(uint32_t, half_to_f32<DT>(word, NEAR)) : 0;
     };
     uint4v b[8];
     auto hand = [](auto u, uint32_t x) {
@@ -218,17 +227,25 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
                 off = half_turn(off);
                 a = half_turn(a);
             }
+            // (the first addition stands before the branch, or the compiler converts its eight values there and holds them in registers)
+            add(hand(c0, now), b[0]);
             if (left > 8) {
-                go_on(c0, now, c4, c0);
+                b[0] = load(hand(c0, off));
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<7>([&](auto u) {
+                    add(hand(constant<u.value + 1>(), now), b[u.value + 1]);
+                    if constexpr (u.value < 3) b[u.value + 1] = load(hand(constant<u.value + 1>(), off));
+                    __builtin_amdgcn_sched_barrier(0);
+                });
                 finish(c4, c0, a);
             } else {
-                finish(c8, c0, now);
+                static_for<7>([&](auto u) { add(hand(constant<u.value + 1>(), now), b[u.value + 1]); });
             }
         }
     }
     if constexpr (kPair) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] += __shfl_xor(acc[i], 8);
+        for (int i = 0; i < 8; ++i) acc[i] += __builtin_bit_cast(float, half_turn(__builtin_bit_cast(uint32_t, acc[i])));
     }
     if (parts > 1) {
 #pragma unroll
@@ -268,6 +285,11 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
     }
 }
 
+using EntryKernel = void (*)(EntryParams);
+template <int DT, bool NEAR>
+constexpr EntryKernel entry_kernels[6] = {entry_rows_kernel<DT, false, 8, NEAR>, entry_rows_kernel<DT, false, 16, NEAR>, entry_rows_kernel<DT, false, 32, NEAR>,
+                                          entry_rows_kernel<DT, true, 8, NEAR>, entry_rows_kernel<DT, true, 16, NEAR>, entry_rows_kernel<DT, true, 32, NEAR>};
+
 inline int64_t align_up256(int64_t x) { return (x + 255) / 256 * 256; }
 
 }  // namespace
@@ -293,13 +315,10 @@ int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &r
     p.n_long = L.n_long;
     p.n_waves = (int32_t)L.waves;
     if (L.waves > INT32_MAX || L.grid > INT32_MAX) return VBR_EUNSUPPORTED;
-    const int variant = (dtype == VBR_F16 ? 0 : 6) + (wide ? 3 : 0) + (L.lanes == 32 ? 2 : L.lanes == 16 ? 1 : 0);
-    void (*const kernels[12])(EntryParams) = {
-        entry_rows_kernel<VBR_F16, false, 8>, entry_rows_kernel<VBR_F16, false, 16>, entry_rows_kernel<VBR_F16, false, 32>,
-        entry_rows_kernel<VBR_F16, true, 8>, entry_rows_kernel<VBR_F16, true, 16>, entry_rows_kernel<VBR_F16, true, 32>,
-        entry_rows_kernel<VBR_BF16, false, 8>, entry_rows_kernel<VBR_BF16, false, 16>, entry_rows_kernel<VBR_BF16, false, 32>,
-        entry_rows_kernel<VBR_BF16, true, 8>, entry_rows_kernel<VBR_BF16, true, 16>, entry_rows_kernel<VBR_BF16, true, 32>};
-    hipLaunchKernelGGL(kernels[variant], dim3((unsigned)L.grid), dim3(kCsrThreads), 0, static_cast<hipStream_t>(hip_stream), p);
+    const int variant = (wide ? 3 : 0) + (L.lanes == 32 ? 2 : L.lanes == 16 ? 1 : 0);
+    const EntryKernel kernel = dtype == VBR_F16 ? (rows.near ? entry_kernels<VBR_F16, true>[variant] : entry_kernels<VBR_F16, false>[variant])
+                                                : (rows.near ? entry_kernels<VBR_BF16, true>[variant] : entry_kernels<VBR_BF16, false>[variant]);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)L.grid), dim3(kCsrThreads), 0, static_cast<hipStream_t>(hip_stream), p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
     return VBR_OK;
@@ -365,7 +384,7 @@ extern "C" int csr_spmm(const csr_dev_t *h, const void *B_dev, int64_t ldb, floa
     if (!B_dev || !C_dev || ldb < N || ldc < N || ldb % 8 != 0 || ldc % 4 != 0) return VBR_EINVAL;
     if ((reinterpret_cast<uintptr_t>(B_dev) & 15) != 0 || (reinterpret_cast<uintptr_t>(C_dev) & 15) != 0) return VBR_EINVAL;
     const char *d = static_cast<const char *>(h->dev);
-    const vbrk::EntryRowsDev rows{reinterpret_cast<const vbrk::EntryRow *>(d), reinterpret_cast<const vbrk::Entry *>(d + h->entry_off)};
+    const vbrk::EntryRowsDev rows{reinterpret_cast<const vbrk::EntryRow *>(d), d + h->entry_off, h->rows.near};
     const vbrk::EntryLaunch L = vbrk::plan_entry_rows(h->rows.start, h->n_cols, N, ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0);
     return vbrk::launch_entry_rows(L, h->dtype, rows, h->n_rows, h->n_cols, B_dev, ldb, C_dev, ldc, N, hip_stream);
 }

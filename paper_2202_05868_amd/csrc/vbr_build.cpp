@@ -1063,12 +1063,16 @@ extern "C" int vbr_unpack_block(const vbr_t *v, int64_t blk, void *dst_)
     if (v->by_entries) {
         for (int64_t i = 0; i < v->row_groups[g + 1] - v->row_groups[g]; ++i) {
             const int64_t e = v->row_pos[(size_t)(v->row_groups[g] + i)];
-            const Entry *b = v->entries.entry.get() + v->entries.start[(size_t)e], *end = v->entries.entry.get() + v->entries.start[(size_t)e + 1];
-            for (int64_t c = 0; c < cb; ++c) {
-                const int32_t col = (int32_t)((int64_t)v->blk_col[blk] * cb + c);
-                const Entry *it = std::lower_bound(b, end, col, [](const Entry &x, int32_t c) { return x.col < c; });
-                dst[i * cb + c] = it != end && it->col == col ? (uint16_t)it->val : 0;
+            const int64_t end = v->entries.start[(size_t)e + 1], first = (int64_t)v->blk_col[blk] * cb;
+            int64_t at = v->entries.start[(size_t)e], n = end - at;      // the row's first entry in the block
+            while (n > 0) {
+                const int64_t half = n / 2;
+                const bool before = v->entries.get(at + half).col < first;
+                at = before ? at + half + 1 : at;
+                n = before ? n - half - 1 : half;
             }
+            std::fill(dst + i * cb, dst + (i + 1) * cb, (uint16_t)0);
+            for (Entry x; at < end && (x = v->entries.get(at)).col < first + cb; ++at) dst[i * cb + x.col - first] = (uint16_t)x.val;
         }
         return VBR_OK;
     }
@@ -1209,7 +1213,7 @@ extern "C" int vbr_audit(const vbr_t *v)
             if (i > 0 && e.start[(size_t)i + 1] - e.start[(size_t)i] > e.start[(size_t)i] - e.start[(size_t)i - 1]) return VBR_EINVAL;
         }
         for (int64_t i = 0; i < e.count; ++i)
-            if (e.entry[(size_t)i].col < 0 || e.entry[(size_t)i].col >= K) return VBR_EINVAL;
+            if (e.get(i).col < 0 || e.get(i).col >= K) return VBR_EINVAL;
     }
     for (size_t i = v->by_entries ? 0 : (size_t)n_vals - kFragElems; i < (size_t)n_vals; ++i)
         if (values[i] != 0) return VBR_EINVAL;                                               // the zero fragment
@@ -1250,15 +1254,16 @@ void make_entry_rows(const vbr_csr_t *csr, Team &team, EntryRows &out)
         r.len = (int32_t)(csr->row_ptr[r.row + 1] - csr->row_ptr[r.row]);
         out.start[(size_t)k + 1] = r.start + r.len;
     }
-    out.count = csr->nnz;
-    out.entry.reset(new Entry[(size_t)(csr->nnz + kEntryPad)]);
-    std::fill(out.entry.get() + csr->nnz, out.entry.get() + csr->nnz + kEntryPad, Entry{0, 0});
+    out.allocate(csr->nnz, csr->n_cols);
     const uint16_t *v = static_cast<const uint16_t *>(csr->vals);
     team.each(M, 256, [&](int64_t b, int64_t e) {
         for (int64_t k = b; k < e; ++k) {
-            const int64_t p0 = csr->row_ptr[out.row[(size_t)k].row], n = out.start[(size_t)k + 1] - out.start[(size_t)k];
-            Entry *to = out.entry.get() + out.start[(size_t)k];
-            for (int64_t i = 0; i < n; ++i) to[i] = Entry{csr->col_idx[p0 + i], v[p0 + i]};
+            const int64_t p0 = csr->row_ptr[out.row[(size_t)k].row], to = out.start[(size_t)k], n = out.start[(size_t)k + 1] - to;
+            if (out.near) {
+                for (int64_t i = 0; i < n; ++i) out.entry[(size_t)(to + i)] = (uint32_t)csr->col_idx[p0 + i] | (uint32_t)v[p0 + i] << 16;
+            } else {
+                for (int64_t i = 0; i < n; ++i) out.put(to + i, csr->col_idx[p0 + i], v[p0 + i]);
+            }
         }
     });
 }

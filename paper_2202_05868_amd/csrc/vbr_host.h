@@ -28,7 +28,8 @@ void make_entry_rows(const vbr_csr_t *csr, Team &team, EntryRows &out);
 // The same on the device.
 struct EntryRowsDev {
     const EntryRow *row;
-    const Entry *entry;
+    const void *entry;
+    bool near;
 };
 struct EntryLaunch { int32_t lanes, n_huge, n_long; int64_t waves, grid; bool even; };
 // the launch for dense width N; aligned: rows of B begin on a cache line

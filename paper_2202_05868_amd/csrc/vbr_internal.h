@@ -208,7 +208,9 @@ private:
     size_t n_ = 0;
 };
 
-// An entry: its column and the 16 bits of its value in one word each, so that one load brings both.
+// An entry: its column and the 16 bits of its value, together so that one load brings both: the low and the high half of a word where all columns
+// are below kEntryNear, else a word each.
+constexpr int64_t kEntryNear = 1 << 16;
 struct Entry {
     int32_t col;
     uint32_t val;
@@ -220,16 +222,38 @@ struct EntryRow {
     int64_t start;
     int32_t len, row;
 };
-static_assert(sizeof(Entry) == 8 && sizeof(EntryRow) == 16, "read by the kernels as 8 and 16 bytes");
+static_assert(sizeof(Entry) == 8 && sizeof(EntryRow) == 16, "read by the kernels as 4 or 8 and 16 bytes");
 
 // Rows of a matrix as lists of entries, the longest row first (csr_spmm.hip multiplies them): positions 0 .. rows-1,
 // the entries of a position at start[pos] .. start[pos + 1].
 struct EntryRows {
     std::vector<int64_t> start;      // [rows + 1]
     std::vector<EntryRow> row;       // what the device knows of every position
-    std::unique_ptr<Entry[]> entry;  // and kEntryPad behind them
+    bool near = false;               // an entry is one word
+    std::unique_ptr<uint32_t[]> entry;      // of one or two words, and kEntryPad behind them
     int64_t count = 0;               // of them, without these
-    size_t bytes() const { return entry ? (size_t)(count + kEntryPad) * sizeof(Entry) : 0; }
+    void allocate(int64_t n, int64_t n_cols)
+    {
+        near = n_cols <= kEntryNear;
+        count = n;
+        entry.reset(new uint32_t[(size_t)(n + kEntryPad) * (near ? 1 : 2)]);
+        for (int64_t i = n; i < n + kEntryPad; ++i) put(i, 0, 0);
+    }
+    void put(int64_t i, int32_t col, uint16_t val)
+    {
+        if (near) {
+            entry[(size_t)i] = (uint32_t)col | (uint32_t)val << 16;
+        } else {
+            entry[(size_t)i * 2] = (uint32_t)col;
+            entry[(size_t)i * 2 + 1] = val;
+        }
+    }
+    Entry get(int64_t i) const
+    {
+        if (near) return Entry{(int32_t)(entry[(size_t)i] & 0xFFFFu), entry[(size_t)i] >> 16};
+        return Entry{(int32_t)entry[(size_t)i * 2], entry[(size_t)i * 2 + 1]};
+    }
+    size_t bytes() const { return entry ? (size_t)(count + kEntryPad) * (near ? 4 : sizeof(Entry)) : 0; }
 };
 
 }  // namespace vbrk

@@ -1205,7 +1205,7 @@ extern "C" int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C
     if ((reinterpret_cast<uintptr_t>(B_dev) & 15) != 0 || (reinterpret_cast<uintptr_t>(C_dev) & 15) != 0) return VBR_EINVAL;
     const char *d = static_cast<const char *>(v->dev);
     if (v->by_entries) {
-        const vbrk::EntryRowsDev rows{reinterpret_cast<const vbrk::EntryRow *>(d + v->lay.prow_off), reinterpret_cast<const vbrk::Entry *>(d + v->lay.gcol_off)};
+        const vbrk::EntryRowsDev rows{reinterpret_cast<const vbrk::EntryRow *>(d + v->lay.prow_off), d + v->lay.gcol_off, v->entries.near};
         const vbrk::EntryLaunch L = vbrk::plan_entry_rows(v->entries.start, v->n_cols, N, ldb % 64 == 0 && (reinterpret_cast<uintptr_t>(B_dev) & 127) == 0);
         return vbrk::launch_entry_rows(L, v->dtype, rows, v->n_rows, v->n_cols, B_dev, ldb, C_dev, ldc, N, hip_stream);
     }

@@ -886,6 +886,23 @@ def test_csr_comparator_at_every_length_of_a_rows_end(n, ldb_pad, dtype):
     assert torch.equal(again.cpu()[short], c.cpu()[short]) and not torch.isfinite(again.cpu()[~short]).any()
 
 
+@pytest.mark.parametrize("n", [24, 72, 208])
+@pytest.mark.parametrize("n_cols,dtype", [(65535, "f16"), (65536, "f16"), (65536, "bf16"), (65537, "bf16"), (70000, "f16")])
+def test_entries_of_one_and_of_two_words(n_cols, dtype, n):
+    # an entry is one word where every column fits its low half: columns on both sides of that, values of either sign, rows of 0 to 40
+    # entries that end at the last column, fewer rows than a wave's groups take behind the last full one
+    import torch
+    rng = np.random.default_rng(n)
+    rows = [sorted({n_cols - 1, *rng.integers(0, n_cols, size=x).tolist()}) if x else [] for x in rng.integers(0, 40, size=41)]
+    csr = csr_from_rows(rows, n_cols, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, n_cols, n, dtype)
+    b = torch_io.bits_to_device(bits, dtype)
+    c = binding.CsrDev(csr).upload("cuda:0").spmm(b)
+    torch.cuda.synchronize()
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n_cols=%d" % n_cols)
+
+
 @pytest.mark.parametrize("n,ldb_pad,dtype", [(520, 0, "f16"), (576, 0, "bf16"), (776, 8, "f16"), (1096, 0, "bf16")])
 def test_csr_comparator_with_many_long_rows(n, ldb_pad, dtype):
     # rows for a wave and for a workgroup with 128 and 256 columns a wave: none is much longer than the others

@@ -371,6 +371,24 @@ def test_a_matrix_kept_as_entry_rows_reports_its_rows_and_no_tiles():
     assert n.value == 1 and kinds[0] == 10               # a code no other kernel ever had
 
 
+@pytest.mark.parametrize("n_cols", [65536, 65552])
+def test_blocks_of_a_matrix_kept_as_entry_rows_unpack_from_entries_of_one_and_of_two_words(n_cols):
+    rng = np.random.default_rng(n_cols)
+    rows = [sorted({int(c), int(c) | 15, n_cols - 1}) for c in rng.integers(0, n_cols, size=9000)]
+    csr = csr_from_rows(rows, n_cols, rng)
+    v = binding.vbr_build(csr, np.arange(9000, dtype=np.int32), np.arange(9001, dtype=np.int32), 16)
+    assert [p["kernel"] for p in v.launches(256)] == ["entry_rows_kernel"]
+    v.audit()
+    ix = v.index()
+    for row in [0, 1, 4999, 8999]:
+        p0, p1 = csr["row_ptr"][row], csr["row_ptr"][row + 1]
+        dense = np.zeros(n_cols, dtype=np.uint16)
+        dense[csr["col_idx"][p0:p1]] = csr["vals"][p0:p1]
+        for b in range(ix["blk_ptr"][row], ix["blk_ptr"][row + 1]):
+            c0 = int(ix["blk_col"][b]) * 16
+            assert np.array_equal(np.asarray(v.unpack_block(int(b), 1, 16)).ravel(), dense[c0:c0 + 16])
+
+
 def full_csr(n_rows, n_cols):
     """Every entry stored: for plans, which look at the pattern alone."""
     return dict(n_rows=n_rows, n_cols=n_cols, nnz=n_rows * n_cols, row_ptr=np.arange(n_rows + 1, dtype=np.int64) * n_cols,
