@@ -47,6 +47,14 @@ __device__ __forceinline__ float half_to_f32(uint32_t pair, int hi)      // the 
     else return __builtin_bit_cast(float, hi ? pair & 0xFFFF0000u : pair << 16);
 }
 
+// LDS of a workgroup: partial sums of three waves, results on their way to C
+template <int LANES>
+constexpr int kPartialBytes = 3 * 8 * LANES * 4;
+template <int LANES>
+constexpr int kTurnedBytes = LANES == 8 ? 0 : 4 * 64 * 8 * 4;
+constexpr int kSixBytes = 26 * 1024;       // so much of it is there six times on a CU, and not seven times
+static_assert(6 * kSixBytes <= 160 * 1024 && 7 * kSixBytes > 160 * 1024 && kPartialBytes<32> + kTurnedBytes<32> <= kSixBytes, "six workgroups on a CU");
+
 template <int U>
 __device__ __forceinline__ uint32_t row_pair(uint32_t x)     // lane 2U of every row of 16 lanes to its first eight, lane 2U + 1 to the others
 {
@@ -84,7 +92,7 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
 {
     constexpr bool kPair = LANES == 8;                               // 16 lanes own a row, two entries at a time
     constexpr int kGroups = kPair ? 4 : 64 / LANES, kLgGroups = kGroups == 4 ? 2 : 1, kTileN = 8 * LANES;
-    __shared__ float partial[3][kTileN];
+    __shared__ float partial[kPartialBytes<LANES> / (kTileN * 4)][kTileN];
     const int lane = threadIdx.x & 63, g = lane / (64 / kGroups), s16 = lane & 15, chunk0 = lane % LANES;
     // workgroup -> (column tile, four waves' rows): workgroups are dealt to the 8 L2 domains round-robin
     const int T = (p.n_waves + 3) / 4, Q = p.n_ntiles;
@@ -271,7 +279,7 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
     } else {
         // A lane holds eight columns, 32 bytes of C: stored as they are, a store takes every other 16 bytes of its lines.  Through LDS, it is 1 KiB of whole
         // lines (16384 rows, N = 4096, only the rows' descriptions and stores: 116 and 52 us; that graph without its loads of B: 141 and 110).
-        __shared__ __attribute__((aligned(16))) float turned[4][64 * 8];
+        __shared__ __attribute__((aligned(16))) float turned[kTurnedBytes<LANES> / (64 * 8 * 4)][64 * 8];
         float *out_lds = turned[in_wg];
         *reinterpret_cast<float4v *>(out_lds + 8 * lane) = float4v{acc[0], acc[1], acc[2], acc[3]};
         *reinterpret_cast<float4v *>(out_lds + 8 * lane + 4) = float4v{acc[4], acc[5], acc[6], acc[7]};
@@ -318,7 +326,8 @@ int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &r
     const int variant = (wide ? 3 : 0) + (L.lanes == 32 ? 2 : L.lanes == 16 ? 1 : 0);
     const EntryKernel kernel = dtype == VBR_F16 ? (rows.near ? entry_kernels<VBR_F16, true>[variant] : entry_kernels<VBR_F16, false>[variant])
                                                 : (rows.near ? entry_kernels<VBR_BF16, true>[variant] : entry_kernels<VBR_BF16, false>[variant]);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)L.grid), dim3(kCsrThreads), 0, static_cast<hipStream_t>(hip_stream), p);
+    const int lds = L.lanes == 32 ? kPartialBytes<32> + kTurnedBytes<32> : L.lanes == 16 ? kPartialBytes<16> + kTurnedBytes<16> : kPartialBytes<8> + kTurnedBytes<8>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)L.grid), dim3(kCsrThreads), L.six ? (unsigned)(kSixBytes - lds) : 0u, static_cast<hipStream_t>(hip_stream), p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
     return VBR_OK;

@@ -302,6 +302,14 @@ void check_entry_plan()
         if (L.lanes != x.lanes) std::fprintf(stderr, "%lld rows of %lld entries, %lld, %lld of B, N = %lld: %d lanes\n", (long long)x.rows, (long long)x.len, (long long)x.longest, (long long)x.n_cols, (long long)x.N, L.lanes);
         REQUIRE(L.lanes == x.lanes);
     }
+    // six workgroups on a CU: for rows of unlike length, long ones among them, with 24 entries and more on average
+    struct { int64_t rows, len, longest; bool six; } const unlike[] = {
+        {16384, 25, 3700, true}, {16384, 24, 257, true}, {16384, 23, 300, false}, {16384, 25, 256, false}, {16384, 65, 257, false}, {4096, 600, 600, false}, {4096, 300, 1300, true}, {9000, 5, 5, false}};
+    for (const auto &x : unlike) {
+        std::vector<int64_t> start = {0, x.longest};
+        for (int64_t i = 1; i < x.rows; ++i) start.push_back(start.back() + x.len);
+        REQUIRE(vbrk::plan_entry_rows(start, 16384, 1024, true).six == x.six);
+    }
     // widths of as many column tiles have as many lanes, rows of B padded to a cache line or not; long rows, in waves and workgroups of their own
     struct { int64_t rows, len, longest, n_cols, first_N, last_N; bool aligned; int lanes; } const widths[] = {
         {16384, 5, 5, 16384, 72, 256, true, 8},     {20000, 5, 5, 20000, 264, 320, true, 8},   {20000, 5, 5, 20000, 456, 512, true, 8},  {20000, 4, 4, 20000, 264, 1024, true, 16},
