@@ -1481,7 +1481,14 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         // workgroups: 13.1 and 9.7, 42.4 and 32.2, 63 and 52; N = 592, 1416 of them, 236 on the busiest domain: 33.2 and 24.5; 1744: 22.1 and 24.8,
         // 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
         const int64_t grid = grid_size(T, Qt);             // as if of whole column tiles
-        const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= 3 * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= (grid <= kTwoOnACu / 2 ? 5 : 18));
+        // Beyond, where the column tiles leave some domains with less than others or two domains to one column tile, the chip is not full at the end and the
+        // chains still count: up to six column tiles, as far as it was measured (graphs of 16384 nodes, two slots and four: 944 columns 48.9 and 35.5,
+        // 880 32.5 and 25.6, 1040 49.1 and 40.5, 1264 89.9 and 86.5, 1416 52.1 and 45.1; 15 graphs 15 % less) and nine to twelve (4096 nodes, 2144 columns
+        // 35.1 and 32.1; 8192, 2592: 48.8 and 44.3; 16384, 2552: 96.9 and 88.9, 2904: 203 and 198; 22 graphs 5 % less).  Seven and eight take the
+        // same on average (1664 columns 56.4 and 60.2, 1672: 60.5 and 57.8; 1952: 21.5 and 23.3), as do 13; 14 to 16 take more (3400: 46.0 and 49.3, 3720:
+        // 40.6 and 44.4, 3920: 37.6 and 41.6).
+        const int64_t deep_most = Qt <= 6 ? 6 : Qt >= 9 && Qt <= 12 ? 10 : 3;
+        const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= deep_most * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= (grid <= kTwoOnACu / 2 ? 5 : 18));
         // workgroups an L2 domain holds at once
         const int64_t at_once = (few || v->class_count[3] > 0 || kind == VBR_LAUNCH_TILE_4 ? kTwoOnACu : kind == VBR_LAUNCH_TILE_MIXED || kind == VBR_LAUNCH_GATHER_4 ? kThreeOnACu
                                                                                                                                                                   : kFourOnACu) / kXcd;

@@ -164,6 +164,26 @@ def test_tiles_with_long_column_lists_split_their_k_steps(n, rows_of_hubs, ldb_p
     check_c(c, c_ref, s, "hub rows, n=%d" % n)
 
 
+@pytest.mark.parametrize("n,ldb_pad,dtype", [(1024, 0, "f16"), (1032, 8, "bf16"), (1416, 0, "f16"), (1544, 0, "f16"), (2056, 0, "bf16"), (2568, 0, "f16")])
+def test_tiles_with_long_column_lists_among_more_workgroups_than_are_resident(n, ldb_pad, dtype):
+    # the same beside 293 tiles of one and two slabs: the rings of launches of up to six and nine to twelve column tiles, and of others
+    rng = np.random.default_rng(n)
+    k, hubs = 4800, 40
+    heights = [17, 16, 20] * 97 + [17, 16]
+    rows = [sorted(rng.choice(k, size=4700 - 37 * i, replace=False).tolist()) for i in range(hubs)]
+    for g, h in enumerate(heights):
+        blocks = np.sort(rng.choice(k // 32, size=1 + g % 3, replace=False))
+        rows += [(blocks[:, None] * 32 + np.arange(32)).reshape(-1).tolist()] * h
+    csr = csr_from_rows(rows, k, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, k, n, dtype)
+    perm, rg = np.arange(len(rows), dtype=np.int32), np.cumsum([0] + [1] * hubs + heights).astype(np.int32)
+    c, v = gpu_spmm(csr, perm, rg, 32, bits, ldb_pad=ldb_pad)
+    assert [p["kernel"] for p in v.launches(n)] == ["vbr_spmm_mixed_kernel"] and v.tile_ksteps().max() >= 128
+    assert v.launches(n)[0]["tiles"] * ((n + 255) // 256) > 1536
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c, c_ref, s, "hub rows among blocks, n=%d" % n)
+
+
 @pytest.mark.parametrize("n,ldb_pad,dtype", [(8, 0, "f16"), (64, 64, "bf16"), (248, 0, "f16"), (256, 0, "f16"), (1032, 8, "bf16")])
 def test_large_matrix_that_shares_nothing_is_multiplied_entry_by_entry(n, ldb_pad, dtype):
     # 8200 rows of 0 to 30 entries anywhere, some of 300 and one of 1500 (a wave, a workgroup for a row)
