@@ -58,7 +58,8 @@ inline ColumnMap column_map(uint32_t Q, bool even)
 
 // Workgroup -> (one of T tiles, one of Q column tiles); false: nothing to do.  Workgroups are dealt to the 8 L2 domains round-robin; a
 // domain keeps to few column tiles, every eighth, so that the B columns it gathers stay in its L2, and takes one after the other.  (Column tiles
-// side by side on a domain: 16 x 16 blocks, 4096 x 16384, N = 4096 165.4 and 165.3 us among other calls, 64 x 64 blocks at 40 %, N = 8192 471 and 477.)
+// side by side on a domain: 16 x 16 blocks, 4096 x 16384, N = 4096 160 and 175 us among other calls, 64 x 64 blocks at 40 %, N = 8192 396 and 487;
+// only in launches of the mixed kernel, graph of 16384 nodes, N = 4096 173.2 and 170.5, 40 other graphs the same.)
 // The column tiles left over when every domain has as many: a domain takes one or none, with fewer than 8 column tiles in all several domains
 // share one as long as there are domains.  Five or nine column tiles leave most domains half idle that way; `even` cuts each that is left over in
 // shares, 8 or 4 of its tiles' workgroups in turn, so that all domains have the same number, of two column tiles at most (what it gains and
