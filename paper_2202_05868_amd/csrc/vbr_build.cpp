@@ -983,6 +983,11 @@ void Builder::schedule()
         v->n_work = (int32_t)v->dev_tiles.size();
         v->class_count[tile_class(it.td)]++;
         if (it.td.n_ks >= kSplitSteps) v->long_count[tile_class(it.td)]++;
+        if (it.td.group >= kTileDeep) {                              // (of the four of a deep tile the first)
+            v->work_steps += it.td.n_ks;
+            ++v->work_lists;
+            v->longest_list = std::max(v->longest_list, it.td.n_ks);
+        }
     }
 }
 
@@ -1481,13 +1486,17 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         // workgroups: 13.1 and 9.7, 42.4 and 32.2, 63 and 52; N = 592, 1416 of them, 236 on the busiest domain: 33.2 and 24.5; 1744: 22.1 and 24.8,
         // 1776: 27.8 and 26.8, 2272: 43.1 and 47.2).
         const int64_t grid = grid_size(T, Qt);             // as if of whole column tiles
-        // Beyond, where the column tiles leave some domains with less than others or two domains to one column tile, the chip is not full at the end and the
-        // chains still count: up to six column tiles, as far as it was measured (graphs of 16384 nodes, two slots and four: 944 columns 48.9 and 35.5,
-        // 880 32.5 and 25.6, 1040 49.1 and 40.5, 1264 89.9 and 86.5, 1416 52.1 and 45.1; 15 graphs 15 % less) and nine to twelve (4096 nodes, 2144 columns
-        // 35.1 and 32.1; 8192, 2592: 48.8 and 44.3; 16384, 2552: 96.9 and 88.9, 2904: 203 and 198; 22 graphs 5 % less).  Seven and eight take the
-        // same on average (1664 columns 56.4 and 60.2, 1672: 60.5 and 57.8; 1952: 21.5 and 23.3), as do 13; 14 to 16 take more (3400: 46.0 and 49.3, 3720:
-        // 40.6 and 44.4, 3920: 37.6 and 41.6).
-        const int64_t deep_most = Qt <= 6 ? 6 : Qt >= 9 && Qt <= 12 ? 10 : 3;
+        // Beyond, only where the longest list is far longer than the others, five times the average and more, as in graphs with hubs: then its chain is
+        // what counts while others fill the chip (nine to twelve column tiles, up to ten rounds, graphs of 4096 nodes, 2144 columns 35.1 and 32.1; 8192, 2592:
+        // 48.8 and 44.3; 16384, 2552: 96.9 and 88.9; 86 products 8 % less, none more; up to six, where in addition it takes 3.5 times as long as all
+        // lists shared out among the 512 places: 16384 nodes, 816 columns 49.1 and 36.3, 1048 59.8 and 49.7, 1352 58.0 and 54.5, 13 products 18 % less, none
+        // more; below that 12 take from 7 % less to 6 % more).  Lists of like length, deep because the matrix is small, lose the places (64 x 64 blocks with
+        // noise, two slots and four: 2816 x 4224, 1424 columns 19.6 and 21.5; 3776 x 2880, 824: 23.6 and 25.6; 1728 x 5248, 2432: 18.5 and 20.6; groups of
+        // 1 to 100 rows, 1703 x 7440, 2624: 26.8 and 29.1; 65 products 3 % more).  Seven and eight column tiles take the same on average (1664 columns
+        // 56.4 and 60.2, 1672: 60.5 and 57.8; 1952: 21.5 and 23.3), as do 13; 14 to 16 take more (3400: 46.0 and 49.3, 3720: 40.6 and 44.4).
+        const bool hub = (int64_t)v->longest_list * v->work_lists >= 5 * v->work_steps;
+        const bool outlasts = 2 * (int64_t)v->longest_list * kTwoOnACu >= 7 * v->work_steps * Qt;
+        const int64_t deep_most = hub && Qt <= 6 && outlasts ? 6 : hub && Qt >= 9 && Qt <= 12 ? 10 : 3;
         const bool few = split || (v->class_count[kClassDeep] > 0 ? T * Qt <= deep_most * kTwoOnACu : grid <= kTwoOnACu && v->dev_tiles[0].n_ks >= (grid <= kTwoOnACu / 2 ? 5 : 18));
         // workgroups an L2 domain holds at once
         const int64_t at_once = (few || v->class_count[3] > 0 || kind == VBR_LAUNCH_TILE_4 ? kTwoOnACu : kind == VBR_LAUNCH_TILE_MIXED || kind == VBR_LAUNCH_GATHER_4 ? kThreeOnACu

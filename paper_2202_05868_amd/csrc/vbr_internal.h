@@ -278,6 +278,8 @@ struct vbr {
     int32_t n_work = 0;                         // of them with a K-step
     int32_t class_count[vbrk::kClasses] = {0};  // of these, per class ...
     int32_t long_count[vbrk::kClasses] = {0};   // ... and with at least kSplitSteps K-steps
+    int64_t work_steps = 0;                     // the K-steps of these, a deep tile once, ...
+    int32_t work_lists = 0, longest_list = 0;   // ... in how many lists, and of the longest one
     vbrk::HostValues vals;               // packed fragments: block tiles, panels, gathered tiles, then 1 KiB of zeros
     // Rows that are not multiplied in block tiles stand in a row list (prow): first those of groups of height < 16
     // ("low rows"), in an order of the packing's own, then those of taller groups whose blocks are mostly fill-in.

@@ -190,6 +190,54 @@ void check_plan()
     }
 }
 
+// `clusters` stretches of 16 rows, each a group of its own, that hold the same `len` of 4096 columns; before them 16 rows of `hub` columns.
+vbr_t *clusters(int n, int len, int hub)
+{
+    Csr a;
+    a.k = 4096;
+    a.row_ptr.push_back(0);
+    Rng rng(n + len);
+    std::vector<int32_t> all(4096);
+    for (int i = 0; i < 4096; ++i) all[(size_t)i] = i;
+    for (int s = hub ? -1 : 0; s < n; ++s) {
+        const int count = s < 0 ? hub : len;
+        for (int i = 0; i < count; ++i) std::swap(all[(size_t)i], all[(size_t)(i + rng.below(4096 - i))]);
+        std::sort(all.begin(), all.begin() + count);
+        for (int r = 0; r < 16; ++r) {
+            a.col.insert(a.col.end(), all.begin(), all.begin() + count);
+            a.row_ptr.push_back((int64_t)a.col.size());
+        }
+    }
+    a.m = (int64_t)a.row_ptr.size() - 1;
+    a.val.assign(a.col.size(), 0x3c00);
+    std::vector<int32_t> perm, rg;
+    for (int64_t i = 0; i < a.m; ++i) perm.push_back((int32_t)i);
+    for (int64_t i = 0; i <= a.m; ++i) rg.push_back((int32_t)i);
+    const vbr_csr_t c = a.view();
+    vbr_t *v = nullptr;
+    REQUIRE(vbr_build(&c, perm.data(), rg.data(), (int32_t)a.m, 32, &v) == VBR_OK);
+    return v;
+}
+
+// Deep tiles beyond 1536 workgroups: deep rings only where one list is far longer than the others, and up to six column tiles longer than all shared out.
+void check_deep_rings()
+{
+    ++g_cases;
+    struct { int n, len, hub; int64_t N; bool few; } const cases[] = {
+        {88, 544, 0, 1024, true},  {88, 544, 0, 1280, false}, {88, 544, 0, 1536, false}, {88, 544, 0, 2304, false}, {88, 544, 0, 3072, false},
+        {400, 64, 4096, 1280, true}, {400, 64, 4096, 1536, true}, {400, 64, 4096, 1792, false}, {400, 64, 4096, 2304, true}, {400, 64, 4096, 3328, false},
+        {300, 192, 1600, 1536, false}, {300, 192, 1600, 2304, true}};
+    for (const auto &x : cases) {
+        vbr_t *v = clusters(x.n, x.len, x.hub);
+        vbrk::Launch plan[VBR_MAX_LAUNCHES];
+        REQUIRE(vbrk::plan_launches(v, x.N, true, plan) == 1 && plan[0].kind == VBR_LAUNCH_TILE_MIXED && !plan[0].split);
+        REQUIRE(v->class_count[vbrk::kClassDeep] > 0 && (int64_t)plan[0].n_tiles * ((x.N + 255) / 256) > (x.N == 1024 ? 0 : 1536));
+        if (plan[0].few != x.few) std::fprintf(stderr, "%d clusters of %d, hub %d, N = %lld: few %d\n", x.n, x.len, x.hub, (long long)x.N, plan[0].few);
+        REQUIRE(plan[0].few == x.few);
+        vbr_free(v);
+    }
+}
+
 // Short lists are split, whatever the grid is rounded up to: the plans of a few tiles of one height and of two.
 void check_short_lists()
 {
@@ -419,6 +467,7 @@ int main()
         ++g_cases;
     }
     check_plan();
+    check_deep_rings();
     check_short_lists();
     check_map<false>();
     check_map<true>();
