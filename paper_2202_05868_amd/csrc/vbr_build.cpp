@@ -1380,8 +1380,10 @@ EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, i
     // ask for fewer rows of B in the L2 and leave the load path to those that take longest.  Eight, six and five workgroups on a CU: graph of 4096 nodes,
     // 39 edges a node, N = 2720 44.9, 40.8, 38.3 us; 94, 3408: 81.8, 77.1, 74.4; of 8192, 96, 256: 16.8, 16.4, 15.6; of 16384, 84, 256: 29.5, 28.1, 28.9; 34
     // graphs of 24 edges and more 2.7 % less with six (worst 3 % more) and 2 with five, of fewer edges 0 and 5 % more; like rows 1 % less and the
-    // same; short rows 3 and 11 % more.
-    L.six = !alike && longest > kEntryLongRow && nnz >= 24 * M;
+    // same; short rows 3 and 11 % more.  Waves of 128 and 256 columns ask for two and four times as much of B; with a row for a workgroup, six pay from 12
+    // entries on (16384 nodes, eight and six: 14 edges, N = 736 36.1 and 28.3, 760 42.9 and 32.9; 18, 736: 36.7 and 30.7; 8192, 18, 2792: 65.7 and 62.4;
+    // 4096, 17, 2152: 28.3 and 24.3; 70 graphs of 12 to 24 edges 4 % less, worst 3 % more).
+    L.six = !alike && ((longest > kEntryLongRow && nnz >= 24 * M) || (L.lanes > 8 && longest > kEntryHugeRow && nnz >= 12 * M));
     return L;
 }
 

@@ -358,6 +358,15 @@ void check_entry_plan()
         for (int64_t i = 1; i < x.rows; ++i) start.push_back(start.back() + x.len);
         REQUIRE(vbrk::plan_entry_rows(start, 16384, 1024, true).six == x.six);
     }
+    // ... with 12 where a wave takes 128 columns or more and a row has a workgroup
+    struct { int64_t len, longest, N; int lanes; bool six; } const wider[] = {{12, 1900, 736, 16, true}, {11, 1700, 736, 16, false}, {20, 1024, 1400, 16, false}, {20, 1030, 1400, 16, true}, {14, 2000, 256, 8, false}};
+    for (const auto &x : wider) {
+        std::vector<int64_t> start = {0, x.longest};
+        for (int64_t i = 1; i < 16384; ++i) start.push_back(start.back() + x.len);
+        const vbrk::EntryLaunch L = vbrk::plan_entry_rows(start, 16384, x.N, x.N % 64 == 0);
+        if (L.six != x.six || L.lanes != x.lanes) std::fprintf(stderr, "%lld entries, %lld, N = %lld: %d lanes, six %d\n", (long long)x.len, (long long)x.longest, (long long)x.N, L.lanes, L.six);
+        REQUIRE(L.six == x.six && L.lanes == x.lanes);
+    }
     // widths of as many column tiles have as many lanes, rows of B padded to a cache line or not; long rows, in waves and workgroups of their own
     struct { int64_t rows, len, longest, n_cols, first_N, last_N; bool aligned; int lanes; } const widths[] = {
         {16384, 5, 5, 16384, 72, 256, true, 8},     {20000, 5, 5, 20000, 264, 320, true, 8},   {20000, 5, 5, 20000, 456, 512, true, 8},  {20000, 4, 4, 20000, 264, 1024, true, 16},
