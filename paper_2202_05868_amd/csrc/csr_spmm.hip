@@ -83,11 +83,12 @@ __device__ __forceinline__ uint32_t half_turn(uint32_t x)    // the halves of ev
 // cycles, a word a lane 7, two words 17: so an entry whose column fits 16 bits is one word (NEAR), any other and a row's description are one load each.
 // (Words against two words, both with eight waves a SIMD: 120 products of the cases' ranges 3 % less on average, 3648 x 4864, 253 entries a row, N = 88
 // 15.1 and 12.7 us, 32768 x 32768, 16 a row, N = 256 24.9 and 23.0.)  A row leaves through LDS: see there.
+// TOGETHER: every eight loads a wave waits for all of them, which keeps the waves in step (plan_entry_rows says where that pays).
 // Up to 64 registers, eight waves a SIMD; where the compiler keeps values across a branch at a row's end it takes more.
 // Measured on a graph of 16384 nodes with 426 000 entries (rows of 0 to 3600), with B and C beyond the caches, N = 4096: 214 us with the waits of a
 // batch for all of its loads, columns and values apart and 16 bytes of every 32 a store, 197 with entries of two words, now 194 (18.0 TB/s of gathered B,
 // texture-address unit 84 % busy).
-template <int DT, bool WIDE, int LANES, bool NEAR>
+template <int DT, bool WIDE, int LANES, bool NEAR, bool TOGETHER = false>
 __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryParams p)
 {
     constexpr bool kPair = LANES == 8;                               // 16 lanes own a row, two entries at a time
@@ -181,6 +182,9 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
             __builtin_amdgcn_sched_barrier(0);
         });
     };
+    auto keep_step = [&]() {
+        if constexpr (TOGETHER) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
     constexpr constant<0> c0;
     constexpr constant<4> c4;
     constexpr constant<8> c8;
@@ -199,6 +203,7 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
                 for (; left > 24; left -= 16) {
                     const uint32_t now = a;
                     take();
+                    keep_step();
                     fetch(++batch);
                     go_on(c0, now, c8, c0);
                 }
@@ -217,10 +222,12 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
         } else {
             issue(c8, c0);
             for (; left > 20; left -= 16) {
+                keep_step();
                 fetch(batch++);
                 go_on(c0, a, c8, c8);
                 const uint32_t now = a;
                 take();
+                keep_step();
                 go_on(c8, now, c8, c0);
             }
             // 5 to 20 are left, eight of them on their way: those beyond 12, and the last four of more than eight
@@ -295,8 +302,9 @@ __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryPara
 
 using EntryKernel = void (*)(EntryParams);
 template <int DT, bool NEAR>
-constexpr EntryKernel entry_kernels[6] = {entry_rows_kernel<DT, false, 8, NEAR>, entry_rows_kernel<DT, false, 16, NEAR>, entry_rows_kernel<DT, false, 32, NEAR>,
-                                          entry_rows_kernel<DT, true, 8, NEAR>, entry_rows_kernel<DT, true, 16, NEAR>, entry_rows_kernel<DT, true, 32, NEAR>};
+constexpr EntryKernel entry_kernels[9] = {entry_rows_kernel<DT, false, 8, NEAR>, entry_rows_kernel<DT, false, 16, NEAR>, entry_rows_kernel<DT, false, 32, NEAR>,
+                                          entry_rows_kernel<DT, true, 8, NEAR>, entry_rows_kernel<DT, true, 16, NEAR>, entry_rows_kernel<DT, true, 32, NEAR>,
+                                          entry_rows_kernel<DT, false, 8, NEAR, true>, entry_rows_kernel<DT, false, 16, NEAR, true>, entry_rows_kernel<DT, false, 32, NEAR, true>};
 
 inline int64_t align_up256(int64_t x) { return (x + 255) / 256 * 256; }
 
@@ -323,7 +331,7 @@ int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &r
     p.n_long = L.n_long;
     p.n_waves = (int32_t)L.waves;
     if (L.waves > INT32_MAX || L.grid > INT32_MAX) return VBR_EUNSUPPORTED;
-    const int variant = (wide ? 3 : 0) + (L.lanes == 32 ? 2 : L.lanes == 16 ? 1 : 0);
+    const int variant = (wide ? 3 : L.together ? 6 : 0) + (L.lanes == 32 ? 2 : L.lanes == 16 ? 1 : 0);
     const EntryKernel kernel = dtype == VBR_F16 ? (rows.near ? entry_kernels<VBR_F16, true>[variant] : entry_kernels<VBR_F16, false>[variant])
                                                 : (rows.near ? entry_kernels<VBR_BF16, true>[variant] : entry_kernels<VBR_BF16, false>[variant]);
     const int lds = L.lanes == 32 ? kPartialBytes<32> + kTurnedBytes<32> : L.lanes == 16 ? kPartialBytes<16> + kTurnedBytes<16> : kPartialBytes<8> + kTurnedBytes<8>;

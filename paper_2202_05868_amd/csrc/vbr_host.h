@@ -31,8 +31,8 @@ struct EntryRowsDev {
     const void *entry;
     bool near;
 };
-// six: only six workgroups on a CU at a time, of the eight that fit
-struct EntryLaunch { int32_t lanes, n_huge, n_long; int64_t waves, grid; bool even, six; };
+// six: only six workgroups on a CU at a time, of the eight that fit; together: waves wait for all of their loads of B every eight of them
+struct EntryLaunch { int32_t lanes, n_huge, n_long; int64_t waves, grid; bool even, six, together; };
 // the launch for dense width N; aligned: rows of B begin on a cache line
 EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned);
 int launch_entry_rows(const EntryLaunch &L, int32_t dtype, const EntryRowsDev &rows, int64_t n_rows, int64_t n_cols,

@@ -367,6 +367,18 @@ void check_entry_plan()
         if (L.six != x.six || L.lanes != x.lanes) std::fprintf(stderr, "%lld entries, %lld, N = %lld: %d lanes, six %d\n", (long long)x.len, (long long)x.longest, (long long)x.N, L.lanes, L.six);
         REQUIRE(L.six == x.six && L.lanes == x.lanes);
     }
+    // waves that keep step: 128 and 256 columns of a B that does not stay, all resident, rows of like length that use rows of B now and then
+    struct { int64_t rows, len, longest, n_cols, N; bool together; } const steps[] = {
+        {2048, 48, 64, 20000, 1024, true},  {2048, 48, 64, 70000, 1024, true},  {4096, 48, 64, 20000, 200, true},   {4096, 48, 64, 70000, 200, true}, {8192, 128, 150, 32768, 200, true}, {4096, 256, 300, 32768, 200, true},
+        {8192, 128, 257, 32768, 200, false}, {8192, 31, 50, 32768, 200, false}, {8192, 128, 150, 26000, 200, false}, {8192, 128, 150, 32768, 64, false}, {4096, 60, 64, 10400, 200, false},
+        {4096, 48, 64, 10600, 200, true},   {8192, 128, 150, 65536, 128, true}, {4096, 48, 64, 40000, 128, true}, {4096, 48, 64, 32768, 128, false}, {4507, 486, 560, 132664, 64, false}, {4000, 48, 64, 20000, 200, false},  {16384, 64, 90, 32768, 200, true},   {16392, 64, 90, 32768, 200, false}};
+    for (const auto &x : steps) {
+        std::vector<int64_t> start = {0, x.longest};
+        for (int64_t i = 1; i < x.rows; ++i) start.push_back(start.back() + x.len);
+        const vbrk::EntryLaunch L = vbrk::plan_entry_rows(start, x.n_cols, x.N, x.N % 64 == 0);
+        if (L.together != x.together) std::fprintf(stderr, "%lld x %lld, %lld entries, N = %lld: %d lanes, grid %lld, together %d\n", (long long)x.rows, (long long)x.n_cols, (long long)x.len, (long long)x.N, L.lanes, (long long)L.grid, L.together);
+        REQUIRE(L.together == x.together);
+    }
     // widths of as many column tiles have as many lanes, rows of B padded to a cache line or not; long rows, in waves and workgroups of their own
     struct { int64_t rows, len, longest, n_cols, first_N, last_N; bool aligned; int lanes; } const widths[] = {
         {16384, 5, 5, 16384, 72, 256, true, 8},     {20000, 5, 5, 20000, 264, 320, true, 8},   {20000, 5, 5, 20000, 456, 512, true, 8},  {20000, 4, 4, 20000, 264, 1024, true, 16},

@@ -906,6 +906,19 @@ def test_csr_comparator_at_every_length_of_a_rows_end(n, ldb_pad, dtype):
     assert torch.equal(again.cpu()[short], c.cpu()[short]) and not torch.isfinite(again.cpu()[~short]).any()
 
 
+@pytest.mark.parametrize("rows,n,n_cols,dtype", [(2048, 1024, 20000, "f16"), (2048, 1024, 70000, "bf16"), (4096, 200, 20000, "bf16"), (4096, 200, 70000, "f16"), (4096, 128, 40000, "f16"), (4096, 128, 70000, "bf16")])
+def test_csr_comparator_with_waves_that_keep_step(rows, n, n_cols, dtype):
+    # rows of 33 to 64 entries of a B that does not stay in an L2, all resident, with 64, 128 and 256 columns a wave and entries of one and of two words
+    import torch
+    rng = np.random.default_rng(n)
+    csr = csr_from_rows([np.sort(rng.choice(n_cols, size=33 + i % 32, replace=False)).tolist() for i in range(rows)], n_cols, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, n_cols, n, dtype)
+    c = binding.CsrDev(csr).upload("cuda:0").spmm(torch_io.bits_to_device(bits, dtype))
+    torch.cuda.synchronize()
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr %d rows, n=%d" % (rows, n))
+
+
 @pytest.mark.parametrize("n", [24, 72, 208])
 @pytest.mark.parametrize("n_cols,dtype", [(65535, "f16"), (65536, "f16"), (65536, "bf16"), (65537, "bf16"), (70000, "f16")])
 def test_entries_of_one_and_of_two_words(n_cols, dtype, n):
