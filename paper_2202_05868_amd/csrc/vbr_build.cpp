@@ -1297,7 +1297,9 @@ static bool even_columns(int64_t T, int64_t Q)
 // 21 K-steps 186 and 163, 11: 136 and 126, 5: 91.3 and 88.9, 3: 71.5 and 71.4; 96 tiles, 1: 42.4 and 43.0.  Tiles have to be of like length: a
 // workgroup of the wide kernel takes half as long again for a K-step, which a few long tiles would make the whole launch wait for.  Against up to 1024
 // columns it has nothing to save, A and B stay in the L2 (512 tiles of 33 rows, 5 K-steps, N = 1024: 26.8 and 30.0; 256 of 64, N = 648: 20.5 and 18.5,
-// N = 1024: 21.4 and 21.7).
+// N = 1024: 21.4 and 21.7).  512 columns of more than 12288 rows of B are three times the L2: where tiles ask for them often, half as wide ones stay there better
+// (195 tiles of 47 rows, 24 K-steps, 12544 rows, N = 2272: 73.4 and 92.0; 134, 27, 13504, 3072: 69.5 and 80.4; 230, 15, 16272, 3840: 124 and 138; 29 products
+// 1.5 % more; 42 that use them up to four times 4 % less).
 static bool wide_pays(const vbr *v, int64_t T, int64_t N)
 {
     constexpr int64_t kHere = kTwoOnACu / kXcd;
@@ -1306,6 +1308,7 @@ static bool wide_pays(const vbr *v, int64_t T, int64_t N)
         return n / kHere * full + (over > kHere / 2 ? full : over > 0 ? half : 0);
     };
     const int32_t longest = v->dev_tiles[0].n_ks, median = v->dev_tiles[(size_t)v->n_work / 2].n_ks;
+    if (v->n_cols > 12288 && v->work_steps * kStepK > 4 * v->n_cols) return false;
     return N > 1024 && longest >= 4 && longest <= 2 * median && 10 * (10 + cost(kWideN, 100, 77)) <= 9 * cost(kTileN, 62, 50);
 }
 

@@ -219,6 +219,50 @@ vbr_t *clusters(int n, int len, int hub)
     return v;
 }
 
+// `groups` groups of 64 rows that hold n_ks blocks of 32 columns each, others for every group; the first `first` blocks
+vbr_t *blocks_of(int groups, int n_ks, int64_t n_cols, int first)
+{
+    Csr a;
+    a.m = (int64_t)groups * 64;
+    a.k = n_cols;
+    a.row_ptr.push_back(0);
+    std::vector<int32_t> perm, rg = {0};
+    for (int g = 0; g < groups; ++g) {
+        std::vector<int32_t> cols;
+        const int n = g == 0 ? first : n_ks;
+        for (int i = 0; i < n; ++i)
+            for (int c = 0; c < 32; ++c) cols.push_back((int32_t)((g * 5 + i * (n_cols / 32 / n)) % (n_cols / 32)) * 32 + c);
+        std::sort(cols.begin(), cols.end());
+        for (int r = 0; r < 64; ++r) {
+            a.col.insert(a.col.end(), cols.begin(), cols.end());
+            a.row_ptr.push_back((int64_t)a.col.size());
+            perm.push_back((int32_t)perm.size());
+        }
+        rg.push_back((int32_t)perm.size());
+    }
+    a.val.assign(a.col.size(), 0x3c00);
+    const vbr_csr_t c = a.view();
+    vbr_t *v = nullptr;
+    REQUIRE(vbr_build(&c, perm.data(), rg.data(), groups, 32, &v) == VBR_OK);
+    return v;
+}
+
+// The wide kernel: not where 512 columns of B are far beyond the L2 and used often.
+void check_wide()
+{
+    ++g_cases;
+    struct { int groups, n_ks; int64_t n_cols, N; int first; bool wide; } const cases[] = {
+        {128, 12, 12288, 4096, 12, true}, {128, 12, 12320, 4096, 12, true}, {128, 13, 12288, 4096, 13, true}, {128, 13, 12320, 4096, 13, false}, {128, 13, 12320, 1024, 13, false}};
+    for (const auto &x : cases) {
+        vbr_t *v = blocks_of(x.groups, x.n_ks, x.n_cols, x.first);
+        vbrk::Launch plan[VBR_MAX_LAUNCHES];
+        REQUIRE(vbrk::plan_launches(v, x.N, true, plan) == 1 && plan[0].kind == VBR_LAUNCH_TILE_4 && !plan[0].split);
+        if (plan[0].wide != x.wide) std::fprintf(stderr, "%d tiles, %d K-steps, %lld rows of B, N = %lld: wide %d\n", x.groups, x.n_ks, (long long)x.n_cols, (long long)x.N, plan[0].wide);
+        REQUIRE(plan[0].wide == x.wide);
+        vbr_free(v);
+    }
+}
+
 // Deep tiles beyond 1536 workgroups: deep rings only where one list is far longer than the others, and up to six column tiles longer than all shared out.
 void check_deep_rings()
 {
@@ -489,6 +533,7 @@ int main()
     }
     check_plan();
     check_deep_rings();
+    check_wide();
     check_short_lists();
     check_map<false>();
     check_map<true>();
