@@ -1295,7 +1295,10 @@ static bool even_columns(int64_t T, int64_t Q)
 // and 396; 42 K-steps: 1024 24.3 and 28.0, 2048 42.0 and 40.5, 4096 86 and 81, 8192 184 and 153; 6144 rows (96 tiles), 98 K-steps: 2048 81 and 77, 3072
 // 118 and 133, 4096 150 and 135, 8192 286 and 235; 64 tiles, 68: 4096 65.8 and 66.0, 8192 146 and 113.  Short lists mostly store: 132 tiles, N = 8192,
 // 21 K-steps 186 and 163, 11: 136 and 126, 5: 91.3 and 88.9, 3: 71.5 and 71.4; 96 tiles, 1: 42.4 and 43.0.  Tiles have to be of like length: a
-// workgroup of the wide kernel takes half as long again for a K-step, which a few long tiles would make the whole launch wait for.  Against up to 1024
+// workgroup of the wide kernel takes half as long again for a K-step, which a few long tiles would make the whole launch wait for, all the more
+// where they are few and a domain has two column tiles and more at a time (K-steps of the longest and half of all, 40 tiles of 48 rows, 64 and 36, N = 5168: 54.8 and
+// 66.1; 37, 124 and 69, 5952: 78.7 and 84.5; 32, 26 and 16, 7456: 26.8 and 28.3; 11 such products 3 % more; 38, 41 of all, 6200: 71.3 and 70.1; 48 tiles, 46 and
+// 28, 4608: 40.1 and 37.5).  Against up to 1024
 // columns it has nothing to save, A and B stay in the L2 (512 tiles of 33 rows, 5 K-steps, N = 1024: 26.8 and 30.0; 256 of 64, N = 648: 20.5 and 18.5,
 // N = 1024: 21.4 and 21.7).  512 columns of more than 12288 rows of B are three times the L2: where tiles ask for them often, half as wide ones stay there better
 // (195 tiles of 47 rows, 24 K-steps, 12544 rows, N = 2272: 73.4 and 92.0; 134, 27, 13504, 3072: 69.5 and 80.4; 230, 15, 16272, 3840: 124 and 138; 29 products
@@ -1309,7 +1312,7 @@ static bool wide_pays(const vbr *v, int64_t T, int64_t N)
     };
     const int32_t longest = v->dev_tiles[0].n_ks, median = v->dev_tiles[(size_t)v->n_work / 2].n_ks;
     if (v->n_cols > 12288 && v->work_steps * kStepK > 4 * v->n_cols) return false;
-    return N > 1024 && longest >= 4 && longest <= 2 * median && 10 * (10 + cost(kWideN, 100, 77)) <= 9 * cost(kTileN, 62, 50);
+    return N > 1024 && longest >= 4 && 10 * longest <= (T < 44 ? 14 : 20) * median && 10 * (10 + cost(kWideN, 100, 77)) <= 9 * cost(kTileN, 62, 50);
 }
 
 EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned)

@@ -247,12 +247,13 @@ vbr_t *blocks_of(int groups, int n_ks, int64_t n_cols, int first)
     return v;
 }
 
-// The wide kernel: not where 512 columns of B are far beyond the L2 and used often.
+// The wide kernel: not where 512 columns of B are far beyond the L2 and used often, nor where one list is longer than the others, the less of few tiles.
 void check_wide()
 {
     ++g_cases;
     struct { int groups, n_ks; int64_t n_cols, N; int first; bool wide; } const cases[] = {
-        {128, 12, 12288, 4096, 12, true}, {128, 12, 12320, 4096, 12, true}, {128, 13, 12288, 4096, 13, true}, {128, 13, 12320, 4096, 13, false}, {128, 13, 12320, 1024, 13, false}};
+        {128, 12, 12288, 4096, 12, true}, {128, 12, 12320, 4096, 12, true}, {128, 13, 12288, 4096, 13, true}, {128, 13, 12320, 4096, 13, false}, {128, 13, 12320, 1024, 13, false},
+        {43, 10, 8192, 5632, 14, true}, {43, 10, 8192, 5632, 15, false}, {44, 10, 8192, 5632, 20, true}, {44, 10, 8192, 5632, 21, false}};
     for (const auto &x : cases) {
         vbr_t *v = blocks_of(x.groups, x.n_ks, x.n_cols, x.first);
         vbrk::Launch plan[VBR_MAX_LAUNCHES];
