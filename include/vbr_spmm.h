@@ -155,8 +155,9 @@ int vbr_spmm(const vbr_t *v, const void *B_dev, int64_t ldb, float *C_dev, int64
  * The kernel launches one vbr_spmm call with dense width N issues, in issue order (for reporting), for a B
  * whose rows follow each other without padding from a 128-byte aligned address on (ldb = N).  vbr_spmm
  * plans likewise with the ldb and the address it is given: with rows of B that begin inside a cache line where N is a
- * multiple of 64, or on one where it is not, the launches, their kernels and tiles are the same, the grid sizes
- * may differ (whether a launch is split over the K-steps, how many columns a wave of the entry-row kernel takes).
+ * multiple of 64, or on one where it is not, the launches, their kinds and tiles are the same, the grid sizes
+ * may differ (whether a launch is split over the K-steps, how many columns a wave of the entry-row kernel takes), and
+ * with them the function that runs; a B that spans 4 GiB or more never has the wide kernel (vbr_get_launch_functions).
  * Rows of groups lower than 16 rows stand in a list of their own.  128 of them may be a panel (their slabs of 16 rows
  * share the B rows of the union of their column blocks), where that needs fewer loads; the others form column-gathered
  * tiles of 1 to 4 slabs (every tile loads exactly the B rows of the columns its rows touch).  The other groups are
@@ -179,6 +180,14 @@ enum {
 };
 int vbr_get_launches(const vbr_t *v, int64_t N, int32_t *n_launches, int32_t *kinds, int64_t *tiles,
                      int64_t *workgroups);
+
+/*
+ * The functions these launches run, as a profiler shows them: names[i] (room for VBR_MAX_LAUNCHES entries; static strings)
+ * of launch i of vbr_get_launches.  Tiles of one kind have up to three: VBR_LAUNCH_TILE_* and VBR_LAUNCH_GATHER_* run
+ * vbr_spmm_kernel, 256 columns of C a workgroup, or vbr_spmm_split_kernel, 64 columns, whose waves split the K-steps;
+ * VBR_LAUNCH_TILE_4 with long lists against a wide B also vbr_spmm_wide_kernel, 512 columns.
+ */
+int vbr_get_launch_functions(const vbr_t *v, int64_t N, const char **names);
 
 /*
  * Number of workgroup tiles and panels, and of K-steps, of the schedule, and of packed 16-bit values (for reporting).  A

@@ -26,7 +26,8 @@ _TORCH_DTYPES = {"f16": torch.float16, "bf16": torch.bfloat16}
 EXPORTS = ("sa1_reorder", "vbr_build", "vbr_get_index", "vbr_unpack_block", "vbr_device_bytes",
            "vbr_upload", "vbr_spmm", "vbr_get_schedule", "vbr_free", "vbr_strerror",
            "vbr_last_hip_error", "sa1_blocking_curve", "csr_spmm_create", "csr_device_bytes", "csr_upload",
-           "csr_spmm", "csr_free", "vbr_probe_launch", "vbr_get_launches", "vbr_audit", "vbr_get_tile_ksteps")
+           "csr_spmm", "csr_free", "vbr_probe_launch", "vbr_get_launches", "vbr_audit", "vbr_get_tile_ksteps",
+           "vbr_get_launch_functions")
 
 
 class VbrError(RuntimeError):
@@ -62,6 +63,8 @@ def _load():
     lib.vbr_get_schedule.argtypes = [vp, P(i64), P(i64), P(i64)]
     lib.vbr_get_launches.argtypes = [vp, i64, P(i32), vp, vp, vp]
     lib.vbr_get_launches.restype = ctypes.c_int
+    lib.vbr_get_launch_functions.argtypes = [vp, i64, P(ctypes.c_char_p)]
+    lib.vbr_get_launch_functions.restype = ctypes.c_int
     lib.vbr_get_tile_ksteps.argtypes = [vp, vp, i64]
     lib.vbr_get_tile_ksteps.restype = i64
     lib.vbr_audit.argtypes = [vp]
@@ -230,7 +233,8 @@ class Vbr:
 
     def launches(self, n: int) -> list:
         """The kernel launches one ``spmm`` with a B of shape [K, n], rows not padded, issues, from the library's plan (with padded
-        rows or a slice the grid sizes may differ)."""
+        rows or a slice the grid sizes may differ, and the functions).  ``kernel`` says what kind of tiles a launch has,
+        ``function`` the function that runs, as a profiler shows it."""
         kinds = np.zeros(16, dtype=np.int32)
         tiles = np.zeros(16, dtype=np.int64)
         wgs = np.zeros(16, dtype=np.int64)
@@ -239,8 +243,12 @@ class Vbr:
                                    tiles.ctypes.data_as(ctypes.c_void_p), wgs.ctypes.data_as(ctypes.c_void_p))
         if rc != 0:
             raise VbrError(rc, "vbr_get_launches")
-        return [dict(kernel=self.LAUNCH_KINDS[int(kinds[i])], tiles=int(tiles[i]), workgroups=int(wgs[i]))
-                for i in range(cnt.value)]
+        names = (ctypes.c_char_p * 16)()
+        rc = _lib.vbr_get_launch_functions(self._h, int(n), names)
+        if rc != 0:
+            raise VbrError(rc, "vbr_get_launch_functions")
+        return [dict(kernel=self.LAUNCH_KINDS[int(kinds[i])], tiles=int(tiles[i]), workgroups=int(wgs[i]),
+                     function=names[i].decode()) for i in range(cnt.value)]
 
     def unpack_block(self, blk: int, h: int, col_block: int) -> np.ndarray:
         out = np.empty((h, col_block), dtype=np.uint16)

@@ -1582,6 +1582,23 @@ extern "C" int vbr_get_launches(const vbr_t *v, int64_t N, int32_t *n_launches, 
     return VBR_OK;
 }
 
+extern "C" int vbr_get_launch_functions(const vbr_t *v, int64_t N, const char **names)
+{
+    if (!v || !names || N < 0) return VBR_EINVAL;
+    vbrk::Launch plan[VBR_MAX_LAUNCHES];
+    const int n = (N == 0 || v->n_rows == 0) ? 0 : vbrk::plan_launches(v, N, N % 64 == 0, plan);
+    for (int i = 0; i < n; ++i) {
+        switch (plan[i].kind) {
+        case VBR_LAUNCH_PANEL: names[i] = "vbr_spmm_panel_kernel"; break;
+        case VBR_LAUNCH_TILE_MIXED: names[i] = "vbr_spmm_mixed_kernel"; break;
+        case VBR_LAUNCH_ENTRIES: names[i] = "entry_rows_kernel"; break;
+        case VBR_LAUNCH_ZERO_ROWS: names[i] = "vbr_spmm_zero_rows_kernel"; break;
+        default: names[i] = plan[i].split ? "vbr_spmm_split_kernel" : plan[i].wide ? "vbr_spmm_wide_kernel" : "vbr_spmm_kernel"; break;
+        }
+    }
+    return VBR_OK;
+}
+
 extern "C" int vbr_get_schedule(const vbr_t *v, int64_t *n_tiles, int64_t *n_ksteps, int64_t *packed_elems)
 {
     if (!v) return VBR_EINVAL;

@@ -443,6 +443,18 @@ def test_tiles_of_short_lists_hardly_count_for_the_split(height, n, long_groups,
     assert len(plan) == 1 and (plan[0]["workgroups"] >= 3 * tiles if split else plan[0]["workgroups"] <= tiles + 8), plan
 
 
+@pytest.mark.parametrize("height,groups,n_ks,n,function", [(64, 128, 5, 1920, "vbr_spmm_wide_kernel"), (64, 128, 5, 1024, "vbr_spmm_kernel"), (64, 43, 10, 5632, "vbr_spmm_wide_kernel"),
+                                                           (64, 10, 12, 256, "vbr_spmm_split_kernel"), (32, 300, 5, 1920, "vbr_spmm_kernel"), (16, 10, 12, 256, "vbr_spmm_split_kernel")])
+def test_launches_name_the_function_that_runs(height, groups, n_ks, n, function):
+    csr = full_csr(height * groups, 32 * n_ks)
+    v = binding.vbr_build(csr, np.arange(height * groups, dtype=np.int32), np.arange(0, height * groups + 1, height, dtype=np.int32), 32)
+    columns = {"vbr_spmm_wide_kernel": 512, "vbr_spmm_kernel": 256, "vbr_spmm_split_kernel": 64}[function]
+    plan = v.launches(n)
+    assert [(p["kernel"], p["function"]) for p in plan] == [("vbr_spmm_kernel<%d slab%s>" % (height // 16, "s" * (height > 16)), function)]
+    whole = groups * -(-n // columns)              # and the grid is rounded up for the domains
+    assert whole <= plan[0]["workgroups"] < 1.6 * whole + 8
+
+
 def test_launches_are_not_split_where_a_tile_that_cannot_be_takes_longest():
     csr = csr_from_rows([list(range(416))] * 180, 416)
     rg = np.array([0, 100, 120, 140, 160, 180], dtype=np.int32)         # one group of seven slabs, four of two
