@@ -279,8 +279,9 @@ def main() -> int:
     packed = v.schedule()["packed_elems"]
     flops_exec = min(flops_stored, 2.0 * packed * n)
     tflops_exec = flops_exec / (ms * 1e-3) * 1e-12
-    # compulsory HBM bytes of one multiply: packed A once, B once, C once
-    hbm_min = packed * 2 + a["n_cols"] * n * 2 + a["n_rows"] * n * 4
+    # compulsory HBM bytes of one multiply: packed A once (values; an entry row's entries with their columns), B once, C once
+    entries = v.launches(n)[0]["kernel"] == "entry_rows_kernel"
+    hbm_min = packed * (2 if not entries else 4 if a["n_cols"] <= 65536 else 8) + a["n_cols"] * n * 2 + a["n_rows"] * n * 4
     # the bound: the MFMA time of the executed flops against the compulsory HBM time
     t_mfma = flops_exec / (PEAK_MFMA_F16_TFLOPS * 1e12)
     t_hbm = hbm_min / (PEAK_HBM_GBS * 1e9)

@@ -191,7 +191,8 @@ int vbr_get_launch_functions(const vbr_t *v, int64_t N, const char **names);
 
 /*
  * Number of workgroup tiles and panels, and of K-steps, of the schedule, and of packed 16-bit values (for reporting).  A
- * matrix kept as entry rows (VBR_LAUNCH_ENTRIES) has none of either: n_tiles is its rows, n_ksteps 0.
+ * matrix kept as entry rows (VBR_LAUNCH_ENTRIES) has no tiles and no K-steps: n_tiles is its rows, n_ksteps 0, and
+ * packed_elems its entries, each of which takes 4 bytes with its column, 8 in matrices of more than 65536 columns.
  */
 int vbr_get_schedule(const vbr_t *v, int64_t *n_tiles, int64_t *n_ksteps, int64_t *packed_elems);
 

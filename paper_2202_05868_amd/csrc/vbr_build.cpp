@@ -1604,7 +1604,7 @@ extern "C" int vbr_get_schedule(const vbr_t *v, int64_t *n_tiles, int64_t *n_kst
     if (!v) return VBR_EINVAL;
     if (n_tiles) *n_tiles = v->by_entries ? v->n_rows : (int64_t)v->tiles.size() + (int64_t)v->panels.size() + (int64_t)v->gtiles.size();
     if (n_ksteps) *n_ksteps = v->ks_ptr.back() + (int64_t)v->pk_mask.size() + (int64_t)v->gcol.size() / vbrk::kStepK;
-    if (packed_elems) *packed_elems = v->by_entries ? v->entries.count + vbrk::kFragElems : (int64_t)v->vals.size();
+    if (packed_elems) *packed_elems = v->by_entries ? v->entries.count : (int64_t)v->vals.size();
     return VBR_OK;
 }
 

@@ -443,6 +443,21 @@ def test_tiles_of_short_lists_hardly_count_for_the_split(height, n, long_groups,
     assert len(plan) == 1 and (plan[0]["workgroups"] >= 3 * tiles if split else plan[0]["workgroups"] <= tiles + 8), plan
 
 
+@pytest.mark.parametrize("n_cols,entry_bytes", [(65536, 4), (65537, 8)])
+def test_a_matrix_kept_as_entries_reports_its_entries_and_holds_no_more(n_cols, entry_bytes):
+    rows, each = 9000, 6
+    cols = np.sort((np.arange(rows * each) * 7919 % n_cols).reshape(rows, each), axis=1).astype(np.int32)
+    csr = dict(n_rows=rows, n_cols=n_cols, nnz=rows * each, row_ptr=np.arange(rows + 1, dtype=np.int64) * each, col_idx=cols.reshape(-1),
+               vals=np.full(rows * each, 0x3c00, dtype=np.uint16), dtype="f16")
+    v = binding.vbr_build(csr, np.arange(rows, dtype=np.int32), np.arange(rows + 1, dtype=np.int32), 1)
+    v.audit()
+    assert [p["kernel"] for p in v.launches(256)] == ["entry_rows_kernel"]
+    assert v.schedule() == dict(n_tiles=rows, n_ksteps=0, packed_elems=rows * each)
+    # the entries, 16 bytes a row, the permutation; sections begin at multiples of 256 bytes
+    held = rows * each * entry_bytes + rows * (16 + 4)
+    assert held <= v.device_bytes() <= held + 10 * 256
+
+
 @pytest.mark.parametrize("height,groups,n_ks,n,function", [(64, 128, 5, 1920, "vbr_spmm_wide_kernel"), (64, 128, 5, 1024, "vbr_spmm_kernel"), (64, 43, 10, 5632, "vbr_spmm_wide_kernel"),
                                                            (64, 10, 12, 256, "vbr_spmm_split_kernel"), (32, 300, 5, 1920, "vbr_spmm_kernel"), (16, 10, 12, 256, "vbr_spmm_split_kernel")])
 def test_launches_name_the_function_that_runs(height, groups, n_ks, n, function):
