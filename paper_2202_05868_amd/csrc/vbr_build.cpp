@@ -1217,6 +1217,7 @@ extern "C" int vbr_audit(const vbr_t *v)
             if (r.row < 0 || r.row >= M || r.len < 0 || r.start != e.start[(size_t)i] || r.start + r.len != e.start[(size_t)i + 1]) return VBR_EINVAL;
             if (i > 0 && e.start[(size_t)i + 1] - e.start[(size_t)i] > e.start[(size_t)i] - e.start[(size_t)i - 1]) return VBR_EINVAL;
         }
+        if ((e.count + 1) * (e.near ? 4 : (int64_t)sizeof(Entry)) > (int64_t)e.bytes()) return VBR_EINVAL;      // the one behind the last is read, too
         for (int64_t i = 0; i < e.count; ++i)
             if (e.get(i).col < 0 || e.get(i).col >= K) return VBR_EINVAL;
     }

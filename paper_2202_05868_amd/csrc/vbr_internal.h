@@ -216,7 +216,7 @@ struct Entry {
     int32_t col;
     uint32_t val;
 };
-constexpr int kEntryPad = 8;         // entries of zeros behind the last one: eight are read at a time
+constexpr int kEntryPad = 1;         // entries of zeros behind the last one: rows without entries, which stand last, read the one at their start, without effect
 
 // A row of entries: the first of them, how many, and its row of C; 16 bytes, which one load brings.
 struct EntryRow {

@@ -441,6 +441,34 @@ void check_entry_plan()
         }
 }
 
+// A matrix kept as entries whose last rows have none: the entry behind the last one, which these read, lies in the buffer, and is zero.
+void check_last_entry()
+{
+    for (int64_t k : {65536, 65537}) {
+        ++g_cases;
+        Csr a;
+        a.m = 9000;
+        a.k = k;
+        a.row_ptr.push_back(0);
+        for (int64_t i = 0; i < a.m; ++i) {
+            for (int64_t j = 0; i < 8990 && j < 6; ++j) a.col.push_back((int32_t)(j * (k / 6) + i * 7 % (k / 6)));
+            a.row_ptr.push_back((int64_t)a.col.size());
+        }
+        a.val.assign(a.col.size(), 0x3c00);
+        std::vector<int32_t> perm, rg;
+        for (int64_t i = 0; i <= a.m; ++i) rg.push_back((int32_t)i);
+        perm.assign(rg.begin(), rg.end() - 1);
+        const vbr_csr_t c = a.view();
+        vbr_t *v = nullptr;
+        REQUIRE(vbr_build(&c, perm.data(), rg.data(), (int32_t)a.m, 1, &v) == VBR_OK && v->by_entries && vbr_audit(v) == VBR_OK);
+        const vbrk::EntryRows &e = v->entries;
+        REQUIRE(e.near == (k <= 65536) && e.row.back().len == 0 && e.row.back().start == e.count && e.count == (int64_t)a.col.size());
+        REQUIRE(e.get(e.count).col == 0 && e.get(e.count).val == 0);
+        REQUIRE(v->lay.gcol_off + (e.count + 1) * (e.near ? 4 : 8) <= vbr_device_bytes(v));
+        vbr_free(v);
+    }
+}
+
 // Every call with the first 0, 1, 2 ... of its allocations succeeding, up to `most` or until it gets all it asks for: it
 // reports the failure, and nothing is thrown through the C interface.
 template <class F>
@@ -540,6 +568,7 @@ int main()
     check_map<true>();
     check_split_tile();
     check_entry_plan();
+    check_last_entry();
     // memory that runs out: at every allocation of a small matrix, and at the first ones of a matrix whose check takes threads
     {
         check_out_of_memory(make(rng, 90, 20, 8, 0.2, 40), 8, 100000);
