@@ -260,6 +260,10 @@ void check_wide()
         REQUIRE(vbrk::plan_launches(v, x.N, true, plan) == 1 && plan[0].kind == VBR_LAUNCH_TILE_4 && !plan[0].split);
         if (plan[0].wide != x.wide) std::fprintf(stderr, "%d tiles, %d K-steps, %lld rows of B, N = %lld: wide %d\n", x.groups, x.n_ks, (long long)x.n_cols, (long long)x.N, plan[0].wide);
         REQUIRE(plan[0].wide == x.wide);
+        // its offsets reach 4 GiB less a page
+        const int64_t most = (0xFFFFF000ll / 2 - x.N) / (x.n_cols - 1) / 8 * 8;
+        REQUIRE(vbrk::plan_launches(v, x.N, true, plan, most) == 1 && plan[0].wide == x.wide);
+        REQUIRE(vbrk::plan_launches(v, x.N, true, plan, most + 8) == 1 && !plan[0].wide && plan[0].grid == vbrk::grid_size(x.groups, (x.N + 255) / 256, plan[0].even));
         vbr_free(v);
     }
 }
@@ -423,6 +427,23 @@ void check_entry_plan()
         const vbrk::EntryLaunch L = vbrk::plan_entry_rows(start, x.n_cols, x.N, x.N % 64 == 0);
         if (L.together != x.together) std::fprintf(stderr, "%lld x %lld, %lld entries, N = %lld: %d lanes, grid %lld, together %d\n", (long long)x.rows, (long long)x.n_cols, (long long)x.len, (long long)x.N, L.lanes, (long long)L.grid, L.together);
         REQUIRE(L.together == x.together);
+    }
+    // the widths the tests of every length of a row's end stand for: four rows of every length up to 45, long rows among many others, and both
+    for (int which : {0, 1, 2}) {
+        std::vector<int64_t> start = {0};
+        auto add = [&](int64_t first, int64_t last, int64_t step, int times) {
+            for (int64_t len = last; len >= first; len -= step)
+                for (int i = 0; i < times; ++i) start.push_back(start.back() + len);
+        };
+        if (which == 1) { add(1025, 1289, 8, 1); add(600, 600, 1, 500); add(257, 329, 1, 1); }
+        if (which == 2) { add(1025, 1169, 16, 1); add(257, 329, 8, 4); }
+        if (which != 1) add(0, 45, 1, 4);
+        for (int64_t N : {64, 120, 128, 200, 208, 256}) {
+            const bool aligned = N == 64 || N == (which == 2 ? 128 : 256);
+            REQUIRE(vbrk::plan_entry_rows(start, 1500, N, aligned).lanes == (aligned || which == 2 ? 8 : N <= 128 ? 16 : 32));
+        }
+        // B beyond 4 GiB: with rows that begin inside cache lines
+        if (which == 0) REQUIRE(vbrk::plan_entry_rows(start, 70000, 64, false).lanes == 8 && vbrk::plan_entry_rows(start, 65536, 128, false).lanes == 16 && vbrk::plan_entry_rows(start, 70000, 200, false).lanes == 32);
     }
     // widths of as many column tiles have as many lanes, rows of B padded to a cache line or not; long rows, in waves and workgroups of their own
     struct { int64_t rows, len, longest, n_cols, first_N, last_N; bool aligned; int lanes; } const widths[] = {

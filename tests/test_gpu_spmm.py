@@ -842,6 +842,62 @@ def test_right_hand_side_larger_than_4_gib():
     del big
 
 
+@pytest.mark.parametrize("n_cols,dtype", [(65536, "f16"), (65536, "bf16"), (70000, "f16"), (70000, "bf16")])
+def test_csr_comparator_with_a_right_hand_side_larger_than_4_gib(n_cols, dtype):
+    # rows of 0 to 45 entries, the last column among them, of one and of two words, with 64, 128 and 256 columns a wave; rows for a
+    # wave and for a workgroup; infinities in rows of B that only the long rows have
+    import torch
+    rng = np.random.default_rng(n_cols)
+    ld = 33000
+    short, long = np.repeat(np.arange(46), 4).tolist(), [257, 300, 520, 1030, 1200]
+    lists = [np.sort(rng.choice(n_cols - 1000, size=x, replace=False)).tolist() for x in rng.permutation(short)]
+    lists = [x[:-1] + [n_cols - 1] if x else x for x in lists]
+    big = torch.zeros((n_cols, ld), dtype=torch.float16 if dtype == "f16" else torch.bfloat16, device="cuda:0")
+    assert n_cols * ld * 2 > (1 << 32)
+    for rows in (lists, lists + [np.sort(rng.choice(n_cols, size=x, replace=False)).tolist() for x in long]):
+        csr = csr_from_rows(rows, n_cols, rng, dtype=dtype)
+        m = binding.CsrDev(csr).upload("cuda:0")
+        for n in (64, 128, 200):
+            bits = synth.dense_rhs(rng, n_cols, n, dtype)
+            b = big[:, 1000:1000 + n]
+            b.copy_(torch_io.bits_to_device(bits, dtype))
+            c = m.spmm(b)
+            torch.cuda.synchronize()
+            c_ref, s = oracle.spmm(csr, bits)
+            check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "B beyond 4 GiB, %d rows, n=%d" % (len(rows), n))
+            b[n_cols - 1000:n_cols - 1] = float("inf")
+            again = m.spmm(b)
+            torch.cuda.synchronize()
+            assert torch.equal(again.cpu()[:len(lists)], c.cpu()[:len(lists)])
+    del big, b
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_long_lists_against_a_wide_b_on_both_sides_of_4_gib(dtype):
+    # rows of B up to the last the offsets of the wide kernel reach, and one step beyond, where the tile kernel takes them
+    import torch
+    rng = np.random.default_rng(7)
+    n_cols, n, groups, h, cb = 2560, 1544, 128, 40, 64
+    lists = [(np.sort(rng.choice(n_cols // cb - 1, size=2, replace=False)).tolist() + [n_cols // cb - 1]) for _ in range(groups)]
+    csr = csr_from_rows([np.concatenate([np.arange(b * cb, (b + 1) * cb) for b in x]).tolist() for x in lists for _ in range(h)], n_cols, rng, dtype=dtype)
+    perm, rg = np.arange(groups * h, dtype=np.int32), np.arange(0, groups * h + 1, h, dtype=np.int32)
+    v = binding.vbr_build(csr, perm, rg, cb).upload("cuda:0")
+    v.audit()
+    assert [p["function"] for p in v.launches(n)] == ["vbr_spmm_wide_kernel"]
+    bits = synth.dense_rhs(rng, n_cols, n, dtype)
+    c_ref, s = oracle.spmm(csr, bits)
+    most = ((0xFFFFF000 // 2 - n) // (n_cols - 1)) // 8 * 8
+    flat = torch.zeros(n_cols * (most + 8), dtype=torch.float16 if dtype == "f16" else torch.bfloat16, device="cuda:0")
+    for ld in (most, most + 8):
+        b = flat[:n_cols * ld].view(n_cols, ld)[:, :n]
+        b.copy_(torch_io.bits_to_device(bits, dtype))
+        c = torch.full((groups * h, n), float("nan"), dtype=torch.float32, device="cuda:0")
+        v.spmm(b, c)
+        torch.cuda.synchronize()
+        check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "ldb = %d" % ld)
+    del flat, b
+
+
 # --------------------------------------------------------------------------- the CSR comparator kernel
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_csr_comparator_matches_oracle(dtype):
@@ -884,7 +940,7 @@ def test_csr_comparator_at_the_row_lengths_where_it_splits(n, ldb_pad, dtype):
 
 @pytest.mark.parametrize("n,ldb_pad,dtype", [(64, 0, "bf16"), (128, 0, "f16"), (200, 8, "bf16"), (256, 8, "f16")])
 def test_csr_comparator_at_every_length_of_a_rows_end(n, ldb_pad, dtype):
-    # four rows of every length, so that a wave has them alone: each way the loads in flight end, of rows for 16 and 32 lanes, and of the
+    # four rows of every length, so that a wave has them alone: each way the loads in flight end with 64 columns a wave, of rows for 16 lanes and of the
     # shares of rows for a wave and for a workgroup; infinities in the rows of B that only the longest rows have
     import torch
     rng = np.random.default_rng(n)
@@ -899,6 +955,31 @@ def test_csr_comparator_at_every_length_of_a_rows_end(n, ldb_pad, dtype):
     c_ref, s = oracle.spmm(csr, np.ascontiguousarray(bits[:, :n]))
     check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
     first = 20
+    b[first:] = float("inf")
+    short = np.diff(csr["row_ptr"]) <= first
+    again = m.spmm(b)
+    torch.cuda.synchronize()
+    assert torch.equal(again.cpu()[short], c.cpu()[short]) and not torch.isfinite(again.cpu()[~short]).any()
+
+
+@pytest.mark.parametrize("n,ldb_pad,dtype", [(128, 8, "f16"), (200, 8, "bf16"), (120, 0, "bf16"), (208, 0, "f16")])
+@pytest.mark.parametrize("long_rows", [False, True])
+def test_csr_comparator_at_every_length_of_a_rows_end_in_wide_waves(n, ldb_pad, dtype, long_rows):
+    # the same with 128 columns a wave up to N = 128 and 256 beyond: four rows of every length, which a wave has alone; then the shares of rows for a
+    # wave and for a workgroup among so many others that the waves stay as wide
+    import torch
+    rng = np.random.default_rng(n)
+    k = 1500
+    lens = list(range(257, 330)) + list(range(1025, 1290, 8)) + [600] * 500 if long_rows else np.repeat(np.arange(46), 4).tolist()
+    csr = csr_from_rows([list(range(x)) for x in rng.permutation(lens)], k, rng, dtype=dtype)
+    bits = synth.dense_rhs(rng, k, n + ldb_pad, dtype)
+    b = torch_io.bits_to_device(bits, dtype)[:, :n]
+    m = binding.CsrDev(csr).upload("cuda:0")
+    c = m.spmm(b)
+    torch.cuda.synchronize()
+    c_ref, s = oracle.spmm(csr, np.ascontiguousarray(bits[:, :n]))
+    check_c(c.cpu().numpy().astype(np.float64), c_ref, s, "csr n=%d" % n)
+    first = 300 if long_rows else 20
     b[first:] = float("inf")
     short = np.diff(csr["row_ptr"]) <= first
     again = m.spmm(b)
