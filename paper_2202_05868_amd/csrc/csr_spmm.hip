@@ -81,13 +81,17 @@ __device__ __forceinline__ uint32_t half_turn(uint32_t x)    // the halves of ev
 // Eight loads of B are in flight from a row's first entry to its last: an addition is followed by the load of the entry eight further on, whose column
 // was fetched a batch earlier, and no load stands in a branch, so that every wait is for one load and not for all.  A load of B takes the load path 17
 // cycles, a word a lane 7, two words 17: so an entry whose column fits 16 bits is one word (NEAR), any other and a row's description are one load each.
-// (Words against two words, both with eight waves a SIMD: 120 products of the cases' ranges 3 % less on average, 3648 x 4864, 253 entries a row, N = 88
-// 15.1 and 12.7 us, 32768 x 32768, 16 a row, N = 256 24.9 and 23.0.)  A row leaves through LDS: see there.
+// (Two words and one, and from six or seven waves a SIMD to eight for fp16: 3648 x 4864, 253 entries a row, N = 88 14.9 and 13.9 us, 32768 x 32768, 16 a row,
+// N = 256 22.5 and 21.3, the graph below 199 and 196; 120 products of the cases' ranges 3 % less by the word alone.)  A row leaves through LDS: see there.
 // TOGETHER: every eight loads a wave waits for all of them, which keeps the waves in step (plan_entry_rows says where that pays).
 // Up to 64 registers, eight waves a SIMD; where the compiler keeps values across a branch at a row's end it takes more.
-// Measured on a graph of 16384 nodes with 426 000 entries (rows of 0 to 3600), with B and C beyond the caches, N = 4096: 214 us with the waits of a
-// batch for all of its loads, columns and values apart and 16 bytes of every 32 a store, 197 with entries of two words, now 194 (18.0 TB/s of gathered B,
-// texture-address unit 84 % busy).
+// WIDE, a B of 4 GiB and more, has 64-bit addresses: there an entry that is not there is a branch around its load, waits are for what the branch may have
+// left open, and 62 to 74 registers leave six to eight waves a SIMD.  Against columns and values apart and waits for a batch (32768 x 65536, 16 a row, rows of B
+// 66 kB apart, N = 64 33.7 and 33.6, 256: 54.3 and 52.8, 4096: 828 and 801; rows of 6 to 4000, 16384 x 65536: 30.1 and 28.6, 44.5 and 42.4, 467 and 436;
+// two words, 32768 x 100000: 11.5 and 11.9, 50.0 and 49.9, 589 and 592).
+// Measured on a graph of 16384 nodes with 426 000 entries (rows of 0 to 3600), with B and C beyond the caches, N = 4096: 215 us with the waits of a
+// batch for all of its loads, columns and values apart and 16 bytes of every 32 a store, 199 with entries of two words, now 196 (17.8 TB/s of gathered B,
+// texture-address unit 83 % busy).
 template <int DT, bool WIDE, int LANES, bool NEAR, bool TOGETHER = false>
 __global__ void __launch_bounds__(kCsrThreads) entry_rows_kernel(const EntryParams p)
 {

@@ -709,7 +709,7 @@ constexpr int kWideWaveN = kWideN / 4;           // C columns per wave of the wi
 //   - the fragments of A, the same for all waves, go through registers into LDS, two K-steps at a time, one slab a wave, two K-steps ahead, with one
 //     barrier; 512 columns instead of 256 also halve what is fetched of A, which comes from beyond the L2;
 //   - rows of the next K-step are requested as soon as the registers of this one's are free, before its 32 matrix instructions.
-// Bound by the load path, 36 KiB a K-step of 64 x 512 (texture-address unit 86 % busy), then by the matrix unit (59 %).
+// Bound by the load path, 36 KiB a K-step of 64 x 512 (texture-address unit 82 % busy), then by the matrix unit (68 %).
 // Blocks of 64 x 64 at 40 %, 8192 x 8192, N = 8192: 473 -> 392 us (with fragments that are always in the L2 371); at 4096 x 4096, N = 4096: 63.4 -> 58.3.
 // The same for tiles of one and two slabs is slower (16 x 16 blocks at 10 %, N = 4096: 163 and 200; 32 x 32, 102 and 107): more waves ask for more
 // parts of B at a time than stay in the L2.

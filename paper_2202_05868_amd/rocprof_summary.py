@@ -2,6 +2,9 @@
 that is kept under ``profiles/``.
 
     python -m paper_2202_05868_amd.rocprof_summary --workload c4 --out /tmp/prof_c4
+    python -m paper_2202_05868_amd.rocprof_summary --case csr_graph --out /tmp/prof_csr
+
+(the second form profiles a multiply of ``perf/cases.py``, run by this file itself with ``--run-case``.)
 
 Runs, one after the other, each as its own process and under its own time limit:
 
@@ -16,7 +19,7 @@ that let the clocks settle, the warm-up and the timed steps.  The summary theref
 average over the dispatches of the TIMED steps (the last ``steps`` calls) beside the average over
 all dispatches, and the ``ms_per_step`` the benchmark printed in that same run.  HBM bytes are the
 counters scaled by what they read for a plain 256 MiB streaming kernel in the same process.
-This process never touches the GPU itself; the profiled program is the one named after ``--``.
+The process that collects never touches the GPU itself; the profiled program is the one named after ``--``.
 """
 from __future__ import annotations
 
@@ -40,6 +43,36 @@ def short(kernel: str, n: int) -> str:
     return kernel[kernel.find("vbr_spmm" if "vbr_spmm" in kernel else "entry_rows"):][:n]
 
 
+def run_case(args) -> int:
+    """The profiled program of ``--case``: the multiply again and again, one JSON line with what the summary needs."""
+    sys.path.insert(0, ROOT)
+    os.chdir(ROOT)
+    import torch
+    from perf import cases
+    case = next(c for c in cases.listed() if c["name"] == args.run_case)
+    state = cases.prepare(case, 1)
+    work = cases.work(case)
+    ramp = 0 if args.no_ramp else 300
+    for _ in range(ramp + args.warmup):
+        cases.run(state)
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    start.record()
+    for _ in range(args.steps):
+        cases.run(state)
+    end.record()
+    torch.cuda.synchronize()
+    ms = start.elapsed_time(end) / args.steps
+    if args.calib_copy:
+        x = torch.zeros(COPY_BYTES // 4, dtype=torch.float32, device="cuda:0")
+        y = torch.empty_like(x)
+        torch.neg(x, out=y)                # a kernel that making the inputs has not used
+        torch.cuda.synchronize()
+    kernels = state["M"].launches(case["n"]) if case["path"] == "multiply" else [dict(kernel="entry_rows_kernel")]
+    print(json.dumps(dict(ms_per_step=ms, value=work["flops"] / ms * 1e-9, unit="TFLOP/s of entries", clock_ramp_launches=ramp,
+                          roofline=dict(kernel=kernels, algorithmic_hbm_bytes=work["bytes"]))), flush=True)
+    return 0
+
+
 def run(cmd, log, limit):
     print("[rocprof_summary] " + " ".join(cmd), flush=True)
     env = dict(os.environ, TMPDIR="/tmp")
@@ -57,22 +90,35 @@ def main() -> int:
     ap.add_argument("--workload", default="c4")
     ap.add_argument("--clean", action="store_true")
     ap.add_argument("--dense", action="store_true", help="the dense product on the zero-filled matrix (bench.py --dense)")
-    ap.add_argument("--out", required=True)
+    ap.add_argument("--case", help="a multiply of perf/cases.py instead of a workload of the benchmark")
+    ap.add_argument("--run-case", help="run that multiply here (the profiled program)")
+    ap.add_argument("--warmup", type=int, default=5)
+    ap.add_argument("--no-ramp", action="store_true")
+    ap.add_argument("--calib-copy", action="store_true")
+    ap.add_argument("--out")
     ap.add_argument("--steps", type=int, default=50)
     ap.add_argument("--no-counters", action="store_true", help="kernel trace only")
     args = ap.parse_args()
+    if args.run_case:
+        return run_case(args)
+    if not args.out:
+        ap.error("--out is needed")
     out_dir = os.path.abspath(args.out)
     os.makedirs(out_dir, exist_ok=True)
     bench = ["python3", os.path.join(ROOT, "bench.py"), "--workload", args.workload, "--timed-only"]
     flags = (" --clean" if args.clean else "") + (" --dense" if args.dense else "")
     bench += flags.split()
     shown = "python3 bench.py --workload %s --timed-only%s" % (args.workload, flags)
+    what, how = "workload " + args.workload, "--workload %s%s" % (args.workload, flags)
+    if args.case:
+        bench = ["python3", os.path.abspath(__file__), "--run-case", args.case]
+        shown = "python3 paper_2202_05868_amd/rocprof_summary.py --run-case " + args.case
+        what, how = "case %s of perf/cases.py" % args.case, "--case " + args.case
     pmc_tail = ["--no-ramp", "--steps", "5", "--warmup", "2", "--calib-copy"]
-    text = ["# rocprofv3 summary: vbr_spmm on workload %s%s (MI355X, gfx950)" % (
-                args.workload, (" (noise-free)" if args.clean else "") + (" stored zero-filled: the dense product" if args.dense else "")),
+    text = ["# rocprofv3 summary: vbr_spmm on %s%s (MI355X, gfx950)" % (
+                what, (" (noise-free)" if args.clean else "") + (" stored zero-filled: the dense product" if args.dense else "")),
             "",
-            "made by             : python -m paper_2202_05868_amd.rocprof_summary --workload %s%s --out <out>" % (
-                args.workload, flags),
+            "made by             : python -m paper_2202_05868_amd.rocprof_summary %s --out <out>" % how,
             "kernel trace command: cd /tmp && export TMPDIR=/tmp && rocprofv3 --kernel-trace --stats -d <out>/trace -o t -- %s --steps %d" % (shown, args.steps)]
 
     bj = run(["rocprofv3", "--kernel-trace", "--stats", "-d", os.path.join(out_dir, "trace"), "-o", "t", "--"] + bench +
@@ -100,7 +146,7 @@ def main() -> int:
                  for i in range(0, len(timed), per_step)]
         text.append("  the launches of one call follow each other: first start to last end of a timed step, average %.3f us" % (
             sum(spans) / len(spans) / 1e3))
-    text.append("bench.py in the same run: ms_per_step %.4f (HIP events around the %d timed steps), value %.1f %s, clock-ramp launches %d" % (
+    text.append(("the case" if args.case else "bench.py") + " in the same run: ms_per_step %.4f (HIP events around the %d timed steps), value %.1f %s, clock-ramp launches %d" % (
         bj["ms_per_step"], args.steps, bj["value"], bj["unit"], bj["clock_ramp_launches"]))
     text.append("(under the profiler every dispatch is followed by a completion signal, so the GPU idles between launches and")
     text.append(" its clocks settle lower than in an unprofiled run; compare with the ms_per_step of this run, not of another)")
@@ -120,8 +166,8 @@ def main() -> int:
                 if is_multiply(k):
                     text.append("  %-70s %14.1f KiB (n=%d)" % (short(k, 70), val, cnt))
                     spmm_sum[tag] += val
-                elif "elementwise" in k and "Fill" not in k:
-                    text.append("  %-70s %14.1f KiB (n=%d)" % ("256 MiB streaming kernel (torch.mul out=)", val, cnt))
+                elif "neg_kernel" in k if args.case else "elementwise" in k and "Fill" not in k:
+                    text.append("  %-70s %14.1f KiB (n=%d)" % ("256 MiB streaming kernel (torch.%s out=)" % ("neg" if args.case else "mul"), val, cnt))
                     res[tag] = val
         if "FETCH_SIZE" in res and "WRITE_SIZE" in res:
             sf = COPY_BYTES / (res["FETCH_SIZE"] * 1024)
