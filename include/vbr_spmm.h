@@ -185,7 +185,8 @@ int vbr_get_launches(const vbr_t *v, int64_t N, int32_t *n_launches, int32_t *ki
  * The functions these launches run, as a profiler shows them: names[i] (room for VBR_MAX_LAUNCHES entries; static strings)
  * of launch i of vbr_get_launches.  Tiles of one kind have up to three: VBR_LAUNCH_TILE_* and VBR_LAUNCH_GATHER_* run
  * vbr_spmm_kernel, 256 columns of C a workgroup, or vbr_spmm_split_kernel, 64 columns, whose waves split the K-steps;
- * VBR_LAUNCH_TILE_4 with long lists against a wide B also vbr_spmm_wide_kernel, 512 columns.
+ * VBR_LAUNCH_TILE_4 with long lists against a wide B also vbr_spmm_wide_kernel, 512 columns; VBR_LAUNCH_TILE_1 with many
+ * groups against a wide B also vbr_spmm_stream_kernel, up to 64 tiles and 64 columns.
  */
 int vbr_get_launch_functions(const vbr_t *v, int64_t N, const char **names);
 

@@ -26,9 +26,7 @@ namespace {
 
 constexpr int kCsrThreads = 256;     // 4 waves
 
-typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef float float2v __attribute__((ext_vector_type(2)));
-typedef float float4v __attribute__((ext_vector_type(4)));
 
 struct EntryParams {
     EntryRowsDev rows;

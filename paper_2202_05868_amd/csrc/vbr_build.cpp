@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "host_threads.h"
+#include "stream_schedule.h"
 #include "vbr_host.h"
 
 namespace vbrk {
@@ -164,6 +165,7 @@ private:
     int emit_gather_tiles();
     void fill_values();
     void schedule();
+    void stream();
     void lay_out();
 
     const vbr_csr_t *csr;
@@ -230,6 +232,7 @@ int Builder::build()
     if (rc != VBR_OK) return rc;
     fill_values();
     schedule();
+    stream();
     lay_out();
     return VBR_OK;
 }
@@ -991,6 +994,71 @@ void Builder::schedule()
     }
 }
 
+// The schedules of the stream kernel, where all tiles with a K-step are block tiles of one slab.  The groups are dealt to the waves of as few workgroups as
+// hold them, the longest first, each to the wave with the fewest K-steps.
+void Builder::stream()
+{
+    constexpr int kAll = kStreamWaves * kStreamGroups;
+    const int64_t T = v->n_work, n_tiles = (T + kAll - 1) / kAll;
+    if (T < kStreamMinTiles || v->class_count[0] != T || v->lg_gran < 4 || !v->panels.empty()) return;
+    if ((int64_t)v->vals.size() * 2 > kNearBytes || v->n_cols > INT32_MAX / 2) return;
+    struct Wave { int64_t load; int32_t tiles; int32_t wave; };
+    auto heavier = [](const Wave &a, const Wave &b) { return a.load != b.load ? a.load > b.load : a.wave > b.wave; };
+    std::vector<Wave> waves;
+    for (int32_t w = 0; w < n_tiles * kStreamWaves; ++w) waves.push_back(Wave{0, 0, w});
+    std::vector<int32_t> tile_of((size_t)(n_tiles * kAll), -1);
+    for (int32_t i = 0; i < T; ++i) {
+        std::pop_heap(waves.begin(), waves.end(), heavier);
+        Wave w = waves.back();
+        waves.pop_back();
+        tile_of[(size_t)(w.wave * kStreamGroups + w.tiles)] = i;
+        w.load += v->dev_tiles[(size_t)i].n_ks;
+        if (++w.tiles == kStreamGroups) continue;
+        waves.push_back(w);
+        std::push_heap(waves.begin(), waves.end(), heavier);
+    }
+    const int per = kStepK >> v->lg_gran;
+    // K-steps of a wave in a step: as many as the units of a step have on average
+    const int64_t units = n_tiles * kStreamWaves * v->n_cols / (kSlabRows * kStreamWaves * kStreamUnits);
+    v->stream_ops = (int32_t)std::min<int64_t>(std::max<int64_t>((v->work_steps + units - 1) / units, kStreamLeastOps), kStreamMostOps);
+    std::vector<std::vector<StreamRecord>> records((size_t)n_tiles);
+    std::vector<int64_t> n_steps((size_t)n_tiles, 0);
+    each(n_tiles, 1, [&](Scratch &, int64_t t) {
+        const int32_t *group_of = tile_of.data() + t * kAll;
+        int32_t n_ks[kAll], first[kAll];
+        int64_t frag[kAll];
+        for (int l = 0; l < kAll; ++l) {
+            if (group_of[l] < 0) continue;
+            const TileDesc &td = v->dev_tiles[(size_t)group_of[l]];
+            n_ks[l] = td.n_ks;
+            first[l] = td.ks_begin;
+            frag[l] = td.a_off * 16 >> 10;
+        }
+        auto unit = [&](int l, int32_t k, int h) { return v->krow[(size_t)(first[l] + k) * per + (per == 2 ? h : 0)] / kSlabRows + (per == 2 ? 0 : h); };
+        const int sharers = (int)std::min<int64_t>(n_tiles, kStreamShare);
+        n_steps[(size_t)t] = stream_schedule(v->stream_ops, group_of, n_ks, frag, unit, v->n_cols / kSlabRows, (int)(t % sharers), sharers, records[(size_t)t]);
+    });
+    int64_t total = 0;
+    for (const int64_t n : n_steps) {
+        if (n == 0) return;
+        total += n;
+    }
+    v->stream_steps.reserve((size_t)((total + 2) * 2 * kStreamWaves));
+    for (int64_t t = 0; t < n_tiles; ++t) {
+        StreamTile st;
+        st.first_step = (int32_t)(v->stream_steps.size() / (2 * kStreamWaves));
+        st.n_steps = (int32_t)n_steps[(size_t)t];
+        for (int l = 0; l < kAll; ++l) {
+            const int32_t i = tile_of[(size_t)(t * kAll + l)];
+            st.row_begin[l] = i < 0 ? -1 : v->dev_tiles[(size_t)i].row_begin;
+        }
+        v->stream_tiles.push_back(st);
+        v->stream_longest = std::max(v->stream_longest, st.n_steps);
+        v->stream_steps.insert(v->stream_steps.end(), records[(size_t)t].begin(), records[(size_t)t].end());
+    }
+    v->stream_steps.resize(v->stream_steps.size() + 2 * 2 * kStreamWaves, StreamRecord());      // looked up behind the last step, and not used
+}
+
 void Builder::lay_out()
 {
     DeviceLayout &L = v->lay;
@@ -1002,7 +1070,9 @@ void Builder::lay_out()
     L.pk_meta_off = align_up(L.panels_off + (int64_t)v->panels.size() * (int64_t)sizeof(PanelDesc), 256);
     L.prow_off = align_up(L.pk_meta_off + (int64_t)v->pk_meta.size() * 4, 256);
     L.gcol_off = align_up(L.prow_off + (int64_t)(v->by_entries ? v->entries.row.size() * sizeof(EntryRow) : v->prow.size() * 4), 256);
-    L.vals_off = align_up(L.gcol_off + (int64_t)(v->by_entries ? v->entries.bytes() : v->gcol.size() * 4), 256);
+    L.stream_tiles_off = align_up(L.gcol_off + (int64_t)(v->by_entries ? v->entries.bytes() : v->gcol.size() * 4), 256);
+    L.stream_steps_off = align_up(L.stream_tiles_off + (int64_t)v->stream_tiles.size() * (int64_t)sizeof(StreamTile), 256);
+    L.vals_off = align_up(L.stream_steps_off + (int64_t)v->stream_steps.size() * (int64_t)sizeof(StreamRecord), 256);
     L.total = std::max<int64_t>(256, align_up(L.vals_off + (int64_t)v->vals.size() * 2, 256));
 }
 
@@ -1141,6 +1211,86 @@ extern "C" int vbr_unpack_block(const vbr_t *v, int64_t blk, void *dst_)
 
 // Everything the kernels index with, checked against the sizes of what they index into: a wrong
 // entry here would be a device access out of bounds, so the check is plain and complete.
+namespace vbrk {
+
+// Goes through the steps of the stream kernel as it does: every index inside what it indexes; every K-step of every tile once and in order, with the units
+// of B in its slots that it takes, written in the step before its operands are read or earlier; no slot written while a K-step still reads it.
+static bool stream_holds(const vbr *v)
+{
+    constexpr int kStep = 2 * kStreamWaves, kAll = kStreamWaves * kStreamGroups, kZeros = kStreamSlots * kStreamUnitBytes;
+    if (v->stream_tiles.empty()) return v->stream_steps.empty();
+    if (v->stream_ops < kStreamLeastOps || v->stream_ops > kStreamMostOps || v->stream_steps.size() % kStep != 0 || (int64_t)v->vals.size() * 2 > kNearBytes) return false;
+    const int64_t n_steps = (int64_t)v->stream_steps.size() / kStep - 2;      // two more are looked up behind the last
+    std::vector<int32_t> tile_at((size_t)v->n_rows, -1);
+    for (int32_t i = 0; i < v->n_work; ++i) {
+        const TileDesc &td = v->dev_tiles[(size_t)i];
+        if (td.group < 0 || td.n_rows != kSlabRows || td.a_off % 64 != 0) return false;
+        tile_at[(size_t)td.row_begin] = i;
+    }
+    int64_t tiles = 0;
+    for (const StreamTile &st : v->stream_tiles) {
+        if (st.first_step < 0 || st.n_steps < 0 || st.n_steps % kStreamAhead != 0 || st.first_step + (int64_t)st.n_steps > n_steps) return false;
+        int32_t done[kAll] = {0}, tile[kAll];
+        for (int l = 0; l < kAll; ++l) {
+            tile[l] = -1;
+            if (st.row_begin[l] < 0) continue;
+            if ((int64_t)st.row_begin[l] + kSlabRows > v->n_rows) return false;
+            std::swap(tile[l], tile_at[(size_t)st.row_begin[l]]);
+            if (tile[l] < 0) return false;
+            ++tiles;
+        }
+        struct Slot { int32_t row = -1, written = -1, read = -1; } slots[kStreamSlots];
+        for (int32_t t = 0; t < st.n_steps; ++t) {
+            const StreamRecord *now = v->stream_steps.data() + (int64_t)(st.first_step + t) * kStep, *before = t > 0 ? now - kStep : nullptr;
+            for (int e = 0; e < kStreamWaves * v->stream_ops; ++e) {
+                const int w = e / v->stream_ops, i = e % v->stream_ops, g = now[2 * w].group(i);
+                int32_t at[2], frag[2];
+                for (int h = 0; h < 2; ++h) {
+                    // (the kernel begins with zeros)
+                    at[h] = i > 0 ? now[2 * w + h].slot(i - 1) : before ? before[2 * w + h].slot(v->stream_ops - 1) : kZeros;
+                    frag[h] = before ? before[2 * w + h].frag(i) : kStreamNone;
+                    if (at[h] < 0 || at[h] > kZeros || at[h] % kStreamUnitBytes != 0) return false;
+                }
+                if (frag[0] != frag[1] || g > kStreamGroups || g != now[2 * w + 1].group(i) || (frag[0] == kStreamNone) != (g == kStreamGroups)) return false;
+                if (g == kStreamGroups) continue;
+                const int l = w * kStreamGroups + g;
+                if (tile[l] < 0) return false;
+                const TileDesc &td = v->dev_tiles[(size_t)tile[l]];
+                const int32_t k = done[l]++;
+                if (k >= td.n_ks || (uint32_t)frag[0] != (uint32_t)(td.a_off * 16 + (int64_t)k * kFragElems * 2)) return false;
+                for (int h = 0; h < 2; ++h) {
+                    const int64_t b = (int64_t)(td.ks_begin + k) * kStepK + kSlabRows * h;
+                    const int32_t row = v->krow[(size_t)(b >> v->lg_gran)] + (int32_t)(b & ((1 << v->lg_gran) - 1));
+                    if (at[h] == kZeros) return false;
+                    Slot &s = slots[at[h] / kStreamUnitBytes];
+                    if (s.row != row || s.written > t - (i == 0 ? 2 : 1)) return false;
+                    s.read = t;
+                }
+            }
+            for (int i = 0; i < kStep; ++i) {
+                // what this step asks for is written kStreamAhead steps later
+                const StreamRecord &r = now[i];
+                for (int e = 0; e < 2; ++e)
+                    if (r.early(e) < -1 || (int64_t)r.early(e) + kSlabRows > v->n_cols) return false;
+                if (r.none() == kStreamNone) {
+                    if (r.to() != kZeros || r.row() != 0) return false;           // zeros to where the zeros are
+                    continue;
+                }
+                if (r.none() != 0 || r.row() < 0 || r.row() % kSlabRows != 0 || (int64_t)r.row() + kSlabRows > v->n_cols) return false;
+                if (r.to() < 0 || r.to() >= kZeros || r.to() % kStreamUnitBytes != 0) return false;
+                Slot &s = slots[r.to() / kStreamUnitBytes];
+                if (s.written >= t + kStreamAhead || s.read >= t + kStreamAhead) return false;
+                s = Slot{r.row(), t + kStreamAhead, -1};
+            }
+        }
+        for (int l = 0; l < kAll; ++l)
+            if (tile[l] >= 0 && done[l] != v->dev_tiles[(size_t)tile[l]].n_ks) return false;
+    }
+    return tiles == v->n_work;
+}
+
+}  // namespace vbrk
+
 extern "C" int vbr_audit(const vbr_t *v)
 {
     using namespace vbrk;
@@ -1223,18 +1373,20 @@ extern "C" int vbr_audit(const vbr_t *v)
     }
     for (size_t i = v->by_entries ? 0 : (size_t)n_vals - kFragElems; i < (size_t)n_vals; ++i)
         if (values[i] != 0) return VBR_EINVAL;                                               // the zero fragment
+    if (!stream_holds(v)) return VBR_EINVAL;
     const DeviceLayout &L = v->lay;
-    const int64_t ends[9] = {L.zeros_off + 256, L.tiles_off + (int64_t)v->dev_tiles.size() * (int64_t)sizeof(TileDesc),
+    const int64_t ends[11] = {L.zeros_off + 256, L.tiles_off + (int64_t)v->dev_tiles.size() * (int64_t)sizeof(TileDesc),
                               L.krow_off + (int64_t)v->krow.size() * 4, L.perm_off + M * 4,
                               L.panels_off + (int64_t)v->panels.size() * (int64_t)sizeof(PanelDesc),
                               L.pk_meta_off + (int64_t)v->pk_meta.size() * 4, L.prow_off + (int64_t)(v->by_entries ? v->entries.row.size() * sizeof(EntryRow) : v->prow.size() * 4),
                               L.gcol_off + (int64_t)(v->by_entries ? v->entries.bytes() : v->gcol.size() * 4),
-                              L.vals_off + n_vals * 2};
-    const int64_t begins[9] = {L.zeros_off, L.tiles_off, L.krow_off, L.perm_off, L.panels_off, L.pk_meta_off, L.prow_off,
-                                L.gcol_off, L.vals_off};
-    for (int i = 0; i < 9; ++i) {
+                              L.stream_tiles_off + (int64_t)v->stream_tiles.size() * (int64_t)sizeof(StreamTile),
+                              L.stream_steps_off + (int64_t)(v->stream_steps.size() * sizeof(StreamRecord)), L.vals_off + n_vals * 2};
+    const int64_t begins[11] = {L.zeros_off, L.tiles_off, L.krow_off, L.perm_off, L.panels_off, L.pk_meta_off, L.prow_off,
+                                L.gcol_off, L.stream_tiles_off, L.stream_steps_off, L.vals_off};
+    for (int i = 0; i < 11; ++i) {
         if (begins[i] % 256 != 0 || ends[i] > L.total) return VBR_EINVAL;
-        if (i + 1 < 9 && ends[i] > begins[i + 1]) return VBR_EINVAL;                         // sections in this order, disjoint
+        if (i + 1 < 11 && ends[i] > begins[i + 1]) return VBR_EINVAL;                         // sections in this order, disjoint
     }
     return VBR_OK;
 }
@@ -1314,6 +1466,25 @@ static bool wide_pays(const vbr *v, int64_t T, int64_t N)
     const int32_t longest = v->dev_tiles[0].n_ks, median = v->dev_tiles[(size_t)v->n_work / 2].n_ks;
     if (v->n_cols > 12288 && v->work_steps * kStepK > 4 * v->n_cols) return false;
     return N > 1024 && longest >= 4 && 10 * longest <= (T < 44 ? 14 : 20) * median && 10 * (10 + cost(kWideN, 100, 77)) <= 9 * cost(kTileN, 62, 50);
+}
+
+// Is the stream kernel faster than `workgroups` of the kernel of one-slab tiles, 256 columns each?  It has one workgroup on a CU, 32 on an L2 domain, which
+// all take their steps, whether the round is full or not: that and what goes before and behind, 10 us a round, is its time, 0.5 us a step and 0.117 for
+// each K-step of a wave in it.  The other takes 0.7 ns for a K-step of a workgroup, and somewhat longer where rows of B begin inside cache lines, as this one does.
+// Tile and stream kernel, 16 x 16 blocks, other operands in every call: 4096 x 16384 at 10 %, N = 4096 163 and 109 us, 3072 126 and 104, 2560 123 and
+// 105, unaligned 3504 176 and 121; at 6 % 114 and 87, 89 and 85, 85 and 84, 122 and 100; at 15 % 227 and 136, 174 and 130, 168 and 131, 243 and 148;
+// 3072 rows, N = 4096, 10 % 135 and 105; 2048: 91 and 107, at 15 % 121 and 133; 1024: 56 and 124; 8192 x 8192, N = 4096 165 and 113, 2048: 83 and 57;
+// 16384 x 8192, N = 1024 82 and 59; 4096 x 8192, N = 4096, 3 % 42.0 and 41.4, 10 %: 86 and 58, 30 %: 215 and 123, 50 %: 343 and 189; two rounds: N = 4160
+// 103 and 103, 6144: 135 and 110, 8192: 175 and 121; 5120 rows, N = 4096: 110 and 106; 4096 x 4096, 10 % 49 and 39, 6 %: 37 and 32.  32-column blocks,
+// 11200 x 1280 at 62 %, N = 1024 56 and 47, 4104: 222 and 196; short lists, 32768 x 512 at half, N = 512 38.3 and 38.4, 520: 58 and 66.
+static bool stream_pays(const vbr *v, int64_t N, int64_t ldb, bool aligned, int64_t workgroups)
+{
+    const int64_t tiles = (int64_t)v->stream_tiles.size();
+    if (tiles == 0 || N < 512 || b_bytes_of(v->n_cols, ldb, N) > kNearBytes || ldb * 2 >= 1 << 24 || v->n_cols > 1 << 24) return false;
+    const int64_t rounds = (grid_size(tiles, (N + kStreamN - 1) / kStreamN) / kXcd + 31) / 32;
+    const int64_t stream_ns = 4000 + rounds * (10000 + v->stream_longest * (500 + 117 * v->stream_ops));
+    const int64_t tile_ns = 12000 + v->work_steps * workgroups / std::max<int32_t>(v->n_work, 1) * 7 / 10;
+    return 100 * (aligned ? stream_ns : stream_ns * 9 / 8) < 95 * (aligned ? tile_ns : tile_ns * 7 / 6);
 }
 
 EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned)
@@ -1529,7 +1700,11 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         auto rounds = [&](bool even) { return std::max<int64_t>((grid_size(T, Qt, even) / kXcd - at_once / 16 + at_once - 1) / at_once, 1); };
         const bool narrow_sixth = Qt == 6 && N - 5 * kTileN <= kTileN / 2 && v->class_count[3] == 0 && rounds(false) == rounds(true);
         Launch L{kind, 0, T, 0, split, few, 0, 0, !split && !narrow_sixth && even_columns(T, Qt)};
-        if (kind == VBR_LAUNCH_TILE_MIXED) {
+        if (kind == VBR_LAUNCH_TILE_1 && !split && stream_pays(v, N, ldb ? ldb : N, aligned, grid_size(T, Qt, L.even))) {
+            L.stream = true;
+            L.even = false;
+            L.grid = grid_size((int64_t)v->stream_tiles.size(), (N + kStreamN - 1) / kStreamN) + (T - v->n_work) * Qt;
+        } else if (kind == VBR_LAUNCH_TILE_MIXED) {
             L.whole = split ? 0 : T;
             L.rest = split ? v->n_work : 0;
             // A last round of few workgroups takes as long as a full one.  Where an L2 domain has up to a quarter more than it holds at once (or
@@ -1594,7 +1769,7 @@ extern "C" int vbr_get_launch_functions(const vbr_t *v, int64_t N, const char **
         case VBR_LAUNCH_TILE_MIXED: names[i] = "vbr_spmm_mixed_kernel"; break;
         case VBR_LAUNCH_ENTRIES: names[i] = "entry_rows_kernel"; break;
         case VBR_LAUNCH_ZERO_ROWS: names[i] = "vbr_spmm_zero_rows_kernel"; break;
-        default: names[i] = plan[i].split ? "vbr_spmm_split_kernel" : plan[i].wide ? "vbr_spmm_wide_kernel" : "vbr_spmm_kernel"; break;
+        default: names[i] = plan[i].split ? "vbr_spmm_split_kernel" : plan[i].stream ? "vbr_spmm_stream_kernel" : plan[i].wide ? "vbr_spmm_wide_kernel" : "vbr_spmm_kernel"; break;
         }
     }
     return VBR_OK;

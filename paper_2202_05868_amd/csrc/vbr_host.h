@@ -16,8 +16,9 @@ int sa1_reorder_impl(const vbr_csr_t *csr, int32_t col_block, double tau, int32_
 // kernel, first tile and number of tiles (or panels) of the launch, grid size; split: 64 columns of C a workgroup,
 // whose waves split the K-steps; few: rings of four slots; wide: the wide kernel.  aligned: rows of B begin on a cache line.
 // split: 0, or the K-steps from which on its tiles are split, of the mixed kernel `rest` of them from number `whole` on
-struct Launch { int32_t kind; int32_t first_tile, n_tiles; int64_t grid; int32_t split = 0; bool few = false; int32_t whole = 0, rest = 0; bool even = false, wide = false; };
+struct Launch { int32_t kind; int32_t first_tile, n_tiles; int64_t grid; int32_t split = 0; bool few = false; int32_t whole = 0, rest = 0; bool even = false, wide = false, stream = false; };
 int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUNCHES], int64_t ldb = 0);      // 0: N
+int launch_stream(const vbr *v, const Launch &L, const void *B_dev, int64_t ldb, float *C_dev, int64_t ldc, int64_t N, void *hip_stream);
 
 constexpr int kEntryLongRow = 256;     // entries beyond which a row gets a wave of its own ...
 constexpr int kEntryHugeRow = 1024;    // ... and a workgroup of its own

@@ -188,9 +188,48 @@ static_assert(sizeof(PanelDesc) == 32, "PanelDesc is read by the kernel as 2 x 1
 constexpr int kPanelMaxFrags = 8;    // fragments per physical K-step (one load per wave); more -> the step is split
 constexpr int kPanelMetaPad = 12;    // records appended to a panel's K-step stream, so that the kernel's look-ahead needs no bound checks
 
+// The stream kernel: a workgroup owns up to kStreamWaves * kStreamGroups row groups of one slab and kStreamN columns of C, and multiplies by a schedule
+// (stream_schedule.h) of steps.  In a step every wave multiplies up to 4 .. kStreamMostOps K-steps of its groups, and brings up to two units of 16 B rows.
+constexpr int kStreamN = 64, kStreamWaves = 8, kStreamGroups = 8;
+constexpr int kStreamLeastOps = 4, kStreamMostOps = 8;
+constexpr int kStreamUnits = 2;
+constexpr int kStreamAhead = 2;        // units are in LDS that many steps after they were asked for
+constexpr int kStreamSlots = 79;       // places for units in LDS, and one more that holds zeros
+constexpr int kStreamUnitBytes = kSlabRows * kStreamN * 2;
+constexpr int kStreamShare = 4;        // row tiles that share the first requests of B
+constexpr int kStreamEarly = 48;       // units before its own that a workgroup asks for its share of them
+constexpr int kStreamMinTiles = 64;    // tiles from which on a matrix gets a schedule
+// Of every step a wave has two of these records, one for each half of its lanes: of the two units of a K-step, and of those it brings.
+struct StreamRecord {
+    // the lanes of a row of 16 hold two words each, which the others of the row get by a broadcast
+    int32_t word[16][2];
+    int32_t &slot(int i) { return word[i][0]; }                        // where the unit of the K-step behind this one is in LDS, in bytes
+    int32_t &frag(int i) { return word[kStreamMostOps + i][0]; }       // fragments of the next step's K-steps, in bytes from the first value (in both records the same)
+    int32_t &row() { return word[0][1]; }                              // first B row of the unit to ask for, ...
+    int32_t &none() { return word[1][1]; }                             // ... kStreamNone if there is none, else 0, ...
+    int32_t &to() { return word[2][1]; }                               // ... and where it goes
+    int32_t &groups() { return word[3][1]; }                           // groups of this step's K-steps, four bits each, kStreamGroups: none (in both records the same)
+    int32_t &early(int i) { return word[5 + i][1]; }                   // first B rows of two units to bring into the L2, -1: none
+    int32_t slot(int i) const { return word[i][0]; }
+    int32_t frag(int i) const { return word[kStreamMostOps + i][0]; }
+    int32_t row() const { return word[0][1]; }
+    int32_t none() const { return word[1][1]; }
+    int32_t to() const { return word[2][1]; }
+    int32_t early(int i) const { return word[5 + i][1]; }
+    int32_t group(int i) const { return word[3][1] >> (4 * i) & 15; }
+};
+static_assert(sizeof(StreamRecord) == 128 && kStreamMostOps == 8, "read by the kernel as 16 x 8 bytes");
+constexpr int32_t kStreamNone = (int32_t)(uint32_t)kNearBytes;
+// what a workgroup's groups are: first positions in perm of wave w's at row_begin[w * kStreamGroups], -1: none
+struct StreamTile {
+    int32_t first_step, n_steps;
+    int32_t row_begin[kStreamWaves * kStreamGroups];
+};
+
 // Byte offsets of the sections inside the device buffer (each 256-byte aligned).
 struct DeviceLayout {
     int64_t zeros_off = 0, tiles_off = 0, krow_off = 0, perm_off = 0, vals_off = 0, total = 0;
+    int64_t stream_tiles_off = 0, stream_steps_off = 0;
     int64_t panels_off = 0, pk_meta_off = 0, prow_off = 0;
     int64_t gcol_off = 0;      // by_entries: the entries; prow their rows
 };
@@ -303,6 +342,11 @@ struct vbr {
     std::vector<int64_t> pk_frag;        // host only: ordinal of the step's first fragment inside its panel
     std::vector<int64_t> p_union_ptr;    // host only: [n_panels+1] into p_union
     std::vector<int32_t> p_union;        // host only: ascending union of the column blocks of each panel
+    // Block tiles of one slab, if all tiles are, for the stream kernel, too.
+    std::vector<vbrk::StreamTile> stream_tiles;
+    std::vector<vbrk::StreamRecord> stream_steps;
+    int32_t stream_ops = 0;              // K-steps of a wave in a step of theirs
+    int32_t stream_longest = 0;          // steps of the longest
     // A matrix whose blocking found next to nothing to share is kept as entries only: no tiles, no panels, no values above.
     bool by_entries = false;
     vbrk::EntryRows entries;

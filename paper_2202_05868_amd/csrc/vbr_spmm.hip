@@ -8,6 +8,7 @@
 //                  rows of low groups, and of tall groups whose blocks are mostly fill-in
 //   deep tiles     gathered tiles with very many columns: the waves of a workgroup split the K-steps
 //   wide kernel    3 to 4 slabs of one row group x 512 columns, for long lists against a wide B: B goes to registers, A through LDS
+//   stream kernel  up to 64 row groups of one slab x 64 columns, which share B rows (stream_spmm.hip)
 //   panel kernel   8 slabs of low groups x 128 columns walking the union of their column blocks
 //   mixed kernel   tiles of several of these classes in one launch
 // Matrices whose rows share nothing are multiplied by the kernel in csr_spmm.hip.
@@ -34,13 +35,8 @@ constexpr int kPanelBytes = kStepK * kRowBytes;   // 16 KiB of B per K-step
 constexpr int kFragBytes = kFragElems * 2;        // 1 KiB per A fragment
 
 typedef short short4v __attribute__((ext_vector_type(4)));
-typedef short short8v __attribute__((ext_vector_type(8)));
-typedef _Float16 half8v __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
-typedef float float4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4v *lds_short4_ptr;
 typedef __attribute__((address_space(3))) short8v *lds_short8_ptr;
-typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) float4v *lds_float4_ptr;
 typedef __attribute__((address_space(3))) uint4v *lds_uint4_ptr;
 typedef __attribute__((address_space(3))) int32_t *lds_i32_ptr;
@@ -67,15 +63,6 @@ struct Params {
     int32_t whole, rest;      // mixed kernel: tiles with one workgroup a column tile, and behind them some with four, see there ...
     int32_t split;            // ... and from how many K-steps on these are split
 };
-
-template <int DT>
-__device__ __forceinline__ float4v mfma16x16x32(short8v a, short8v b, float4v c)
-{
-    if constexpr (DT == VBR_F16)
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a), __builtin_bit_cast(half8v, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8v, a), __builtin_bit_cast(bf16x8v, b), c, 0, 0, 0);
-}
 
 // 16 bytes per active lane from global memory straight into LDS, no register staging: lane l's
 // data lands at lds_base + 16 l (lds_base wave-uniform, passed in M0).  The load is counted in
@@ -1105,6 +1092,11 @@ int launch_all(const vbr *v, const Params &base, PanelParams pp, hipStream_t str
             if (e != hipSuccess) { set_last_hip_error((int)e); return VBR_EHIP; }
             continue;
         }
+        if (L.stream) {
+            const int rc = launch_stream(v, L, base.B, base.ldb, base.C, base.ldc, base.N, stream);
+            if (rc != VBR_OK) return rc;
+            continue;
+        }
         const bool few = L.few;
         void (*kernel)(Params) = nullptr;
         if (L.kind == VBR_LAUNCH_TILE_MIXED) {
@@ -1171,11 +1163,13 @@ extern "C" int vbr_upload(vbr_t *v, void *buf_dev, void *hip_stream)
     static const unsigned char kZeros[256] = {0};
     const Part rows = v->by_entries ? Part{L.prow_off, v->entries.row.data(), v->entries.row.size() * sizeof(vbrk::EntryRow)} : Part{L.prow_off, v->prow.data(), v->prow.size() * 4};
     const Part cols = v->by_entries ? Part{L.gcol_off, v->entries.entry.get(), v->entries.bytes()} : Part{L.gcol_off, v->gcol.data(), v->gcol.size() * 4};
-    const Part parts[9] = {
+    const Part parts[11] = {
         cols,
         {L.panels_off, v->panels.data(), v->panels.size() * sizeof(vbrk::PanelDesc)},
         {L.pk_meta_off, v->pk_meta.data(), v->pk_meta.size() * 4},
         rows,
+        {L.stream_tiles_off, v->stream_tiles.data(), v->stream_tiles.size() * sizeof(vbrk::StreamTile)},
+        {L.stream_steps_off, v->stream_steps.data(), v->stream_steps.size() * sizeof(vbrk::StreamRecord)},
         {L.zeros_off, kZeros, sizeof(kZeros)},
         {L.tiles_off, v->dev_tiles.data(), v->dev_tiles.size() * sizeof(vbrk::TileDesc)},
         {L.krow_off, v->krow.data(), v->krow.size() * 4},

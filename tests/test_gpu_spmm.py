@@ -372,6 +372,32 @@ def test_long_lists_against_a_wide_b(heights, groups, col_block, n_ks, n, pad, d
     check_c(out, c_ref, s, "%d K-steps, N = %d" % (n_ks, n))
 
 
+@pytest.mark.parametrize("groups,col_block,blocks,least,most,empty,n,pad,dtype", [
+    (1024, 16, 512, 28, 32, 0, 1024, 0, "f16"), (1024, 16, 512, 36, 40, 0, 1024, 0, "bf16"), (1024, 16, 256, 21, 24, 0, 1024, 64, "f16"), (290, 64, 40, 2, 39, 64, 2040, 0, "bf16"),
+    (700, 32, 40, 20, 30, 100, 520, 0, "f16"), (600, 16, 64, 24, 40, 0, 1032, 8, "bf16"), (2048, 16, 32, 14, 18, 0, 512, 0, "f16"), (520, 48, 24, 10, 20, 77, 1032, 0, "f16"),
+    (300, 80, 20, 8, 20, 64, 2552, 0, "bf16"), (129, 64, 40, 30, 40, 1, 4096, 0, "f16")])
+def test_many_groups_of_one_slab_against_a_wide_b(groups, col_block, blocks, least, most, empty, n, pad, dtype):
+    # schedules of four to eight K-steps a step; units of two halves of a block and of one; lists of an even and an odd number of blocks, of one length and of many; the last
+    # workgroup with one group, and with waves that have fewer than others; the last column tile of 8, 56 and 64 columns; rows without entries, less than a tile and more
+    rng = np.random.default_rng(groups + n)
+    r, c = [], []
+    for g in range(groups):
+        cols = (np.sort(rng.choice(blocks, size=rng.integers(least, most + 1), replace=False))[:, None] * col_block + np.arange(col_block)).reshape(-1)
+        r.append(np.repeat(np.arange(16 * g, 16 * g + 16), cols.size))
+        c.append(np.tile(cols, 16))
+    r, c, rows = np.concatenate(r), np.concatenate(c), 16 * groups + empty
+    csr = synth.csr_from_coo(rows, blocks * col_block, r, c, synth.to_bits(rng.uniform(-1, 1, size=r.size).astype(np.float32), dtype), dtype)
+    rg = np.append(16 * np.arange(groups + 1), [rows] if empty else []).astype(np.int32)
+    perm = rng.permutation(rows).astype(np.int32)
+    csr = synth.permute_rows(csr, np.argsort(perm))
+    bits = synth.dense_rhs(rng, blocks * col_block, n, dtype)
+    out, v = gpu_spmm(csr, perm, rg, col_block, bits, ldb_pad=pad, ldc_pad=pad)
+    assert [(p["function"], p["tiles"]) for p in v.launches(n)] == [("vbr_spmm_stream_kernel", groups + -(-empty // 64))]
+    c_ref, s = oracle.spmm(csr, bits)
+    check_c(out, c_ref, s, "%d groups, N = %d" % (groups, n))
+    assert np.all(out[perm[16 * groups:]] == 0.0)
+
+
 @pytest.mark.parametrize("n", [8, 24, 64, 72, 120, 128, 136, 264, 384, 392])
 @pytest.mark.parametrize("heights,col_block", [([128, 70, 100], 16), ([128, 70, 40, 18, 33, 16, 3, 9, 2], 16), ([60, 20, 7], 3)])
 def test_narrow_column_tiles(heights, col_block, n):

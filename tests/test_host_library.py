@@ -546,3 +546,18 @@ def test_six_column_tiles_with_a_narrow_last_one_are_shared_where_that_saves_a_r
     csr = full_csr(height * groups, 96)
     v = binding.vbr_build(csr, np.arange(height * groups, dtype=np.int32), np.arange(0, height * groups + 1, height, dtype=np.int32), 32)
     assert [p["workgroups"] for p in v.launches(n)] == [8 * domain]
+
+
+@pytest.mark.parametrize("groups,col_block,blocks,least,most", [(64, 16, 6, 1, 6), (65, 16, 40, 1, 40), (127, 32, 30, 1, 2), (128, 64, 30, 30, 30), (129, 48, 33, 1, 33),
+                                                                (513, 16, 300, 2, 4), (64, 16, 2000, 1, 1), (70, 16, 900, 700, 900), (200, 80, 1, 1, 1)])
+def test_schedules_of_one_slab_groups_hold(groups, col_block, blocks, least, most):
+    # what the audit goes through step by step; lists of one block, of every block, of far apart ones; the last two groups in the row tile behind the others
+    rng = np.random.default_rng(groups + blocks)
+    rows = []
+    for g in range(groups):
+        cols = np.sort(rng.choice(blocks, size=rng.integers(least, most + 1), replace=False))[:, None] * col_block + np.arange(col_block)
+        rows += [cols.reshape(-1).tolist()] * 16
+    csr = csr_from_rows(rows, blocks * col_block, rng)
+    v = binding.vbr_build(csr, rng.permutation(16 * groups).astype(np.int32), (16 * np.arange(groups + 1)).astype(np.int32), col_block)
+    v.audit()
+    assert v.launches(512)[0]["tiles"] >= 1
