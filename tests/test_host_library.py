@@ -346,6 +346,21 @@ def test_launch_plan_lists_what_a_call_issues():
     v.audit()
 
 
+@pytest.mark.parametrize("n_cols", [504, 512, 520, 1016, 1032])
+@pytest.mark.parametrize("used", [31, 32, 33, 64])
+@pytest.mark.parametrize("last", [True, False])
+def test_columns_of_gathered_tiles_found_by_sorting_and_by_marks(n_cols, used, last):
+    # a slab of single-row groups, sixteen times whose K-steps are fewer columns than the matrix has, as many, or more; lists that end with a K-step and that do not
+    rng = np.random.default_rng(n_cols + used)
+    cols = np.arange(n_cols - used, n_cols) if last else np.sort(rng.choice(n_cols, size=used, replace=False))
+    rows = [cols[i::16].tolist() for i in range(15)] + [cols[[0, -1]].tolist()]
+    csr = csr_from_rows([sorted(set(r) | set(cols[15::16].tolist())) if i == 3 else r for i, r in enumerate(rows)], n_cols)
+    perm, rg = np.arange(16, dtype=np.int32), np.arange(17, dtype=np.int32)
+    assert_same_index(csr, perm, rg, 8)
+    v = binding.vbr_build(csr, perm, rg, 8)
+    assert [p["kernel"] for p in v.launches(256)] == ["vbr_spmm_kernel<1 slab, column-gathered>"]
+    v.audit()
+
 
 @pytest.mark.parametrize("dense_rows,panels", [(128 * 10, False), (128 * 24, True)])
 def test_a_few_panels_are_not_worth_a_launch_of_their_own(dense_rows, panels):
