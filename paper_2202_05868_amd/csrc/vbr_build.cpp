@@ -1034,8 +1034,8 @@ void Builder::stream()
         std::push_heap(waves.begin(), waves.end(), heavier);
     }
     const int per = kStepK >> v->lg_gran;
-    // K-steps of a wave in a step: as many as the units of a step have on average
-    const int64_t units = n_tiles * kStreamWaves * v->n_cols / (kSlabRows * kStreamWaves * kStreamUnits);
+    // K-steps of a wave in a step: as many as the units of a step have on average (one row tile may have a single unit)
+    const int64_t units = std::max<int64_t>(n_tiles * kStreamWaves * v->n_cols / (kSlabRows * kStreamWaves * kStreamUnits), 1);
     v->stream_ops = (int32_t)std::min<int64_t>(std::max<int64_t>((v->work_steps + units - 1) / units, kStreamLeastOps), kStreamMostOps);
     std::vector<std::vector<StreamRecord>> records((size_t)n_tiles);
     std::vector<int64_t> n_steps((size_t)n_tiles, 0);

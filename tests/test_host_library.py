@@ -576,3 +576,12 @@ def test_schedules_of_one_slab_groups_hold(groups, col_block, blocks, least, mos
     v = binding.vbr_build(csr, rng.permutation(16 * groups).astype(np.int32), (16 * np.arange(groups + 1)).astype(np.int32), col_block)
     v.audit()
     assert v.launches(512)[0]["tiles"] >= 1
+
+
+@pytest.mark.parametrize("groups", [63, 64, 65, 128])
+@pytest.mark.parametrize("col_block,blocks", [(16, 1), (16, 2), (32, 1), (48, 1)])
+def test_one_slab_groups_of_very_few_columns(groups, col_block, blocks):
+    # fewer B rows than a step of the schedules brings
+    csr = full_csr(16 * groups, col_block * blocks)
+    v = assert_same_index(csr, np.arange(16 * groups, dtype=np.int32), (16 * np.arange(groups + 1)).astype(np.int32), col_block)
+    assert v.launches(512)[0]["tiles"] == groups
