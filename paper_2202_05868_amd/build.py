@@ -18,6 +18,17 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvbr_spmm.so")
 SOURCES = ["sa1_reorder.cpp", "vbr_build.cpp", "vbr_spmm.hip", "stream_spmm.hip", "csr_spmm.hip", "denominators.hip"]
 
+FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
+         # packed fp32 instructions are kept out of the generated device code
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # Instructions are fetched 32 bytes at a time, which shows where few waves are on a CU: the loop over the K-steps of one-slab tiles with deep
+         # rings, column-gathered, begun at byte 20 of such a piece (107 tiles, 100 K-steps, N = 488) 41.5 us, at 0 and at 8 38.0; of block tiles
+         # (60 tiles, 40 K-steps, N = 952) at 4 17.5, at 16 17.7, at 0 17.9.  Other kernels take the same.
+         "-Xarch_device", "-falign-loops=32",
+         "-Xarch_host", "-mpopcnt", "-pthread",
+         "-Wall", "-Wno-unused-command-line-argument",
+         "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
 
 def hipcc() -> str:
     for cand in (os.environ.get("HIPCC"), shutil.which("hipcc"), "/opt/rocm/bin/hipcc"):
@@ -28,16 +39,7 @@ def hipcc() -> str:
 
 def build(verbose: bool = False) -> str:
     """Compile every source for gfx950 and link the shared library.  Always recompiles."""
-    cmd = [hipcc(), "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
-           # packed fp32 instructions are kept out of the generated device code
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           # Instructions are fetched 32 bytes at a time, which shows where few waves are on a CU: the loop over the K-steps of one-slab tiles with deep
-           # rings, column-gathered, begun at byte 20 of such a piece (107 tiles, 100 K-steps, N = 488) 41.5 us, at 0 and at 8 38.0; of block tiles
-           # (60 tiles, 40 K-steps, N = 952) at 4 17.5, at 16 17.7, at 0 17.9.  Other kernels take the same.
-           "-Xarch_device", "-falign-loops=32",
-           "-Xarch_host", "-mpopcnt", "-pthread",
-           "-Wall", "-Wno-unused-command-line-argument",
-           "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+    cmd = [hipcc(), "-shared"] + FLAGS
     for s in SOURCES:
         p = os.path.join(CSRC, s)
         cmd += (["-x", "hip", p] if s.endswith(".hip") else ["-x", "c++", p])

@@ -228,12 +228,12 @@ __global__ void __launch_bounds__(kStreamThreads, 2) vbr_spmm_stream_kernel(cons
         __builtin_amdgcn_sched_barrier(0);
         cur = nxt;
         nxt = then;
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        // The compiler does not know the matrix instructions, and may read or move the accumulators as soon as the loop ends: eight wait states, inside it
+        if constexpr (set.value == kStreamAhead - 1) asm volatile("s_nop 7\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        else asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     };
     while (t < n_steps) static_for<kStreamAhead>(step);        // (their number is a multiple)
 
-    // the last products are there
-    asm volatile("s_nop 15\n\ts_nop 15" : STREAM_ACC(0), STREAM_ACC(1), STREAM_ACC(2), STREAM_ACC(3), STREAM_ACC(4), STREAM_ACC(5), STREAM_ACC(6), STREAM_ACC(7));
     // lane (q, s16) holds, of row s16 of a group, columns 32 (q % 2) + 4 (q / 2) + 8 r + f: turned round in LDS, whole lines
     constexpr int kOutRow = kStreamN * 4 + 16;
     const lds_u8_ptr out = sm + wave * kSlabRows * kOutRow;

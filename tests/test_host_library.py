@@ -14,7 +14,7 @@ import numpy as np
 import pytest
 
 import oracle
-from paper_2202_05868_amd import binding, synth
+from paper_2202_05868_amd import binding, build, synth
 from helpers import check_partition_shape, csr_from_rows, random_csr, sa1_sets
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -585,3 +585,25 @@ def test_one_slab_groups_of_very_few_columns(groups, col_block, blocks):
     csr = full_csr(16 * groups, col_block * blocks)
     v = assert_same_index(csr, np.arange(16 * groups, dtype=np.int32), (16 * np.arange(groups + 1)).astype(np.int32), col_block)
     assert v.launches(512)[0]["tiles"] == groups
+
+
+def test_stream_kernel_waits_for_its_last_products(tmp_path):
+    """Its matrix instructions are inline assembly, whose latency the compiler does not see: behind them every other access to an
+    accumulator has to find eight wait states, what the compiler itself puts behind such an instruction before its result is read."""
+    out = str(tmp_path / "stream.s")
+    subprocess.check_call([build.hipcc()] + build.FLAGS + ["--offload-device-only", "-S", "-x", "hip", os.path.join(build.CSRC, "stream_spmm.hip"), "-o", out],
+                          stderr=subprocess.DEVNULL)
+    products, waited, kernels = 0, True, set()
+    for line in open(out):
+        head, code = re.match(r"(_Z\w*stream_kernel\w*):", line), line.split(";")[0].strip()
+        if head:
+            kernels.add(head.group(1))
+            waited = True
+        elif code.startswith("v_mfma_"):
+            products += 1
+            waited = False
+        elif code.startswith("s_nop") and int(code.split()[1]) >= 7:
+            waited = True
+        else:
+            assert waited or not re.search(r"\ba(\d|\[\d)", code), "%s in %s" % (code, sorted(kernels)[-1])
+    assert len(kernels) == 10 and products == 2 * 8 * 4 * 2 * sum(range(4, 9))       # types, groups, column pieces, steps of a turn, K-steps of a step
