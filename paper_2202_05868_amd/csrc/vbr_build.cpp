@@ -1484,7 +1484,7 @@ static bool wide_pays(const vbr *v, int64_t T, int64_t N)
     return N > 1024 && longest >= 4 && 10 * longest <= (T < 44 ? 14 : 20) * median && 10 * (10 + cost(kWideN, 100, 77)) <= 9 * cost(kTileN, 62, 50);
 }
 
-// Is the stream kernel faster than `workgroups` of the kernel of one-slab tiles, 256 columns each?  It has one workgroup on a CU, 32 on an L2 domain, which
+// Is the stream kernel faster than `workgroups` of the kernel of one-slab tiles with a K-step, 256 columns each?  It has one workgroup on a CU, 32 on an L2 domain, which
 // all take their steps, whether the round is full or not: that and what goes before and behind, 10 us a round, is its time, 0.5 us a step and 0.117 for
 // each K-step of a wave in it.  The other takes 0.7 ns for a K-step of a workgroup, and somewhat longer where rows of B begin inside cache lines, as this one does.
 // Tile and stream kernel, 16 x 16 blocks, other operands in every call: 4096 x 16384 at 10 %, N = 4096 163 and 109 us, 3072 126 and 104, 2560 123 and
@@ -1493,6 +1493,8 @@ static bool wide_pays(const vbr *v, int64_t T, int64_t N)
 // 16384 x 8192, N = 1024 82 and 59; 4096 x 8192, N = 4096, 3 % 42.0 and 41.4, 10 %: 86 and 58, 30 %: 215 and 123, 50 %: 343 and 189; two rounds: N = 4160
 // 103 and 103, 6144: 135 and 110, 8192: 175 and 121; 5120 rows, N = 4096: 110 and 106; 4096 x 4096, 10 % 49 and 39, 6 %: 37 and 32.  32-column blocks,
 // 11200 x 1280 at 62 %, N = 1024 56 and 47, 4104: 222 and 196; short lists, 32768 x 512 at half, N = 512 38.3 and 38.4, 520: 58 and 66.
+// Tiles without a K-step cost either kernel the same (64 groups, 10 % of 16384 columns, and 10000 rows without entries, N = 4096 76.7 and 140; 200 groups
+// and as many: 164 and 115).
 static bool stream_pays(const vbr *v, int64_t N, int64_t ldb, bool aligned, int64_t workgroups)
 {
     const int64_t tiles = (int64_t)v->stream_tiles.size();
@@ -1716,7 +1718,7 @@ int plan_launches(const vbr *v, int64_t N, bool aligned, Launch out[VBR_MAX_LAUN
         auto rounds = [&](bool even) { return std::max<int64_t>((grid_size(T, Qt, even) / kXcd - at_once / 16 + at_once - 1) / at_once, 1); };
         const bool narrow_sixth = Qt == 6 && N - 5 * kTileN <= kTileN / 2 && v->class_count[3] == 0 && rounds(false) == rounds(true);
         Launch L{kind, 0, T, 0, split, few, 0, 0, !split && !narrow_sixth && even_columns(T, Qt)};
-        if (kind == VBR_LAUNCH_TILE_1 && !split && stream_pays(v, N, ldb ? ldb : N, aligned, grid_size(T, Qt, L.even))) {
+        if (kind == VBR_LAUNCH_TILE_1 && !split && stream_pays(v, N, ldb ? ldb : N, aligned, grid_size(v->n_work, Qt, L.even))) {
             L.stream = true;
             L.even = false;
             L.grid = grid_size((int64_t)v->stream_tiles.size(), (N + kStreamN - 1) / kStreamN) + (T - v->n_work) * Qt;

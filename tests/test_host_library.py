@@ -607,3 +607,15 @@ def test_stream_kernel_waits_for_its_last_products(tmp_path):
         else:
             assert waited or not re.search(r"\ba(\d|\[\d)", code), "%s in %s" % (code, sorted(kernels)[-1])
     assert len(kernels) == 10 and products == 2 * 8 * 4 * 2 * sum(range(4, 9))       # types, groups, column pieces, steps of a turn, K-steps of a step
+
+
+@pytest.mark.parametrize("groups,n,stream", [(64, 4096, False), (128, 2048, False), (256, 4096, True)])
+@pytest.mark.parametrize("empty", [0, 10000, 40000])
+def test_rows_without_entries_do_not_choose_the_stream_kernel(groups, n, stream, empty):
+    # their tiles cost either kernel next to nothing
+    csr = full_csr(16 * groups, 768)
+    csr = dict(csr, n_rows=16 * groups + empty, row_ptr=np.append(csr["row_ptr"], np.full(empty, csr["nnz"], dtype=np.int64)))
+    rg = np.append(16 * np.arange(groups + 1), [csr["n_rows"]] if empty else []).astype(np.int32)
+    v = binding.vbr_build(csr, np.arange(csr["n_rows"], dtype=np.int32), rg, 16)
+    v.audit()
+    assert v.launches(n)[0]["function"] == ("vbr_spmm_stream_kernel" if stream else "vbr_spmm_kernel")
