@@ -97,6 +97,27 @@ __device__ __forceinline__ void zero_rows(const StreamParams &p)
     }
 }
 
+// 16 bytes of a row of C, at byte `at` of the `bytes` that a workgroup has of it.  Nothing reads them soon, so they go past the caches; but a cache line of which
+// this is not all, where rows of C begin inside lines, is finished by another workgroup, and its parts are collected in the caches (with the hint for all, for
+// these only not, for none; kernel times: 127 groups and 1000 rows without entries, N = 8184 55, 42 and 42 us, 229 groups, N = 3992 44, 37 and 37; 2452 groups, C
+// of 277 MB, 240, 221 and 250; by halves of lines instead of lines 51, 41 and 238).  Rows that begin at half a line have the hint for all (N = 8176 41 and 40,
+// 1008: 80 and 79), as those that begin with one (4096 x 16384 at 10 %, N = 4096, with it and without 100 and 107).
+template <bool WHOLE>
+__device__ __forceinline__ void store(float *to, float4v x, int at, int bytes)
+{
+    float4v *const to4 = reinterpret_cast<float4v *>(to);
+    const int off = (int)(reinterpret_cast<uintptr_t>(to) & 127);
+    if constexpr (WHOLE) {
+        __builtin_nontemporal_store(x, to4);
+    } else if (off <= at && at - off + 128 <= bytes) {
+        asm volatile("" ::: "memory");                   // or the compiler makes one store of the two, without the hint
+        __builtin_nontemporal_store(x, to4);
+        asm volatile("" ::: "memory");
+    } else {
+        *to4 = x;
+    }
+}
+
 // The tile kernel gathers the B rows of every group for itself, at 16 rows a group one load of 1 KiB for every four matrix instructions, and the load path
 // bounds it.  Here a workgroup owns up to 64 groups and 64 columns of C and brings every unit of 16 B rows into LDS once for all of them: at 10 % of
 // the blocks 6.4 groups use it.  A unit is used when a group comes to it, so what is brought and multiplied when is a schedule that the host
@@ -115,7 +136,7 @@ __device__ __forceinline__ void zero_rows(const StreamParams &p)
 // That matrix: 163 us in the tile kernel, 109 here, with the same operands in every call 145 and 92.  Bound by the load path: 6700 loads a CU, 22 clocks
 // each where they come from the L2 (alone 73 us; without loads 50; without matrix instructions 78).  Deeper rings for A or B, loads of no value left out by
 // the execution mask, other ways to deal column tiles to domains, row tiles that begin at different places of K: within 4 %.
-template <int DT, int OPS>
+template <int DT, int OPS, bool WHOLE>
 __global__ void __launch_bounds__(kStreamThreads, 2) vbr_spmm_stream_kernel(const StreamParams p)
 {
     constexpr int F = kStreamN / 16;
@@ -142,7 +163,7 @@ __global__ void __launch_bounds__(kStreamThreads, 2) vbr_spmm_stream_kernel(cons
 
     // B: lane l brings columns 8 (l % 8) .. + 7 of four consecutive rows of one of the wave's two units
     const int cl = lane & 7, hf = lane >> 3 & 1, o = lane >> 4 & 1;
-    const int last_chunk = (p.N - n0 < kStreamN ? p.N - n0 : kStreamN) / 8 - 1;
+    const int columns = p.N - n0 < kStreamN ? p.N - n0 : kStreamN, last_chunk = columns / 8 - 1;
     const uint32_t ldb_bytes = (uint32_t)(p.ldb * 2);
     const __amdgpu_buffer_rsrc_t b_rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.B + n0), 0, (int)(p.b_bytes - (uint32_t)n0 * 2), 0x00020000);
@@ -250,15 +271,16 @@ __global__ void __launch_bounds__(kStreamThreads, 2) vbr_spmm_stream_kernel(cons
             const float4v x = *(lds_float4_ptr)(out + (4 * i + q) * kOutRow + s16 * 16);
             const int32_t row = __shfl(c_row, 4 * i + q);
             const int n = n0 + 4 * s16;
-            if (n < p.N) __builtin_nontemporal_store(x, reinterpret_cast<float4v *>(p.C + row * p.ldc + n));
+            if (n < p.N) store<WHOLE>(p.C + row * p.ldc + n, x, (n - n0) * 4, columns * 4);
         }
     }
 }
 
 using StreamKernel = void (*)(StreamParams);
-template <int DT>
-constexpr StreamKernel stream_kernels[kStreamMostOps - kStreamLeastOps + 1] = {vbr_spmm_stream_kernel<DT, 4>, vbr_spmm_stream_kernel<DT, 5>, vbr_spmm_stream_kernel<DT, 6>,
-                                                                               vbr_spmm_stream_kernel<DT, 7>, vbr_spmm_stream_kernel<DT, 8>};
+template <int DT, bool WHOLE>
+constexpr StreamKernel stream_kernels[kStreamMostOps - kStreamLeastOps + 1] = {
+    vbr_spmm_stream_kernel<DT, 4, WHOLE>, vbr_spmm_stream_kernel<DT, 5, WHOLE>, vbr_spmm_stream_kernel<DT, 6, WHOLE>, vbr_spmm_stream_kernel<DT, 7, WHOLE>,
+    vbr_spmm_stream_kernel<DT, 8, WHOLE>};
 
 }  // namespace
 
@@ -283,7 +305,10 @@ int launch_stream(const vbr *v, const Launch &L, const void *B_dev, int64_t ldb,
     p.empty = reinterpret_cast<const TileDesc *>(d + v->lay.tiles_off) + v->n_work;
     p.prow = reinterpret_cast<const int32_t *>(d + v->lay.prow_off);
     p.first_empty = (uint32_t)grid_size(p.n_tiles, p.n_ntiles);
-    const StreamKernel kernel = (v->dtype == VBR_F16 ? stream_kernels<VBR_F16> : stream_kernels<VBR_BF16>)[v->stream_ops - kStreamLeastOps];
+    const bool whole = ldc % 16 == 0 && (reinterpret_cast<uintptr_t>(C_dev) & 63) == 0;
+    const StreamKernel *kernels = v->dtype == VBR_F16 ? (whole ? stream_kernels<VBR_F16, true> : stream_kernels<VBR_F16, false>)
+                                                      : (whole ? stream_kernels<VBR_BF16, true> : stream_kernels<VBR_BF16, false>);
+    const StreamKernel kernel = kernels[v->stream_ops - kStreamLeastOps];
     hipLaunchKernelGGL(kernel, dim3((unsigned)L.grid), dim3(kStreamThreads), 0,
                        static_cast<hipStream_t>(hip_stream), p);
     const hipError_t e = hipGetLastError();

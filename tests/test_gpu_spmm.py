@@ -398,6 +398,33 @@ def test_many_groups_of_one_slab_against_a_wide_b(groups, col_block, blocks, lea
     assert np.all(out[perm[16 * groups:]] == 0.0)
 
 
+@pytest.mark.parametrize("n,dtype", [(1416, "f16"), (1464, "bf16"), (1472, "f16")])
+def test_rows_of_c_that_begin_inside_cache_lines(n, dtype):
+    # the stream kernel stores whole lines and parts of lines differently: rows that begin anywhere in a line, at its half, with it; the last column tile of 8, 56 and 64 columns
+    import torch
+    groups, blocks, k = 512, 128, 64
+    rng = np.random.default_rng(n)
+    cols = [(np.sort(rng.choice(blocks, size=k, replace=False))[:, None] * 16 + np.arange(16)).reshape(-1) for _ in range(groups)]
+    r, c = np.repeat(np.arange(16 * groups), 16 * k), np.concatenate([np.tile(x, 16) for x in cols])
+    csr = synth.csr_from_coo(16 * groups, 16 * blocks, r, c, synth.to_bits(rng.uniform(-1, 1, size=r.size).astype(np.float32), dtype), dtype)
+    bits = synth.dense_rhs(rng, 16 * blocks, n, dtype)
+    c_ref, s = oracle.spmm(csr, bits)
+    v = binding.vbr_build(csr, np.arange(16 * groups, dtype=np.int32), (16 * np.arange(groups + 1)).astype(np.int32), 16)
+    v.audit()
+    assert [p["function"] for p in v.launches(n)] == ["vbr_spmm_stream_kernel"]
+    v.upload("cuda:0")
+    b = torch_io.bits_to_device(bits, dtype)
+    for ldc, shift in [(n, 0), (1472, 0), (1472, 4), (1472, 16), (1488, 0), (1488, 16), (1476, 0), (1484, 8), (1480, 28)]:
+        flat = torch.full((16 * groups * ldc + shift,), float("nan"), device="cuda:0")
+        assert flat.data_ptr() % 128 == 0
+        v.spmm(b, torch.as_strided(flat, (16 * groups, n), (ldc, 1), shift))
+        torch.cuda.synchronize()
+        out = flat.cpu().numpy()
+        rows = out[shift:].reshape(16 * groups, ldc)
+        assert np.isnan(out[:shift]).all() and np.isnan(rows[:, n:]).all(), "wrote outside the N columns"
+        check_c(rows[:, :n].astype(np.float64), c_ref, s, "N = %d, rows of %d from %d on" % (n, ldc, shift))
+
+
 @pytest.mark.parametrize("n", [8, 24, 64, 72, 120, 128, 136, 264, 384, 392])
 @pytest.mark.parametrize("heights,col_block", [([128, 70, 100], 16), ([128, 70, 40, 18, 33, 16, 3, 9, 2], 16), ([60, 20, 7], 3)])
 def test_narrow_column_tiles(heights, col_block, n):

@@ -606,7 +606,8 @@ def test_stream_kernel_waits_for_its_last_products(tmp_path):
             waited = True
         else:
             assert waited or not re.search(r"\ba(\d|\[\d)", code), "%s in %s" % (code, sorted(kernels)[-1])
-    assert len(kernels) == 10 and products == 2 * 8 * 4 * 2 * sum(range(4, 9))       # types, groups, column pieces, steps of a turn, K-steps of a step
+    # types, stores, groups, column pieces, steps of a turn, K-steps of a step
+    assert len(kernels) == 20 and products == 2 * 2 * 8 * 4 * 2 * sum(range(4, 9))
 
 
 @pytest.mark.parametrize("groups,n,stream", [(64, 4096, False), (128, 2048, False), (256, 4096, True)])
