@@ -1495,6 +1495,8 @@ static bool wide_pays(const vbr *v, int64_t T, int64_t N)
 // 11200 x 1280 at 62 %, N = 1024 56 and 47, 4104: 222 and 196; short lists, 32768 x 512 at half, N = 512 38.3 and 38.4, 520: 58 and 66.
 // Tiles without a K-step cost either kernel the same (64 groups, 10 % of 16384 columns, and 10000 rows without entries, N = 4096 76.7 and 140; 200 groups
 // and as many: 164 and 115).
+// With 24 row tiles and more the estimate is the least sure (2011 groups at 10 % of 2784 columns, N = 512 33.8 and 37.8; 2354, 15 % of 3904, 2752: 344 and 382; of
+// 39 drawn ones between 92 and 95 % nine were slower, on average 3 % faster; of 2725 others six, up to 6 %).
 static bool stream_pays(const vbr *v, int64_t N, int64_t ldb, bool aligned, int64_t workgroups)
 {
     const int64_t tiles = (int64_t)v->stream_tiles.size();
@@ -1502,7 +1504,7 @@ static bool stream_pays(const vbr *v, int64_t N, int64_t ldb, bool aligned, int6
     const int64_t rounds = (grid_size(tiles, (N + kStreamN - 1) / kStreamN) / kXcd + 31) / 32;
     const int64_t stream_ns = 4000 + rounds * (10000 + v->stream_longest * (500 + 117 * v->stream_ops));
     const int64_t tile_ns = 12000 + v->work_steps * workgroups / std::max<int32_t>(v->n_work, 1) * 7 / 10;
-    return 100 * (aligned ? stream_ns : stream_ns * 9 / 8) < 95 * (aligned ? tile_ns : tile_ns * 7 / 6);
+    return 100 * (aligned ? stream_ns : stream_ns * 9 / 8) < (tiles >= 24 ? 92 : 95) * (aligned ? tile_ns : tile_ns * 7 / 6);
 }
 
 EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned)

@@ -620,3 +620,16 @@ def test_rows_without_entries_do_not_choose_the_stream_kernel(groups, n, stream,
     v = binding.vbr_build(csr, np.arange(csr["n_rows"], dtype=np.int32), rg, 16)
     v.audit()
     assert v.launches(n)[0]["function"] == ("vbr_spmm_stream_kernel" if stream else "vbr_spmm_kernel")
+
+
+@pytest.mark.parametrize("groups,blocks,used,n,stream", [(1536, 81, 14, 512, False), (1536, 81, 16, 512, False), (1472, 81, 16, 512, True), (1536, 81, 20, 512, True)])
+def test_many_row_tiles_have_to_be_clearly_faster_in_the_stream_kernel(groups, blocks, used, n, stream):
+    # 24 row tiles of 64 groups and more, and one less
+    rng = np.random.default_rng(groups)
+    cols = [(np.sort(rng.choice(blocks, size=used, replace=False))[:, None] * 32 + np.arange(32)).reshape(-1) for _ in range(groups)]
+    nnz = 16 * 32 * used * groups
+    csr = dict(n_rows=16 * groups, n_cols=32 * blocks, nnz=nnz, row_ptr=np.arange(16 * groups + 1, dtype=np.int64) * (32 * used),
+               col_idx=np.concatenate([np.tile(c, 16) for c in cols]).astype(np.int32), vals=np.full(nnz, 0x3c00, dtype=np.uint16), dtype="f16")
+    v = binding.vbr_build(csr, np.arange(16 * groups, dtype=np.int32), (16 * np.arange(groups + 1)).astype(np.int32), 32)
+    v.audit()
+    assert v.launches(n)[0]["function"] == ("vbr_spmm_stream_kernel" if stream else "vbr_spmm_kernel")
