@@ -10,9 +10,9 @@
 
 namespace vbrk {
 
-// The groups of one workgroup: wave w's are group_of[w * kStreamGroups ...], -1 none; unit(l, k, h) is the unit of 16 B rows that half h of the l-th's
-// K-step k takes and frag_of its first fragment in KiB of the values.  Writes the steps' records behind those in `out` and returns the number of
-// steps, 0 if there is no schedule.
+// The groups of one workgroup: wave w's are group_of[w * kStreamGroups ...], -1 none; `units` the units of 16 B rows they take (unit i: B rows 16 i ..), rising;
+// unit(l, k, h) the place in `units` of the one that half h of the l-th's K-step k takes, and frag_of its first fragment in KiB of the values.  Writes the
+// steps' records behind those in `out` and returns the number of steps, 0 if there is no schedule.
 //
 // A step is what happens between two barriers: every wave asks for up to kStreamUnits units of B, multiplies up to `ops` K-steps, and turns the units it asked
 // for kStreamAhead steps before into LDS.  The operands of a step's first K-step are read at the end of the step before.  So a unit asked for
@@ -20,11 +20,11 @@ namespace vbrk {
 // when step t + 1 writes.  Units come in the order of their rows, into any slot that is free, and stay until their last use.  A group waits with the
 // first half of at most one K-step for the second, so kStreamWaves * kStreamGroups slots can be taken and one more is enough to go on.
 template <class Unit>
-int64_t stream_schedule(int ops, const int32_t *group_of, const int32_t *n_ks_of, const int64_t *frag_of, Unit unit, int64_t n_units, int share, int sharers, std::vector<StreamRecord> &out)
+int64_t stream_schedule(int ops, const int32_t *group_of, const int32_t *n_ks_of, const int64_t *frag_of, const std::vector<int32_t> &units, Unit unit, int share, int sharers, std::vector<StreamRecord> &out)
 {
     constexpr int kAll = kStreamWaves * kStreamGroups, kZeros = kStreamSlots * kStreamUnitBytes;
     const size_t begin = out.size();
-    std::vector<int32_t> uses((size_t)n_units, 0), slot((size_t)n_units, -1), from((size_t)n_units, INT32_MAX), order, free_slots;
+    std::vector<int32_t> uses(units.size(), 0), slot(units.size(), -1), from(units.size(), INT32_MAX), free_slots;
     int32_t next[kAll], left[kAll], u[kAll][2];
     int64_t todo = 0;
     for (int l = 0; l < kAll; ++l) {
@@ -35,10 +35,8 @@ int64_t stream_schedule(int ops, const int32_t *group_of, const int32_t *n_ks_of
             for (int h = 0; h < 2; ++h) ++uses[(size_t)unit(l, k, h)];
         for (int h = 0; h < 2 && left[l] > 0; ++h) u[l][h] = unit(l, 0, h);
     }
-    for (int64_t i = 0; i < n_units; ++i)
-        if (uses[(size_t)i] > 0) order.push_back((int32_t)i);
     for (int32_t s = kStreamSlots; s-- > 0;) free_slots.push_back(s);
-    out.reserve(begin + 2 * kStreamWaves * std::max<size_t>(order.size() / (kStreamWaves * kStreamUnits), (size_t)todo / (kStreamWaves * ops)) * 9 / 8 + 16 * kStreamWaves);
+    out.reserve(begin + 2 * kStreamWaves * std::max<size_t>(units.size() / (kStreamWaves * kStreamUnits), (size_t)todo / (kStreamWaves * ops)) * 9 / 8 + 16 * kStreamWaves);
     size_t staged = 0;
     int idle = 0;
     StreamRecord empty = {};
@@ -79,20 +77,20 @@ int64_t stream_schedule(int ops, const int32_t *group_of, const int32_t *n_ks_of
                     if (next[best] < left[best]) u[best][h] = unit(best, next[best], h);
                 }
             }
-        for (int i = 0; i < kStreamWaves * kStreamUnits && staged < order.size() && !free_slots.empty(); ++i) {
-            const int32_t fresh = order[staged++];
-            slot[(size_t)fresh] = free_slots.back();
+        for (int i = 0; i < kStreamWaves * kStreamUnits && staged < units.size() && !free_slots.empty(); ++i) {
+            const size_t fresh = staged++;
+            slot[fresh] = free_slots.back();
             free_slots.pop_back();
-            from[(size_t)fresh] = (int32_t)t + kStreamAhead + 1;
-            now[i].row() = fresh * kSlabRows;
+            from[fresh] = (int32_t)t + kStreamAhead + 1;
+            now[i].row() = units[fresh] * kSlabRows;
             now[i].none() = 0;
-            now[i].to() = slot[(size_t)fresh] * kStreamUnitBytes;
+            now[i].to() = slot[fresh] * kStreamUnitBytes;
             moved = true;
         }
         // this workgroup's share of the units up to kStreamEarly further on, by another wave in every step
-        for (int i = 0; sharers > 1 && i < 4 * kStreamWaves && ahead < std::min(order.size(), staged + kStreamEarly); ++ahead) {
-            if (order[ahead] % sharers != share || ahead < staged) continue;
-            now[2 * ((t + i / 4) % kStreamWaves) + (i / 2 & 1)].early(i & 1) = order[ahead] * kSlabRows;
+        for (int i = 0; sharers > 1 && i < 4 * kStreamWaves && ahead < std::min(units.size(), staged + kStreamEarly); ++ahead) {
+            if (units[ahead] % sharers != share || ahead < staged) continue;
+            now[2 * ((t + i / 4) % kStreamWaves) + (i / 2 & 1)].early(i & 1) = units[ahead] * kSlabRows;
             ++i;
         }
         idle = moved ? 0 : idle + 1;

@@ -13,6 +13,9 @@
 #include "vbr_host.h"
 
 namespace vbrk {
+
+static int64_t stream_most_steps(const vbr *v, int64_t tiles, int ops);
+
 namespace {
 
 inline int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
@@ -111,8 +114,8 @@ struct Scratch {
 
 class Builder {
 public:
-    Builder(const vbr_csr_t *csr, const int32_t *perm, const int32_t *row_groups, int32_t G, int32_t col_block, vbr *v)
-        : csr(csr), perm(perm), rg(row_groups), G(G), cb(col_block), M(csr->n_rows), KB(csr->n_cols / col_block), v(v),
+    Builder(const vbr_csr_t *csr, const int32_t *perm, const int32_t *row_groups, int32_t G, int32_t col_block, vbr *v, bool schedules)
+        : csr(csr), perm(perm), rg(row_groups), G(G), cb(col_block), M(csr->n_rows), KB(csr->n_cols / col_block), v(v), schedules(schedules),
           team(threads_for(csr->nnz + csr->n_rows, 1 << 15)), scratch((size_t)team.size())
     {
     }
@@ -173,6 +176,7 @@ private:
     const int32_t G, cb;
     const int64_t M, KB;
     vbr *v;
+    const bool schedules;
     Team team;
     std::vector<Scratch> scratch;
     std::vector<Kind> kind;
@@ -1010,14 +1014,23 @@ void Builder::schedule()
     }
 }
 
-// The schedules of the stream kernel, where all tiles with a K-step are block tiles of one slab.  The groups are dealt to the waves of as few workgroups as
-// hold them, the longest first, each to the wave with the fewest K-steps.
+// The schedules of the stream kernel, where all tiles with a K-step are block tiles of one slab and some call takes the kernel (or `schedules` wants them).  The
+// groups are dealt to the waves of as few workgroups as hold them, the longest first, each to the wave with the fewest K-steps.  A schedule takes some 70 ns
+// a K-step and 0.1 to 0.25 KiB beside the one of its values, so it is made only where what is known before leaves the kernel a chance (65536 rows,
+// 8 blocks of 16 a group of 1048576 columns, build on 8 threads 5.7 ms and 17.3 MB, with schedules that no call takes 6.3 and 22.3; 262144 x 16384 27.4 and 69.2, 28.4 and 85.1).
 void Builder::stream()
 {
     constexpr int kAll = kStreamWaves * kStreamGroups;
     const int64_t T = v->n_work, n_tiles = (T + kAll - 1) / kAll;
     if (T < kStreamMinTiles || v->class_count[0] != T || v->lg_gran < 4 || !v->panels.empty()) return;
-    if ((int64_t)v->vals.size() * 2 > kNearBytes || v->n_cols > INT32_MAX / 2) return;
+    if ((int64_t)v->vals.size() * 2 > kNearBytes || v->n_cols > kStreamMostCols) return;
+    // K-steps of a wave in a step: as many as the units of a step have on average (one row tile may have a single unit)
+    const int64_t all_units = std::max<int64_t>(n_tiles * kStreamWaves * v->n_cols / (kSlabRows * kStreamWaves * kStreamUnits), 1);
+    const int ops = (int)std::min<int64_t>(std::max<int64_t>((v->work_steps + all_units - 1) / all_units, kStreamLeastOps), kStreamMostOps);
+    // the last of a row tile's units and the last K-step of a wave come at the earliest
+    auto least = [&](int64_t units, int64_t load) { return std::max((units + kStreamWaves * kStreamUnits - 1) / (kStreamWaves * kStreamUnits), (load + ops - 1) / ops) + kStreamAhead + 1; };
+    const int64_t most = schedules ? INT64_MAX : stream_most_steps(v, n_tiles, ops);
+    if (least(0, (v->work_steps + n_tiles * kStreamWaves - 1) / (n_tiles * kStreamWaves)) > most) return;
     struct Wave { int64_t load; int32_t tiles; int32_t wave; };
     auto heavier = [](const Wave &a, const Wave &b) { return a.load != b.load ? a.load > b.load : a.wave > b.wave; };
     std::vector<Wave> waves;
@@ -1034,31 +1047,57 @@ void Builder::stream()
         std::push_heap(waves.begin(), waves.end(), heavier);
     }
     const int per = kStepK >> v->lg_gran;
-    // K-steps of a wave in a step: as many as the units of a step have on average (one row tile may have a single unit)
-    const int64_t units = std::max<int64_t>(n_tiles * kStreamWaves * v->n_cols / (kSlabRows * kStreamWaves * kStreamUnits), 1);
-    v->stream_ops = (int32_t)std::min<int64_t>(std::max<int64_t>((v->work_steps + units - 1) / units, kStreamLeastOps), kStreamMostOps);
     std::vector<std::vector<StreamRecord>> records((size_t)n_tiles);
+    std::vector<std::vector<int32_t>> units((size_t)n_tiles);
     std::vector<int64_t> n_steps((size_t)n_tiles, 0);
-    each(n_tiles, 1, [&](Scratch &, int64_t t) {
+    std::atomic<bool> pays(true);
+    auto unit_of = [&](int32_t g, int32_t k, int h) {
+        return v->krow[(size_t)(v->dev_tiles[(size_t)g].ks_begin + k) * per + (per == 2 ? h : 0)] / kSlabRows + (per == 2 ? 0 : h);
+    };
+    each(n_tiles, 1, [&](Scratch &s, int64_t t) {
+        if (!pays.load(std::memory_order_relaxed)) return;
+        std::vector<int32_t> &list = units[(size_t)t];
+        int64_t load = 0;
+        s.begin();
+        for (int l = 0; l < kAll; ++l) {
+            if (l % kStreamGroups == 0) load = 0;
+            const int32_t g = tile_of[(size_t)(t * kAll + l)], n_ks = g < 0 ? 0 : v->dev_tiles[(size_t)g].n_ks;
+            for (int32_t k = 0; k < n_ks; ++k)
+                for (int h = 0; h < 2; ++h) {
+                    const int32_t u = unit_of(g, k, h);
+                    if (s.stamp[(size_t)u] != s.now) { s.stamp[(size_t)u] = s.now; list.push_back(u); }
+                }
+            load += n_ks;
+            if (least((int64_t)list.size(), load) > most) {
+                pays.store(false, std::memory_order_relaxed);
+                return;
+            }
+        }
+        std::sort(list.begin(), list.end());
+    });
+    if (!pays.load()) return;
+    each(n_tiles, 1, [&](Scratch &s, int64_t t) {
+        if (!pays.load(std::memory_order_relaxed)) return;
         const int32_t *group_of = tile_of.data() + t * kAll;
-        int32_t n_ks[kAll], first[kAll];
+        const std::vector<int32_t> &list = units[(size_t)t];
+        for (size_t i = 0; i < list.size(); ++i) s.pos[(size_t)list[i]] = (int32_t)i;
+        int32_t n_ks[kAll];
         int64_t frag[kAll];
         for (int l = 0; l < kAll; ++l) {
             if (group_of[l] < 0) continue;
             const TileDesc &td = v->dev_tiles[(size_t)group_of[l]];
             n_ks[l] = td.n_ks;
-            first[l] = td.ks_begin;
             frag[l] = td.a_off * 16 >> 10;
         }
-        auto unit = [&](int l, int32_t k, int h) { return v->krow[(size_t)(first[l] + k) * per + (per == 2 ? h : 0)] / kSlabRows + (per == 2 ? 0 : h); };
+        auto unit = [&](int l, int32_t k, int h) { return s.pos[(size_t)unit_of(group_of[l], k, h)]; };
         const int sharers = (int)std::min<int64_t>(n_tiles, kStreamShare);
-        n_steps[(size_t)t] = stream_schedule(v->stream_ops, group_of, n_ks, frag, unit, v->n_cols / kSlabRows, (int)(t % sharers), sharers, records[(size_t)t]);
+        n_steps[(size_t)t] = stream_schedule(ops, group_of, n_ks, frag, list, unit, (int)(t % sharers), sharers, records[(size_t)t]);
+        if (n_steps[(size_t)t] == 0 || n_steps[(size_t)t] > most) pays.store(false, std::memory_order_relaxed);
     });
+    if (!pays.load()) return;
+    v->stream_ops = ops;
     int64_t total = 0;
-    for (const int64_t n : n_steps) {
-        if (n == 0) return;
-        total += n;
-    }
+    for (const int64_t n : n_steps) total += n;
     v->stream_steps.reserve((size_t)((total + 2) * 2 * kStreamWaves));
     for (int64_t t = 0; t < n_tiles; ++t) {
         StreamTile st;
@@ -1095,31 +1134,36 @@ void Builder::lay_out()
 }  // namespace
 }  // namespace vbrk
 
+int vbrk::build_impl(const vbr_csr_t *csr, const int32_t *perm, const int32_t *row_groups, int32_t n_groups, int32_t col_block, vbr_t **out, bool schedules)
+{
+    int rc = validate_csr(csr, true);
+    if (rc != VBR_OK) return rc;
+    if (csr->n_cols % col_block != 0) return VBR_EINVAL;
+    const int64_t M = csr->n_rows;
+    if ((M > 0 && (!perm || !row_groups)) || !row_groups) return VBR_EINVAL;
+    if (n_groups > M || (M > 0 && n_groups == 0)) return VBR_EINVAL;
+    if (row_groups[0] != 0 || row_groups[n_groups] != M) return VBR_EINVAL;
+    for (int32_t g = 0; g < n_groups; ++g)
+        if (row_groups[g + 1] <= row_groups[g]) return VBR_EINVAL;
+    std::vector<uint8_t> seen((size_t)M, 0);
+    for (int64_t i = 0; i < M; ++i) {
+        if (perm[i] < 0 || perm[i] >= M || seen[perm[i]]) return VBR_EINVAL;   // not a bijection
+        seen[perm[i]] = 1;
+    }
+    std::unique_ptr<vbr> v(new vbr());
+    rc = Builder(csr, perm, row_groups, n_groups, col_block, v.get(), schedules).build();
+    if (rc != VBR_OK) return rc;
+    *out = v.release();
+    return VBR_OK;
+}
+
 extern "C" int vbr_build(const vbr_csr_t *csr, const int32_t *perm, const int32_t *row_groups,
                          int32_t n_groups, int32_t col_block, vbr_t **out)
 {
     if (!csr || !out || n_groups < 0 || col_block <= 0) return VBR_EINVAL;
     *out = nullptr;
     try {
-        int rc = vbrk::validate_csr(csr, true);
-        if (rc != VBR_OK) return rc;
-        if (csr->n_cols % col_block != 0) return VBR_EINVAL;
-        const int64_t M = csr->n_rows;
-        if ((M > 0 && (!perm || !row_groups)) || !row_groups) return VBR_EINVAL;
-        if (n_groups > M || (M > 0 && n_groups == 0)) return VBR_EINVAL;
-        if (row_groups[0] != 0 || row_groups[n_groups] != M) return VBR_EINVAL;
-        for (int32_t g = 0; g < n_groups; ++g)
-            if (row_groups[g + 1] <= row_groups[g]) return VBR_EINVAL;
-        std::vector<uint8_t> seen((size_t)M, 0);
-        for (int64_t i = 0; i < M; ++i) {
-            if (perm[i] < 0 || perm[i] >= M || seen[perm[i]]) return VBR_EINVAL;   // not a bijection
-            seen[perm[i]] = 1;
-        }
-        std::unique_ptr<vbr> v(new vbr());
-        rc = vbrk::Builder(csr, perm, row_groups, n_groups, col_block, v.get()).build();
-        if (rc != VBR_OK) return rc;
-        *out = v.release();
-        return VBR_OK;
+        return vbrk::build_impl(csr, perm, row_groups, n_groups, col_block, out, false);
     } catch (const std::bad_alloc &) {
         return VBR_ENOMEM;
     } catch (...) {
@@ -1484,6 +1528,12 @@ static bool wide_pays(const vbr *v, int64_t T, int64_t N)
     return N > 1024 && longest >= 4 && 10 * longest <= (T < 44 ? 14 : 20) * median && 10 * (10 + cost(kWideN, 100, 77)) <= 9 * cost(kTileN, 62, 50);
 }
 
+// Parts of stream_pays.
+static int64_t stream_rounds(int64_t tiles, int64_t N) { return (grid_size(tiles, (N + kStreamN - 1) / kStreamN) / kXcd + 31) / 32; }
+static int64_t stream_step_ns(int ops) { return 500 + 117 * ops; }
+static int64_t stream_margin(int64_t tiles) { return tiles >= 24 ? 92 : 95; }
+static int64_t tile_kernel_ns(const vbr *v, int64_t workgroups) { return 12000 + v->work_steps * workgroups / std::max<int32_t>(v->n_work, 1) * 7 / 10; }
+
 // Is the stream kernel faster than `workgroups` of the kernel of one-slab tiles with a K-step, 256 columns each?  It has one workgroup on a CU, 32 on an L2 domain, which
 // all take their steps, whether the round is full or not: that and what goes before and behind, 10 us a round, is its time, 0.5 us a step and 0.117 for
 // each K-step of a wave in it.  The other takes 0.7 ns for a K-step of a workgroup, and somewhat longer where rows of B begin inside cache lines, as this one does.
@@ -1500,11 +1550,26 @@ static bool wide_pays(const vbr *v, int64_t T, int64_t N)
 static bool stream_pays(const vbr *v, int64_t N, int64_t ldb, bool aligned, int64_t workgroups)
 {
     const int64_t tiles = (int64_t)v->stream_tiles.size();
-    if (tiles == 0 || N < 512 || b_bytes_of(v->n_cols, ldb, N) > kNearBytes || ldb * 2 >= 1 << 24 || v->n_cols > 1 << 24) return false;
-    const int64_t rounds = (grid_size(tiles, (N + kStreamN - 1) / kStreamN) / kXcd + 31) / 32;
-    const int64_t stream_ns = 4000 + rounds * (10000 + v->stream_longest * (500 + 117 * v->stream_ops));
-    const int64_t tile_ns = 12000 + v->work_steps * workgroups / std::max<int32_t>(v->n_work, 1) * 7 / 10;
-    return 100 * (aligned ? stream_ns : stream_ns * 9 / 8) < (tiles >= 24 ? 92 : 95) * (aligned ? tile_ns : tile_ns * 7 / 6);
+    if (tiles == 0 || N < kStreamLeastN || b_bytes_of(v->n_cols, ldb, N) > kNearBytes || ldb * 2 >= 1 << 24) return false;
+    const int64_t stream_ns = 4000 + stream_rounds(tiles, N) * (10000 + v->stream_longest * stream_step_ns(v->stream_ops)), tile_ns = tile_kernel_ns(v, workgroups);
+    return 100 * (aligned ? stream_ns : stream_ns * 9 / 8) < stream_margin(tiles) * (aligned ? tile_ns : tile_ns * 7 / 6);
+}
+
+// The most steps that the longest of `tiles` row tiles may take for stream_pays to hold for any N and ldb: of the columns that make as many workgroups of the tile kernel
+// the fewest, rows of B not aligned.  Beyond 64 column tiles by the rounds that the workgroups fill; fewer steps with every further one.
+static int64_t stream_most_steps(const vbr *v, int64_t tiles, int ops)
+{
+    int64_t most = 0;
+    for (int64_t Qt = 2; Qt <= 64; ++Qt) {
+        const int64_t N = std::max<int64_t>(kStreamLeastN, (Qt - 1) * kTileN + 8);
+        if (b_bytes_of(v->n_cols, N, N) > kNearBytes) break;
+        const bool last = Qt == 64;
+        const double rounds = last ? (double)tiles * (double)(4 * Qt - 3) / (32 * kXcd) : (double)stream_rounds(tiles, N);
+        const double tile_ns = (double)tile_kernel_ns(v, last ? v->n_work * (Qt + kXcd - 1) : grid_size(v->n_work, Qt)) * 7 / 6;
+        const double stream_ns = tile_ns * (double)stream_margin(tiles) / 100 * 8 / 9 + 2;
+        most = std::max(most, (int64_t)(((stream_ns - 4000) / rounds - 10000) / (double)stream_step_ns(ops)));
+    }
+    return most;
 }
 
 EntryLaunch plan_entry_rows(const std::vector<int64_t> &start, int64_t n_cols, int64_t N, bool aligned)

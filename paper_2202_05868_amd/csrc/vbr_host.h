@@ -12,6 +12,9 @@ int validate_csr(const vbr_csr_t *csr, bool need_vals);
 int sa1_reorder_impl(const vbr_csr_t *csr, int32_t col_block, double tau, int32_t *perm,
                      int32_t *row_groups, int32_t *n_groups);
 
+// vbr_build without its first checks; schedules: with the stream kernel's where no call takes it, too.
+int build_impl(const vbr_csr_t *csr, const int32_t *perm, const int32_t *row_groups, int32_t n_groups, int32_t col_block, vbr_t **out, bool schedules);
+
 // The launches one vbr_spmm call issues for dense width N, in issue order (at most VBR_MAX_LAUNCHES):
 // kernel, first tile and number of tiles (or panels) of the launch, grid size; split: 64 columns of C a workgroup,
 // whose waves split the K-steps; few: rings of four slots; wide: the wide kernel.  aligned: rows of B begin on a cache line.

@@ -198,7 +198,9 @@ constexpr int kStreamSlots = 79;       // places for units in LDS, and one more 
 constexpr int kStreamUnitBytes = kSlabRows * kStreamN * 2;
 constexpr int kStreamShare = 4;        // row tiles that share the first requests of B
 constexpr int kStreamEarly = 48;       // units before its own that a workgroup asks for its share of them
-constexpr int kStreamMinTiles = 64;    // tiles from which on a matrix gets a schedule
+constexpr int kStreamMinTiles = 64;    // tiles from which on a matrix may get a schedule
+constexpr int kStreamLeastN = 512;     // columns of B from which on a call may take it
+constexpr int kStreamMostCols = 1 << 24;      // B rows: what the kernel multiplies row numbers with has 24 bits
 // Of every step a wave has two of these records, one for each half of its lanes: of the two units of a K-step, and of those it brings.
 struct StreamRecord {
     // the lanes of a row of 16 hold two words each, which the others of the row get by a broadcast
@@ -342,7 +344,7 @@ struct vbr {
     std::vector<int64_t> pk_frag;        // host only: ordinal of the step's first fragment inside its panel
     std::vector<int64_t> p_union_ptr;    // host only: [n_panels+1] into p_union
     std::vector<int32_t> p_union;        // host only: ascending union of the column blocks of each panel
-    // Block tiles of one slab, if all tiles are, for the stream kernel, too.
+    // Block tiles of one slab, if all tiles are and some call takes the stream kernel, for that, too.
     std::vector<vbrk::StreamTile> stream_tiles;
     std::vector<vbrk::StreamRecord> stream_steps;
     int32_t stream_ops = 0;              // K-steps of a wave in a step of theirs

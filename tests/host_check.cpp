@@ -268,6 +268,92 @@ void check_wide()
     }
 }
 
+// Groups of 16 rows, each with `least` to `most` of the column blocks, all columns of which some row of the group has, and `empty` rows without entries.
+struct OneSlabGroups {
+    Csr a;
+    std::vector<int32_t> perm, rg;
+    OneSlabGroups(Rng &rng, int groups, int col_block, int blocks, int least, int most, int empty)
+    {
+        a.m = 16 * groups + empty;
+        a.k = (int64_t)blocks * col_block;
+        a.row_ptr.push_back(0);
+        rg.push_back(0);
+        for (int g = 0; g < groups; ++g) {
+            std::vector<uint8_t> on((size_t)blocks, 0);
+            for (int64_t n = least + rng.below(most - least + 1); n > 0;) {
+                uint8_t &b = on[(size_t)rng.below(blocks)];
+                n -= !b;
+                b = 1;
+            }
+            for (int r = 0; r < 16; ++r) {
+                for (int b = 0; b < blocks; ++b)
+                    for (int c = r % 4; on[(size_t)b] && c < col_block; c += 4) a.col.push_back(b * col_block + c);
+                a.row_ptr.push_back((int64_t)a.col.size());
+            }
+            rg.push_back(16 * (g + 1));
+        }
+        for (int i = 0; i < empty; ++i) a.row_ptr.push_back((int64_t)a.col.size());
+        if (empty) rg.push_back((int32_t)a.m);
+        a.val.assign(a.col.size(), 0x3c00);
+        for (int64_t i = 0; i < a.m; ++i) perm.push_back((int32_t)i);
+    }
+    vbr_t *build(int col_block, bool schedules) const
+    {
+        const vbr_csr_t c = a.view();
+        vbr_t *v = nullptr;
+        REQUIRE(vbrk::build_impl(&c, perm.data(), rg.data(), (int32_t)rg.size() - 1, col_block, &v, schedules) == VBR_OK && vbr_audit(v) == VBR_OK);
+        return v;
+    }
+};
+
+// The schedules of the stream kernel hold, whether a call takes them or not; vbr_build makes them exactly where some call may, and the plans are the same with
+// and without those that none takes.
+void check_stream()
+{
+    struct { int groups, col_block, blocks, least, most, empty; } const fixed[] = {
+        {64, 16, 1, 1, 1, 0}, {64, 32, 1, 1, 1, 0}, {65, 16, 40, 1, 40, 0}, {127, 32, 30, 1, 2, 0}, {129, 48, 33, 1, 33, 5}, {200, 80, 1, 1, 1, 70}, {64, 16, 2000, 1, 1, 0},
+        {70, 16, 300, 250, 300, 0}, {256, 16, 120, 90, 120, 0}, {256, 16, 120, 10, 120, 200}, {300, 64, 16, 16, 16, 0}, {1000, 16, 64, 20, 24, 0}, {1600, 16, 40, 20, 30, 0}, {520, 32, 16, 1, 16, 0}};
+    Rng rng(77);
+    int chosen = 0, refused = 0;
+    for (int i = 0; i < 70; ++i) {
+        ++g_cases;
+        const int n_fixed = (int)(sizeof(fixed) / sizeof(fixed[0]));
+        const int cbs[] = {16, 32, 48, 64, 80};
+        int groups = 64 + (int)rng.below(150), cb = cbs[rng.below(5)], blocks = 1 + (int)rng.below(rng.below(2) ? 30 : 200), most = 1 + (int)rng.below(blocks), least = 1 + (int)rng.below(most);
+        int empty = (int)rng.below(3) * 33;
+        if (i < n_fixed) { groups = fixed[i].groups; cb = fixed[i].col_block; blocks = fixed[i].blocks; least = fixed[i].least; most = fixed[i].most; empty = fixed[i].empty; }
+        const OneSlabGroups m(rng, groups, cb, blocks, least, most, empty);
+        vbr_t *all = m.build(cb, true), *v = m.build(cb, false);
+        REQUIRE(all->n_work == groups && (int)all->stream_tiles.size() == (groups + 63) / 64);
+        REQUIRE(v->stream_tiles.empty() ? v->stream_steps.empty() && v->lay.vals_off == v->lay.stream_tiles_off : v->stream_steps.size() == all->stream_steps.size());
+        bool taken = false;
+        for (int64_t N = 64; N <= 40000; N += N < 9000 ? 8 : 1000)
+            for (int64_t pad : {0, 8, 64}) {
+                vbrk::Launch p[VBR_MAX_LAUNCHES], q[VBR_MAX_LAUNCHES];
+                const bool aligned = (N + pad) % 64 == 0;
+                const int n = vbrk::plan_launches(all, N, aligned, p, N + pad);
+                REQUIRE(n == vbrk::plan_launches(v, N, aligned, q, N + pad));
+                for (int l = 0; l < n; ++l) {
+                    taken |= p[l].stream;
+                    REQUIRE(p[l].stream == q[l].stream && p[l].kind == q[l].kind && p[l].grid == q[l].grid && p[l].split == q[l].split && p[l].even == q[l].even);
+                }
+            }
+        (taken ? chosen : refused) += 1;
+        vbr_free(all);
+        vbr_free(v);
+    }
+    if (chosen < 10 || refused < 10) std::fprintf(stderr, "schedules of %d matrices taken, of %d not\n", chosen, refused);
+    REQUIRE(chosen >= 10 && refused >= 10);
+    // far from it: few K-steps against many rows of B, many groups
+    struct { int groups, blocks, used; } const far[] = {{1024, 16384, 8}, {2048, 1024, 8}, {1024, 4096, 4}, {64, 1 << 18, 6}};
+    for (const auto &x : far) {
+        ++g_cases;
+        vbr_t *v = OneSlabGroups(rng, x.groups, 16, x.blocks, x.used, x.used, 0).build(16, false);
+        REQUIRE(v->n_work == x.groups && v->stream_tiles.empty() && v->stream_steps.empty() && v->lay.vals_off == v->lay.stream_tiles_off);
+        vbr_free(v);
+    }
+}
+
 // Deep tiles beyond 1536 workgroups: deep rings only where one list is far longer than the others, and up to six column tiles longer than all shared out.
 void check_deep_rings()
 {
@@ -584,6 +670,7 @@ int main()
     check_plan();
     check_deep_rings();
     check_wide();
+    check_stream();
     check_short_lists();
     check_map<false>();
     check_map<true>();
