@@ -102,7 +102,7 @@ int vbr_unpack_block(const vbr_t *v, int64_t blk, void *dst);
 /*
  * Check of a built matrix against itself: every index the kernels use (B rows of the gather lists,
  * value offsets of tiles and panels, row positions, the schedule's class ranges, the sections of the
- * device buffer) lies inside what it indexes.  VBR_OK, or VBR_EINVAL at the first violation.  vbr_build
+ * device buffer) lies inside what it indexes.  VBR_OK, VBR_EINVAL at the first violation, or VBR_ENOMEM.  vbr_build
  * produces matrices that pass; the tests call this on every matrix they build.
  */
 int vbr_audit(const vbr_t *v);

@@ -1433,7 +1433,11 @@ extern "C" int vbr_audit(const vbr_t *v)
     }
     for (size_t i = v->by_entries ? 0 : (size_t)n_vals - kFragElems; i < (size_t)n_vals; ++i)
         if (values[i] != 0) return VBR_EINVAL;                                               // the zero fragment
-    if (!stream_holds(v)) return VBR_EINVAL;
+    try {
+        if (!stream_holds(v)) return VBR_EINVAL;
+    } catch (const std::bad_alloc &) {
+        return VBR_ENOMEM;
+    }
     const DeviceLayout &L = v->lay;
     const int64_t ends[11] = {L.zeros_off + 256, L.tiles_off + (int64_t)v->dev_tiles.size() * (int64_t)sizeof(TileDesc),
                               L.krow_off + (int64_t)v->krow.size() * 4, L.perm_off + M * 4,

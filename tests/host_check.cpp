@@ -687,6 +687,10 @@ int main()
         for (int64_t i = 0; i < a.m * a.k; ++i) a.col.push_back((int32_t)(i % a.k));
         a.val.assign(a.col.size(), 0x3c00);
         check_out_of_memory(a, 64, 4);
+        // the audit of a matrix with schedules
+        vbr_t *v = OneSlabGroups(rng, 70, 16, 40, 1, 40, 3).build(16, true);
+        check_out_of_memory([&] { return vbr_audit(v); }, 100000);
+        vbr_free(v);
     }
     std::printf("host_check ok: %d cases\n", g_cases);
     return 0;
