@@ -1269,12 +1269,11 @@ extern "C" int vbr_unpack_block(const vbr_t *v, int64_t blk, void *dst_)
     return VBR_OK;
 }
 
-// Everything the kernels index with, checked against the sizes of what they index into: a wrong
-// entry here would be a device access out of bounds, so the check is plain and complete.
 namespace vbrk {
 
 // Goes through the steps of the stream kernel as it does: every index inside what it indexes; every K-step of every tile once and in order, with the units
-// of B in its slots that it takes, written in the step before its operands are read or earlier; no slot written while a K-step still reads it.
+// of B in its slots that it takes, written in the step before its operands are read or earlier.  A slot counts as its next unit's from the step on that asks for
+// it, so one written while a K-step still reads it shows as a K-step that finds another unit, or one not yet written.
 static bool stream_holds(const vbr *v)
 {
     constexpr int kStep = 2 * kStreamWaves, kAll = kStreamWaves * kStreamGroups, kZeros = kStreamSlots * kStreamUnitBytes;
@@ -1299,7 +1298,7 @@ static bool stream_holds(const vbr *v)
             if (tile[l] < 0) return false;
             ++tiles;
         }
-        struct Slot { int32_t row = -1, written = -1, read = -1; } slots[kStreamSlots];
+        struct Slot { int32_t row = -1, written = -1; } slots[kStreamSlots];
         for (int32_t t = 0; t < st.n_steps; ++t) {
             const StreamRecord *now = v->stream_steps.data() + (int64_t)(st.first_step + t) * kStep, *before = t > 0 ? now - kStep : nullptr;
             for (int e = 0; e < kStreamWaves * v->stream_ops; ++e) {
@@ -1322,9 +1321,8 @@ static bool stream_holds(const vbr *v)
                     const int64_t b = (int64_t)(td.ks_begin + k) * kStepK + kSlabRows * h;
                     const int32_t row = v->krow[(size_t)(b >> v->lg_gran)] + (int32_t)(b & ((1 << v->lg_gran) - 1));
                     if (at[h] == kZeros) return false;
-                    Slot &s = slots[at[h] / kStreamUnitBytes];
+                    const Slot &s = slots[at[h] / kStreamUnitBytes];
                     if (s.row != row || s.written > t - (i == 0 ? 2 : 1)) return false;
-                    s.read = t;
                 }
             }
             for (int i = 0; i < kStep; ++i) {
@@ -1339,8 +1337,8 @@ static bool stream_holds(const vbr *v)
                 if (r.none() != 0 || r.row() < 0 || r.row() % kSlabRows != 0 || (int64_t)r.row() + kSlabRows > v->n_cols) return false;
                 if (r.to() < 0 || r.to() >= kZeros || r.to() % kStreamUnitBytes != 0) return false;
                 Slot &s = slots[r.to() / kStreamUnitBytes];
-                if (s.written >= t + kStreamAhead || s.read >= t + kStreamAhead) return false;
-                s = Slot{r.row(), t + kStreamAhead, -1};
+                if (s.written >= t + kStreamAhead) return false;                          // two units at once
+                s = Slot{r.row(), t + kStreamAhead};
             }
         }
         for (int l = 0; l < kAll; ++l)
@@ -1351,6 +1349,8 @@ static bool stream_holds(const vbr *v)
 
 }  // namespace vbrk
 
+// Everything the kernels index with, checked against the sizes of what they index into: a wrong
+// entry here would be a device access out of bounds, so the check is plain and complete.
 extern "C" int vbr_audit(const vbr_t *v)
 {
     using namespace vbrk;

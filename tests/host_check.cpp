@@ -354,6 +354,54 @@ void check_stream()
     }
 }
 
+// The audit finds a schedule that is wrong in one place: another slot for a unit or an operand, another unit, fragment or group, steps that are not there.
+void check_stream_audit()
+{
+    using namespace vbrk;
+    Rng rng(78);
+    vbr_t *v = OneSlabGroups(rng, 100, 16, 200, 60, 90, 0).build(16, true);
+    REQUIRE(v->stream_tiles.size() == 2);
+    auto wrong = [&](int32_t &x, int32_t y) {
+        ++g_cases;
+        REQUIRE(x != y);
+        std::swap(x, y);
+        REQUIRE(vbr_audit(v) == VBR_EINVAL);
+        std::swap(x, y);
+    };
+    for (int trial = 0; trial < 200; ++trial) {
+        const StreamTile &st = v->stream_tiles[(size_t)rng.below(2)];
+        const int64_t t = st.first_step + 1 + rng.below(st.n_steps - 1);
+        StreamRecord *now = v->stream_steps.data() + t * 2 * kStreamWaves, &r = now[rng.below(2 * kStreamWaves)], &before = *(&r - 2 * kStreamWaves);
+        const int i = (int)rng.below(v->stream_ops), other = kStreamUnitBytes * (1 + (int)rng.below(kStreamSlots - 1)), all = kStreamSlots * kStreamUnitBytes;
+        if (r.none() == 0) {
+            wrong(r.to(), (r.to() + other) % all);
+            wrong(r.to(), all);
+            wrong(r.row(), r.row() < kSlabRows ? r.row() + kSlabRows : r.row() - kSlabRows);
+            wrong(r.row(), (int32_t)v->n_cols);
+            wrong(r.none(), kStreamNone);
+        }
+        if (r.group(i) != kStreamGroups) {
+            int32_t &at = i > 0 ? r.slot(i - 1) : before.slot(v->stream_ops - 1);
+            wrong(at, (at + other) % all);
+            wrong(at, all);
+            wrong(before.frag(i), before.frag(i) + 1024);
+            wrong(r.groups(), r.groups() ^ 1 << 4 * i);
+            wrong(r.groups(), (r.groups() & ~(15 << 4 * i)) | kStreamGroups << 4 * i);
+        }
+        wrong(r.early(trial & 1), (int32_t)v->n_cols - kSlabRows + 1);
+    }
+    for (StreamTile &st : v->stream_tiles) {
+        wrong(st.n_steps, st.n_steps + 1);
+        wrong(st.n_steps, st.n_steps / 4 * kStreamAhead);
+        wrong(st.n_steps, (int32_t)(v->stream_steps.size() / (2 * kStreamWaves)) / kStreamAhead * kStreamAhead);
+        wrong(st.first_step, -1);
+        wrong(st.first_step, st.first_step + 1);
+        wrong(st.row_begin[0], -1);
+    }
+    REQUIRE(vbr_audit(v) == VBR_OK);
+    vbr_free(v);
+}
+
 // Deep tiles beyond 1536 workgroups: deep rings only where one list is far longer than the others, and up to six column tiles longer than all shared out.
 void check_deep_rings()
 {
@@ -671,6 +719,7 @@ int main()
     check_deep_rings();
     check_wide();
     check_stream();
+    check_stream_audit();
     check_short_lists();
     check_map<false>();
     check_map<true>();
