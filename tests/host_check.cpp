@@ -311,7 +311,7 @@ struct OneSlabGroups {
 void check_stream()
 {
     struct { int groups, col_block, blocks, least, most, empty; } const fixed[] = {
-        {64, 16, 1, 1, 1, 0}, {64, 32, 1, 1, 1, 0}, {65, 16, 40, 1, 40, 0}, {127, 32, 30, 1, 2, 0}, {129, 48, 33, 1, 33, 5}, {200, 80, 1, 1, 1, 70}, {64, 16, 2000, 1, 1, 0},
+        {64, 16, 1, 1, 1, 0}, {64, 32, 1, 1, 1, 0}, {65, 16, 40, 1, 40, 0}, {127, 32, 30, 1, 2, 0}, {129, 48, 33, 1, 33, 5}, {200, 80, 1, 1, 1, 70}, {64, 16, 2000, 1, 1, 0}, {64, 16, 6, 1, 6, 0}, {513, 16, 300, 2, 4, 0},
         {70, 16, 300, 250, 300, 0}, {256, 16, 120, 90, 120, 0}, {256, 16, 120, 10, 120, 200}, {300, 64, 16, 16, 16, 0}, {1000, 16, 64, 20, 24, 0}, {1600, 16, 40, 20, 30, 0}, {520, 32, 16, 1, 16, 0}};
     Rng rng(77);
     int chosen = 0, refused = 0;

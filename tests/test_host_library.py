@@ -563,10 +563,12 @@ def test_six_column_tiles_with_a_narrow_last_one_are_shared_where_that_saves_a_r
     assert [p["workgroups"] for p in v.launches(n)] == [8 * domain]
 
 
-@pytest.mark.parametrize("groups,col_block,blocks,least,most", [(64, 16, 6, 1, 6), (65, 16, 40, 1, 40), (127, 32, 30, 1, 2), (128, 64, 30, 30, 30), (129, 48, 33, 1, 33),
-                                                                (513, 16, 300, 2, 4), (64, 16, 2000, 1, 1), (70, 16, 900, 700, 900), (200, 80, 1, 1, 1)])
-def test_schedules_of_one_slab_groups_hold(groups, col_block, blocks, least, most):
-    # what the audit goes through step by step; lists of one block, of every block, of far apart ones; the last two groups in the row tile behind the others
+@pytest.mark.parametrize("groups,col_block,blocks,least,most,n", [(64, 16, 6, 1, 6, 0), (65, 16, 40, 1, 40, 0), (127, 32, 30, 1, 2, 0), (128, 64, 30, 30, 30, 8000), (129, 48, 33, 1, 33, 8000),
+                                                                  (513, 16, 300, 2, 4, 0), (64, 16, 2000, 1, 1, 0), (70, 16, 900, 700, 900, 8000), (200, 80, 1, 1, 1, 0),
+                                                                  (129, 64, 40, 30, 40, 4096), (300, 80, 20, 8, 20, 2552), (520, 48, 24, 10, 20, 1536), (1000, 16, 64, 20, 40, 840)])
+def test_schedules_of_one_slab_groups_hold(groups, col_block, blocks, least, most, n):
+    # what the audit goes through step by step; lists of one block, of every block, of far apart ones; the last two groups in the row tile behind the others.  n: columns of B
+    # that take the schedule, 0: none up to 4096 do (the host check makes it all the same)
     rng = np.random.default_rng(groups + blocks)
     rows = []
     for g in range(groups):
@@ -575,7 +577,10 @@ def test_schedules_of_one_slab_groups_hold(groups, col_block, blocks, least, mos
     csr = csr_from_rows(rows, blocks * col_block, rng)
     v = binding.vbr_build(csr, rng.permutation(16 * groups).astype(np.int32), (16 * np.arange(groups + 1)).astype(np.int32), col_block)
     v.audit()
-    assert v.launches(512)[0]["tiles"] >= 1
+    if n:
+        assert v.launches(n)[0]["function"] == "vbr_spmm_stream_kernel"
+    else:
+        assert all(v.launches(k)[0]["function"] != "vbr_spmm_stream_kernel" for k in range(512, 4097, 8))
 
 
 @pytest.mark.parametrize("groups", [63, 64, 65, 128])
