@@ -478,15 +478,13 @@ bool Builder::hubs_first()
     for (const int32_t q : given) sorted[(size_t)at[key(q)]++] = q;
     std::atomic<int64_t> shared[2] = {{0}, {0}};
     const int64_t n_tiles = (n + step - 1) / step;
-    // one at a time, those of the longest rows first: 64 rows of a graph's hubs have as many entries as a thousand others (16384 nodes, the whole build, with
-    // this and the column lists below: 2.9 and 2.35 ms)
-    each(2 * n_tiles, 1, [&](Scratch &s, int64_t i) {
-        const std::vector<int32_t> &list = i < n_tiles ? sorted : given;
+    each(2 * n_tiles, 4, [&](Scratch &s, int64_t i) {
+        const std::vector<int32_t> &list = i < n_tiles ? given : sorted;
         const int64_t b = (i % n_tiles) * step;
         int64_t cols = 0;
         s.begin();
         for (int64_t k = b; k < std::min(n, b + step); ++k) cols += s.add(csr, perm[list[(size_t)k]]);
-        shared[i < n_tiles] += cols;
+        shared[i / n_tiles] += cols;
     });
     if (5 * shared[1] > 4 * shared[0]) return false;
     v->prow.resize((size_t)n);
