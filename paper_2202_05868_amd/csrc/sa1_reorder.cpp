@@ -131,8 +131,9 @@ bool has_vpopcnt()
 }
 
 // Threads of a call on a matrix of n_rows rows and nnz entries; the environment variable VBR_SA1_THREADS
-// overrides the count.  One for every 2^16 of them, on 16 CPUs half as many and these (ms): graph of 16384 nodes 7.2 and 6.1, of 8192 nodes 1.8 and 1.4;
-// no structure, 8448 rows 3.9 and 2.4, 21856 rows 10.5 and 9.0; blocks, which mostly take less than a millisecond, the same.
+// overrides the count.  One for every 2^16 of them, on 16 CPUs half as many and these (ms): a reordering of a graph of 16384 nodes 7.7 and 6.5, of 4096 nodes 0.93 and
+// 0.65, no structure, 8704 rows 4.1 and 2.8, 12224 rows 3.5 and 2.6; a curve of ten thresholds of the 4096 nodes 7.1 and 5.7, of the 8704 rows 22.0 and 13.3, of
+// the 12224 13.5 and 10.2, of 8192 rows of 64 x 64 blocks 1.53 and 1.39; other blocks, which mostly take less than a millisecond, the same.
 int sa1_threads(int64_t n_rows, int64_t nnz)
 {
     if (const char *e = std::getenv("VBR_SA1_THREADS")) {

@@ -100,8 +100,8 @@ __device__ __forceinline__ void zero_rows(const StreamParams &p)
 // 16 bytes of a row of C, at byte `at` of the `bytes` that a workgroup has of it.  Nothing reads them soon, so they go past the caches; but a cache line of which
 // this is not all, where rows of C begin inside lines, is finished by another workgroup, and its parts are collected in the caches (with the hint for all, for
 // these only not, for none; kernel times: 127 groups and 1000 rows without entries, N = 8184 55, 42 and 42 us, 229 groups, N = 3992 44, 37 and 37; 2452 groups, C
-// of 277 MB, 240, 221 and 250; by halves of lines instead of lines 51, 41 and 238).  Rows that begin at half a line have the hint for all (N = 8176 41 and 40,
-// 1008: 80 and 79), as those that begin with one (4096 x 16384 at 10 %, N = 4096, with it and without 100 and 107).
+// of 277 MB, 240, 221 and 250; by halves of lines instead of lines 51, 41 and 238).  Rows that begin at half a line have the hint for all (127
+// groups, N = 8176 40.6 and 38.3, but 4096 x 16384 at 10 %, N = 3504 103 and 105, 3056 99 and 101), as those that begin with one (4096: 100 and 107).
 template <bool WHOLE>
 __device__ __forceinline__ void store(float *to, float4v x, int at, int bytes)
 {
@@ -124,18 +124,21 @@ __device__ __forceinline__ void store(float *to, float4v x, int at, int bytes)
 // makes once (stream_schedule.h); a step of it, between two barriers:
 //   - a wave multiplies up to OPS K-steps of its eight groups, any group in any place: the 128 accumulators stay in place and a jump picks the four instructions;
 //   - the operands of a K-step are its two units out of LDS, wherever these lie: half of the lanes read the one and half the other, 16 bytes a lane of
-//     columns that were turned round on their way in, 4 clocks per KiB and no transposed read;
+//     columns that were turned round on their way in, and no transposed read;
 //   - its fragment of A, which no other wave needs, comes straight into registers, asked for a step before;
 //   - the units: a lane loads eight columns of four rows, turns them by byte permutes and writes 8 bytes of each column, two steps later.  A row of 16
 //     lanes writes 128 bytes in one piece (8 clocks a write where it did not, else 4), and operand f of the LDS image holds columns f and 4 + f of eight;
 //   - where units and fragments are goes into addresses by the DPP of an addition, from a record of the step that each row of 16 lanes holds.
-// No load of A or B stands in a branch, so that every wait is for one of them and not for all.
+// No load that the products wait for stands in a branch, so that every wait is for one of them and not for all.  (Those that only bring lines into the L2 do.)
 // A CU has some 80 lines on the way whatever it asks for, and returns them in order, so a line that comes from HBM holds up what follows it.  The row tiles
 // on a domain ask for the same units at about the same time; each brings a quarter of them into the L2 three steps ahead, four bytes of a line a
 // lane (other operands in every call: 16 x 16 blocks at 10 %, 4096 x 16384, N = 4096 116 and 108 us, 2048: 108 and 92).
-// That matrix: 163 us in the tile kernel, 109 here, with the same operands in every call 145 and 92.  Bound by the load path: 6700 loads a CU, 22 clocks
-// each where they come from the L2 (alone 73 us; without loads 50; without matrix instructions 78).  Deeper rings for A or B, loads of no value left out by
-// the execution mask, other ways to deal column tiles to domains, row tiles that begin at different places of K: within 4 %.
+// That matrix: 163 us in the tile kernel, 109 here, with the same operands in every call 145 and 93.  Its loads alone take 73, all but the loads 50, all but the
+// matrix instructions 78.  By its profile (same operands) a CU makes 6900 loads, 29 clocks each, for 20 of which the texture-address unit is busy, 68 % of
+// the time; the matrix unit is 26 % busy, waves wait 38 % of their time.  LDS counts 16.4 million cycles of bank conflicts, 32 % of the CUs' cycles, about four for each
+// of the 4.0 million reads of operands, which the contiguous reads of a probe do without.  No unit is full: steps are short, and a CU has one workgroup.
+// Deeper rings for A or B, loads of no value left out by the execution mask, other ways to deal column tiles to domains, row tiles that begin at different
+// places of K: within 4 %.
 template <int DT, int OPS, bool WHOLE>
 __global__ void __launch_bounds__(kStreamThreads, 2) vbr_spmm_stream_kernel(const StreamParams p)
 {

@@ -809,6 +809,7 @@ void Builder::cut_into_tiles()
     auto in_panel = [&](int64_t sl) { return part[(size_t)sl] == 0 && v->chunk_panel[(size_t)(sl / kPanelSlabs)] >= 0; };
     // columns of the tile of len slabs from slab i on, -1 = not possible
     std::vector<int32_t> cols((size_t)n_slabs * kMaxGatherSlabs, -1);
+    // (two at a time, not sixteen: the slabs of a graph's hubs have most of the entries; 4096 nodes, a build 1.02 and 0.88 ms, 16384 the same)
     each(n_slabs, 2, [&](Scratch &s, int64_t i) {
         if (in_panel(i)) return;
         int64_t n = 0;
@@ -904,7 +905,8 @@ int Builder::emit_gather_tiles()
     each((int64_t)v->gtiles.size(), 1, [&](Scratch &s, int64_t i) {
         const TileDesc &td = v->gtiles[(size_t)i];
         int32_t *out = v->gcol.data() + (int64_t)td.ks_begin * kStepK, *at = out;
-        // of many columns the marks are gone through, of few the columns are sorted: a mark takes about 1 ns, a column 13 to 18
+        // of many columns the marks are gone through, of few the columns are sorted: a mark takes about 1 ns, a column 13 to 18 (a build of a graph of 16384 nodes,
+        // with all sorted and four tiles at a time, 3.0 and 2.4 ms, of 4096 nodes 1.25 and 0.88)
         const bool marks = 16 * (int64_t)td.n_ks * kStepK > csr->n_cols;
         int64_t n = 0;
         s.begin();
@@ -1013,9 +1015,9 @@ void Builder::schedule()
 }
 
 // The schedules of the stream kernel, where all tiles with a K-step are block tiles of one slab and some call takes the kernel (or `schedules` wants them).  The
-// groups are dealt to the waves of as few workgroups as hold them, the longest first, each to the wave with the fewest K-steps.  A schedule takes some 70 ns
-// a K-step and 0.1 to 0.25 KiB beside the one of its values, so it is made only where what is known before leaves the kernel a chance (65536 rows,
-// 8 blocks of 16 a group of 1048576 columns, build on 8 threads 5.7 ms and 17.3 MB, with schedules that no call takes 6.3 and 22.3; 262144 x 16384 27.4 and 69.2, 28.4 and 85.1).
+// groups are dealt to the waves of as few workgroups as hold them, the longest first, each to the wave with the fewest K-steps.  A schedule takes a thread
+// some 0.1 us and the device 40 to 300 bytes a K-step, beside 1 KiB of values, so it is made only where what is known before leaves the kernel a chance (65536 rows,
+// 8 blocks of 16 a group of 1048576 columns, build on 8 threads 5.3 ms and 17.3 MB, with schedules that no call takes 7.0 and 22.3; 262144 x 16384 25.7 and 69.2, 29.1 and 85.1).
 void Builder::stream()
 {
     constexpr int kAll = kStreamWaves * kStreamGroups;
@@ -1545,6 +1547,8 @@ static int64_t tile_kernel_ns(const vbr *v, int64_t workgroups) { return 12000 +
 // 16384 x 8192, N = 1024 82 and 59; 4096 x 8192, N = 4096, 3 % 42.0 and 41.4, 10 %: 86 and 58, 30 %: 215 and 123, 50 %: 343 and 189; two rounds: N = 4160
 // 103 and 103, 6144: 135 and 110, 8192: 175 and 121; 5120 rows, N = 4096: 110 and 106; 4096 x 4096, 10 % 49 and 39, 6 %: 37 and 32.  32-column blocks,
 // 11200 x 1280 at 62 %, N = 1024 56 and 47, 4104: 222 and 196; short lists, 32768 x 512 at half, N = 512 38.3 and 38.4, 520: 58 and 66.
+// The line lies where the estimate wins by 5 %, on the tile kernel's side of some that would gain: of these 2560 at 10 %, 3072 at 6 %, 4096 x 4096 at 6 % and 5120
+// rows.  (5500 products drawn over what it takes, 64 to 3000 groups, 256 to 32768 columns, N up to 8192: 36 % less on average, 0.5 % of them more than 2 % slower.)
 // Tiles without a K-step cost either kernel the same (64 groups, 10 % of 16384 columns, and 10000 rows without entries, N = 4096 76.7 and 140; 200 groups
 // and as many: 164 and 115).
 // With 24 row tiles and more the estimate is the least sure (2011 groups at 10 % of 2784 columns, N = 512 33.8 and 37.8; 2354, 15 % of 3904, 2752: 344 and 382; of
