@@ -1278,7 +1278,8 @@ static bool stream_holds(const vbr *v)
 {
     constexpr int kStep = 2 * kStreamWaves, kAll = kStreamWaves * kStreamGroups, kZeros = kStreamSlots * kStreamUnitBytes;
     if (v->stream_tiles.empty()) return v->stream_steps.empty();
-    if (v->stream_ops < kStreamLeastOps || v->stream_ops > kStreamMostOps || v->stream_steps.size() % kStep != 0 || (int64_t)v->vals.size() * 2 > kNearBytes) return false;
+    if (v->stream_ops < kStreamLeastOps || v->stream_ops > kStreamMostOps || v->stream_steps.size() % kStep != 0) return false;
+    if ((int64_t)v->vals.size() * 2 > kNearBytes || v->n_cols > kStreamMostCols || v->lg_gran < 4) return false;
     const int64_t n_steps = (int64_t)v->stream_steps.size() / kStep - 2;      // two more are looked up behind the last
     std::vector<int32_t> tile_at((size_t)v->n_rows, -1);
     for (int32_t i = 0; i < v->n_work; ++i) {
